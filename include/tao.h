@@ -126,7 +126,10 @@ double tao_gamma(long k, const tao_fp_model *model);
  * a zero accumulator; eight chain results are added as a binary32 tree and the
  * root is folded into a binary64 accumulator (at most 7 binary32 roundings per
  * term); the result is inflated by the proven rounding error of that scheme, so
- * exact <= tau <= exact * (1 + 1e-6).  M, N or batch equal to 0 is a no-op;
+ * exact <= tau <= exact * (1 + 1e-6).  Outputs too small for that kernel's tiles
+ * to fill the chip run on the binary64 matrix cores instead (exact products,
+ * binary64 sums: the bound is then within one binary32 step of the exact value).
+ * M, N or batch equal to 0 is a no-op;
  * K == 0 gives tau = Gamma(K') |bias| (0 without bias).
  * Gradual underflow inside the bound's own evaluation: partial sums that fall
  * below 2^-126 are rounded absolutely (2^-150 per rounding), so a positive sum

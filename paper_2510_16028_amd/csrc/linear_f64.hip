@@ -1,0 +1,263 @@
+// tao_bound_linear on the binary64 matrix cores, for products whose output is too small for the
+// 128 x 128 (or 64 x 128) tiles of linear.hip to fill the chip: a decode step's projections, small layers.
+//
+// What bounds them: the weights have to be read once (M = 8 rows against a 4096 x 4096 weight: 64 MB,
+// 13 us at the rate a large copy reaches here), while the tiles of the FP32 kernel leave 32 workgroups
+// walking the whole reduction one after the other (381 us for that product, whatever M up to 128).  Here a
+// workgroup owns a small tile (16 to 64 rows x 16 to 64 columns) and its wavefronts divide the
+// reduction: each streams its own 32-k chunks of both operands from global memory straight into
+// registers, double-buffered, and the wavefronts' sums meet in LDS once at the end.  No operand goes through
+// LDS: a weight value is used by one wavefront only.
+//
+// Arithmetic: v_mfma_f64_16x16x4_f64 on the magnitudes converted to binary64.  The product of two binary32
+// values is exact there and every addition errs by less than 2^-52 of the sum of non-negative terms, so
+// the computed sum lies in [S (1 - m), S (1 + m)] with m = (K + 64) 2^-52 < 2^-27, against 7 x 2^-24 for
+// the FP32 scheme: the bound is tighter, and no partial sum can be subnormal (a product of two binary32
+// subnormals is 2^-298), so the absolute term of the FP32 scheme disappears.  The instruction runs at half
+// the rate of the FP32 one and without that scheme's folding: 78.6 against 96 TFLOP/s reached.
+#include <type_traits>
+#include "linear_f64.hpp"
+#include "tao_device.hpp"
+
+namespace tao {
+
+typedef double doublex4 __attribute__((ext_vector_type(4)));
+
+constexpr int kF64Chunk = 32;        // k per chunk: one 128-byte line of a row
+
+struct F64Args {
+    const float* A; const float* W; const float* bias; float* tau;
+    long M, N, K, lda, ldw, ldt, strideA, strideW, strideT;
+    unsigned tiles_m, tiles_n;
+    double c;                        // Gamma(K') guard, upper
+    double infl;                     // reciprocal of the lower rounding factor
+    double uflow;                    // TAO_FLAG_UNDERFLOW_TERMS
+};
+
+// Four consecutive values of a row from column k on; FULL: all of them lie inside it, else zeros beyond K.
+template <bool VEC, bool FULL>
+__device__ __forceinline__ float4 row4(const float* __restrict__ row, long k, long K) {
+    if (FULL && VEC) return *reinterpret_cast<const float4*>(row + k);
+    if (FULL) return make_float4(row[k], row[k + 1], row[k + 2], row[k + 3]);
+    return make_float4(k < K ? row[k] : 0.f, k + 1 < K ? row[k + 1] : 0.f, k + 2 < K ? row[k + 2] : 0.f, k + 3 < K ? row[k + 3] : 0.f);
+}
+
+// WAVES wavefronts; the workgroup's tile is MT x NT matrix tiles of 16 x 16.  Lane l of a wavefront holds
+// row (column) l % 16 of a matrix tile; k runs over the lane's quarter l / 16 and its four loaded values.
+// (Which k a lane holds does not matter as long as both operands agree.)
+// TRANS: W is [K][N].
+template <bool TRANS, bool VEC, int MT, int NT, int WAVES>
+__global__ __launch_bounds__(WAVES * 64) void absgemm_f64(F64Args p) {
+    // the wavefronts' sums; with eight matrix tiles the upper half of the wavefronts hands its sums to the lower first
+    constexpr int SLOTS = MT * NT > 4 ? WAVES / 2 : WAVES;
+    __shared__ double part[SLOTS][MT * NT * 256];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int r = lane & 15, q = lane >> 4;
+    // Row tiles that share a slab of W go to one XCD (workgroups are dealt round-robin to the eight XCDs, each
+    // with its own L2): workgroup b takes column tile 8 (b / 8 / tiles_m) + b % 8, row tile (b / 8) % tiles_m.
+    const unsigned b8 = blockIdx.x >> 3;
+    const unsigned tm = b8 % p.tiles_m, tn = (b8 / p.tiles_m) * 8 + (blockIdx.x & 7);
+    if (tn >= p.tiles_n) return;                                       // whole workgroup
+    const long z = blockIdx.y;
+    const long m0 = (long)tm * (MT * 16), n0 = (long)tn * (NT * 16);
+    const float* Ab = p.A + z * p.strideA;
+    const float* Wb = p.W + z * p.strideW;
+    const float* arow[MT];
+#pragma unroll
+    for (int i = 0; i < MT; ++i) {                                     // rows beyond the edge repeat the last one
+        const long m = m0 + i * 16 + r;
+        arow[i] = Ab + (m < p.M ? m : p.M - 1) * p.lda;
+    }
+    const float* wrow[NT];                                             // row of W (!TRANS)
+    unsigned wcol[NT];                                                 // byte offset of the column in the lane's first k row (TRANS)
+#pragma unroll
+    for (int j = 0; j < NT; ++j) {
+        const long n = n0 + j * 16 + r, nc = n < p.N ? n : p.N - 1;
+        wrow[j] = Wb + (TRANS ? 0 : nc * p.ldw);
+        wcol[j] = TRANS ? (unsigned)(nc + q * 4 * p.ldw) * 4u : 0u;    // (the host keeps this in 32 bits)
+    }
+
+    doublex4 acc[MT][NT];
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int j = 0; j < NT; ++j) acc[i][j] = doublex4{0.0, 0.0, 0.0, 0.0};
+
+    // One chunk: A as two vectors of four k per row, half a chunk apart; W likewise, or (TRANS) eight k of NT columns.
+    float4 a[2][MT][2];
+    float w[2][NT][8];
+    auto load = [&](auto full, int s, long k0) __attribute__((always_inline)) {
+        constexpr bool FULL = decltype(full)::value;
+#pragma unroll
+        for (int i = 0; i < MT; ++i)
+#pragma unroll
+            for (int hf = 0; hf < 2; ++hf) a[s][i][hf] = row4<VEC, FULL>(arow[i], k0 + hf * 16 + q * 4, p.K);
+        if (!TRANS) {
+#pragma unroll
+            for (int j = 0; j < NT; ++j)
+#pragma unroll
+                for (int hf = 0; hf < 2; ++hf) {
+                    const float4 v = row4<VEC, FULL>(wrow[j], k0 + hf * 16 + q * 4, p.K);
+                    w[s][j][4 * hf] = v.x; w[s][j][4 * hf + 1] = v.y; w[s][j][4 * hf + 2] = v.z; w[s][j][4 * hf + 3] = v.w;
+                }
+        } else {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const long ks = k0 + (e >> 2) * 16 + (e & 3);              // the lane's k is ks + 4 q
+                long krow = ks * p.ldw;
+                asm("" : "+s"(krow));                                      // (one scalar base per k: else the compiler keeps a 64-bit pointer per load)
+                const char* base = reinterpret_cast<const char*>(Wb + krow);
+#pragma unroll
+                for (int j = 0; j < NT; ++j) w[s][j][e] = (FULL || ks + q * 4 < p.K) ? *reinterpret_cast<const float*>(base + wcol[j]) : 0.f;
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);                                 // (the loads stay ahead of the arithmetic they overlap)
+    };
+    auto multiply = [&](int s) __attribute__((always_inline)) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            double ad[MT], wd[NT];
+#pragma unroll
+            for (int i = 0; i < MT; ++i) {
+                const float4 v = a[s][i][e >> 2];
+                ad[i] = fabs((double)((e & 3) == 0 ? v.x : (e & 3) == 1 ? v.y : (e & 3) == 2 ? v.z : v.w));
+            }
+#pragma unroll
+            for (int j = 0; j < NT; ++j) wd[j] = fabs((double)w[s][j][e]);
+#pragma unroll
+            for (int i = 0; i < MT; ++i)
+#pragma unroll
+                for (int j = 0; j < NT; ++j) acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(ad[i], wd[j], acc[i][j], 0, 0, 0);
+        }
+    };
+    // whole chunks double-buffered, then the ragged one, which belongs to one wavefront
+    const long step = (long)WAVES * kF64Chunk;
+    const long whole = p.K / kF64Chunk * kF64Chunk;
+    long k0 = (long)__builtin_amdgcn_readfirstlane(wave) * kF64Chunk;
+    if (k0 < whole) {
+        load(std::true_type(), 0, k0);
+        // (nothing conditional inside: the compiler then waits for the older chunk only)
+        for (; k0 + 2 * step < whole; k0 += 2 * step) {
+            load(std::true_type(), 1, k0 + step);
+            multiply(0);
+            load(std::true_type(), 0, k0 + 2 * step);
+            multiply(1);
+        }
+        if (k0 + step < whole) {
+            load(std::true_type(), 1, k0 + step);
+            multiply(0);
+            multiply(1);
+            k0 += step;
+        } else {
+            multiply(0);
+        }
+        k0 += step;
+    }
+    if (k0 < p.K) {
+        load(std::false_type(), 0, k0);
+        multiply(0);
+    }
+    // register v of a matrix tile: row lane / 16 + 4 v, column lane % 16
+    const long chunks = (p.K + kF64Chunk - 1) / kF64Chunk;
+    int holders = chunks < WAVES ? (int)chunks : WAVES;                // wavefronts that had a chunk
+    auto each = [&](auto&& f) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < MT; ++i)
+#pragma unroll
+            for (int j = 0; j < NT; ++j)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) f(acc[i][j], v, (i * NT + j) * 256 + v * 64 + lane);
+    };
+    if (SLOTS < WAVES && holders > SLOTS) {
+        if (wave >= SLOTS && wave < holders) each([&](doublex4& x, int v, int at) { part[wave - SLOTS][at] = x[v]; });
+        __syncthreads();
+        if (wave + SLOTS < holders) each([&](doublex4& x, int v, int at) { x[v] += part[wave][at]; });
+        holders = SLOTS;                                               // (a wavefront reads and writes its own slot only)
+    }
+    if (wave < holders) each([&](doublex4& x, int v, int at) { part[wave][at] = x[v]; });
+    __syncthreads();
+    // every output element: the wavefronts' sums in a fixed order, then the bound
+    for (int t = threadIdx.x; t < MT * NT * 256; t += WAVES * 64) {
+        double s = 0.0;
+        for (int g = 0; g < holders; ++g) s += part[g][t];
+        const int tile = t >> 8, i = tile / NT, j = tile % NT, v = (t >> 6) & 3, l = t & 63;
+        const long row = m0 + i * 16 + (l >> 4) + 4 * v;
+        const long col = n0 + j * 16 + (l & 15);
+        if (row < p.M && col < p.N) {
+            const double ab = p.bias ? fabs((double)p.bias[col]) : 0.0;
+            p.tau[z * p.strideT + row * p.ldt + col] = up32((s * p.infl + ab) * p.c + p.uflow);
+        }
+    }
+}
+
+// Tile of a problem: as many rows as M asks for, fewer while the workgroups would not fill the chip, then as
+// many columns as still leave one workgroup per compute unit.  64 x 32 outputs (one workgroup resident per
+// compute unit) run at 61 TFLOP/s, 64 x 16 at 54 (more operand bytes from L2 per product): the larger tile
+// where its last round is not the emptier one (M = 255, K = 4096: N = 4096 148 against 159 us, but N = 3072, K = 768
+// 39 against 31).  Up to 32 rows the weights' bytes decide, not the tile.
+struct F64Tile { int mt, nt; long tiles_m, tiles_n; double rounds, tflops; };
+static F64Tile f64_tile(long M, long N, long batch, int cus) {
+    F64Tile t;
+    t.mt = M > 32 ? 4 : M > 16 ? 2 : 1;
+    auto count = [&](int mt, int nt) { return ((M + 16 * mt - 1) / (16 * mt)) * ((N + 16 * nt - 1) / (16 * nt)) * batch; };
+    auto rounds = [&](int mt, int nt) { return (double)((count(mt, nt) + cus - 1) / cus); };
+    while (t.mt > 1 && count(t.mt, 1) < cus) t.mt /= 2;
+    t.nt = 1;
+    if (t.mt == 4) { if (rounds(4, 2) * 2.0 / 61.0 < rounds(4, 1) / 54.0) t.nt = 2; }
+    else           { while (t.mt * t.nt < 4 && count(t.mt, 2 * t.nt) >= cus) t.nt *= 2; }
+    t.tiles_m = (M + 16 * t.mt - 1) / (16 * t.mt);
+    t.tiles_n = (N + 16 * t.nt - 1) / (16 * t.nt);
+    t.rounds = rounds(t.mt, t.nt);
+    t.tflops = t.mt * t.nt == 8 ? 61.0 : 54.0;
+    return t;
+}
+
+// Times in us as measured: a workgroup here takes its products at 1 / cus of the rate above and about 1.2 us
+// besides; a round of the FP32 tiles takes 1.5 (64 rows) or 2.95 us per 32 k-steps and about 4 us besides.
+// Measured on both sides of the line (us, here / FP32 tiles): 8 x 4096 x 4096 (M x K x N) 17 / 381, 128 x 4096 x 4096
+// 78 / 195, 255 x 8192 x 8192 537 / 542; 255 x 4096 x 12288 423 / 416, 255 x 256 x 8192 35 / 22, 200 x 64 x 12288 29 / 15.
+bool f64_route(const LinearProblem& p, int cus) {
+    if (p.batch >= 65536 || p.K < 1) return false;
+    if (p.trans_w && p.N + 16 * p.ldw >= (1L << 30)) return false;     // (32-bit column offsets)
+    const F64Tile t = f64_tile(p.M, p.N, p.batch, cus);
+    const double k = (double)p.K;
+    const double here = t.rounds * (t.mt * t.nt * 512.0 * k * (double)cus / (t.tflops * 1e6) + 1.2);
+    auto tiles = [&](long rows) { return (double)((((p.M + rows - 1) / rows) * ((p.N + 127) / 128) * p.batch + cus - 1) / cus); };
+    const double groups = (double)((p.K + 31) / 32);
+    double fp32 = tiles(128) * (groups * 2.95 + 4.0);
+    if (p.M > 64) fp32 = std::fmin(fp32, tiles(64) * (groups * 1.5 + 4.0));
+    return here < fp32;
+}
+
+template <bool TRANS, bool VEC>
+static void f64_dispatch(const F64Tile& t, dim3 grid, hipStream_t st, const F64Args& p) {
+#define TAO_F64(MT, NT, WAVES) hipLaunchKernelGGL((absgemm_f64<TRANS, VEC, MT, NT, WAVES>), grid, dim3(WAVES * 64), 0, st, p)
+    if (t.mt == 1)      { if (t.nt == 1) TAO_F64(1, 1, 16); else if (t.nt == 2) TAO_F64(1, 2, 16); else TAO_F64(1, 4, 8); }
+    else if (t.mt == 2) { if (t.nt == 1) TAO_F64(2, 1, 16); else TAO_F64(2, 2, 8); }
+    else                { if (t.nt == 1) TAO_F64(4, 1, 8); else TAO_F64(4, 2, 8); }
+#undef TAO_F64
+}
+
+int f64_launch(const LinearProblem& q, const tao_fp_model& md, double gamma, int cus, hipStream_t st) {
+    const F64Tile t = f64_tile(q.M, q.N, q.batch, cus);
+    F64Args p;
+    p.A = q.A; p.W = q.W; p.bias = q.bias; p.tau = q.tau;
+    p.M = q.M; p.N = q.N; p.K = q.K; p.lda = q.lda; p.ldw = q.ldw; p.ldt = q.ldt;
+    p.strideA = q.strideA; p.strideW = q.strideW; p.strideT = q.strideT;
+    p.tiles_m = (unsigned)t.tiles_m; p.tiles_n = (unsigned)t.tiles_n;
+    // every addition of non-negative terms within 2^-52 (1 for the product, K - 1 additions in the instruction's
+    // chain, a few more where the wavefronts' sums meet)
+    const double lower = 1.0 - ((double)q.K + 64.0) * 0x1p-52;
+    p.infl = widen(1.0 / lower);
+    p.c = widen(gamma * kGuard);
+    p.uflow = (md.flags & TAO_FLAG_UNDERFLOW_TERMS) ? widen((double)(q.K + (q.bias ? 1 : 0)) * 0x1p-149) : 0.0;
+    const bool vec = aligned(q.A, 16) && q.lda % 4 == 0 && q.strideA % 4 == 0 && aligned(q.W, 16) && q.ldw % 4 == 0 && q.strideW % 4 == 0;
+    const long blocks = (t.tiles_n + 7) / 8 * 8 * t.tiles_m;
+    if (blocks >= (1L << 31)) return TAO_ERR_SHAPE;
+    const dim3 grid((unsigned)blocks, (unsigned)q.batch);
+    if (q.trans_w) { if (vec) f64_dispatch<true, true>(t, grid, st, p); else f64_dispatch<true, false>(t, grid, st, p); }
+    else           { if (vec) f64_dispatch<false, true>(t, grid, st, p); else f64_dispatch<false, false>(t, grid, st, p); }
+    return launch_status();
+}
+
+}  // namespace tao
