@@ -2,14 +2,18 @@
 // reductions; App. A.2 Eq. det-sum) on the BF16 matrix cores of gfx950, which run at 16 times the
 // FP32 MFMA rate.
 //
-// Every binary32 magnitude is cut exactly into three BF16 pieces, a = hi + mid + lo (8 + 8 + 8
-// significand bits, all non-negative), by a streaming pre-pass.  The product of two operands is
-// then the sum of nine BF16 x BF16 products, each exact in binary32; lo x lo is below 2^-30 of
-// hi x hi and is covered by the inflation, the other eight go through v_mfma_f32_32x32x16_bf16:
+// Every binary32 magnitude is cut exactly into three BF16 pieces, a = hi + mid + lo, each the
+// remainder of the one before rounded to nearest (hi non-negative, mid and lo signed: |mid| <= 2^-8 a,
+// |lo| <= 2^-17 a), by a streaming pre-pass or while it is loaded.  The product of two operands is
+// then the sum of nine BF16 x BF16 products, each exact in binary32; mid x lo, lo x mid and lo x lo
+// together stay below 1.001u of it and are covered by the inflation, the other six go through
+// v_mfma_f32_32x32x16_bf16:
 //   main   hi x hi                        one instruction from a zero accumulator per 16 k-steps,
 //                                         folded into a binary64 running sum right away;
-//   cross  hi x mid, mid x hi, hi x lo, lo x hi, mid x mid, mid x lo, lo x mid  (together below
-//          2^-6 of the main term)         one chain of 14 instructions per 32 k-steps, then folded.
+//   cross  mid x mid, hi x lo, lo x hi, hi x mid, mid x hi (in magnitude together below 1.008 x 2^-7 of
+//          the total)                     one chain of 10 instructions per 32 k-steps, then folded.
+// (Pieces cut by masking instead are all non-negative, but then mid x lo reaches 8u and two more
+// products are needed: 2048 x 4096 x 12288 with its check 1481 - 1522 us against 1343 - 1394 us with six.)
 //
 // Accuracy.  For non-negative operands the instruction was characterised on the device (280 000
 // cases against exact rational arithmetic, all reproduced) as two sequential steps over k = 0..7
@@ -19,14 +23,18 @@
 // exponent exceeds e_P by 28 or more);  sum rounded to nearest even.  Hence per instruction from
 // a zero accumulator the result lies in [S (1 - 10u), S (1 + 2u)] (at most seven truncated
 // products per step, each losing less than 2^-24 of the step's largest product; one rounding per
-// step; a dropped second step is below 2u of the first).  A cross chain of 28 steps stays within
-// [X (1 - 92u), X (1 + 28u)] (7u for the truncated products, u for the truncated accumulator, 2u per
-// step for a dropped sum and u per step for the rounding), which is 1.44u and 0.44u of the total.
-// The epilogue multiplies by 1/(1 - 11.5u) (and the binary64 slack), by Gamma and the guard factor
-// and rounds up:  exact <= tau <= exact (1 + 11.5u + 2.44u + 2u + ...) < exact (1 + 16u) < exact (1 + 1e-6).
+// step; a dropped second step is below 2u of the first).  With signed operands the same steps err, in
+// either direction, by at most 7u of the step's sum of magnitudes for the truncated products and 2.01u of the sum
+// of all magnitudes so far for the rest (u for the truncated accumulator, 2^-7 u for the truncated P and u for the
+// rounding, or 2u for a dropped P alone).  A cross chain runs the three small products first in each half:
+// 14 of its 20 steps have a hi x mid in the accumulator, so it errs by at most (7 + 14 x 2.01)u of its sum of
+// magnitudes, 0.28u of the total; the six steps before are below 2^-15 of the total.  hi x hi is at most 1 + 2^-7
+// of the total.  Altogether the sum lies in [S (1 - 11.36u), S (1 + 3.30u)]; the
+// epilogue multiplies by 1/(1 - 11.4u) (and the binary64 slack), by Gamma and the guard factor
+// and rounds up:  exact <= tau <= exact (1 + 11.4u + 3.3u + 2u + ...) < exact (1 + 16.75u) < exact (1 + 1e-6).
 // tao_selftest_matrix_core_bf16 re-checks the instruction model on the device in use.  Operands below
-// 2^-110 in magnitude lose low bits of their lo piece in BF16's subnormal range; the pre-pass rounds
-// that piece up, so the bound stays an upper bound but can exceed 1e-6 there.  Sums that reach
+// 2^-110 in magnitude lose low bits of their lo piece in BF16's subnormal range; that piece is then raised
+// (see split_pack8), so the bound stays an upper bound but can exceed 1e-6 there.  Sums that reach
 // down into the binary32 subnormal range carry an absolute error instead of a relative one; the
 // epilogue adds a bound on it (see split_run), which is far below 1e-6 of any bound above 2^-120.
 #include <cstring>
@@ -61,30 +69,44 @@ constexpr int kWalkMinTilesPerCu = 4;   // ... when a compute unit has at least 
 
 // ---- pre-pass: binary32 -> BF16 blocks [k / 32][row / 128][piece][row % 128][32] with the 16-byte units of
 // a row swizzled: the LDS image of a workgroup's slab; zero-padded to Kp columns ----------------------
-// The three pieces of |v| as binary32 bit patterns whose upper halves are the BF16 pieces: hi by
-// masking, mid by masking the exact remainder, lo = the exact second remainder (at most 8 significant
-// bits), rounded up to a BF16 value by adding 0xffff before the upper half is taken (exact unless the
-// remainder lies below BF16's subnormal step: then up).  An infinite or NaN operand leaves pieces that
-// are infinite or NaN (inf - inf), so its outputs are never finite.
-__device__ __forceinline__ void split_bits(float v, unsigned& h, unsigned& m, unsigned& l) {
-    const float a = fabsf(v);
-    h = __float_as_uint(a) & 0xffff0000u;
-    const float r1 = a - __uint_as_float(h);                           // exact
-    m = __float_as_uint(r1) & 0xffff0000u;
-    const float r2 = r1 - __uint_as_float(m);                          // exact
-    l = __float_as_uint(r2) + 0xffffu;
+// The three pieces of |v|: hi = |v| rounded to the nearest BF16 value, mid = the exact remainder (signed) rounded to
+// nearest, lo = the exact second remainder, six significant bits, so that hi + mid + lo = |v| with
+// |mid| <= 2^-8 |v| and |lo| <= 2^-17 |v|.  hi is kept finite (a value beyond the largest BF16 number leaves its
+// excess to mid, which stays within that bound).  An infinite or NaN operand leaves an infinite or NaN mid and a NaN
+// lo (inf - inf), so its outputs are never finite.  Where lo falls below BF16's subnormal step, 2^-133 (operands below
+// 2^-110), it is rounded up and raised by one step more: the pieces then sum to at least |v| + 2^-133, which covers what
+// the dropped products (split_run) can amount to there, relative to such an operand.
+// Eight consecutive values -> the three 16-byte units of BF16 pieces.
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float floatx2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ unsigned pack_bf16(float even, float odd) {                 // both rounded to nearest even
+    return __builtin_bit_cast(unsigned, __builtin_convertvector((floatx2{even, odd}), bf16x2));
 }
-// Eight consecutive values -> the three 16-byte units of BF16 pieces (upper halves packed in pairs).
+__device__ __forceinline__ unsigned short lo_below_step(float r2) {
+    if (!(r2 == r2)) return 0x7fc0u;
+    const unsigned bits = __float_as_uint(r2);
+    if (!(bits & 0xffffu)) return (unsigned short)(bits >> 16);
+    const unsigned up = __float_as_uint(r2 + 0x1p-133f);                               // exact: multiples of 2^-149 below 2^-126
+    return (unsigned short)((up + ((up >> 31) ? 0u : 0xffffu)) >> 16);                 // towards +infinity
+}
 __device__ __forceinline__ void split_pack8(const float (&v)[8], uintx4& H, uintx4& Mi, uintx4& L) {
-    unsigned h[8], m[8], l[8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) split_bits(v[j], h[j], m[j], l[j]);
+    float r2[8];
+    unsigned below = 0;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-        // bytes 2, 3 of the even element, then bytes 2, 3 of the odd one
-        H[j] = __builtin_amdgcn_perm(h[2 * j + 1], h[2 * j], 0x07060302u);
-        Mi[j] = __builtin_amdgcn_perm(m[2 * j + 1], m[2 * j], 0x07060302u);
-        L[j] = __builtin_amdgcn_perm(l[2 * j + 1], l[2 * j], 0x07060302u);
+        constexpr float kMaxBf16 = 0x1.fep127f;
+        const float a0 = fabsf(v[2 * j]), a1 = fabsf(v[2 * j + 1]);
+        H[j] = pack_bf16(fminf(a0, kMaxBf16), fminf(a1, kMaxBf16));
+        const float r0 = a0 - __uint_as_float(H[j] << 16), r1 = a1 - __uint_as_float(H[j] & 0xffff0000u);
+        Mi[j] = pack_bf16(r0, r1);
+        r2[2 * j] = r0 - __uint_as_float(Mi[j] << 16);
+        r2[2 * j + 1] = r1 - __uint_as_float(Mi[j] & 0xffff0000u);
+        L[j] = __builtin_amdgcn_perm(__float_as_uint(r2[2 * j + 1]), __float_as_uint(r2[2 * j]), 0x07060302u);
+        below |= __float_as_uint(r2[2 * j]) | __float_as_uint(r2[2 * j + 1]);
+    }
+    if (__builtin_expect((below & 0xffffu) != 0, 0)) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) L[j] = lo_below_step(r2[2 * j]) | ((unsigned)lo_below_step(r2[2 * j + 1]) << 16);
     }
 }
 
@@ -182,7 +204,7 @@ __device__ __forceinline__ double bound_offset(const SplitArgs& p, double s_abs,
     return fma(p.cg, s_abs + ab, p.uflow);
 }
 __device__ __forceinline__ double bound_of_sum(const SplitArgs& p, double sv, double off_pos, double off_zero) {
-    return fma(sv, p.c1, sv > 0.0 ? off_pos : off_zero);
+    return fma(sv, p.c1, sv != 0.0 ? off_pos : off_zero);
 }
 
 // check_one with the histogram layout of the CHECK instantiation below (16-bit counters, bin b in
@@ -367,15 +389,15 @@ __global__ __launch_bounds__(kSplitThreads) void absgemm_split(SplitArgs p) {
         return *reinterpret_cast<const bf16x8*>(stage + off);
     };
     // One group (32 k-steps) of both tiles of the wavefront, in four parts (k half, tile): a part
-    // issues the eight matrix-core instructions of its tile (hi x hi from zero into D, the seven
-    // cross products into the chain X) and, in their shadow, folds into the binary64 sums what the
+    // issues the six matrix-core instructions of its tile (hi x hi from zero into D, the five
+    // cross products into the chain X, the small ones first) and, in their shadow, folds into the binary64 sums what the
     // OTHER tile finished one part earlier: its D always, its chain X where the chain has just ended
     // (tile 0's ends in the third part, tile 1's in the fourth and is folded in the first part of the
     // next group).  A matrix-core instruction occupies its pipe for 32 cycles, in which the SIMD
     // issues up to eight vector instructions; folding a result right after the instruction that
     // produced it instead stalls the wavefront until that instruction has drained (measured: the loop
     // runs at the matrix cores' own pace with this order and 19 % slower without).  The scheduling
-    // directives ask for exactly that interleaving: one matrix-core instruction, then 4 or 8 vector
+    // directives ask for exactly that interleaving: one matrix-core instruction, then 6 or 11 vector
     // instructions.
     auto fold = [&](double (&acc)[16], const floatx16& part) __attribute__((always_inline)) {
 #pragma unroll
@@ -399,19 +421,17 @@ __global__ __launch_bounds__(kSplitThreads) void absgemm_split(SplitArgs p) {
                 fold(S[o], D[o]);
                 if (chain_ended) fold(S[o], X[o]);
                 D[t] = TAO_MFMA_BF16(a[0], b[t][0], zero);
-                // the cross products: hi x mid, mid x hi, then the five of the order of 2^-14 and below
-                X[t] = TAO_MFMA_BF16(a[0], b[t][1], kg == 0 ? zero : X[t]);
-                X[t] = TAO_MFMA_BF16(a[1], b[t][0], X[t]);
+                // the cross products: the three of the order of 2^-16, then hi x mid and mid x hi
+                X[t] = TAO_MFMA_BF16(a[1], b[t][1], kg == 0 ? zero : X[t]);
                 X[t] = TAO_MFMA_BF16(a[0], b[t][2], X[t]);
                 X[t] = TAO_MFMA_BF16(a[2], b[t][0], X[t]);
-                X[t] = TAO_MFMA_BF16(a[1], b[t][1], X[t]);
-                X[t] = TAO_MFMA_BF16(a[1], b[t][2], X[t]);
-                X[t] = TAO_MFMA_BF16(a[2], b[t][1], X[t]);
+                X[t] = TAO_MFMA_BF16(a[0], b[t][1], X[t]);
+                X[t] = TAO_MFMA_BF16(a[1], b[t][0], X[t]);
 #pragma unroll
-                for (int q = 0; q < 8; ++q) {
+                for (int q = 0; q < 6; ++q) {
                     __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                     // one MFMA
-                    if (chain_ended) __builtin_amdgcn_sched_group_barrier(0x002, 8, 0);    // vector ALU
-                    else             __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);
+                    if (chain_ended) __builtin_amdgcn_sched_group_barrier(0x002, 11, 0);   // vector ALU
+                    else             __builtin_amdgcn_sched_group_barrier(0x002, 6, 0);
                 }
             }
         }
@@ -715,18 +735,24 @@ int tao_selftest_matrix_core_bf16(unsigned* report, long cases, void* ws, size_t
     auto bf = [](int e, unsigned man7) { return (unsigned short)(((127 + e) << 7) | (man7 & 127u)); };
     auto f32 = [](int e, unsigned man23) { const unsigned u = ((unsigned)(127 + e) << 23) | (man23 & 0x7fffffu); float f; memcpy(&f, &u, 4); return f; };
     // four seeded families of non-negative operands: narrow exponents; wide exponents; products far
-    // below an accumulator of the order of 1; products and sums in the binary32 subnormal range
+    // below an accumulator of the order of 1; products and sums in the binary32 subnormal range; and a fifth
+    // of signed operands over the exponents of the second (the cross products)
     for (int i = 0; i < kCases; ++i) {
         Bf16Case& c = hc[i];
-        const int fam = i % 4;
+        const int fam = i % 5;
         const int shift = 20 + (int)(rnd() % 10);
         for (int k = 0; k < 16; ++k) {
             if (fam == 0)      { c.a[k] = bf((int)(rnd() % 3) - 1, rnd()); c.b[k] = bf((int)(rnd() % 3) - 1, rnd()); }     // narrow
             else if (fam == 1) { c.a[k] = bf((int)(rnd() % 25) - 12, rnd()); c.b[k] = bf((int)(rnd() % 25) - 12, rnd()); } // wide
             else if (fam == 2) { c.a[k] = bf(-(shift / 2) + (int)(rnd() % 3) - 1, rnd()); c.b[k] = bf(-(shift - shift / 2), rnd()); }  // far below c
-            else               { c.a[k] = bf(-75 + (int)(rnd() % 11), rnd()); c.b[k] = bf(-75 + (int)(rnd() % 11), rnd()); }           // 2^-150 .. 2^-128
+            else if (fam == 3) { c.a[k] = bf(-75 + (int)(rnd() % 11), rnd()); c.b[k] = bf(-75 + (int)(rnd() % 11), rnd()); }           // 2^-150 .. 2^-128
+            else {
+                const int w = i % 2 ? 25 : 3;
+                c.a[k] = bf((int)(rnd() % w) - w / 2, rnd()); c.b[k] = bf((int)(rnd() % w) - w / 2, rnd());
+                c.b[k] |= (unsigned short)((rnd() & 1u) << 15);
+            }
         }
-        c.c = fam == 3 ? 0.f : fam == 2 ? f32(0, rnd()) : ((i & 1) ? f32((int)(rnd() % 25) - 12, rnd()) : 0.f);
+        c.c = fam == 3 ? 0.f : fam == 2 ? f32(0, rnd()) : fam == 4 ? ((i & 2) ? -1.f : 1.f) * f32((int)(rnd() % 25) - 12, rnd()) : ((i & 1) ? f32((int)(rnd() % 25) - 12, rnd()) : 0.f);
     }
     Bf16Case* dc = static_cast<Bf16Case*>(ws);
     float* dd = reinterpret_cast<float*>(static_cast<char*>(ws) + ((size_t)kCases * sizeof(Bf16Case) + 255) / 256 * 256);
@@ -742,12 +768,14 @@ int tao_selftest_matrix_core_bf16(unsigned* report, long cases, void* ws, size_t
         unsigned u; memcpy(&u, &f, 4);
         if (f == 0.f) return 0;
         const int ex = (int)((u >> 23) & 255) - 127;
-        return (u128)((u & 0x7fffffu) | 0x800000u) << (kScale + ex - 23);
+        const u128 m = (u & 0x7fffffu) | 0x800000u;
+        const int sh = kScale + ex - 23;
+        return sh >= 0 ? m << sh : m >> -sh;                  // (what cancellation leaves: low bits zero)
     };
     bool exact = true, within = true, tiny = true;
     for (int i = 0; i < kCases; ++i) {
         const Bf16Case& c = hc[i];
-        if (i % 4 == 3) {
+        if (i % 5 == 3) {
             // subnormal range: the exact sum (16 products of 16 bits within 22 binades: exact in
             // binary64) against the result, in steps of 2^-149
             double sum = 0.0;
@@ -756,6 +784,21 @@ int tao_selftest_matrix_core_bf16(unsigned* report, long cases, void* ws, size_t
                 sum += std::ldexp((double)(((c.a[k] & 127u) | 128u) * ((c.b[k] & 127u) | 128u)), ea + eb - 14);
             }
             if (!(std::fabs((double)hd[i] - sum) <= 2.0 * 0x1p-149)) tiny = false;
+            continue;
+        }
+        if (i % 5 == 4) {
+            // signed operands: within 2 x 2.01u + 7u < 11.25u of the sum of all magnitudes
+            __int128 sum = c.c < 0.f ? -(__int128)to_int(-c.c) : (__int128)to_int(c.c);
+            u128 mag = to_int(std::fabs(c.c));
+            for (int k = 0; k < 16; ++k) {
+                const int ea = (int)((c.a[k] >> 7) & 255) - 127, eb = (int)((c.b[k] >> 7) & 255) - 127;
+                const u128 v = (u128)(((c.a[k] & 127u) | 128u) * ((c.b[k] & 127u) | 128u)) << (kScale + ea + eb - 14);
+                sum += (c.b[k] & 0x8000u) ? -(__int128)v : (__int128)v;
+                mag += v;
+            }
+            const __int128 got = hd[i] < 0.f ? -(__int128)to_int(-hd[i]) : (__int128)to_int(hd[i]);
+            const __int128 off = got > sum ? got - sum : sum - got;
+            if (!((u128)off <= (mag >> 26) * 45u)) within = false;
             continue;
         }
         u128 prod[16]; int pexp[16];
@@ -958,17 +1001,18 @@ static int split_core(const unsigned short* A3, const unsigned short* W3, const 
     p.batchA3 = (Kp / SBK) * blocksA * (kBlock / 2); p.batchW3 = shared_w ? 0 : (Kp / SBK) * blocksW * (kBlock / 2);
     p.tiles_n = (unsigned)tiles_n; p.tiles_m = (unsigned)tiles_m;
     const double u = md.u;
-    // lower factor of the accumulation: (1 - 11.5u) for the matrix-core steps (10u main, 1.44u
-    // cross, rounded up), 2^-53 per binary64 addition (three per 32 k-steps and output element)
+    // lower factor of the accumulation: (1 - 11.4u) for the matrix-core steps and the dropped products (10.08u main,
+    // 0.28u cross, 1.001u dropped), 2^-53 per binary64 addition (three per 32 k-steps and output element)
     const double f64 = (double)(3 * (Kp / SBK) + 4 + 16);             // + the additions of up to 16 parts
-    const double lower = (1.0 - 11.5 * u) * (1.0 - f64 * 0x1p-53);
+    const double lower = (1.0 - 11.4 * u) * (1.0 - f64 * 0x1p-53);
     const double infl = widen(1.0 / (lower * (1.0 - 0x1p-52)));
     p.uflow = (md.flags & TAO_FLAG_UNDERFLOW_TERMS) ? widen((double)Kp_ * 0x1p-149) : 0.0;
     // Results in the binary32 subnormal range: the instruction keeps subnormal operands, products
     // and sums (gradual underflow) and then errs absolutely, by less than one step of 2^-149 per
     // instruction (probed like the model above: 160 000 cases with products between 2^-160 and
-    // 2^-120); two steps are budgeted for each of the 16 instructions an output element sees per
-    // 32 k-steps.  Added to every positive sum; to an exactly zero sum only when the caller asked for
+    // 2^-120); two steps are budgeted for each of the 12 instructions an output element sees per
+    // 32 k-steps, and some to spare.  Added to every sum but an exact zero (the signed cross products can leave a sum
+    // this far below zero); to an exactly zero sum only when the caller asked for
     // underflow terms (otherwise such a sum is taken as the exact zero of zero operands).
     const double sabs = K > 0 ? ((double)Kp + 32.0) * 0x1p-149 : 0.0;
     // The folded constants; every product is rounded up with room for the two or three roundings of its

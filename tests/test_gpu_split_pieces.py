@@ -1,0 +1,77 @@
+"""The BF16-split matmul bound on operands at the edges of its three pieces: halfway remainders, the top of the binary32
+range, operands below 2^-110 (whose last piece leaves BF16's grid) and subnormal ones, infinities and NaN."""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+U = 2.0 ** -24
+
+
+@pytest.fixture(scope="module")
+def tao():
+    import paper_2510_16028_amd as t
+    t.lib()
+    assert torch.cuda.is_available()
+    return t
+
+
+def _operand(rng, rows, K, kind):
+    sign = np.where(rng.random((rows, K)) < 0.5, -1.0, 1.0)
+    man = rng.integers(0, 1 << 23, (rows, K))
+    if kind == "halves":                                     # remainders of half a step, one unit to either side
+        man = (rng.integers(0, 128, (rows, K)) << 16) | (0x8000 + rng.integers(-1, 2, (rows, K)))
+        man = np.where(rng.random((rows, K)) < 0.5, man, (1 << 15) - (1 << 14) - (1 << 6) + rng.integers(0, 2, (rows, K)))
+        e = rng.integers(-3, 4, (rows, K))
+    elif kind == "top":
+        man = np.where(rng.random((rows, K)) < 0.5, man, (1 << 23) - 1 - rng.integers(0, 1 << 15, (rows, K)))
+        e = np.full((rows, K), 127)
+    elif kind == "small":
+        e = rng.integers(-126, -104, (rows, K))
+    elif kind == "subnormal":
+        return (sign * rng.integers(0, 1 << 23, (rows, K)) * 2.0 ** -149).astype(np.float32)
+    else:
+        e = rng.integers(-2, 3, (rows, K))
+    return (sign * np.ldexp(((1 << 23) + man).astype(np.float64), e - 23)).astype(np.float32)
+
+
+# relative room above the exact bound: 1e-6, and what the raised last piece adds to operands below 2^-110:
+# at most two steps of 2^-133 relative to 2^-126 (normal) -- subnormal ones are bounded from below only
+@pytest.mark.parametrize("a,w,scale,room", [
+    ("plain", "plain", 0, 1e-6), ("halves", "halves", 0, 1e-6), ("top", "plain", -60, 1e-6), ("plain", "top", -60, 1e-6),
+    ("small", "halves", 60, 1e-6 + 2.0 ** -6), ("halves", "small", 60, 1e-6 + 2.0 ** -6), ("subnormal", "halves", 60, None),
+])
+@pytest.mark.parametrize("M,N,K", [(5, 3, 33), (130, 200, 160)])
+def test_bound_at_the_edges_of_the_pieces(tao, a, w, scale, room, M, N, K):
+    rng = np.random.Generator(np.random.Philox(M + K + len(a)))
+    A, W = _operand(rng, M, K, a), _operand(rng, N, K, w)
+    if scale > 0:                                            # products well inside the normal range
+        A, W = (A, (W * 2.0 ** scale).astype(np.float32)) if a in ("small", "subnormal") else ((A * 2.0 ** scale).astype(np.float32), W)
+    elif scale < 0:
+        A, W = (A, (W * 2.0 ** scale).astype(np.float32)) if a == "top" else ((A * 2.0 ** scale).astype(np.float32), W)
+    tau = tao.tao_bound_linear_split(torch.from_numpy(A).cuda(), torch.from_numpy(W).cuda()).cpu().numpy().astype(np.float64)
+    # products of two binary32 values are exact in binary64; K additions of them stay within K 2^-53
+    exact = np.abs(A.astype(np.float64)) @ np.abs(W.astype(np.float64)).T * (K * U / (1 - K * U))
+    slack = (K + 8) * 2.0 ** -53
+    assert np.isfinite(tau).all()
+    assert (tau >= exact * (1 - slack)).all()
+    if room is not None:
+        assert (tau <= exact * (1 + room) * (1 + slack)).all()
+
+
+@pytest.mark.parametrize("bad", [float("inf"), float("-inf"), float("nan"), "payload"])
+def test_non_finite_operands_never_give_a_finite_bound(tao, bad):
+    g = torch.Generator().manual_seed(3)
+    A, W = torch.randn((40, 96), generator=g), torch.randn((24, 96), generator=g)
+    if bad == "payload":                                     # NaN patterns at both ends of the payload
+        A.view(torch.int32)[7, 50] = 0x7f800001
+        A.view(torch.int32)[8, 51] = 0x7fffffff
+        W.view(torch.int32)[3, 60] = -1
+    else:
+        A[7, 50] = bad; A[8, 51] = bad; W[3, 60] = bad
+    W[5] = 0.0                                               # inf x 0 as well
+    tau = tao.tao_bound_linear_split(A.cuda(), W.cuda()).cpu()
+    hit = torch.zeros(40, 24, dtype=torch.bool)
+    hit[7], hit[8], hit[:, 3] = True, True, True
+    assert not torch.isfinite(tau[hit]).any() and torch.isfinite(tau[~hit]).all()
