@@ -12,6 +12,7 @@
 // Formulas: Sec. 3.1 softmax template closed to second order; LayerNorm,
 // RMSNorm, BatchNorm-affine, sum and mean (operators of App. A.3) from the
 // primitive rule of Sec. 3.1 with Gamma(n-1) for the reductions (App. A.2).
+#include <type_traits>
 #include "tao_check.hpp"
 #include "tao_device.hpp"
 #include "tao_host.hpp"
@@ -171,6 +172,11 @@ __global__ __launch_bounds__(kRowThreads) void softmax_bound(
 // histogram of relative errors in LDS and leave one partial per workgroup, like the streaming
 // check pass; the same finalising kernel turns the partials into the profile.  HBM traffic:
 // x, y and claimed read once (12 B per element), nothing written.
+// QUICK: most elements are settled in binary32 (QuickCheck), with a lower estimate of the bound; the
+// others form the bound in binary64 as softmax_bound does.  FULL: aligned rows of whole vectors.
+// What bounds it: HBM, 5.6 TB/s on 65536 causal or dense rows of 2048 columns (462 -> 286 us, 16384 x 1024 83 -> 50 us,
+// 8192 x 4096 131 -> 110 us).  Before, a wavefront waited for each of its loads (a test for the row's
+// end around every one of them), four wavefronts met at three barriers per row, and an element took 58 vector instructions.
 template <int TPR>
 __device__ __forceinline__ void wide_group_sum(double* v, int count, double* smem) {
     for (int i = 0; i < count; ++i) v[i] = wave_sum(v[i]);
@@ -201,35 +207,67 @@ __device__ __forceinline__ void wide_group_max_or(float& m, int& flag, double* s
     }
 }
 
-template <int TPR, int V>
+// Four values of a row from column idx on, loaded without a branch: from clamped positions that exist; row_fill then
+// replaces those at and beyond `limit`.  (Behind a test for the row's end every load waited for the one before it.)
+// FULL: 16-byte aligned rows of whole vectors.  last: the last position of a vector (FULL) or value.
+template <bool FULL, bool STREAM, class Idx>
+__device__ __forceinline__ float4 row_vec(const float* __restrict__ row, Idx idx, Idx last) {
+    if (FULL) {
+        const float4* p = reinterpret_cast<const float4*>(row + min(idx, last));
+        return STREAM ? ntload4(p) : *p;
+    }
+    return make_float4(row[min(idx, last)], row[min((Idx)(idx + 1), last)], row[min((Idx)(idx + 2), last)], row[min((Idx)(idx + 3), last)]);
+}
+template <bool FULL, class Idx>
+__device__ __forceinline__ float4 row_fill(float4 r, Idx idx, Idx limit, float fill) {
+    const bool i0 = idx < limit, i1 = FULL ? i0 : idx + 1 < limit, i2 = FULL ? i0 : idx + 2 < limit, i3 = FULL ? i0 : idx + 3 < limit;
+    return make_float4(i0 ? r.x : fill, i1 ? r.y : fill, i2 ? r.z : fill, i3 ? r.w : fill);
+}
+#define TAO_VEC_IDX(v) (((Idx)(v) * TPR + lt) * 4)
+
+template <int TPR, int V, bool FULL, bool QUICK>
 __global__ __launch_bounds__(kCheckThreads) void softmax_check(
     const float* __restrict__ x, const float* __restrict__ y, const float* __restrict__ claimed,
-    long rows, long cols, long ld, int vec_ok, RowConsts k, double alpha, double eps_rel,
+    long rows, long cols, long ld, RowConsts k, double alpha, double eps_rel,
     unsigned int* __restrict__ ws_hist, unsigned int* __restrict__ ws_coarse, BlockStats* __restrict__ ws_stats) {
     constexpr int RPB = kCheckThreads / TPR;
-    constexpr bool CACHED = (V > 0);
+    using Idx = typename std::conditional<(V > 0), int, long>::type;     // columns: a cached row has at most 8192
+    constexpr bool CACHED = (V > 0), CLAIMS = CACHED && V <= 4;      // claims requested with the row
     __shared__ unsigned int hist[kBins * kReplicas];
     __shared__ unsigned int red[3 * (kCheckThreads / kWave)];
     __shared__ double smem[2 * 4 * (kCheckThreads / kWave)];       // one slot per reduction of a row
+    __shared__ unsigned int largest;
     const int tid = threadIdx.x;
+    const QuickCheck qc(alpha, eps_rel);
+    unsigned known = 0;
     for (int i = tid; i < kBins * kReplicas; i += kCheckThreads) hist[i] = 0;
+    if (tid == 0) largest = 0;
     __syncthreads();
     ThreadAcc acc_chk;
     const int rep = tid & (kReplicas - 1);
-    const int lt = tid % TPR;
     const int nv = CACHED ? V : (int)((cols + TPR * 4 - 1) / (TPR * 4));
     const long nblocks = (rows + RPB - 1) / RPB;
     // every thread of the workgroup takes the same number of trips (the reductions hold barriers)
     for (long rb = blockIdx.x; rb < nblocks; rb += gridDim.x) {
+        int lt = tid % TPR;
+        if (CACHED) asm volatile("" : "+v"(lt));            // (positions are formed anew for every row and pass: hoisted they would take the registers of the row)
         const long row = rb * RPB + tid / TPR;
         const bool active = row < rows;
-        const long limit = active ? cols : 0;
-        const long roff = active ? row * ld : 0;
-        float4 xv[CACHED ? V : 1], yv[CACHED ? V : 1];
+        const Idx limit = active ? (Idx)cols : 0, last = (Idx)cols - (FULL ? 4 : 1);
+        const long roff = (active ? row : rows - 1) * ld;
+        float4 xv[CACHED ? V : 1], yv[CACHED ? V : 1], cv[CLAIMS ? V : 1];
         float m = -INFINITY; int bad = 0;
+        if (CACHED) {
+            for (int v = 0; v < nv; ++v) {
+                xv[v] = row_vec<FULL, true>(x + roff, TAO_VEC_IDX(v), last);
+                yv[v] = row_vec<FULL, true>(y + roff, TAO_VEC_IDX(v), last);
+                if (CLAIMS) cv[v] = row_vec<FULL, true>(claimed + roff, TAO_VEC_IDX(v), last);
+            }
+            __builtin_amdgcn_sched_barrier(0);               // (all requests leave before the first is waited for)
+        }
         for (int v = 0; v < nv; ++v) {
-            const float4 X = load4<CACHED>(x + roff, TAO_VEC_INDEX(v), limit, vec_ok, -INFINITY);
-            if (CACHED) { xv[v] = X; yv[v] = load4<true>(y + roff, TAO_VEC_INDEX(v), limit, vec_ok, 0.f); }
+            const float4 X = row_fill<FULL>(CACHED ? xv[v] : row_vec<FULL, false>(x + roff, TAO_VEC_IDX(v), last), TAO_VEC_IDX(v), limit, -INFINITY);
+            if (CACHED) { xv[v] = X; yv[v] = row_fill<FULL>(yv[v], TAO_VEC_IDX(v), limit, 0.f); }
             const float e[4] = {X.x, X.y, X.z, X.w};
 #pragma unroll
             for (int c = 0; c < 4; ++c) { bad |= (e[c] != e[c]) | (e[c] == INFINITY); m = fmaxf(m, e[c]); }
@@ -247,8 +285,8 @@ __global__ __launch_bounds__(kCheckThreads) void softmax_check(
             q = (double)(masked ? 0.f : fabsf(ye)) * k.inv1mu;
         };
         for (int v = 0; v < nv; ++v) {
-            const float4 X = CACHED ? xv[v] : load4(x + roff, TAO_VEC_INDEX(v), limit, vec_ok, -INFINITY);
-            const float4 Y = CACHED ? yv[v] : load4(y + roff, TAO_VEC_INDEX(v), limit, vec_ok, 0.f);
+            const float4 X = CACHED ? xv[v] : row_fill<FULL>(row_vec<FULL, false>(x + roff, TAO_VEC_IDX(v), last), TAO_VEC_IDX(v), limit, -INFINITY);
+            const float4 Y = CACHED ? yv[v] : row_fill<FULL>(row_vec<FULL, false>(y + roff, TAO_VEC_IDX(v), last), TAO_VEC_IDX(v), limit, 0.f);
             const float xe[4] = {X.x, X.y, X.z, X.w}, ye[4] = {Y.x, Y.y, Y.z, Y.w};
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
@@ -264,31 +302,49 @@ __global__ __launch_bounds__(kCheckThreads) void softmax_check(
         const double w1 = bad ? NAN : 1.0 + sfac;
         const double w0 = bad ? NAN : sfac + k.u;
         const UpFactors up(k.m * (1.0 + 2.0 / (1.0 - sigma)));
+        // alpha tau = |y| (rho w1 + w0) from below, in binary32 (rho held finite: a mask of the lowest finite value
+        // has no square there)
+        const float w1f = (float)(w1 * k.inv1mu) * qc.alpha, w0f = (float)(w0 * k.inv1mu) * qc.alpha;
+        const float uf = (float)k.u, uamf = (float)uam, invf = (float)k.inv1mce, cef = (float)ce_inv;
+        if (QUICK) known = newest(&largest);
+        if (CACHED) asm volatile("" : "+v"(lt));
+        float4 next = make_float4(0.f, 0.f, 0.f, 0.f);       // the next vector's claims are on their way while one is checked
+        if (!CLAIMS) next = row_vec<FULL, true>(claimed + roff, TAO_VEC_IDX(0), last);
         for (int v = 0; v < nv; ++v) {
-            const long idx = TAO_VEC_INDEX(v);
+            const Idx idx = TAO_VEC_IDX(v);
+            const float4 C = CLAIMS ? cv[v] : next;
+            if (!CLAIMS && v + 1 < nv) next = row_vec<FULL, true>(claimed + roff, TAO_VEC_IDX(v + 1), last);
             if (idx >= limit) continue;
-            const float4 X = CACHED ? xv[v] : load4(x + roff, idx, limit, vec_ok, -INFINITY);
-            const float4 Y = CACHED ? yv[v] : load4(y + roff, idx, limit, vec_ok, 0.f);
-            const float4 C = load4<true>(claimed + roff, idx, limit, vec_ok, 0.f);
-            const float xe[4] = {X.x, X.y, X.z, X.w}, ye[4] = {Y.x, Y.y, Y.z, Y.w}, ce[4] = {C.x, C.y, C.z, C.w};
-            if (idx + 3 < limit) {                           // a whole vector: four chains side by side
-                float te[4];
+            const float4 X = CACHED ? xv[v] : row_vec<FULL, false>(x + roff, idx, last);
+            const float4 Y = CACHED ? yv[v] : row_vec<FULL, false>(y + roff, idx, last);
+            floatv4 xe = {X.x, X.y, X.z, X.w}, ye = {Y.x, Y.y, Y.z, Y.w}, ce = {C.x, C.y, C.z, C.w};
+            asm volatile("" : "+v"(xe), "+v"(ye));           // (keeps the first pass's binary64 values from living on until here)
+            auto tau = [&](int c) __attribute__((always_inline)) {
+                double q, rho;
+                q_rho(xe[c], ye[c], q, rho);
+                return up32g(q * fma(rho, w1, w0), up.mul, up.sub);
+            };
+            if (FULL || idx + 3 < limit) {
+                if (!QUICK) {
+                    const float c4[4] = {ce[0], ce[1], ce[2], ce[3]}, y4[4] = {ye[0], ye[1], ye[2], ye[3]};
+                    const float t4[4] = {tau(0), tau(1), tau(2), tau(3)};
+                    check_four(c4, y4, t4, alpha, eps_rel, hist, rep, acc_chk);
+                    continue;
+                }
+                floatv4 at;
 #pragma unroll
                 for (int c = 0; c < 4; ++c) {
-                    double q, rho;
-                    q_rho(xe[c], ye[c], q, rho);
-                    te[c] = up32g(q * fma(rho, w1, w0), up.mul, up.sub);
+                    const float a = fmaf(uf, fabsf(xe[c]), uamf);
+                    const float rho = fminf(fmaf(fmaf(a, a, a), invf, cef), 0x1p60f);
+                    at[c] = (xe[c] == -INFINITY ? 0.f : fabsf(ye[c])) * fmaf(rho, w1f, w0f);
                 }
-                check_four(ce, ye, te, alpha, eps_rel, hist, rep, acc_chk);
+                quick_check_four<(V == 1 || (V == 2 && TPR < 1024))>(ce, ye, at, tau, qc, alpha, eps_rel, hist, rep, acc_chk, &largest, known);
                 continue;
             }
 #pragma unroll
-            for (int c = 0; c < 4; ++c) {
+            for (int c = 0; c < 3; ++c) {
                 if (idx + c >= limit) break;
-                double q, rho;
-                q_rho(xe[c], ye[c], q, rho);
-                const float t = up32g(q * fma(rho, w1, w0), up.mul, up.sub);
-                check_one(ce[c], ye[c], t, alpha, eps_rel, hist, rep, acc_chk);
+                check_one(ce[c], ye[c], tau(c), alpha, eps_rel, hist, rep, acc_chk);
             }
         }
     }
@@ -1042,28 +1098,38 @@ int tao_bound_check_softmax(const float* x, const float* y_ref, const float* cla
     if (rc != TAO_OK) return rc;
     hipStream_t st = (hipStream_t)stream;
     const CheckWorkspace w = carve_check_workspace(ws);
-    const int vec_ok = aligned(x, 16) && aligned(y_ref, 16) && aligned(claimed, 16) && (ld % 4 == 0);
+    const bool full = aligned(x, 16) && aligned(y_ref, 16) && aligned(claimed, 16) && (ld % 4 == 0) && (cols % 4 == 0);
     int nblocks = 1;
     if (n > 0) {
         auto launch = [&](auto kernel, int tpr) {
             const long rb = (rows + (kCheckThreads / tpr) - 1) / (kCheckThreads / tpr);
             nblocks = (int)(rb < kMaxCheckBlocks ? rb : kMaxCheckBlocks);
             hipLaunchKernelGGL(kernel, dim3(nblocks), dim3(kCheckThreads), 0, st, x, y_ref, claimed, rows, cols, ld,
-                               vec_ok, k, alpha, eps_rel, w.hist, w.coarse, w.stats);
+                               k, alpha, eps_rel, w.hist, w.coarse, w.stats);
         };
-        // at most two vectors per thread (the check's binary64 division leaves no room for more
-        // under the 128-register limit of a 1024-thread workgroup): longer rows take wider groups
-        if (cols <= 256)       launch(softmax_check<64, 1>, 64);
-        else if (cols <= 512)  launch(softmax_check<64, 2>, 64);
-        else if (cols <= 1024) launch(softmax_check<256, 1>, 256);
-        else if (cols <= 2048) launch(softmax_check<256, 2>, 256);
-        else if (cols <= 4096) launch(softmax_check<512, 2>, 512);
-        else if (cols <= 8192) launch(softmax_check<1024, 2>, 1024);
-        else                   launch(softmax_check<1024, 0>, 1024);
+        // Quick settlement pays from four rows per row group on; below, most elements are the first a workgroup sees
+        // and the second route is only more code to fetch (512 x 512 16 against 20 us, 256 x 4096 19 against 22).
+        // With that many rows a row of up to 2048 columns belongs to one wavefront (no barrier: the wavefronts of a
+        // workgroup drift apart, so that some load while others calculate); fewer rows of more than 512 columns are
+        // divided among four, which fill the chip sooner (2048 x 2048 26 against 41 us).
+        auto quick = [&](int tpr) { return rows >= 4L * kMaxCheckBlocks * (kCheckThreads / tpr); };
+#define TAO_SOFTMAX_CHECK_Q(TPR, V, Q) (full ? launch(softmax_check<TPR, V, true, Q>, TPR) : launch(softmax_check<TPR, V, false, Q>, TPR))
+#define TAO_SOFTMAX_CHECK(TPR, V) do { if (quick(TPR)) TAO_SOFTMAX_CHECK_Q(TPR, V, true); else TAO_SOFTMAX_CHECK_Q(TPR, V, false); } while (0)
+        if (cols <= 256)       TAO_SOFTMAX_CHECK(64, 1);
+        else if (cols <= 512)  TAO_SOFTMAX_CHECK(64, 2);
+        else if (cols <= 1024 && quick(64)) TAO_SOFTMAX_CHECK_Q(64, 4, true);
+        else if (cols <= 1024) TAO_SOFTMAX_CHECK(256, 1);
+        else if (cols <= 2048 && quick(64) && full) launch(softmax_check<64, 8, true, true>, 64);   // (four addresses to a vector: no registers for eight)
+        else if (cols <= 2048) TAO_SOFTMAX_CHECK(256, 2);
+        else if (cols <= 4096) TAO_SOFTMAX_CHECK(512, 2);
+        else if (cols <= 8192) TAO_SOFTMAX_CHECK(1024, 2);
+        else                   TAO_SOFTMAX_CHECK_Q(1024, 0, false);
+#undef TAO_SOFTMAX_CHECK
+#undef TAO_SOFTMAX_CHECK_Q
     } else {
         // nothing to examine: an empty partial, so that the profile reports n = 0
-        hipLaunchKernelGGL((softmax_check<64, 1>), dim3(1), dim3(kCheckThreads), 0, st, x, y_ref, claimed, 0L, 1L, 1L,
-                           0, k, alpha, eps_rel, w.hist, w.coarse, w.stats);
+        hipLaunchKernelGGL((softmax_check<64, 1, false, false>), dim3(1), dim3(kCheckThreads), 0, st, x, y_ref, claimed, 0L, 1L, 1L,
+                           k, alpha, eps_rel, w.hist, w.coarse, w.stats);
     }
     launch_profile_reduce(w, nblocks, (unsigned long long)n, out, st);
     return launch_status();

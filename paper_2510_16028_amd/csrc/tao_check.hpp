@@ -92,6 +92,64 @@ __device__ __forceinline__ void check_one(float c, float r, float t, double alph
     atomicAdd(&hist[o.bin * R + rep], 1u);
 }
 
+// Quick settlement of an element in binary32.  The check's results do not need the error of every element to the
+// last bit: the histogram takes its leading 11 bits, the maximum is one element's, and a violation is a comparison.  A
+// binary32 estimate of the error (relative error below 2^-21: a subtraction, an addition, v_rcp_f32 and a
+// product) and a lower estimate of alpha tau therefore decide, unless the estimate lies within 16 steps of an edge of
+// its bin, might exceed the largest error the workgroup has seen exactly so far, is not clearly below alpha tau, or
+// is no ordinary number; such elements (about one in 2^15, and the first ones) take check_arith, so the results are
+// the same bit for bit.  About 18 instructions instead of 35, a dozen of them a binary64 division.
+struct QuickCheck {
+    float alpha, eps;
+    __device__ __forceinline__ QuickCheck(double a, double e)
+        : alpha((float)(fmin(a, 1e30) * (1.0 - 0x1p-18))), eps(e >= 0x1p-60 && e <= 0x1p60 ? (float)e : INFINITY) {}   // (an infinite eps settles nothing)
+};
+// at <= alpha tau (1 + 2^-18), positive or zero (NaN settles nothing); known: bits of an error that occurs.  bin: the error's bin.
+__device__ __forceinline__ bool quick_settled(float c, float r, float at, const QuickCheck& q, unsigned known, unsigned& bin) {
+    const float d = fabsf(c - r);
+    const float den = fabsf(r) + q.eps;
+    const unsigned bits = __float_as_uint(d * __builtin_amdgcn_rcpf(den));
+    bin = bits >> 20;
+    const bool zero = d == 0.f;                              // exactly: c == r
+    const unsigned t = bits + 16u;
+    const float lhs = zero ? 0.f : fmaf(d, 1.f + 0x1p-16f, 0x1p-90f);     // (a bound near the subnormal range settles nothing)
+    return lhs <= at && den <= 0x1p100f && (zero || ((t & 0xfffffu) >= 32u && t <= known));
+}
+typedef float floatv4 __attribute__((ext_vector_type(4)));      // (indexed by a variable it stays in registers)
+// Four elements: settled together or checked exactly, with tau(i) the binary32 bound of element i.  largest: the
+// workgroup's largest exactly computed error (LDS), known: this thread's copy, no newer than it needs to be.  WIDE: the
+// exact way takes the four side by side, for kernels that have the registers (small tensors see little else);
+// otherwise one after the other in a loop, as four binary64 divisions would set the kernel's register count.
+template <bool WIDE, int R = kReplicas, class Tau>
+__device__ __forceinline__ void quick_check_four(floatv4 c, floatv4 r, floatv4 at, Tau&& tau,
+                                                 const QuickCheck& q, double alpha, double eps_rel, unsigned int* hist, int rep,
+                                                 ThreadAcc& acc, unsigned int* largest, unsigned& known) {
+    if (known) {
+        unsigned bin[4];
+        bool ok = true;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) ok &= quick_settled(c[i], r[i], at[i], q, known, bin[i]);
+        if (ok) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) atomicAdd(&hist[bin[i] * R + rep], 1u);
+            return;
+        }
+    }
+    if (WIDE) {
+        const float c4[4] = {c[0], c[1], c[2], c[3]}, r4[4] = {r[0], r[1], r[2], r[3]};
+        const float t4[4] = {tau(0), tau(1), tau(2), tau(3)};
+        check_four<R>(c4, r4, t4, alpha, eps_rel, hist, rep, acc);
+    } else {
+#pragma unroll 1
+        for (int i = 0; i < 4; ++i) check_one<R>(c[i], r[i], tau(i), alpha, eps_rel, hist, rep, acc);
+    }
+    if (acc.max_bits > known) atomicMax(largest, acc.max_bits);
+    known = max(known, acc.max_bits);
+}
+__device__ __forceinline__ unsigned newest(unsigned int* largest) {
+    return __hip_atomic_load(largest, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
 // Workgroup totals of the per-thread counters (kCheckThreads threads) into ws_stats[blockIdx.x];
 // red: 3 * (kCheckThreads / kWave) words of LDS.  Contains one barrier.
 __device__ __forceinline__ void flush_block_stats(const ThreadAcc& acc, unsigned int* red, BlockStats* __restrict__ ws_stats) {

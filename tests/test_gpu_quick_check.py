@@ -1,0 +1,50 @@
+"""Quick settlement of the check (binary32 estimates, exact arithmetic only where they do not decide): the profile of the
+one-pass softmax check against bound and streaming check on the CPU's own arithmetic, field for field, with errors on bin
+edges, bounds just met and just missed, masked halves, and values no estimate can settle."""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def tao():
+    import paper_2510_16028_amd as t
+    t.lib()
+    assert torch.cuda.is_available()
+    return t
+
+
+def _claims(y, tau, g):
+    """Claims around y: equal, off by powers of two of y and of the bound (errors on and next to bin edges), at the bound."""
+    yd, td = y.double(), tau.double()
+    pick = torch.randint(0, 8, y.shape, generator=g, device=y.device)
+    k = torch.randint(-30, -16, y.shape, generator=g, device=y.device).double()
+    edge = yd * (1 + torch.exp2(k) * (1 + torch.randint(0, 8, y.shape, generator=g, device=y.device) / 8))
+    noise = yd + td * (2 * torch.rand(y.shape, generator=g, device=y.device, dtype=torch.float64) - 1) * 0.9
+    c = torch.where(pick < 3, noise, torch.where(pick < 5, edge, torch.where(pick == 5, yd + td, torch.where(pick == 6, yd + 1.000001 * td, yd))))
+    return c.float()
+
+
+# both sides of the rules on rows (four per row group), row lengths (wavefront, wide group) and whole vectors
+@pytest.mark.parametrize("rows,cols", [(16384, 128), (16383, 200), (16384, 511), (16384, 1024), (16385, 1021), (16384, 1028),
+                                       (16384, 2048), (16384, 1500), (4096, 1030), (4096, 2046), (2048, 4096), (1024, 8190)])
+@pytest.mark.parametrize("alpha,eps_rel", [(1.0, 1e-12), (2.0, 0.0)])
+def test_profile_equals_bound_and_streaming_check(tao, rows, cols, alpha, eps_rel):
+    g = torch.Generator(device="cuda").manual_seed(rows + cols)
+    x = torch.randn((rows, cols), generator=g, device="cuda")
+    if cols % 2 == 0:
+        x.masked_fill_(torch.arange(cols, device="cuda")[None] > torch.arange(rows, device="cuda")[:, None] % cols, float("-inf"))
+        x[::5] = x[::5].clamp(min=-3.0e38)                   # masks of (nearly) the lowest finite value as well
+    y = torch.softmax(x, -1)
+    tau = tao.tao_bound_softmax(x, y)
+    c = _claims(y, tau, g)
+    c[3, 5] = float("nan"); c[rows - 1, cols - 1] = float("inf"); y[7, 1] = 0.0; c[7, 1] = 1e-40; x[11, 2] = float("nan")
+    tau = tao.tao_bound_softmax(x, y)
+    want = tao.tao_check_and_profile(c, y, tau, alpha=alpha, eps_rel=eps_rel)
+    got = tao.tao_bound_check_softmax(x, y, c, alpha=alpha, eps_rel=eps_rel)
+    assert set(got) == set(want)
+    for key in want:
+        a, b = np.asarray(got[key]), np.asarray(want[key])
+        assert np.array_equal(a, b, equal_nan=a.dtype.kind == "f"), key
