@@ -4,14 +4,23 @@
 //   project_empirical  (ii) cap the k-th smallest magnitude by the cap curve of Sec. 4.2 at rank
 //                      (k - 1/2)/n, after a running maximum over k, and put sign and place back.
 //
-// (ii) needs every element's rank, i.e. a stable sort of the magnitudes.  The sort is a
-// least-significant-digit radix sort of the 31 magnitude bits (a non-negative binary32 orders like
+// (ii) needs an element's rank, i.e. a stable sort of the magnitudes, but only where its cap may bind.  A
+// histogram over the leading 11 bits (eight bins to an octave) gives the first rank of every bin;
+// caps do not decrease with the rank, so a bin whose largest magnitude stays within the cap of its first rank
+// needs no ranks at all.  The elements of the other bins, the candidates, are sorted; a candidate's rank is
+// its place among them plus the number of others in lower bins.  With a heavy upper tail over a calibrated
+// threshold that is a tenth of the tensor; where every bin is a candidate the histogram is the only extra work.
+// (8.4 M elements: none capped 257 -> 77 us, a heavy tail against calibrated thresholds 260 -> 106 us, all capped 343 -> 355 us;
+// 67 M: 1608 -> 343, 1629 -> 376, 2405 -> 2479 us.)  What bounds it now: three passes over delta and some fifteen launches.
+// The sort is a least-significant-digit radix sort of the 31 magnitude bits (a non-negative binary32 orders like
 // its bit pattern, NaN above infinity) in four 8-bit passes; the payload is the element's index
-// with its sign bit on top.  Per pass: count (digit histogram per tile), scan (of the digit-major
-// counter array), scatter (stable rank inside the tile by wave-wide digit matching, elements
+// with its sign bit on top.  Per pass: count (digit histogram per tile), scan (of each digit's counters over
+// the tiles; the digits' own totals are scanned by every workgroup of the next kernel), scatter (stable
+// rank inside the tile by wave-wide digit matching, elements
 // reordered in LDS so that runs of one digit leave as contiguous writes).  The first pass reads
-// delta itself (its count kernel copies it to out when the two differ); the last pass writes no sorted array at
-// all: the destination of an element IS its rank, so the cap is evaluated there and only the
+// delta itself and drops what is no candidate (its count kernel copies delta to out when the two differ); the last
+// pass writes no sorted array at
+// all: the destination of an element gives its rank, so the cap is evaluated there and only the
 // elements that exceed their cap are written, straight to out[index] -- the one access of the
 // whole path that is random, 4 bytes per 64-byte line, and therefore kept to the elements that
 // need it.
@@ -31,7 +40,9 @@ constexpr int kSortWaves = kSortThreads / kWave;
 constexpr int kSortItems = 16;                                // per thread
 constexpr int kSortTile = kSortThreads * kSortItems;          // 4096 elements per workgroup
 constexpr int kRadix = 256;
-constexpr int kScanChunk = kSortThreads * 16;                 // counters per scan workgroup
+constexpr int kScanChunk = kSortThreads * 16;                 // counters per step of a scan
+constexpr int kMagBins = 2048;                                // bins of the leading 11 magnitude bits
+constexpr int kMagShift = 20;
 constexpr int kXcds = 8;
 constexpr int kCountCopies = 4;                               // histogram copies per wave in radix_count
 constexpr int kCountStride = kRadix + 4;                      // copy c of digit d in LDS bank (d + 4c) % 32
@@ -115,9 +126,46 @@ __device__ __forceinline__ void build_cap_table(const float* __restrict__ thr, d
     __syncthreads();
 }
 
+// The magnitudes' histogram and what follows from it (in the workspace).
+struct MagTable {
+    unsigned count[kMagBins];
+    unsigned others_below[kMagBins];       // elements of lower bins that are no candidates
+    unsigned flag[kMagBins / 32];          // one bit per bin: candidates
+    unsigned candidates;
+    unsigned digit_total[kRadix];          // of the pass under way
+};
+
 __global__ void __launch_bounds__(kWave) cap_table_kernel(const float* __restrict__ thr, double alpha, long n,
-                                                          CapTable* __restrict__ tab) {
+                                                          CapTable* __restrict__ tab, MagTable* __restrict__ mag) {
+    for (int i = threadIdx.x; i < kMagBins; i += kWave) mag->count[i] = 0;
     build_cap_table(thr, alpha, n, tab);
+}
+
+// Histogram of the leading magnitude bits: 4 bytes per element read, one set of integer atomics per workgroup.
+__global__ void __launch_bounds__(1024) magnitude_bins(const float* __restrict__ delta, long n, int vec_ok, MagTable* __restrict__ mag) {
+    constexpr int kCopies = 4;
+    __shared__ unsigned cnt[kMagBins * kCopies];
+    for (int i = threadIdx.x; i < kMagBins * kCopies; i += 1024) cnt[i] = 0;
+    __syncthreads();
+    const int copy = threadIdx.x & (kCopies - 1);
+    const unsigned* src = reinterpret_cast<const unsigned*>(delta);
+    auto add = [&](unsigned v) __attribute__((always_inline)) { atomicAdd(&cnt[((v & 0x7fffffffu) >> kMagShift) * kCopies + copy], 1u); };
+    const long nvec = vec_ok ? n >> 2 : 0, stride = (long)gridDim.x * 1024;
+    long i = (long)blockIdx.x * 1024 + threadIdx.x;
+    for (; i + stride < nvec; i += 2 * stride) {
+        const uint4 a = reinterpret_cast<const uint4*>(src)[i], b = reinterpret_cast<const uint4*>(src)[i + stride];
+        add(a.x); add(a.y); add(a.z); add(a.w);
+        add(b.x); add(b.y); add(b.z); add(b.w);
+    }
+    if (i < nvec) { const uint4 a = reinterpret_cast<const uint4*>(src)[i]; add(a.x); add(a.y); add(a.z); add(a.w); }
+    for (long e = (nvec << 2) + (long)blockIdx.x * 1024 + threadIdx.x; e < n; e += stride) add(src[e]);
+    __syncthreads();
+    for (int b = threadIdx.x; b < kMagBins; b += 1024) {
+        unsigned t = 0;
+#pragma unroll
+        for (int c = 0; c < kCopies; ++c) t += cnt[b * kCopies + c];
+        if (t) atomicAdd(&mag->count[b], t);
+    }
 }
 
 // ---- (i) -------------------------------------------------------------------------------------
@@ -144,23 +192,27 @@ __global__ void __launch_bounds__(256) project_clip_kernel(const float* __restri
 
 // ---- (ii): radix sort passes --------------------------------------------------------------------
 
+// What a pass works on: all of the tensor in the first one, then the candidates.  Few candidates take tiles of a
+// quarter or half the size: some 768 tiles, to fill the chip, but no more than the tensor's own (the grid and the
+// counters are sized for those).
+struct PassShape { long n; int items; long tiles; };           // elements, elements per thread, tiles
+template <bool FIRST>
+__device__ __forceinline__ PassShape pass_shape(long all, const MagTable* __restrict__ mag) {
+    PassShape p = {all, kSortItems, 0};
+    if (!FIRST) {
+        p.n = (long)mag->candidates;
+        p.items = p.n <= 768L * kSortThreads * 4 && p.n * 4 <= all ? 4 : p.n <= 768L * kSortThreads * 8 && p.n * 2 <= all ? 8 : kSortItems;
+    }
+    const int tile = p.items * kSortThreads;
+    p.tiles = (p.n + tile - 1) / tile;
+    return p;
+}
+
 // Workgroups are dealt round-robin to the eight XCDs; giving XCD x the x-th contiguous eighth of
 // the tiles keeps the counter cache lines that neighbouring tiles share inside one L2.
 __device__ __forceinline__ long tile_of_block(long tiles_per_xcd) {
-    return (long)(blockIdx.x % kXcds) * tiles_per_xcd + blockIdx.x / kXcds;
-}
-
-template <bool FIRST>
-__device__ __forceinline__ void load_item(const float* delta, const unsigned* __restrict__ keys,
-                                          const unsigned* __restrict__ vals, long e, unsigned& key, unsigned& val) {
-    if (FIRST) {
-        const unsigned b = __float_as_uint(delta[e]);
-        key = b & 0x7fffffffu;
-        val = (unsigned)e | (b & 0x80000000u);
-    } else {
-        key = keys[e];
-        val = vals[e];
-    }
+    const long i = blockIdx.x / kXcds;                         // (the grid is sized for the whole tensor: -1 beyond a pass's tiles)
+    return i < tiles_per_xcd ? (long)(blockIdx.x % kXcds) * tiles_per_xcd + i : -1;
 }
 
 // Digit histogram of every tile: hist[digit * tiles + tile].  Counting does not depend on the
@@ -168,22 +220,31 @@ __device__ __forceinline__ void load_item(const float* delta, const unsigned* __
 // issued before the first is used).  The first pass also copies delta to out on the way.
 template <bool FIRST>
 __global__ void __launch_bounds__(kSortThreads) radix_count(const float* delta, const unsigned* __restrict__ keys,
-                                                            long n, long tiles, long tiles_per_xcd, int shift, int vec_ok,
+                                                            long all, int shift, int vec_ok, const MagTable* __restrict__ mag,
                                                             unsigned* __restrict__ hist, unsigned* copy_to) {
     __shared__ unsigned cnt[kSortWaves][kCountCopies][kCountStride];
-    const long tile = tile_of_block(tiles_per_xcd);
-    if (tile >= tiles) return;                                 // whole workgroup
+    __shared__ unsigned flag[FIRST ? kMagBins / 32 : 1];
+    const PassShape shape = pass_shape<FIRST>(all, mag);
+    const long n = shape.n, tiles = shape.tiles;
+    const int items = FIRST ? kSortItems : shape.items;
+    const long tile = tile_of_block((tiles + kXcds - 1) / kXcds);
+    if (tile < 0 || tile >= tiles) return;                     // whole workgroup
+    if (FIRST) {
+        if (threadIdx.x < kMagBins / 32) flag[threadIdx.x] = mag->flag[threadIdx.x];
+        __syncthreads();
+    }
     const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
     for (int d = lane; d < kCountCopies * kCountStride; d += kWave) (&cnt[wave][0][0])[d] = 0;
     __builtin_amdgcn_wave_barrier();
     const unsigned* src = FIRST ? reinterpret_cast<const unsigned*>(delta) : keys;
-    const long tile_base = tile * kSortTile;
+    const long tile_base = tile * (items * kSortThreads);
     unsigned key[kSortItems];
-    const bool full = tile_base + kSortTile <= n;
+    const bool full = tile_base + items * kSortThreads <= n;
     if (full && vec_ok) {
 #pragma unroll
         for (int q = 0; q < kSortItems / 4; ++q) {
             const long e = tile_base + ((long)q * kSortThreads + threadIdx.x) * 4;
+            if (4 * q >= items) continue;
             const uint4 v = *reinterpret_cast<const uint4*>(src + e);
             if (FIRST && copy_to) *reinterpret_cast<uint4*>(copy_to + e) = v;
             key[4 * q] = v.x; key[4 * q + 1] = v.y; key[4 * q + 2] = v.z; key[4 * q + 3] = v.w;
@@ -192,29 +253,36 @@ __global__ void __launch_bounds__(kSortThreads) radix_count(const float* delta, 
 #pragma unroll
         for (int i = 0; i < kSortItems; ++i) {
             const long e = tile_base + (long)i * kSortThreads + threadIdx.x;
-            key[i] = e < n ? src[e] : 0u;
+            key[i] = i < items && e < n ? src[e] : 0u;
             if (FIRST && copy_to && e < n) copy_to[e] = key[i];
         }
     }
 #pragma unroll
     for (int i = 0; i < kSortItems; ++i) {
-        // element index of key[i] in the scalar layout (the vector layout is only used on full tiles)
-        const bool valid = full || tile_base + (long)i * kSortThreads + threadIdx.x < n;
-        const unsigned d = ((FIRST ? key[i] & 0x7fffffffu : key[i]) >> shift) & (kRadix - 1);
-        // A wave whose valid lanes all hold one digit (the rule in the top byte of narrow data) adds
-        // once.  Otherwise LDS atomics, spread over eight copies of the histogram chosen by the lane
-        // (a few distinct digits per wave -- exponent bytes, trailing zero bytes of deviations that are
-        // differences of nearby values -- would serialise 64 atomics on a handful of addresses); the
-        // copies are 260 counters apart, so equal digits of different copies fall into different banks.
-        const unsigned long long vmask = __ballot(valid);
-        if (vmask == 0) continue;
-        const unsigned d0 = __shfl(d, (int)__builtin_ctzll(vmask), kWave);
-        if (__ballot(valid && d == d0) == vmask) {
-            if (lane == (int)__builtin_ctzll(vmask)) cnt[wave][0][d0] += (unsigned)__popcll(vmask);
-        } else if (valid) {
-            atomicAdd(&cnt[wave][lane & (kCountCopies - 1)][d], 1u);
+        if (i < items) {
+            // element index of key[i] in the scalar layout (the vector layout is only used on full tiles)
+            bool valid = full || tile_base + (long)i * kSortThreads + threadIdx.x < n;
+            if (FIRST) {
+                const unsigned bin = (key[i] & 0x7fffffffu) >> kMagShift;
+                valid = valid && ((flag[bin >> 5] >> (bin & 31)) & 1u);
+            }
+            const unsigned d = ((FIRST ? key[i] & 0x7fffffffu : key[i]) >> shift) & (kRadix - 1);
+            // A wave whose valid lanes all hold one digit (the rule in the top byte of narrow data) adds
+            // once.  Otherwise LDS atomics, spread over eight copies of the histogram chosen by the lane
+            // (a few distinct digits per wave -- exponent bytes, trailing zero bytes of deviations that are
+            // differences of nearby values -- would serialise 64 atomics on a handful of addresses); the
+            // copies are 260 counters apart, so equal digits of different copies fall into different banks.
+            const unsigned long long vmask = __ballot(valid);
+            if (vmask != 0) {
+                const unsigned d0 = __shfl(d, (int)__builtin_ctzll(vmask), kWave);
+                if (__ballot(valid && d == d0) == vmask) {
+                    if (lane == (int)__builtin_ctzll(vmask)) cnt[wave][0][d0] += (unsigned)__popcll(vmask);
+                } else if (valid) {
+                    atomicAdd(&cnt[wave][lane & (kCountCopies - 1)][d], 1u);
+                }
+            }
+            __builtin_amdgcn_wave_barrier();
         }
-        __builtin_amdgcn_wave_barrier();
     }
     __syncthreads();
     const int d = threadIdx.x;                                 // kSortThreads == kRadix
@@ -246,67 +314,63 @@ __device__ __forceinline__ unsigned block_exclusive_scan(unsigned v, unsigned* w
     return before + inc - v;
 }
 
-__global__ void __launch_bounds__(kSortThreads) scan_chunk_sums(const unsigned* __restrict__ c, long count,
-                                                                unsigned* __restrict__ sums) {
-    __shared__ unsigned wave_tot[kSortWaves];
-    const long base = (long)blockIdx.x * kScanChunk;
-    unsigned s = 0;
-    for (int i = threadIdx.x; i < kScanChunk; i += kSortThreads) {
-        const long e = base + i;
-        if (e < count) s += c[e];
-    }
+// First rank of every bin, the bins whose elements may exceed their caps, and the numbers that lead from a
+// candidate's place to its rank.  One workgroup; thread t has bins 2 t and 2 t + 1.
+__global__ void __launch_bounds__(1024) find_candidates(const CapTable* __restrict__ tab, MagTable* __restrict__ mag) {
+    static_assert(kMagBins == 2 * 1024, "two bins per thread");
+    __shared__ unsigned wave_tot[1024 / kWave];
+    const int t = threadIdx.x;
+    const unsigned n0 = mag->count[2 * t], n1 = mag->count[2 * t + 1];
     unsigned total;
-    block_exclusive_scan(s, wave_tot, total);
-    if (threadIdx.x == 0) sums[blockIdx.x] = total;
+    const unsigned first0 = block_exclusive_scan(n0 + n1, wave_tot, total), first1 = first0 + n0;
+    auto candidate = [&](unsigned bin, unsigned count, unsigned first) {
+        if (count == 0 || bin >= (0x7f800000u >> kMagShift) + 1u) return false;        // (NaN stays whatever its rank)
+        const float top = bin == (0x7f800000u >> kMagShift) ? INFINITY : __uint_as_float(((bin + 1u) << kMagShift) - 1u);
+        const double r = rank_percent((double)first + 1.0, tab->n);
+        const CapSeg sg = tab->seg[segment_of(r)];
+        return !((double)top <= fmax(sg.head, cap_in_segment(sg, r)));
+    };
+    const bool c0 = candidate(2 * t, n0, first0), c1 = candidate(2 * t + 1, n1, first1);
+    const unsigned o0 = c0 ? 0u : n0, o1 = c1 ? 0u : n1;
+    const unsigned below = block_exclusive_scan(o0 + o1, wave_tot, total);
+    mag->others_below[2 * t] = below;
+    mag->others_below[2 * t + 1] = below + o0;
+    if (t == 0) mag->candidates = (unsigned)((long)tab->n) - total;
+    // thread pairs of 16 threads make a word of flags
+    unsigned bits = (unsigned)c0 | ((unsigned)c1 << 1);
+    bits <<= 2 * (t & 15);
+#pragma unroll
+    for (int o = 1; o < 16; o <<= 1) bits |= __shfl_xor(bits, o, kWave);
+    if ((t & 15) == 0) mag->flag[t >> 4] = bits;
 }
 
-__global__ void __launch_bounds__(1024) scan_spine(unsigned* __restrict__ sums, long chunks) {
-    __shared__ unsigned wave_tot[1024 / kWave];
+// Exclusive scan of one digit's counters over the tiles; workgroup d has digit d.
+template <bool FIRST>
+__global__ void __launch_bounds__(kSortThreads) scan_digit(unsigned* __restrict__ hist, long n, MagTable* __restrict__ mag) {
+    __shared__ unsigned wave_tot[kSortWaves];
+    const long tiles = pass_shape<FIRST>(n, mag).tiles;
+    unsigned* c = hist + (long)blockIdx.x * tiles;
     unsigned carry = 0;
-    for (long base = 0; base < chunks; base += 1024) {          // uniform trip count
-        const long e = base + threadIdx.x;
-        const unsigned v = e < chunks ? sums[e] : 0u;
+    for (long base = 0; base < tiles; base += kScanChunk) {     // uniform trip count
+        // 16 consecutive counters per thread (several steps), or one
+        const bool few = tiles <= kSortThreads;
+        const long e0 = base + (few ? (long)threadIdx.x : (long)threadIdx.x * 16);
+        unsigned v[16], s = 0;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            v[i] = (!few || i == 0) && e0 + i < tiles ? c[e0 + i] : 0u;
+            s += v[i];
+        }
         unsigned total;
-        const unsigned ex = block_exclusive_scan(v, wave_tot, total);
-        if (e < chunks) sums[e] = carry + ex;
+        unsigned run = carry + block_exclusive_scan(s, wave_tot, total);
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            if ((!few || i == 0) && e0 + i < tiles) c[e0 + i] = run;
+            run += v[i];
+        }
         carry += total;
     }
-}
-
-__global__ void __launch_bounds__(kSortThreads) scan_apply(unsigned* __restrict__ c, long count,
-                                                           const unsigned* __restrict__ sums) {
-    __shared__ unsigned wave_tot[kSortWaves];
-    // thread t owns 16 consecutive counters (the array is 256-byte aligned and chunks start at
-    // multiples of 4096 counters): local sequential scan between two block scans
-    const long base = (long)blockIdx.x * kScanChunk + (long)threadIdx.x * 16;
-    unsigned v[16];
-    unsigned s = 0;
-    const bool whole = base + 16 <= count;
-    if (whole) {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const uint4 t = *reinterpret_cast<const uint4*>(c + base + 4 * q);
-            v[4 * q] = t.x; v[4 * q + 1] = t.y; v[4 * q + 2] = t.z; v[4 * q + 3] = t.w;
-        }
-    } else {
-#pragma unroll
-        for (int i = 0; i < 16; ++i) v[i] = base + i < count ? c[base + i] : 0u;
-    }
-#pragma unroll
-    for (int i = 0; i < 16; ++i) s += v[i];
-    unsigned total;
-    unsigned run = block_exclusive_scan(s, wave_tot, total) + sums[blockIdx.x];
-#pragma unroll
-    for (int i = 0; i < 16; ++i) { const unsigned t = v[i]; v[i] = run; run += t; }
-    if (whole) {
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-            *reinterpret_cast<uint4*>(c + base + 4 * q) = make_uint4(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]);
-    } else {
-#pragma unroll
-        for (int i = 0; i < 16; ++i)
-            if (base + i < count) c[base + i] = v[i];
-    }
+    if (threadIdx.x == 0) mag->digit_total[blockIdx.x] = carry;
 }
 
 // LDS of one tile's pass.
@@ -319,16 +383,16 @@ struct TileSort {
     unsigned wave_tot[kSortWaves];
 };
 
-// One stable counting-sort step of a tile on the digit at `shift`: element i of lane l of wave w is
-// the tile's element w * 1024 + i * 64 + l (`valid_count` of them exist); on return sh.skey / sh.sval
+// One stable counting-sort step of a tile on the digit at `shift`: with `items` elements per thread, element i of
+// lane l of wave w is the tile's element (w * items + i) * 64 + l (`valid_count` of them exist); on return sh.skey / sh.sval
 // hold the tile ordered by digit, equal digits in their old order, and sh.tile_excl the start of
 // every digit's run.  All threads of the workgroup call it; it ends with a barrier.
 __device__ __forceinline__ void tile_sort_step(TileSort& sh, const unsigned (&key)[kSortItems],
-                                               const unsigned (&val)[kSortItems], int valid_count, int shift) {
+                                               const unsigned (&val)[kSortItems], int items, int valid_count, int shift) {
     const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
     for (int d = lane; d < kRadix; d += kWave) sh.cnt[wave][d] = 0;
     __builtin_amdgcn_wave_barrier();
-    const int first = wave * (kSortItems * kWave) + lane;
+    const int first = wave * (items * kWave) + lane;
     unsigned short rank[kSortItems];
     // Stable rank of every element among those of its wave with the same digit: the elements of a
     // wave are ordered by (i, lane), which is their order in memory.  Eight ballots find the lanes
@@ -336,21 +400,23 @@ __device__ __forceinline__ void tile_sort_step(TileSort& sh, const unsigned (&ke
     const unsigned long long lanes_below = (1ull << lane) - 1ull;
 #pragma unroll
     for (int i = 0; i < kSortItems; ++i) {
-        const bool valid = first + i * kWave < valid_count;
-        const unsigned d = (key[i] >> shift) & (kRadix - 1);
-        unsigned long long same = __ballot(valid);
-#pragma unroll
-        for (int b = 0; b < 8; ++b) {
-            const bool bit = (d >> b) & 1u;
-            const unsigned long long bal = __ballot(bit);
-            same &= bit ? bal : ~bal;
+        if (i < items) {                                       // (uniform)
+            const bool valid = first + i * kWave < valid_count;
+            const unsigned d = (key[i] >> shift) & (kRadix - 1);
+            unsigned long long same = __ballot(valid);
+    #pragma unroll
+            for (int b = 0; b < 8; ++b) {
+                const bool bit = (d >> b) & 1u;
+                const unsigned long long bal = __ballot(bit);
+                same &= bit ? bal : ~bal;
+            }
+            const unsigned prev = valid ? sh.cnt[wave][d] : 0u;
+            const unsigned r = prev + (unsigned)__popcll(same & lanes_below);
+            __builtin_amdgcn_wave_barrier();                       // all reads of this round before its writes
+            if (valid && (same & lanes_below) == 0) sh.cnt[wave][d] = prev + (unsigned)__popcll(same);
+            rank[i] = (unsigned short)r;
+            __builtin_amdgcn_wave_barrier();
         }
-        const unsigned prev = valid ? sh.cnt[wave][d] : 0u;
-        const unsigned r = prev + (unsigned)__popcll(same & lanes_below);
-        __builtin_amdgcn_wave_barrier();                       // all reads of this round before its writes
-        if (valid && (same & lanes_below) == 0) sh.cnt[wave][d] = prev + (unsigned)__popcll(same);
-        rank[i] = (unsigned short)r;
-        __builtin_amdgcn_wave_barrier();
     }
     __syncthreads();
     {   // per digit: offsets of the waves inside the digit's run, the run's place in the tile
@@ -364,7 +430,7 @@ __device__ __forceinline__ void tile_sort_step(TileSort& sh, const unsigned (&ke
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < kSortItems; ++i) {
-        if (first + i * kWave < valid_count) {
+        if (i < items && first + i * kWave < valid_count) {
             const unsigned d = (key[i] >> shift) & (kRadix - 1);
             const unsigned pos = sh.tile_excl[d] + sh.cnt[wave][d] + rank[i];
             if (pos < (unsigned)kSortTile) { sh.skey[pos] = key[i]; sh.sval[pos] = val[i]; }
@@ -401,20 +467,22 @@ __device__ __forceinline__ void cap_and_store(const CapTable& tab, unsigned rank
     out[idx] = __uint_as_float(__float_as_uint(star) | (v & 0x80000000u));
 }
 
-// Scatter pass.  `hist` holds the scanned counters: hist[d * tiles + tile] is the destination of
-// the tile's first element with digit d.
+// Scatter pass.  `hist` holds the scanned counters: hist[d * tiles + tile] elements with digit d lie in the tiles before.
+// The first pass closes up the tile's candidates in LDS, in order, and sorts those.
 template <bool FIRST, bool LAST>
-__global__ void __launch_bounds__(kSortThreads) radix_scatter(const float* delta,
+__global__ void __launch_bounds__(kSortThreads, LAST ? 3 : 4) radix_scatter(const float* delta,
                                                               const unsigned* __restrict__ keys_in, const unsigned* __restrict__ vals_in,
                                                               unsigned* __restrict__ keys_out, unsigned* __restrict__ vals_out,
-                                                              long n, long tiles, long tiles_per_xcd, int shift,
-                                                              const unsigned* __restrict__ hist,
-                                                              const CapTable* __restrict__ tab, float* out) {
+                                                              long total, int shift, const unsigned* __restrict__ hist,
+                                                              const MagTable* __restrict__ mag, const CapTable* __restrict__ tab, float* out) {
     __shared__ TileSort sh;
     __shared__ CapTable stab;                                  // LAST: the cap table, read per element
     __shared__ double run_cap[LAST ? kRadix : 1];
-    const long tile = tile_of_block(tiles_per_xcd);
-    if (tile >= tiles) return;                                 // whole workgroup
+    __shared__ unsigned flag[FIRST ? kMagBins / 32 : 1];
+    const PassShape shape = pass_shape<FIRST>(total, mag);
+    const long n = shape.n, tiles = shape.tiles;
+    const long tile = tile_of_block((tiles + kXcds - 1) / kXcds);
+    if (tile < 0 || tile >= tiles) return;                     // whole workgroup
     if (LAST) {
         static_assert(sizeof(CapTable) % sizeof(double) == 0 && sizeof(CapTable) / sizeof(double) <= kSortThreads, "one double per thread");
         if (threadIdx.x < sizeof(CapTable) / sizeof(double))
@@ -422,43 +490,92 @@ __global__ void __launch_bounds__(kSortThreads) radix_scatter(const float* delta
         // visible after the barriers of the sort step
     }
     const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
-    const long tile_base = tile * kSortTile;
-    const long base = tile_base + (long)wave * (kSortItems * kWave) + lane;
+    int items = FIRST ? kSortItems : shape.items;
+    const long tile_base = tile * (items * kSortThreads);
+    const long base = tile_base + (long)wave * (items * kWave) + lane;
     const long left = n - tile_base;
-    const int tile_count = left < kSortTile ? (int)left : kSortTile;
+    int count = left < items * kSortThreads ? (int)left : items * kSortThreads;
 
     unsigned key[kSortItems], val[kSortItems];
+    if (FIRST) {
+        if (threadIdx.x < kMagBins / 32) flag[threadIdx.x] = mag->flag[threadIdx.x];
+        __syncthreads();
+        // every wavefront closes up its quarter of the tile in its quarter of the LDS arrays ...
+        const unsigned* src = reinterpret_cast<const unsigned*>(delta) + tile_base;
+        const unsigned long long lanes_below = (1ull << lane) - 1ull;
+        unsigned at = 0;
 #pragma unroll
-    for (int i = 0; i < kSortItems; ++i) {
-        const long e = base + (long)i * kWave;
-        key[i] = 0xffffffffu; val[i] = 0;
-        if (e < n) load_item<FIRST>(delta, keys_in, vals_in, e, key[i], val[i]);
+        for (int i = 0; i < kSortItems; ++i) {
+            const int e = wave * (kSortItems * kWave) + i * kWave + lane;
+            key[i] = e < count ? src[e] : 0xffffffffu;         // (a NaN: never a candidate)
+        }
+#pragma unroll
+        for (int i = 0; i < kSortItems; ++i) {
+            const int e = wave * (kSortItems * kWave) + i * kWave + lane;
+            const unsigned k = key[i] & 0x7fffffffu, bin = k >> kMagShift;
+            const bool c = e < count && ((flag[bin >> 5] >> (bin & 31)) & 1u);
+            const unsigned long long b = __ballot(c);
+            if (c) {
+                const unsigned pos = wave * (kSortItems * kWave) + at + (unsigned)__popcll(b & lanes_below);
+                sh.skey[pos] = k;
+                sh.sval[pos] = ((unsigned)tile_base + (unsigned)e) | (key[i] & 0x80000000u);
+            }
+            at += (unsigned)__popcll(b);
+        }
+        if (lane == 0) sh.wave_tot[wave] = at;
+        __syncthreads();
+        // ... and the workgroup takes the four pieces one after the other
+        const int p1 = (int)sh.wave_tot[0], p2 = p1 + (int)sh.wave_tot[1], p3 = p2 + (int)sh.wave_tot[2];
+        count = p3 + (int)sh.wave_tot[3];
+        items = (count + kSortThreads - 1) / kSortThreads;
+#pragma unroll
+        for (int i = 0; i < kSortItems; ++i) {
+            const int e = (wave * items + i) * kWave + lane;
+            key[i] = 0xffffffffu; val[i] = 0;
+            if (i < items && e < count) {
+                const int from = e < p1 ? e : e < p2 ? e - p1 + kSortItems * kWave : e < p3 ? e - p2 + 2 * kSortItems * kWave : e - p3 + 3 * kSortItems * kWave;
+                key[i] = sh.skey[from]; val[i] = sh.sval[from];
+            }
+        }
+        __syncthreads();                                       // (wave_tot and the tile are written again)
+    } else {
+#pragma unroll
+        for (int i = 0; i < kSortItems; ++i) {
+            const long e = base + (long)i * kWave;
+            key[i] = 0xffffffffu; val[i] = 0;
+            if (i < items && e < n) { key[i] = keys_in[e]; val[i] = vals_in[e]; }
+        }
     }
-    tile_sort_step(sh, key, val, tile_count, shift);
+    tile_sort_step(sh, key, val, items, count, shift);
     {
-        const unsigned first_dest = hist[(long)threadIdx.x * tiles + tile];                  // kSortThreads == kRadix
+        const unsigned digit_total = mag->digit_total[threadIdx.x];                              // kSortThreads == kRadix
+        unsigned sum;
+        const unsigned first_dest = block_exclusive_scan(digit_total, sh.wave_tot, sum) + hist[(long)threadIdx.x * tiles + tile];
         sh.dest_off[threadIdx.x] = first_dest - sh.tile_excl[threadIdx.x];
         if (LAST) {
-            // Caps do not decrease with the rank: the exact cap of the first rank this tile reaches
-            // with digit d is a lower bound for all its elements of that digit, and most elements are
-            // settled by one comparison with it.
-            const double r = rank_percent((double)first_dest + 1.0, stab.n);
+            // Caps do not decrease with the rank: the exact cap of a rank that all elements of this tile with digit d
+            // reach or exceed is a lower bound for theirs, and most elements are settled by one comparison with it.
+            static_assert(kMagShift >= 16 && kMagShift <= 24, "a digit of the last pass is a run of bins");
+            const unsigned low_bin = (unsigned)threadIdx.x << (24 - kMagShift);
+            const unsigned rank0 = first_dest + (low_bin < (unsigned)kMagBins ? mag->others_below[low_bin] : 0u);
+            const double r = rank_percent((double)rank0 + 1.0, stab.n);
             const CapSeg s = stab.seg[segment_of(r)];
-            run_cap[threadIdx.x] = (long)first_dest < n ? fmax(s.head, cap_in_segment(s, r)) : 0.0;
+            run_cap[threadIdx.x] = (long)rank0 < total ? fmax(s.head, cap_in_segment(s, r)) : 0.0;
         }
     }
     __syncthreads();
-    for (int j = threadIdx.x; j < tile_count; j += kSortThreads) {
+    for (int j = threadIdx.x; j < count; j += kSortThreads) {
         const unsigned k = sh.skey[j], v = sh.sval[j];
         const unsigned d = (k >> shift) & (kRadix - 1);
         const unsigned dest = sh.dest_off[d] + (unsigned)j;
-        if ((long)dest >= n) continue;                         // cannot happen with consistent counters
+        if ((long)dest >= total) continue;                     // cannot happen with consistent counters
         if (!LAST) {
             keys_out[dest] = k;
             vals_out[dest] = v;
         } else {
             if ((double)__uint_as_float(k) <= run_cap[d]) continue;
-            cap_and_store<false>(stab, dest, k, v, n, out);     // dest is the 0-based rank
+            const unsigned rank0 = dest + (n == total ? 0u : mag->others_below[min(k >> kMagShift, (unsigned)kMagBins - 1u)]);
+            cap_and_store<false>(stab, rank0, k, v, total, out);
         }
     }
 }
@@ -476,11 +593,15 @@ __global__ void __launch_bounds__(kSortThreads) project_one_tile(const float* de
     for (int i = 0; i < kSortItems; ++i) {
         const int e = first + i * kWave;
         key[i] = 0xffffffffu; val[i] = 0;
-        if (e < n) load_item<true>(delta, nullptr, nullptr, e, key[i], val[i]);
+        if (e < n) {
+            const unsigned b = __float_as_uint(delta[e]);
+            key[i] = b & 0x7fffffffu;
+            val[i] = (unsigned)e | (b & 0x80000000u);
+        }
     }
 #pragma unroll 1
     for (int pass = 0; pass < 4; ++pass) {
-        tile_sort_step(sh, key, val, n, 8 * pass);
+        tile_sort_step(sh, key, val, kSortItems, n, 8 * pass);
         if (pass < 3) {
 #pragma unroll
             for (int i = 0; i < kSortItems; ++i) {
@@ -496,8 +617,9 @@ __global__ void __launch_bounds__(kSortThreads) project_one_tile(const float* de
 
 struct ProjectWorkspace {
     CapTable* tab;
-    unsigned *hist, *sums, *keys_a, *vals_a, *keys_b, *vals_b;
-    long tiles, counters, chunks;
+    MagTable* mag;
+    unsigned *hist, *keys_a, *vals_a, *keys_b, *vals_b;
+    long tiles;
 };
 
 inline size_t round256(size_t b) { return (b + 255) / 256 * 256; }
@@ -505,18 +627,17 @@ inline size_t round256(size_t b) { return (b + 255) / 256 * 256; }
 inline size_t carve_project(long n, char* ws, ProjectWorkspace* w) {
     const long tiles = (n + kSortTile - 1) / kSortTile;
     const long counters = tiles * kRadix;
-    const long chunks = (counters + kScanChunk - 1) / kScanChunk;
     size_t off = 0;
     auto take = [&](size_t bytes) { char* p = ws ? ws + off : nullptr; off += round256(bytes); return p; };
     char* tab = take(sizeof(CapTable));
+    char* mag = take(sizeof(MagTable));
     char* hist = take((size_t)counters * 4);
-    char* sums = take((size_t)chunks * 4);
     char* ka = take((size_t)n * 4); char* va = take((size_t)n * 4);
     char* kb = take((size_t)n * 4); char* vb = take((size_t)n * 4);
     if (w) {
-        w->tab = (CapTable*)tab; w->hist = (unsigned*)hist; w->sums = (unsigned*)sums;
+        w->tab = (CapTable*)tab; w->mag = (MagTable*)mag; w->hist = (unsigned*)hist;
         w->keys_a = (unsigned*)ka; w->vals_a = (unsigned*)va; w->keys_b = (unsigned*)kb; w->vals_b = (unsigned*)vb;
-        w->tiles = tiles; w->counters = counters; w->chunks = chunks;
+        w->tiles = tiles;
     }
     return off;
 }
@@ -560,31 +681,29 @@ int tao_project_empirical(const float* delta, const float* thr_abs, double alpha
     ProjectWorkspace w;
     carve_project(n, (char*)ws, &w);
     hipStream_t st = (hipStream_t)stream;
-    hipLaunchKernelGGL(cap_table_kernel, dim3(1), dim3(kWave), 0, st, thr_abs, alpha, n, w.tab);
+    hipLaunchKernelGGL(cap_table_kernel, dim3(1), dim3(kWave), 0, st, thr_abs, alpha, n, w.tab, w.mag);
+    const int vec_in = aligned(delta, 16);
+    const long want = (n + 8191) / 8192;                        // two vectors per thread before another workgroup is worth it
+    hipLaunchKernelGGL(magnitude_bins, dim3((unsigned)(want < 256 ? want : 256)), dim3(1024), 0, st, delta, n, vec_in, w.mag);
+    hipLaunchKernelGGL(find_candidates, dim3(1), dim3(1024), 0, st, w.tab, w.mag);
 
     const long per_xcd = (w.tiles + kXcds - 1) / kXcds;
-    const dim3 grid((unsigned)(per_xcd * kXcds)), blk(kSortThreads);
-    const dim3 sgrid((unsigned)w.chunks);
+    const dim3 grid((unsigned)(per_xcd * kXcds)), blk(kSortThreads), digits(kRadix);
     unsigned* kin = nullptr; unsigned* vin = nullptr;
     unsigned* kout = w.keys_a; unsigned* vout = w.vals_a;
     for (int pass = 0; pass < 4; ++pass) {
         const int shift = 8 * pass;
-        if (pass == 0) hipLaunchKernelGGL((radix_count<true>), grid, blk, 0, st, delta, kin, n, w.tiles, per_xcd, shift,
-                                          (int)(aligned(delta, 16) && aligned(out, 16)), w.hist,
-                                          out != delta ? reinterpret_cast<unsigned*>(out) : nullptr);
-        else           hipLaunchKernelGGL((radix_count<false>), grid, blk, 0, st, delta, kin, n, w.tiles, per_xcd, shift, 1, w.hist, nullptr);
-        hipLaunchKernelGGL(scan_chunk_sums, sgrid, blk, 0, st, w.hist, w.counters, w.sums);
-        hipLaunchKernelGGL(scan_spine, dim3(1), dim3(1024), 0, st, w.sums, w.chunks);
-        hipLaunchKernelGGL(scan_apply, sgrid, blk, 0, st, w.hist, w.counters, w.sums);
-        if (pass == 0)
-            hipLaunchKernelGGL((radix_scatter<true, false>), grid, blk, 0, st, delta, kin, vin, kout, vout, n, w.tiles, per_xcd,
-                               shift, w.hist, w.tab, out);
-        else if (pass < 3)
-            hipLaunchKernelGGL((radix_scatter<false, false>), grid, blk, 0, st, delta, kin, vin, kout, vout, n, w.tiles, per_xcd,
-                               shift, w.hist, w.tab, out);
-        else
-            hipLaunchKernelGGL((radix_scatter<false, true>), grid, blk, 0, st, delta, kin, vin, kout, vout, n, w.tiles, per_xcd,
-                               shift, w.hist, w.tab, out);
+        if (pass == 0) {
+            hipLaunchKernelGGL((radix_count<true>), grid, blk, 0, st, delta, kin, n, shift, (int)(vec_in && aligned(out, 16)), w.mag,
+                               w.hist, out != delta ? reinterpret_cast<unsigned*>(out) : nullptr);
+            hipLaunchKernelGGL((scan_digit<true>), digits, blk, 0, st, w.hist, n, w.mag);
+            hipLaunchKernelGGL((radix_scatter<true, false>), grid, blk, 0, st, delta, kin, vin, kout, vout, n, shift, w.hist, w.mag, w.tab, out);
+        } else {
+            hipLaunchKernelGGL((radix_count<false>), grid, blk, 0, st, delta, kin, n, shift, 1, w.mag, w.hist, nullptr);
+            hipLaunchKernelGGL((scan_digit<false>), digits, blk, 0, st, w.hist, n, w.mag);
+            if (pass < 3) hipLaunchKernelGGL((radix_scatter<false, false>), grid, blk, 0, st, delta, kin, vin, kout, vout, n, shift, w.hist, w.mag, w.tab, out);
+            else          hipLaunchKernelGGL((radix_scatter<false, true>), grid, blk, 0, st, delta, kin, vin, kout, vout, n, shift, w.hist, w.mag, w.tab, out);
+        }
         kin = kout; vin = vout;
         kout = kin == w.keys_a ? w.keys_b : w.keys_a;
         vout = vin == w.vals_a ? w.vals_b : w.vals_a;

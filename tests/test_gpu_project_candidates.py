@@ -1,0 +1,48 @@
+"""The order-statistic projection where only some bins of magnitudes need ranks, bit for bit against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def tao():
+    import paper_2510_16028_amd as t
+    t.lib()
+    assert torch.cuda.is_available()
+    return t
+
+
+def _same(got, want):
+    nan = np.isnan(want)
+    return np.array_equal(np.isnan(got), nan) and np.array_equal(got.view(np.uint32)[~nan], want.view(np.uint32)[~nan])
+
+
+@pytest.mark.parametrize("n", [4097, 8191, 40000, 262145])
+@pytest.mark.parametrize("share", ["none", "few", "half", "all", "one bin"])
+def test_empirical_with_candidates_in_some_bins(tao, oracle_mod, n, share):
+    """Ranks only for the magnitudes whose cap may bind: no bin, the top bins, every other stretch, all bins, one bin."""
+    rng = np.random.Generator(np.random.Philox(n + len(share)))
+    d = (rng.standard_normal(n) * np.exp(rng.standard_normal(n)) * 1e-6).astype(np.float32)
+    if share == "one bin":
+        d = (np.sign(d) * np.float32(1.0 + 1e-3) * (1 + np.abs(d))).astype(np.float32)
+    d[rng.integers(0, n, n // 16)] = d[rng.integers(0, n, n // 16)]          # ties
+    d[:5] = [np.inf, -np.inf, np.nan, 0.0, -0.0]
+    P = [1] + list(range(5, 100, 5)) + [99, 100]
+    a = np.sort(np.abs(d[np.isfinite(d)]))
+    thr = np.array([a[min(len(a) - 1, int(len(a) * p / 100))] for p in P], np.float32)
+    if share == "none":
+        thr = (thr * 100).astype(np.float32)
+    elif share == "few":
+        thr = (thr * np.where(np.arange(22) < 18, 10, 0.5)).astype(np.float32)
+    elif share == "half":
+        thr = (thr * np.where(np.arange(22) % 4 < 2, 1.5, 0.7)).astype(np.float32)
+    else:
+        thr = (thr * 0.5).astype(np.float32)
+    want = oracle_mod.project_empirical(d, thr, 1.0)
+    x = torch.from_numpy(d).cuda()
+    got = tao.tao_project_empirical(x, torch.from_numpy(thr).cuda(), 1.0).cpu().numpy()
+    assert _same(got, want)
+    inplace = tao.tao_project_empirical(x, torch.from_numpy(thr).cuda(), 1.0, out=x).cpu().numpy()
+    assert _same(inplace, want)
