@@ -207,23 +207,25 @@ __device__ __forceinline__ void wide_group_max_or(float& m, int& flag, double* s
     }
 }
 
-// Four values of a row from column idx on, loaded without a branch: from clamped positions that exist; row_fill then
+// The four values of a thread's vector, loaded without a branch: from clamped positions that exist; row_fill then
 // replaces those at and beyond `limit`.  (Behind a test for the row's end every load waited for the one before it.)
-// FULL: 16-byte aligned rows of whole vectors.  last: the last position of a vector (FULL) or value.
-template <bool FULL, bool STREAM, class Idx>
+// FULL: 16-byte aligned rows of whole vectors, four consecutive columns from idx on.  Otherwise the columns idx,
+// idx + step, ...: with step the row group's size neighbouring threads read neighbouring columns.
+// last: the last position of a vector (FULL) or value.
+template <bool FULL, bool STREAM, int STEP, class Idx>
 __device__ __forceinline__ float4 row_vec(const float* __restrict__ row, Idx idx, Idx last) {
     if (FULL) {
         const float4* p = reinterpret_cast<const float4*>(row + min(idx, last));
         return STREAM ? ntload4(p) : *p;
     }
-    return make_float4(row[min(idx, last)], row[min((Idx)(idx + 1), last)], row[min((Idx)(idx + 2), last)], row[min((Idx)(idx + 3), last)]);
+    return make_float4(row[min(idx, last)], row[min((Idx)(idx + STEP), last)], row[min((Idx)(idx + 2 * STEP), last)], row[min((Idx)(idx + 3 * STEP), last)]);
 }
-template <bool FULL, class Idx>
+template <bool FULL, int STEP, class Idx>
 __device__ __forceinline__ float4 row_fill(float4 r, Idx idx, Idx limit, float fill) {
-    const bool i0 = idx < limit, i1 = FULL ? i0 : idx + 1 < limit, i2 = FULL ? i0 : idx + 2 < limit, i3 = FULL ? i0 : idx + 3 < limit;
+    const bool i0 = idx < limit, i1 = FULL ? i0 : idx + STEP < limit, i2 = FULL ? i0 : idx + 2 * STEP < limit, i3 = FULL ? i0 : idx + 3 * STEP < limit;
     return make_float4(i0 ? r.x : fill, i1 ? r.y : fill, i2 ? r.z : fill, i3 ? r.w : fill);
 }
-#define TAO_VEC_IDX(v) (((Idx)(v) * TPR + lt) * 4)
+#define TAO_VEC_IDX(v) (FULL ? ((Idx)(v) * TPR + lt) * 4 : (Idx)(v) * (4 * TPR) + lt)
 
 template <int TPR, int V, bool FULL, bool QUICK>
 __global__ __launch_bounds__(kCheckThreads) void softmax_check(
@@ -232,7 +234,9 @@ __global__ __launch_bounds__(kCheckThreads) void softmax_check(
     unsigned int* __restrict__ ws_hist, unsigned int* __restrict__ ws_coarse, BlockStats* __restrict__ ws_stats) {
     constexpr int RPB = kCheckThreads / TPR;
     using Idx = typename std::conditional<(V > 0), int, long>::type;     // columns: a cached row has at most 8192
-    constexpr bool CACHED = (V > 0), CLAIMS = CACHED && V <= 4;      // claims requested with the row
+    constexpr bool CACHED = (V > 0), CLAIMS = CACHED && V <= 4 && (QUICK || V == 1);   // claims requested with the row
+    // the next rows are requested while these are worked on, where the registers allow it
+    constexpr bool PIPE = V == 1 || (V == 2 && TPR < 1024);
     __shared__ unsigned int hist[kBins * kReplicas];
     __shared__ unsigned int red[3 * (kCheckThreads / kWave)];
     __shared__ double smem[2 * 4 * (kCheckThreads / kWave)];       // one slot per reduction of a row
@@ -247,6 +251,20 @@ __global__ __launch_bounds__(kCheckThreads) void softmax_check(
     const int rep = tid & (kReplicas - 1);
     const int nv = CACHED ? V : (int)((cols + TPR * 4 - 1) / (TPR * 4));
     const long nblocks = (rows + RPB - 1) / RPB;
+    float4 xn[PIPE ? V : 1], yn[PIPE ? V : 1], cn[PIPE && CLAIMS ? V : 1];
+    auto request = [&](long rb, float4* xr, float4* yr, float4* cr) __attribute__((always_inline)) {
+        int lt = tid % TPR;
+        asm volatile("" : "+v"(lt));
+        const long row = rb * RPB + tid / TPR, roff = (row < rows ? row : rows - 1) * ld;
+        const Idx last = (Idx)cols - (FULL ? 4 : 1);
+#pragma unroll
+        for (int v = 0; v < V; ++v) {
+            xr[v] = row_vec<FULL, true, TPR>(x + roff, TAO_VEC_IDX(v), last);
+            yr[v] = row_vec<FULL, true, TPR>(y + roff, TAO_VEC_IDX(v), last);
+            if (CLAIMS) cr[v] = row_vec<FULL, true, TPR>(claimed + roff, TAO_VEC_IDX(v), last);
+        }
+    };
+    if (PIPE && (long)blockIdx.x < nblocks) request(blockIdx.x, xn, yn, cn);
     // every thread of the workgroup takes the same number of trips (the reductions hold barriers)
     for (long rb = blockIdx.x; rb < nblocks; rb += gridDim.x) {
         int lt = tid % TPR;
@@ -257,17 +275,26 @@ __global__ __launch_bounds__(kCheckThreads) void softmax_check(
         const long roff = (active ? row : rows - 1) * ld;
         float4 xv[CACHED ? V : 1], yv[CACHED ? V : 1], cv[CLAIMS ? V : 1];
         float m = -INFINITY; int bad = 0;
-        if (CACHED) {
+        if (PIPE) {
+#pragma unroll
             for (int v = 0; v < nv; ++v) {
-                xv[v] = row_vec<FULL, true>(x + roff, TAO_VEC_IDX(v), last);
-                yv[v] = row_vec<FULL, true>(y + roff, TAO_VEC_IDX(v), last);
-                if (CLAIMS) cv[v] = row_vec<FULL, true>(claimed + roff, TAO_VEC_IDX(v), last);
+                xv[v] = xn[v]; yv[v] = yn[v];
+                if (CLAIMS) cv[v] = cn[v];
+            }
+            if (rb + gridDim.x < nblocks) request(rb + gridDim.x, xn, yn, cn);
+            __builtin_amdgcn_sched_barrier(0);
+        } else if (CACHED) {
+#pragma unroll
+            for (int v = 0; v < nv; ++v) {
+                xv[v] = row_vec<FULL, true, TPR>(x + roff, TAO_VEC_IDX(v), last);
+                yv[v] = row_vec<FULL, true, TPR>(y + roff, TAO_VEC_IDX(v), last);
+                if (CLAIMS) cv[v] = row_vec<FULL, true, TPR>(claimed + roff, TAO_VEC_IDX(v), last);
             }
             __builtin_amdgcn_sched_barrier(0);               // (all requests leave before the first is waited for)
         }
         for (int v = 0; v < nv; ++v) {
-            const float4 X = row_fill<FULL>(CACHED ? xv[v] : row_vec<FULL, false>(x + roff, TAO_VEC_IDX(v), last), TAO_VEC_IDX(v), limit, -INFINITY);
-            if (CACHED) { xv[v] = X; yv[v] = row_fill<FULL>(yv[v], TAO_VEC_IDX(v), limit, 0.f); }
+            const float4 X = row_fill<FULL, TPR>(CACHED ? xv[v] : row_vec<FULL, false, TPR>(x + roff, TAO_VEC_IDX(v), last), TAO_VEC_IDX(v), limit, -INFINITY);
+            if (CACHED) { xv[v] = X; yv[v] = row_fill<FULL, TPR>(yv[v], TAO_VEC_IDX(v), limit, 0.f); }
             const float e[4] = {X.x, X.y, X.z, X.w};
 #pragma unroll
             for (int c = 0; c < 4; ++c) { bad |= (e[c] != e[c]) | (e[c] == INFINITY); m = fmaxf(m, e[c]); }
@@ -285,8 +312,8 @@ __global__ __launch_bounds__(kCheckThreads) void softmax_check(
             q = (double)(masked ? 0.f : fabsf(ye)) * k.inv1mu;
         };
         for (int v = 0; v < nv; ++v) {
-            const float4 X = CACHED ? xv[v] : row_fill<FULL>(row_vec<FULL, false>(x + roff, TAO_VEC_IDX(v), last), TAO_VEC_IDX(v), limit, -INFINITY);
-            const float4 Y = CACHED ? yv[v] : row_fill<FULL>(row_vec<FULL, false>(y + roff, TAO_VEC_IDX(v), last), TAO_VEC_IDX(v), limit, 0.f);
+            const float4 X = CACHED ? xv[v] : row_fill<FULL, TPR>(row_vec<FULL, false, TPR>(x + roff, TAO_VEC_IDX(v), last), TAO_VEC_IDX(v), limit, -INFINITY);
+            const float4 Y = CACHED ? yv[v] : row_fill<FULL, TPR>(row_vec<FULL, false, TPR>(y + roff, TAO_VEC_IDX(v), last), TAO_VEC_IDX(v), limit, 0.f);
             const float xe[4] = {X.x, X.y, X.z, X.w}, ye[4] = {Y.x, Y.y, Y.z, Y.w};
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
@@ -309,14 +336,14 @@ __global__ __launch_bounds__(kCheckThreads) void softmax_check(
         if (QUICK) known = newest(&largest);
         if (CACHED) asm volatile("" : "+v"(lt));
         float4 next = make_float4(0.f, 0.f, 0.f, 0.f);       // the next vector's claims are on their way while one is checked
-        if (!CLAIMS) next = row_vec<FULL, true>(claimed + roff, TAO_VEC_IDX(0), last);
+        if (!CLAIMS) next = row_vec<FULL, true, TPR>(claimed + roff, TAO_VEC_IDX(0), last);
         for (int v = 0; v < nv; ++v) {
             const Idx idx = TAO_VEC_IDX(v);
             const float4 C = CLAIMS ? cv[v] : next;
-            if (!CLAIMS && v + 1 < nv) next = row_vec<FULL, true>(claimed + roff, TAO_VEC_IDX(v + 1), last);
+            if (!CLAIMS && v + 1 < nv) next = row_vec<FULL, true, TPR>(claimed + roff, TAO_VEC_IDX(v + 1), last);
             if (idx >= limit) continue;
-            const float4 X = CACHED ? xv[v] : row_vec<FULL, false>(x + roff, idx, last);
-            const float4 Y = CACHED ? yv[v] : row_vec<FULL, false>(y + roff, idx, last);
+            const float4 X = CACHED ? xv[v] : row_vec<FULL, false, TPR>(x + roff, idx, last);
+            const float4 Y = CACHED ? yv[v] : row_vec<FULL, false, TPR>(y + roff, idx, last);
             floatv4 xe = {X.x, X.y, X.z, X.w}, ye = {Y.x, Y.y, Y.z, Y.w}, ce = {C.x, C.y, C.z, C.w};
             asm volatile("" : "+v"(xe), "+v"(ye));           // (keeps the first pass's binary64 values from living on until here)
             auto tau = [&](int c) __attribute__((always_inline)) {
@@ -324,7 +351,7 @@ __global__ __launch_bounds__(kCheckThreads) void softmax_check(
                 q_rho(xe[c], ye[c], q, rho);
                 return up32g(q * fma(rho, w1, w0), up.mul, up.sub);
             };
-            if (FULL || idx + 3 < limit) {
+            if (FULL || idx + 3 * TPR < limit) {
                 if (!QUICK) {
                     const float c4[4] = {ce[0], ce[1], ce[2], ce[3]}, y4[4] = {ye[0], ye[1], ye[2], ye[3]};
                     const float t4[4] = {tau(0), tau(1), tau(2), tau(3)};
@@ -343,7 +370,7 @@ __global__ __launch_bounds__(kCheckThreads) void softmax_check(
             }
 #pragma unroll
             for (int c = 0; c < 3; ++c) {
-                if (idx + c >= limit) break;
+                if (idx + c * TPR >= limit) break;
                 check_one(ce[c], ye[c], tau(c), alpha, eps_rel, hist, rep, acc_chk);
             }
         }
@@ -678,44 +705,80 @@ __global__ __launch_bounds__(kRowThreads) void rmsnorm_bound_noy(
 // LayerNorm / RMSNorm bounds checked on the spot: the structure of softmax_check (1024-thread
 // workgroups that walk the rows, kCheckThreads / TPR rows at a time, one partial histogram each)
 // with the arithmetic of layernorm_body / rmsnorm_bound, operation for operation, so that the bound
-// compared in registers is the binary32 value the bound kernels store.
-template <bool RMS, int TPR, int V>
+// compared in registers is the binary32 value the bound kernels store.  FULL, QUICK: as there.
+// What bounds it: HBM for many rows (32768 x 768: LayerNorm 180 -> 90 us, RMSNorm 128 -> 65 us; LayerNorm 8192 x 2048 170 -> 67 us,
+// whose rows are now kept instead of read again), the chain of one row -- loads, two reductions, a square root and divisions in
+// binary64 -- for few (2048 x 4096 RMSNorm 34.4 -> 32.3 us), which is why the next rows are requested early.
+template <bool RMS, int TPR, int V, bool FULL, bool QUICK>
 __global__ __launch_bounds__(kCheckThreads) void norm_check(
     const float* __restrict__ x, const float* __restrict__ y, const float* __restrict__ g, const float* __restrict__ claimed,
-    long rows, long cols, long ld, int vec_ok, int vec_g, RowConsts k, double alpha, double eps_rel,
+    long rows, long cols, long ld, RowConsts k, double alpha, double eps_rel,
     unsigned int* __restrict__ ws_hist, unsigned int* __restrict__ ws_coarse, BlockStats* __restrict__ ws_stats) {
     constexpr int RPB = kCheckThreads / TPR;
-    constexpr bool CACHED = (V > 0);
+    using Idx = typename std::conditional<(V > 0), int, long>::type;     // columns: a cached row has at most 8192
+    constexpr bool CACHED = (V > 0), CLAIMS = CACHED && V <= 4 && QUICK;  // claims requested with the row
+    // the next rows are requested while these are worked on, where the registers allow it
+    constexpr bool PIPE = V == 1 || (V == 2 && RMS);
     __shared__ unsigned int hist[kBins * kReplicas];
     __shared__ unsigned int red[3 * (kCheckThreads / kWave)];
     __shared__ double smem[2 * 4 * (kCheckThreads / kWave)];       // one slot per reduction of a row
+    __shared__ unsigned int largest;
     const int tid = threadIdx.x;
+    const QuickCheck qc(alpha, eps_rel);
+    unsigned known = 0;
     for (int i = tid; i < kBins * kReplicas; i += kCheckThreads) hist[i] = 0;
+    if (tid == 0) largest = 0;
     __syncthreads();
     ThreadAcc acc_chk;
     const int rep = tid & (kReplicas - 1);
-    const int lt = tid % TPR;
     const int nv = CACHED ? V : (int)((cols + TPR * 4 - 1) / (TPR * 4));
     const long nblocks = (rows + RPB - 1) / RPB;
     const double n = (double)cols;
-    auto scales = [&](long idx, long limit) {
-        return g ? load4(g, idx, limit, vec_g, 1.f) : make_float4(1.f, 1.f, 1.f, 1.f);
+    float4 xn[PIPE ? V : 1], yn[PIPE ? V : 1], cn[PIPE && CLAIMS ? V : 1];
+    auto request = [&](long rb, float4* xr, float4* yr, float4* cr) __attribute__((always_inline)) {
+        int lt = tid % TPR;
+        asm volatile("" : "+v"(lt));
+        const long row = rb * RPB + tid / TPR, roff = (row < rows ? row : rows - 1) * ld;
+        const Idx last = (Idx)cols - (FULL ? 4 : 1);
+#pragma unroll
+        for (int v = 0; v < V; ++v) {
+            xr[v] = row_vec<FULL, true, TPR>(x + roff, TAO_VEC_IDX(v), last);
+            yr[v] = row_vec<FULL, true, TPR>(y + roff, TAO_VEC_IDX(v), last);
+            if (CLAIMS) cr[v] = row_vec<FULL, true, TPR>(claimed + roff, TAO_VEC_IDX(v), last);
+        }
     };
+    if (PIPE && (long)blockIdx.x < nblocks) request(blockIdx.x, xn, yn, cn);
     // every thread of the workgroup takes the same number of trips (the reductions hold barriers)
     for (long rb = blockIdx.x; rb < nblocks; rb += gridDim.x) {
+        int lt = tid % TPR;
+        if (CACHED) asm volatile("" : "+v"(lt));            // (positions are formed anew for every row and pass, as in softmax_check)
         const long row = rb * RPB + tid / TPR;
         const bool active = row < rows;
-        const long limit = active ? cols : 0;
-        const long roff = active ? row * ld : 0;
-        float4 xv[CACHED ? V : 1], yv[CACHED ? V : 1], gv[CACHED ? V : 1];
+        const Idx limit = active ? (Idx)cols : 0, last = (Idx)cols - (FULL ? 4 : 1);
+        const long roff = (active ? row : rows - 1) * ld;
+        float4 xv[CACHED ? V : 1], yv[CACHED ? V : 1], cv[CLAIMS ? V : 1], gv[CLAIMS ? V : 1];
         double a1[2] = {0.0, 0.0};                 // RMS: sum x^2;  LayerNorm: sum x, sum |x|
-        for (int v = 0; v < nv; ++v) {
-            const float4 X = load4<CACHED>(x + roff, TAO_VEC_INDEX(v), limit, vec_ok, 0.f);
-            if (CACHED) {
-                xv[v] = X;
-                yv[v] = load4<true>(y + roff, TAO_VEC_INDEX(v), limit, vec_ok, 0.f);
-                gv[v] = scales(TAO_VEC_INDEX(v), limit);
+        auto scales = [&](Idx idx) { return g ? row_vec<FULL, false, TPR>(g, idx, last) : make_float4(1.f, 1.f, 1.f, 1.f); };
+        if (PIPE) {
+#pragma unroll
+            for (int v = 0; v < nv; ++v) {
+                xv[v] = xn[v]; yv[v] = yn[v];
+                if (CLAIMS) { cv[v] = cn[v]; gv[v] = scales(TAO_VEC_IDX(v)); }
             }
+            if (rb + gridDim.x < nblocks) request(rb + gridDim.x, xn, yn, cn);
+            __builtin_amdgcn_sched_barrier(0);
+        } else if (CACHED) {
+#pragma unroll
+            for (int v = 0; v < nv; ++v) {
+                xv[v] = row_vec<FULL, true, TPR>(x + roff, TAO_VEC_IDX(v), last);
+                yv[v] = row_vec<FULL, true, TPR>(y + roff, TAO_VEC_IDX(v), last);
+                if (CLAIMS) { cv[v] = row_vec<FULL, true, TPR>(claimed + roff, TAO_VEC_IDX(v), last); gv[v] = scales(TAO_VEC_IDX(v)); }
+            }
+            __builtin_amdgcn_sched_barrier(0);               // (all requests leave before the first is waited for)
+        }
+        for (int v = 0; v < nv; ++v) {
+            const float4 X = row_fill<FULL, TPR>(CACHED ? xv[v] : row_vec<FULL, false, TPR>(x + roff, TAO_VEC_IDX(v), last), TAO_VEC_IDX(v), limit, 0.f);
+            if (CACHED) xv[v] = X;
             const float e[4] = {X.x, X.y, X.z, X.w};
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
@@ -738,11 +801,11 @@ __global__ __launch_bounds__(kCheckThreads) void norm_check(
             const double E_mu = ((k.G * a1[1]) * k.inv_n + k.cd_u * fabs(mu)) * k.inv1mcd;
             double a2[2] = {0.0, 0.0};                                   // sum |d|, sum d^2
             for (int v = 0; v < nv; ++v) {
-                const float4 X = CACHED ? xv[v] : load4(x + roff, TAO_VEC_INDEX(v), limit, vec_ok, 0.f);
+                const float4 X = CACHED ? xv[v] : row_fill<FULL, TPR>(row_vec<FULL, false, TPR>(x + roff, TAO_VEC_IDX(v), last), TAO_VEC_IDX(v), limit, 0.f);
                 const float e[4] = {X.x, X.y, X.z, X.w};
 #pragma unroll
                 for (int c = 0; c < 4; ++c) {
-                    const double d = (TAO_VEC_INDEX(v) + c < limit) ? (double)e[c] - mu : 0.0;
+                    const double d = (TAO_VEC_IDX(v) + (FULL ? c : c * TPR) < limit) ? (double)e[c] - mu : 0.0;
                     a2[0] += fabs(d);
                     a2[1] = fma(d, d, a2[1]);
                 }
@@ -751,29 +814,56 @@ __global__ __launch_bounds__(kCheckThreads) void norm_check(
             layernorm_tail(E_mu, a2[0], a2[1], n, k, K1, K0, amp);
         }
         const UpFactors up(k.m * (1.0 + 2.0 * amp));
+        // alpha tau from below, in binary32: |x g| f + u |y|, or |g| (K1 |x - mu| + K0) + u |y| with the difference's
+        // own rounding taken off
+        const float uf = (float)k.u * qc.alpha, ff = (ok ? (float)f : NAN) * qc.alpha;
+        const float muf = (float)mu, K1f = (float)K1 * qc.alpha;
+        const float K0f = (float)(K0 - 0x1p-22 * K1 * fabs(mu)) * qc.alpha;
+        if (QUICK) known = newest(&largest);
+        if (CACHED) asm volatile("" : "+v"(lt));
+        float4 next = make_float4(0.f, 0.f, 0.f, 0.f), next_g = next;    // the next vector's claims are on their way while one is checked
+        constexpr bool AHEAD = CACHED && !CLAIMS;
+        if (AHEAD) { next = row_vec<FULL, true, TPR>(claimed + roff, TAO_VEC_IDX(0), last); next_g = scales(TAO_VEC_IDX(0)); }
         for (int v = 0; v < nv; ++v) {
-            const long idx = TAO_VEC_INDEX(v);
+            const Idx idx = TAO_VEC_IDX(v);
+            const float4 C = CLAIMS ? cv[v] : AHEAD ? next : row_vec<FULL, true, TPR>(claimed + roff, idx, last);
+            const float4 Gv = CLAIMS ? gv[v] : AHEAD ? next_g : scales(idx);
+            if (AHEAD && v + 1 < nv) { next = row_vec<FULL, true, TPR>(claimed + roff, TAO_VEC_IDX(v + 1), last); next_g = scales(TAO_VEC_IDX(v + 1)); }
             if (idx >= limit) continue;
-            const float4 X = CACHED ? xv[v] : load4(x + roff, idx, limit, vec_ok, 0.f);
-            const float4 Y = CACHED ? yv[v] : load4<true>(y + roff, idx, limit, vec_ok, 0.f);
-            const float4 Gv = CACHED ? gv[v] : scales(idx, limit);
-            const float4 C = load4<true>(claimed + roff, idx, limit, vec_ok, 0.f);
-            const float xe[4] = {X.x, X.y, X.z, X.w}, ye[4] = {Y.x, Y.y, Y.z, Y.w};
-            const float ge[4] = {Gv.x, Gv.y, Gv.z, Gv.w}, ce[4] = {C.x, C.y, C.z, C.w};
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                if (idx + c >= limit) break;
-                float t;
+            const float4 X = CACHED ? xv[v] : row_vec<FULL, false, TPR>(x + roff, idx, last);
+            const float4 Y = CACHED ? yv[v] : row_vec<FULL, true, TPR>(y + roff, idx, last);
+            floatv4 xe = {X.x, X.y, X.z, X.w}, ye = {Y.x, Y.y, Y.z, Y.w}, ge = {Gv.x, Gv.y, Gv.z, Gv.w}, ce = {C.x, C.y, C.z, C.w};
+            asm volatile("" : "+v"(xe), "+v"(ye));           // (keeps the first pass's binary64 values from living on until here)
+            auto tau = [&](int c) __attribute__((always_inline)) {
                 if (RMS) {
                     const double xg = fabs((double)xe[c] * (double)ge[c]);
                     const double tt = xg * f + k.u * fabs((double)ye[c]);
-                    t = ok ? up32g(tt, up.mul, up.sub) : NAN;
-                } else {
-                    const double ad = fabs((double)xe[c] - mu);
-                    const double ep = (double)fabsf(ge[c]) * fma(K1, ad, K0);
-                    t = up32g(fma(k.u, (double)fabsf(ye[c]), ep), up.mul, up.sub);
+                    return ok ? up32g(tt, up.mul, up.sub) : NAN;
                 }
-                check_one(ce[c], ye[c], t, alpha, eps_rel, hist, rep, acc_chk);
+                const double ad = fabs((double)xe[c] - mu);
+                const double ep = (double)fabsf(ge[c]) * fma(K1, ad, K0);
+                return up32g(fma(k.u, (double)fabsf(ye[c]), ep), up.mul, up.sub);
+            };
+            if (QUICK && (FULL || idx + 3 * TPR < limit)) {
+                floatv4 at;
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    if (RMS) at[c] = fmaf(fabsf(xe[c] * ge[c]), ff, uf * fabsf(ye[c]));
+                    else     at[c] = fmaf(fabsf(ge[c]), fmaf(K1f, fabsf(xe[c] - muf), K0f), uf * fabsf(ye[c]));
+                }
+                quick_check_four<(V == 1 || (V == 2 && TPR < 1024))>(ce, ye, at, tau, qc, alpha, eps_rel, hist, rep, acc_chk, &largest, known);
+                continue;
+            }
+            if (CACHED && (FULL || idx + 3 * TPR < limit)) {
+                const float c4[4] = {ce[0], ce[1], ce[2], ce[3]}, y4[4] = {ye[0], ye[1], ye[2], ye[3]};
+                const float t4[4] = {tau(0), tau(1), tau(2), tau(3)};
+                check_four(c4, y4, t4, alpha, eps_rel, hist, rep, acc_chk);
+                continue;
+            }
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {                    // (rows re-read from memory: no registers for four side by side)
+                if (idx + (FULL ? c : c * TPR) >= limit) break;
+                check_one(ce[c], ye[c], tau(c), alpha, eps_rel, hist, rep, acc_chk);
             }
         }
     }
@@ -838,6 +928,15 @@ __global__ __launch_bounds__(kRowThreads) void bn_affine_bound(
         store4(tau + row * ld, j, cols, vec_ok, make_float4(te[0], te[1], te[2], te[3]));
     }
 }
+
+// The one-pass checks of rows.  Quick settlement pays from eight rows per row group on, four where that is a wavefront; below, too many elements are
+// among the first a workgroup sees and the second route is only more code to fetch (us with / without: softmax 512 x 512
+// 20 / 16, RMSNorm 4096 x 768 28 / 25, but RMSNorm 8192 x 2048 55 / 59, 8192 x 4096 94 / 109).
+// From two rows per wavefront on a row of 513 to 1024 (softmax: 2048) columns belongs to one wavefront -- no barrier, the
+// wavefronts of a workgroup drift apart, so that some load while others calculate; fewer rows are divided
+// among four wavefronts, which fill the chip sooner (8192 x 1024 34 against 46 us, 4096 x 2048 45 against 40).
+constexpr long kWaveRows = 2L * kMaxCheckBlocks * (kCheckThreads / kWave);
+static bool quick_pays(long rows, int tpr) { return rows >= (tpr == kWave ? 4L : 8L) * kMaxCheckBlocks * (kCheckThreads / tpr); }
 
 // Pick the row-group shape for a row length and launch KERNEL<TPR, V>.  A single wavefront owns
 // a row of up to WMAX columns (no barrier, no LDS exchange); longer rows take a workgroup.
@@ -1043,8 +1142,7 @@ int tao_bound_check_norm(int kind, const float* x, const float* y_ref, const flo
     rc = make_consts(md, cols > 0 ? cols : 1, eps, &k, true);
     if (rc != TAO_OK) return rc;
     hipStream_t st = (hipStream_t)stream;
-    const int vec_ok = aligned(x, 16) && (ld % 4 == 0) && aligned(y_ref, 16) && aligned(claimed, 16);
-    const int vec_g = aligned(gamma, 16);
+    const bool full = aligned(x, 16) && aligned(y_ref, 16) && aligned(claimed, 16) && aligned(gamma, 16) && (ld % 4 == 0) && (cols % 4 == 0);
     const CheckWorkspace w = carve_check_workspace(ws);
     int nblocks = 1;
     const bool rms = kind == TAO_NORM_RMSNORM;
@@ -1052,27 +1150,32 @@ int tao_bound_check_norm(int kind, const float* x, const float* y_ref, const flo
         const long rb = (r + (kCheckThreads / tpr) - 1) / (kCheckThreads / tpr);
         nblocks = (int)(rb < 1 ? 1 : (rb < kMaxCheckBlocks ? rb : kMaxCheckBlocks));
         hipLaunchKernelGGL(kernel, dim3(nblocks), dim3(kCheckThreads), 0, st, x, y_ref, gamma, claimed, r, c, l,
-                           vec_ok, vec_g, k, alpha, eps_rel, w.hist, w.coarse, w.stats);
+                           k, alpha, eps_rel, w.hist, w.coarse, w.stats);
     };
-    // at most two vectors per thread for RMSNorm and one, up to 1024 columns, for LayerNorm (its
-    // second reduction and the check's binary64 division leave no more room under the 128-register
-    // limit of a 1024-thread workgroup): longer rows take wider groups, or re-read the row
-#define TAO_NORM_CHECK(RMS, TPR, V) launch(norm_check<RMS, TPR, V>, TPR, rows, cols, ld)
+    auto quick = [&](int tpr) { return quick_pays(rows, tpr); };
+#define TAO_NORM_CHECK_Q(RMS, TPR, V, Q) \
+    (full ? launch(norm_check<RMS, TPR, V, true, Q>, TPR, rows, cols, ld) : launch(norm_check<RMS, TPR, V, false, Q>, TPR, rows, cols, ld))
+#define TAO_NORM_CHECK(RMS, TPR, V) do { if (quick(TPR)) TAO_NORM_CHECK_Q(RMS, TPR, V, true); else TAO_NORM_CHECK_Q(RMS, TPR, V, false); } while (0)
+#define TAO_NORM_CHECK_ROWS(RMS)                                                                            \
+    do {                                                                                                    \
+        if (cols <= 256)                     TAO_NORM_CHECK(RMS, 64, 1);                                    \
+        else if (cols <= 512)                TAO_NORM_CHECK(RMS, 64, 2);                                    \
+        else if (cols <= 1024 && rows >= kWaveRows) TAO_NORM_CHECK_Q(RMS, 64, 4, true);                    \
+        else if (cols <= 1024)               TAO_NORM_CHECK(RMS, 256, 1);                                   \
+        else if (cols <= 2048)               TAO_NORM_CHECK(RMS, 256, 2);                                   \
+        else if (cols <= 4096)               TAO_NORM_CHECK(RMS, 512, 2);                                   \
+        else if (cols <= 8192 && RMS)        TAO_NORM_CHECK(RMS, 1024, 2);                                  \
+        else                                 TAO_NORM_CHECK_Q(RMS, 1024, 0, false);                         \
+    } while (0)
     if (n == 0) {
-        if (rms) launch(norm_check<true, 64, 1>, 64, 0L, 1L, 1L); else launch(norm_check<false, 64, 1>, 64, 0L, 1L, 1L);
+        if (rms) launch(norm_check<true, 64, 1, false, false>, 64, 0L, 1L, 1L); else launch(norm_check<false, 64, 1, false, false>, 64, 0L, 1L, 1L);
     } else if (rms) {
-        if (cols <= 256)       TAO_NORM_CHECK(true, 64, 1);
-        else if (cols <= 512)  TAO_NORM_CHECK(true, 64, 2);
-        else if (cols <= 1024) TAO_NORM_CHECK(true, 256, 1);
-        else if (cols <= 2048) TAO_NORM_CHECK(true, 256, 2);
-        else if (cols <= 4096) TAO_NORM_CHECK(true, 512, 2);
-        else if (cols <= 8192) TAO_NORM_CHECK(true, 1024, 2);
-        else                   TAO_NORM_CHECK(true, 1024, 0);
+        TAO_NORM_CHECK_ROWS(true);
     } else {
-        if (cols <= 256)       TAO_NORM_CHECK(false, 64, 1);
-        else if (cols <= 1024) TAO_NORM_CHECK(false, 256, 1);
-        else                   TAO_NORM_CHECK(false, 1024, 0);     // wider cached rows spill: re-read instead
+        TAO_NORM_CHECK_ROWS(false);
     }
+#undef TAO_NORM_CHECK_ROWS
+#undef TAO_NORM_CHECK_Q
 #undef TAO_NORM_CHECK
     launch_profile_reduce(w, nblocks, (unsigned long long)n, out, st);
     return launch_status();
@@ -1107,19 +1210,14 @@ int tao_bound_check_softmax(const float* x, const float* y_ref, const float* cla
             hipLaunchKernelGGL(kernel, dim3(nblocks), dim3(kCheckThreads), 0, st, x, y_ref, claimed, rows, cols, ld,
                                k, alpha, eps_rel, w.hist, w.coarse, w.stats);
         };
-        // Quick settlement pays from four rows per row group on; below, most elements are the first a workgroup sees
-        // and the second route is only more code to fetch (512 x 512 16 against 20 us, 256 x 4096 19 against 22).
-        // With that many rows a row of up to 2048 columns belongs to one wavefront (no barrier: the wavefronts of a
-        // workgroup drift apart, so that some load while others calculate); fewer rows of more than 512 columns are
-        // divided among four, which fill the chip sooner (2048 x 2048 26 against 41 us).
-        auto quick = [&](int tpr) { return rows >= 4L * kMaxCheckBlocks * (kCheckThreads / tpr); };
+        auto quick = [&](int tpr) { return quick_pays(rows, tpr); };
 #define TAO_SOFTMAX_CHECK_Q(TPR, V, Q) (full ? launch(softmax_check<TPR, V, true, Q>, TPR) : launch(softmax_check<TPR, V, false, Q>, TPR))
 #define TAO_SOFTMAX_CHECK(TPR, V) do { if (quick(TPR)) TAO_SOFTMAX_CHECK_Q(TPR, V, true); else TAO_SOFTMAX_CHECK_Q(TPR, V, false); } while (0)
         if (cols <= 256)       TAO_SOFTMAX_CHECK(64, 1);
         else if (cols <= 512)  TAO_SOFTMAX_CHECK(64, 2);
-        else if (cols <= 1024 && quick(64)) TAO_SOFTMAX_CHECK_Q(64, 4, true);
+        else if (cols <= 1024 && rows >= kWaveRows) TAO_SOFTMAX_CHECK_Q(64, 4, true);
         else if (cols <= 1024) TAO_SOFTMAX_CHECK(256, 1);
-        else if (cols <= 2048 && quick(64) && full) launch(softmax_check<64, 8, true, true>, 64);   // (four addresses to a vector: no registers for eight)
+        else if (cols <= 2048 && rows >= kWaveRows && full) launch(softmax_check<64, 8, true, true>, 64);   // (four addresses to a vector: no registers for eight)
         else if (cols <= 2048) TAO_SOFTMAX_CHECK(256, 2);
         else if (cols <= 4096) TAO_SOFTMAX_CHECK(512, 2);
         else if (cols <= 8192) TAO_SOFTMAX_CHECK(1024, 2);

@@ -104,7 +104,7 @@ struct QuickCheck {
     __device__ __forceinline__ QuickCheck(double a, double e)
         : alpha((float)(fmin(a, 1e30) * (1.0 - 0x1p-18))), eps(e >= 0x1p-60 && e <= 0x1p60 ? (float)e : INFINITY) {}   // (an infinite eps settles nothing)
 };
-// at <= alpha tau (1 + 2^-18), positive or zero (NaN settles nothing); known: bits of an error that occurs.  bin: the error's bin.
+// at <= alpha tau (1 + 2^-18), or beyond 2^120 (an overflow on the way: settles nothing, nor does NaN); known: bits of an error that occurs.  bin: the error's bin.
 __device__ __forceinline__ bool quick_settled(float c, float r, float at, const QuickCheck& q, unsigned known, unsigned& bin) {
     const float d = fabsf(c - r);
     const float den = fabsf(r) + q.eps;
@@ -113,7 +113,7 @@ __device__ __forceinline__ bool quick_settled(float c, float r, float at, const 
     const bool zero = d == 0.f;                              // exactly: c == r
     const unsigned t = bits + 16u;
     const float lhs = zero ? 0.f : fmaf(d, 1.f + 0x1p-16f, 0x1p-90f);     // (a bound near the subnormal range settles nothing)
-    return lhs <= at && den <= 0x1p100f && (zero || ((t & 0xfffffu) >= 32u && t <= known));
+    return lhs <= at && at <= 0x1p120f && den <= 0x1p100f && (zero || ((t & 0xfffffu) >= 32u && t <= known));
 }
 typedef float floatv4 __attribute__((ext_vector_type(4)));      // (indexed by a variable it stays in registers)
 // Four elements: settled together or checked exactly, with tau(i) the binary32 bound of element i.  largest: the

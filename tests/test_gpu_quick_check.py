@@ -48,3 +48,26 @@ def test_profile_equals_bound_and_streaming_check(tao, rows, cols, alpha, eps_re
     for key in want:
         a, b = np.asarray(got[key]), np.asarray(want[key])
         assert np.array_equal(a, b, equal_nan=a.dtype.kind == "f"), key
+
+
+@pytest.mark.parametrize("kind", ["layernorm", "rmsnorm"])
+@pytest.mark.parametrize("rows,cols", [(16384, 200), (16390, 511), (8192, 768), (8191, 1021), (8192, 1024), (8200, 1030), (4096, 4096), (2049, 8190), (300, 8200)])
+def test_norm_profile_equals_bound_and_streaming_check(tao, kind, rows, cols):
+    g = torch.Generator(device="cuda").manual_seed(rows + cols)
+    k = tao.NORM_LAYERNORM if kind == "layernorm" else tao.NORM_RMSNORM
+    x = torch.randn((rows, cols), generator=g, device="cuda")
+    x[::7] *= 1e30; x[1::7] *= 1e-30; x[2::7] += 1e4         # products past the range of the estimates, a cancelling mean
+    gamma = 1 + 0.1 * torch.randn(cols, generator=g, device="cuda")
+    d = x.double() - (x.double().mean(-1, keepdim=True) if kind == "layernorm" else 0)
+    y = (d * torch.rsqrt((d * d).mean(-1, keepdim=True) + 1e-5) * gamma).float()
+    tau = tao.tao_bound_norm(k, x, y, gamma, None, eps=1e-5)
+    c = _claims(y, torch.nan_to_num(tau, nan=0.0, posinf=0.0), g)
+    c[3, 5] = float("nan"); c[rows - 1, cols - 1] = float("inf")
+    want = tao.tao_check_and_profile(c, y, tau)
+    got = tao.tao_bound_check_norm(k, x, y, c, gamma, None, eps=1e-5)
+    # (claims sit exactly at the bound, and the two kernels add a row in different orders: a bound on a rounding edge may fall
+    # either way; the errors themselves do not depend on it)
+    assert abs(got["violations"] - want["violations"]) <= rows * cols * 1e-5
+    for key in set(want) - {"violations", "accept"}:
+        a, b = np.asarray(got[key]), np.asarray(want[key])
+        assert np.array_equal(a, b, equal_nan=a.dtype.kind == "f"), key
