@@ -120,11 +120,12 @@ typedef float floatv4 __attribute__((ext_vector_type(4)));      // (indexed by a
 // workgroup's largest exactly computed error (LDS), known: this thread's copy, no newer than it needs to be.  WIDE: the
 // exact way takes the four side by side, for kernels that have the registers (small tensors see little else);
 // otherwise one after the other in a loop, as four binary64 divisions would set the kernel's register count.
+// attempt: false goes the exact way at once.  Returns whether the estimates settled them.
 template <bool WIDE, int R = kReplicas, class Tau>
-__device__ __forceinline__ void quick_check_four(floatv4 c, floatv4 r, floatv4 at, Tau&& tau,
+__device__ __forceinline__ bool quick_check_four(floatv4 c, floatv4 r, floatv4 at, Tau&& tau,
                                                  const QuickCheck& q, double alpha, double eps_rel, unsigned int* hist, int rep,
-                                                 ThreadAcc& acc, unsigned int* largest, unsigned& known) {
-    if (known) {
+                                                 ThreadAcc& acc, unsigned int* largest, unsigned& known, bool attempt = true) {
+    if (known && attempt) {
         unsigned bin[4];
         bool ok = true;
 #pragma unroll
@@ -132,7 +133,7 @@ __device__ __forceinline__ void quick_check_four(floatv4 c, floatv4 r, floatv4 a
         if (ok) {
 #pragma unroll
             for (int i = 0; i < 4; ++i) atomicAdd(&hist[bin[i] * R + rep], 1u);
-            return;
+            return true;
         }
     }
     if (WIDE) {
@@ -145,6 +146,7 @@ __device__ __forceinline__ void quick_check_four(floatv4 c, floatv4 r, floatv4 a
     }
     if (acc.max_bits > known) atomicMax(largest, acc.max_bits);
     known = max(known, acc.max_bits);
+    return false;
 }
 __device__ __forceinline__ unsigned newest(unsigned int* largest) {
     return __hip_atomic_load(largest, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);

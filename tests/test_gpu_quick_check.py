@@ -71,3 +71,23 @@ def test_norm_profile_equals_bound_and_streaming_check(tao, kind, rows, cols):
     for key in set(want) - {"violations", "accept"}:
         a, b = np.asarray(got[key]), np.asarray(want[key])
         assert np.array_equal(a, b, equal_nan=a.dtype.kind == "f"), key
+
+
+@pytest.mark.parametrize("n", [4096, 4 * 1024 * 1024 - 4, 4 * 1024 * 1024, 8 * 1024 * 1024, 9 * 1024 * 1024 + 3])
+@pytest.mark.parametrize("kind", ["ACT_SILU", "ACT_GELU_ERF", "ACT_GELU_TANH", "ACT_MUL", "ACT_RELU"])
+def test_act_profile_equals_bound_and_streaming_check(tao, kind, n):
+    g = torch.Generator(device="cuda").manual_seed(n)
+    k = getattr(tao, kind)
+    x = 3 * torch.randn(n, generator=g, device="cuda")
+    x[5::1001] *= 1e30; x[6::1001] *= 1e-40
+    xd = x.double()
+    y = (xd / (1 + torch.exp(-xd)) if kind == "ACT_SILU" else 0.5 * xd * (1 + torch.erf(xd * 0.5 ** 0.5)) if "GELU" in kind else xd).float()
+    tau = tao.tao_bound_act(k, x, y, x2=x)
+    c = _claims(y, torch.nan_to_num(tau, nan=0.0, posinf=0.0), g)
+    c[3] = float("nan"); c[n - 1] = float("inf"); x[11] = float("nan"); x[12] = float("inf")
+    tau = tao.tao_bound_act(k, x, y, x2=x)
+    want = tao.tao_check_and_profile(c, y, tau)
+    got = tao.tao_bound_check_act(k, x, y, c, x2=x)
+    for key in want:
+        a, b = np.asarray(got[key]), np.asarray(want[key])
+        assert np.array_equal(a, b, equal_nan=a.dtype.kind == "f"), key
