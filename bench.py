@@ -501,7 +501,7 @@ def main():
         ms = _event_time(torch, lambda: tao.tao_bound_linear_images(a_img, w_img, n, n, n, out=out), args.steps, args.warmup)
         tf = 2.0 * n ** 3 / (ms * 1e-3) / 1e12
         print(json.dumps({"workload": "BF16-split product %d^3 on prepared operand images" % n, "ms": ms, "TFLOP/s": tf,
-                          "issued_frac_of_bf16_peak": 8.0 * tf / PEAK_BF16_MFMA_TFLOPS}))
+                          "issued_frac_of_bf16_peak": 6.0 * tf / PEAK_BF16_MFMA_TFLOPS}))
         return
 
     other = {1: ("config 1: one 64x256 @ 256x128 linear and a 64x128 softmax", lambda: tao_inputs.config1(dev)),
@@ -542,11 +542,11 @@ def main():
     lin_flops = sum(p.flops * len(p.bound_events) for p in lin)
     achieved = lin_flops / (lin_ms * 1e-3) / 1e12
     # the matmul bound, both paths together: algorithmic flop (2MNK) per second against the FP32 MFMA
-    # peak the metric names; a BF16-split launch issues 8 BF16 products per operand pair and includes
+    # peak the metric names; a BF16-split launch issues 6 BF16 products per operand pair and includes
     # the pre-pass of its activation (and of its weight, unless that was prepared)
     sp = [p for p in lin if p.split]
     paths = {}
-    for nm, sel, mult, peak in (("bf16_split", sp, 8.0, PEAK_BF16_MFMA_TFLOPS), ("fp32", [p for p in lin if not p.split], 1.0, PEAK_FP32_MFMA_TFLOPS)):
+    for nm, sel, mult, peak in (("bf16_split", sp, 6.0, PEAK_BF16_MFMA_TFLOPS), ("fp32", [p for p in lin if not p.split], 1.0, PEAK_FP32_MFMA_TFLOPS)):
         if sel:
             ms = sum(sum(_ms(p.bound_events)) for p in sel)
             fl = sum(p.flops * len(p.bound_events) for p in sel)
@@ -560,7 +560,7 @@ def main():
                 "achieved": achieved, "peak": PEAK_FP32_MFMA_TFLOPS,
                 "unit": "TFLOP/s", "frac": achieved / PEAK_FP32_MFMA_TFLOPS,
                 # the two paths against the peak of the matrix cores each of them runs on: the FP32 path's
-                # algorithmic flop against the FP32 MFMA peak, the BF16-split path's issued flop (8 BF16
+                # algorithmic flop against the FP32 MFMA peak, the BF16-split path's issued flop (6 BF16
                 # products per operand pair) against the BF16 MFMA peak
                 "frac_fp32_path_of_fp32_peak": paths["fp32"]["issued_frac_of_own_peak"] if "fp32" in paths else None,
                 "frac_bf16_path_of_bf16_peak": paths["bf16_split"]["issued_frac_of_own_peak"] if "bf16_split" in paths else None,
@@ -609,18 +609,18 @@ def main():
         ms = _event_time(torch, lambda: tao.tao_bound_linear_split(A, W, out=out, ws=ws5), 5, 1)
         tf = 2.0 * 8192 ** 3 / (ms * 1e-3) / 1e12
         kernels["linear_8192^3_bf16_split"] = {"ms": ms, "TFLOP/s": tf, "frac_mfma": tf / PEAK_FP32_MFMA_TFLOPS,
-                                               "issued_frac_of_bf16_peak": 8.0 * tf / PEAK_BF16_MFMA_TFLOPS}
+                                               "issued_frac_of_bf16_peak": 6.0 * tf / PEAK_BF16_MFMA_TFLOPS}
         a_img, w_img = tao.tao_split_operand(A), tao.tao_split_operand(W)
         ms = _event_time(torch, lambda: tao.tao_bound_linear_images(a_img, w_img, 8192, 8192, 8192, out=out), 5, 1)
         tf = 2.0 * 8192 ** 3 / (ms * 1e-3) / 1e12
         kernels["linear_8192^3_bf16_split_prepared_operands"] = {"ms": ms, "TFLOP/s": tf, "frac_mfma": tf / PEAK_FP32_MFMA_TFLOPS,
-                                                                 "issued_frac_of_bf16_peak": 8.0 * tf / PEAK_BF16_MFMA_TFLOPS}
+                                                                 "issued_frac_of_bf16_peak": 6.0 * tf / PEAK_BF16_MFMA_TFLOPS}
         # the clock the chip holds under either path's kernel (the peaks assume 2400 MHz)
         mhz = shader_clock_under(torch, lambda: tao.tao_bound_linear_images(a_img, w_img, 8192, 8192, 8192, out=out))
         kernels["linear_8192^3_bf16_split_prepared_operands"]["sclk_mhz"] = mhz
         if mhz:
             kernels["linear_8192^3_bf16_split_prepared_operands"]["issued_frac_of_bf16_peak_at_that_clock"] = \
-                8.0 * tf / (PEAK_BF16_MFMA_TFLOPS * mhz / 2400.0)
+                6.0 * tf / (PEAK_BF16_MFMA_TFLOPS * mhz / 2400.0)
         kernels["linear_8192^3"]["sclk_mhz"] = shader_clock_under(torch, lambda: tao.tao_bound_linear(A, W, out=out))
         del ws5, a_img, w_img
         tao.tao_bound_linear(A, W, out=out)      # the stored bound of the check below: the FP32 path's
@@ -643,7 +643,7 @@ def main():
                         "operators": 1, "elements": ref.numel(), "ms_per_pass": ms, "GB/s_verified": 4.0 * ref.numel() / (ms * 1e-3) / 1e9,
                         "violations": prof["violations"], "expected_violations": int((cls == 2).sum()),
                         "matmul": {"TFLOP/s": tf, "frac_fp32_mfma_peak": tf / PEAK_FP32_MFMA_TFLOPS,
-                                   "issued_frac_of_bf16_peak": 8.0 * tf / PEAK_BF16_MFMA_TFLOPS, "path": "bf16_split+check"}}
+                                   "issued_frac_of_bf16_peak": 6.0 * tf / PEAK_BF16_MFMA_TFLOPS, "path": "bf16_split+check"}}
         del ws5
         # the two projections of Sec. 4.4 on the 67M deviations claimed - ref; thresholds: the
         # deviations' own percentile profile (bin upper edges: part of the elements is capped) and a
