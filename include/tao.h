@@ -201,6 +201,8 @@ size_t tao_bound_check_linear_workspace_bytes(long M, long N, long K, long batch
  *                              parts; ws may then be NULL), 256-byte aligned.
  *   tao_bound_check_linear_images  tao_bound_check_linear on two images (same result, field for field);
  *                              ws of tao_check_linear_images_workspace_bytes(M, N, K, batch) bytes.
+ * An image is for the build of the library that wrote it (the pieces' rounding is part of the scheme): it is
+ * prepared anew, not kept in a file, across builds.
  * Images are read only by the products; products that share an image may run concurrently.  Errors
  * as for the calls they mirror; TAO_ERR_ALIGN for an image that is not 256-byte aligned. */
 size_t tao_split_image_bytes(long rows, long K, long batch);
