@@ -19,6 +19,7 @@ struct ActConsts {
     double scale_f;        // factor of the one-step kinds: u, or c u/(1 - c u), upper
     double g7;             // Gamma(7), upper (tanh-form GELU: roundings of the polynomial)
     double c_tanh_u;       // c_tanh * u
+    float quick_alpha;     // the one-pass check: alpha of the estimates
 };
 // kernel variants beyond the public kinds' own: every one-step kind is |y| * scale_f
 constexpr int kKindScale = 100;
@@ -153,7 +154,7 @@ __global__ __launch_bounds__(kCheckThreads) void act_check(
     const long nvec = vec_ok ? (n >> 2) : 0;
     const long stride = (long)gridDim.x * kCheckThreads;
     if (QUICK) {
-        const QuickCheck qc(alpha, eps_rel);
+        const QuickCheck qc(k.quick_alpha, eps_rel);
         unsigned known = 0;
         int exact = 0;
         long i = (long)blockIdx.x * kCheckThreads + tid;
@@ -323,6 +324,7 @@ static int act_setup(int kind, const tao_fp_model* model, tao::ActConsts* out) {
     }
     if (cf >= 0.0 && !(cf * u < 0.5)) return TAO_ERR_MODEL;
     k.scale_f = cf >= 0.0 ? widen(cf * u / (1.0 - cf * u)) : u;
+    k.quick_alpha = NAN;
     *out = k;
     return TAO_OK;
 }
@@ -379,6 +381,7 @@ int tao_bound_check_act(int kind, const float* x, const float* x2, const float* 
     // (one vector per thread before another workgroup, as in the check pass: GELU of 65536 elements 11.3 against 19.9 us with four)
     long want = (n + (long)kCheckThreads * 4 - 1) / ((long)kCheckThreads * 4);
     const int nblocks = (int)(want < 1 ? 1 : (want > kMaxCheckBlocks ? kMaxCheckBlocks : want));
+    k.quick_alpha = quick_alpha(alpha);
     const CheckWorkspace w = carve_check_workspace(ws);
     hipStream_t st = (hipStream_t)stream;
     dim3 grid((unsigned)nblocks), blk(kCheckThreads);

@@ -34,6 +34,7 @@ struct RowConsts {
     double inv_n;      // 1/cols (nearest; covered by the guard factor)
     double mean_f;     // c_div u / (1 - c_div u), upper
     double m;          // rounding margin of a bound of this row length (see make_consts)
+    float quick_alpha; // the one-pass checks: alpha of the estimates
 };
 
 // Factors of the final upper rounding (up32g) for a rounding margin m.
@@ -242,7 +243,7 @@ __global__ __launch_bounds__(kCheckThreads) void softmax_check(
     __shared__ double smem[2 * 4 * (kCheckThreads / kWave)];       // one slot per reduction of a row
     __shared__ unsigned int largest;
     const int tid = threadIdx.x;
-    const QuickCheck qc(alpha, eps_rel);
+    const QuickCheck qc(k.quick_alpha, eps_rel);
     unsigned known = 0;
     for (int i = tid; i < kBins * kReplicas; i += kCheckThreads) hist[i] = 0;
     if (tid == 0) largest = 0;
@@ -724,7 +725,7 @@ __global__ __launch_bounds__(kCheckThreads) void norm_check(
     __shared__ double smem[2 * 4 * (kCheckThreads / kWave)];       // one slot per reduction of a row
     __shared__ unsigned int largest;
     const int tid = threadIdx.x;
-    const QuickCheck qc(alpha, eps_rel);
+    const QuickCheck qc(k.quick_alpha, eps_rel);
     unsigned known = 0;
     for (int i = tid; i < kBins * kReplicas; i += kCheckThreads) hist[i] = 0;
     if (tid == 0) largest = 0;
@@ -985,6 +986,7 @@ static int make_consts(const tao_fp_model& md, long cols, double eps, RowConsts*
     // bound that depends on the sums with unit sensitivity; the kernels scale it where a sum enters
     // through a difference (1 - sigma of the softmax, the lower end w_lo of the variance).
     k->m = ((double)cols + 130.0) * 0x1p-51;
+    k->quick_alpha = NAN;
     if (!(md.c_exp * u < 0.5) || !(md.c_div * u < 0.5)) return TAO_ERR_MODEL;
     return TAO_OK;
 }
@@ -1143,6 +1145,7 @@ int tao_bound_check_norm(int kind, const float* x, const float* y_ref, const flo
     if (rc != TAO_OK) return rc;
     hipStream_t st = (hipStream_t)stream;
     const bool full = aligned(x, 16) && aligned(y_ref, 16) && aligned(claimed, 16) && aligned(gamma, 16) && (ld % 4 == 0) && (cols % 4 == 0);
+    k.quick_alpha = quick_alpha(alpha);
     const CheckWorkspace w = carve_check_workspace(ws);
     int nblocks = 1;
     const bool rms = kind == TAO_NORM_RMSNORM;
@@ -1200,6 +1203,7 @@ int tao_bound_check_softmax(const float* x, const float* y_ref, const float* cla
     rc = make_consts(md, cols > 0 ? cols : 1, 0.0, &k);
     if (rc != TAO_OK) return rc;
     hipStream_t st = (hipStream_t)stream;
+    k.quick_alpha = quick_alpha(alpha);
     const CheckWorkspace w = carve_check_workspace(ws);
     const bool full = aligned(x, 16) && aligned(y_ref, 16) && aligned(claimed, 16) && (ld % 4 == 0) && (cols % 4 == 0);
     int nblocks = 1;

@@ -99,10 +99,15 @@ __device__ __forceinline__ void check_one(float c, float r, float t, double alph
 // its bin, might exceed the largest error the workgroup has seen exactly so far, is not clearly below alpha tau, or
 // is no ordinary number; such elements (about one in 2^15, and the first ones) take check_arith, so the results are
 // the same bit for bit.  About 18 instructions instead of 35, a dozen of them a binary64 division.
+// alpha for the estimates: lowered by 2^-18; NaN, which settles nothing, unless it is an ordinary factor (a NaN alpha
+// admits no element and an infinite one none whose bound is 0, which no estimate tells apart).
+inline float quick_alpha(double alpha) {
+    return alpha >= 0x1p-30 && alpha <= 0x1p30 ? (float)(alpha * (1.0 - 0x1p-18)) : NAN;
+}
 struct QuickCheck {
     float alpha, eps;
-    __device__ __forceinline__ QuickCheck(double a, double e)
-        : alpha((float)(fmin(a, 1e30) * (1.0 - 0x1p-18))), eps(e >= 0x1p-60 && e <= 0x1p60 ? (float)e : INFINITY) {}   // (an infinite eps settles nothing)
+    __device__ __forceinline__ QuickCheck(float a, double e)
+        : alpha(a), eps(e >= 0x1p-60 && e <= 0x1p60 ? (float)e : INFINITY) {}   // (an infinite eps settles nothing)
 };
 // at <= alpha tau (1 + 2^-18), or beyond 2^120 (an overflow on the way: settles nothing, nor does NaN); known: bits of an error that occurs.  bin: the error's bin.
 __device__ __forceinline__ bool quick_settled(float c, float r, float at, const QuickCheck& q, unsigned known, unsigned& bin) {

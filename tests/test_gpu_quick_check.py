@@ -91,3 +91,21 @@ def test_act_profile_equals_bound_and_streaming_check(tao, kind, n):
     for key in want:
         a, b = np.asarray(got[key]), np.asarray(want[key])
         assert np.array_equal(a, b, equal_nan=a.dtype.kind == "f"), key
+
+
+# alphas under which the estimates must settle nothing: the softmax check takes any alpha, like the streaming check (whose
+# comparison fails for NaN everywhere, and for an infinite alpha where the bound is 0)
+@pytest.mark.parametrize("alpha", [float("nan"), float("inf"), -1.0, 0.0, 2.0 ** -40, 2.0 ** 40, 1e300])
+@pytest.mark.parametrize("rows,cols", [(16384, 128), (16384, 1024), (16384, 2048)])
+def test_alphas_that_are_no_ordinary_factor(tao, rows, cols, alpha):
+    g = torch.Generator(device="cuda").manual_seed(rows + cols)
+    x = torch.randn((rows, cols), generator=g, device="cuda")
+    x.masked_fill_(torch.arange(cols, device="cuda")[None] > torch.arange(rows, device="cuda")[:, None] % cols, float("-inf"))
+    y = torch.softmax(x, -1)
+    tau = tao.tao_bound_softmax(x, y)
+    c = _claims(y, tau, g)
+    want = tao.tao_check_and_profile(c, y, tau, alpha=alpha)
+    got = tao.tao_bound_check_softmax(x, y, c, alpha=alpha)
+    for key in want:
+        a, b = np.asarray(got[key]), np.asarray(want[key])
+        assert np.array_equal(a, b, equal_nan=a.dtype.kind == "f"), key
