@@ -292,8 +292,8 @@ __global__ __launch_bounds__(kCheckThreads) void rope_check(
 
 extern "C" {
 
-// Validates kind and model and fills the constants of the element-wise kernels.
-static int act_setup(int kind, const tao_fp_model* model, tao::ActConsts* out) {
+// Validates kind and model and fills the constants of the element-wise kernels (alpha: the one-pass check's).
+static int act_setup(int kind, const tao_fp_model* model, tao::ActConsts* out, double alpha = NAN) {
     using namespace tao;
     tao_fp_model md;
     int rc = resolve_model(model, &md);
@@ -324,7 +324,7 @@ static int act_setup(int kind, const tao_fp_model* model, tao::ActConsts* out) {
     }
     if (cf >= 0.0 && !(cf * u < 0.5)) return TAO_ERR_MODEL;
     k.scale_f = cf >= 0.0 ? widen(cf * u / (1.0 - cf * u)) : u;
-    k.quick_alpha = NAN;
+    k.quick_alpha = quick_alpha(alpha, md);
     *out = k;
     return TAO_OK;
 }
@@ -368,7 +368,7 @@ int tao_bound_check_act(int kind, const float* x, const float* x2, const float* 
     using namespace tao;
     (void)x2;
     ActConsts k;
-    int rc = act_setup(kind, model, &k);
+    int rc = act_setup(kind, model, &k, alpha);
     if (rc != TAO_OK) return rc;
     if (!out || !ws) return out ? TAO_ERR_WORKSPACE : TAO_ERR_NULL;
     if (n < 0 || n >= (1L << 36) || !(alpha >= 0.0) || !std::isfinite(alpha) || !(eps_rel >= 0.0) || !std::isfinite(eps_rel))
@@ -381,7 +381,6 @@ int tao_bound_check_act(int kind, const float* x, const float* x2, const float* 
     // (one vector per thread before another workgroup, as in the check pass: GELU of 65536 elements 11.3 against 19.9 us with four)
     long want = (n + (long)kCheckThreads * 4 - 1) / ((long)kCheckThreads * 4);
     const int nblocks = (int)(want < 1 ? 1 : (want > kMaxCheckBlocks ? kMaxCheckBlocks : want));
-    k.quick_alpha = quick_alpha(alpha);
     const CheckWorkspace w = carve_check_workspace(ws);
     hipStream_t st = (hipStream_t)stream;
     dim3 grid((unsigned)nblocks), blk(kCheckThreads);

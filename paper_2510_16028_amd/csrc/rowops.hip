@@ -816,10 +816,14 @@ __global__ __launch_bounds__(kCheckThreads) void norm_check(
         }
         const UpFactors up(k.m * (1.0 + 2.0 * amp));
         // alpha tau from below, in binary32: |x g| f + u |y|, or |g| (K1 |x - mu| + K0) + u |y| with the difference's
-        // own rounding taken off
-        const float uf = (float)k.u * qc.alpha, ff = (ok ? (float)f : NAN) * qc.alpha;
-        const float muf = (float)mu, K1f = (float)K1 * qc.alpha;
-        const float K0f = (float)(K0 - 0x1p-22 * K1 * fabs(mu)) * qc.alpha;
+        // own rounding taken off.  The factor of a row has to be an ordinary number (else NaN: nothing of the row is
+        // settled): a subnormal one has lost bits, and a large one magnifies what a subnormal product |x g| has
+        // lost (2^-150; with f alpha below 2^55 that stays far below the 2^-90 of quick_settled).  What mu, the conversions and
+        // the products of the LayerNorm row lose there is taken off K0.
+        const float uf = (float)k.u * qc.alpha;
+        const float ff = (ok && f >= 0x1p-90 && f <= 0x1p25 ? (float)f : NAN) * qc.alpha;
+        const float muf = (float)mu, K1f = (K1 >= 0x1p-90 && K1 <= 0x1p25 ? (float)K1 : NAN) * qc.alpha;
+        const float K0f = (float)((K0 - K1 * (0x1p-22 * fabs(mu) + 0x1p-149)) * (double)qc.alpha - 0x1p-140);
         if (QUICK) known = newest(&largest);
         if (CACHED) asm volatile("" : "+v"(lt));
         float4 next = make_float4(0.f, 0.f, 0.f, 0.f), next_g = next;    // the next vector's claims are on their way while one is checked
@@ -1145,7 +1149,7 @@ int tao_bound_check_norm(int kind, const float* x, const float* y_ref, const flo
     if (rc != TAO_OK) return rc;
     hipStream_t st = (hipStream_t)stream;
     const bool full = aligned(x, 16) && aligned(y_ref, 16) && aligned(claimed, 16) && aligned(gamma, 16) && (ld % 4 == 0) && (cols % 4 == 0);
-    k.quick_alpha = quick_alpha(alpha);
+    k.quick_alpha = quick_alpha(alpha, md);
     const CheckWorkspace w = carve_check_workspace(ws);
     int nblocks = 1;
     const bool rms = kind == TAO_NORM_RMSNORM;
@@ -1203,7 +1207,7 @@ int tao_bound_check_softmax(const float* x, const float* y_ref, const float* cla
     rc = make_consts(md, cols > 0 ? cols : 1, 0.0, &k);
     if (rc != TAO_OK) return rc;
     hipStream_t st = (hipStream_t)stream;
-    k.quick_alpha = quick_alpha(alpha);
+    k.quick_alpha = quick_alpha(alpha, md);
     const CheckWorkspace w = carve_check_workspace(ws);
     const bool full = aligned(x, 16) && aligned(y_ref, 16) && aligned(claimed, 16) && (ld % 4 == 0) && (cols % 4 == 0);
     int nblocks = 1;

@@ -100,9 +100,13 @@ __device__ __forceinline__ void check_one(float c, float r, float t, double alph
 // is no ordinary number; such elements (about one in 2^15, and the first ones) take check_arith, so the results are
 // the same bit for bit.  About 18 instructions instead of 35, a dozen of them a binary64 division.
 // alpha for the estimates: lowered by 2^-18; NaN, which settles nothing, unless it is an ordinary factor (a NaN alpha
-// admits no element and an infinite one none whose bound is 0, which no estimate tells apart).
-inline float quick_alpha(double alpha) {
-    return alpha >= 0x1p-30 && alpha <= 0x1p30 ? (float)(alpha * (1.0 - 0x1p-18)) : NAN;
+// admits no element and an infinite one none whose bound is 0, which no estimate tells apart) and the model's
+// constants, which the estimates take as binary32 factors, are ordinary too.
+inline float quick_alpha(double alpha, const tao_fp_model& m) {
+    auto ordinary = [](double c) { return c == 0.0 || c >= 0x1p-20; };
+    const bool ok = alpha >= 0x1p-30 && alpha <= 0x1p30 && m.u >= 0x1p-40 && ordinary(m.c_exp) && ordinary(m.c_erf) && ordinary(m.c_rsqrt) &&
+                    ordinary(m.c_div) && ordinary(m.c_log) && ordinary(m.c_sin) && ordinary(m.c_cos) && ordinary(m.c_tanh) && ordinary(m.c_pow);
+    return ok ? (float)(alpha * (1.0 - 0x1p-18)) : NAN;
 }
 struct QuickCheck {
     float alpha, eps;

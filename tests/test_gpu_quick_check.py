@@ -109,3 +109,46 @@ def test_alphas_that_are_no_ordinary_factor(tao, rows, cols, alpha):
     for key in want:
         a, b = np.asarray(got[key]), np.asarray(want[key])
         assert np.array_equal(a, b, equal_nan=a.dtype.kind == "f"), key
+
+
+# Rows at which a binary32 estimate of the bound would be formed from subnormal numbers.  Claims lie 2^-14 ... 2^-8 of the
+# bound inside and outside it (y = 0, so that they can): far beyond the last bit, in which the two kernels' bounds may differ.
+@pytest.mark.parametrize("kind,rows_are", [("rmsnorm", "tiny products"), ("rmsnorm", "huge"), ("layernorm", "huge"), ("layernorm", "subnormal"),
+                                           ("rmsnorm", "subnormal")])
+@pytest.mark.parametrize("rows,cols", [(16384, 512), (16384, 511), (16384, 1024)])
+def test_norm_rows_at_the_ends_of_the_range(tao, kind, rows_are, rows, cols):
+    g = torch.Generator(device="cuda").manual_seed(rows + cols)
+    k = tao.NORM_LAYERNORM if kind == "layernorm" else tao.NORM_RMSNORM
+    rand = lambda: torch.rand((rows, cols), generator=g, device="cuda")
+    gamma = torch.ones(cols, device="cuda")
+    if rows_are == "tiny products":
+        x = 1e-30 * (0.5 + rand())
+        x[:, ::8] *= 1e-6; gamma[::8] = 1e-6                 # x g about 1e-42
+    elif rows_are == "huge":
+        x = 3e38 * (2 * rand() - 1)
+    else:
+        x = (torch.randint(-260, 261, (rows, cols), generator=g, device="cuda").double() * 2.0 ** -149).float()
+    y = torch.zeros_like(x)
+    tau = tao.tao_bound_norm(k, x, y, gamma, None, eps=0.0)
+    assert torch.isfinite(tau).all()
+    off = torch.exp2(-torch.randint(8, 15, x.shape, generator=g, device="cuda").double()) * (2.0 * torch.randint(0, 2, x.shape, generator=g, device="cuda") - 1)
+    c = (tau.double() * (1 + off)).float()
+    want = tao.tao_check_and_profile(c, y, tau)
+    got = tao.tao_bound_check_norm(k, x, y, c, gamma, None, eps=0.0)
+    for key in want:
+        assert np.array_equal(np.asarray(got[key]), np.asarray(want[key])), key
+
+
+def test_act_factor_below_the_normal_range(tao):
+    n = 5 << 20
+    g = torch.Generator(device="cuda").manual_seed(n)
+    model = tao.FpModel(c_erf=1e-36)                         # c_erf u is a subnormal binary32 number
+    x = 1e37 * (0.5 + torch.rand(n, generator=g, device="cuda"))
+    y = torch.zeros_like(x)
+    tau = tao.tao_bound_act(tao.ACT_GELU_ERF, x, y, model=model)
+    off = torch.exp2(-torch.randint(8, 15, x.shape, generator=g, device="cuda").double()) * (2.0 * torch.randint(0, 2, x.shape, generator=g, device="cuda") - 1)
+    c = (tau.double() * (1 + off)).float()
+    want = tao.tao_check_and_profile(c, y, tau)
+    got = tao.tao_bound_check_act(tao.ACT_GELU_ERF, x, y, c, model=model)
+    for key in want:
+        assert np.array_equal(np.asarray(got[key]), np.asarray(want[key])), key
