@@ -153,8 +153,10 @@ int tao_bound_linear(const float *A, const float *W, const float *bias, float *t
  * tao_bound_linear, plus ws: device scratch, 256-byte aligned, at least
  * tao_linear_split_workspace_bytes(M, N, K, batch, shared_w) bytes (shared_w != 0 when
  * strideW == 0 or batch == 1); contents irrelevant before and garbage after; calls sharing ws
- * must be ordered on one stream.  Operands below 2^-110 in magnitude keep the bound sound but may
- * push it beyond 1e-6.  TAO_FLAG_FAST_ACCUM is ignored.  TAO_ERR_WORKSPACE when ws is missing,
+ * must be ordered on one stream.  Sums that leave the binary32 range on the matrix cores are formed again in binary64:
+ * the bound is then exact to 1e-6 as well, +inf where it exceeds the binary32 range itself, and NaN only for
+ * operands that are not finite (tao_bound_linear's FP32 tiles give +inf as soon as 32 k-steps' products overflow).
+ * Operands below 2^-110 in magnitude keep the bound sound but may push it beyond 1e-6.  TAO_FLAG_FAST_ACCUM is ignored.  TAO_ERR_WORKSPACE when ws is missing,
  * misaligned or too small. */
 int tao_bound_linear_split(const float *A, const float *W, const float *bias, float *tau,
                            long M, long N, long K, long lda, long ldw, long ldt, int trans_w,

@@ -129,23 +129,25 @@ __global__ __launch_bounds__(256) void split3_bf16(const float* __restrict__ src
     const long rblocks = (rows + STILE - 1) / STILE;
     const float* s = src + z * src_batch_stride;
     unsigned short* d = dst + z * ((Kp / SBK) * rblocks * (kBlock / 2));
-    // work items: TRANS (chunk, row) pairs, row fastest; else (row group, k span, slab, row, chunk of the slab)
+    // work items: TRANS (chunk, row) pairs, row fastest; else (row group, k span, slab, row, chunk of the slab).  Rows up
+    // to the next multiple of four are zeros: the product's epilogue looks at its sums by groups of four rows.
+    const long rows4 = (rows + 3) & ~3L;
     const long kspans = (Kp + 255) >> 8, rgroups = (rows + 63) >> 6;
-    const long total = TRANS ? rows * chunks : rgroups * kspans * 8 * 256;
+    const long total = TRANS ? rows4 * chunks : rgroups * kspans * 8 * 256;
     for (long w = (long)blockIdx.x * blockDim.x + threadIdx.x; w < total; w += (long)gridDim.x * blockDim.x) {
         long row, ch;
         if (TRANS) {
-            ch = w / rows; row = w - ch * rows;
+            ch = w / rows4; row = w - ch * rows4;
         } else {
             const long patch = w >> 11, in = w & 2047;          // 8 slabs x 64 rows x 4 chunks
             const long rg = patch / kspans, ks = patch - rg * kspans;
             row = (rg << 6) + ((in & 255) >> 2);
             ch = (ks << 5) + ((in >> 8) << 2) + (in & 3);
-            if (row >= rows || ch >= chunks) continue;
+            if (row >= rows4 || ch >= chunks) continue;
         }
         const long k0 = ch << 3;
         float v[8];
-        if (!TRANS && vec_ok && k0 + 8 <= K) {
+        if (!TRANS && vec_ok && row < rows && k0 + 8 <= K) {
             const float4 a = *reinterpret_cast<const float4*>(s + row * ld + k0);
             const float4 b = *reinterpret_cast<const float4*>(s + row * ld + k0 + 4);
             v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w; v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
@@ -153,7 +155,7 @@ __global__ __launch_bounds__(256) void split3_bf16(const float* __restrict__ src
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
                 const long k = k0 + j;
-                v[j] = (k < K) ? (TRANS ? s[k * ld + row] : s[row * ld + k]) : 0.f;
+                v[j] = (row < rows && k < K) ? (TRANS ? s[k * ld + row] : s[row * ld + k]) : 0.f;
             }
         }
         uintx4 H, Mi, L;
@@ -205,6 +207,77 @@ __device__ __forceinline__ double bound_offset(const SplitArgs& p, double s_abs,
 }
 __device__ __forceinline__ double bound_of_sum(const SplitArgs& p, double sv, double off_pos, double off_zero) {
     return fma(sv, p.c1, sv != 0.0 ? off_pos : off_zero);
+}
+
+// Sums beyond binary32.  hi is rounded up, so hi x hi can overflow where the magnitudes' own product (or the sum of 16 of
+// them) does not, and an infinite main term meets an infinite cross term of the other sign: a sum that is not finite
+// is formed again in binary64 from the same pieces (the products of two binary32 values are exact there, and every addition
+// errs by 2^-53, far inside the inflation).  It stays NaN where an operand is not finite.
+// Eight pieces' sums, exact: |v| (or the raised value of split_pack8).
+__device__ __forceinline__ void piece_sums(const uintx4& H, const uintx4& Mi, const uintx4& L, double (&v)[8]) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        v[2 * j] = (double)__uint_as_float(H[j] << 16) + (double)__uint_as_float(Mi[j] << 16) + (double)__uint_as_float(L[j] << 16);
+        v[2 * j + 1] = (double)__uint_as_float(H[j] & 0xffff0000u) + (double)__uint_as_float(Mi[j] & 0xffff0000u) +
+                       (double)__uint_as_float(L[j] & 0xffff0000u);
+    }
+}
+// The same of an image: unit `unit` (8 consecutive k) of group g of a row; base: the batch entry, blocks: its 128-row blocks.
+__device__ __forceinline__ void image_values(const unsigned short* base, long blocks, long row, long g, int unit, double (&v)[8]) {
+    const int r = (int)(row & (STILE - 1));
+    const unsigned short* at = base + (g * blocks + row / STILE) * (kBlock / 2) + r * (SROW / 2) + (unit ^ ((r >> 2) & 3)) * 8;
+    piece_sums(*reinterpret_cast<const uintx4*>(at), *reinterpret_cast<const uintx4*>(at + kSlab / 2),
+               *reinterpret_cast<const uintx4*>(at + kSlab), v);
+}
+// Where a convolution's patch row begins: input coordinates of filter tap (0, 0), offset of that pixel's first channel.
+__device__ __forceinline__ void patch_origin(const SplitArgs& p, unsigned row, int& ih0, int& iw0, long& base) {
+    const unsigned img = row / p.cohow, rem = row - img * p.cohow;
+    const unsigned oh = rem / (unsigned)p.cOW, ow = rem - oh * (unsigned)p.cOW;
+    ih0 = (int)oh * p.csh - p.cph; iw0 = (int)ow * p.csw - p.cpw;
+    base = (((long)img * p.cH + ih0) * p.cW + iw0) * p.cC;
+}
+// The eight values' place of k group g, unit `unit`, of a patch row (inside: false for a tap in the zero padding, whose
+// address is then the input's first).
+__device__ __forceinline__ const float* patch_values(const SplitArgs& p, int ih0, int iw0, long base, long g, int unit, bool& inside) {
+    const unsigned k0 = (unsigned)(g * SBK);
+    const unsigned tap = k0 / (unsigned)p.cC, c0 = k0 - tap * (unsigned)p.cC;
+    const unsigned r = tap / (unsigned)p.cS, sx = tap - r * (unsigned)p.cS;
+    const int dr = (int)r * p.cdh, ds = (int)sx * p.cdw;
+    inside = (unsigned)(ih0 + dr) < (unsigned)p.cH && (unsigned)(iw0 + ds) < (unsigned)p.cW;
+    return p.Af + (inside ? base + ((long)dr * p.cW + ds) * p.cC + c0 : 0L) + unit * 8;
+}
+template <bool AREG, bool CONV>
+__device__ __forceinline__ double sum_in_binary64(const SplitArgs& p, long row, long col, unsigned z, long g0, long ngroup) {
+    const long blocksA = (p.M + STILE - 1) / STILE, blocksW = (p.N + STILE - 1) / STILE;
+    const unsigned short* w = p.W3 + (long)z * p.batchW3;
+    int ih0 = 0, iw0 = 0; long base = 0;
+    if (CONV) patch_origin(p, (unsigned)row, ih0, iw0, base);
+    double s = 0.0;
+#pragma unroll 1
+    for (long g = g0; g < g0 + ngroup; ++g) {
+#pragma unroll 1
+        for (int unit = 0; unit < 4; ++unit) {
+            double av[8], wv[8];
+            if (AREG) {
+                bool inside = true;
+                const float* src = CONV ? patch_values(p, ih0, iw0, base, g, unit, inside)
+                                        : p.Af + (long)z * p.strideA + row * p.lda + g * SBK + unit * 8;
+                float v[8];
+#pragma unroll
+                for (int j = 0; j < 8; ++j) v[j] = inside ? src[j] : 0.f;
+                uintx4 H, Mi, L;
+                split_pack8(v, H, Mi, L);
+                piece_sums(H, Mi, L, av);
+            } else {
+                image_values(p.A3 + (long)z * p.batchA3, blocksA, row, g, unit, av);
+            }
+            image_values(w, blocksW, col, g, unit, wv);
+#pragma unroll
+            for (int j = 0; j < 8; ++j) s = fma(av[j], wv[j], s);
+        }
+        if (s != s) break;
+    }
+    return s;
 }
 
 // check_one with the histogram layout of the CHECK instantiation below (16-bit counters, bin b in
@@ -330,11 +403,7 @@ __global__ __launch_bounds__(kSplitThreads) void absgemm_split(SplitArgs p) {
     int cv_ih0 = 0, cv_iw0 = 0; long cv_base = 0;
     if (CONV) {
         const long m = (long)m0 + (tid >> 2);
-        const unsigned mm = m < p.M ? (unsigned)m : 0u;
-        const unsigned img = mm / p.cohow, rem = mm - img * p.cohow;
-        const unsigned oh = rem / (unsigned)p.cOW, ow = rem - oh * (unsigned)p.cOW;
-        cv_ih0 = (int)oh * p.csh - p.cph; cv_iw0 = (int)ow * p.csw - p.cpw;
-        cv_base = (((long)img * p.cH + cv_ih0) * p.cW + cv_iw0) * p.cC;
+        patch_origin(p, m < p.M ? (unsigned)m : 0u, cv_ih0, cv_iw0, cv_base);
         if (m >= p.M) cv_ih0 = -(1 << 30);
     }
     // `inside`: CONV only, whether the slab's tap lies inside the input for this row (else the loaded
@@ -342,12 +411,7 @@ __global__ __launch_bounds__(kSplitThreads) void absgemm_split(SplitArgs p) {
     auto fetch_a = [&](floatx4& lo4, floatx4& hi4, bool& inside, long g) __attribute__((always_inline)) {
         const float* src;
         if (CONV) {
-            const unsigned k0 = (unsigned)(g * SBK);
-            const unsigned tap = k0 / (unsigned)p.cC, c0 = k0 - tap * (unsigned)p.cC;
-            const unsigned r = tap / (unsigned)p.cS, sx = tap - r * (unsigned)p.cS;
-            const int dr = (int)r * p.cdh, ds = (int)sx * p.cdw;
-            inside = (unsigned)(cv_ih0 + dr) < (unsigned)p.cH && (unsigned)(cv_iw0 + ds) < (unsigned)p.cW;
-            src = p.Af + (inside ? cv_base + ((long)dr * p.cW + ds) * p.cC + c0 : 0L) + (tid & 3) * 8;
+            src = patch_values(p, cv_ih0, cv_iw0, cv_base, g, tid & 3, inside);
         } else {
             inside = true;
             long row = (long)m0 + (tid >> 2);
@@ -462,6 +526,7 @@ __global__ __launch_bounds__(kSplitThreads) void absgemm_split(SplitArgs p) {
     }
     int cur = 0;
     bool first = true;
+    unsigned top = 0;                                        // largest upper half of a sum (see the epilogue)
     ThreadAcc acc;
     const long nbatch = PARTIAL ? (long)(p.ntiles / p.slots_per_z) : 1;
 #pragma unroll 1
@@ -551,6 +616,49 @@ __global__ __launch_bounds__(kSplitThreads) void absgemm_split(SplitArgs p) {
         fold(S[1], D[1]);                                    // what the last part left unfolded
         fold(S[1], X[1]);
 
+        // Sums that are not finite: first whether there are any (a negative one, left by sums below 2^-126, passes for one), by
+        // groups of four rows that exist (an image's rows end with zeros up to a multiple of four; what lies beyond is arbitrary).
+        {
+            const long rows_left = p.M - m0 - wm * 32 - 4 * h, cols_left = p.N - n0 - wn * 64 - r32;
+#pragma unroll
+            for (int tj = 0; tj < 2; ++tj) {
+                unsigned most = 0;
+#pragma unroll
+                for (int b = 0; b < 4; ++b) {
+                    unsigned four = 0;
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) four = max(four, (unsigned)__double2hiint(S[tj][4 * b + v]));
+                    most = max(most, 8 * b < rows_left ? four : 0u);
+                }
+                top = max(top, 32 * tj < cols_left ? most : 0u);
+            }
+        }
+        if (CHECK && __builtin_expect(__any(top >= 0x7ff00000u), 0)) {
+            // (positions and arguments in vector registers, the arguments read again: scalar ones would be taken from the loops)
+            typedef const SplitArgs __attribute__((address_space(1)))* ArgsPtr;
+            ArgsPtr q = (ArgsPtr)(size_t)__builtin_amdgcn_kernarg_segment_ptr();
+            long row0 = (long)m0 + wm * 32 + 4 * h, col0 = (long)n0 + wn * 64 + r32, first_group = g0, groups = ngroup;
+            unsigned zz = z;
+            asm volatile("" : "+v"(q), "+v"(row0), "+v"(col0), "+v"(zz), "+v"(first_group), "+v"(groups));
+            const SplitArgs& pa = *(const SplitArgs*)q;
+            unsigned again = 0;
+#pragma unroll
+            for (int e = 0; e < 32; ++e) again |= (((unsigned)__double2hiint(S[e >> 4][e & 15]) & 0x7fffffffu) + 0x100000u) >> 31 << e;
+            unsigned rows = 0;
+#pragma unroll
+            for (int b = 0; b < 4; ++b) rows |= ((1u << (int)max(0L, min(4L, pa.M - row0 - 8 * b))) - 1u) << (4 * b);
+            again &= (col0 < pa.N ? rows : 0u) | (col0 + 32 < pa.N ? rows << 16 : 0u);
+            if (__any(again != 0)) {
+#pragma unroll 1
+                for (int e = 0; e < 32; ++e) {
+                    if (((again >> e) & 1u) == 0) continue;
+                    const double s = sum_in_binary64<AREG, CONV>(pa, row0 + 8 * ((e & 15) >> 2) + (e & 3), col0 + (e >> 4) * 32, zz, first_group, groups);
+#pragma unroll
+                    for (int w = 0; w < 32; ++w) S[w >> 4][w & 15] = w == e ? s : S[w >> 4][w & 15];
+                }
+            }
+        }
+
         // epilogue: D[i][j] of a 32x32 tile sits in lane (j + 32*((i/4)%2)), register 4*(i/8) + i%4
         float* __restrict__ T = p.tau ? p.tau + (long)z * p.strideT : nullptr;
         unsigned me = m0, ne = n0;
@@ -604,6 +712,37 @@ __global__ __launch_bounds__(kSplitThreads) void absgemm_split(SplitArgs p) {
         for (int v = 0; v < 16; ++v) {
 #pragma unroll
             for (int tj = 0; tj < 2; ++tj) { S[tj][v] = 0.0; X[tj][v] = 0.f; D[tj][v] = 0.f; }
+        }
+    }
+    // Plain bounds: the elements whose stored value is not finite once more, after the walk.  (Among the loops this code cost
+    // the loops their schedule -- 1111 x 1001 x 3001: 64 against 59 us; positions and arguments are taken anew so that nothing of
+    // it lives through them: else 4 spilled registers in the convolution, 988 against 978 us at 32 x 56 x 56 x 256.)
+    if (!CHECK && __builtin_expect(__any(top >= 0x7ff00000u), 0)) {
+        __builtin_amdgcn_s_waitcnt(0x0F70);                  // vmcnt(0): what this wavefront stored is in place
+        typedef const SplitArgs __attribute__((address_space(1)))* ArgsPtr;
+        ArgsPtr q = (ArgsPtr)(size_t)__builtin_amdgcn_kernarg_segment_ptr();
+        int lid = threadIdx.x;
+        asm volatile("" : "+v"(q), "+v"(lid));
+        const SplitArgs& pa = *(const SplitArgs*)q;
+        const int lrow = (lid >> 7) * 32 + ((lid >> 5) & 1) * 4, lcol = ((lid >> 6) & 1) * 64 + (lid & 31);
+        unsigned mt, nt, zt;
+        for (unsigned tt = next_tile(PARTIAL ? blockIdx.x % p.ntiles : blockIdx.x, mt, nt, zt); tt < p.ntiles;
+             tt = WALK ? next_tile(tt + gridDim.x, mt, nt, zt) : p.ntiles) {
+#pragma unroll 1
+            for (int e = 0; e < 32; ++e) {
+                const long row = (long)mt + lrow + 8 * ((e & 15) >> 2) + (e & 3), col = (long)nt + lcol + (e >> 4) * 32;
+                if (row >= pa.M || col >= pa.N) continue;
+                if (PARTIAL) {
+                    double* at = pa.partial + ((part * nbatch + zt) * pa.M + row) * pa.N + col;
+                    if (!(fabs(*at) < (double)INFINITY)) *at = sum_in_binary64<AREG, CONV>(pa, row, col, zt, g0, ngroup);
+                } else {
+                    float* at = pa.tau + (long)zt * pa.strideT + row * pa.ldt + col;
+                    if (fabsf(*at) < INFINITY) continue;
+                    const double ab = pa.bias ? fabs((double)pa.bias[col]) : 0.0;
+                    const double s = sum_in_binary64<AREG, CONV>(pa, row, col, zt, g0, ngroup);
+                    *at = up32(bound_of_sum(pa, s, bound_offset(pa, pa.si, ab), bound_offset(pa, pa.si0, ab)));
+                }
+            }
         }
     }
     if (CHECK) {
@@ -931,7 +1070,7 @@ static void launch_split3(const float* src, long rows, long K, long ld, int tran
                           unsigned short* image, unsigned int* zero_ptr, long zero_n, hipStream_t st) {
     const long Kp = (K + SBK - 1) / SBK * SBK;
     // work items of split3_bf16: (row, chunk) pairs, or whole 64-row x 256-k patches of 2048
-    long b = trans ? (rows * (Kp >> 3) + 255) / 256 : ((rows + 63) / 64) * ((Kp + 255) / 256) * 8;
+    long b = trans ? (((rows + 3) & ~3L) * (Kp >> 3) + 255) / 256 : ((rows + 63) / 64) * ((Kp + 255) / 256) * 8;
     const unsigned blocks = (unsigned)(b < 1 ? 1 : (b > 256L * 64 ? 256L * 64 : b));
     if (trans) {
         hipLaunchKernelGGL((split3_bf16<true>), dim3(blocks, (unsigned)batch), dim3(256), 0, st,

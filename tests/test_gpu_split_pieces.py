@@ -75,3 +75,62 @@ def test_non_finite_operands_never_give_a_finite_bound(tao, bad):
     hit = torch.zeros(40, 24, dtype=torch.bool)
     hit[7], hit[8], hit[:, 3] = True, True, True
     assert not torch.isfinite(tau[hit]).any() and torch.isfinite(tau[~hit]).all()
+
+
+def _overflowing(rng, M, N, K, what):
+    """Finite operands whose products, or their sums, leave the binary32 range or stay just below its end."""
+    A = rng.uniform(0.5, 1.0, (M, K)).astype(np.float32)
+    W = rng.uniform(0.5, 1.0, (N, K)).astype(np.float32)
+    if what == "products":                                   # every product is beyond 2^128; pieces with a negative middle one
+        A, W = (1.998 * 2.0 ** 70 * np.sign(A)).astype(np.float32), (2.0 ** 70 * np.sign(W)).astype(np.float32)
+    elif what == "some":                                     # a few products of some rows
+        A[::3, 5::32] = 1.998 * 2.0 ** 70
+        W[::2, 5::32] = 2.0 ** 66
+    else:                                                    # sums of 16 products 2^128 (1 - 2^-8): each hi piece is rounded up to 2^62
+        A[:] = np.float32((1.0 - 0.49 * 2.0 ** -8) * 2.0 ** 62)
+        W[:] = A[0, 0]
+    return A * rng.choice([-1.0, 1.0], A.shape).astype(np.float32), W
+
+
+# the routes of the BF16 scheme: parts, one workgroup per tile, A cut while it is loaded, the walk over tiles; bound and check
+@pytest.mark.parametrize("M,N,K", [(130, 200, 96), (256, 256, 1088), (4200, 4100, 64), (2100, 2060, 1088), (33000, 128, 1056)])
+@pytest.mark.parametrize("what", ["products", "some", "sums"])
+def test_finite_operands_beyond_the_range(tao, M, N, K, what):
+    rng = np.random.Generator(np.random.Philox(M + K))
+    A, W = _overflowing(rng, M, N, K, what)
+    a, w = torch.from_numpy(A).cuda(), torch.from_numpy(W).cuda()
+    tau = tao.tao_bound_linear_split(a, w)
+    # (torch's binary64 product: K additions within K 2^-53)
+    exact = torch.matmul(a.double().abs(), w.double().abs().t().contiguous()) * (K * U / (1 - K * U))
+    slack = (K + 8) * 2.0 ** -53
+    assert not torch.isnan(tau).any()
+    assert (tau.double() >= exact * (1 - slack)).all()
+    assert (tau.double() <= exact * (1 + 1e-6) * (1 + slack))[exact * (1 + 1e-6) < 2.0 ** 128].all()
+    y = torch.zeros_like(tau)
+    c = torch.full_like(tau, 3e38)
+    c[::2] = 1.0
+    want = tao.tao_check_and_profile(c, y, tau)
+    for got in (tao.tao_bound_check_linear(a, w, None, y, c), tao.tao_bound_check_linear(a, w, None, y, c, model=tao.FpModel(flags=tao.FLAG_CHECK_IN_EPILOGUE))):
+        for key in want:
+            assert np.array_equal(np.asarray(got[key]), np.asarray(want[key])), key
+    images = tao.tao_split_operand(a), tao.tao_split_operand(w)
+    assert torch.equal(tao.tao_bound_linear_images(*images, M, N, K), tau)
+
+
+def test_conv_of_finite_operands_beyond_the_range(tao):
+    rng = np.random.Generator(np.random.Philox(5))
+    x = np.abs(rng.standard_normal((32, 34, 34, 32))).astype(np.float32)
+    w = rng.standard_normal((128, 3, 3, 32)).astype(np.float32)
+    x[3, 4:9, 7, 11] = 1.998 * 2.0 ** 70
+    w[5, 1, 1, 11] = 2.0 ** 70
+    x, w = torch.from_numpy(x).cuda(), torch.from_numpy(w).cuda()
+    assert tao.tao_conv2d_split_supported(tuple(x.shape), tuple(w.shape), 1, 1, 1)
+    tau = tao.tao_bound_conv2d_split(x, w, None, 1, 1)
+    cols = torch.nn.functional.unfold(x.double().permute(0, 3, 1, 2), 3, padding=1)           # [batch][C R S][positions]
+    K = 288
+    exact = torch.matmul(cols.transpose(1, 2).contiguous(), w.double().abs().permute(0, 3, 1, 2).reshape(128, -1).t().contiguous())
+    exact = (exact * (K * U / (1 - K * U))).reshape(tau.shape)
+    slack = (K + 8) * 2.0 ** -53
+    assert not torch.isnan(tau).any()
+    assert (tau.double() >= exact * (1 - slack)).all()
+    assert (tau.double() <= exact * (1 + 1e-6) * (1 + slack))[exact * (1 + 1e-6) < 2.0 ** 128].all()
