@@ -29,6 +29,7 @@ struct F64Args {
     const float* A; const float* W; const float* bias; float* tau;
     long M, N, K, lda, ldw, ldt, strideA, strideW, strideT;
     unsigned tiles_m, tiles_n;
+    unsigned items, share;           // tiles of all batch entries, of one XCD
     double c;                        // Gamma(K') guard, upper
     double infl;                     // reciprocal of the lower rounding factor
     double uflow;                    // TAO_FLAG_UNDERFLOW_TERMS
@@ -53,12 +54,15 @@ __global__ __launch_bounds__(WAVES * 64) void absgemm_f64(F64Args p) {
     __shared__ double part[SLOTS][MT * NT * 256];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int r = lane & 15, q = lane >> 4;
-    // Row tiles that share a slab of W go to one XCD (workgroups are dealt round-robin to the eight XCDs, each
-    // with its own L2): workgroup b takes column tile 8 (b / 8 / tiles_m) + b % 8, row tile (b / 8) % tiles_m.
-    const unsigned b8 = blockIdx.x >> 3;
-    const unsigned tm = b8 % p.tiles_m, tn = (b8 / p.tiles_m) * 8 + (blockIdx.x & 7);
-    if (tn >= p.tiles_n) return;                                       // whole workgroup
-    const long z = blockIdx.y;
+    // Workgroups are dealt round-robin to the eight XCDs, each with its own L2: XCD x takes the x-th contiguous eighth of the
+    // tiles, row tiles first, so that those that share a slab of W meet in one.  (By columns -- column tile tn on XCD tn % 8 --
+    // outputs of fewer than eight column tiles left XCDs idle: 65536 x 256 x 16 (M x K x N) 148 us against 22 now, 64
+    // products of 512 x 512 x 64 230 against 60; wide outputs as before.)
+    const unsigned item = (blockIdx.x & 7) * p.share + (blockIdx.x >> 3);
+    if (item >= p.items) return;                                       // whole workgroup
+    const unsigned column = item / p.tiles_m, tm = item - column * p.tiles_m;
+    const unsigned zb = column / p.tiles_n, tn = column - zb * p.tiles_n;
+    const long z = zb;
     const long m0 = (long)tm * (MT * 16), n0 = (long)tn * (NT * 16);
     const float* Ab = p.A + z * p.strideA;
     const float* Wb = p.W + z * p.strideW;
@@ -212,20 +216,26 @@ static F64Tile f64_tile(long M, long N, long batch, int cus) {
     return t;
 }
 
-// Times in us as measured: a workgroup here takes its products at 1 / cus of the rate above and about 1.2 us
-// besides; a round of the FP32 tiles takes 1.5 (64 rows) or 2.95 us per 32 k-steps and about 4 us besides.
-// Measured on both sides of the line (us, here / FP32 tiles): 8 x 4096 x 4096 (M x K x N) 17 / 381, 128 x 4096 x 4096
-// 78 / 195, 255 x 8192 x 8192 537 / 542; 255 x 4096 x 12288 423 / 416, 255 x 256 x 8192 35 / 22, 200 x 64 x 12288 29 / 15.
+// Times in us as measured on both sides of the line at 260 shapes (8 ... 65536 rows, 16 ... 12288 columns, K = 32 ... 8192, up to
+// 1024 batch entries), fitted so that the chosen side is within 1.1 of the better one: a round of workgroups here takes its
+// products at the rate above and, per matrix tile, 0.5 for first loads and the meeting of the wavefronts' sums, up to
+// 0.4 more for a long reduction and 0.2 for a ragged last chunk; a round of the FP32 tiles takes 1.5 (64 rows)
+// or 2.95 per 32 k-steps and 2.5 or 5 besides.  (us, here / FP32 tiles: 8 x 4096 x 4096 (M x K x N) 17 / 381, 128 x 4096 x 4096
+// 75 / 194, 65536 x 512 x 32 62 / 112, 255 x 8192 x 8192 521 / 519; 65536 x 147 x 64 89 / 50, 250 x 1024 x 12288 147 / 111,
+// 145 x 60 x 1065 x 5 entries 17 / 9.)
 bool f64_route(const LinearProblem& p, int cus) {
     if (p.batch >= 65536 || p.K < 1) return false;
     if (p.trans_w && p.N + 16 * p.ldw >= (1L << 30)) return false;     // (32-bit column offsets)
     const F64Tile t = f64_tile(p.M, p.N, p.batch, cus);
+    if (t.rounds * (double)cus >= 0x1p30) return false;                // (32-bit tile numbers)
     const double k = (double)p.K;
-    const double here = t.rounds * (t.mt * t.nt * 512.0 * k * (double)cus / (t.tflops * 1e6) + 1.2);
+    const int matrix_tiles = t.mt * t.nt;
+    const double here = t.rounds * matrix_tiles * (512.0 * k * (double)cus / (t.tflops * 1e6) + 0.5 + 0.375 * std::fmin(k / 1024.0, 1.0) +
+                                                   (p.K % kF64Chunk ? 0.1875 : 0.0));
     auto tiles = [&](long rows) { return (double)((((p.M + rows - 1) / rows) * ((p.N + 127) / 128) * p.batch + cus - 1) / cus); };
     const double groups = (double)((p.K + 31) / 32);
-    double fp32 = tiles(128) * (groups * 2.95 + 4.0);
-    if (p.M > 64) fp32 = std::fmin(fp32, tiles(64) * (groups * 1.5 + 4.0));
+    double fp32 = tiles(128) * (groups * 2.95 + 5.0);
+    if (p.M > 64) fp32 = std::fmin(fp32, tiles(64) * (groups * 1.5 + 2.5));
     return here < fp32;
 }
 
@@ -252,9 +262,9 @@ int f64_launch(const LinearProblem& q, const tao_fp_model& md, double gamma, int
     p.c = widen(gamma * kGuard);
     p.uflow = (md.flags & TAO_FLAG_UNDERFLOW_TERMS) ? widen((double)(q.K + (q.bias ? 1 : 0)) * 0x1p-149) : 0.0;
     const bool vec = aligned(q.A, 16) && q.lda % 4 == 0 && q.strideA % 4 == 0 && aligned(q.W, 16) && q.ldw % 4 == 0 && q.strideW % 4 == 0;
-    const long blocks = (t.tiles_n + 7) / 8 * 8 * t.tiles_m;
-    if (blocks >= (1L << 31)) return TAO_ERR_SHAPE;
-    const dim3 grid((unsigned)blocks, (unsigned)q.batch);
+    p.items = (unsigned)(t.tiles_m * t.tiles_n * q.batch);             // (f64_route: below 2^30)
+    p.share = (p.items + 7) / 8;
+    const dim3 grid(p.share * 8);
     if (q.trans_w) { if (vec) f64_dispatch<true, true>(t, grid, st, p); else f64_dispatch<true, false>(t, grid, st, p); }
     else           { if (vec) f64_dispatch<false, true>(t, grid, st, p); else f64_dispatch<false, false>(t, grid, st, p); }
     return launch_status();

@@ -54,3 +54,28 @@ def test_small_output_products(tao, oracle_mod, M, N, K, bias, trans_w, batch, p
     got = tao.tao_bound_linear(padded(A[0] if batch == 1 else A), padded(W[0] if batch == 1 else W), None if b is None else b.cuda(),
                                trans_w=trans_w)
     assert_bound_parity(got.cpu().numpy(), want, str((M, N, K, bias, trans_w, batch, pad)), rel_tol=tol)
+
+
+# Workgroups are dealt round-robin to the XCDs: outputs of few column tiles with many row tiles or batch entries keep all
+# of them busy only if the tiles, not the columns, are dealt out.  Swapping the operands transposes such an output
+# into a wide one with the same bytes and products (with the columns dealt out it took 3.5 - 7 times as long).
+@pytest.mark.parametrize("M,N,K,batch", [(65536, 16, 256, 1), (50176, 64, 147, 1), (512, 64, 512, 64), (8192, 16, 1024, 8)])
+def test_narrow_outputs_use_the_whole_chip(tao, M, N, K, batch):
+    A, W = torch.randn((batch, M, K), device="cuda"), torch.randn((batch, N, K), device="cuda")
+
+    def us(a, w):
+        out = tao.tao_bound_linear(a, w)
+        times = []
+        for _ in range(5):
+            start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            start.record()
+            for _ in range(20):
+                tao.tao_bound_linear(a, w, out=out)
+            end.record()
+            end.synchronize()
+            times.append(start.elapsed_time(end) * 50)
+        return min(times)
+
+    narrow, wide = us(A, W), us(W, A)
+    print("%d x %d x %d, batch %d: %.1f us, transposed %.1f us" % (M, N, K, batch, narrow, wide))
+    assert narrow < 2 * wide
