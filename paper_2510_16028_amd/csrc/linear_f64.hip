@@ -223,20 +223,30 @@ static F64Tile f64_tile(long M, long N, long batch, int cus) {
 // or 2.95 per 32 k-steps and 2.5 or 5 besides.  (us, here / FP32 tiles: 8 x 4096 x 4096 (M x K x N) 17 / 381, 128 x 4096 x 4096
 // 75 / 194, 65536 x 512 x 32 62 / 112, 255 x 8192 x 8192 521 / 519; 65536 x 147 x 64 89 / 50, 250 x 1024 x 12288 147 / 111,
 // 145 x 60 x 1065 x 5 entries 17 / 9.)
+struct LinearTimes { double f64, fp32; };
+static LinearTimes linear_times(const F64Tile& t, long M, long N, long K, long batch, int cus) {
+    const double k = (double)K;
+    const int matrix_tiles = t.mt * t.nt;
+    LinearTimes r;
+    r.f64 = t.rounds * matrix_tiles * (512.0 * k * (double)cus / (t.tflops * 1e6) + 0.5 + 0.375 * std::fmin(k / 1024.0, 1.0) +
+                                       (K % kF64Chunk ? 0.1875 : 0.0));
+    auto tiles = [&](long rows) { return (double)((((M + rows - 1) / rows) * ((N + 127) / 128) * batch + cus - 1) / cus); };
+    const double groups = (double)((K + 31) / 32);
+    r.fp32 = tiles(128) * (groups * 2.95 + 5.0);
+    if (M > 64) r.fp32 = std::fmin(r.fp32, tiles(64) * (groups * 1.5 + 2.5));
+    return r;
+}
 bool f64_route(const LinearProblem& p, int cus) {
     if (p.batch >= 65536 || p.K < 1) return false;
     if (p.trans_w && p.N + 16 * p.ldw >= (1L << 30)) return false;     // (32-bit column offsets)
     const F64Tile t = f64_tile(p.M, p.N, p.batch, cus);
     if (t.rounds * (double)cus >= 0x1p30) return false;                // (32-bit tile numbers)
-    const double k = (double)p.K;
-    const int matrix_tiles = t.mt * t.nt;
-    const double here = t.rounds * matrix_tiles * (512.0 * k * (double)cus / (t.tflops * 1e6) + 0.5 + 0.375 * std::fmin(k / 1024.0, 1.0) +
-                                                   (p.K % kF64Chunk ? 0.1875 : 0.0));
-    auto tiles = [&](long rows) { return (double)((((p.M + rows - 1) / rows) * ((p.N + 127) / 128) * p.batch + cus - 1) / cus); };
-    const double groups = (double)((p.K + 31) / 32);
-    double fp32 = tiles(128) * (groups * 2.95 + 5.0);
-    if (p.M > 64) fp32 = std::fmin(fp32, tiles(64) * (groups * 1.5 + 2.5));
-    return here < fp32;
+    const LinearTimes r = linear_times(t, p.M, p.N, p.K, p.batch, cus);
+    return r.f64 < r.fp32;
+}
+double linear_us(long M, long N, long K, long batch, int cus) {
+    const LinearTimes r = linear_times(f64_tile(M, N, batch, cus), M, N, K, batch, cus);
+    return std::fmin(r.f64, r.fp32);
 }
 
 template <bool TRANS, bool VEC>

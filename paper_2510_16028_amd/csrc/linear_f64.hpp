@@ -12,6 +12,7 @@ struct LinearProblem {               // arguments of tao_bound_linear, validated
     long batch, strideA, strideW, strideT;
 };
 bool f64_route(const LinearProblem& p, int cus);          // is this kernel the faster one?
+double linear_us(long M, long N, long K, long batch, int cus);     // what tao_bound_linear takes, contiguous operands
 int f64_launch(const LinearProblem& p, const tao_fp_model& md, double gamma, int cus, hipStream_t st);
 
 }  // namespace tao

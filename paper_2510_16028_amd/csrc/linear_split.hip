@@ -42,6 +42,7 @@
 #include <vector>
 #include "tao_device.hpp"
 #include "tao_host.hpp"
+#include "linear_f64.hpp"
 #include "tao_check.hpp"
 
 namespace tao {
@@ -1035,25 +1036,31 @@ size_t tao_check_linear_images_workspace_bytes(long M, long N, long K, long batc
 int tao_linear_split_preferred(long M, long N, long K, long batch) {
     // The BF16 path has one tile shape (128 x 128) and pays a pre-pass of 10 bytes per operand
     // element: it wins when the tiles fill the chip and each operand slab is shared by at least
-    // two of them (measured: 1.2 - 1.4 x on such shapes, slower on 128-column or half-empty launches).
-    // Launches with fewer tiles than compute units cut the reduction into parts; they count when the
+    // two of them.  Launches with fewer tiles than compute units cut the reduction into parts; they count when the
     // parts fill the chip.
     if (M <= 0 || N <= 0 || K <= 0 || batch <= 0) return 0;
     const long tiles = ((M + tao::STILE - 1) / tao::STILE) * ((N + tao::STILE - 1) / tao::STILE) * batch;
     // (a single column tile pays when its A operand can be split while it is loaded: a long reduction of whole groups)
-    // (even half a column tile pays where the tiles are so few that the reduction is cut into four parts or more:
-    // bound and check of 12 x 512 x 64 outputs over K = 512 take 0.041 against 0.054 ms, of 4096 x 128 over K = 4096
-    // 0.087 against 0.208 ms; with 128 tiles in two parts -- 8 x 2048 x 128 over K = 2048 -- the pre-pass over A still
-    // outweighs the gain: 0.170 against 0.132 ms)
+    // (even half a column tile counts where the tiles are so few that the reduction is cut into four parts or more; with 128
+    // tiles in two parts -- 8 x 2048 x 128 over K = 2048 -- the pre-pass over A outweighs the gain: 0.137 against 0.111 ms)
     const bool n_ok = N >= 2 * tao::STILE || (N >= tao::STILE && K % tao::SBK == 0 && K / tao::SBK > tao::kWalkMaxGroups &&
                                               tao::split_k_parts(M, N, K, batch) < 2) ||
                       (N >= tao::STILE / 2 && tao::split_k_parts(M, N, K, batch) >= 4);
-    // (a long reduction cut into parts also pays on half the chip: the FP32 path would leave its few
-    // tiles on as few compute units for the whole reduction -- measured 0.092 against 0.147 ms on
-    // 512 x 768 x 3072, where shorter reductions of that size stay faster on the FP32 path)
+    // (a long reduction cut into parts also pays on half the chip: 512 x 768 x 3072 0.045 against 0.057 ms)
     const long parts = tao::split_k_parts(M, N, K, batch), cus = tao::device_cus();
     const bool fills = tiles * parts >= cus || (parts >= 2 && tiles * parts * 2 >= cus);
-    return fills && M >= 2 * tao::STILE && n_ok && K >= 64;
+    if (!(fills && M >= 2 * tao::STILE && n_ok && K >= 64)) return 0;
+    // What is left is small enough in places for the binary64 matrix cores of tao_bound_linear, which need no pre-pass and no parts
+    // (us, BF16 path / tao_bound_linear: 12 x 512 x 64 over K = 512 28 / 17, 1024 x 512 over 512 29 / 18, 256 x 1024 over 1024
+    // 30 / 15, 4 x 1024 x 64 over 1024 35 / 15; 512 x 3072 over 768 42 / 42, 1024 x 1024 over 1024 38 / 55).  Estimate of the BF16
+    // path, fitted to 51 shapes: launches, operand images, groups of the walk, partial sums.  The line lies below equal times,
+    // as the checked entry points save a launch and the bound's traffic on this path: 512 x 768 over 768 takes 28 / 21, with
+    // the check 35 / 31 (this path kept), 512 x 512 over 4096 45 / 44, with the check 53 / 54.
+    const double groups = (double)((K + tao::SBK - 1) / tao::SBK), elements = ((double)M + (double)N) * (double)K * (double)batch;
+    const double rounds = std::ceil((double)(tiles * parts) / (double)cus);
+    const double split_us = 14.0 + 1.47e-6 * elements + 1.56 * rounds * std::ceil(groups / (double)parts) +
+                            (parts >= 2 ? 2.0 + 1.84e-6 * (double)parts * (double)M * (double)N * (double)batch : 0.0);
+    return tao::linear_us(M, N, K, batch, (int)cus) >= 0.69 * split_us;
 }
 
 }  // extern "C"
