@@ -152,3 +152,43 @@ def test_act_factor_below_the_normal_range(tao):
     got = tao.tao_bound_check_act(tao.ACT_GELU_ERF, x, y, c, model=model)
     for key in want:
         assert np.array_equal(np.asarray(got[key]), np.asarray(want[key])), key
+
+
+def _padded(t, ld, offset):
+    """The same values with a leading dimension beyond the row, `offset` floats into it; what lies between is NaN."""
+    wide = torch.full((t.shape[0], ld), float("nan"), device=t.device)
+    wide[:, offset:offset + t.shape[1]] = t
+    return wide[:, offset:offset + t.shape[1]]
+
+
+# rows with ld > cols on the quick routes: whole aligned vectors, padded; rows misaligned by 4 bytes; ragged rows
+@pytest.mark.parametrize("kind", ["softmax", "layernorm", "rmsnorm"])
+@pytest.mark.parametrize("rows,cols,ld,offset", [(16384, 128, 136, 0), (16384, 128, 132, 1), (16385, 511, 513, 0), (16390, 512, 520, 4), (8192, 768, 772, 0),
+                                                 (8193, 1021, 1030, 2), (8192, 1024, 1028, 0), (16384, 1028, 1032, 0), (16384, 2048, 2052, 0),
+                                                 (16385, 2048, 2053, 1), (4096, 4096, 4100, 0), (2048, 8190, 8193, 1)])
+def test_strided_rows(tao, kind, rows, cols, ld, offset):
+    g = torch.Generator(device="cuda").manual_seed(rows + cols + ld)
+    x = torch.randn((rows, cols), generator=g, device="cuda")
+    if kind == "softmax":
+        x[::3, cols // 2:] = float("-inf")
+        y = torch.softmax(x, -1)
+        tau = tao.tao_bound_softmax(x, y)
+    else:
+        k = tao.NORM_LAYERNORM if kind == "layernorm" else tao.NORM_RMSNORM
+        gamma = 1 + 0.1 * torch.randn(cols, generator=g, device="cuda")
+        y = ((x - (x.mean(-1, keepdim=True) if kind == "layernorm" else 0)) * torch.rsqrt((x * x).mean(-1, keepdim=True) + 1e-5) * gamma)
+        tau = tao.tao_bound_norm(k, x, y, gamma, None, eps=1e-5)
+    # claims two output steps and more inside or outside the bound, so that a last-bit difference between the two kernels'
+    # bounds (rows added in another order) cannot move one across it
+    step = (torch.nextafter(y.abs(), torch.full_like(y, float("inf"))) - y.abs()).double()
+    f = torch.randint(0, 8, y.shape, generator=g, device="cuda").double()
+    t = tau.double()
+    c = (y.double() + torch.where(f == 0, t + 2 * step, torch.where(f == 1, (t - 2 * step).clamp(min=0), t * (f - 4) / 4))).float()
+    keep = (((c.double() - y.double()).abs() - t).abs() > 1e-6 * t) | (t == 0)
+    c = torch.where(keep, c, y)
+    want = tao.tao_check_and_profile(c, y, tau)
+    assert want["violations"] > 0
+    xs, ys, cs = (_padded(v, ld, offset) for v in (x, y, c))
+    got = tao.tao_bound_check_softmax(xs, ys, cs) if kind == "softmax" else tao.tao_bound_check_norm(k, xs, ys, cs, gamma, None, eps=1e-5)
+    for key in want:
+        assert np.array_equal(np.asarray(got[key]), np.asarray(want[key])), key
