@@ -76,8 +76,9 @@ enum {
                                        (App. A.1 excludes it); a product sum that comes out as exactly zero is
                                        then no longer taken for an exact zero (see tao_bound_linear); the
                                        result is the reference value or the next binary32 value above it */
-    TAO_FLAG_FAST_ACCUM = 2u,       /* linear: one FP32 accumulation chain over K; still an upper
-                                       bound, but looser than the default by about 2*K*u relative */
+    TAO_FLAG_FAST_ACCUM = 2u,       /* linear: one FP32 accumulation chain over K where the FP32 tiles run; still an
+                                       upper bound, but looser than the default by about 2*K*u relative
+                                       (small outputs, on the binary64 matrix cores, keep the default bound) */
     TAO_FLAG_CHECK_IN_EPILOGUE = 4u /* tao_bound_check_linear: check in the matrix kernel's epilogue for
                                        every reduction length (no stored bound, its workspace unused);
                                        same result, slower for short reductions */
@@ -375,8 +376,10 @@ int tao_bound_rope(const float *x, const float *cos_table, const float *sin_tabl
                    const tao_fp_model *model, void *stream);
 
 /* tao_bound_norm checked on the spot, for kind TAO_NORM_LAYERNORM and TAO_NORM_RMSNORM (TAO_ERR_KIND
- * otherwise): *out receives exactly what tao_check_and_profile(claimed, y_ref, tau, ...) returns for the
- * tau of tao_bound_norm(kind, x, y_ref, gamma, beta, eps, ...), never stored.  claimed: DEVICE, laid out
+ * otherwise): *out receives what tao_check_and_profile(claimed, y_ref, tau, ...) returns for the
+ * tau of tao_bound_norm(kind, x, y_ref, gamma, beta, eps, ...), never stored.  The two may add a row in different orders:
+ * an element's bound may be the binary32 neighbour of the stored one (either is within the bound's contract), so
+ * `violations` and `accept` may differ for claims within that step of alpha tau; the other fields do not depend on tau.  claimed: DEVICE, laid out
  * like x and y_ref (rows x cols, leading dimension ld).  ws / ws_bytes: DEVICE scratch of at least
  * tao_check_workspace_bytes(rows * cols), 256-byte aligned. */
 int tao_bound_check_norm(int kind, const float *x, const float *y_ref, const float *gamma, const float *beta,
@@ -439,8 +442,8 @@ int tao_bound_check_act(int kind, const float *x, const float *x2, const float *
 /* Softmax bound and leaf check in one pass (Sec. 3.1 softmax template, Sec. 5.4
  * check, Sec. 5.3 profile): the result is, field by field, that of
  *     tao_bound_softmax(x, y_ref, tau, ...); tao_check_and_profile(claimed, y_ref, tau, ...)
- * but tau lives only in registers (rounded to binary32 as it would have been
- * stored): the pass reads x, y_ref and claimed once and writes nothing but the
+ * (up to a binary32 step in tau where the two add a row in different orders, as for
+ * tao_bound_check_norm), but tau lives only in registers, rounded to binary32: the pass reads x, y_ref and claimed once and writes nothing but the
  * profile.  x, y_ref, claimed: [rows][cols], row stride ld (n = rows * cols).
  * alpha, eps_rel, out, ws, ws_bytes: as for tao_check_and_profile (workspace of
  * tao_check_workspace_bytes(n)).  Errors as for the two calls. */

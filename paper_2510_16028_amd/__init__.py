@@ -777,8 +777,8 @@ def tao_bound_check_rope(x, cos, sin, y_ref, claimed, inner=1, interleaved=False
 
 def tao_bound_check_softmax(x, y_ref, claimed, alpha=1.0, eps_rel=1e-12, model=None, out=None, ws=None,
                             readback=True):
-    """The softmax bound checked against `claimed` in one pass; same result as tao_bound_softmax
-    followed by tao_check_and_profile(claimed, y_ref, tau), without a stored tau."""
+    """The softmax bound checked against `claimed` in one pass; the result of tao_bound_softmax
+    followed by tao_check_and_profile(claimed, y_ref, tau), up to a binary32 step in tau, without a stored tau."""
     x = _dev(x, "x"); y_ref = _dev(y_ref, "y_ref"); claimed = _dev(claimed, "claimed")
     if x.shape != y_ref.shape or x.stride() != y_ref.stride() or claimed.shape != x.shape or claimed.stride() != x.stride():
         raise ValueError("x, y_ref and claimed must have the same shape and strides")

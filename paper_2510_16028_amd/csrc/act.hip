@@ -126,7 +126,7 @@ __device__ __forceinline__ float act_below(float x, float y, const ActConsts& k)
         const float p = (float)kBetaLo * ax * fmaf((float)kCubicLo * ax, ax, 1.f);
         return fmaf(0.5f * ax * (float)k.c_tanh_u, fminf(p, 1.f), ay * (float)k.fresh2);
     }
-    return KIND == TAO_ACT_SILU ? ay * (float)k.silu_f : KIND == kKindScale ? ay * (float)k.scale_f : 0.f;
+    return ay * (float)(KIND == TAO_ACT_SILU ? k.silu_f : k.scale_f);
 }
 
 // The same bound checked on the spot (Sec. 5.4 / 5.3): the structure of the streaming check pass
@@ -153,7 +153,8 @@ __global__ __launch_bounds__(kCheckThreads) void act_check(
     const int rep = tid & (kReplicas - 1);
     const long nvec = vec_ok ? (n >> 2) : 0;
     const long stride = (long)gridDim.x * kCheckThreads;
-    if (QUICK) {
+    if constexpr (QUICK) {
+        static_assert(KIND != TAO_ACT_RELU, "exact operators have no estimate");
         const QuickCheck qc(k.quick_alpha, eps_rel);
         unsigned known = 0;
         int exact = 0;
@@ -386,21 +387,18 @@ int tao_bound_check_act(int kind, const float* x, const float* x2, const float* 
     dim3 grid((unsigned)nblocks), blk(kCheckThreads);
     // (correctly rounded and exact operators mostly find equal values, for which the exact way is the shorter one:
     // 25 M products 39.0 against 41.4 us)
-    const bool rounded = kind == TAO_ACT_MUL || kind == TAO_ACT_ADD || kind == TAO_ACT_SUB || kind == TAO_ACT_SQRT ||
-                         kind == TAO_ACT_RELU || kind == TAO_ACT_EXACT;
+    const bool rounded = kind == TAO_ACT_MUL || kind == TAO_ACT_ADD || kind == TAO_ACT_SUB || kind == TAO_ACT_SQRT;
     const bool quick = !rounded && n >= (needs_x ? 16L : 32L) * kMaxCheckBlocks * kCheckThreads;
-#define TAO_ACT_CHECK(K) \
-    do { \
-        if (quick) hipLaunchKernelGGL((act_check<K, true>), grid, blk, 0, st, x, y_ref, claimed, n, vec_ok, k, alpha, eps_rel, w.hist, w.coarse, w.stats); \
-        else       hipLaunchKernelGGL((act_check<K, false>), grid, blk, 0, st, x, y_ref, claimed, n, vec_ok, k, alpha, eps_rel, w.hist, w.coarse, w.stats); \
-    } while (0)
+#define TAO_ACT_CHECK_Q(K, Q) hipLaunchKernelGGL((act_check<K, Q>), grid, blk, 0, st, x, y_ref, claimed, n, vec_ok, k, alpha, eps_rel, w.hist, w.coarse, w.stats)
+#define TAO_ACT_CHECK(K) do { if (quick) TAO_ACT_CHECK_Q(K, true); else TAO_ACT_CHECK_Q(K, false); } while (0)
     switch (kind) {
         case TAO_ACT_GELU_ERF: TAO_ACT_CHECK(TAO_ACT_GELU_ERF); break;
         case TAO_ACT_GELU_TANH: TAO_ACT_CHECK(TAO_ACT_GELU_TANH); break;
         case TAO_ACT_SILU: case TAO_ACT_SIGMOID: TAO_ACT_CHECK(TAO_ACT_SILU); break;
-        case TAO_ACT_RELU: case TAO_ACT_EXACT: TAO_ACT_CHECK(TAO_ACT_RELU); break;
+        case TAO_ACT_RELU: case TAO_ACT_EXACT: TAO_ACT_CHECK_Q(TAO_ACT_RELU, false); break;
         default: TAO_ACT_CHECK(kKindScale); break;
     }
+#undef TAO_ACT_CHECK_Q
 #undef TAO_ACT_CHECK
     launch_profile_reduce(w, nblocks, (unsigned long long)n, out, st);
     return launch_status();

@@ -155,7 +155,6 @@ int tao_check_and_profile(const float* claimed, const float* ref, const float* t
     if (n >= (1L << 36)) return TAO_ERR_SHAPE;   // 32-bit per-workgroup counters
     hipStream_t st = (hipStream_t)stream;
     const int vec_ok = aligned(claimed, 16) && aligned(ref, 16) && aligned(tau, 16);
-    // 16 elements (four 16-byte vectors) per thread before another workgroup is worth it
     // one 16-byte vector per thread before another workgroup is worth it: up to a million elements the pass takes as long as
     // one thread's chain of loads, divisions and atomics (with four vectors per thread, bound and reduction included: 8192
     // elements 10.5 against 9.3 us, 262144 13.5 against 9.8, a million 14.4 against 11.0)

@@ -1118,9 +1118,10 @@ static int split_core(const unsigned short* A3, const unsigned short* W3, const 
         // instructions per element on a compute unit whose matrix cores idle meanwhile), while the
         // streaming check spends the same arithmetic under its loads and the plain bound walks its
         // tiles.  Up to K = 1024 the bound is therefore stored (in the workspace unless the caller
-        // wants it) and checked by that pass: the same results, field for field, 1 - 8 % sooner
-        // (measured at K = 128 ... 1024); beyond, the two routes take the same time and the epilogue
-        // saves the traffic of the stored bound.
+        // wants it) and checked by that pass: the same results, field for field, 5 - 9 % sooner at K = 128 ... 512
+        // (8 x 8192 x 2048 over 128 608 against 666 us) and the same within 2 % at 1024 (2048 x 12288 410 / 419, 4096 x 4096 277 / 274);
+        // beyond, the two routes take the same time (2048 x 12288 over 2048 747 / 745, over 4096 1422 / 1416) and the epilogue
+        // saves the memory of the stored bound.
         // (A reduction cut into parts is checked by the pass that adds the parts, whatever its length.)
         two_pass = parts < 2 && K < kEpilogueCheckMinK && !(md.flags & TAO_FLAG_CHECK_IN_EPILOGUE) &&
                    chk->ldy == N && (batch == 1 || chk->strideY == M * N);

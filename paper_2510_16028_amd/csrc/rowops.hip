@@ -167,7 +167,7 @@ __global__ __launch_bounds__(kRowThreads) void softmax_bound(
 }
 
 // ---- softmax bound checked in registers (the bound is never stored) --------------------------
-// Same arithmetic as softmax_bound element by element, followed by the leaf check of
+// Same arithmetic as softmax_bound element by element (a row's sums in an order of their own, see norm_check), followed by the leaf check of
 // tao_check_and_profile on (claimed, y, tau) with tau first rounded to binary32 as it would have
 // been stored.  Workgroups of 1024 threads walk the rows (1024 / TPR at a time), keep the
 // histogram of relative errors in LDS and leave one partial per workgroup, like the streaming
@@ -705,8 +705,9 @@ __global__ __launch_bounds__(kRowThreads) void rmsnorm_bound_noy(
 
 // LayerNorm / RMSNorm bounds checked on the spot: the structure of softmax_check (1024-thread
 // workgroups that walk the rows, kCheckThreads / TPR rows at a time, one partial histogram each)
-// with the arithmetic of layernorm_body / rmsnorm_bound, operation for operation, so that the bound
-// compared in registers is the binary32 value the bound kernels store.  FULL, QUICK: as there.
+// with the arithmetic of layernorm_body / rmsnorm_bound per element.  A row's sums may be added in another order (row groups
+// of another size, ragged rows read column by column): the bound compared is the binary32 value the bound kernels
+// store or, rarely, its neighbour.  FULL, QUICK: as there.
 // What bounds it: HBM for many rows (32768 x 768: LayerNorm 180 -> 90 us, RMSNorm 128 -> 65 us; LayerNorm 8192 x 2048 170 -> 67 us,
 // whose rows are now kept instead of read again), the chain of one row -- loads, two reductions, a square root and divisions in
 // binary64 -- for few (2048 x 4096 RMSNorm 34.4 -> 32.3 us), which is why the next rows are requested early.
