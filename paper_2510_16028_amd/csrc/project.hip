@@ -10,8 +10,8 @@
 // needs no ranks at all.  The elements of the other bins, the candidates, are sorted; a candidate's rank is
 // its place among them plus the number of others in lower bins.  With a heavy upper tail over a calibrated
 // threshold that is a tenth of the tensor; where every bin is a candidate the histogram is the only extra work.
-// (8.4 M elements: none capped 257 -> 77 us, a heavy tail against calibrated thresholds 260 -> 106 us, all capped 343 -> 355 us;
-// 67 M: 1608 -> 343, 1629 -> 376, 2405 -> 2479 us.)  What bounds it now: three passes over delta and some fifteen launches.
+// (8.4 M elements: none capped 257 -> 74 us, a heavy tail against calibrated thresholds 260 -> 104 us, all capped 343 -> 350 us;
+// 67 M: 1608 -> 325, 1621 -> 354, 2406 -> 2415 us.)  What bounds it now: three passes over delta and some fifteen launches.
 // The sort is a least-significant-digit radix sort of the 31 magnitude bits (a non-negative binary32 orders like
 // its bit pattern, NaN above infinity) in four 8-bit passes; the payload is the element's index
 // with its sign bit on top.  Per pass: count (digit histogram per tile), scan (of each digit's counters over
@@ -195,16 +195,18 @@ __global__ void __launch_bounds__(256) project_clip_kernel(const float* __restri
 // What a pass works on: all of the tensor in the first one, then the candidates.  Few candidates take tiles of a
 // quarter or half the size: some 768 tiles, to fill the chip, but no more than the tensor's own (the grid and the
 // counters are sized for those).
-struct PassShape { long n; int items; long tiles; };           // elements, elements per thread, tiles
+struct PassShape { long n; int items; long tiles, row; };      // elements, elements per thread, tiles; counters per digit (16-byte rows)
+inline __host__ __device__ long counter_row(long tiles) { return (tiles + 3) & ~3L; }
 template <bool FIRST>
 __device__ __forceinline__ PassShape pass_shape(long all, const MagTable* __restrict__ mag) {
-    PassShape p = {all, kSortItems, 0};
+    PassShape p = {all, kSortItems, 0, 0};
     if (!FIRST) {
         p.n = (long)mag->candidates;
         p.items = p.n <= 768L * kSortThreads * 4 && p.n * 4 <= all ? 4 : p.n <= 768L * kSortThreads * 8 && p.n * 2 <= all ? 8 : kSortItems;
     }
     const int tile = p.items * kSortThreads;
     p.tiles = (p.n + tile - 1) / tile;
+    p.row = counter_row(p.tiles);
     return p;
 }
 
@@ -215,7 +217,7 @@ __device__ __forceinline__ long tile_of_block(long tiles_per_xcd) {
     return i < tiles_per_xcd ? (long)(blockIdx.x % kXcds) * tiles_per_xcd + i : -1;
 }
 
-// Digit histogram of every tile: hist[digit * tiles + tile].  Counting does not depend on the
+// Digit histogram of every tile: hist[digit * row + tile].  Counting does not depend on the
 // order inside the tile, so a thread takes four runs of four consecutive keys (16-byte loads, all
 // issued before the first is used).  The first pass also copies delta to out on the way.
 template <bool FIRST>
@@ -291,11 +293,10 @@ __global__ void __launch_bounds__(kSortThreads) radix_count(const float* delta, 
     for (int w = 0; w < kSortWaves; ++w)
 #pragma unroll
         for (int c = 0; c < kCountCopies; ++c) total += cnt[w][c][d];
-    hist[(long)d * tiles + tile] = total;
+    hist[(long)d * shape.row + tile] = total;
 }
 
-// Exclusive scan of `count` 32-bit counters in three steps (chunk sums, scan of the sums by one
-// workgroup, rescan of each chunk with its offset).
+// Exclusive scan of one value per thread over the workgroup; ends with a barrier.
 __device__ __forceinline__ unsigned block_exclusive_scan(unsigned v, unsigned* wave_tot, unsigned& block_total) {
     const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
     unsigned inc = v;
@@ -348,25 +349,38 @@ __global__ void __launch_bounds__(1024) find_candidates(const CapTable* __restri
 template <bool FIRST>
 __global__ void __launch_bounds__(kSortThreads) scan_digit(unsigned* __restrict__ hist, long n, MagTable* __restrict__ mag) {
     __shared__ unsigned wave_tot[kSortWaves];
-    const long tiles = pass_shape<FIRST>(n, mag).tiles;
-    unsigned* c = hist + (long)blockIdx.x * tiles;
+    const PassShape shape = pass_shape<FIRST>(n, mag);
+    const long tiles = shape.tiles;
+    unsigned* c = hist + (long)blockIdx.x * shape.row;
     unsigned carry = 0;
+    // 16 consecutive counters per thread, in 16-byte loads (16384 tiles: 34 us counter by counter, 14 so), or one
+    const bool few = tiles <= kSortThreads;
     for (long base = 0; base < tiles; base += kScanChunk) {     // uniform trip count
-        // 16 consecutive counters per thread (several steps), or one
-        const bool few = tiles <= kSortThreads;
         const long e0 = base + (few ? (long)threadIdx.x : (long)threadIdx.x * 16);
         unsigned v[16], s = 0;
+        if (!few && e0 + 16 <= tiles) {
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            v[i] = (!few || i == 0) && e0 + i < tiles ? c[e0 + i] : 0u;
-            s += v[i];
+            for (int q = 0; q < 4; ++q) {
+                const uint4 r = reinterpret_cast<const uint4*>(c + e0)[q];
+                v[4 * q] = r.x; v[4 * q + 1] = r.y; v[4 * q + 2] = r.z; v[4 * q + 3] = r.w;
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < 16; ++i) v[i] = (!few || i == 0) && e0 + i < tiles ? c[e0 + i] : 0u;
         }
+#pragma unroll
+        for (int i = 0; i < 16; ++i) s += v[i];
         unsigned total;
         unsigned run = carry + block_exclusive_scan(s, wave_tot, total);
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            if ((!few || i == 0) && e0 + i < tiles) c[e0 + i] = run;
-            run += v[i];
+        for (int i = 0; i < 16; ++i) { const unsigned t = v[i]; v[i] = run; run += t; }
+        if (!few && e0 + 16 <= tiles) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) reinterpret_cast<uint4*>(c + e0)[q] = make_uint4(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]);
+        } else {
+#pragma unroll
+            for (int i = 0; i < 16; ++i)
+                if ((!few || i == 0) && e0 + i < tiles) c[e0 + i] = v[i];
         }
         carry += total;
     }
@@ -467,7 +481,7 @@ __device__ __forceinline__ void cap_and_store(const CapTable& tab, unsigned rank
     out[idx] = __uint_as_float(__float_as_uint(star) | (v & 0x80000000u));
 }
 
-// Scatter pass.  `hist` holds the scanned counters: hist[d * tiles + tile] elements with digit d lie in the tiles before.
+// Scatter pass.  `hist` holds the scanned counters: hist[d * row + tile] elements with digit d lie in the tiles before.
 // The first pass closes up the tile's candidates in LDS, in order, and sorts those.
 template <bool FIRST, bool LAST>
 __global__ void __launch_bounds__(kSortThreads, LAST ? 3 : 4) radix_scatter(const float* delta,
@@ -550,7 +564,7 @@ __global__ void __launch_bounds__(kSortThreads, LAST ? 3 : 4) radix_scatter(cons
     {
         const unsigned digit_total = mag->digit_total[threadIdx.x];                              // kSortThreads == kRadix
         unsigned sum;
-        const unsigned first_dest = block_exclusive_scan(digit_total, sh.wave_tot, sum) + hist[(long)threadIdx.x * tiles + tile];
+        const unsigned first_dest = block_exclusive_scan(digit_total, sh.wave_tot, sum) + hist[(long)threadIdx.x * shape.row + tile];
         sh.dest_off[threadIdx.x] = first_dest - sh.tile_excl[threadIdx.x];
         if (LAST) {
             // Caps do not decrease with the rank: the exact cap of a rank that all elements of this tile with digit d
@@ -626,7 +640,7 @@ inline size_t round256(size_t b) { return (b + 255) / 256 * 256; }
 
 inline size_t carve_project(long n, char* ws, ProjectWorkspace* w) {
     const long tiles = (n + kSortTile - 1) / kSortTile;
-    const long counters = tiles * kRadix;
+    const long counters = counter_row(tiles) * kRadix;
     size_t off = 0;
     auto take = [&](size_t bytes) { char* p = ws ? ws + off : nullptr; off += round256(bytes); return p; };
     char* tab = take(sizeof(CapTable));

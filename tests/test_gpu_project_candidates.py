@@ -46,3 +46,20 @@ def test_empirical_with_candidates_in_some_bins(tao, oracle_mod, n, share):
     assert _same(got, want)
     inplace = tao.tao_project_empirical(x, torch.from_numpy(thr).cuda(), 1.0, out=x).cpu().numpy()
     assert _same(inplace, want)
+
+
+# tiles (4096 elements) around what the scan of the tiles' counters takes singly, in fours and sixteens, and in one step
+@pytest.mark.parametrize("tiles,missing", [(256, 0), (257, 4095), (259, 0), (272, 17), (273, 0), (4096, 1), (4099, 3000)])
+@pytest.mark.parametrize("share", ["half", "all"])
+def test_empirical_tile_counts(tao, oracle_mod, tiles, missing, share):
+    n = tiles * 4096 - missing
+    rng = np.random.Generator(np.random.Philox(tiles))
+    d = (rng.standard_normal(n, dtype=np.float32) * np.float32(1e-6)) * np.exp(rng.standard_normal(n, dtype=np.float32))
+    d[rng.integers(0, n, n // 16)] = d[rng.integers(0, n, n // 16)]          # ties
+    P = [1] + list(range(5, 100, 5)) + [99, 100]
+    a = np.sort(np.abs(d))
+    thr = np.array([a[min(n - 1, int(n * p / 100))] for p in P], np.float32)
+    thr = (thr * (np.where(np.arange(22) % 4 < 2, 1.5, 0.7) if share == "half" else 0.0)).astype(np.float32)
+    want = oracle_mod.project_empirical(d, thr, 1.0)
+    got = tao.tao_project_empirical(torch.from_numpy(d).cuda(), torch.from_numpy(thr).cuda(), 1.0).cpu().numpy()
+    assert _same(got, want)
