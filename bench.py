@@ -134,7 +134,7 @@ class PlannedOp:
         if self.conv:
             return ("bf16_split (patch matrix gathered while loaded)" + ("+check" if self.fused else "")) if self.split else "fp32 (implicit patch matrix)"
         if not self.split:
-            return "fp32"
+            return "fp32 tiles or binary64 matrix cores (tao_bound_linear)"
         return "bf16_split" + ("+prepared_w" if self.prepared else "") + ("+check" if self.fused else "")
 
     def bound(self):
