@@ -100,3 +100,18 @@ def test_fp32_tiles_on_vanishing_products(tao, oracle_mod):
     got = tao.tao_bound_linear(A, W, model=tao.FpModel(flags=tao.FLAG_UNDERFLOW_TERMS))
     g, o = _compare(oracle_mod, got, A, W, None, False, rng, model=oracle_mod.Model(flags=1))
     assert (g >= o).all() and (g <= o + np.float32(2.0 ** -149)).all()
+
+
+@pytest.mark.parametrize("M,N,K,exact", [(1300, 1500, 200, False), (2048, 2048, 64, False), (40, 60, 200, True)])
+def test_finite_operands_whose_products_overflow(tao, oracle_mod, M, N, K, exact):
+    """Products beyond 2^128 in some rows and columns: +inf on the FP32 tiles, the bound itself on the binary64 route; never NaN,
+    never below the reference, and the other elements as always."""
+    rng = np.random.Generator(np.random.Philox(11))
+    A, W = _operands(rng, M, N, K, False, 1, 0, 0)
+    A[::3, 5::32] = 1.998 * 2.0 ** 70
+    W[::2, 5::32] = -2.0 ** 66
+    g, o = _compare(oracle_mod, tao.tao_bound_linear(A, W), A, W, None, False, rng)
+    assert not np.isnan(g).any() and (g >= o).all()
+    fits = np.isfinite(g) if not exact else np.isfinite(o)
+    assert (g[fits] <= o[fits].astype(np.float64) * (1 + 1e-6)).all()
+    assert np.isfinite(g[:, 1::2]).all()                     # (columns without the large operand)
