@@ -216,36 +216,44 @@ static F64Tile f64_tile(long M, long N, long batch, int cus) {
     return t;
 }
 
-// Times in us as measured on both sides of the line at 260 shapes (8 ... 65536 rows, 16 ... 12288 columns, K = 32 ... 8192, up to
-// 1024 batch entries), fitted so that the chosen side is within 1.1 of the better one: a round of workgroups here takes its
-// products at the rate above and, per matrix tile, 0.5 for first loads and the meeting of the wavefronts' sums, up to
-// 0.4 more for a long reduction and 0.2 for a ragged last chunk; a round of the FP32 tiles takes 1.5 (64 rows)
-// or 2.95 per 32 k-steps and 2.5 or 5 besides.  (us, here / FP32 tiles: 8 x 4096 x 4096 (M x K x N) 17 / 381, 128 x 4096 x 4096
-// 75 / 194, 65536 x 512 x 32 62 / 112, 255 x 8192 x 8192 521 / 519; 65536 x 147 x 64 89 / 50, 250 x 1024 x 12288 147 / 111,
+// Times in us as measured on both sides of the line at 480 shapes (8 ... 65536 rows, 16 ... 12288 columns, K = 32 ... 8192, up to
+// 1024 batch entries), fitted so that the chosen side is within 1.15 of the better one, mostly the better one: a round of
+// workgroups here takes its products at 1.09 times the rate above and, per matrix tile, 0.38 for first loads and the meeting of the
+// wavefronts' sums, up to 0.6 more for a long reduction and 0.48 for a ragged last chunk; a round of the FP32 tiles
+// takes 1.5 (64 rows) or 2.95 per 32 k-steps, 1.18 times that with ragged tiles and 1.43 times with unaligned rows, and 2.5 or 2
+// besides.  (us, here / FP32 tiles: 8 x 4096 x 4096 (M x K x N) 17 / 381, 128 x 4096 x 4096 75 / 194, 65536 x 512 x 32 62 / 112,
+// 1000 x 1000 x 1000 55 / 66, 255 x 8192 x 8192 521 / 519; 65536 x 147 x 64 89 / 50, 250 x 1024 x 12288 147 / 111,
 // 145 x 60 x 1065 x 5 entries 17 / 9.)
 struct LinearTimes { double f64, fp32; };
-static LinearTimes linear_times(const F64Tile& t, long M, long N, long K, long batch, int cus) {
+static LinearTimes linear_times(const F64Tile& t, long M, long N, long K, long batch, bool vec, int cus) {
     const double k = (double)K;
     const int matrix_tiles = t.mt * t.nt;
     LinearTimes r;
-    r.f64 = t.rounds * matrix_tiles * (512.0 * k * (double)cus / (t.tflops * 1e6) + 0.5 + 0.375 * std::fmin(k / 1024.0, 1.0) +
-                                       (K % kF64Chunk ? 0.1875 : 0.0));
-    auto tiles = [&](long rows) { return (double)((((M + rows - 1) / rows) * ((N + 127) / 128) * batch + cus - 1) / cus); };
-    const double groups = (double)((K + 31) / 32);
-    r.fp32 = tiles(128) * (groups * 2.95 + 5.0);
-    if (M > 64) r.fp32 = std::fmin(r.fp32, tiles(64) * (groups * 1.5 + 2.5));
+    r.f64 = t.rounds * matrix_tiles * (0.92 * 512.0 * k * (double)cus / (t.tflops * 1e6) + 0.38 + 0.6 * std::fmin(k / 1024.0, 1.0) +
+                                       (K % kF64Chunk ? 0.48 : 0.0));
+    auto fp32 = [&](long rows, double per_group, double besides) {
+        const double rounds = (double)((((M + rows - 1) / rows) * ((N + 127) / 128) * batch + cus - 1) / cus);
+        const bool clean = vec && M % rows == 0 && N % 128 == 0 && K % 32 == 0;
+        return rounds * ((double)((K + 31) / 32) * per_group * (clean ? 1.0 : vec ? 1.18 : 1.43) + besides);
+    };
+    r.fp32 = fp32(128, 2.95, 2.0);
+    if (M > 64) r.fp32 = std::fmin(r.fp32, fp32(64, 1.5, 2.5));
     return r;
+}
+// 16-byte loads of both operands
+static bool vector_rows(const LinearProblem& p) {
+    return aligned(p.A, 16) && p.lda % 4 == 0 && p.strideA % 4 == 0 && aligned(p.W, 16) && p.ldw % 4 == 0 && p.strideW % 4 == 0;
 }
 bool f64_route(const LinearProblem& p, int cus) {
     if (p.batch >= 65536 || p.K < 1) return false;
     if (p.trans_w && p.N + 16 * p.ldw >= (1L << 30)) return false;     // (32-bit column offsets)
     const F64Tile t = f64_tile(p.M, p.N, p.batch, cus);
     if (t.rounds * (double)cus >= 0x1p30) return false;                // (32-bit tile numbers)
-    const LinearTimes r = linear_times(t, p.M, p.N, p.K, p.batch, cus);
+    const LinearTimes r = linear_times(t, p.M, p.N, p.K, p.batch, vector_rows(p) && p.K % 4 == 0, cus);
     return r.f64 < r.fp32;
 }
 double linear_us(long M, long N, long K, long batch, int cus) {
-    const LinearTimes r = linear_times(f64_tile(M, N, batch, cus), M, N, K, batch, cus);
+    const LinearTimes r = linear_times(f64_tile(M, N, batch, cus), M, N, K, batch, K % 4 == 0, cus);
     return std::fmin(r.f64, r.fp32);
 }
 
@@ -271,7 +279,7 @@ int f64_launch(const LinearProblem& q, const tao_fp_model& md, double gamma, int
     p.infl = widen(1.0 / lower);
     p.c = widen(gamma * kGuard);
     p.uflow = (md.flags & TAO_FLAG_UNDERFLOW_TERMS) ? widen((double)(q.K + (q.bias ? 1 : 0)) * 0x1p-149) : 0.0;
-    const bool vec = aligned(q.A, 16) && q.lda % 4 == 0 && q.strideA % 4 == 0 && aligned(q.W, 16) && q.ldw % 4 == 0 && q.strideW % 4 == 0;
+    const bool vec = vector_rows(q);
     p.items = (unsigned)(t.tiles_m * t.tiles_n * q.batch);             // (f64_route: below 2^30)
     p.share = (p.items + 7) / 8;
     const dim3 grid(p.share * 8);

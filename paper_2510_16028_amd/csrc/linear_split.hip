@@ -1060,7 +1060,7 @@ int tao_linear_split_preferred(long M, long N, long K, long batch) {
     const double rounds = std::ceil((double)(tiles * parts) / (double)cus);
     const double split_us = 14.0 + 1.47e-6 * elements + 1.56 * rounds * std::ceil(groups / (double)parts) +
                             (parts >= 2 ? 2.0 + 1.84e-6 * (double)parts * (double)M * (double)N * (double)batch : 0.0);
-    return tao::linear_us(M, N, K, batch, (int)cus) >= 0.69 * split_us;
+    return tao::linear_us(M, N, K, batch, (int)cus) >= 0.66 * split_us;
 }
 
 }  // extern "C"
