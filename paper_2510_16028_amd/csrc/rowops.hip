@@ -822,9 +822,10 @@ __global__ __launch_bounds__(kCheckThreads) void norm_check(
         // lost (2^-150; with f alpha below 2^55 that stays far below the 2^-90 of quick_settled).  What mu, the conversions and
         // the products of the LayerNorm row lose there is taken off K0.
         const float uf = (float)k.u * qc.alpha;
-        const float ff = (ok && f >= 0x1p-90 && f <= 0x1p25 ? (float)f : NAN) * qc.alpha;
-        const float muf = (float)mu, K1f = (K1 >= 0x1p-90 && K1 <= 0x1p25 ? (float)K1 : NAN) * qc.alpha;
-        const float K0f = (float)((K0 - K1 * (0x1p-22 * fabs(mu) + 0x1p-149)) * (double)qc.alpha - 0x1p-140);
+        const float factor = (float)(RMS ? f : K1);
+        const float scaled = (ok && factor >= 0x1p-90f && factor <= 0x1p25f ? factor : NAN) * qc.alpha;
+        const float ff = scaled, muf = (float)mu, K1f = scaled;
+        const float K0f = (float)(K0 - 0x1p-22 * K1 * (fabs(mu) + 0x1p-126)) * qc.alpha - 0x1p-140f;
         if (QUICK) known = newest(&largest);
         if (CACHED) asm volatile("" : "+v"(lt));
         float4 next = make_float4(0.f, 0.f, 0.f, 0.f), next_g = next;    // the next vector's claims are on their way while one is checked
