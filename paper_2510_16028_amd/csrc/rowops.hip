@@ -366,7 +366,7 @@ __global__ __launch_bounds__(kCheckThreads) void softmax_check(
                     const float rho = fminf(fmaf(fmaf(a, a, a), invf, cef), 0x1p60f);
                     at[c] = (xe[c] == -INFINITY ? 0.f : fabsf(ye[c])) * fmaf(rho, w1f, w0f);
                 }
-                quick_check_four<(V == 1 || (V == 2 && TPR < 1024))>(ce, ye, at, tau, qc, alpha, eps_rel, hist, rep, acc_chk, &largest, known);
+                quick_check_four<(V == 1 || (V == 2 && TPR < 1024))>(ce, ye, at, tau, qc, alpha, eps_rel, hist, rep, acc_chk, &largest, known, known != 0);
                 continue;
             }
 #pragma unroll
@@ -858,7 +858,7 @@ __global__ __launch_bounds__(kCheckThreads) void norm_check(
                     if (RMS) at[c] = fmaf(fabsf(xe[c] * ge[c]), ff, uf * fabsf(ye[c]));
                     else     at[c] = fmaf(fabsf(ge[c]), fmaf(K1f, fabsf(xe[c] - muf), K0f), uf * fabsf(ye[c]));
                 }
-                quick_check_four<(V == 1 || (V == 2 && TPR < 1024))>(ce, ye, at, tau, qc, alpha, eps_rel, hist, rep, acc_chk, &largest, known);
+                quick_check_four<(V == 1 || (V == 2 && TPR < 1024))>(ce, ye, at, tau, qc, alpha, eps_rel, hist, rep, acc_chk, &largest, known, known != 0);
                 continue;
             }
             if (CACHED && (FULL || idx + 3 * TPR < limit)) {

@@ -129,12 +129,13 @@ typedef float floatv4 __attribute__((ext_vector_type(4)));      // (indexed by a
 // workgroup's largest exactly computed error (LDS), known: this thread's copy, no newer than it needs to be.  WIDE: the
 // exact way takes the four side by side, for kernels that have the registers (small tensors see little else);
 // otherwise one after the other in a loop, as four binary64 divisions would set the kernel's register count.
-// attempt: false goes the exact way at once.  Returns whether the estimates settled them.
+// attempt: false goes the exact way at once (before any error is known, known == 0, only equal values can be settled).
+// Returns whether the estimates settled them.
 template <bool WIDE, int R = kReplicas, class Tau>
 __device__ __forceinline__ bool quick_check_four(floatv4 c, floatv4 r, floatv4 at, Tau&& tau,
                                                  const QuickCheck& q, double alpha, double eps_rel, unsigned int* hist, int rep,
-                                                 ThreadAcc& acc, unsigned int* largest, unsigned& known, bool attempt = true) {
-    if (known && attempt) {
+                                                 ThreadAcc& acc, unsigned int* largest, unsigned& known, bool attempt) {
+    if (attempt) {
         unsigned bin[4];
         bool ok = true;
 #pragma unroll

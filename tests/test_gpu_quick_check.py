@@ -192,3 +192,30 @@ def test_strided_rows(tao, kind, rows, cols, ld, offset):
     got = tao.tao_bound_check_softmax(xs, ys, cs) if kind == "softmax" else tao.tao_bound_check_norm(k, xs, ys, cs, gamma, None, eps=1e-5)
     for key in want:
         assert np.array_equal(np.asarray(got[key]), np.asarray(want[key])), key
+
+
+@pytest.mark.parametrize("share", [0.0, 1e-5, 0.01])
+@pytest.mark.parametrize("op", ["gelu", "silu", "softmax", "layernorm", "rmsnorm"])
+def test_claims_that_equal_the_reference(tao, op, share):
+    """All claims, or all but a few, equal to the re-executed values: no error is known for long, or ever."""
+    rows, cols = 16384, 640
+    g = torch.Generator(device="cuda").manual_seed(5)
+    x = torch.randn((rows, cols), generator=g, device="cuda")
+    x[:, 3] = 0.0
+    gamma = 1 + 0.1 * torch.randn(cols, generator=g, device="cuda")
+    y = dict(gelu=lambda: torch.nn.functional.gelu(x), silu=lambda: torch.nn.functional.silu(x), softmax=lambda: torch.softmax(x, -1),
+             layernorm=lambda: (x - x.mean(-1, keepdim=True)) * torch.rsqrt(x.var(-1, keepdim=True, unbiased=False) + 1e-5) * gamma,
+             rmsnorm=lambda: x * torch.rsqrt((x * x).mean(-1, keepdim=True) + 1e-5) * gamma)[op]()
+    c = torch.where(torch.rand(y.shape, generator=g, device="cuda") < share, y * (1 + 2.0 ** -12), y)
+    y[5, 7] = c[5, 7] = float("inf"); y[6, 7] = c[6, 7] = float("nan")
+    kind = dict(gelu=tao.ACT_GELU_ERF, silu=tao.ACT_SILU, layernorm=tao.NORM_LAYERNORM, rmsnorm=tao.NORM_RMSNORM).get(op)
+    if op == "softmax":
+        tau, got = tao.tao_bound_softmax(x, y), tao.tao_bound_check_softmax(x, y, c)
+    elif op in ("gelu", "silu"):
+        tau, got = tao.tao_bound_act(kind, x, y), tao.tao_bound_check_act(kind, x, y, c)
+    else:
+        tau, got = tao.tao_bound_norm(kind, x, y, gamma, None, eps=1e-5), tao.tao_bound_check_norm(kind, x, y, c, gamma, None, eps=1e-5)
+    want = tao.tao_check_and_profile(c, y, tau)
+    for key in want:
+        a, b = np.asarray(got[key]), np.asarray(want[key])
+        assert np.array_equal(a, b, equal_nan=a.dtype.kind == "f"), key
