@@ -176,9 +176,10 @@ __global__ __launch_bounds__(kCheckThreads) void act_check(
             const bool tried = known != 0 && exact == 0;
             const bool settled = quick_check_four<true>(ce, ye, at, [&](int c) __attribute__((always_inline)) { return act_one<KIND>(xe[c], ye[c], k); },
                                                         qc, alpha, eps_rel, hist, rep, acc, &largest, known, exact == 0);
-            // (claims that leave the bound do so in crowds: after a quarter of a wavefront its next three vectors go the exact
-            // way at once -- 25 M elements of which most leave it 58 us without this, 52 with it or without estimates)
-            exact = exact ? exact - 1 : __popcll(__ballot(tried && !settled)) > kWave / 4 ? 3 : 0;
+            // (claims that leave the bound, or come close to it, do so in crowds: after an eighth of a wavefront its next seven
+            // vectors go the exact way at once -- 25 M tanh GELUs, claims 3 tau off 121 -> 116 us, 106 without estimates; one
+            // binary32 step off 123.5 -> 118.5; a lower mark takes 4 us more off those, and costs 6 where 0.1 % leave the bound)
+            exact = exact ? exact - 1 : __popcll(__ballot(tried && !settled)) > 8 ? 7 : 0;
         }
     } else
     for (long i = (long)blockIdx.x * kCheckThreads + tid; i < nvec; i += stride) {
