@@ -50,50 +50,13 @@ __global__ __launch_bounds__(kCheckThreads) void check_pass(
     flush_histogram(hist, ws_hist + (size_t)blockIdx.x * kBins, ws_coarse + blockIdx.x * kGroups);
 }
 
-__global__ __launch_bounds__(kReduceThreads) void profile_reduce(
-    const unsigned int* __restrict__ ws_hist, const unsigned int* __restrict__ ws_coarse,
-    const BlockStats* __restrict__ ws_stats, int nblocks, unsigned long long n, tao_profile* out) {
-    __shared__ unsigned long long smem[kReduceThreads + kReduceWaves];
-    __shared__ unsigned long long wv[kReduceWaves], wq[kReduceWaves];
-    __shared__ unsigned int wm[kReduceWaves];
-    const int tid = threadIdx.x;
-    const int lane = tid & (kWave - 1), wave = tid / kWave;
-    // nearest-rank percentiles p50, p99, p99.9; the three bin and three edge fields of tao_profile
-    // are consecutive
-    const RankQuery q[3] = {{1, 2}, {99, 100}, {999, 1000}};
-    reduce_group<3>(ws_hist, ws_coarse, nblocks, blockIdx.x, n, out->hist, q, &out->p50_bin, &out->p50, smem);
-    if (blockIdx.x != 0) return;
-    // counters of pass 1 (at most one record per thread)
-    unsigned long long v = 0, qn = 0; unsigned int m = 0;
-    for (int k = tid; k < nblocks; k += kReduceThreads) {
-        v += ws_stats[k].violations; qn += ws_stats[k].nans; m = max(m, ws_stats[k].max_bits);
-    }
-#pragma unroll
-    for (int o = kWave / 2; o > 0; o >>= 1) {
-        v += __shfl_xor(v, o, kWave); qn += __shfl_xor(qn, o, kWave);
-        m = max(m, (unsigned int)__shfl_xor(m, o, kWave));
-    }
-    if (lane == 0) { wv[wave] = v; wq[wave] = qn; wm[wave] = m; }
-    __syncthreads();
-    if (tid == 0) {
-        v = 0; qn = 0; m = 0;
-        for (int w = 0; w < kReduceWaves; ++w) { v += wv[w]; qn += wq[w]; m = max(m, wm[w]); }
-        out->n = n;
-        out->violations = v;
-        out->nan_count = qn;
-        out->max_rel = __uint_as_float(m);
-        out->accept = (v == 0) ? 1u : 0u;
-        out->pad_ = 0;
-        if (n == 0) {
-            out->p50_bin = out->p99_bin = out->p999_bin = 0;
-            out->p50 = out->p99 = out->p999 = bin_upper_edge(0);
-        }
-    }
+__global__ __launch_bounds__(kReduceThreads) void profile_reduce(CheckWorkspace w, int nblocks, unsigned long long n, tao_profile* out) {
+    __shared__ unsigned long long smem[profile_smem_words(kReduceThreads)];
+    profile_group<kReduceThreads, kMaxPartials>(w, nblocks, blockIdx.x, n, out, smem);
 }
 
 void launch_profile_reduce(const CheckWorkspace& w, int nblocks, unsigned long long n, tao_profile* out, hipStream_t st) {
-    hipLaunchKernelGGL(profile_reduce, dim3(kReduceBlocks), dim3(kReduceThreads), 0, st, w.hist, w.coarse,
-                       w.stats, nblocks, n, out);
+    hipLaunchKernelGGL(profile_reduce, dim3(kReduceBlocks), dim3(kReduceThreads), 0, st, w, nblocks, n, out);
 }
 
 // ---- the entry point that allocates nothing -------------------------------------------------

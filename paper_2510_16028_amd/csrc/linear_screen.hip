@@ -1,0 +1,590 @@
+// The screen of a checked matmul bound (Sec. 3.1 reductions, checked as Sec. 5.4 and profiled as Sec. 5.3 say).
+//
+// A check needs of a bound only the answer to  d <= alpha tau,  and most answers do not hang on tau's last bits:
+// honest claims stay far below their bounds, and a violation is rarely within a per cent of it.  The screen forms the sum
+//     P = sum_k hi(a_k) hi(w_k),    hi(v) = |v| rounded to the nearest BF16 value,
+// with one chain of v_mfma_f32_32x32x16_bf16 where the bound itself takes six products and their binary64 folds
+// (linear_split.hip), and encloses the real sum S = sum_k |a_k||w_k| from both sides:
+//   rounding of the operands:  |v| in hi(v) [1 - 2^-8, 1 + 2^-8], so S in P [(1 - 2^-8)^2, (1 + 2^-8)^2];
+//   accumulation: the instruction's two steps of 8 k each err by at most 2.01u of the sum so far and 7u of the step's own
+//     (the model that tao_selftest_matrix_core_bf16 re-checks), so the chain returns P (1 +- acc), acc = (2.01 Kp / 8 + 8) u;
+//   the bound's own slack: tau lies in [1, 1 + 1e-6] of Gamma (S + |b|) and its absolute terms are below 2^-20 of it;
+//     2^-14 covers these and the few binary32 roundings of the comparison.
+// Hence  d <= alpha cg (P lower + |b|)  proves that the exact check finds no violation and  d > alpha cg (P upper + |b|)
+// that it finds one.  The enclosure holds where every operand is below 2^32 in magnitude (nothing overflows, and what
+// operands below 2^-126 lose in BF16's subnormal range, 2^-134 each, weighs at most K 2^-101) and the sum at least
+// Kp 2^-80; an element with d = 0 never violates a bound that is not NaN.  Whatever else is met -- a larger or
+// non-finite operand anywhere in a tile, a bias beyond 2^60, a claim between the two limits, NaN -- sets the `unsettled`
+// flag: the screen's results are then void and the exact route, enqueued behind it, does the whole work; otherwise
+// that route's kernels return at once.  So every profile is the exact route's, bit for bit.
+// The errors' bins and maximum do not depend on tau: quick settlement as in tao_check.hpp, exact arithmetic where
+// an estimate does not decide.
+#include <cmath>
+#include <type_traits>
+#include "tao_device.hpp"
+#include "tao_host.hpp"
+#include "linear_screen.hpp"
+
+namespace tao {
+namespace {
+
+typedef float floatx16 __attribute__((ext_vector_type(16)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float floatx2 __attribute__((ext_vector_type(2)));
+typedef unsigned int uintx4 __attribute__((ext_vector_type(4)));
+typedef unsigned short ushortx2 __attribute__((ext_vector_type(2)));
+
+constexpr int SBK = 32;
+constexpr int kImageBlock = 3 * 128 * 64;               // bytes of an image's block of 128 rows x 32 k, three pieces
+constexpr unsigned kLargeBf16 = (127u + 32u) << 7;      // 2^32: operands from here on are not screened
+constexpr float kTinyPerStep = 0x1p-80f;
+constexpr int kHistWords = 2044;                        // bins up to infinity's, 2040 (NaN is counted apart), then three words more
+
+__device__ __forceinline__ unsigned pack_abs_bf16(float even, float odd) {
+    return __builtin_bit_cast(unsigned, __builtin_convertvector((floatx2{fabsf(even), fabsf(odd)}), bf16x2));
+}
+
+// ---- the product and its check ------------------------------------------------------------------
+struct ScreenArgs {
+    const char* A; const char* W;
+    long stepA, stepW;                 // bytes between k groups (rows: 128; pixels: unused)
+    long batchA, batchW;               // bytes between batch entries
+    int last_blkA, last_blkW;          // image: the last block of an operand (tiles beyond it read that one)
+    long ldA;                          // rows: bytes between rows
+    ScreenPixels px;                   // pixels: the convolution
+    long M, N;
+    int groups;
+    unsigned tiles_m, tiles_n, ntiles;
+    const float* claimed; const float* ref; const float* bias;
+    long ldy, strideY;
+    int vec;                           // claimed and ref: 16-byte aligned rows of a multiple of four
+    double eps_rel;
+    float low, high, low_b, high_b, tiny;
+    unsigned int* unsettled;
+    unsigned int* hist; unsigned int* coarse; BlockStats* stats;
+};
+
+enum { IMAGE, ROWS, PIXELS };
+
+// Waits until at most min(behind, MOST) slabs of COPIES copies each are outstanding.
+template <int COPIES, int MOST>
+__device__ __forceinline__ void wait_for_copies(int behind) {
+    constexpr int n = COPIES * MOST;
+    if constexpr (MOST == 0) {
+        __builtin_amdgcn_s_waitcnt(0x0F70);
+    } else {
+        if (behind >= MOST) __builtin_amdgcn_s_waitcnt(0x0F70 | (n & 15) | (n >> 4 << 14));
+        else wait_for_copies<COPIES, MOST - 1>(behind);
+    }
+}
+
+// WVM x WVN wavefronts of RM x RN accumulator tiles of 32 x 32.  A stage holds 32 k of the tile's operands as the images
+// hold them (ROWS: of A the binary32 values, cut when a fragment is read; PIXELS: gathered from BF16 magnitudes of the input,
+// taps in the padding from a line of zeros); NST stages filled by 16-byte copies that go to LDS directly, requested NST - 1 groups
+// ahead, one barrier per group.  The matrix instruction takes W as its row operand, so a lane holds four consecutive columns
+// of one row; the sums pass through LDS (32 rows of a wavefront at a time) so that claims and outputs are read along their
+// rows.  Workgroups walk the tiles; each XCD (workgroups are dealt to them in turn) owns a contiguous eighth of them, eight
+// tile rows deep, for its L2.
+template <int RM, int RN, int WVM, int WVN, int NST, int PER_CU, int SRC>
+__global__ __launch_bounds__(WVM * WVN * 64, WVM * WVN * PER_CU / 4) void screen_product(ScreenArgs p) {
+    constexpr int WAVES = WVM * WVN, THREADS = WAVES * 64;
+    constexpr int TM = WVM * RM * 32, TN = WVN * RN * 32;
+    constexpr int ROWB = SRC == ROWS ? 128 : 64;                               // bytes of a row of A's slab
+    constexpr int SLAB_A = TM * ROWB, SLAB_W = TN * 64, STAGE = SLAB_A + SLAB_W;
+    constexpr int NA = SLAB_A / 1024 / WAVES, NW = SLAB_W / 1024 / WAVES;      // copies of a wavefront per group
+    static_assert(RN <= 2, "a lane has a column where rows are not aligned");
+    static_assert(NA * WAVES * 1024 == SLAB_A && NW * WAVES * 1024 == SLAB_W, "whole copies");
+    constexpr int COLS = RN * 32, STRIP = COLS + 4;                            // a wavefront's strip of sums: 32 x COLS, padded rows
+    static_assert(WAVES * 32 * STRIP * 4 <= NST * STAGE, "the strips lie in the stages");
+    constexpr int CHAINS = RM * RN == 1 ? 2 : 1;                               // (a single accumulator would be one serial chain)
+    extern __shared__ __attribute__((aligned(16))) char lds[];
+    unsigned int* const hist = reinterpret_cast<unsigned int*>(lds);
+    char* const stages = lds + kHistWords * 4;
+    unsigned int& largest = hist[2041];                      // a lower bound of an error that occurs (its bits)
+    volatile unsigned int& void_seen = hist[2042];           // another workgroup / this one has met what it cannot settle
+    volatile unsigned int& open_seen = hist[2043];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave / WVN, wn = wave % WVN;
+    const int r32 = lane & 31, h = lane >> 5;
+    for (int i = tid; i < kHistWords / 4; i += THREADS) reinterpret_cast<uintx4*>(hist)[i] = uintx4{0, 0, 0, 0};
+
+    // fragments: lane (r32, h) holds k = 16 kg + 8 h .. + 7 of its row.  The first k half a wavefront takes is (wm ^ wn) & 1, so that
+    // the first halves of all wavefronts cover every operand value of the tile: only those are looked at for large ones.
+    const int swz = (r32 >> 2) & 3, swr = (r32 >> 1) & 7, flip = (wm ^ wn) & 1;
+    int unitW[2], unitA[2][2];
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+        const int kg = s ^ flip;
+        unitW[s] = ((2 * kg + h) ^ swz) * 16;
+        unitA[s][0] = SRC == ROWS ? ((4 * kg + 2 * h) ^ swr) * 16 : unitW[s];
+        unitA[s][1] = SRC == ROWS ? ((4 * kg + 2 * h + 1) ^ swr) * 16 : 0;
+    }
+    const int fragA = (wm * RM * 32 + r32) * ROWB;
+    const int fragW = SLAB_A + (wn * RN * 32 + r32) * 64;
+
+    const QuickCheck qc(1.f, p.eps_rel);
+    unsigned nans = 0, vio = 0, max_bits = 0, known = 0;
+    int zeros = 0;                                           // elements with d = 0 (a lane's own, to be added to all_zeros)
+    int all_zeros = 0;                                       // (the same in all lanes)
+    float* strip = reinterpret_cast<float*>(stages) + wave * 32 * STRIP;
+    // what stands for the bits of an error of 0, which is counted elsewhere: the middle of a "bin" that is a padding word of the
+    // first strip
+    constexpr int SPARE_ROWS = 22;
+    static_assert(kHistWords + SPARE_ROWS * STRIP < 4096, "twelve bits of bin");
+    const unsigned zero_bits = (unsigned)(kHistWords + (lane % SPARE_ROWS) * STRIP + COLS + lane / SPARE_ROWS) << 20 | 0x80000u;
+    // Elements of a strip: a lane has four consecutive columns where rows are 16-byte aligned, else one column of four rows.
+    constexpr int LPR = COLS / 4, RPI = 64 / LPR, STEPS = 32 / RPI;           // lanes per row, rows per step
+    constexpr int SPR = 64 / COLS;                                            // (unaligned) rows side by side
+    const int lrow0 = p.vec ? lane / LPR : (lane / COLS) * 4, lstep = p.vec ? RPI : 4 * SPR;
+    const int lcol = p.vec ? (lane % LPR) * 4 : lane % COLS;
+    const int de_row = p.vec ? 0 : 1, de_col = 1 - de_row;
+
+    const unsigned xcd = blockIdx.x & 7u, per = gridDim.x >> 3;
+    const unsigned t_end = (unsigned)((unsigned long long)p.ntiles * (xcd + 1) >> 3);
+    const unsigned per_z = p.tiles_m * p.tiles_n;
+    bool dropped = false;
+    for (unsigned t = (unsigned)((unsigned long long)p.ntiles * xcd >> 3) + (blockIdx.x >> 3); t < t_end; t += per) {
+        const unsigned z = t / per_z, b = t - z * per_z;
+        const unsigned grp = b / (8 * p.tiles_n), in = b - grp * 8 * p.tiles_n;
+        const unsigned deep = min(8u, p.tiles_m - grp * 8);
+        const unsigned tx = in / deep, ty = grp * 8 + (in - tx * deep);
+        const long m0 = (long)ty * TM, n0 = (long)tx * TN;
+        const int rows_left = (int)min((long)TM, p.M - m0), cols_left = (int)min((long)TN, p.N - n0);
+        // (whether another workgroup has met an element that it could not settle: then nothing here counts any more)
+        unsigned gone = 0;
+        if (wave == 0) gone = __hip_atomic_load(p.unsettled, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+
+        // claims and outputs of a strip; positions beyond the edge read the edge's elements.  The first strip's are requested before
+        // the product: their latency passes under it.
+        const float* __restrict__ C = p.claimed + (long)z * p.strideY + m0 * p.ldy + n0;
+        const float* __restrict__ Y = p.ref + (long)z * p.strideY + m0 * p.ldy + n0;
+        const int ldy = (int)p.ldy, srow = wm * RM * 32, scol = wn * COLS;
+        floatv4 cv[STEPS], rv[STEPS];
+        auto fetch = [&](int i, int k) __attribute__((always_inline)) {
+            const int row = srow + i * 32 + lrow0 + k * lstep;
+            if (p.vec) {
+                const unsigned at = (unsigned)(min(row, rows_left - 1) * ldy + min(scol + lcol, cols_left - 4));
+                cv[k] = __builtin_nontemporal_load(reinterpret_cast<const floatv4*>(C + at));
+                rv[k] = __builtin_nontemporal_load(reinterpret_cast<const floatv4*>(Y + at));
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const unsigned at = (unsigned)(min(row + e, rows_left - 1) * ldy + min(scol + lcol, cols_left - 1));
+                    cv[k][e] = C[at]; rv[k][e] = Y[at];
+                }
+            }
+        };
+#pragma unroll
+        for (int k = 0; k < STEPS; ++k) fetch(0, k);
+
+        // sources of this wavefront's copies: scalar bases, 32-bit lane offsets
+        const char* baseA[NA]; const char* baseW[NW];
+        unsigned offA[NA];
+        int pix_h[SRC == PIXELS ? NA : 1], pix_w[SRC == PIXELS ? NA : 1];     // PIXELS: input coordinates of tap (0, 0)
+        int tap_c = 0, tap_s = 0, tap_r = 0;
+        const unsigned off = lane * 16;
+#pragma unroll
+        for (int i = 0; i < NA; ++i) {
+            const int chunk = wave + i * WAVES;
+            if (SRC == ROWS) {
+                const int r = chunk * 8 + (lane >> 3);
+                offA[i] = (unsigned)(min(r, rows_left - 1) * p.ldA) + ((unsigned)((lane & 7) ^ ((r >> 1) & 7))) * 16u;
+                baseA[i] = p.A + z * p.batchA + m0 * p.ldA;
+            } else if (SRC == PIXELS) {
+                const int r = chunk * 16 + (lane >> 2);
+                const unsigned m = (unsigned)m0 + (unsigned)min(r, rows_left - 1);
+                const unsigned img = m / p.px.ohow, rem = m - img * p.px.ohow;
+                const unsigned oh = rem / (unsigned)p.px.OW, ow = rem - oh * (unsigned)p.px.OW;
+                pix_h[i] = (int)oh * p.px.sh - p.px.ph; pix_w[i] = (int)ow * p.px.sw - p.px.pw;
+                // (modulo 2^32: a tap inside the input has an offset below 2^31)
+                offA[i] = (unsigned)((((int)img * p.px.H + pix_h[i]) * p.px.W + pix_w[i])) * (unsigned)p.px.C * 2u +
+                          (unsigned)((lane & 3) ^ ((r >> 2) & 3)) * 16u;
+                baseA[i] = p.A;
+            } else {
+                const int row = (int)m0 + chunk * 16, blk = min(row >> 7, p.last_blkA);
+                baseA[i] = p.A + z * p.batchA + (long)blk * kImageBlock + (row & 127) * 64;
+                offA[i] = off;
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < NW; ++i) {
+            const int row = (int)n0 + (wave + i * WAVES) * 16, blk = min(row >> 7, p.last_blkW);
+            baseW[i] = p.W + z * p.batchW + (long)blk * kImageBlock + (row & 127) * 64;
+        }
+        auto request = [&](int stage) __attribute__((always_inline)) {
+            const unsigned dst = (unsigned)(size_t)(__attribute__((address_space(3))) char*)stages + (unsigned)(stage * STAGE) + (unsigned)wave * 1024u;
+            const int dr = tap_r * p.px.dh, ds = tap_s * p.px.dw;
+            const unsigned tap = (unsigned)((dr * p.px.W + ds) * p.px.C + tap_c * SBK) * 2u;
+#pragma unroll
+            for (int i = 0; i < NA; ++i) {
+                unsigned o = offA[i];
+                if (SRC == PIXELS) {
+                    const bool inside = (unsigned)(pix_h[i] + dr) < (unsigned)p.px.H && (unsigned)(pix_w[i] + ds) < (unsigned)p.px.W;
+                    o = inside ? o + tap : p.px.zeros;
+                }
+                asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+                             :: "s"(dst + (unsigned)(i * WAVES * 1024)), "v"(o), "s"(baseA[i]) : "memory");
+                if (SRC != PIXELS) baseA[i] += p.stepA;
+            }
+#pragma unroll
+            for (int i = 0; i < NW; ++i) {
+                asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+                             :: "s"(dst + (unsigned)(SLAB_A + i * WAVES * 1024)), "v"(off), "s"(baseW[i]) : "memory");
+                baseW[i] += p.stepW;
+            }
+            if (SRC == PIXELS && ++tap_c == p.px.slabs) {
+                tap_c = 0;
+                if (++tap_s == p.px.S) { tap_s = 0; ++tap_r; }
+            }
+        };
+
+        floatx16 acc[RM][RN], more;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            more[v] = 0.f;
+#pragma unroll
+            for (int i = 0; i < RM; ++i)
+#pragma unroll
+                for (int j = 0; j < RN; ++j) acc[i][j][v] = 0.f;
+        }
+        ushortx2 mostA[RM], mostW[RN];
+#pragma unroll
+        for (int i = 0; i < RM; ++i) mostA[i] = ushortx2{0, 0};
+#pragma unroll
+        for (int j = 0; j < RN; ++j) mostW[j] = ushortx2{0, 0};
+        auto most = [&](ushortx2& m, const bf16x8& f) __attribute__((always_inline)) {
+            const uintx4 u = __builtin_bit_cast(uintx4, f);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const unsigned two = u[j];                   // (a bit cast of the element itself takes the vector's first)
+                m = __builtin_elementwise_max(m, __builtin_bit_cast(ushortx2, two));
+            }
+        };
+        auto compute = [&](const char* stage) __attribute__((always_inline)) {
+#pragma unroll
+            for (int s = 0; s < 2; ++s) {
+                bf16x8 a[RM], w[RN];
+#pragma unroll
+                for (int i = 0; i < RM; ++i) {
+                    if (SRC == ROWS) {
+                        const float4 x = *reinterpret_cast<const float4*>(stage + fragA + i * 32 * 128 + unitA[s][0]);
+                        const float4 y = *reinterpret_cast<const float4*>(stage + fragA + i * 32 * 128 + unitA[s][1]);
+                        a[i] = __builtin_bit_cast(bf16x8, (uintx4{pack_abs_bf16(x.x, x.y), pack_abs_bf16(x.z, x.w),
+                                                                  pack_abs_bf16(y.x, y.y), pack_abs_bf16(y.z, y.w)}));
+                    } else {
+                        a[i] = *reinterpret_cast<const bf16x8*>(stage + fragA + i * 32 * 64 + unitA[s][0]);
+                    }
+                }
+#pragma unroll
+                for (int j = 0; j < RN; ++j) w[j] = *reinterpret_cast<const bf16x8*>(stage + fragW + j * 32 * 64 + unitW[s]);
+#pragma unroll
+                for (int i = 0; i < RM; ++i)
+#pragma unroll
+                    for (int j = 0; j < RN; ++j) {
+                        floatx16& sum = CHAINS == 2 && s == 1 ? more : acc[i][j];
+                        sum = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w[j], a[i], sum, 0, 0, 0);
+                    }
+                if (s == 0) {
+#pragma unroll
+                    for (int i = 0; i < RM; ++i) most(mostA[i], a[i]);
+#pragma unroll
+                    for (int j = 0; j < RN; ++j) most(mostW[j], w[j]);
+                }
+            }
+        };
+
+        __syncthreads();                                     // the strips of the tile before have been read
+        if (void_seen | open_seen) { dropped = true; break; }
+        constexpr int COPIES = NA + NW;
+#pragma unroll
+        for (int i = 0; i + 1 < NST; ++i)
+            if (i < p.groups) request(i);
+        int cur = 0;
+#pragma unroll 1
+        for (int g = 0; g < p.groups; ++g) {
+            // slab g has landed when only the copies of the slabs behind it are outstanding; the barrier publishes it and
+            // separates the last reads of the stage before from its next fill
+            wait_for_copies<COPIES, NST - 2>(p.groups - 1 - g);
+            __syncthreads();
+            if (g + NST - 1 < p.groups) request(cur == 0 ? NST - 1 : cur - 1);
+            compute(stages + cur * STAGE);
+            cur = cur == NST - 1 ? 0 : cur + 1;
+        }
+        if (CHAINS == 2) {
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[0][0][v] += more[v];
+        }
+
+        // operands that are not screened, of rows that exist
+        bool large = false;
+#pragma unroll
+        for (int i = 0; i < RM; ++i)
+            large |= srow + i * 32 + r32 < rows_left && (mostA[i][0] >= kLargeBf16 || mostA[i][1] >= kLargeBf16);
+#pragma unroll
+        for (int j = 0; j < RN; ++j)
+            large |= scol + j * 32 + r32 < cols_left && (mostW[j][0] >= kLargeBf16 || mostW[j][1] >= kLargeBf16);
+        floatv4 bias4, bl, bh;
+        float bias_low = INFINITY;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int col = scol + lcol + e * de_col;
+            bias4[e] = p.bias && col < cols_left ? fabsf(p.bias[n0 + col]) : 0.f;
+            large |= !(bias4[e] <= 0x1p60f);
+            bl[e] = bias4[e] * p.low_b; bh[e] = bias4[e] * p.high_b;
+            bias_low = fminf(bias_low, bl[e]);
+        }
+
+        // An error that occurs, to begin with (without one no element could be settled for the maximum): the largest of a lane's first
+        // elements, lowered by what the estimate may be off.
+        if (known == 0) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float den = fabsf(rv[0][e]) + qc.eps;
+                const unsigned bits = __float_as_uint(fabsf(cv[0][e] - rv[0][e]) * __builtin_amdgcn_rcpf(den));
+                if (den <= 0x1p100f && bits <= 0x7f800000u && bits > 16u) known = max(known, bits - 16u);
+            }
+            // (rows and columns beyond the edge repeat elements that exist)
+            if (known) atomicMax(&largest, known);
+        }
+        __syncthreads();                                     // every wavefront is done with the stages
+        known = max(known, newest(&largest));
+
+        unsigned open = 0;                                   // elements that were not settled
+        // Four elements of a lane: violations, and bins and maximum where the estimates decide (false: exact4).  Tests are made for the
+        // four together first: a test per element costs as much as the estimate.
+        auto check4 = [&](const floatv4& c, const floatv4& r, const floatv4& s) __attribute__((always_inline)) -> bool {
+            unsigned word[4], bits[4], edge[4], least[4];
+            float over[4], den[4];
+            int found = 0;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float d = fabsf(c[e] - r[e]);
+                den[e] = fabsf(r[e]) + qc.eps;
+                bits[e] = __float_as_uint(d * __builtin_amdgcn_rcpf(den[e]));
+                const bool zero = d == 0.f;
+                found += __popcll(__ballot(zero));
+                over[e] = fmaf(s[e], -p.low, d);
+                const unsigned b = zero ? zero_bits : bits[e];
+                edge[e] = (b + 16u) << 12;                   // (below 32 << 12 within 16 steps of a bin's edge)
+                word[e] = b >> 20;
+                least[e] = __float_as_uint(s[e]);            // (sums are not negative)
+            }
+            asm volatile("" : "+s"(found));                  // (counted here: masks kept until later exceed the scalar registers)
+            all_zeros += found;
+            int inside = fmaxf(fmaxf(over[0], over[1]), fmaxf(over[2], over[3])) <= bias_low;
+            inside &= min(min(least[0], least[1]), min(least[2], least[3])) >= __float_as_uint(p.tiny);
+            const unsigned most_bits = max(max(bits[0], bits[1]), max(bits[2], bits[3]));      // (a NaN's are the largest)
+            int ok = most_bits + 16u <= known;
+            ok &= min(min(edge[0], edge[1]), min(edge[2], edge[3])) >= 32u << 12;
+            ok &= fmaxf(fmaxf(den[0], den[1]), fmaxf(den[2], den[3])) <= 0x1p100f;
+            if (!inside || most_bits > 0x7f800000u) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const float d = fabsf(c[e] - r[e]);
+                    const bool above = d > fmaf(s[e], p.high, bh[e]);
+                    vio += above;
+                    open += !((d == 0.f) | (((d <= fmaf(s[e], p.low, bl[e])) | above) & (s[e] >= p.tiny)));
+                }
+            }
+            if (ok) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) atomicAdd(&hist[word[e]], 1u);
+            }
+            return ok;
+        };
+        // The exact way for bins and maximum of step k of strip i, its elements read again.
+        auto exact4 = [&](int i, int k) __attribute__((always_inline)) {
+            const int row = srow + i * 32 + lrow0 + k * lstep, col = scol + lcol;
+            float c[4], r[4];
+            bool in_range[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int re = row + e * de_row, ce = col + e * de_col;
+                in_range[e] = re < rows_left && ce < cols_left;
+                const unsigned at = in_range[e] ? (unsigned)(re * ldy + ce) : 0u;
+                c[e] = C[at]; r[e] = Y[at];
+            }
+            CheckedElement o[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) o[e] = check_arith<false>(c[e], r[e], 0.f, 1.0, p.eps_rel);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                if (!in_range[e]) continue;
+                if (c[e] == r[e] && fabsf(c[e]) < INFINITY) zeros -= 1;              // (counted in check4)
+                nans += o[e].is_nan;
+                if (!o[e].is_nan) { max_bits = max(max_bits, o[e].bits); atomicAdd(&hist[o[e].bin], 1u); }
+            }
+            if (max_bits > known) atomicMax(&largest, max_bits);
+            known = max(known, newest(&largest));
+        };
+        unsigned again = 0;                                  // steps for exact4
+#pragma unroll
+        for (int i = 0; i < RM; ++i) {
+#pragma unroll
+            for (int j = 0; j < RN; ++j)
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    *reinterpret_cast<floatv4*>(strip + r32 * STRIP + j * 32 + 8 * q + 4 * h) =
+                        floatv4{acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
+            const int in_rows = max(0, min(32, rows_left - srow - i * 32)), in_cols = max(0, min(COLS, cols_left - scol));
+            const bool whole = in_rows == 32 && in_cols == COLS;
+            all_zeros -= 32 * COLS - in_rows * in_cols;      // (positions beyond the edge pass for zeros below)
+#pragma unroll
+            for (int k = 0; k < STEPS; ++k) {
+                __builtin_amdgcn_sched_barrier(0);           // (side by side the steps' lane masks exceed the scalar registers)
+                floatv4 s;
+                if (p.vec) {
+                    s = *reinterpret_cast<const floatv4*>(strip + (lrow0 + k * lstep) * STRIP + lcol);
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) s[e] = strip[(lrow0 + k * lstep + e) * STRIP + lcol];
+                }
+                if (!whole) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const bool out = (lrow0 + k * lstep + e * de_row >= in_rows) | (lcol + e * de_col >= in_cols);
+                        cv[k][e] = out ? 0.f : cv[k][e]; rv[k][e] = out ? 0.f : rv[k][e];
+                        s[e] = out ? p.tiny : s[e];
+                    }
+                }
+                if (!check4(cv[k], rv[k], s)) again |= 1u << (i * STEPS + k);
+                if (i + 1 < RM) fetch(i + 1, k);             // the next strip's, as soon as the registers are free
+            }
+        }
+        while (again) {
+            const int at = __ffs((int)again) - 1;
+            again &= again - 1;
+            exact4(at / STEPS, at % STEPS);
+        }
+        if (__any(open != 0 || large) && lane == 0) open_seen = 1;
+        if (wave == 0 && lane == 0 && gone) void_seen = 1;
+    }
+    // this workgroup's counts to one of the partial results (integer atomics: the sums do not depend on the order)
+    __syncthreads();
+    if (open_seen) {
+        // (once per workgroup, and not where it is known: stores to one word are served one after the other, 60 us of them from 400 workgroups)
+        if (tid == 0 && !void_seen && __hip_atomic_load(p.unsettled, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0)
+            __hip_atomic_store(p.unsettled, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        return;
+    }
+    if (dropped || void_seen) return;
+#pragma unroll
+    for (int o = kWave / 2; o > 0; o >>= 1) {
+        zeros += __shfl_xor(zeros, o, kWave);
+        vio += __shfl_xor(vio, o, kWave);
+        nans += __shfl_xor(nans, o, kWave);
+        max_bits = max(max_bits, (unsigned)__shfl_xor(max_bits, o, kWave));
+    }
+    zeros += all_zeros;
+    const unsigned slot = blockIdx.x % (unsigned)kScreenSlots;
+    if (lane == 0) {
+        if (zeros) atomicAdd(&hist[0], (unsigned)zeros);
+        if (nans) {
+            atomicAdd(&p.hist[(size_t)slot * kBins + kBins - 1], nans);
+            atomicAdd(&p.coarse[slot * kGroups + kGroups - 1], nans);
+        }
+        BlockStats* st = p.stats + slot;
+        if (vio) atomicAdd(&st->violations, (unsigned long long)vio);
+        if (nans) atomicAdd(&st->nans, (unsigned long long)nans);
+        if (max_bits) atomicMax(&st->max_bits, max_bits);
+    }
+    __syncthreads();
+    // (eight bins a thread, eight threads a group of 64)
+    for (int b8 = tid; b8 < kBins / 8; b8 += THREADS) {
+        unsigned gsum = 0;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const int bin = b8 * 8 + j;
+            const unsigned cnt = bin <= 2040 ? hist[bin] : 0u;
+            if (cnt) atomicAdd(&p.hist[(size_t)slot * kBins + bin], cnt);
+            gsum += cnt;
+        }
+#pragma unroll
+        for (int o = 4; o > 0; o >>= 1) gsum += __shfl_xor(gsum, o, kWave);
+        if ((b8 & 7) == 0 && gsum) atomicAdd(&p.coarse[slot * kGroups + b8 / 8], gsum);
+    }
+}
+
+double accumulation_error(long K) { return (2.01 * (double)((K + SBK - 1) / SBK * SBK) / 8.0 + 8.0) * 0x1p-24; }
+
+int cus() {
+    int dev = 0, n = 256;
+    if (hipGetDevice(&dev) == hipSuccess) (void)hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev);
+    return n;
+}
+
+template <int RM, int RN, int WVM, int WVN, int NST, int PER_CU, int SRC>
+int launch_config(ScreenArgs& p, long batch, hipStream_t st) {
+    constexpr int TM = WVM * RM * 32, TN = WVN * RN * 32;
+    constexpr int lds_bytes = NST * (TM * (SRC == ROWS ? 128 : 64) + TN * 64) + kHistWords * 4;
+    auto kernel = &screen_product<RM, RN, WVM, WVN, NST, PER_CU, SRC>;
+    static OncePerDevice configured;
+    const hipError_t e = configured.run([&] {
+        return hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
+    });
+    if (e != hipSuccess) { g_last_hip_error = (int)e; return TAO_ERR_LAUNCH; }
+    p.tiles_m = (unsigned)((p.M + TM - 1) / TM); p.tiles_n = (unsigned)((p.N + TN - 1) / TN);
+    const long ntiles = (long)p.tiles_m * p.tiles_n * batch;
+    if (ntiles >= (1L << 30)) return TAO_ERR_SHAPE;
+    p.ntiles = (unsigned)ntiles;
+    long grid = (long)cus() * PER_CU & ~7L;
+    if (grid < 8) grid = 8;
+    const long want = (ntiles + 7) & ~7L;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)(want < grid ? want : grid)), dim3(WVM * WVN * 64), lds_bytes, st, p);
+    return launch_status();
+}
+
+}  // namespace
+
+bool screen_usable(long K, double u, double cg, double alpha, double uflow) {
+    // a bound inflated by its own 11.4u well within 2^-14, factors that stay ordinary in binary32 (bounds of at least 2^-120, limits
+    // below 2^109), absolute terms below 2^-20 of them
+    const double a = alpha * cg;
+    return K > 0 && u <= 0x1p-20 && accumulation_error(K) <= 0x1p-6 && cg >= 0x1p-40 && cg <= 0x1p10 && a >= 0x1p-40 && a <= 0x1p20 &&
+           uflow <= cg * (double)K * 0x1p-100;
+}
+
+int launch_screen(const ScreenOperand& A, const ScreenOperand& W, const float* bias, long M, long N, long K, long batch,
+                  double cg, const ScreenCheck& chk, const CheckWorkspace& ws, hipStream_t st) {
+    const long groups = (K + SBK - 1) / SBK, blocksA = (M + 127) / 128, blocksW = (N + 127) / 128;
+    ScreenArgs p = {};
+    const bool rows = A.ld != 0, pixels = A.pixels != nullptr;
+    if (pixels) p.px = *A.pixels;
+    p.A = static_cast<const char*>(A.data); p.W = static_cast<const char*>(W.data);
+    p.stepA = rows ? SBK * 4 : blocksA * kImageBlock; p.stepW = blocksW * kImageBlock;
+    p.batchA = A.batch_bytes; p.batchW = W.batch_bytes;
+    p.last_blkA = (int)blocksA - 1; p.last_blkW = (int)blocksW - 1;
+    p.ldA = A.ld * 4;
+    p.M = M; p.N = N; p.groups = (int)groups;
+    p.claimed = chk.claimed; p.ref = chk.ref; p.bias = bias; p.ldy = chk.ldy; p.strideY = chk.strideY;
+    p.vec = aligned(chk.claimed, 16) && aligned(chk.ref, 16) && N % 4 == 0 && chk.ldy % 4 == 0 && chk.strideY % 4 == 0;
+    p.eps_rel = chk.eps_rel;
+    const double acc = accumulation_error(K), half = 0x1p-8, a = chk.alpha * cg;
+    const double lower = (1.0 - half) * (1.0 - half) / (1.0 + acc), upper = (1.0 + half) * (1.0 + half) / (1.0 - acc);
+    p.low = (float)(a * lower * (1.0 - 0x1p-14)); p.high = (float)(a * upper * (1.0 + 0x1p-14));
+    p.low_b = (float)(a * (1.0 - 0x1p-14)); p.high_b = (float)(a * (1.0 + 0x1p-14));
+    p.tiny = (float)(groups * SBK) * kTinyPerStep;
+    p.unsettled = &ws.stats[kOpenFlag].flag;
+    p.hist = ws.hist; p.coarse = ws.coarse; p.stats = ws.stats;
+    if (chk.ldy >= kScreenMaxLd) return TAO_ERR_SHAPE;
+    const long n = cus();
+    const long t128 = ((M + 127) / 128) * ((N + 127) / 128) * batch;
+    // Tiles of 128 x 128, two workgroups to a compute unit, where they give every compute unit one (us of the whole call on images, with
+    // them / with 64 x 64: 2048 x 12288 over 4096 236 / 390, 2048 x 4096 over 4096 92 / 137, 1111 x 3001 over 1001, 216 tiles, 38 / 36);
+    // up to 256 k, where the check is most of the work, 64 x 128 and three (8 x 8192 x 2048 over 128 250, with 128 x 128 257 - 296).
+    // Otherwise, and where a column tile would be half empty, 64 x 64: four to a compute unit, or two with eight stages, which hide the
+    // copies' latency, where there are no more (512 x 3072 over 768 25, 128 x 128 32; 256 x 1024 over 8192 64 with eight stages, 68
+    // with four).
+    const bool wide = t128 >= n && N > 64;
+    if (rows) return launch_config<1, 2, 2, 2, 4, 2, ROWS>(p, batch, st);
+    if (pixels) return wide ? launch_config<2, 2, 2, 2, 4, 2, PIXELS>(p, batch, st) : launch_config<1, 1, 2, 2, 4, 4, PIXELS>(p, batch, st);
+    if (wide && groups <= 8) return launch_config<1, 2, 2, 2, 3, 3, IMAGE>(p, batch, st);
+    if (wide) return launch_config<2, 2, 2, 2, 4, 2, IMAGE>(p, batch, st);
+    const long t64 = ((M + 63) / 64) * ((N + 63) / 64) * batch;
+    if (t64 <= 2 * n) return launch_config<1, 1, 2, 2, 8, 2, IMAGE>(p, batch, st);
+    return launch_config<1, 1, 2, 2, 4, 4, IMAGE>(p, batch, st);
+}
+
+}  // namespace tao

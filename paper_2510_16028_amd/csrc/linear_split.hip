@@ -43,6 +43,7 @@
 #include "tao_device.hpp"
 #include "tao_host.hpp"
 #include "linear_f64.hpp"
+#include "linear_screen.hpp"
 #include "tao_check.hpp"
 
 namespace tao {
@@ -111,33 +112,52 @@ __device__ __forceinline__ void split_pack8(const float (&v)[8], uintx4& H, uint
     }
 }
 
-// One thread per 8 consecutive k of one row.  TRANS: the source is [K][ld] with the row index
-// running along its columns (W stored K x N); adjacent threads then take adjacent rows.  Otherwise a
+// One thread per 8 consecutive k of one row, for one or two operands in one launch.  TRANSPOSED: the source is [K][ld] with the row
+// index running along its columns (W stored K x N); adjacent threads then take adjacent rows.  MAGNITUDES: no image but the
+// BF16 magnitudes alone, in the source's layout (K a multiple of 8, one row), and 64 bytes of zeros behind them.  Otherwise a
 // workgroup takes patches of 64 rows x 256 k: per 32-k slab its 256 threads read 128 contiguous bytes
 // of each row (1 KB per row over the patch) and write 4 KB contiguous per piece (64 rows of one
 // slab are adjacent in the block layout) -- with threads running along k instead, every 64 bytes
 // written landed in another block.
-template <bool TRANS>
-__global__ __launch_bounds__(256) void split3_bf16(const float* __restrict__ src, long rows, long K, long ld,
-                                                    long src_batch_stride, unsigned short* __restrict__ dst, long Kp,
-                                                    int vec_ok, unsigned int* __restrict__ zero_ptr, long zero_n) {
-    // (side job for the launch that follows: clears zero_n words at zero_ptr, the partial results of
-    // a check in the matrix kernel's epilogue, so that no launch of its own is needed for that)
-    if (zero_ptr && blockIdx.y == 0)
-        for (long i = (long)blockIdx.x * blockDim.x + threadIdx.x; i < zero_n; i += (long)gridDim.x * blockDim.x) zero_ptr[i] = 0;
-    const long chunks = Kp >> 3;
-    const long z = blockIdx.y;
-    const long rblocks = (rows + STILE - 1) / STILE;
-    const float* s = src + z * src_batch_stride;
-    unsigned short* d = dst + z * ((Kp / SBK) * rblocks * (kBlock / 2));
-    // work items: TRANS (chunk, row) pairs, row fastest; else (row group, k span, slab, row, chunk of the slab).  Rows up
+enum { STRAIGHT, TRANSPOSED, MAGNITUDES };
+struct SplitOperand { const float* src; long rows, K, ld, batch, stride; unsigned short* dst; int form; };
+struct SplitOperands {
+    SplitOperand op[2];
+    long first[3];                     // workgroups [first[o], first[o + 1]) serve operand o
+    unsigned int* zero_ptr; long zero_n;
+};
+typedef float floatx4u __attribute__((ext_vector_type(4), aligned(4)));          // (16-byte loads need no more than 4-byte alignment)
+__global__ __launch_bounds__(256) void split3_bf16(SplitOperands a) {
+    // (side job for the launch that follows: clears the partial results of a check, so that no launch of its own is needed for that)
+    for (long i = (long)blockIdx.x * 256 + threadIdx.x; i < a.zero_n; i += (long)gridDim.x * 256) a.zero_ptr[i] = 0;
+    const int o = (long)blockIdx.x >= a.first[1] ? 1 : 0;
+    const SplitOperand& p = a.op[o];
+    const long nblk = a.first[o + 1] - a.first[o], blk = (long)blockIdx.x - a.first[o];
+    if (p.form == MAGNITUDES) {
+        for (long i = blk * 256 + threadIdx.x; i < p.K / 8 + 4; i += nblk * 256) {
+            uintx4 H = {0, 0, 0, 0};
+            if (i < p.K / 8) {
+                const floatx4u* q = reinterpret_cast<const floatx4u*>(p.src) + 2 * i;
+                const floatx4u x = q[0], y = q[1];
+                H = uintx4{pack_bf16(fabsf(x[0]), fabsf(x[1])), pack_bf16(fabsf(x[2]), fabsf(x[3])),
+                           pack_bf16(fabsf(y[0]), fabsf(y[1])), pack_bf16(fabsf(y[2]), fabsf(y[3]))};
+            }
+            reinterpret_cast<uintx4*>(p.dst)[i] = H;
+        }
+        return;
+    }
+    const bool trans = p.form == TRANSPOSED;
+    const long groups = (p.K + SBK - 1) / SBK, chunks = groups * (SBK / 8);
+    const long rblocks = (p.rows + STILE - 1) / STILE;
+    // work items: trans (chunk, row) pairs, row fastest; else (row group, k span, slab, row, chunk of the slab).  Rows up
     // to the next multiple of four are zeros: the product's epilogue looks at its sums by groups of four rows.
-    const long rows4 = (rows + 3) & ~3L;
-    const long kspans = (Kp + 255) >> 8, rgroups = (rows + 63) >> 6;
-    const long total = TRANS ? rows4 * chunks : rgroups * kspans * 8 * 256;
-    for (long w = (long)blockIdx.x * blockDim.x + threadIdx.x; w < total; w += (long)gridDim.x * blockDim.x) {
+    const long rows4 = (p.rows + 3) & ~3L;
+    const long kspans = (groups + 7) >> 3, rgroups = (p.rows + 63) >> 6;
+    const long per = trans ? rows4 * chunks : rgroups * kspans * 8 * 256, total = per * p.batch;
+    for (long w0 = blk * 256 + threadIdx.x; w0 < total; w0 += nblk * 256) {
+        const long z = p.batch == 1 ? 0 : w0 / per, w = w0 - z * per;
         long row, ch;
-        if (TRANS) {
+        if (trans) {
             ch = w / rows4; row = w - ch * rows4;
         } else {
             const long patch = w >> 11, in = w & 2047;          // 8 slabs x 64 rows x 4 chunks
@@ -147,26 +167,28 @@ __global__ __launch_bounds__(256) void split3_bf16(const float* __restrict__ src
             if (row >= rows4 || ch >= chunks) continue;
         }
         const long k0 = ch << 3;
+        const float* s = p.src + z * p.stride;
         float v[8];
-        if (!TRANS && vec_ok && row < rows && k0 + 8 <= K) {
-            const float4 a = *reinterpret_cast<const float4*>(s + row * ld + k0);
-            const float4 b = *reinterpret_cast<const float4*>(s + row * ld + k0 + 4);
-            v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w; v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
+        if (!trans && row < p.rows && k0 + 8 <= p.K) {
+            const floatx4u* q = reinterpret_cast<const floatx4u*>(s + row * p.ld + k0);
+            const floatx4u x = q[0], y = q[1];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) { v[j] = x[j]; v[4 + j] = y[j]; }
         } else {
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
                 const long k = k0 + j;
-                v[j] = (row < rows && k < K) ? (TRANS ? s[k * ld + row] : s[row * ld + k]) : 0.f;
+                v[j] = (row < p.rows && k < p.K) ? (trans ? s[k * p.ld + row] : s[row * p.ld + k]) : 0.f;
             }
         }
         uintx4 H, Mi, L;
         split_pack8(v, H, Mi, L);
         const long r = row & (STILE - 1);
         const long unit = ((k0 & (SBK - 1)) >> 3) ^ ((r >> 2) & 3);
-        const long o = ((k0 >> 5) * rblocks + (row >> 7)) * (kBlock / 2) + r * (SROW / 2) + unit * 8;
-        *reinterpret_cast<uintx4*>(d + o) = H;
-        *reinterpret_cast<uintx4*>(d + (kSlab / 2) + o) = Mi;
-        *reinterpret_cast<uintx4*>(d + 2 * (kSlab / 2) + o) = L;
+        unsigned short* d = p.dst + ((z * groups + (k0 >> 5)) * rblocks + (row >> 7)) * (kBlock / 2) + r * (SROW / 2) + unit * 8;
+        *reinterpret_cast<uintx4*>(d) = H;
+        *reinterpret_cast<uintx4*>(d + (kSlab / 2)) = Mi;
+        *reinterpret_cast<uintx4*>(d + 2 * (kSlab / 2)) = L;
     }
 }
 
@@ -186,7 +208,7 @@ struct SplitArgs {
     const float* claimed; const float* ref;
     long ldy, strideY;
     double alpha, eps_rel;
-    unsigned int* ws_hist; unsigned int* ws_coarse; BlockStats* ws_stats;
+    unsigned int* ws_hist; unsigned int* ws_coarse; BlockStats* ws_stats; unsigned check_slots;
     // PARTIAL instantiation (the reduction cut into `ksplit` parts of `gpp` groups, one workgroup per
     // tile and part): binary64 partial sums [part][batch][M][N]
     unsigned ntiles; int ksplit; long gpp;
@@ -292,6 +314,55 @@ __device__ __forceinline__ void check_one_packed(float c, float r, float t, doub
     atomicAdd(&hist[(o.bin >> 1) * 4 + copy], (o.bin & 1) ? 0x10000u : 1u);
 }
 
+// Slot t -> tile (first row and column, batch entry); false if the slot has none (see absgemm_split_slot).
+__device__ __forceinline__ bool locate_tile(const SplitArgs& p, unsigned t, unsigned& tm0, unsigned& tn0, unsigned& tz) {
+    const unsigned zp = t / p.slots_per_z, bb = t - zp * p.slots_per_z;
+    if (p.linear) {                                          // fewer tiles than compute units: row by row, no empty slot
+        const unsigned ty = bb / p.tiles_n, tx = bb - ty * p.tiles_n;
+        tn0 = tx * STILE; tm0 = ty * STILE; tz = zp;
+        return true;
+    }
+    const unsigned sup = bb / p.slots, w8 = bb - sup * p.slots;
+    const unsigned xcd = w8 & 7u, j = w8 >> 3;
+    const unsigned ly = (xcd / p.npx) * p.ph + j / p.pw, lx = (xcd % p.npx) * p.pw + j % p.pw;
+    const unsigned sband = sup / p.super_rows, srow = sup - sband * p.super_rows;
+    const unsigned ty = srow * 16u + ly, tx = sband * 16u + lx;
+    tn0 = tx * STILE; tm0 = ty * STILE; tz = zp;
+    return ly < 16u && lx < 16u && ty < p.tiles_m && tx < p.tiles_n;
+}
+
+// Adds a workgroup's histogram (CHECK, below) to a partial result: non-empty bins; a wavefront covers one group of 64 bins.
+__device__ __forceinline__ void flush_packed(const SplitArgs& p, const unsigned int* chk_hist) {
+    const int tid = threadIdx.x, lane = tid & 63;
+    const unsigned slot = blockIdx.x % p.check_slots;
+    for (int b = tid; b < kBins; b += kSplitThreads) {
+        unsigned int cnt = 0;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) cnt += (chk_hist[(b >> 1) * 4 + c] >> (16 * (b & 1))) & 0xffffu;
+        if (cnt) atomicAdd(&p.ws_hist[(size_t)slot * kBins + b], cnt);
+        unsigned int gsum = cnt;
+#pragma unroll
+        for (int o = kWave / 2; o > 0; o >>= 1) gsum += __shfl_xor(gsum, o, kWave);
+        if (lane == 0 && gsum) atomicAdd(&p.ws_coarse[slot * kGroups + b / kBinsPerReduceBlock], gsum);
+    }
+}
+__device__ __forceinline__ void flush_counters(const SplitArgs& p, const ThreadAcc& acc) {
+    const unsigned slot = blockIdx.x % p.check_slots;
+    unsigned int vio = acc.violations, nn = acc.nans, mx = acc.max_bits;
+#pragma unroll
+    for (int o = kWave / 2; o > 0; o >>= 1) {
+        vio += __shfl_xor(vio, o, kWave);
+        nn += __shfl_xor(nn, o, kWave);
+        mx = max(mx, (unsigned int)__shfl_xor(mx, o, kWave));
+    }
+    if ((threadIdx.x & 63) == 0) {
+        BlockStats* st = p.ws_stats + slot;
+        if (vio) atomicAdd(&st->violations, (unsigned long long)vio);
+        if (nn) atomicAdd(&st->nans, (unsigned long long)nn);
+        if (mx) atomicMax(&st->max_bits, mx);
+    }
+}
+
 // CHECK: the epilogue also runs the leaf check of Sec. 5.4 and the relative-error profile of Sec. 5.3
 // on every bound it has just formed (the binary32 value the plain instantiation would store), against
 // `claimed` and `ref`, with a 2048-bin histogram in the 16 KB of LDS the three stages leave free; tau
@@ -313,18 +384,24 @@ __device__ __forceinline__ void check_one_packed(float c, float r, float t, doub
 // of 32), 16-byte aligned rows: the host checks all of it.
 // CONV (with AREG): the A operand is the implicit patch matrix of a convolution, gathered from the
 // channels-last input while loading; taps in the zero padding contribute zeros.
-template <bool CHECK, bool PARTIAL = false, bool WALK = false, bool AREG = false, bool CONV = false>
-__global__ __launch_bounds__(kSplitThreads) void absgemm_split(SplitArgs p) {
+template <bool SHARED>
+__device__ __forceinline__ void store_sum(double* at, double s) {
+    if (SHARED) __hip_atomic_store(at, s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    else *at = s;
+}
+
+// The work of slot `wg` of `nwg` (false: the slot has no tile).  lds: the stages; chk_hist: see below.
+// SHARED (with PARTIAL): the sums are for another workgroup of the same launch.
+template <bool CHECK, bool PARTIAL, bool WALK, bool AREG, bool CONV, bool SHARED = false>
+__device__ __forceinline__ bool absgemm_split_slot(const SplitArgs& p, unsigned wg, unsigned nwg, char* lds, unsigned int* chk_hist) {
     static_assert(!CONV || AREG, "the patch matrix exists only as a gather");
     static_assert(!(CHECK && PARTIAL), "the parts are checked by split_combine");
     static_assert(!(WALK && (CHECK || PARTIAL)), "only the plain bound walks tiles");
     static_assert(!(AREG && (WALK || PARTIAL)), "the in-load split keeps one tile per workgroup and the whole reduction");
-    extern __shared__ __attribute__((aligned(16))) char lds[];
     // CHECK: four copies of the 2048-bin histogram with 16-bit counters (a tile has 16384 elements, so
     // none overflows), two bins to a word and the four copies of a word in consecutive banks: 16 KB,
     // all the LDS the stages leave.  The copy is chosen by the lane; errors crowd into a few bins, and
     // a single copy serialised the workgroup's atomics.
-    __shared__ unsigned int chk_hist[CHECK ? kBins * 2 : 1];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave >> 1, wn = wave & 1;                 // 4 x 2 wavefronts, two 32x32 tiles each (along N)
     const int r32 = lane & 31, h = lane >> 5;
@@ -337,31 +414,19 @@ __global__ __launch_bounds__(kSplitThreads) void absgemm_split(SplitArgs p) {
     // so its tiles share ph + pw blocks (4 + 8 for a full super-tile).  Slots that fall beyond the
     // output's edge belong to no tile.  (A walk's stride is a multiple of 8, so a workgroup stays
     // with its XCD's patches.)  CHECK and PARTIAL launches have one workgroup per slot (and part).
-    const long part = PARTIAL ? blockIdx.x / p.ntiles : 0;
+    const long part = PARTIAL ? wg / p.ntiles : 0;
     unsigned m0 = 0, n0 = 0, z = 0;                          // first row and column of the tile, batch entry
     auto locate = [&](unsigned t, unsigned& tm0, unsigned& tn0, unsigned& tz) __attribute__((always_inline)) -> bool {
-        const unsigned zp = t / p.slots_per_z, bb = t - zp * p.slots_per_z;
-        if (p.linear) {                                      // fewer tiles than compute units: row by row, no empty slot
-            const unsigned ty = bb / p.tiles_n, tx = bb - ty * p.tiles_n;
-            tn0 = tx * STILE; tm0 = ty * STILE; tz = zp;
-            return true;
-        }
-        const unsigned sup = bb / p.slots, w8 = bb - sup * p.slots;
-        const unsigned xcd = w8 & 7u, j = w8 >> 3;
-        const unsigned ly = (xcd / p.npx) * p.ph + j / p.pw, lx = (xcd % p.npx) * p.pw + j % p.pw;
-        const unsigned sband = sup / p.super_rows, srow = sup - sband * p.super_rows;
-        const unsigned ty = srow * 16u + ly, tx = sband * 16u + lx;
-        tn0 = tx * STILE; tm0 = ty * STILE; tz = zp;
-        return ly < 16u && lx < 16u && ty < p.tiles_m && tx < p.tiles_n;
+        return locate_tile(p, t, tm0, tn0, tz);
     };
     // first slot at or after t (stepping by the grid) that holds a tile; p.ntiles if there is none
     auto next_tile = [&](unsigned t, unsigned& tm0, unsigned& tn0, unsigned& tz) __attribute__((always_inline)) -> unsigned {
         if (!WALK) return (t < p.ntiles && locate(t, tm0, tn0, tz)) ? t : p.ntiles;
-        while (t < p.ntiles && !locate(t, tm0, tn0, tz)) t += gridDim.x;
+        while (t < p.ntiles && !locate(t, tm0, tn0, tz)) t += nwg;
         return t < p.ntiles ? t : p.ntiles;
     };
-    unsigned t = next_tile(PARTIAL ? blockIdx.x % p.ntiles : blockIdx.x, m0, n0, z);
-    if (t >= p.ntiles) return;                               // whole workgroup
+    unsigned t = next_tile(PARTIAL ? wg % p.ntiles : wg, m0, n0, z);
+    if (t >= p.ntiles) return false;                             // whole workgroup
     if (CHECK) {
         for (int i = threadIdx.x; i < kBins * 2; i += kSplitThreads) chk_hist[i] = 0;
         __syncthreads();
@@ -534,7 +599,7 @@ __global__ __launch_bounds__(kSplitThreads) void absgemm_split(SplitArgs p) {
     for (;;) {
         float pc[CHECK ? 2 : 1][CHECK ? 16 : 1], pr[CHECK ? 2 : 1][CHECK ? 16 : 1];
         unsigned m1 = 0, n1 = 0, z1 = 0;
-        const unsigned tnext = WALK ? next_tile(t + gridDim.x, m1, n1, z1) : p.ntiles;
+        const unsigned tnext = WALK ? next_tile(t + nwg, m1, n1, z1) : p.ntiles;
         const bool more = WALK && tnext < p.ntiles;          // (the host walks tiles only if ngroup >= 2)
         // CHECK: the tile's claimed and re-executed values, requested before the last group so that their
         // latency passes under its arithmetic (the first 32-column half; the second half is requested
@@ -674,7 +739,7 @@ __global__ __launch_bounds__(kSplitThreads) void absgemm_split(SplitArgs p) {
             for (int v = 0; v < 16; ++v) {
                 const long row = (long)me + erow + 8 * (v >> 2) + (v & 3);
                 if (PARTIAL) {
-                    if (row < p.M && col < p.N) p.partial[((part * nbatch + z) * p.M + row) * p.N + col] = S[tj][v];
+                    if (row < p.M && col < p.N) store_sum<SHARED>(p.partial + ((part * nbatch + z) * p.M + row) * p.N + col, S[tj][v]);
                     continue;
                 }
                 if (row < p.M && col < p.N) {
@@ -690,19 +755,7 @@ __global__ __launch_bounds__(kSplitThreads) void absgemm_split(SplitArgs p) {
         }
         if (CHECK) {
             __syncthreads();
-            const unsigned slot = blockIdx.x % (unsigned)kMaxCheckBlocks;
-            // non-empty bins to the slot's partial histogram; a wavefront covers one group of 64 bins
-            // (a checking workgroup has one tile, so the histogram is not cleared again)
-            for (int b = tid; b < kBins; b += kSplitThreads) {
-                unsigned int cnt = 0;
-#pragma unroll
-                for (int c = 0; c < 4; ++c) cnt += (chk_hist[(b >> 1) * 4 + c] >> (16 * (b & 1))) & 0xffffu;
-                if (cnt) atomicAdd(&p.ws_hist[(size_t)slot * kBins + b], cnt);
-                unsigned int gsum = cnt;
-#pragma unroll
-                for (int o = kWave / 2; o > 0; o >>= 1) gsum += __shfl_xor(gsum, o, kWave);
-                if (lane == 0 && gsum) atomicAdd(&p.ws_coarse[slot * kGroups + b / kBinsPerReduceBlock], gsum);
-            }
+            flush_packed(p, chk_hist);                       // (a checking workgroup has one tile, so the histogram is not cleared again)
         }
         if (!more) break;
         // Everything this tile has in flight ends here (the next tile's first two slabs were requested
@@ -727,15 +780,15 @@ __global__ __launch_bounds__(kSplitThreads) void absgemm_split(SplitArgs p) {
         const SplitArgs& pa = *(const SplitArgs*)q;
         const int lrow = (lid >> 7) * 32 + ((lid >> 5) & 1) * 4, lcol = ((lid >> 6) & 1) * 64 + (lid & 31);
         unsigned mt, nt, zt;
-        for (unsigned tt = next_tile(PARTIAL ? blockIdx.x % p.ntiles : blockIdx.x, mt, nt, zt); tt < p.ntiles;
-             tt = WALK ? next_tile(tt + gridDim.x, mt, nt, zt) : p.ntiles) {
+        for (unsigned tt = next_tile(PARTIAL ? wg % p.ntiles : wg, mt, nt, zt); tt < p.ntiles;
+             tt = WALK ? next_tile(tt + nwg, mt, nt, zt) : p.ntiles) {
 #pragma unroll 1
             for (int e = 0; e < 32; ++e) {
                 const long row = (long)mt + lrow + 8 * ((e & 15) >> 2) + (e & 3), col = (long)nt + lcol + (e >> 4) * 32;
                 if (row >= pa.M || col >= pa.N) continue;
                 if (PARTIAL) {
                     double* at = pa.partial + ((part * nbatch + zt) * pa.M + row) * pa.N + col;
-                    if (!(fabs(*at) < (double)INFINITY)) *at = sum_in_binary64<AREG, CONV>(pa, row, col, zt, g0, ngroup);
+                    if (!(fabs(*at) < (double)INFINITY)) store_sum<SHARED>(at, sum_in_binary64<AREG, CONV>(pa, row, col, zt, g0, ngroup));
                 } else {
                     float* at = pa.tau + (long)zt * pa.strideT + row * pa.ldt + col;
                     if (fabsf(*at) < INFINITY) continue;
@@ -746,22 +799,180 @@ __global__ __launch_bounds__(kSplitThreads) void absgemm_split(SplitArgs p) {
             }
         }
     }
-    if (CHECK) {
-        const unsigned slot = blockIdx.x % (unsigned)kMaxCheckBlocks;
-        unsigned int vio = acc.violations, nn = acc.nans, mx = acc.max_bits;
+    if (CHECK) flush_counters(p, acc);
+    return true;
+}
+
+template <bool CHECK, bool PARTIAL = false, bool WALK = false, bool AREG = false, bool CONV = false>
+__global__ __launch_bounds__(kSplitThreads) void absgemm_split(SplitArgs p) {
+    extern __shared__ __attribute__((aligned(16))) char lds[];
+    __shared__ unsigned int chk_hist[CHECK ? kBins * 2 : 1];
+    absgemm_split_slot<CHECK, PARTIAL, WALK, AREG, CONV>(p, blockIdx.x, gridDim.x, lds, chk_hist);
+}
+
+// ---- behind a screen (linear_screen.hip) -------------------------------------------------------
+// One launch that settles the check: where the screen has settled every element, the first workgroups form the profile of its
+// partial results and nothing else happens; otherwise the bound is formed and checked by the code above, and the
+// workgroup that finishes the last tile (counted in the workspace; nobody waits) forms the profile.
+constexpr unsigned kSettleSlots = 64;      // partial results, which one workgroup adds
+struct SettleArgs {
+    CheckWorkspace check;              // the whole of it (linear_screen.hpp)
+    unsigned tiles;
+    unsigned long long n;
+    tao_profile* out;
+};
+// true: settled by the screen, nothing is left to do
+__device__ __forceinline__ bool settled_by_screen(const SettleArgs& r, char* lds) {
+    if (r.check.stats[kOpenFlag].flag != 0) return false;
+    for (int grp = blockIdx.x; grp < kGroups; grp += gridDim.x)
+        profile_group<kSplitThreads, kScreenSlots>(r.check, kScreenSlots, grp, r.n, r.out, reinterpret_cast<unsigned long long*>(lds));
+    return true;
+}
+// The profile of all partial results by one workgroup (profile_group takes one per 64 bins): four bins a thread.
+__device__ __forceinline__ void profile_alone(const CheckWorkspace& w, int nblocks, unsigned long long n, tao_profile* out, unsigned long long* smem) {
+    static_assert(kSplitThreads * 4 == kBins, "four bins a thread");
+    constexpr int WAVES = kSplitThreads / kWave;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    unsigned long long c[4] = {0, 0, 0, 0}, v = 0, q = 0; unsigned m = 0;
+    for (int k = 0; k < nblocks; ++k) {
+        const uintx4 h = *reinterpret_cast<const uintx4*>(w.hist + (size_t)k * kBins + tid * 4);
 #pragma unroll
-        for (int o = kWave / 2; o > 0; o >>= 1) {
-            vio += __shfl_xor(vio, o, kWave);
-            nn += __shfl_xor(nn, o, kWave);
-            mx = max(mx, (unsigned int)__shfl_xor(mx, o, kWave));
+        for (int j = 0; j < 4; ++j) c[j] += h[j];
+    }
+    for (int k = tid; k < nblocks; k += kSplitThreads) { v += w.stats[k].violations; q += w.stats[k].nans; m = max(m, w.stats[k].max_bits); }
+    const unsigned long long mine = c[0] + c[1] + c[2] + c[3];
+    unsigned long long upto = mine;                          // elements in this thread's bins and all below, within the wavefront first
+#pragma unroll
+    for (int o = 1; o < kWave; o <<= 1) {
+        const unsigned long long up = __shfl_up(upto, o, kWave);
+        if (lane >= o) upto += up;
+    }
+#pragma unroll
+    for (int o = kWave / 2; o > 0; o >>= 1) {
+        v += __shfl_xor(v, o, kWave); q += __shfl_xor(q, o, kWave);
+        m = max(m, (unsigned)__shfl_xor(m, o, kWave));
+    }
+    if (lane == kWave - 1) { smem[wave] = upto; smem[WAVES + wave] = v; smem[2 * WAVES + wave] = q; smem[3 * WAVES + wave] = m; }
+    __syncthreads();
+    for (int k = 0; k < wave; ++k) upto += smem[k];
+    const RankQuery ranks[3] = {{1, 2}, {99, 100}, {999, 1000}};
+    unsigned long long below = upto - mine;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const unsigned bin = tid * 4 + j;
+        out->hist[bin] = c[j];
+        for (int i = 0; i < 3 && n > 0; ++i) {
+            const unsigned long long r = rank_of(n, ranks[i].num, ranks[i].den);
+            if (below < r && r <= below + c[j]) { (&out->p50_bin)[i] = bin; (&out->p50)[i] = bin_upper_edge(bin); }
         }
-        if (lane == 0) {
-            BlockStats* st = p.ws_stats + slot;
-            if (vio) atomicAdd(&st->violations, (unsigned long long)vio);
-            if (nn) atomicAdd(&st->nans, (unsigned long long)nn);
-            if (mx) atomicMax(&st->max_bits, mx);
+        below += c[j];
+    }
+    if (tid == 0) {
+        v = q = 0; m = 0;
+        for (int k = 0; k < WAVES; ++k) { v += smem[WAVES + k]; q += smem[2 * WAVES + k]; m = max(m, (unsigned)smem[3 * WAVES + k]); }
+        out->n = n; out->violations = v; out->nan_count = q;
+        out->max_rel = __uint_as_float(m); out->accept = v == 0 ? 1u : 0u; out->pad_ = 0;
+    }
+}
+// What workgroups exchange within a launch goes past the XCDs' caches (atomics and write-through stores of agent scope), so a count that
+// follows its completion publishes it; a release fence would write back an L2 for every workgroup (100 us of them at 256).
+__device__ __forceinline__ unsigned publish(unsigned int* count, unsigned add, unsigned int& word) {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __builtin_amdgcn_s_waitcnt(0x0F70);                      // vmcnt(0): this wavefront's are complete
+    __syncthreads();
+    if (threadIdx.x == 0) word = add ? __hip_atomic_fetch_add(count, add, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + add : 0;
+    __syncthreads();
+    return word;
+}
+// Counts `done` more tiles, whose results this workgroup has added; the workgroup that completes the count forms the profile.
+__device__ __forceinline__ void tiles_done(const SplitArgs& p, const SettleArgs& r, unsigned done, char* lds, unsigned int& word) {
+    if (publish(&r.check.stats[kDoneFlag].flag, done, word) != r.tiles) return;
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    profile_alone(CheckWorkspace{p.ws_hist, p.ws_coarse, p.ws_stats}, (int)p.check_slots, r.n, r.out, reinterpret_cast<unsigned long long*>(lds));
+}
+// On images a workgroup per compute unit walks the slots (where the screen has settled everything, thousands would only be given LDS
+// and leave); the in-load forms have no registers for that (39 spilled instead of 12) and take a workgroup per slot.
+template <bool AREG, bool CONV>
+__global__ __launch_bounds__(kSplitThreads) void absgemm_settle(SplitArgs p, SettleArgs r) {
+    extern __shared__ __attribute__((aligned(16))) char lds[];
+    __shared__ unsigned int chk_hist[kBins * 2];
+    if (settled_by_screen(r, lds)) return;
+    unsigned done = 0;
+    if (AREG) {
+        if (blockIdx.x < p.ntiles) done = absgemm_split_slot<true, false, false, AREG, CONV>(p, blockIdx.x, gridDim.x, lds, chk_hist);
+    } else {
+        for (unsigned wg = blockIdx.x; wg < p.ntiles; wg += gridDim.x) {
+            __syncthreads();                                 // the tile before has read its histogram
+            // (the arguments are read anew for each tile: kept in registers through it they cost the loop of the product some)
+            typedef const SplitArgs __attribute__((address_space(4)))* ArgsPtr;
+            ArgsPtr q = (ArgsPtr)__builtin_amdgcn_kernarg_segment_ptr();
+            asm volatile("" : "+s"(q));
+            done += absgemm_split_slot<true, false, false, AREG, CONV>(*(const SplitArgs*)q, wg, gridDim.x, lds, chk_hist);
+            __builtin_amdgcn_s_waitcnt(0x0F70);              // vmcnt(0): nothing of it counts in the next tile's waits
         }
     }
+    tiles_done(p, r, done, lds, chk_hist[0]);
+}
+// The reduction in parts: a workgroup leaves its part's sums in the workspace, and the one that brings a tile's last part adds
+// them in split_combine's order, forms the bound and checks it.
+__global__ __launch_bounds__(kSplitThreads) void absgemm_settle_parts(SplitArgs p, SettleArgs r) {
+    extern __shared__ __attribute__((aligned(16))) char lds[];
+    __shared__ unsigned int chk_hist[kBins * 2];
+    if (settled_by_screen(r, lds)) return;
+    if (blockIdx.x >= p.ntiles * (unsigned)p.ksplit) return;
+    if (!absgemm_split_slot<false, true, false, false, false, true>(p, blockIdx.x, gridDim.x, lds, chk_hist)) return;
+    const unsigned tile = blockIdx.x % p.ntiles;
+    const bool last = publish(&r.check.stats[tile].flag, 1u, chk_hist[0]) == (unsigned)p.ksplit;
+    if (!last) return;
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    __syncthreads();
+    for (int i = threadIdx.x; i < kBins * 2; i += kSplitThreads) chk_hist[i] = 0;
+    __syncthreads();
+    unsigned m0, n0, z;
+    locate_tile(p, tile, m0, n0, z);
+    const long per = p.M * p.N, total = per * (long)(p.ntiles / p.slots_per_z);
+    ThreadAcc acc;
+    const QuickCheck quick(1.f, p.eps_rel);                  // (of the estimates only the bins: the bound is at hand)
+    unsigned known = 0;
+    // a thread has a column of every fourth row, eight of them at a time: the loads' latency is what the loop waits for
+    constexpr int BATCH = 8, RSTEP = kSplitThreads / STILE;
+    const long col = (long)n0 + (threadIdx.x & (STILE - 1)), row0 = (long)m0 + threadIdx.x / STILE;
+    if (col < p.N) {
+        const double ab = p.bias ? fabs((double)p.bias[col]) : 0.0;
+        const double off_pos = bound_offset(p, p.si, ab), off_zero = bound_offset(p, p.si0, ab);
+#pragma unroll 1
+        for (int i0 = 0; i0 < STILE / RSTEP; i0 += BATCH) {
+            double sv[BATCH];
+            float c[BATCH], rf[BATCH];
+            long at[BATCH];
+#pragma unroll
+            for (int i = 0; i < BATCH; ++i) {
+                const long row = min(row0 + (i0 + i) * RSTEP, p.M - 1), y = (long)z * p.strideY + row * p.ldy + col;
+                at[i] = (long)z * per + row * p.N + col;
+                sv[i] = 0.0; c[i] = p.claimed[y]; rf[i] = p.ref[y];
+            }
+            for (int k = 0; k < p.ksplit; ++k)
+#pragma unroll
+                for (int i = 0; i < BATCH; ++i) sv[i] += p.partial[(long)k * total + at[i]];
+#pragma unroll
+            for (int i = 0; i < BATCH; ++i) {
+                if (row0 + (i0 + i) * RSTEP >= p.M) continue;
+                const float t32 = up32(bound_of_sum(p, sv[i], off_pos, off_zero));
+                unsigned bin;
+                if (fabsf(c[i] - rf[i]) <= 0x1p100f && quick_settled(c[i], rf[i], 0x1p120f, quick, known, bin)) {
+                    acc.violations += !(fabs((double)c[i] - (double)rf[i]) <= p.alpha * (double)t32);
+                    atomicAdd(&chk_hist[(bin >> 1) * 4 + (threadIdx.x & 3)], (bin & 1) ? 0x10000u : 1u);
+                } else {
+                    check_one_packed(c[i], rf[i], t32, p.alpha, p.eps_rel, chk_hist, threadIdx.x & 3, acc);
+                    known = acc.max_bits;
+                }
+            }
+        }
+    }
+    __syncthreads();
+    flush_packed(p, chk_hist);
+    flush_counters(p, acc);
+    tiles_done(p, r, 1u, lds, chk_hist[0]);
 }
 
 // Adds the parts of a PARTIAL launch in a fixed order and forms the bound exactly as the epilogue
@@ -1071,22 +1282,24 @@ struct SplitCheckHost {
     const float* claimed; const float* ref; long ldy, strideY; double alpha, eps_rel; tao_profile* out;
 };
 
-// Launches split3_bf16 for one operand: src [batch][rows][K] with row stride ld (trans == 0) or
-// [batch][K][rows] (trans != 0) -> image.  zero_ptr / zero_n: the side job described at the kernel.
-static void launch_split3(const float* src, long rows, long K, long ld, int trans, long batch, long stride,
-                          unsigned short* image, unsigned int* zero_ptr, long zero_n, hipStream_t st) {
-    const long Kp = (K + SBK - 1) / SBK * SBK;
-    // work items of split3_bf16: (row, chunk) pairs, or whole 64-row x 256-k patches of 2048
-    long b = trans ? (((rows + 3) & ~3L) * (Kp >> 3) + 255) / 256 : ((rows + 63) / 64) * ((Kp + 255) / 256) * 8;
-    const unsigned blocks = (unsigned)(b < 1 ? 1 : (b > 256L * 64 ? 256L * 64 : b));
-    if (trans) {
-        hipLaunchKernelGGL((split3_bf16<true>), dim3(blocks, (unsigned)batch), dim3(256), 0, st,
-                           src, rows, K, ld, stride, image, Kp, 0, zero_ptr, zero_n);
-    } else {
-        const int vec = aligned(src, 16) && (ld % 4 == 0) && (stride % 4 == 0);
-        hipLaunchKernelGGL((split3_bf16<false>), dim3(blocks, (unsigned)batch), dim3(256), 0, st,
-                           src, rows, K, ld, stride, image, Kp, vec, zero_ptr, zero_n);
+// Launches split3_bf16 for one or two operands: src [batch][rows][K] with row stride ld (STRAIGHT) or
+// [batch][K][rows] (TRANSPOSED) -> image.  zero_ptr / zero_n: the side job described at the kernel.
+static void launch_split3(const SplitOperand* ops, int n, unsigned int* zero_ptr, long zero_n, hipStream_t st) {
+    SplitOperands a = {};
+    a.zero_ptr = zero_ptr; a.zero_n = zero_ptr ? zero_n : 0;
+    long first = 0;
+    for (int o = 0; o < n; ++o) {
+        const SplitOperand& p = ops[o];
+        a.op[o] = p;
+        const long groups = (p.K + SBK - 1) / SBK;
+        // work items of split3_bf16: (row, chunk) pairs, or whole 64-row x 256-k patches of 2048
+        const long b = ((p.form == MAGNITUDES ? p.K / 8 + 4 : p.form == TRANSPOSED ? ((p.rows + 3) & ~3L) * groups * 4
+                         : (p.rows + 63) / 64 * ((groups + 7) / 8) * 2048) * p.batch + 255) / 256;
+        a.first[o] = first;
+        first += b < 1 ? 1 : (b > 256L * 64 ? 256L * 64 : b);
     }
+    for (int o = n; o < 3; ++o) a.first[o] = first;
+    hipLaunchKernelGGL(split3_bf16, dim3((unsigned)first), dim3(256), 0, st, a);
 }
 
 // The product on prepared images.  ws: what core_workspace_bytes(M, N, K, batch, chk != NULL) asks for.
@@ -1095,12 +1308,14 @@ static void launch_split3(const float* src, long rows, long K, long ld, int tran
 // claimed as well when tau is stored.
 // Af != NULL: the A operand is split while it is loaded (AREG instantiations; the caller has
 // checked in_load_split_ok); A3 is then unused.
+// screened: a screen has been enqueued with this workspace; one launch here settles the check.
 struct ConvHost { int H, W, C, OW, S, sh, sw, ph, pw, dh, dw; unsigned ohow; };
 // cv != NULL (with Af): Af is a convolution's channels-last input and A its implicit patch matrix.
 static int split_core(const unsigned short* A3, const unsigned short* W3, const float* bias, float* tau,
                       long M, long N, long K, long ldt, long batch, long strideT, bool shared_w,
                       const tao_fp_model& md, void* ws, void* stream, const SplitCheckHost* chk, bool cleared,
-                      const float* Af = nullptr, long lda = 0, long strideA = 0, const ConvHost* cv = nullptr) {
+                      const float* Af = nullptr, long lda = 0, long strideA = 0, const ConvHost* cv = nullptr,
+                      bool screened = false) {
     const long Kp_ = K + (bias ? 1 : 0);
     const double c = gamma_up(Kp_, md);
     if (!(c == c)) return TAO_ERR_K_RANGE;
@@ -1123,10 +1338,10 @@ static int split_core(const unsigned short* A3, const unsigned short* W3, const 
         // beyond, the two routes take the same time (2048 x 12288 over 2048 747 / 745, over 4096 1422 / 1416) and the epilogue
         // saves the memory of the stored bound.
         // (A reduction cut into parts is checked by the pass that adds the parts, whatever its length.)
-        two_pass = parts < 2 && K < kEpilogueCheckMinK && !(md.flags & TAO_FLAG_CHECK_IN_EPILOGUE) &&
+        two_pass = !screened && parts < 2 && K < kEpilogueCheckMinK && !(md.flags & TAO_FLAG_CHECK_IN_EPILOGUE) &&
                    chk->ldy == N && (batch == 1 || chk->strideY == M * N);
         if (two_pass && !tau) {
-            tau = reinterpret_cast<float*>(wsb + partial_bytes + round_up_256(check_workspace_bytes()));
+            tau = reinterpret_cast<float*>(static_cast<char*>(check_ws) + round_up_256(check_workspace_bytes()));
             ldt = N; strideT = M * N;
         }
     }
@@ -1193,12 +1408,15 @@ static int split_core(const unsigned short* A3, const unsigned short* W3, const 
             if (r == hipSuccess)
                 r = hipFuncSetAttribute(reinterpret_cast<const void*>(&absgemm_split<true, false, false, true, true>),
                                         hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
+            for (const void* settling : {reinterpret_cast<const void*>(&absgemm_settle<false, false>), reinterpret_cast<const void*>(&absgemm_settle<true, false>),
+                                         reinterpret_cast<const void*>(&absgemm_settle<true, true>), reinterpret_cast<const void*>(&absgemm_settle_parts)})
+                if (r == hipSuccess) r = hipFuncSetAttribute(settling, hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
             return r;
         });
         if (e != hipSuccess) { g_last_hip_error = (int)e; return TAO_ERR_LAUNCH; }
     }
     p.claimed = nullptr; p.ref = nullptr; p.ldy = 0; p.strideY = 0; p.alpha = 0.0; p.eps_rel = 0.0;
-    p.ws_hist = nullptr; p.ws_coarse = nullptr; p.ws_stats = nullptr;
+    p.ws_hist = nullptr; p.ws_coarse = nullptr; p.ws_stats = nullptr; p.check_slots = kMaxCheckBlocks;
     p.ksplit = 1; p.gpp = Kp / SBK; p.partial = nullptr;
     {
         const unsigned gw = (unsigned)(tiles_n < 16 ? tiles_n : 16), gh = (unsigned)(tiles_m < 16 ? tiles_m : 16);
@@ -1223,6 +1441,11 @@ static int split_core(const unsigned short* A3, const unsigned short* W3, const 
         p.claimed = chk->claimed; p.ref = chk->ref; p.ldy = chk->ldy; p.strideY = chk->strideY;
         p.alpha = chk->alpha; p.eps_rel = chk->eps_rel;
         p.ws_hist = cw.hist; p.ws_coarse = cw.coarse; p.ws_stats = cw.stats;
+        if (screened) {
+            const CheckWorkspace half = screened_second_half(cw);
+            p.ws_hist = half.hist; p.ws_coarse = half.coarse; p.ws_stats = half.stats;
+            p.check_slots = kSettleSlots;
+        }
     }
     // the streaming check of a stored bound, after the launches that store it
     auto then_check = [&]() -> int {
@@ -1231,6 +1454,7 @@ static int split_core(const unsigned short* A3, const unsigned short* W3, const 
         return tao_check_and_profile(chk->claimed, chk->ref, tau, M * N * batch, chk->alpha, chk->eps_rel, chk->out,
                                      check_ws, check_workspace_bytes(), stream);
     };
+    const SettleArgs settle = {cw, (unsigned)ntiles, (unsigned long long)((__int128)M * N * batch), chk ? chk->out : nullptr};
     if (parts >= 2) {
         // the reduction in parts, then one pass that adds them and forms (and checks) the bound
         const long groups = Kp / SBK;
@@ -1238,6 +1462,11 @@ static int split_core(const unsigned short* A3, const unsigned short* W3, const 
         p.ksplit = parts; p.gpp = (groups + parts - 1) / parts;
         p.ksplit = (int)((groups + p.gpp - 1) / p.gpp);             // no empty part
         p.partial = reinterpret_cast<double*>(wsb);
+        if (screened) {
+            const long wgs = (long)p.ntiles * p.ksplit;              // (the profile's 32 groups have a workgroup each)
+            hipLaunchKernelGGL(absgemm_settle_parts, dim3((unsigned)(wgs < kGroups ? kGroups : wgs)), dim3(kSplitThreads), lds_bytes, st, p, settle);
+            return launch_status();
+        }
         hipLaunchKernelGGL((absgemm_split<false, true>), dim3(p.ntiles * (unsigned)p.ksplit), dim3(kSplitThreads), lds_bytes, st, p);
         const long total = M * N * batch;
         long want = (total + (long)kCheckThreads * 2 - 1) / ((long)kCheckThreads * 2);   // (a few elements per thread: outputs that need parts are small)
@@ -1266,6 +1495,14 @@ static int split_core(const unsigned short* A3, const unsigned short* W3, const 
         else          hipLaunchKernelGGL((absgemm_split<false, false, true>), dim3(walk ? cus : p.ntiles), dim3(kSplitThreads), lds_bytes, st, p);
         return then_check();
     }
+    if (screened) {
+        const unsigned cus = (unsigned)device_cus() & ~7u, g = Af || p.ntiles < cus ? p.ntiles : cus;      // (see absgemm_settle)
+        const dim3 grid(g < (unsigned)kGroups ? (unsigned)kGroups : g);
+        if (Af && cv) hipLaunchKernelGGL((absgemm_settle<true, true>), grid, dim3(kSplitThreads), lds_bytes, st, p, settle);
+        else if (Af)  hipLaunchKernelGGL((absgemm_settle<true, false>), grid, dim3(kSplitThreads), lds_bytes, st, p, settle);
+        else          hipLaunchKernelGGL((absgemm_settle<false, false>), grid, dim3(kSplitThreads), lds_bytes, st, p, settle);
+        return launch_status();
+    }
     const int slots = kMaxCheckBlocks;                       // workgroup b adds to partial result b % 256
     if (!cleared) hipLaunchKernelGGL(zero_words, dim3(64), dim3(256), 0, st, cw.hist, (long)(check_workspace_bytes() / 4));
     if (Af && cv) hipLaunchKernelGGL((absgemm_split<true, false, false, true, true>), dim3(p.ntiles), dim3(kSplitThreads), lds_bytes, st, p);
@@ -1282,6 +1519,26 @@ static bool epilogue_check_without_parts(long M, long N, long K, long batch, con
     const bool two_pass = K < kEpilogueCheckMinK && !(md.flags & TAO_FLAG_CHECK_IN_EPILOGUE) &&
                           chk->ldy == N && (batch == 1 || chk->strideY == M * N);
     return !two_pass && split_k_parts(M, N, K, batch) < 2;
+}
+
+// The screen of a checked bound (linear_screen.hip).  Whether one goes ahead of the exact route: the bound itself is not asked for,
+// and its constants allow it.
+static bool screened(long M, long N, long K, long batch, const float* bias, const float* tau, const tao_fp_model& md, const SplitCheckHost* chk) {
+    if (!chk || tau || K <= 0 || (md.flags & TAO_FLAG_CHECK_IN_EPILOGUE) || chk->ldy >= kScreenMaxLd) return false;
+    const long Kp_ = K + (bias ? 1 : 0);
+    const double uflow = (md.flags & TAO_FLAG_UNDERFLOW_TERMS) ? (double)Kp_ * 0x1p-148 : 0.0;
+    return screen_usable(K, md.u, gamma_up(Kp_, md) * kGuard, chk->alpha, uflow);
+}
+// The check's workspace within what core_workspace_bytes asks for; the screen's launches want all of it cleared.
+static CheckWorkspace core_check_workspace(void* rest, long M, long N, long K, long batch) {
+    const int parts = split_k_parts(M, N, K, batch);
+    const size_t partial_bytes = parts >= 2 ? round_up_256((size_t)parts * (size_t)batch * (size_t)M * (size_t)N * sizeof(double)) : 0;
+    return carve_check_workspace(static_cast<char*>(rest) + partial_bytes);
+}
+static int run_screen(const ScreenOperand& A, const ScreenOperand& W, const float* bias, long M, long N, long K, long batch,
+                      const tao_fp_model& md, const SplitCheckHost* chk, const CheckWorkspace& cw, hipStream_t st) {
+    const ScreenCheck sc = {chk->claimed, chk->ref, chk->ldy, chk->strideY, chk->alpha, chk->eps_rel};
+    return launch_screen(A, W, bias, M, N, K, batch, gamma_up(K + (bias ? 1 : 0), md) * kGuard, sc, cw, st);
 }
 
 // Validation shared by the entry points below (everything but the operands themselves).
@@ -1347,25 +1604,32 @@ static int split_run(const float* A, const float* W, const float* bias, float* t
     unsigned short* W3 = reinterpret_cast<unsigned short*>(wsb + bytesA);
     void* rest = wsb + bytesA + bytesW;
     hipStream_t st = (hipStream_t)stream;
-    bool cleared = false;
     // An A operand that only one or two column tiles use is split while the product loads it (no
     // pre-pass over it, no image): whole groups, 16-byte aligned rows, the reduction in one part, and
     // not a launch whose short reduction is better served by the tile walk.
     const bool in_load = K > 0 && K % SBK == 0 && N <= 2 * STILE && aligned(A, 16) && lda % 4 == 0 && strideA % 4 == 0 &&
                          split_k_parts(M, N, K, batch) < 2 && K / SBK > kWalkMaxGroups &&
                          (__int128)M * lda < ((__int128)1 << 40);
+    const bool scr = screened(M, N, K, batch, bias, tau, md, chk) && !(in_load && lda >= kScreenMaxLd);
+    const CheckWorkspace cw = core_check_workspace(rest, M, N, K, batch);
+    bool cleared = false;
     if (K > 0) {
-        // the operand pre-pass also clears the partial results of an epilogue check (no parts: those
+        // the operand pre-pass also clears the partial results of a screen and of an epilogue check (no parts: those
         // are checked by the combining pass, which needs none)
-        cleared = epilogue_check_without_parts(M, N, K, batch, md, chk);
-        unsigned int* zp = nullptr;
-        if (cleared) zp = carve_check_workspace(rest).hist;       // (no parts: the check's workspace comes first)
-        const long zn = (long)(check_workspace_bytes() / 4);
-        if (!in_load) launch_split3(A, M, K, lda, 0, batch, strideA, A3, zp, zn, st);
-        launch_split3(W, N, K, ldw, trans_w, shared_w ? 1 : batch, strideW, W3, in_load ? zp : nullptr, in_load ? zn : 0L, st);
+        cleared = scr || epilogue_check_without_parts(M, N, K, batch, md, chk);
+        const SplitOperand ops[2] = {{W, N, K, ldw, shared_w ? 1 : batch, strideW, W3, trans_w ? TRANSPOSED : STRAIGHT}, {A, M, K, lda, batch, strideA, A3, STRAIGHT}};
+        launch_split3(ops, in_load ? 1 : 2, cleared ? cw.hist : nullptr, (long)(check_workspace_bytes() / 4), st);
+    }
+    if (scr) {
+        const long groups = (K + SBK - 1) / SBK;
+        ScreenOperand oa = {A3, groups * ((M + STILE - 1) / STILE) * kBlock, 0, nullptr};
+        if (in_load) oa = {A, strideA * 4, lda, nullptr};
+        const ScreenOperand ow = {W3, shared_w ? 0 : groups * ((N + STILE - 1) / STILE) * kBlock, 0, nullptr};
+        rc = run_screen(oa, ow, bias, M, N, K, batch, md, chk, cw, st);
+        if (rc != TAO_OK) return rc;
     }
     return split_core(A3, W3, bias, tau, M, N, K, ldt, batch, strideT, shared_w, md, rest, stream, chk, cleared,
-                      in_load ? A : nullptr, lda, strideA);
+                      in_load ? A : nullptr, lda, strideA, nullptr, scr);
 }
 
 // The same on images the caller has prepared with tao_split_operand.
@@ -1385,8 +1649,23 @@ static int images_run(const void* A_image, const void* W_image, const float* bia
     if (chk && (!chk->claimed || !chk->ref)) return TAO_ERR_NULL;
     if (!aligned(A_image, 256) || !aligned(W_image, 256) || !aligned(bias, 4) || !aligned(tau, 4)) return TAO_ERR_ALIGN;
     if (chk && (!aligned(chk->claimed, 4) || !aligned(chk->ref, 4))) return TAO_ERR_ALIGN;
-    return split_core(static_cast<const unsigned short*>(A_image), static_cast<const unsigned short*>(W_image), bias, tau,
-                      M, N, K, ldt, batch, strideT, sw, md, ws, stream, chk, false);
+    const unsigned short* A3 = static_cast<const unsigned short*>(A_image);
+    const unsigned short* W3 = static_cast<const unsigned short*>(W_image);
+    bool cleared = false;
+    const bool scr = screened(M, N, K, batch, bias, tau, md, chk);
+    if (scr) {
+        hipStream_t st = (hipStream_t)stream;
+        const CheckWorkspace cw = core_check_workspace(ws, M, N, K, batch);
+        cleared = true;
+        hipLaunchKernelGGL(zero_words, dim3(256), dim3(256), 0, st, cw.hist, (long)(check_workspace_bytes() / 4));
+        const long groups = (K + SBK - 1) / SBK;
+        const ScreenOperand oa = {A3, groups * ((M + STILE - 1) / STILE) * kBlock, 0, nullptr};
+        const ScreenOperand ow = {W3, sw ? 0 : groups * ((N + STILE - 1) / STILE) * kBlock, 0, nullptr};
+        rc = run_screen(oa, ow, bias, M, N, K, batch, md, chk, cw, st);
+        if (rc != TAO_OK) return rc;
+    }
+    return split_core(A3, W3, bias, tau, M, N, K, ldt, batch, strideT, sw, md, ws, stream, chk, cleared,
+                      nullptr, 0, 0, nullptr, scr);
 }
 }  // namespace tao
 
@@ -1405,7 +1684,8 @@ int tao_split_operand(const float* src, long rows, long K, long ld, int trans, l
     const size_t need = tao::image_bytes(rows, K, batch);
     if (need == 0 || !image || !aligned(image, 256) || image_bytes < need) return TAO_ERR_WORKSPACE;
     if (batch >= 65536) return TAO_ERR_SHAPE;                      // (second grid dimension)
-    launch_split3(src, rows, K, ld, trans, batch, stride, static_cast<unsigned short*>(image), nullptr, 0L, (hipStream_t)stream);
+    const SplitOperand op = {src, rows, K, ld, batch, stride, static_cast<unsigned short*>(image), trans ? TRANSPOSED : STRAIGHT};
+    launch_split3(&op, 1, nullptr, 0L, (hipStream_t)stream);
     return launch_status();
 }
 
@@ -1433,6 +1713,12 @@ static bool conv_split_ok(long M, long N, long K, long C, long batch_hwc, const 
     // pixels, 32-bit pixel arithmetic in the kernel
     return C % SBK == 0 && K / SBK >= 1 && split_k_parts(M, N, K, 1) < 2 && aligned(x, 16) && batch_hwc < (1L << 40);
 }
+// What the screen of a checked convolution takes behind the rest of the workspace: the input's BF16 magnitudes and a line of zeros
+// (0: offsets beyond 31 bits, no screen).
+static size_t conv_pixel_bytes(long batch, long H, long W, long C) {
+    const __int128 b = (__int128)batch * H * W * C * 2 + 64;
+    return b < ((__int128)1 << 31) ? (size_t)b : 0;
+}
 static int conv_split_run(const float* x, const float* w, const float* bias, float* tau,
                           long batch, long H, long W, long C, long Cout, long R, long S,
                           long stride_h, long stride_w, long pad_h, long pad_w, long dil_h, long dil_w,
@@ -1459,14 +1745,26 @@ static int conv_split_run(const float* x, const float* w, const float* bias, flo
     char* wsb = static_cast<char*>(ws);
     unsigned short* W3 = reinterpret_cast<unsigned short*>(wsb);
     void* rest = wsb + bytesW;
-    const bool cleared = epilogue_check_without_parts(M, N, K, 1, md, chk);
-    launch_split3(w, N, K, K, 0, 1, 0, W3, cleared ? carve_check_workspace(rest).hist : nullptr,
-                  cleared ? (long)(check_workspace_bytes() / 4) : 0L, (hipStream_t)stream);
     ConvHost cv;
     cv.H = (int)H; cv.W = (int)W; cv.C = (int)C; cv.OW = (int)OW; cv.S = (int)S;
     cv.sh = (int)stride_h; cv.sw = (int)stride_w; cv.ph = (int)pad_h; cv.pw = (int)pad_w; cv.dh = (int)dil_h; cv.dw = (int)dil_w;
     cv.ohow = (unsigned)(OH * OW);
-    return split_core(nullptr, W3, bias, tau, M, N, K, N, 1, M * N, true, md, rest, stream, chk, cleared, x, K, 0, &cv);
+    // (a workspace without room for the input's magnitudes, as the exact route needs none, gets no screen)
+    const size_t pixel_bytes = conv_pixel_bytes(batch, H, W, C), pixels_at = round_up_256(need);
+    const bool scr = pixel_bytes > 0 && ws_bytes >= pixels_at + pixel_bytes && screened(M, N, K, 1, bias, tau, md, chk);
+    const bool cleared = scr || epilogue_check_without_parts(M, N, K, 1, md, chk);
+    const CheckWorkspace cw = carve_check_workspace(rest);
+    unsigned short* px = reinterpret_cast<unsigned short*>(wsb + pixels_at);
+    const SplitOperand ops[2] = {{w, N, K, K, 1, 0, W3, STRAIGHT}, {x, 1, batch * H * W * C, 0, 1, 0, px, MAGNITUDES}};
+    launch_split3(ops, scr ? 2 : 1, cleared ? cw.hist : nullptr, (long)(check_workspace_bytes() / 4), (hipStream_t)stream);
+    if (scr) {
+        const ScreenPixels pixels = {cv.H, cv.W, cv.C, cv.OW, cv.S, cv.sh, cv.sw, cv.ph, cv.pw, cv.dh, cv.dw, cv.ohow, cv.C / SBK,
+                                     (unsigned)(batch * H * W * C * 2)};
+        const ScreenOperand oa = {px, 0, 0, &pixels}, ow = {W3, 0, 0, nullptr};
+        rc = run_screen(oa, ow, bias, M, N, K, 1, md, chk, cw, (hipStream_t)stream);
+        if (rc != TAO_OK) return rc;
+    }
+    return split_core(nullptr, W3, bias, tau, M, N, K, N, 1, M * N, true, md, rest, stream, chk, cleared, x, K, 0, &cv, scr);
 }
 }  // namespace tao
 
@@ -1486,7 +1784,8 @@ size_t tao_conv2d_split_workspace_bytes(long batch, long H, long W, long C, long
     long OH = 0, OW = 0, M = 0, K = 0;
     if (tao::conv_geometry(batch, H, W, C, Cout, R, S, stride_h, stride_w, pad_h, pad_w, dil_h, dil_w, &OH, &OW, &M, &K) != TAO_OK) return 0;
     const size_t img = (M == 0 || Cout == 0) ? 0 : tao::image_bytes(Cout, K, 1);
-    return img + tao::core_workspace_bytes(M, Cout, K, 1, with_check != 0);
+    const size_t need = img + tao::core_workspace_bytes(M, Cout, K, 1, with_check != 0);
+    return with_check && img ? tao::round_up_256(need) + tao::conv_pixel_bytes(batch, H, W, C) : need;
 }
 
 int tao_bound_conv2d_split(const float* x, const float* w, const float* bias, float* tau,

@@ -16,7 +16,7 @@ struct BlockStats {          // one per pass-1 workgroup, in the workspace after
     unsigned long long violations;
     unsigned long long nans;
     unsigned int max_bits;   // bit pattern of the largest non-NaN error (errors are >= 0)
-    unsigned int pad;
+    unsigned int flag;       // not a counter: no pass writes it (linear_screen.hpp)
 };
 
 struct ThreadAcc {
@@ -182,7 +182,8 @@ __device__ __forceinline__ void flush_block_stats(const ThreadAcc& acc, unsigned
             s.violations += red[w * 3]; s.nans += red[w * 3 + 1];
             s.max_bits = max(s.max_bits, red[w * 3 + 2]);
         }
-        ws_stats[blockIdx.x] = s;
+        BlockStats& o = ws_stats[blockIdx.x];
+        o.violations = s.violations; o.nans = s.nans; o.max_bits = s.max_bits;
     }
 }
 
@@ -199,6 +200,50 @@ inline CheckWorkspace carve_check_workspace(void* ws) {
     w.coarse = w.hist + (size_t)kMaxCheckBlocks * kBins;
     w.stats = (BlockStats*)(w.coarse + (size_t)kMaxCheckBlocks * kGroups);
     return w;
+}
+// Group `grp` of the profile of the partial results of `nblocks` (at most PARTIALS) pass-1 workgroups, by one workgroup of
+// THREADS threads; group 0 brings the scalar fields.  smem: profile_smem_words(THREADS) 64-bit words.
+constexpr int profile_smem_words(int threads) { return threads + 4 * (threads / kWave); }
+template <int THREADS, int PARTIALS>
+__device__ __forceinline__ void profile_group(const CheckWorkspace& w, int nblocks, int grp, unsigned long long n, tao_profile* out,
+                                              unsigned long long* smem) {
+    constexpr int WAVES = THREADS / kWave;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+    // nearest-rank percentiles p50, p99, p99.9; the three bin and three edge fields of tao_profile
+    // are consecutive
+    const RankQuery q[3] = {{1, 2}, {99, 100}, {999, 1000}};
+    reduce_group<3, THREADS, PARTIALS>(w.hist, w.coarse, nblocks, grp, n, out->hist, q, &out->p50_bin, &out->p50, smem);
+    if (grp != 0) return;
+    unsigned long long* wv = smem + THREADS + WAVES;
+    unsigned long long* wq = wv + WAVES;
+    unsigned int* wm = reinterpret_cast<unsigned int*>(wq + WAVES);
+    // counters of pass 1
+    unsigned long long v = 0, qn = 0; unsigned int m = 0;
+    for (int k = tid; k < nblocks; k += THREADS) {
+        v += w.stats[k].violations; qn += w.stats[k].nans; m = max(m, w.stats[k].max_bits);
+    }
+#pragma unroll
+    for (int o = kWave / 2; o > 0; o >>= 1) {
+        v += __shfl_xor(v, o, kWave); qn += __shfl_xor(qn, o, kWave);
+        m = max(m, (unsigned int)__shfl_xor(m, o, kWave));
+    }
+    if (lane == 0) { wv[wave] = v; wq[wave] = qn; wm[wave] = m; }
+    __syncthreads();
+    if (tid == 0) {
+        v = 0; qn = 0; m = 0;
+        for (int k = 0; k < WAVES; ++k) { v += wv[k]; qn += wq[k]; m = max(m, wm[k]); }
+        out->n = n;
+        out->violations = v;
+        out->nan_count = qn;
+        out->max_rel = __uint_as_float(m);
+        out->accept = (v == 0) ? 1u : 0u;
+        out->pad_ = 0;
+        if (n == 0) {
+            out->p50_bin = out->p99_bin = out->p999_bin = 0;
+            out->p50 = out->p99 = out->p999 = bin_upper_edge(0);
+        }
+    }
+    __syncthreads();
 }
 // Enqueue the finalising kernel over the partials of `nblocks` pass-1 workgroups (defined with the check pass).
 void launch_profile_reduce(const CheckWorkspace& w, int nblocks, unsigned long long n, tao_profile* out, hipStream_t st);

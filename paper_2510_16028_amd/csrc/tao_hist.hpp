@@ -14,8 +14,6 @@ constexpr int kMaxPartials = 256;            // pass-1 workgroups (one per CU), 
 constexpr int kBinsPerReduceBlock = 64;
 constexpr int kGroups = kBins / kBinsPerReduceBlock;                      // 32 coarse groups of 64 bins
 constexpr int kReduceThreads = 1024;
-constexpr int kReduceSlices = kReduceThreads / kBinsPerReduceBlock;      // 16
-constexpr int kPartialsPerThread = kMaxPartials / kReduceSlices;         // 16 independent loads
 constexpr int kReduceWaves = kReduceThreads / kWave;
 
 // bin of an error value: bits >> 20 (8 exponent bits, 3 mantissa bits); NaN -> last bin
@@ -60,42 +58,43 @@ __device__ __forceinline__ void flush_histogram(const unsigned int* hist, unsign
 
 struct RankQuery { unsigned int num, den; };
 
-// Second level, one 1024-thread workgroup per group `grp` of 64 bins: sums the partial histograms
-// of `nblocks` pass-1 workgroups (ws_hist[k][kBins], 256-byte contiguous reads, all loads
+// Second level, one workgroup (THREADS threads) per group `grp` of 64 bins: sums the partial histograms
+// of `nblocks` (at most PARTIALS) pass-1 workgroups (ws_hist[k][kBins], 256-byte contiguous reads, all loads
 // independent), writes the 64-bit totals to hist_out, derives the number of elements below its own
 // bins from the coarse counts (ws_coarse[k][kGroups]) and, for each of the NQ rank queries, writes
 // the bin holding rank max(1, ceil(n num/den)) and its upper edge if that bin is one of its own.
 // Every query is answered by exactly one workgroup when n > 0; nothing is written for n == 0.
-// smem: kReduceThreads + kReduceWaves 64-bit words.
-template <int NQ>
+// smem: THREADS + THREADS / kWave 64-bit words.
+template <int NQ, int THREADS = kReduceThreads, int PARTIALS = kMaxPartials>
 __device__ __forceinline__ void reduce_group(const unsigned int* __restrict__ ws_hist,
                                              const unsigned int* __restrict__ ws_coarse, int nblocks, int grp,
                                              unsigned long long n, uint64_t* __restrict__ hist_out,
                                              const RankQuery* q, unsigned int* __restrict__ bin_out,
                                              float* __restrict__ edge_out, unsigned long long* smem) {
+    constexpr int SLICES = THREADS / kBinsPerReduceBlock, PER_THREAD = PARTIALS / SLICES;       // (16 independent loads)
     unsigned long long* part = smem;
-    unsigned long long* wsum = smem + kReduceThreads;
+    unsigned long long* wsum = smem + THREADS;
     const int tid = threadIdx.x;
     const int lane = tid & (kWave - 1), wave = tid / kWave;
     const int b = tid & (kBinsPerReduceBlock - 1);
     const int slice = tid / kBinsPerReduceBlock;
     const int bin = grp * kBinsPerReduceBlock + b;
-    unsigned int vals[kPartialsPerThread];
+    unsigned int vals[PER_THREAD];
 #pragma unroll
-    for (int j = 0; j < kPartialsPerThread; ++j) {
-        const int k = slice + kReduceSlices * j;
+    for (int j = 0; j < PER_THREAD; ++j) {
+        const int k = slice + SLICES * j;
         vals[j] = (k < nblocks) ? ws_hist[(size_t)k * kBins + bin] : 0u;
     }
     unsigned long long below = 0;
     const int total = nblocks * kGroups;
 #pragma unroll
-    for (int j = 0; j < (kMaxPartials * kGroups) / kReduceThreads; ++j) {
-        const int e = tid + kReduceThreads * j;
+    for (int j = 0; j < (PARTIALS * kGroups) / THREADS; ++j) {
+        const int e = tid + THREADS * j;
         if (e < total && (e % kGroups) < grp) below += ws_coarse[e];
     }
     unsigned long long s = 0;
 #pragma unroll
-    for (int j = 0; j < kPartialsPerThread; ++j) s += vals[j];
+    for (int j = 0; j < PER_THREAD; ++j) s += vals[j];
     part[tid] = s;
 #pragma unroll
     for (int o = kWave / 2; o > 0; o >>= 1) below += __shfl_xor(below, o, kWave);
@@ -104,11 +103,11 @@ __device__ __forceinline__ void reduce_group(const unsigned int* __restrict__ ws
     if (tid < kBinsPerReduceBlock) {            // first wavefront: one lane per bin
         unsigned long long t = 0;
 #pragma unroll
-        for (int k = 0; k < kReduceSlices; ++k) t += part[k * kBinsPerReduceBlock + tid];
+        for (int k = 0; k < SLICES; ++k) t += part[k * kBinsPerReduceBlock + tid];
         hist_out[bin] = t;
         unsigned long long before = 0;
 #pragma unroll
-        for (int w = 0; w < kReduceWaves; ++w) before += wsum[w];
+        for (int w = 0; w < THREADS / kWave; ++w) before += wsum[w];
         unsigned long long incl = t;
 #pragma unroll
         for (int o = 1; o < kWave; o <<= 1) {
