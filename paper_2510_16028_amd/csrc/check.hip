@@ -50,13 +50,13 @@ __global__ __launch_bounds__(kCheckThreads) void check_pass(
     flush_histogram(hist, ws_hist + (size_t)blockIdx.x * kBins, ws_coarse + blockIdx.x * kGroups);
 }
 
-__global__ __launch_bounds__(kReduceThreads) void profile_reduce(CheckWorkspace w, int nblocks, unsigned long long n, tao_profile* out) {
+__global__ __launch_bounds__(kReduceThreads) void profile_reduce(CheckWorkspace w, int nblocks, ProfileSize size, tao_profile* out) {
     __shared__ unsigned long long smem[profile_smem_words(kReduceThreads)];
-    profile_group<kReduceThreads, kMaxPartials>(w, nblocks, blockIdx.x, n, out, smem);
+    ProfileGroup<kReduceThreads, kMaxPartials>(w, nblocks, blockIdx.x).finish(size, out, smem);
 }
 
 void launch_profile_reduce(const CheckWorkspace& w, int nblocks, unsigned long long n, tao_profile* out, hipStream_t st) {
-    hipLaunchKernelGGL(profile_reduce, dim3(kReduceBlocks), dim3(kReduceThreads), 0, st, w, nblocks, n, out);
+    hipLaunchKernelGGL(profile_reduce, dim3(kReduceBlocks), dim3(kReduceThreads), 0, st, w, nblocks, profile_size(n), out);
 }
 
 // ---- the entry point that allocates nothing -------------------------------------------------

@@ -470,14 +470,8 @@ __global__ __launch_bounds__(WVM * WVN * 64, WVM * WVN * PER_CU / 4) void screen
         return;
     }
     if (dropped || void_seen) return;
-#pragma unroll
-    for (int o = kWave / 2; o > 0; o >>= 1) {
-        zeros += __shfl_xor(zeros, o, kWave);
-        vio += __shfl_xor(vio, o, kWave);
-        nans += __shfl_xor(nans, o, kWave);
-        max_bits = max(max_bits, (unsigned)__shfl_xor(max_bits, o, kWave));
-    }
-    zeros += all_zeros;
+    zeros = wave_sum(zeros) + all_zeros;
+    vio = wave_sum(vio); nans = wave_sum(nans); max_bits = wave_max(max_bits);
     const unsigned slot = blockIdx.x % (unsigned)kScreenSlots;
     if (lane == 0) {
         if (zeros) atomicAdd(&hist[0], (unsigned)zeros);
@@ -501,8 +495,7 @@ __global__ __launch_bounds__(WVM * WVN * 64, WVM * WVN * PER_CU / 4) void screen
             if (cnt) atomicAdd(&p.hist[(size_t)slot * kBins + bin], cnt);
             gsum += cnt;
         }
-#pragma unroll
-        for (int o = 4; o > 0; o >>= 1) gsum += __shfl_xor(gsum, o, kWave);
+        gsum = wave_all<0, 3>(gsum, [](unsigned a, unsigned b) { return a + b; });
         if ((b8 & 7) == 0 && gsum) atomicAdd(&p.coarse[slot * kGroups + b8 / 8], gsum);
     }
 }

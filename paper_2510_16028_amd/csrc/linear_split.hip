@@ -340,21 +340,13 @@ __device__ __forceinline__ void flush_packed(const SplitArgs& p, const unsigned 
 #pragma unroll
         for (int c = 0; c < 4; ++c) cnt += (chk_hist[(b >> 1) * 4 + c] >> (16 * (b & 1))) & 0xffffu;
         if (cnt) atomicAdd(&p.ws_hist[(size_t)slot * kBins + b], cnt);
-        unsigned int gsum = cnt;
-#pragma unroll
-        for (int o = kWave / 2; o > 0; o >>= 1) gsum += __shfl_xor(gsum, o, kWave);
+        const unsigned int gsum = wave_sum(cnt);
         if (lane == 0 && gsum) atomicAdd(&p.ws_coarse[slot * kGroups + b / kBinsPerReduceBlock], gsum);
     }
 }
 __device__ __forceinline__ void flush_counters(const SplitArgs& p, const ThreadAcc& acc) {
     const unsigned slot = blockIdx.x % p.check_slots;
-    unsigned int vio = acc.violations, nn = acc.nans, mx = acc.max_bits;
-#pragma unroll
-    for (int o = kWave / 2; o > 0; o >>= 1) {
-        vio += __shfl_xor(vio, o, kWave);
-        nn += __shfl_xor(nn, o, kWave);
-        mx = max(mx, (unsigned int)__shfl_xor(mx, o, kWave));
-    }
+    const unsigned int vio = wave_sum(acc.violations), nn = wave_sum(acc.nans), mx = wave_max(acc.max_bits);
     if ((threadIdx.x & 63) == 0) {
         BlockStats* st = p.ws_stats + slot;
         if (vio) atomicAdd(&st->violations, (unsigned long long)vio);
@@ -818,18 +810,20 @@ constexpr unsigned kSettleSlots = 64;      // partial results, which one workgro
 struct SettleArgs {
     CheckWorkspace check;              // the whole of it (linear_screen.hpp)
     unsigned tiles;
-    unsigned long long n;
+    ProfileSize size;
     tao_profile* out;
 };
 // true: settled by the screen, nothing is left to do
 __device__ __forceinline__ bool settled_by_screen(const SettleArgs& r, char* lds) {
-    if (r.check.stats[kOpenFlag].flag != 0) return false;
-    for (int grp = blockIdx.x; grp < kGroups; grp += gridDim.x)
-        profile_group<kSplitThreads, kScreenSlots>(r.check, kScreenSlots, grp, r.n, r.out, reinterpret_cast<unsigned long long*>(lds));
+    const unsigned open = r.check.stats[kOpenFlag].flag;
+    if (blockIdx.x >= (unsigned)kGroups) return open == 0;
+    ProfileGroup<kSplitThreads, kScreenSlots> group(r.check, kScreenSlots, blockIdx.x);      // (on its way before the flag is known)
+    if (open != 0) return false;
+    group.finish(r.size, r.out, reinterpret_cast<unsigned long long*>(lds));
     return true;
 }
 // The profile of all partial results by one workgroup (profile_group takes one per 64 bins): four bins a thread.
-__device__ __forceinline__ void profile_alone(const CheckWorkspace& w, int nblocks, unsigned long long n, tao_profile* out, unsigned long long* smem) {
+__device__ __forceinline__ void profile_alone(const CheckWorkspace& w, int nblocks, const ProfileSize& size, tao_profile* out, unsigned long long* smem) {
     static_assert(kSplitThreads * 4 == kBins, "four bins a thread");
     constexpr int WAVES = kSplitThreads / kWave;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -841,28 +835,19 @@ __device__ __forceinline__ void profile_alone(const CheckWorkspace& w, int nbloc
     }
     for (int k = tid; k < nblocks; k += kSplitThreads) { v += w.stats[k].violations; q += w.stats[k].nans; m = max(m, w.stats[k].max_bits); }
     const unsigned long long mine = c[0] + c[1] + c[2] + c[3];
-    unsigned long long upto = mine;                          // elements in this thread's bins and all below, within the wavefront first
-#pragma unroll
-    for (int o = 1; o < kWave; o <<= 1) {
-        const unsigned long long up = __shfl_up(upto, o, kWave);
-        if (lane >= o) upto += up;
-    }
-#pragma unroll
-    for (int o = kWave / 2; o > 0; o >>= 1) {
-        v += __shfl_xor(v, o, kWave); q += __shfl_xor(q, o, kWave);
-        m = max(m, (unsigned)__shfl_xor(m, o, kWave));
-    }
+    unsigned long long upto = wave_scan(mine);               // elements in this thread's bins and all below, within the wavefront first
+    v = wave_sum(v); q = wave_sum(q); m = wave_max(m);
     if (lane == kWave - 1) { smem[wave] = upto; smem[WAVES + wave] = v; smem[2 * WAVES + wave] = q; smem[3 * WAVES + wave] = m; }
     __syncthreads();
     for (int k = 0; k < wave; ++k) upto += smem[k];
-    const RankQuery ranks[3] = {{1, 2}, {99, 100}, {999, 1000}};
     unsigned long long below = upto - mine;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
         const unsigned bin = tid * 4 + j;
         out->hist[bin] = c[j];
-        for (int i = 0; i < 3 && n > 0; ++i) {
-            const unsigned long long r = rank_of(n, ranks[i].num, ranks[i].den);
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            const unsigned long long r = size.ranks.at[i];
             if (below < r && r <= below + c[j]) { (&out->p50_bin)[i] = bin; (&out->p50)[i] = bin_upper_edge(bin); }
         }
         below += c[j];
@@ -870,7 +855,7 @@ __device__ __forceinline__ void profile_alone(const CheckWorkspace& w, int nbloc
     if (tid == 0) {
         v = q = 0; m = 0;
         for (int k = 0; k < WAVES; ++k) { v += smem[WAVES + k]; q += smem[2 * WAVES + k]; m = max(m, (unsigned)smem[3 * WAVES + k]); }
-        out->n = n; out->violations = v; out->nan_count = q;
+        out->n = size.n; out->violations = v; out->nan_count = q;
         out->max_rel = __uint_as_float(m); out->accept = v == 0 ? 1u : 0u; out->pad_ = 0;
     }
 }
@@ -888,7 +873,7 @@ __device__ __forceinline__ unsigned publish(unsigned int* count, unsigned add, u
 __device__ __forceinline__ void tiles_done(const SplitArgs& p, const SettleArgs& r, unsigned done, char* lds, unsigned int& word) {
     if (publish(&r.check.stats[kDoneFlag].flag, done, word) != r.tiles) return;
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-    profile_alone(CheckWorkspace{p.ws_hist, p.ws_coarse, p.ws_stats}, (int)p.check_slots, r.n, r.out, reinterpret_cast<unsigned long long*>(lds));
+    profile_alone(CheckWorkspace{p.ws_hist, p.ws_coarse, p.ws_stats}, (int)p.check_slots, r.size, r.out, reinterpret_cast<unsigned long long*>(lds));
 }
 // On images a workgroup per compute unit walks the slots (where the screen has settled everything, thousands would only be given LDS
 // and leave); the in-load forms have no registers for that (39 spilled instead of 12) and take a workgroup per slot.
@@ -1454,7 +1439,7 @@ static int split_core(const unsigned short* A3, const unsigned short* W3, const 
         return tao_check_and_profile(chk->claimed, chk->ref, tau, M * N * batch, chk->alpha, chk->eps_rel, chk->out,
                                      check_ws, check_workspace_bytes(), stream);
     };
-    const SettleArgs settle = {cw, (unsigned)ntiles, (unsigned long long)((__int128)M * N * batch), chk ? chk->out : nullptr};
+    const SettleArgs settle = {cw, (unsigned)ntiles, profile_size((unsigned long long)((__int128)M * N * batch)), chk ? chk->out : nullptr};
     if (parts >= 2) {
         // the reduction in parts, then one pass that adds them and forms (and checks) the bound
         const long groups = Kp / SBK;

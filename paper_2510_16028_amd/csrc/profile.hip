@@ -24,7 +24,7 @@ struct ErrStats {            // one per pass-1 workgroup
     unsigned int max_abs_bits, max_rel_bits;   // bit patterns of the largest non-NaN errors (>= 0)
 };
 
-__device__ __forceinline__ unsigned int grid_percent(int g) {
+inline unsigned int grid_percent(int g) {
     return g == 0 ? 1u : (g <= 19 ? 5u * (unsigned)g : (g == 20 ? 99u : 100u));
 }
 
@@ -72,23 +72,16 @@ __global__ __launch_bounds__(kErrThreads) void errors_pass(
     for (long i = (nvec << 2) + (long)blockIdx.x * kErrThreads + tid; i < n; i += stride)
         error_one(claimed[i], ref[i], eps_rel, hist_a, hist_r, rep, nans, max_a, max_r);
 
-#pragma unroll
-    for (int o = kWave / 2; o > 0; o >>= 1) {
-        nans += __shfl_xor(nans, o, kWave);
-        max_a = max(max_a, (unsigned int)__shfl_xor(max_a, o, kWave));
-        max_r = max(max_r, (unsigned int)__shfl_xor(max_r, o, kWave));
-    }
+    nans = wave_sum(nans); max_a = wave_max(max_a); max_r = wave_max(max_r);
     const int wave = tid / kWave;
     if ((tid & (kWave - 1)) == 0) { red[wave * 3] = nans; red[wave * 3 + 1] = max_a; red[wave * 3 + 2] = max_r; }
     __syncthreads();
-    if (tid == 0) {
-        ErrStats s{0, 0, 0};
-        for (int w = 0; w < kErrThreads / kWave; ++w) {
-            s.nans += red[w * 3];
-            s.max_abs_bits = max(s.max_abs_bits, red[w * 3 + 1]);
-            s.max_rel_bits = max(s.max_rel_bits, red[w * 3 + 2]);
-        }
-        ws_stats[blockIdx.x] = s;
+    static_assert(kErrThreads / kWave == 16, "a row of lanes reads the wavefronts' totals");
+    if (tid < 16) {
+        const unsigned long long ns = wave_all<0, 4>((unsigned long long)red[tid * 3], [](unsigned long long a, unsigned long long b) { return a + b; });
+        const auto larger = [](unsigned int a, unsigned int b) { return max(a, b); };
+        const unsigned int as = wave_all<0, 4>(red[tid * 3 + 1], larger), rs = wave_all<0, 4>(red[tid * 3 + 2], larger);
+        if (tid == 0) ws_stats[blockIdx.x] = ErrStats{ns, as, rs};
     }
     flush_histogram<kErrReplicas>(hist_a, ws_hist_a + (size_t)blockIdx.x * kBins, ws_coarse_a + blockIdx.x * kGroups);
     flush_histogram<kErrReplicas>(hist_r, ws_hist_r + (size_t)blockIdx.x * kBins, ws_coarse_r + blockIdx.x * kGroups);
@@ -98,56 +91,44 @@ __global__ __launch_bounds__(kErrThreads) void errors_pass(
 __global__ __launch_bounds__(kReduceThreads) void errors_reduce(
     const unsigned int* __restrict__ ws_hist_a, const unsigned int* __restrict__ ws_hist_r,
     const unsigned int* __restrict__ ws_coarse_a, const unsigned int* __restrict__ ws_coarse_r,
-    int nblocks, unsigned long long n, tao_error_profile* out) {
+    int nblocks, Ranks<kGrid> ranks, tao_error_profile* out) {
     __shared__ unsigned long long smem[kReduceThreads + kReduceWaves];
-    RankQuery q[kGrid];
-#pragma unroll
-    for (int g = 0; g < kGrid; ++g) { q[g].num = grid_percent(g); q[g].den = 100u; }
     const bool rel = blockIdx.x >= (unsigned)kGroups;
     const int grp = rel ? blockIdx.x - kGroups : blockIdx.x;
-    if (!rel) reduce_group<kGrid>(ws_hist_a, ws_coarse_a, nblocks, grp, n, out->hist_abs, q, out->abs_bin, out->abs_p, smem);
-    else      reduce_group<kGrid>(ws_hist_r, ws_coarse_r, nblocks, grp, n, out->hist_rel, q, out->rel_bin, out->rel_p, smem);
+    const GroupLoads<kReduceThreads, kMaxPartials> loads(rel ? ws_hist_r : ws_hist_a, rel ? ws_coarse_r : ws_coarse_a, nblocks, grp);
+    reduce_group<kGrid>(loads, grp, rel ? out->hist_rel : out->hist_abs, ranks, rel ? out->rel_bin : out->abs_bin,
+                        rel ? out->rel_p : out->abs_p, smem);
 }
 
-__global__ __launch_bounds__(256) void errors_finalize(const ErrStats* __restrict__ ws_stats, int nblocks,
-                                                        unsigned long long n, const float* __restrict__ thr_abs,
-                                                        const float* __restrict__ thr_rel, tao_error_profile* out) {
-    __shared__ unsigned long long wq[4];
-    __shared__ unsigned int wa[4], wr[4];
-    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+// One wavefront, a lane per grid point (a thread that takes the 22 points and their divisions in turn needs 9 us, this 4).
+__global__ __launch_bounds__(kWave) void errors_finalize(const ErrStats* __restrict__ ws_stats, int nblocks,
+                                                         unsigned long long n, const float* __restrict__ thr_abs,
+                                                         const float* __restrict__ thr_rel, tao_error_profile* out) {
+    static_assert(kGrid <= kWave, "a lane per grid point");
+    const int lane = threadIdx.x, g = lane < kGrid ? lane : 0;
+    unsigned int ba = out->abs_bin[g], br = out->rel_bin[g];
+    float pa = out->abs_p[g], pr = out->rel_p[g];
+    const bool with_thr = thr_abs && thr_rel;
+    const float ta = with_thr ? thr_abs[g] : 0.f, tr = with_thr ? thr_rel[g] : 0.f;
     unsigned long long qn = 0; unsigned int ma = 0, mr = 0;
-    for (int k = tid; k < nblocks; k += 256) {
-        qn += ws_stats[k].nans; ma = max(ma, ws_stats[k].max_abs_bits); mr = max(mr, ws_stats[k].max_rel_bits);
-    }
 #pragma unroll
-    for (int o = kWave / 2; o > 0; o >>= 1) {
-        qn += __shfl_xor(qn, o, kWave);
-        ma = max(ma, (unsigned int)__shfl_xor(ma, o, kWave));
-        mr = max(mr, (unsigned int)__shfl_xor(mr, o, kWave));
+    for (int j = 0; j < kMaxPartials / kWave; ++j) {
+        const int k = lane + j * kWave;
+        if (k < nblocks) { qn += ws_stats[k].nans; ma = max(ma, ws_stats[k].max_abs_bits); mr = max(mr, ws_stats[k].max_rel_bits); }
     }
-    if (lane == 0) { wq[wave] = qn; wa[wave] = ma; wr[wave] = mr; }
-    __syncthreads();
-    if (tid != 0) return;
-    qn = 0; ma = 0; mr = 0;
-    for (int w = 0; w < 4; ++w) { qn += wq[w]; ma = max(ma, wa[w]); mr = max(mr, wr[w]); }
+    qn = wave_sum(qn); ma = wave_max(ma); mr = wave_max(mr);
     const float max_abs = __uint_as_float(ma), max_rel = __uint_as_float(mr);
+    if (n == 0) { ba = br = 0; pa = pr = bin_upper_edge(0); }
+    // a percentile cannot exceed the exact maximum (p = 100 is the maximum itself)
+    if (n > 0 && ba < (unsigned)(kBins - 1) && pa > max_abs) pa = max_abs;
+    if (n > 0 && br < (unsigned)(kBins - 1) && pr > max_rel) pr = max_rel;
+    double pmax = NAN;                                       // the largest ratio that is not NaN (0/0), NaN if there is none
+    const auto larger = [](double a, double b) { return a == a && !(b > a) ? a : b; };
+    if (with_thr && lane < kGrid) pmax = larger((double)pa / (double)ta, (double)pr / (double)tr);
+    pmax = wave_all(pmax, larger);
+    if (lane < kGrid) { out->abs_bin[g] = ba; out->rel_bin[g] = br; out->abs_p[g] = pa; out->rel_p[g] = pr; }
+    if (lane != 0) return;
     out->n = n; out->nan_count = qn; out->max_abs = max_abs; out->max_rel = max_rel; out->pad_ = 0;
-    double pmax = NAN;
-    for (int g = 0; g < kGrid; ++g) {
-        unsigned int ba = out->abs_bin[g], br = out->rel_bin[g];
-        float pa = out->abs_p[g], pr = out->rel_p[g];
-        if (n == 0) { ba = br = 0; pa = pr = bin_upper_edge(0); }
-        // a percentile cannot exceed the exact maximum (p = 100 is the maximum itself)
-        if (n > 0 && ba < (unsigned)(kBins - 1) && pa > max_abs) pa = max_abs;
-        if (n > 0 && br < (unsigned)(kBins - 1) && pr > max_rel) pr = max_rel;
-        out->abs_bin[g] = ba; out->rel_bin[g] = br; out->abs_p[g] = pa; out->rel_p[g] = pr;
-        if (thr_abs && thr_rel) {
-            const double ra = (double)pa / (double)thr_abs[g];
-            const double rr = (double)pr / (double)thr_rel[g];
-            if (ra == ra && !(pmax >= ra)) pmax = ra;       // NaN ratios (0/0) are skipped
-            if (rr == rr && !(pmax >= rr)) pmax = rr;
-        }
-    }
     out->p_max = pmax;
     out->offending = (pmax > 1.0) ? 1u : 0u;
 }
@@ -219,9 +200,11 @@ int tao_profile_errors(const float* claimed, const float* ref, long n, double ep
     ErrStats* ws_stats = (ErrStats*)(ws_coarse_r + (size_t)kMaxPartials * kGroups);
     hipLaunchKernelGGL(errors_pass, dim3(nblocks), dim3(kErrThreads), 0, st, claimed, ref, n, vec_ok, eps_rel,
                        ws_hist_a, ws_hist_r, ws_coarse_a, ws_coarse_r, ws_stats);
+    Ranks<kGrid> ranks;
+    for (int g = 0; g < kGrid; ++g) ranks.at[g] = rank_of((unsigned long long)n, grid_percent(g), 100);
     hipLaunchKernelGGL(errors_reduce, dim3(2 * kGroups), dim3(kReduceThreads), 0, st, ws_hist_a, ws_hist_r,
-                       ws_coarse_a, ws_coarse_r, nblocks, (unsigned long long)n, out);
-    hipLaunchKernelGGL(errors_finalize, dim3(1), dim3(256), 0, st, ws_stats, nblocks, (unsigned long long)n,
+                       ws_coarse_a, ws_coarse_r, nblocks, ranks, out);
+    hipLaunchKernelGGL(errors_finalize, dim3(1), dim3(kWave), 0, st, ws_stats, nblocks, (unsigned long long)n,
                        thr_abs, thr_rel, out);
     return launch_status();
 }

@@ -166,24 +166,19 @@ __device__ __forceinline__ unsigned newest(unsigned int* largest) {
 // red: 3 * (kCheckThreads / kWave) words of LDS.  Contains one barrier.
 __device__ __forceinline__ void flush_block_stats(const ThreadAcc& acc, unsigned int* red, BlockStats* __restrict__ ws_stats) {
     const int tid = threadIdx.x;
-    unsigned int v = acc.violations, q = acc.nans, m = acc.max_bits;
-#pragma unroll
-    for (int o = kWave / 2; o > 0; o >>= 1) {
-        v += __shfl_xor(v, o, kWave);
-        q += __shfl_xor(q, o, kWave);
-        m = max(m, (unsigned int)__shfl_xor(m, o, kWave));
-    }
+    const unsigned int v = wave_sum(acc.violations), q = wave_sum(acc.nans), m = wave_max(acc.max_bits);
     const int wave = tid / kWave;
     if ((tid & (kWave - 1)) == 0) { red[wave * 3] = v; red[wave * 3 + 1] = q; red[wave * 3 + 2] = m; }
     __syncthreads();
-    if (tid == 0) {
-        BlockStats s{0, 0, 0, 0};
-        for (int w = 0; w < kCheckThreads / kWave; ++w) {
-            s.violations += red[w * 3]; s.nans += red[w * 3 + 1];
-            s.max_bits = max(s.max_bits, red[w * 3 + 2]);
+    static_assert(kCheckThreads / kWave == 16, "a row of lanes reads the wavefronts' totals");
+    if (tid < 16) {
+        const unsigned long long vs = wave_all<0, 4>((unsigned long long)red[tid * 3], [](unsigned long long a, unsigned long long b) { return a + b; });
+        const unsigned long long qs = wave_all<0, 4>((unsigned long long)red[tid * 3 + 1], [](unsigned long long a, unsigned long long b) { return a + b; });
+        const unsigned int ms = wave_all<0, 4>(red[tid * 3 + 2], [](unsigned int a, unsigned int b) { return max(a, b); });
+        if (tid == 0) {
+            BlockStats& o = ws_stats[blockIdx.x];
+            o.violations = vs; o.nans = qs; o.max_bits = ms;
         }
-        BlockStats& o = ws_stats[blockIdx.x];
-        o.violations = s.violations; o.nans = s.nans; o.max_bits = s.max_bits;
     }
 }
 
@@ -201,50 +196,55 @@ inline CheckWorkspace carve_check_workspace(void* ws) {
     w.stats = (BlockStats*)(w.coarse + (size_t)kMaxCheckBlocks * kGroups);
     return w;
 }
+// What the finalising kernel needs to know of the tensor: its size and the nearest ranks of p50, p99 and p99.9.
+struct ProfileSize { unsigned long long n; Ranks<3> ranks; };
+inline ProfileSize profile_size(unsigned long long n) { return {n, {{rank_of(n, 1, 2), rank_of(n, 99, 100), rank_of(n, 999, 1000)}}}; }
 // Group `grp` of the profile of the partial results of `nblocks` (at most PARTIALS) pass-1 workgroups, by one workgroup of
-// THREADS threads; group 0 brings the scalar fields.  smem: profile_smem_words(THREADS) 64-bit words.
+// THREADS threads; group 0 brings the scalar fields.  Loads first (construct it early), then finish().
+// smem: profile_smem_words(THREADS) 64-bit words.
 constexpr int profile_smem_words(int threads) { return threads + 4 * (threads / kWave); }
 template <int THREADS, int PARTIALS>
-__device__ __forceinline__ void profile_group(const CheckWorkspace& w, int nblocks, int grp, unsigned long long n, tao_profile* out,
-                                              unsigned long long* smem) {
-    constexpr int WAVES = THREADS / kWave;
-    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
-    // nearest-rank percentiles p50, p99, p99.9; the three bin and three edge fields of tao_profile
-    // are consecutive
-    const RankQuery q[3] = {{1, 2}, {99, 100}, {999, 1000}};
-    reduce_group<3, THREADS, PARTIALS>(w.hist, w.coarse, nblocks, grp, n, out->hist, q, &out->p50_bin, &out->p50, smem);
-    if (grp != 0) return;
-    unsigned long long* wv = smem + THREADS + WAVES;
-    unsigned long long* wq = wv + WAVES;
-    unsigned int* wm = reinterpret_cast<unsigned int*>(wq + WAVES);
-    // counters of pass 1
-    unsigned long long v = 0, qn = 0; unsigned int m = 0;
-    for (int k = tid; k < nblocks; k += THREADS) {
-        v += w.stats[k].violations; qn += w.stats[k].nans; m = max(m, w.stats[k].max_bits);
-    }
+struct ProfileGroup {
+    GroupLoads<THREADS, PARTIALS> loads;
+    unsigned long long v = 0, q = 0;
+    unsigned int m = 0;
+    int grp;
+    __device__ __forceinline__ ProfileGroup(const CheckWorkspace& w, int nblocks, int g) : loads(w.hist, w.coarse, nblocks, g), grp(g) {
+        if (grp == 0) {                                      // counters of pass 1
 #pragma unroll
-    for (int o = kWave / 2; o > 0; o >>= 1) {
-        v += __shfl_xor(v, o, kWave); qn += __shfl_xor(qn, o, kWave);
-        m = max(m, (unsigned int)__shfl_xor(m, o, kWave));
-    }
-    if (lane == 0) { wv[wave] = v; wq[wave] = qn; wm[wave] = m; }
-    __syncthreads();
-    if (tid == 0) {
-        v = 0; qn = 0; m = 0;
-        for (int k = 0; k < WAVES; ++k) { v += wv[k]; qn += wq[k]; m = max(m, wm[k]); }
-        out->n = n;
-        out->violations = v;
-        out->nan_count = qn;
-        out->max_rel = __uint_as_float(m);
-        out->accept = (v == 0) ? 1u : 0u;
-        out->pad_ = 0;
-        if (n == 0) {
-            out->p50_bin = out->p99_bin = out->p999_bin = 0;
-            out->p50 = out->p99 = out->p999 = bin_upper_edge(0);
+            for (int k = threadIdx.x; k < PARTIALS; k += THREADS)
+                if (k < nblocks) { v += w.stats[k].violations; q += w.stats[k].nans; m = max(m, w.stats[k].max_bits); }
         }
     }
-    __syncthreads();
-}
+    __device__ __forceinline__ void finish(const ProfileSize& size, tao_profile* out, unsigned long long* smem) {
+        constexpr int WAVES = THREADS / kWave;
+        const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+        unsigned long long* wv = smem + THREADS + WAVES;
+        unsigned long long* wq = wv + WAVES;
+        unsigned int* wm = reinterpret_cast<unsigned int*>(wq + WAVES);
+        if (grp == 0) {
+            v = wave_sum(v); q = wave_sum(q); m = wave_max(m);
+            if (lane == 0) { wv[wave] = v; wq[wave] = q; wm[wave] = m; }
+        }
+        // the three bin and three edge fields of tao_profile are consecutive
+        reduce_group<3>(loads, grp, out->hist, size.ranks, &out->p50_bin, &out->p50, smem);
+        if (grp == 0 && tid == kWave) {                      // (reduce_group's barrier lies between; not the wavefront that takes the bins)
+            v = 0; q = 0; m = 0;
+#pragma unroll
+            for (int k = 0; k < WAVES; ++k) { v += wv[k]; q += wq[k]; m = max(m, wm[k]); }
+            out->n = size.n;
+            out->violations = v;
+            out->nan_count = q;
+            out->max_rel = __uint_as_float(m);
+            out->accept = (v == 0) ? 1u : 0u;
+            out->pad_ = 0;
+            if (size.n == 0) {
+                out->p50_bin = out->p99_bin = out->p999_bin = 0;
+                out->p50 = out->p99 = out->p999 = bin_upper_edge(0);
+            }
+        }
+    }
+};
 // Enqueue the finalising kernel over the partials of `nblocks` pass-1 workgroups (defined with the check pass).
 void launch_profile_reduce(const CheckWorkspace& w, int nblocks, unsigned long long n, tao_profile* out, hipStream_t st);
 

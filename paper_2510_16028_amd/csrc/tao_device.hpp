@@ -2,6 +2,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <type_traits>
 
 namespace tao {
 
@@ -39,19 +40,68 @@ __device__ __forceinline__ float up32g(double v, double mul = kUpMul, double sub
     return f;
 }
 
-__device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-    for (int o = kWave / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
-    return v;
+// Reductions over the 64 lanes, the result in every lane: four exchanges inside rows of 16 lanes (quads, halves, rows: data-parallel
+// moves), then rows and halves of the wavefront swapped -- register moves throughout, where a shuffle through LDS takes some hundred
+// cycles a step (LayerNorm of 512 x 768 with its check: see rowops.hip).  Each step combines what two groups of lanes hold in
+// an order that is the same for both, so all lanes get the same bits.
+template <int STEP>
+__device__ __forceinline__ void lane_pair(unsigned v, unsigned& a, unsigned& b) {
+    typedef unsigned int uintx2 __attribute__((ext_vector_type(2)));
+    a = v;
+    if constexpr (STEP == 0)      b = (unsigned)__builtin_amdgcn_mov_dpp((int)v, 0xB1, 0xf, 0xf, true);      // quad_perm 1,0,3,2
+    else if constexpr (STEP == 1) b = (unsigned)__builtin_amdgcn_mov_dpp((int)v, 0x4E, 0xf, 0xf, true);      // quad_perm 2,3,0,1
+    else if constexpr (STEP == 2) b = (unsigned)__builtin_amdgcn_mov_dpp((int)v, 0x141, 0xf, 0xf, true);     // row_half_mirror
+    else if constexpr (STEP == 3) b = (unsigned)__builtin_amdgcn_mov_dpp((int)v, 0x140, 0xf, 0xf, true);     // row_mirror
+    else {
+        const uintx2 r = STEP == 4 ? __builtin_amdgcn_permlane16_swap(v, v, false, false) : __builtin_amdgcn_permlane32_swap(v, v, false, false);
+        a = r[0]; b = r[1];
+    }
 }
-__device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-    for (int o = kWave / 2; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, kWave));
-    return v;
+template <int STEP, class T>
+__device__ __forceinline__ void lane_pair(T v, T& a, T& b) {
+    if constexpr (sizeof(T) == 4) {
+        unsigned x, y;
+        lane_pair<STEP>(__builtin_bit_cast(unsigned, v), x, y);
+        a = __builtin_bit_cast(T, x); b = __builtin_bit_cast(T, y);
+    } else {
+        const unsigned long long w = __builtin_bit_cast(unsigned long long, v);
+        unsigned xl, yl, xh, yh;
+        lane_pair<STEP>((unsigned)w, xl, yl);
+        lane_pair<STEP>((unsigned)(w >> 32), xh, yh);
+        a = __builtin_bit_cast(T, (unsigned long long)xh << 32 | xl);
+        b = __builtin_bit_cast(T, (unsigned long long)yh << 32 | yl);
+    }
 }
-__device__ __forceinline__ int wave_or(int v) {
-#pragma unroll
-    for (int o = kWave / 2; o > 0; o >>= 1) v |= __shfl_xor(v, o, kWave);
+template <int FIRST = 0, int STEPS = 6, class T, class Op>
+__device__ __forceinline__ T wave_all(T v, Op op) {
+    if constexpr (FIRST < STEPS) {
+        T a, b;
+        lane_pair<FIRST>(v, a, b);
+        return wave_all<FIRST + 1, STEPS>(op(a, b), op);
+    } else {
+        return v;
+    }
+}
+template <class T>
+__device__ __forceinline__ T wave_sum(T v) { return wave_all(v, [](T a, T b) { return a + b; }); }
+template <class T>
+__device__ __forceinline__ T wave_max(T v) { return wave_all(v, [](T a, T b) { return a > b ? a : b; }); }
+__device__ __forceinline__ float wave_max(float v) { return wave_all(v, [](float a, float b) { return fmaxf(a, b); }); }
+__device__ __forceinline__ int wave_or(int v) { return wave_all(v, [](int a, int b) { return a | b; }); }
+// Sum over the lanes up to this one.
+__device__ __forceinline__ unsigned long long wave_scan(unsigned long long v) {
+    auto step = [&](auto ctrl, auto rows) __attribute__((always_inline)) {
+        const unsigned lo = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)v, ctrl.value, rows.value, 0xf, false);
+        const unsigned hi = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)(v >> 32), ctrl.value, rows.value, 0xf, false);
+        v += (unsigned long long)hi << 32 | lo;
+    };
+    using std::integral_constant;
+    step(integral_constant<int, 0x111>{}, integral_constant<int, 0xf>{});       // row_shr 1, 2, 4, 8
+    step(integral_constant<int, 0x112>{}, integral_constant<int, 0xf>{});
+    step(integral_constant<int, 0x114>{}, integral_constant<int, 0xf>{});
+    step(integral_constant<int, 0x118>{}, integral_constant<int, 0xf>{});
+    step(integral_constant<int, 0x142>{}, integral_constant<int, 0xa>{});       // last lane of a row to the next, rows 1 and 3
+    step(integral_constant<int, 0x143>{}, integral_constant<int, 0xc>{});       // last lane of the lower half to the upper
     return v;
 }
 

@@ -30,11 +30,10 @@ __device__ __forceinline__ float bin_upper_edge(unsigned int b) {
     return __uint_as_float((b + 1u) << 20);
 }
 
-// rank = max(1, ceil(n * num / den)); n < 2^36 and num <= 999 keep the product in 64 bits.
-__device__ __forceinline__ unsigned long long rank_of(unsigned long long n, unsigned long long num,
-                                                       unsigned long long den) {
-    unsigned long long r = (n * num + den - 1) / den;
-    return r < 1 ? 1 : r;
+// rank = max(1, ceil(n * num / den)); n < 2^36 and num <= 999 keep the product in 64 bits.  0 for n == 0: no rank.
+inline unsigned long long rank_of(unsigned long long n, unsigned long long num, unsigned long long den) {
+    const unsigned long long r = (n * num + den - 1) / den;
+    return n == 0 ? 0 : r < 1 ? 1 : r;
 }
 
 // Flush a lane-replicated LDS histogram (kBins * R counters) of a 1024-thread workgroup to its
@@ -49,79 +48,72 @@ __device__ __forceinline__ void flush_histogram(const unsigned int* hist, unsign
         for (int r = 0; r < R; ++r) s += hist[b * R + r];
         dst[b] = s;
         // a wavefront covers exactly one group of 64 consecutive bins
-        unsigned int g = s;
-#pragma unroll
-        for (int o = kWave / 2; o > 0; o >>= 1) g += __shfl_xor(g, o, kWave);
+        const unsigned int g = wave_sum(s);
         if ((tid & (kWave - 1)) == 0) coarse[b / kBinsPerReduceBlock] = g;
     }
 }
 
 struct RankQuery { unsigned int num, den; };
+template <int NQ> struct Ranks { unsigned long long at[NQ]; };        // ranks max(1, ceil(n num / den)), formed on the host; 0: no elements
 
 // Second level, one workgroup (THREADS threads) per group `grp` of 64 bins: sums the partial histograms
 // of `nblocks` (at most PARTIALS) pass-1 workgroups (ws_hist[k][kBins], 256-byte contiguous reads, all loads
 // independent), writes the 64-bit totals to hist_out, derives the number of elements below its own
-// bins from the coarse counts (ws_coarse[k][kGroups]) and, for each of the NQ rank queries, writes
-// the bin holding rank max(1, ceil(n num/den)) and its upper edge if that bin is one of its own.
-// Every query is answered by exactly one workgroup when n > 0; nothing is written for n == 0.
+// bins from the coarse counts (ws_coarse[k][kGroups]) and, for each of the NQ ranks, writes
+// the bin holding it and its upper edge if that bin is one of its own.
+// Every rank is answered by exactly one workgroup when n > 0; nothing is written for n == 0.
+// What bounds it is one chain of latencies: loads (the partial results come from other XCDs), one barrier, sums over lanes.
 // smem: THREADS + THREADS / kWave 64-bit words.
-template <int NQ, int THREADS = kReduceThreads, int PARTIALS = kMaxPartials>
-__device__ __forceinline__ void reduce_group(const unsigned int* __restrict__ ws_hist,
-                                             const unsigned int* __restrict__ ws_coarse, int nblocks, int grp,
-                                             unsigned long long n, uint64_t* __restrict__ hist_out,
-                                             const RankQuery* q, unsigned int* __restrict__ bin_out,
+template <int THREADS, int PARTIALS>
+struct GroupLoads {
+    static constexpr int SLICES = THREADS / kBinsPerReduceBlock, PER_THREAD = PARTIALS / SLICES;       // (16 independent loads)
+    static constexpr int COARSE = PARTIALS * kGroups / THREADS;
+    unsigned int vals[PER_THREAD], coarse[COARSE];
+    __device__ __forceinline__ GroupLoads(const unsigned int* __restrict__ ws_hist, const unsigned int* __restrict__ ws_coarse, int nblocks, int grp) {
+        const int tid = threadIdx.x, slice = tid / kBinsPerReduceBlock, bin = grp * kBinsPerReduceBlock + (tid & (kBinsPerReduceBlock - 1));
+#pragma unroll
+        for (int j = 0; j < PER_THREAD; ++j) {
+            const int k = slice + SLICES * j;
+            vals[j] = (k < nblocks) ? ws_hist[(size_t)k * kBins + bin] : 0u;
+        }
+#pragma unroll
+        for (int j = 0; j < COARSE; ++j) {
+            const int e = tid + THREADS * j;
+            coarse[j] = (e < nblocks * kGroups && (e % kGroups) < grp) ? ws_coarse[e] : 0u;
+        }
+    }
+};
+template <int NQ, int THREADS, int PARTIALS>
+__device__ __forceinline__ void reduce_group(const GroupLoads<THREADS, PARTIALS>& in, int grp, uint64_t* __restrict__ hist_out,
+                                             const Ranks<NQ>& ranks, unsigned int* __restrict__ bin_out,
                                              float* __restrict__ edge_out, unsigned long long* smem) {
-    constexpr int SLICES = THREADS / kBinsPerReduceBlock, PER_THREAD = PARTIALS / SLICES;       // (16 independent loads)
+    using In = GroupLoads<THREADS, PARTIALS>;
     unsigned long long* part = smem;
     unsigned long long* wsum = smem + THREADS;
     const int tid = threadIdx.x;
     const int lane = tid & (kWave - 1), wave = tid / kWave;
-    const int b = tid & (kBinsPerReduceBlock - 1);
-    const int slice = tid / kBinsPerReduceBlock;
-    const int bin = grp * kBinsPerReduceBlock + b;
-    unsigned int vals[PER_THREAD];
+    unsigned long long s = 0, below = 0;
 #pragma unroll
-    for (int j = 0; j < PER_THREAD; ++j) {
-        const int k = slice + SLICES * j;
-        vals[j] = (k < nblocks) ? ws_hist[(size_t)k * kBins + bin] : 0u;
-    }
-    unsigned long long below = 0;
-    const int total = nblocks * kGroups;
+    for (int j = 0; j < In::PER_THREAD; ++j) s += in.vals[j];
 #pragma unroll
-    for (int j = 0; j < (PARTIALS * kGroups) / THREADS; ++j) {
-        const int e = tid + THREADS * j;
-        if (e < total && (e % kGroups) < grp) below += ws_coarse[e];
-    }
-    unsigned long long s = 0;
-#pragma unroll
-    for (int j = 0; j < PER_THREAD; ++j) s += vals[j];
+    for (int j = 0; j < In::COARSE; ++j) below += in.coarse[j];
     part[tid] = s;
-#pragma unroll
-    for (int o = kWave / 2; o > 0; o >>= 1) below += __shfl_xor(below, o, kWave);
+    below = wave_sum(below);
     if (lane == 0) wsum[wave] = below;
     __syncthreads();
     if (tid < kBinsPerReduceBlock) {            // first wavefront: one lane per bin
+        const int bin = grp * kBinsPerReduceBlock + tid;
         unsigned long long t = 0;
 #pragma unroll
-        for (int k = 0; k < SLICES; ++k) t += part[k * kBinsPerReduceBlock + tid];
+        for (int k = 0; k < In::SLICES; ++k) t += part[k * kBinsPerReduceBlock + tid];
         hist_out[bin] = t;
         unsigned long long before = 0;
 #pragma unroll
         for (int w = 0; w < THREADS / kWave; ++w) before += wsum[w];
-        unsigned long long incl = t;
+        const unsigned long long hi = before + wave_scan(t), lo = hi - t;      // ranks (lo, hi] fall in this bin
 #pragma unroll
-        for (int o = 1; o < kWave; o <<= 1) {
-            const unsigned long long up = __shfl_up(incl, o, kWave);
-            if (lane >= o) incl += up;
-        }
-        const unsigned long long hi = before + incl, lo = hi - t;      // ranks (lo, hi] fall in this bin
-        if (n > 0) {
-#pragma unroll
-            for (int i = 0; i < NQ; ++i) {
-                const unsigned long long r = rank_of(n, q[i].num, q[i].den);
-                if (lo < r && r <= hi) { bin_out[i] = bin; edge_out[i] = bin_upper_edge(bin); }
-            }
-        }
+        for (int i = 0; i < NQ; ++i)
+            if (lo < ranks.at[i] && ranks.at[i] <= hi) { bin_out[i] = bin; edge_out[i] = bin_upper_edge(bin); }
     }
     __syncthreads();
 }
