@@ -79,19 +79,19 @@ __device__ __forceinline__ void wait_for_copies(int behind) {
     }
 }
 
-// WVM x WVN wavefronts of RM x RN accumulator tiles of 32 x 32.  A stage holds 32 k of the tile's operands as the images
+// WVM x WVN wavefronts of RM x RN accumulator tiles of 32 x 32.  A stage holds a group of 32 k of the tile's operands as the images
 // hold them (ROWS: of A the binary32 values, cut when a fragment is read; PIXELS: gathered from BF16 magnitudes of the input,
-// taps in the padding from a line of zeros); NST stages filled by 16-byte copies that go to LDS directly, requested NST - 1 groups
-// ahead, one barrier per group.  The matrix instruction takes W as its row operand, so a lane holds four consecutive columns
+// taps in the padding from a line of zeros), GPS times; NST stages filled by 16-byte copies that go to LDS directly, requested
+// NST - 1 stages ahead, one barrier per stage.  The matrix instruction takes W as its row operand, so a lane holds four consecutive columns
 // of one row; the sums pass through LDS (32 rows of a wavefront at a time) so that claims and outputs are read along their
 // rows.  Workgroups walk the tiles; each XCD (workgroups are dealt to them in turn) owns a contiguous eighth of them, eight
 // tile rows deep, for its L2.
-template <int RM, int RN, int WVM, int WVN, int NST, int PER_CU, int SRC>
+template <int RM, int RN, int WVM, int WVN, int GPS, int NST, int PER_CU, int SRC>
 __global__ __launch_bounds__(WVM * WVN * 64, WVM * WVN * PER_CU / 4) void screen_product(ScreenArgs p) {
     constexpr int WAVES = WVM * WVN, THREADS = WAVES * 64;
     constexpr int TM = WVM * RM * 32, TN = WVN * RN * 32;
     constexpr int ROWB = SRC == ROWS ? 128 : 64;                               // bytes of a row of A's slab
-    constexpr int SLAB_A = TM * ROWB, SLAB_W = TN * 64, STAGE = SLAB_A + SLAB_W;
+    constexpr int SLAB_A = TM * ROWB, SLAB_W = TN * 64, GROUP = SLAB_A + SLAB_W, STAGE = GPS * GROUP;
     constexpr int NA = SLAB_A / 1024 / WAVES, NW = SLAB_W / 1024 / WAVES;      // copies of a wavefront per group
     static_assert(RN <= 2, "a lane has a column where rows are not aligned");
     static_assert(NA * WAVES * 1024 == SLAB_A && NW * WAVES * 1024 == SLAB_W, "whole copies");
@@ -184,6 +184,7 @@ __global__ __launch_bounds__(WVM * WVN * 64, WVM * WVN * PER_CU / 4) void screen
         unsigned offA[NA];
         int pix_h[SRC == PIXELS ? NA : 1], pix_w[SRC == PIXELS ? NA : 1];     // PIXELS: input coordinates of tap (0, 0)
         int tap_c = 0, tap_s = 0, tap_r = 0;
+        int left = p.groups;                                 // groups not requested yet
         const unsigned off = lane * 16;
 #pragma unroll
         for (int i = 0; i < NA; ++i) {
@@ -213,30 +214,36 @@ __global__ __launch_bounds__(WVM * WVN * 64, WVM * WVN * PER_CU / 4) void screen
             const int row = (int)n0 + (wave + i * WAVES) * 16, blk = min(row >> 7, p.last_blkW);
             baseW[i] = p.W + z * p.batchW + (long)blk * kImageBlock + (row & 127) * 64;
         }
+        // one stage's copies (a stage's groups beyond the last repeat it: their number is then the same for all)
         auto request = [&](int stage) __attribute__((always_inline)) {
-            const unsigned dst = (unsigned)(size_t)(__attribute__((address_space(3))) char*)stages + (unsigned)(stage * STAGE) + (unsigned)wave * 1024u;
-            const int dr = tap_r * p.px.dh, ds = tap_s * p.px.dw;
-            const unsigned tap = (unsigned)((dr * p.px.W + ds) * p.px.C + tap_c * SBK) * 2u;
 #pragma unroll
-            for (int i = 0; i < NA; ++i) {
-                unsigned o = offA[i];
-                if (SRC == PIXELS) {
-                    const bool inside = (unsigned)(pix_h[i] + dr) < (unsigned)p.px.H && (unsigned)(pix_w[i] + ds) < (unsigned)p.px.W;
-                    o = inside ? o + tap : p.px.zeros;
+            for (int sub = 0; sub < GPS; ++sub) {
+                const unsigned dst = (unsigned)(size_t)(__attribute__((address_space(3))) char*)stages +
+                                     (unsigned)(stage * STAGE + sub * GROUP) + (unsigned)wave * 1024u;
+                const int dr = tap_r * p.px.dh, ds = tap_s * p.px.dw;
+                const unsigned tap = (unsigned)((dr * p.px.W + ds) * p.px.C + tap_c * SBK) * 2u;
+                const bool on = --left > 0;
+#pragma unroll
+                for (int i = 0; i < NA; ++i) {
+                    unsigned o = offA[i];
+                    if (SRC == PIXELS) {
+                        const bool inside = (unsigned)(pix_h[i] + dr) < (unsigned)p.px.H && (unsigned)(pix_w[i] + ds) < (unsigned)p.px.W;
+                        o = inside ? o + tap : p.px.zeros;
+                    }
+                    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+                                 :: "s"(dst + (unsigned)(i * WAVES * 1024)), "v"(o), "s"(baseA[i]) : "memory");
+                    if (SRC != PIXELS) baseA[i] += GPS == 1 || on ? p.stepA : 0;
                 }
-                asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
-                             :: "s"(dst + (unsigned)(i * WAVES * 1024)), "v"(o), "s"(baseA[i]) : "memory");
-                if (SRC != PIXELS) baseA[i] += p.stepA;
-            }
 #pragma unroll
-            for (int i = 0; i < NW; ++i) {
-                asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
-                             :: "s"(dst + (unsigned)(SLAB_A + i * WAVES * 1024)), "v"(off), "s"(baseW[i]) : "memory");
-                baseW[i] += p.stepW;
-            }
-            if (SRC == PIXELS && ++tap_c == p.px.slabs) {
-                tap_c = 0;
-                if (++tap_s == p.px.S) { tap_s = 0; ++tap_r; }
+                for (int i = 0; i < NW; ++i) {
+                    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+                                 :: "s"(dst + (unsigned)(SLAB_A + i * WAVES * 1024)), "v"(off), "s"(baseW[i]) : "memory");
+                    baseW[i] += GPS == 1 || on ? p.stepW : 0;
+                }
+                if (SRC == PIXELS && (GPS == 1 || on) && ++tap_c == p.px.slabs) {
+                    tap_c = 0;
+                    if (++tap_s == p.px.S) { tap_s = 0; ++tap_r; }
+                }
             }
         };
 
@@ -297,19 +304,23 @@ __global__ __launch_bounds__(WVM * WVN * 64, WVM * WVN * PER_CU / 4) void screen
 
         __syncthreads();                                     // the strips of the tile before have been read
         if (void_seen | open_seen) { dropped = true; break; }
-        constexpr int COPIES = NA + NW;
+        constexpr int COPIES = GPS * (NA + NW);
+        const int slabs = (p.groups + GPS - 1) / GPS;
 #pragma unroll
         for (int i = 0; i + 1 < NST; ++i)
-            if (i < p.groups) request(i);
+            if (i < slabs) request(i);
         int cur = 0;
 #pragma unroll 1
-        for (int g = 0; g < p.groups; ++g) {
+        for (int g = 0; g < slabs; ++g) {
             // slab g has landed when only the copies of the slabs behind it are outstanding; the barrier publishes it and
             // separates the last reads of the stage before from its next fill
-            wait_for_copies<COPIES, NST - 2>(p.groups - 1 - g);
+            wait_for_copies<COPIES, NST - 2>(slabs - 1 - g);
             __syncthreads();
-            if (g + NST - 1 < p.groups) request(cur == 0 ? NST - 1 : cur - 1);
+            if (g + NST - 1 < slabs) request(cur == 0 ? NST - 1 : cur - 1);
             compute(stages + cur * STAGE);
+#pragma unroll
+            for (int sub = 1; sub < GPS; ++sub)
+                if (g * GPS + sub < p.groups) compute(stages + cur * STAGE + sub * GROUP);
             cur = cur == NST - 1 ? 0 : cur + 1;
         }
         if (CHAINS == 2) {
@@ -508,11 +519,11 @@ int cus() {
     return n;
 }
 
-template <int RM, int RN, int WVM, int WVN, int NST, int PER_CU, int SRC>
+template <int RM, int RN, int WVM, int WVN, int GPS, int NST, int PER_CU, int SRC>
 int launch_config(ScreenArgs& p, long batch, hipStream_t st) {
     constexpr int TM = WVM * RM * 32, TN = WVN * RN * 32;
-    constexpr int lds_bytes = NST * (TM * (SRC == ROWS ? 128 : 64) + TN * 64) + kHistWords * 4;
-    auto kernel = &screen_product<RM, RN, WVM, WVN, NST, PER_CU, SRC>;
+    constexpr int lds_bytes = GPS * NST * (TM * (SRC == ROWS ? 128 : 64) + TN * 64) + kHistWords * 4;
+    auto kernel = &screen_product<RM, RN, WVM, WVN, GPS, NST, PER_CU, SRC>;
     static OncePerDevice configured;
     const hipError_t e = configured.run([&] {
         return hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
@@ -565,19 +576,22 @@ int launch_screen(const ScreenOperand& A, const ScreenOperand& W, const float* b
     const long n = cus();
     const long t128 = ((M + 127) / 128) * ((N + 127) / 128) * batch;
     // Tiles of 128 x 128, two workgroups to a compute unit, where they give every compute unit one (us of the whole call on images, with
-    // them / with 64 x 64: 2048 x 12288 over 4096 236 / 390, 2048 x 4096 over 4096 92 / 137, 1111 x 3001 over 1001, 216 tiles, 38 / 36);
-    // up to 256 k, where the check is most of the work, 64 x 128 and three (8 x 8192 x 2048 over 128 250, with 128 x 128 257 - 296).
-    // Otherwise, and where a column tile would be half empty, 64 x 64: four to a compute unit, or two with eight stages, which hide the
-    // copies' latency, where there are no more (512 x 3072 over 768 25, 128 x 128 32; 256 x 1024 over 8192 64 with eight stages, 68
-    // with four).
+    // them / with 64 x 64: 2048 x 12288 over 4096 248 / 362, 2048 x 4096 over 4096 94 / 122, 1111 x 3001 over 1001, 216 tiles, 37 / 33);
+    // up to 256 k, where the check is most of the work, 64 x 128 and three (8 x 8192 x 2048 over 128 250, with 128 x 128 280).
+    // Otherwise, and where a column tile would be half empty, 64 x 64: four to a compute unit, or two with four groups to a barrier
+    // where there are no more, as a group's copies, barrier and reads of LDS then are a chain that nothing else hides (512 x 3072 over
+    // 768 21, with a group to a barrier 24, with 128 x 128 31; 512 x 768 over 3072 29 / 37 / 57; 256 x 1024 over 8192 51 / 71 / 110).
+    // A read as rows: 64 x 128 where they fill the chip (8 x 8192 x 128 over 2048 145, with 64 x 64 183), else 64 x 64 (12 x 512 x 64 over
+    // 512 22 / 26).
     const bool wide = t128 >= n && N > 64;
-    if (rows) return launch_config<1, 2, 2, 2, 4, 2, ROWS>(p, batch, st);
-    if (pixels) return wide ? launch_config<2, 2, 2, 2, 4, 2, PIXELS>(p, batch, st) : launch_config<1, 1, 2, 2, 4, 4, PIXELS>(p, batch, st);
-    if (wide && groups <= 8) return launch_config<1, 2, 2, 2, 3, 3, IMAGE>(p, batch, st);
-    if (wide) return launch_config<2, 2, 2, 2, 4, 2, IMAGE>(p, batch, st);
+    if (rows) return ((M + 63) / 64) * ((N + 127) / 128) * batch >= n && N > 64 ? launch_config<1, 2, 2, 2, 1, 4, 2, ROWS>(p, batch, st)
+                                                                               : launch_config<1, 1, 2, 2, 2, 3, 2, ROWS>(p, batch, st);
+    if (pixels) return wide ? launch_config<2, 2, 2, 2, 2, 2, 2, PIXELS>(p, batch, st) : launch_config<1, 1, 2, 2, 2, 2, 4, PIXELS>(p, batch, st);
+    if (wide && groups <= 8) return launch_config<1, 2, 2, 2, 1, 3, 3, IMAGE>(p, batch, st);
+    if (wide) return launch_config<2, 2, 2, 2, 2, 2, 2, IMAGE>(p, batch, st);
     const long t64 = ((M + 63) / 64) * ((N + 63) / 64) * batch;
-    if (t64 <= 2 * n) return launch_config<1, 1, 2, 2, 8, 2, IMAGE>(p, batch, st);
-    return launch_config<1, 1, 2, 2, 4, 4, IMAGE>(p, batch, st);
+    if (t64 <= 2 * n) return launch_config<1, 1, 2, 2, 4, 2, 2, IMAGE>(p, batch, st);
+    return launch_config<1, 1, 2, 2, 2, 2, 4, IMAGE>(p, batch, st);
 }
 
 }  // namespace tao

@@ -112,13 +112,14 @@ __device__ __forceinline__ void split_pack8(const float (&v)[8], uintx4& H, uint
     }
 }
 
-// One thread per 8 consecutive k of one row, for one or two operands in one launch.  TRANSPOSED: the source is [K][ld] with the row
-// index running along its columns (W stored K x N); adjacent threads then take adjacent rows.  MAGNITUDES: no image but the
-// BF16 magnitudes alone, in the source's layout (K a multiple of 8, one row), and 64 bytes of zeros behind them.  Otherwise a
-// workgroup takes patches of 64 rows x 256 k: per 32-k slab its 256 threads read 128 contiguous bytes
-// of each row (1 KB per row over the patch) and write 4 KB contiguous per piece (64 rows of one
-// slab are adjacent in the block layout) -- with threads running along k instead, every 64 bytes
-// written landed in another block.
+// One thread per 8 consecutive k of one row, for one or two operands in one launch; a workgroup's unit is 64 rows of one 32-k group,
+// 4 KB contiguous per piece.  STRAIGHT: four threads to a row, 128 contiguous bytes; units run along k, so the workgroups in
+// flight read rows on.  TRANSPOSED: the source is [K][ld] with the row index running along its columns (W stored K x N); the lanes of
+// a wavefront take the unit's rows.  MAGNITUDES: no image but the BF16 magnitudes alone, in the source's layout (K a
+// multiple of 8, one row), and 64 bytes of zeros behind them.
+// What bounds it: HBM for large operands, else one unit's latency -- its position takes scalar 32-bit arithmetic only (a thread's own
+// 64-bit divisions, units of 256 k, which a short reduction leaves empty, and loads behind branches took 8 x 8192 x 128 19.2 us, now
+// 13.6, 1111 x 1001 5.2, now 4.2, 8 x 128 x 2048 transposed 10.3, now 8.1; 12288 x 4096 103, at 4.9 TB/s).
 enum { STRAIGHT, TRANSPOSED, MAGNITUDES };
 struct SplitOperand { const float* src; long rows, K, ld, batch, stride; unsigned short* dst; int form; };
 struct SplitOperands {
@@ -129,7 +130,7 @@ struct SplitOperands {
 typedef float floatx4u __attribute__((ext_vector_type(4), aligned(4)));          // (16-byte loads need no more than 4-byte alignment)
 __global__ __launch_bounds__(256) void split3_bf16(SplitOperands a) {
     // (side job for the launch that follows: clears the partial results of a check, so that no launch of its own is needed for that)
-    for (long i = (long)blockIdx.x * 256 + threadIdx.x; i < a.zero_n; i += (long)gridDim.x * 256) a.zero_ptr[i] = 0;
+    for (long i = (long)blockIdx.x * 256 + threadIdx.x; i < a.zero_n / 4; i += (long)gridDim.x * 256) reinterpret_cast<uintx4*>(a.zero_ptr)[i] = uintx4{0, 0, 0, 0};
     const int o = (long)blockIdx.x >= a.first[1] ? 1 : 0;
     const SplitOperand& p = a.op[o];
     const long nblk = a.first[o + 1] - a.first[o], blk = (long)blockIdx.x - a.first[o];
@@ -147,26 +148,16 @@ __global__ __launch_bounds__(256) void split3_bf16(SplitOperands a) {
         return;
     }
     const bool trans = p.form == TRANSPOSED;
-    const long groups = (p.K + SBK - 1) / SBK, chunks = groups * (SBK / 8);
+    const unsigned groups = (unsigned)((p.K + SBK - 1) / SBK), rgroups = (unsigned)((p.rows + 63) >> 6);
     const long rblocks = (p.rows + STILE - 1) / STILE;
-    // work items: trans (chunk, row) pairs, row fastest; else (row group, k span, slab, row, chunk of the slab).  Rows up
-    // to the next multiple of four are zeros: the product's epilogue looks at its sums by groups of four rows.
+    // rows up to the next multiple of four are zeros: the product's epilogue looks at its sums by groups of four rows
     const long rows4 = (p.rows + 3) & ~3L;
-    const long kspans = (groups + 7) >> 3, rgroups = (p.rows + 63) >> 6;
-    const long per = trans ? rows4 * chunks : rgroups * kspans * 8 * 256, total = per * p.batch;
-    for (long w0 = blk * 256 + threadIdx.x; w0 < total; w0 += nblk * 256) {
-        const long z = p.batch == 1 ? 0 : w0 / per, w = w0 - z * per;
-        long row, ch;
-        if (trans) {
-            ch = w / rows4; row = w - ch * rows4;
-        } else {
-            const long patch = w >> 11, in = w & 2047;          // 8 slabs x 64 rows x 4 chunks
-            const long rg = patch / kspans, ks = patch - rg * kspans;
-            row = (rg << 6) + ((in & 255) >> 2);
-            ch = (ks << 5) + ((in >> 8) << 2) + (in & 3);
-            if (row >= rows4 || ch >= chunks) continue;
-        }
-        const long k0 = ch << 3;
+    const unsigned units = (unsigned)(groups * (unsigned long long)rgroups * p.batch);
+    const int urow = trans ? threadIdx.x & 63 : threadIdx.x >> 2, uch = trans ? threadIdx.x >> 6 : threadIdx.x & 3;
+    for (unsigned u = (unsigned)blk; u < units; u += (unsigned)nblk) {
+        const unsigned rz = u / groups, g = u - rz * groups, z = rz / rgroups, rg = rz - z * rgroups;
+        const long row = (long)rg * 64 + urow, k0 = (long)g * SBK + uch * 8;
+        if (row >= rows4) continue;
         const float* s = p.src + z * p.stride;
         float v[8];
         if (!trans && row < p.rows && k0 + 8 <= p.K) {
@@ -175,17 +166,21 @@ __global__ __launch_bounds__(256) void split3_bf16(SplitOperands a) {
 #pragma unroll
             for (int j = 0; j < 4; ++j) { v[j] = x[j]; v[4 + j] = y[j]; }
         } else {
+            // (positions beyond the operand read its last element: loads without branches all leave at once)
+            const long rc = row < p.rows ? row : p.rows - 1;
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
-                const long k = k0 + j;
-                v[j] = (row < p.rows && k < p.K) ? (trans ? s[k * p.ld + row] : s[row * p.ld + k]) : 0.f;
+                const long kc = k0 + j < p.K ? k0 + j : p.K - 1;
+                v[j] = trans ? s[kc * p.ld + rc] : s[rc * p.ld + kc];
             }
+#pragma unroll
+            for (int j = 0; j < 8; ++j) v[j] = row < p.rows && k0 + j < p.K ? v[j] : 0.f;
         }
         uintx4 H, Mi, L;
         split_pack8(v, H, Mi, L);
         const long r = row & (STILE - 1);
-        const long unit = ((k0 & (SBK - 1)) >> 3) ^ ((r >> 2) & 3);
-        unsigned short* d = p.dst + ((z * groups + (k0 >> 5)) * rblocks + (row >> 7)) * (kBlock / 2) + r * (SROW / 2) + unit * 8;
+        const long unit = uch ^ ((r >> 2) & 3);
+        unsigned short* d = p.dst + (((long)z * groups + g) * rblocks + (row >> 7)) * (kBlock / 2) + r * (SROW / 2) + unit * 8;
         *reinterpret_cast<uintx4*>(d) = H;
         *reinterpret_cast<uintx4*>(d + (kSlab / 2)) = Mi;
         *reinterpret_cast<uintx4*>(d + 2 * (kSlab / 2)) = L;
@@ -389,7 +384,7 @@ __device__ __forceinline__ bool absgemm_split_slot(const SplitArgs& p, unsigned 
     static_assert(!CONV || AREG, "the patch matrix exists only as a gather");
     static_assert(!(CHECK && PARTIAL), "the parts are checked by split_combine");
     static_assert(!(WALK && (CHECK || PARTIAL)), "only the plain bound walks tiles");
-    static_assert(!(AREG && (WALK || PARTIAL)), "the in-load split keeps one tile per workgroup and the whole reduction");
+    static_assert(!(AREG && WALK), "the in-load split keeps one tile per workgroup");
     // CHECK: four copies of the 2048-bin histogram with 16-bit counters (a tile has 16384 elements, so
     // none overflows), two bins to a word and the four copies of a word in consecutive banks: 16 KB,
     // all the LDS the stages leave.  The copy is chosen by the lane; errors crowd into a few bins, and
@@ -900,12 +895,13 @@ __global__ __launch_bounds__(kSplitThreads) void absgemm_settle(SplitArgs p, Set
 }
 // The reduction in parts: a workgroup leaves its part's sums in the workspace, and the one that brings a tile's last part adds
 // them in split_combine's order, forms the bound and checks it.
+template <bool AREG>
 __global__ __launch_bounds__(kSplitThreads) void absgemm_settle_parts(SplitArgs p, SettleArgs r) {
     extern __shared__ __attribute__((aligned(16))) char lds[];
     __shared__ unsigned int chk_hist[kBins * 2];
     if (settled_by_screen(r, lds)) return;
     if (blockIdx.x >= p.ntiles * (unsigned)p.ksplit) return;
-    if (!absgemm_split_slot<false, true, false, false, false, true>(p, blockIdx.x, gridDim.x, lds, chk_hist)) return;
+    if (!absgemm_split_slot<false, true, false, AREG, false, true>(p, blockIdx.x, gridDim.x, lds, chk_hist)) return;
     const unsigned tile = blockIdx.x % p.ntiles;
     const bool last = publish(&r.check.stats[tile].flag, 1u, chk_hist[0]) == (unsigned)p.ksplit;
     if (!last) return;
@@ -994,9 +990,11 @@ __global__ __launch_bounds__(kCheckThreads) void split_combine(SplitArgs p, long
     }
 }
 
+// (n a multiple of four, p 16-byte aligned: a check's workspace)
 __global__ __launch_bounds__(256) void zero_words(unsigned int* __restrict__ p, long n) {
-    for (long i = (long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (long)gridDim.x * blockDim.x) p[i] = 0;
+    for (long i = (long)blockIdx.x * blockDim.x + threadIdx.x; i < n / 4; i += (long)gridDim.x * blockDim.x) reinterpret_cast<uintx4*>(p)[i] = uintx4{0, 0, 0, 0};
 }
+static_assert(check_workspace_bytes() % 16 == 0, "cleared in 16-byte words");
 
 // ---- instruction self test ------------------------------------------------------------------
 // One wavefront per case: every row of A holds a[0..15], every column of B holds b[0..15], every
@@ -1277,9 +1275,7 @@ static void launch_split3(const SplitOperand* ops, int n, unsigned int* zero_ptr
         const SplitOperand& p = ops[o];
         a.op[o] = p;
         const long groups = (p.K + SBK - 1) / SBK;
-        // work items of split3_bf16: (row, chunk) pairs, or whole 64-row x 256-k patches of 2048
-        const long b = ((p.form == MAGNITUDES ? p.K / 8 + 4 : p.form == TRANSPOSED ? ((p.rows + 3) & ~3L) * groups * 4
-                         : (p.rows + 63) / 64 * ((groups + 7) / 8) * 2048) * p.batch + 255) / 256;
+        const long b = p.form == MAGNITUDES ? (p.K / 8 + 4 + 255) / 256 : groups * ((p.rows + 63) / 64) * p.batch;      // units of split3_bf16
         a.first[o] = first;
         first += b < 1 ? 1 : (b > 256L * 64 ? 256L * 64 : b);
     }
@@ -1394,7 +1390,7 @@ static int split_core(const unsigned short* A3, const unsigned short* W3, const 
                 r = hipFuncSetAttribute(reinterpret_cast<const void*>(&absgemm_split<true, false, false, true, true>),
                                         hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
             for (const void* settling : {reinterpret_cast<const void*>(&absgemm_settle<false, false>), reinterpret_cast<const void*>(&absgemm_settle<true, false>),
-                                         reinterpret_cast<const void*>(&absgemm_settle<true, true>), reinterpret_cast<const void*>(&absgemm_settle_parts)})
+                                         reinterpret_cast<const void*>(&absgemm_settle<true, true>), reinterpret_cast<const void*>(&absgemm_settle_parts<false>), reinterpret_cast<const void*>(&absgemm_settle_parts<true>)})
                 if (r == hipSuccess) r = hipFuncSetAttribute(settling, hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
             return r;
         });
@@ -1449,7 +1445,9 @@ static int split_core(const unsigned short* A3, const unsigned short* W3, const 
         p.partial = reinterpret_cast<double*>(wsb);
         if (screened) {
             const long wgs = (long)p.ntiles * p.ksplit;              // (the profile's 32 groups have a workgroup each)
-            hipLaunchKernelGGL(absgemm_settle_parts, dim3((unsigned)(wgs < kGroups ? kGroups : wgs)), dim3(kSplitThreads), lds_bytes, st, p, settle);
+            const dim3 grid((unsigned)(wgs < kGroups ? kGroups : wgs));
+            if (Af) hipLaunchKernelGGL(absgemm_settle_parts<true>, grid, dim3(kSplitThreads), lds_bytes, st, p, settle);
+            else    hipLaunchKernelGGL(absgemm_settle_parts<false>, grid, dim3(kSplitThreads), lds_bytes, st, p, settle);
             return launch_status();
         }
         hipLaunchKernelGGL((absgemm_split<false, true>), dim3(p.ntiles * (unsigned)p.ksplit), dim3(kSplitThreads), lds_bytes, st, p);
@@ -1590,12 +1588,12 @@ static int split_run(const float* A, const float* W, const float* bias, float* t
     void* rest = wsb + bytesA + bytesW;
     hipStream_t st = (hipStream_t)stream;
     // An A operand that only one or two column tiles use is split while the product loads it (no
-    // pre-pass over it, no image): whole groups, 16-byte aligned rows, the reduction in one part, and
+    // pre-pass over it, no image): whole groups, 16-byte aligned rows, and, without a screen, the reduction in one part and
     // not a launch whose short reduction is better served by the tile walk.
-    const bool in_load = K > 0 && K % SBK == 0 && N <= 2 * STILE && aligned(A, 16) && lda % 4 == 0 && strideA % 4 == 0 &&
-                         split_k_parts(M, N, K, batch) < 2 && K / SBK > kWalkMaxGroups &&
+    const bool rows_ok = K > 0 && K % SBK == 0 && N <= 2 * STILE && aligned(A, 16) && lda % 4 == 0 && strideA % 4 == 0 &&
                          (__int128)M * lda < ((__int128)1 << 40);
-    const bool scr = screened(M, N, K, batch, bias, tau, md, chk) && !(in_load && lda >= kScreenMaxLd);
+    const bool scr = screened(M, N, K, batch, bias, tau, md, chk) && !(rows_ok && lda >= kScreenMaxLd);
+    const bool in_load = rows_ok && (scr || (split_k_parts(M, N, K, batch) < 2 && K / SBK > kWalkMaxGroups));
     const CheckWorkspace cw = core_check_workspace(rest, M, N, K, batch);
     bool cleared = false;
     if (K > 0) {

@@ -53,7 +53,8 @@ KINDS = ["honest", "equal", "far", "near", "one at its bound", "one beyond", "va
 # remainders in every direction, groups of 32 k fewer than the stages and more, reductions in parts and not
 SHAPES = [(1, 1, 1, 1), (1, 64, 64, 32), (1, 65, 63, 31), (3, 127, 129, 33), (1, 129, 130, 224), (1, 130, 131, 288), (1, 700, 66, 1100),
           (1, 2048, 2052, 64), (1, 2047, 2049, 264), (1, 2050, 2052, 300), (1, 1111, 3001, 1001), (2, 1500, 1500, 96), (5, 1000, 64, 160),
-          (1, 33000, 128, 1056), (1, 33001, 100, 1088), (1, 16500, 250, 1056), (1, 300, 200, 4096), (1, 1024, 1024, 2080), (12, 512, 512, 64)]
+          (1, 33000, 128, 1056), (1, 33001, 100, 1088), (1, 16500, 250, 1056), (1, 300, 200, 4096), (1, 1024, 1024, 2080), (12, 512, 512, 64),
+          (3, 200, 70, 96), (12, 512, 64, 512), (4, 300, 250, 4128), (17, 1000, 128, 64)]
 
 
 @pytest.mark.parametrize("batch,M,N,K", SHAPES)
