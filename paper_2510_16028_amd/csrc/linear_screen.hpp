@@ -23,14 +23,22 @@ constexpr long kScreenMaxLd = 1L << 22;      // rows of claims and outputs, and 
 
 struct ScreenCheck { const float* claimed; const float* ref; long ldy, strideY; double alpha, eps_rel; };
 
-// A screened check divides the partial results among the screen (the first half) and the exact route behind it (the second);
-// all of the check's workspace is zero before the screen.  The words of the counters that no check writes hold the flag that the
-// screen could not settle every element and the exact route's counts of finished tiles and parts.
-constexpr int kScreenSlots = kMaxCheckBlocks / 2;
+// A screened check keeps few partial results (they are cleared before and added up after each call): the screen adds to the
+// first kScreenSlots, the exact route behind it to the next kSettleSlots; these and all counters are zero before the screen.  The
+// words of the counters that no check writes hold the flag that the screen could not settle every element and the exact
+// route's counts of finished tiles and parts.
+constexpr int kScreenSlots = 64, kSettleSlots = 32;     // (the screen's: 32 cost perturbed claims of 1111 x 3001 2 us, 128 honest ones 0.4)
 constexpr int kOpenFlag = kMaxCheckBlocks - 1, kDoneFlag = kMaxCheckBlocks - 2, kMaxTileFlags = kMaxCheckBlocks - 2;
-inline CheckWorkspace screened_second_half(const CheckWorkspace& w) {
+inline CheckWorkspace settle_partials(const CheckWorkspace& w) {
     return {w.hist + (size_t)kScreenSlots * kBins, w.coarse + (size_t)kScreenSlots * kGroups, w.stats + kScreenSlots};
 }
+// What a launch before a check clears, in 16-byte words: of `slots` partial results the histograms and coarse counts, and all counters.
+struct ClearJob { void* at[3]; long words[3]; };
+inline ClearJob clear_job(const CheckWorkspace& w, int slots) {
+    return {{w.hist, w.coarse, w.stats},
+            {(long)slots * kBins / 4, (long)slots * kGroups / 4, (long)(kMaxCheckBlocks * sizeof(BlockStats) / 16)}};
+}
+static_assert(kMaxCheckBlocks * sizeof(BlockStats) % 16 == 0, "cleared in 16-byte words");
 
 // Whether the screen can decide for these constants (u: the model's, cg: Gamma with its guard factor; see linear_screen.hip).
 bool screen_usable(long K, double u, double cg, double alpha, double uflow);

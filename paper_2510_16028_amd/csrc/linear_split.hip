@@ -37,6 +37,7 @@
 // (see split_pack8), so the bound stays an upper bound but can exceed 1e-6 there.  Sums that reach
 // down into the binary32 subnormal range carry an absolute error instead of a relative one; the
 // epilogue adds a bound on it (see split_run), which is far below 1e-6 of any bound above 2^-120.
+#include <algorithm>
 #include <cstring>
 #include <type_traits>
 #include <vector>
@@ -125,12 +126,17 @@ struct SplitOperand { const float* src; long rows, K, ld, batch, stride; unsigne
 struct SplitOperands {
     SplitOperand op[2];
     long first[3];                     // workgroups [first[o], first[o + 1]) serve operand o
-    unsigned int* zero_ptr; long zero_n;
+    ClearJob clear;                    // (words 0: nothing)
 };
+__device__ __forceinline__ void clear_words(const ClearJob& c, long i0, long step) {
+#pragma unroll
+    for (int j = 0; j < 3; ++j)
+        for (long i = i0; i < c.words[j]; i += step) static_cast<uintx4*>(c.at[j])[i] = uintx4{0, 0, 0, 0};
+}
 typedef float floatx4u __attribute__((ext_vector_type(4), aligned(4)));          // (16-byte loads need no more than 4-byte alignment)
 __global__ __launch_bounds__(256) void split3_bf16(SplitOperands a) {
     // (side job for the launch that follows: clears the partial results of a check, so that no launch of its own is needed for that)
-    for (long i = (long)blockIdx.x * 256 + threadIdx.x; i < a.zero_n / 4; i += (long)gridDim.x * 256) reinterpret_cast<uintx4*>(a.zero_ptr)[i] = uintx4{0, 0, 0, 0};
+    clear_words(a.clear, (long)blockIdx.x * 256 + threadIdx.x, (long)gridDim.x * 256);
     const int o = (long)blockIdx.x >= a.first[1] ? 1 : 0;
     const SplitOperand& p = a.op[o];
     const long nblk = a.first[o + 1] - a.first[o], blk = (long)blockIdx.x - a.first[o];
@@ -801,7 +807,6 @@ __global__ __launch_bounds__(kSplitThreads) void absgemm_split(SplitArgs p) {
 // One launch that settles the check: where the screen has settled every element, the first workgroups form the profile of its
 // partial results and nothing else happens; otherwise the bound is formed and checked by the code above, and the
 // workgroup that finishes the last tile (counted in the workspace; nobody waits) forms the profile.
-constexpr unsigned kSettleSlots = 64;      // partial results, which one workgroup adds
 struct SettleArgs {
     CheckWorkspace check;              // the whole of it (linear_screen.hpp)
     unsigned tiles;
@@ -990,11 +995,10 @@ __global__ __launch_bounds__(kCheckThreads) void split_combine(SplitArgs p, long
     }
 }
 
-// (n a multiple of four, p 16-byte aligned: a check's workspace)
-__global__ __launch_bounds__(256) void zero_words(unsigned int* __restrict__ p, long n) {
-    for (long i = (long)blockIdx.x * blockDim.x + threadIdx.x; i < n / 4; i += (long)gridDim.x * blockDim.x) reinterpret_cast<uintx4*>(p)[i] = uintx4{0, 0, 0, 0};
+__global__ __launch_bounds__(256) void clear_check(ClearJob c) { clear_words(c, (long)blockIdx.x * 256 + threadIdx.x, (long)gridDim.x * 256); }
+static void launch_clear(const ClearJob& c, hipStream_t st) {
+    hipLaunchKernelGGL(clear_check, dim3((unsigned)std::max(1L, (c.words[0] + 511) / 512)), dim3(256), 0, st, c);
 }
-static_assert(check_workspace_bytes() % 16 == 0, "cleared in 16-byte words");
 
 // ---- instruction self test ------------------------------------------------------------------
 // One wavefront per case: every row of A holds a[0..15], every column of B holds b[0..15], every
@@ -1266,10 +1270,10 @@ struct SplitCheckHost {
 };
 
 // Launches split3_bf16 for one or two operands: src [batch][rows][K] with row stride ld (STRAIGHT) or
-// [batch][K][rows] (TRANSPOSED) -> image.  zero_ptr / zero_n: the side job described at the kernel.
-static void launch_split3(const SplitOperand* ops, int n, unsigned int* zero_ptr, long zero_n, hipStream_t st) {
+// [batch][K][rows] (TRANSPOSED) -> image.  clear: the side job described at the kernel.
+static void launch_split3(const SplitOperand* ops, int n, const ClearJob& clear, hipStream_t st) {
     SplitOperands a = {};
-    a.zero_ptr = zero_ptr; a.zero_n = zero_ptr ? zero_n : 0;
+    a.clear = clear;
     long first = 0;
     for (int o = 0; o < n; ++o) {
         const SplitOperand& p = ops[o];
@@ -1423,7 +1427,7 @@ static int split_core(const unsigned short* A3, const unsigned short* W3, const 
         p.alpha = chk->alpha; p.eps_rel = chk->eps_rel;
         p.ws_hist = cw.hist; p.ws_coarse = cw.coarse; p.ws_stats = cw.stats;
         if (screened) {
-            const CheckWorkspace half = screened_second_half(cw);
+            const CheckWorkspace half = settle_partials(cw);
             p.ws_hist = half.hist; p.ws_coarse = half.coarse; p.ws_stats = half.stats;
             p.check_slots = kSettleSlots;
         }
@@ -1487,7 +1491,7 @@ static int split_core(const unsigned short* A3, const unsigned short* W3, const 
         return launch_status();
     }
     const int slots = kMaxCheckBlocks;                       // workgroup b adds to partial result b % 256
-    if (!cleared) hipLaunchKernelGGL(zero_words, dim3(64), dim3(256), 0, st, cw.hist, (long)(check_workspace_bytes() / 4));
+    if (!cleared) launch_clear(clear_job(cw, kMaxCheckBlocks), st);
     if (Af && cv) hipLaunchKernelGGL((absgemm_split<true, false, false, true, true>), dim3(p.ntiles), dim3(kSplitThreads), lds_bytes, st, p);
     else if (Af)  hipLaunchKernelGGL((absgemm_split<true, false, false, true>), dim3(p.ntiles), dim3(kSplitThreads), lds_bytes, st, p);
     else          hipLaunchKernelGGL((absgemm_split<true>), dim3(p.ntiles), dim3(kSplitThreads), lds_bytes, st, p);
@@ -1552,7 +1556,7 @@ static int split_empty(const SplitCheckHost* chk, void* check_ws, void* stream) 
     if (!chk) return TAO_OK;
     hipStream_t st = (hipStream_t)stream;
     const CheckWorkspace cw = carve_check_workspace(check_ws);
-    hipLaunchKernelGGL(zero_words, dim3(8), dim3(256), 0, st, cw.hist, (long)(check_workspace_bytes() / 4));
+    launch_clear(clear_job(cw, 1), st);
     launch_profile_reduce(cw, 1, 0ull, chk->out, st);
     return launch_status();
 }
@@ -1601,7 +1605,7 @@ static int split_run(const float* A, const float* W, const float* bias, float* t
         // are checked by the combining pass, which needs none)
         cleared = scr || epilogue_check_without_parts(M, N, K, batch, md, chk);
         const SplitOperand ops[2] = {{W, N, K, ldw, shared_w ? 1 : batch, strideW, W3, trans_w ? TRANSPOSED : STRAIGHT}, {A, M, K, lda, batch, strideA, A3, STRAIGHT}};
-        launch_split3(ops, in_load ? 1 : 2, cleared ? cw.hist : nullptr, (long)(check_workspace_bytes() / 4), st);
+        launch_split3(ops, in_load ? 1 : 2, cleared ? clear_job(cw, scr ? kScreenSlots + kSettleSlots : kMaxCheckBlocks) : ClearJob{}, st);
     }
     if (scr) {
         const long groups = (K + SBK - 1) / SBK;
@@ -1640,7 +1644,7 @@ static int images_run(const void* A_image, const void* W_image, const float* bia
         hipStream_t st = (hipStream_t)stream;
         const CheckWorkspace cw = core_check_workspace(ws, M, N, K, batch);
         cleared = true;
-        hipLaunchKernelGGL(zero_words, dim3(256), dim3(256), 0, st, cw.hist, (long)(check_workspace_bytes() / 4));
+        launch_clear(clear_job(cw, kScreenSlots + kSettleSlots), st);
         const long groups = (K + SBK - 1) / SBK;
         const ScreenOperand oa = {A3, groups * ((M + STILE - 1) / STILE) * kBlock, 0, nullptr};
         const ScreenOperand ow = {W3, sw ? 0 : groups * ((N + STILE - 1) / STILE) * kBlock, 0, nullptr};
@@ -1668,7 +1672,7 @@ int tao_split_operand(const float* src, long rows, long K, long ld, int trans, l
     if (need == 0 || !image || !aligned(image, 256) || image_bytes < need) return TAO_ERR_WORKSPACE;
     if (batch >= 65536) return TAO_ERR_SHAPE;                      // (second grid dimension)
     const SplitOperand op = {src, rows, K, ld, batch, stride, static_cast<unsigned short*>(image), trans ? TRANSPOSED : STRAIGHT};
-    launch_split3(&op, 1, nullptr, 0L, (hipStream_t)stream);
+    launch_split3(&op, 1, ClearJob{}, (hipStream_t)stream);
     return launch_status();
 }
 
@@ -1739,7 +1743,7 @@ static int conv_split_run(const float* x, const float* w, const float* bias, flo
     const CheckWorkspace cw = carve_check_workspace(rest);
     unsigned short* px = reinterpret_cast<unsigned short*>(wsb + pixels_at);
     const SplitOperand ops[2] = {{w, N, K, K, 1, 0, W3, STRAIGHT}, {x, 1, batch * H * W * C, 0, 1, 0, px, MAGNITUDES}};
-    launch_split3(ops, scr ? 2 : 1, cleared ? cw.hist : nullptr, (long)(check_workspace_bytes() / 4), (hipStream_t)stream);
+    launch_split3(ops, scr ? 2 : 1, cleared ? clear_job(cw, scr ? kScreenSlots + kSettleSlots : kMaxCheckBlocks) : ClearJob{}, (hipStream_t)stream);
     if (scr) {
         const ScreenPixels pixels = {cv.H, cv.W, cv.C, cv.OW, cv.S, cv.sh, cv.sw, cv.ph, cv.pw, cv.dh, cv.dw, cv.ohow, cv.C / SBK,
                                      (unsigned)(batch * H * W * C * 2)};
