@@ -140,10 +140,10 @@ template <int KIND, bool QUICK>
 __global__ __launch_bounds__(kCheckThreads) void act_check(
     const float* __restrict__ x, const float* __restrict__ y, const float* __restrict__ claimed, long n, int vec_ok,
     ActConsts k, double alpha, double eps_rel,
-    unsigned int* __restrict__ ws_hist, unsigned int* __restrict__ ws_coarse, BlockStats* __restrict__ ws_stats) {
+    PassOut pass) {
     constexpr bool NEEDS_X = (KIND == TAO_ACT_GELU_ERF || KIND == TAO_ACT_GELU_TANH);
     __shared__ unsigned int hist[kBins * kReplicas];
-    __shared__ unsigned int red[3 * (kCheckThreads / kWave)];
+    __shared__ unsigned int red[kRedWords];
     __shared__ unsigned int largest;
     const int tid = threadIdx.x;
     for (int i = tid; i < kBins * kReplicas; i += kCheckThreads) hist[i] = 0;
@@ -194,8 +194,7 @@ __global__ __launch_bounds__(kCheckThreads) void act_check(
     }
     for (long i = (nvec << 2) + (long)blockIdx.x * kCheckThreads + tid; i < n; i += stride)
         check_one(claimed[i], y[i], act_one<KIND>(NEEDS_X ? x[i] : 0.f, y[i], k), alpha, eps_rel, hist, rep, acc);
-    flush_block_stats(acc, red, ws_stats);
-    flush_histogram(hist, ws_hist + (size_t)blockIdx.x * kBins, ws_coarse + blockIdx.x * kGroups);
+    finish_pass(hist, acc, red, pass);
 }
 
 // Rotary embedding: one thread per output pair and float4 of a half (pairs (j, j + d/2)) or per
@@ -279,15 +278,14 @@ __global__ __launch_bounds__(kCheckThreads) void rope_check(
     const float* __restrict__ x, const float* __restrict__ cs, const float* __restrict__ sn,
     const float* __restrict__ y, const float* __restrict__ claimed,
     long rows, int d, long inner, long npos, double g2, double uflow, double alpha, double eps_rel,
-    unsigned int* __restrict__ ws_hist, unsigned int* __restrict__ ws_coarse, BlockStats* __restrict__ ws_stats) {
+    PassOut pass) {
     __shared__ unsigned int hist[kBins * kReplicas];
-    __shared__ unsigned int red[3 * (kCheckThreads / kWave)];
+    __shared__ unsigned int red[kRedWords];
     for (int i = threadIdx.x; i < kBins * kReplicas; i += kCheckThreads) hist[i] = 0;
     __syncthreads();
     CheckSink sink{y, claimed, alpha, eps_rel, hist, (int)(threadIdx.x & (kReplicas - 1)), ThreadAcc()};
     rope_body<INTERLEAVED, VEC>(x, cs, sn, rows, d, inner, npos, g2, uflow, sink);
-    flush_block_stats(sink.acc, red, ws_stats);
-    flush_histogram(hist, ws_hist + (size_t)blockIdx.x * kBins, ws_coarse + blockIdx.x * kGroups);
+    finish_pass(hist, sink.acc, red, pass);
 }
 
 }  // namespace tao
@@ -382,7 +380,7 @@ int tao_bound_check_act(int kind, const float* x, const float* x2, const float* 
     const int vec_ok = aligned(y_ref, 16) && aligned(claimed, 16) && (!needs_x || aligned(x, 16));
     // (one vector per thread before another workgroup, as in the check pass: GELU of 65536 elements 11.3 against 19.9 us with four)
     long want = (n + (long)kCheckThreads * 4 - 1) / ((long)kCheckThreads * 4);
-    const int nblocks = (int)(want < 1 ? 1 : (want > kMaxCheckBlocks ? kMaxCheckBlocks : want));
+    const int nblocks = (int)(want < 1 || n <= (needs_x ? kAloneElements / 2 : kAloneElements) ? 1 : (want > kMaxCheckBlocks ? kMaxCheckBlocks : want));
     const CheckWorkspace w = carve_check_workspace(ws);
     hipStream_t st = (hipStream_t)stream;
     dim3 grid((unsigned)nblocks), blk(kCheckThreads);
@@ -390,7 +388,7 @@ int tao_bound_check_act(int kind, const float* x, const float* x2, const float* 
     // 25 M products 39.0 against 41.4 us)
     const bool rounded = kind == TAO_ACT_MUL || kind == TAO_ACT_ADD || kind == TAO_ACT_SUB || kind == TAO_ACT_SQRT;
     const bool quick = !rounded && n >= (needs_x ? 16L : 32L) * kMaxCheckBlocks * kCheckThreads;
-#define TAO_ACT_CHECK_Q(K, Q) hipLaunchKernelGGL((act_check<K, Q>), grid, blk, 0, st, x, y_ref, claimed, n, vec_ok, k, alpha, eps_rel, w.hist, w.coarse, w.stats)
+#define TAO_ACT_CHECK_Q(K, Q) hipLaunchKernelGGL((act_check<K, Q>), grid, blk, 0, st, x, y_ref, claimed, n, vec_ok, k, alpha, eps_rel, pass_out(w, nblocks, n, out))
 #define TAO_ACT_CHECK(K) do { if (quick) TAO_ACT_CHECK_Q(K, true); else TAO_ACT_CHECK_Q(K, false); } while (0)
     switch (kind) {
         case TAO_ACT_GELU_ERF: TAO_ACT_CHECK(TAO_ACT_GELU_ERF); break;
@@ -401,7 +399,7 @@ int tao_bound_check_act(int kind, const float* x, const float* x2, const float* 
     }
 #undef TAO_ACT_CHECK_Q
 #undef TAO_ACT_CHECK
-    launch_profile_reduce(w, nblocks, (unsigned long long)n, out, st);
+    launch_finish(w, nblocks, n, out, st);
     return launch_status();
 }
 
@@ -462,16 +460,16 @@ int tao_bound_check_rope(const float* x, const float* cos_table, const float* si
                      aligned(sin_table, 16) && (interleaved ? d % 4 == 0 : d % 8 == 0);
     const long per_row = vec ? (interleaved ? d / 4 : d / 8) : d / 2;
     long want = (rows * per_row + (long)kCheckThreads * 4 - 1) / ((long)kCheckThreads * 4);
-    const int nblocks = (int)(want < 1 ? 1 : (want > kMaxCheckBlocks ? kMaxCheckBlocks : want));
+    const int nblocks = (int)(want < 1 || n <= kAloneElements ? 1 : (want > kMaxCheckBlocks ? kMaxCheckBlocks : want));
     const CheckWorkspace w = carve_check_workspace(ws);
     hipStream_t st = (hipStream_t)stream;
     dim3 grid((unsigned)nblocks), blk(kCheckThreads);
 #define TAO_ROPE_CHECK(I, V) hipLaunchKernelGGL((rope_check<I, V>), grid, blk, 0, st, x, cos_table, sin_table, y_ref, claimed, \
-                                                rows, (int)d, inner, npos, g2, uflow, alpha, eps_rel, w.hist, w.coarse, w.stats)
+                                                rows, (int)d, inner, npos, g2, uflow, alpha, eps_rel, pass_out(w, nblocks, n, out))
     if (interleaved) { if (vec) TAO_ROPE_CHECK(true, true); else TAO_ROPE_CHECK(true, false); }
     else             { if (vec) TAO_ROPE_CHECK(false, true); else TAO_ROPE_CHECK(false, false); }
 #undef TAO_ROPE_CHECK
-    launch_profile_reduce(w, nblocks, (unsigned long long)n, out, st);
+    launch_finish(w, nblocks, n, out, st);
     return launch_status();
 }
 

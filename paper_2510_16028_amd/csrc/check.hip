@@ -21,10 +21,9 @@ namespace tao {
 __global__ __launch_bounds__(kCheckThreads) void check_pass(
     const float* __restrict__ claimed, const float* __restrict__ ref, const float* __restrict__ tau,
     long n, int vec_ok, double alpha, double eps_rel,
-    unsigned int* __restrict__ ws_hist, unsigned int* __restrict__ ws_coarse,
-    BlockStats* __restrict__ ws_stats) {
+    PassOut pass) {
     __shared__ unsigned int hist[kBins * kReplicas];
-    __shared__ unsigned int red[3 * (kCheckThreads / kWave)];
+    __shared__ unsigned int red[kRedWords];
     const int tid = threadIdx.x;
     for (int i = tid; i < kBins * kReplicas; i += kCheckThreads) hist[i] = 0;
     __syncthreads();
@@ -46,8 +45,7 @@ __global__ __launch_bounds__(kCheckThreads) void check_pass(
     for (long i = (nvec << 2) + (long)blockIdx.x * kCheckThreads + tid; i < n; i += stride)
         check_one(claimed[i], ref[i], tau[i], alpha, eps_rel, hist, rep, acc);
 
-    flush_block_stats(acc, red, ws_stats);
-    flush_histogram(hist, ws_hist + (size_t)blockIdx.x * kBins, ws_coarse + blockIdx.x * kGroups);
+    finish_pass(hist, acc, red, pass);
 }
 
 __global__ __launch_bounds__(kReduceThreads) void profile_reduce(CheckWorkspace w, int nblocks, ProfileSize size, tao_profile* out) {
@@ -122,11 +120,11 @@ int tao_check_and_profile(const float* claimed, const float* ref, const float* t
     // one thread's chain of loads, divisions and atomics (with four vectors per thread, bound and reduction included: 8192
     // elements 10.5 against 9.3 us, 262144 13.5 against 9.8, a million 14.4 against 11.0)
     long want = (n + (long)kCheckThreads * 4 - 1) / ((long)kCheckThreads * 4);
-    int nblocks = (int)(want < 1 ? 1 : (want > kMaxCheckBlocks ? kMaxCheckBlocks : want));
+    int nblocks = (int)(want < 1 || n <= kAloneElements ? 1 : (want > kMaxCheckBlocks ? kMaxCheckBlocks : want));
     const CheckWorkspace w = carve_check_workspace(ws);
     hipLaunchKernelGGL(check_pass, dim3(nblocks), dim3(kCheckThreads), 0, st, claimed, ref, tau, n,
-                       vec_ok, alpha, eps_rel, w.hist, w.coarse, w.stats);
-    launch_profile_reduce(w, nblocks, (unsigned long long)n, out, st);
+                       vec_ok, alpha, eps_rel, pass_out(w, nblocks, n, out));
+    launch_finish(w, nblocks, n, out, st);
     return launch_status();
 }
 

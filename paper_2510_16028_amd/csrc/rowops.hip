@@ -20,6 +20,10 @@
 namespace tao {
 
 constexpr int kRowThreads = 256;
+// One-pass checks: rows that one workgroup takes in one trip (two of short rows), so that it forms the profile itself (finish_pass): GPU us
+// alone / with the finalising kernel: 4 x 768 6.4 / 10.4, 8 x 768 10.4 / 10.4 (and one launch less to enqueue), 4 x 4096, two trips,
+// 14.4 / 12.6.
+constexpr long alone_row_groups(long cols) { return cols <= 1024 ? 2 : 1; }
 
 struct RowConsts {
     double u;          // unit roundoff
@@ -232,14 +236,14 @@ template <int TPR, int V, bool FULL, bool QUICK>
 __global__ __launch_bounds__(kCheckThreads) void softmax_check(
     const float* __restrict__ x, const float* __restrict__ y, const float* __restrict__ claimed,
     long rows, long cols, long ld, RowConsts k, double alpha, double eps_rel,
-    unsigned int* __restrict__ ws_hist, unsigned int* __restrict__ ws_coarse, BlockStats* __restrict__ ws_stats) {
+    PassOut pass) {
     constexpr int RPB = kCheckThreads / TPR;
     using Idx = typename std::conditional<(V > 0), int, long>::type;     // columns: a cached row has at most 8192
     constexpr bool CACHED = (V > 0), CLAIMS = CACHED && V <= 4 && (QUICK || V == 1);   // claims requested with the row
     // the next rows are requested while these are worked on, where the registers allow it
     constexpr bool PIPE = V == 1 || (V == 2 && TPR < 1024);
     __shared__ unsigned int hist[kBins * kReplicas];
-    __shared__ unsigned int red[3 * (kCheckThreads / kWave)];
+    __shared__ unsigned int red[kRedWords];
     __shared__ double smem[2 * 4 * (kCheckThreads / kWave)];       // one slot per reduction of a row
     __shared__ unsigned int largest;
     const int tid = threadIdx.x;
@@ -377,8 +381,7 @@ __global__ __launch_bounds__(kCheckThreads) void softmax_check(
         }
     }
     __syncthreads();
-    flush_block_stats(acc_chk, red, ws_stats);
-    flush_histogram(hist, ws_hist + (size_t)blockIdx.x * kBins, ws_coarse + blockIdx.x * kGroups);
+    finish_pass(hist, acc_chk, red, pass);
 }
 
 // tail shared by LayerNorm and RMSNorm: from v*, E_v to (r*, E_r, R); ok = finite bound
@@ -715,14 +718,14 @@ template <bool RMS, int TPR, int V, bool FULL, bool QUICK>
 __global__ __launch_bounds__(kCheckThreads) void norm_check(
     const float* __restrict__ x, const float* __restrict__ y, const float* __restrict__ g, const float* __restrict__ claimed,
     long rows, long cols, long ld, RowConsts k, double alpha, double eps_rel,
-    unsigned int* __restrict__ ws_hist, unsigned int* __restrict__ ws_coarse, BlockStats* __restrict__ ws_stats) {
+    PassOut pass) {
     constexpr int RPB = kCheckThreads / TPR;
     using Idx = typename std::conditional<(V > 0), int, long>::type;     // columns: a cached row has at most 8192
     constexpr bool CACHED = (V > 0), CLAIMS = CACHED && V <= 4 && QUICK;  // claims requested with the row
     // the next rows are requested while these are worked on, where the registers allow it
     constexpr bool PIPE = V == 1 || (V == 2 && RMS);
     __shared__ unsigned int hist[kBins * kReplicas];
-    __shared__ unsigned int red[3 * (kCheckThreads / kWave)];
+    __shared__ unsigned int red[kRedWords];
     __shared__ double smem[2 * 4 * (kCheckThreads / kWave)];       // one slot per reduction of a row
     __shared__ unsigned int largest;
     const int tid = threadIdx.x;
@@ -875,8 +878,7 @@ __global__ __launch_bounds__(kCheckThreads) void norm_check(
         }
     }
     __syncthreads();
-    flush_block_stats(acc_chk, red, ws_stats);
-    flush_histogram(hist, ws_hist + (size_t)blockIdx.x * kBins, ws_coarse + blockIdx.x * kGroups);
+    finish_pass(hist, acc_chk, red, pass);
 }
 
 // ------------------------------------------------------------------ sum / mean
@@ -1157,9 +1159,9 @@ int tao_bound_check_norm(int kind, const float* x, const float* y_ref, const flo
     const bool rms = kind == TAO_NORM_RMSNORM;
     auto launch = [&](auto kernel, int tpr, long r, long c, long l) {
         const long rb = (r + (kCheckThreads / tpr) - 1) / (kCheckThreads / tpr);
-        nblocks = (int)(rb < 1 ? 1 : (rb < kMaxCheckBlocks ? rb : kMaxCheckBlocks));
+        nblocks = (int)(rb <= alone_row_groups(cols) ? 1 : (rb < kMaxCheckBlocks ? rb : kMaxCheckBlocks));
         hipLaunchKernelGGL(kernel, dim3(nblocks), dim3(kCheckThreads), 0, st, x, y_ref, gamma, claimed, r, c, l,
-                           k, alpha, eps_rel, w.hist, w.coarse, w.stats);
+                           k, alpha, eps_rel, pass_out(w, nblocks, n, out));
     };
     auto quick = [&](int tpr) { return quick_pays(rows, tpr); };
 #define TAO_NORM_CHECK_Q(RMS, TPR, V, Q) \
@@ -1186,7 +1188,7 @@ int tao_bound_check_norm(int kind, const float* x, const float* y_ref, const flo
 #undef TAO_NORM_CHECK_ROWS
 #undef TAO_NORM_CHECK_Q
 #undef TAO_NORM_CHECK
-    launch_profile_reduce(w, nblocks, (unsigned long long)n, out, st);
+    launch_finish(w, nblocks, n, out, st);
     return launch_status();
 }
 
@@ -1216,9 +1218,9 @@ int tao_bound_check_softmax(const float* x, const float* y_ref, const float* cla
     if (n > 0) {
         auto launch = [&](auto kernel, int tpr) {
             const long rb = (rows + (kCheckThreads / tpr) - 1) / (kCheckThreads / tpr);
-            nblocks = (int)(rb < kMaxCheckBlocks ? rb : kMaxCheckBlocks);
+            nblocks = (int)(rb <= alone_row_groups(cols) ? 1 : (rb < kMaxCheckBlocks ? rb : kMaxCheckBlocks));
             hipLaunchKernelGGL(kernel, dim3(nblocks), dim3(kCheckThreads), 0, st, x, y_ref, claimed, rows, cols, ld,
-                               k, alpha, eps_rel, w.hist, w.coarse, w.stats);
+                               k, alpha, eps_rel, pass_out(w, nblocks, n, out));
         };
         auto quick = [&](int tpr) { return quick_pays(rows, tpr); };
 #define TAO_SOFTMAX_CHECK_Q(TPR, V, Q) (full ? launch(softmax_check<TPR, V, true, Q>, TPR) : launch(softmax_check<TPR, V, false, Q>, TPR))
@@ -1237,9 +1239,9 @@ int tao_bound_check_softmax(const float* x, const float* y_ref, const float* cla
     } else {
         // nothing to examine: an empty partial, so that the profile reports n = 0
         hipLaunchKernelGGL((softmax_check<64, 1, false, false>), dim3(1), dim3(kCheckThreads), 0, st, x, y_ref, claimed, 0L, 1L, 1L,
-                           k, alpha, eps_rel, w.hist, w.coarse, w.stats);
+                           k, alpha, eps_rel, pass_out(w, nblocks, n, out));
     }
-    launch_profile_reduce(w, nblocks, (unsigned long long)n, out, st);
+    launch_finish(w, nblocks, n, out, st);
     return launch_status();
 }
 

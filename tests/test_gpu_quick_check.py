@@ -5,6 +5,8 @@ import numpy as np
 import pytest
 import torch
 
+import oracle
+
 pytestmark = pytest.mark.gpu
 
 
@@ -216,6 +218,40 @@ def test_claims_that_equal_the_reference(tao, op, share):
     else:
         tau, got = tao.tao_bound_norm(kind, x, y, gamma, None, eps=1e-5), tao.tao_bound_check_norm(kind, x, y, c, gamma, None, eps=1e-5)
     want = tao.tao_check_and_profile(c, y, tau)
+    for key in want:
+        a, b = np.asarray(got[key]), np.asarray(want[key])
+        assert np.array_equal(a, b, equal_nan=a.dtype.kind == "f"), key
+
+
+# both sides of the rules by which one workgroup forms the profile itself, and the smallest tensors
+@pytest.mark.parametrize("n", [1, 2, 3, 63, 64, 1025, 4097, 8192, 8193, 16384, 16385])
+def test_small_tensors(tao, n):
+    g = torch.Generator(device="cuda").manual_seed(n)
+    x, x2 = torch.randn(n, generator=g, device="cuda"), torch.randn(n, generator=g, device="cuda")
+    for kind, two in ((tao.ACT_GELU_ERF, False), (tao.ACT_SILU, False), (tao.ACT_MUL, True)):
+        y = x * x2 if two else x / (1 + torch.exp(-x))
+        tau = tao.tao_bound_act(kind, x, y, x2=x2 if two else None)
+        c = _claims(y, tau, g)
+        if n > 3:
+            c[1], y[2], c[2] = float("nan"), 0.0, 0.0
+        tau = tao.tao_bound_act(kind, x, y, x2=x2 if two else None)
+        got = tao.tao_bound_check_act(kind, x, y, c, x2=x2 if two else None, eps_rel=0.0)
+        streamed = tao.tao_check_and_profile(c, y, tau, eps_rel=0.0)
+        want = oracle.check_and_profile(c.cpu().numpy(), y.cpu().numpy(), tau.cpu().numpy(), eps_rel=0.0)
+        for key in streamed:
+            a, b, w = np.asarray(got[key]), np.asarray(streamed[key]), np.asarray(want[key])
+            assert np.array_equal(a, b, equal_nan=a.dtype.kind == "f"), key
+            assert np.array_equal(a, w.astype(a.dtype), equal_nan=a.dtype.kind == "f"), key
+
+
+@pytest.mark.parametrize("rows,cols", [(1, 1), (1, 5), (4, 768), (8, 768), (9, 768), (16, 128), (33, 200), (1, 4096), (2, 4096), (3, 4096), (1, 9000), (2, 9000)])
+def test_few_rows(tao, rows, cols):
+    g = torch.Generator(device="cuda").manual_seed(rows + cols)
+    x = torch.randn((rows, cols), generator=g, device="cuda")
+    y = torch.softmax(x, -1)
+    tau = tao.tao_bound_softmax(x, y)
+    c = _claims(y, tau, g)
+    want, got = tao.tao_check_and_profile(c, y, tau), tao.tao_bound_check_softmax(x, y, c)
     for key in want:
         a, b = np.asarray(got[key]), np.asarray(want[key])
         assert np.array_equal(a, b, equal_nan=a.dtype.kind == "f"), key
