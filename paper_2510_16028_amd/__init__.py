@@ -204,8 +204,8 @@ def _torch():
 
 def _stream():
     # (the raw handle of the current device's current stream: a Stream object on every call takes 2.8 us)
-    torch = _torch()
-    return ctypes.c_void_p(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))
+    c = _torch()._C
+    return c._cuda_getCurrentRawStream(c._cuda_getDevice())
 
 
 def _dev(t, name):
@@ -218,7 +218,8 @@ def _dev(t, name):
 
 
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    # (a plain address: the declared argument types make the pointer)
+    return None if t is None else t.data_ptr()
 
 
 def _mref(model):
@@ -261,31 +262,35 @@ def tao_gamma(k, model=None):
 
 
 def _linear_args(A, W, bias, trans_w, out):
+    # (shapes and strides are asked for once: on a small layer these questions take as long as a launch)
     torch = _torch()
     A = _dev(A, "A"); W = _dev(W, "W"); bias = _dev(bias, "bias")
-    if A.dim() not in (2, 3) or W.dim() not in (2, 3):
+    As, Ws = A.shape, W.shape
+    Ad, Wd = len(As), len(Ws)
+    if Ad not in (2, 3) or Wd not in (2, 3):
         raise ValueError("A and W must be 2-D or 3-D")
-    for t, nm in ((A, "A"), (W, "W")):
-        if t.shape[-1] > 1 and t.stride(-1) != 1:
+    At, Wt = A.stride(), W.stride()
+    for shape, stride, nm in ((As, At, "A"), (Ws, Wt, "W")):
+        if shape[-1] > 1 and stride[-1] != 1:
             raise ValueError("%s: last dimension must be contiguous" % nm)
-    batch = A.shape[0] if A.dim() == 3 else 1
-    M, K = A.shape[-2], A.shape[-1]
-    N = W.shape[-1] if trans_w else W.shape[-2]
-    if (W.shape[-2] if trans_w else W.shape[-1]) != K:
+    batch = As[0] if Ad == 3 else 1
+    M, K = As[-2], As[-1]
+    N = Ws[-1] if trans_w else Ws[-2]
+    if (Ws[-2] if trans_w else Ws[-1]) != K:
         raise ValueError("reduction sizes of A and W differ")
-    if W.dim() == 3 and W.shape[0] != batch:
+    if Wd == 3 and Ws[0] != batch:
         raise ValueError("batch sizes of A and W differ")
     if bias is not None and (bias.dim() != 1 or bias.shape[0] != N or not bias.is_contiguous()):
         raise ValueError("bias must be a contiguous [N] tensor")
-    shape = (batch, M, N) if A.dim() == 3 else (M, N)
+    shape = (batch, M, N) if Ad == 3 else (M, N)
     if out is None:
         out = torch.empty(shape, dtype=torch.float32, device=A.device)
-    elif tuple(out.shape) != shape or not out.is_contiguous() or out.dtype != torch.float32:
+    elif out.shape != shape or not out.is_contiguous() or out.dtype != torch.float32:
         raise ValueError("out must be a contiguous float32 tensor of shape %s" % (shape,))
-    lda = A.stride(-2) if M > 1 else max(K, 1)
-    ldw = W.stride(-2) if W.shape[-2] > 1 else max(W.shape[-1], 1)
-    sA = A.stride(0) if A.dim() == 3 and batch > 1 else M * lda
-    sW = (W.stride(0) if W.shape[0] > 1 else 0) if W.dim() == 3 else 0
+    lda = At[-2] if M > 1 else max(K, 1)
+    ldw = Wt[-2] if Ws[-2] > 1 else max(Ws[-1], 1)
+    sA = At[0] if Ad == 3 and batch > 1 else M * lda
+    sW = (Wt[0] if Ws[0] > 1 else 0) if Wd == 3 else 0
     return A, W, bias, out, (M, N, K, lda, ldw, N, int(bool(trans_w)), batch, sA, sW, M * N)
 
 

@@ -594,9 +594,7 @@ int tao_bound_linear(const float* A, const float* W, const float* bias, float* t
     if (!tau || (K > 0 && (!A || !W))) return TAO_ERR_NULL;
     if (!aligned(A, 4) || !aligned(W, 4) || !aligned(bias, 4) || !aligned(tau, 4)) return TAO_ERR_ALIGN;
 
-    int dev = 0, cus = 256;
-    if (hipGetDevice(&dev) == hipSuccess) (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-    if (cus < 1) cus = 256;
+    const int cus = device_cus();
     const LinearProblem problem = {A, W, bias, tau, M, N, K, lda, ldw, ldt, trans_w != 0, batch, strideA, strideW, strideT};
     if (f64_route(problem, cus)) return f64_launch(problem, md, c, cus, (hipStream_t)stream);
 
@@ -705,9 +703,7 @@ int tao_bound_conv2d(const float* x, const float* w, const float* bias, float* t
     p.sabs0 = (md.flags & TAO_FLAG_UNDERFLOW_TERMS) ? p.sabs : 0.0;
     p.uflow = (md.flags & TAO_FLAG_UNDERFLOW_TERMS) ? (double)Kp * 0x1p-149 : 0.0;
 
-    int dev = 0, cus = 256;
-    if (hipGetDevice(&dev) == hipSuccess) (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-    if (cus < 1) cus = 256;
+    const int cus = device_cus();
     const long tiles_n = (N + BN - 1) / BN;
     const bool small = prefer_64_row_tiles(M, tiles_n, cus);
     const long bm = small ? 64 : 128;

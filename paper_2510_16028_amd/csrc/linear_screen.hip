@@ -504,12 +504,6 @@ __global__ __launch_bounds__(WVM * WVN * 64, WVM * WVN * PER_CU / 4) void screen
 
 double accumulation_error(long K) { return (2.01 * (double)((K + SBK - 1) / SBK * SBK) / 8.0 + 8.0) * 0x1p-24; }
 
-int cus() {
-    int dev = 0, n = 256;
-    if (hipGetDevice(&dev) == hipSuccess) (void)hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev);
-    return n;
-}
-
 template <int RM, int RN, int WVM, int WVN, int GPS, int NST, int PER_CU, int SRC>
 int launch_config(ScreenArgs& p, long batch, hipStream_t st) {
     constexpr int TM = WVM * RM * 32, TN = WVN * RN * 32;
@@ -524,7 +518,7 @@ int launch_config(ScreenArgs& p, long batch, hipStream_t st) {
     const long ntiles = (long)p.tiles_m * p.tiles_n * batch;
     if (ntiles >= (1L << 30)) return TAO_ERR_SHAPE;
     p.ntiles = (unsigned)ntiles;
-    long grid = (long)cus() * PER_CU & ~7L;
+    long grid = (long)device_cus() * PER_CU & ~7L;
     if (grid < 8) grid = 8;
     const long want = (ntiles + 7) & ~7L;
     hipLaunchKernelGGL(kernel, dim3((unsigned)(want < grid ? want : grid)), dim3(WVM * WVN * 64), lds_bytes, st, p);
@@ -565,7 +559,7 @@ int launch_screen(const ScreenOperand& A, const ScreenOperand& W, const float* b
     p.unsettled = &ws.stats[kOpenFlag].flag;
     p.hist = ws.hist; p.coarse = ws.coarse; p.stats = ws.stats;
     if (chk.ldy >= kScreenMaxLd) return TAO_ERR_SHAPE;
-    const long n = cus();
+    const long n = device_cus();
     const long t128 = ((M + 127) / 128) * ((N + 127) / 128) * batch;
     // Tiles of 128 x 128, two workgroups to a compute unit, where they give every compute unit one (us of the whole call on images, with
     // them / with 64 x 64: 2048 x 12288 over 4096 248 / 362, 2048 x 4096 over 4096 94 / 122, 1111 x 3001 over 1001, 216 tiles, 37 / 33);

@@ -1167,11 +1167,6 @@ int tao_selftest_matrix_core_bf16(unsigned* report, long cases, void* ws, size_t
 
 namespace tao {
 inline size_t round_up_256(size_t b) { return (b + 255) / 256 * 256; }
-static int device_cus() {
-    int dev = 0, cus = 256;
-    if (hipGetDevice(&dev) == hipSuccess) (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-    return cus;
-}
 // Parts the reduction is cut into: launches with fewer 128 x 128 tiles than compute units take as
 // many parts as fill the chip, each at least kMinGroupsPerPart groups long.
 static int split_k_parts(long M, long N, long K, long batch) {

@@ -28,6 +28,20 @@ struct OncePerDevice {
     }
 };
 
+// Compute units of the current device (256 assumed without one); asked for once per device, as a call needs it several times.
+inline int device_cus() {
+    static std::atomic<int> known[64];
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess) return 256;
+    std::atomic<int>& slot = known[dev & 63];
+    int cus = dev < 64 ? slot.load(std::memory_order_relaxed) : 0;
+    if (cus == 0) {
+        if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0) return 256;
+        if (dev < 64) slot.store(cus, std::memory_order_relaxed);
+    }
+    return cus;
+}
+
 inline int launch_status() {
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) { g_last_hip_error = (int)e; return TAO_ERR_LAUNCH; }
