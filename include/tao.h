@@ -80,7 +80,8 @@ enum {
                                        upper bound, but looser than the default by about 2*K*u relative
                                        (small outputs, on the binary64 matrix cores, keep the default bound) */
     TAO_FLAG_CHECK_IN_EPILOGUE = 4u /* tao_bound_check_linear: check in the matrix kernel's epilogue for
-                                       every reduction length (no stored bound, its workspace unused);
+                                       every reduction length (no stored bound, its workspace unused; nothing
+                                       is decided ahead of it);
                                        same result, slower for short reductions */
 };
 
@@ -172,11 +173,14 @@ size_t tao_linear_split_workspace_bytes(long M, long N, long K, long batch, int 
 int tao_linear_split_preferred(long M, long N, long K, long batch);
 /* The bound of tao_bound_linear_split checked on the spot (Sec. 5.4 leaf check, Sec. 5.3 profile):
  * *out receives exactly what tao_check_and_profile(claimed, y_ref, tau, ...) would return for the
- * tau that tao_bound_linear_split computes from the same operands, but tau is compared in registers
- * in the matrix kernel's epilogue and only stored when `tau` is not NULL (layout ldy / strideY, like
- * y_ref and claimed: M x N per batch entry, ldy >= N).  Where the epilogue would cost more than it
- * saves -- reductions up to 1024 long with contiguous outputs that are not cut into parts -- the bound is stored instead (into
- * `tau`, else into the workspace) and the streaming check reads it: the same result, sooner.
+ * tau that tao_bound_linear_split computes from the same operands, but tau is only stored when `tau` is
+ * not NULL (layout ldy / strideY, like y_ref and claimed: M x N per batch entry, ldy >= N).
+ * With tau == NULL one BF16 product of the rounded operands first encloses every tau to within 0.8 % and
+ * decides the comparisons it can; if any is left open (a claim that close to its bound, operands from 2^32 on, NaN)
+ * the whole call is then checked against the bound itself: the same result, at the cost of both (up to
+ * 1.4 times the second alone for large products, 2 to 3 times for small ones).  The bound itself is compared in
+ * registers in the matrix kernel's epilogue; where that would cost more than it saves -- `tau` asked for, reductions up to
+ * 1024 long with contiguous outputs that are not cut into parts -- it is stored and the streaming check reads it.
  * y_ref: the verifier's re-executed output, claimed: the proposer's.  out: DEVICE, fully overwritten,
  * valid once the stream has drained.  ws / ws_bytes: DEVICE scratch of at least
  * tao_bound_check_linear_workspace_bytes(...), 256-byte aligned.  Runs the BF16-split kernel for every
@@ -222,8 +226,8 @@ int tao_bound_check_linear_images(const void *A_image, const void *W_image, cons
                                   tao_profile *out, void *ws, size_t ws_bytes, void *stream);
 size_t tao_check_linear_images_workspace_bytes(long M, long N, long K, long batch);
 
-/* 1 if tao_bound_check_linear checks a product of this shape (contiguous outputs) without storing the
- * bound -- in the matrix kernel's epilogue, or in the pass that adds the parts of a reduction cut into
+/* 1 if tao_bound_check_linear, where it forms the bound, checks a product of this shape (contiguous outputs) without storing
+ * it -- in the matrix kernel's epilogue, or in the pass that adds the parts of a reduction cut into
  * parts --, 0 if it stores the bound and runs the streaming check.  Host only: for callers that time or
  * schedule the two kernels separately. */
 int tao_bound_check_linear_in_epilogue(long M, long N, long K, long batch);
@@ -273,7 +277,8 @@ int tao_bound_conv2d(const float *x, const float *w, const float *bias, float *t
  * tao_bound_check_conv2d: the bound checked on the spot like tao_bound_check_linear (y_ref, claimed and
  * the optional tau: [batch][OH][OW][Cout] contiguous; the result of tao_check_and_profile on the stored
  * bound, field for field).  ws / ws_bytes: DEVICE scratch of tao_conv2d_split_workspace_bytes(...,
- * with_check) bytes, 256-byte aligned. */
+ * with_check) bytes, 256-byte aligned (with the check this includes 2 bytes per element of x for the product that
+ * decides ahead of the bound; a workspace without that part is accepted, and the bound itself checked). */
 int tao_conv2d_split_supported(long batch, long H, long W, long C, long Cout, long R, long S,
                                long stride_h, long stride_w, long pad_h, long pad_w, long dil_h, long dil_w);
 size_t tao_conv2d_split_workspace_bytes(long batch, long H, long W, long C, long Cout, long R, long S,

@@ -37,6 +37,10 @@
 // (see split_pack8), so the bound stays an upper bound but can exceed 1e-6 there.  Sums that reach
 // down into the binary32 subnormal range carry an absolute error instead of a relative one; the
 // epilogue adds a bound on it (see split_run), which is far below 1e-6 of any bound above 2^-120.
+//
+// A check needs only the comparisons d <= alpha tau.  Where the caller does not want tau, one BF16 product
+// (linear_screen.hip) decides them first, and the kernels of this file form the bound only if it left one open
+// (absgemm_settle*, launched behind it in either case; screened() holds the rule).
 #include <algorithm>
 #include <cstring>
 #include <type_traits>
@@ -63,7 +67,7 @@ constexpr int kSlab = STILE * SROW;     // one operand, one piece
 constexpr int kBlock = 3 * kSlab;       // one operand, three pieces: 24576 bytes, contiguous in the workspace
 constexpr int kSplitStage = 2 * kBlock; // |A| hi, mid, lo, |W| hi, mid, lo: 49152 bytes
 constexpr int kSplitStages = 3;         // 144 KB of LDS
-constexpr long kEpilogueCheckMinK = 1025; // shorter reductions (up to 1024, as far as the plain bound walks its tiles): the bound is stored and the streaming check reads it (see split_run)
+constexpr long kEpilogueCheckMinK = 1025; // shorter reductions (up to 1024, as far as the plain bound walks its tiles), where no screen decides: the bound is stored and the streaming check reads it (see split_run)
 constexpr long kMinGroupsPerPart = 4;   // a reduction cut into parts: at least 128 k-steps each
 constexpr long kWalkMaxGroups = 32;     // reductions up to 1024 k-steps walk their tiles ...
 constexpr int kWalkMinTilesPerCu = 4;   // ... when a compute unit has at least this many

@@ -713,7 +713,7 @@ __global__ __launch_bounds__(kRowThreads) void rmsnorm_bound_noy(
 // store or, rarely, its neighbour.  FULL, QUICK: as there.
 // What bounds it: HBM for many rows (32768 x 768: LayerNorm 180 -> 90 us, RMSNorm 128 -> 65 us; LayerNorm 8192 x 2048 170 -> 67 us,
 // whose rows are now kept instead of read again), the chain of one row -- loads, two reductions, a square root and divisions in
-// binary64 -- for few (2048 x 4096 RMSNorm 34.4 -> 32.3 us), which is why the next rows are requested early.
+// binary64 -- for few (2048 x 4096 RMSNorm 34.4 -> 29.7 us with its finalising launch), which is why the next rows are requested early.
 template <bool RMS, int TPR, int V, bool FULL, bool QUICK>
 __global__ __launch_bounds__(kCheckThreads) void norm_check(
     const float* __restrict__ x, const float* __restrict__ y, const float* __restrict__ g, const float* __restrict__ claimed,
