@@ -269,7 +269,7 @@ __device__ __forceinline__ void finish_pass(const unsigned int* hist, const Thre
     unsigned int c[2] = {0, 0};
 #pragma unroll
     for (int r = 0; r < kReplicas; ++r) { c[0] += hist[2 * tid * kReplicas + r]; c[1] += hist[(2 * tid + 1) * kReplicas + r]; }
-    const unsigned int mine = c[0] + c[1];                   // (a workgroup that is alone has few elements)
+    const unsigned int mine = c[0] + c[1];                   // (at most kAloneMost elements: every sum here fits 32 bits)
     const unsigned int upto = (unsigned int)wave_scan(mine);
     const unsigned int v = wave_sum(acc.violations), q = wave_sum(acc.nans), m = wave_max(acc.max_bits);
     if (lane == kWave - 1) { red[wave * 4] = v; red[wave * 4 + 1] = q; red[wave * 4 + 2] = m; red[wave * 4 + 3] = upto; }
@@ -305,12 +305,16 @@ __device__ __forceinline__ void finish_pass(const unsigned int* hist, const Thre
 }
 // Enqueue the finalising kernel over the partials of `nblocks` pass-1 workgroups (defined with the check pass).
 void launch_profile_reduce(const CheckWorkspace& w, int nblocks, unsigned long long n, tao_profile* out, hipStream_t st);
-// The outputs of a pass of `nblocks` workgroups over n elements, and the finalising kernel where it is more than one.
+// One workgroup forms the profile itself where it is alone, in sums of 32 bits; a longer tensor that one workgroup takes (a single row of
+// any length) goes through the finalising kernel, which adds in 64.
+constexpr long kAloneMost = 0xffffffffL;
+inline bool forms_profile(int nblocks, long n) { return nblocks == 1 && n <= kAloneMost; }
+// The outputs of a pass of `nblocks` workgroups over n elements, and the finalising kernel where the pass does not end with the profile.
 inline PassOut pass_out(const CheckWorkspace& w, int nblocks, long n, tao_profile* out) {
-    return {w, nblocks == 1 ? out : nullptr, profile_size((unsigned long long)n)};
+    return {w, forms_profile(nblocks, n) ? out : nullptr, profile_size((unsigned long long)n)};
 }
 inline void launch_finish(const CheckWorkspace& w, int nblocks, long n, tao_profile* out, hipStream_t st) {
-    if (nblocks > 1) launch_profile_reduce(w, nblocks, (unsigned long long)n, out, st);
+    if (!forms_profile(nblocks, n)) launch_profile_reduce(w, nblocks, (unsigned long long)n, out, st);
 }
 
 }  // namespace tao
