@@ -1,5 +1,6 @@
 // Screening of a checked matmul bound: one BF16 product decides the comparisons that six would (linear_screen.hip).
 #pragma once
+#include <cmath>
 #include "tao_check.hpp"
 
 namespace tao {
@@ -40,8 +41,21 @@ inline ClearJob clear_job(const CheckWorkspace& w, int slots) {
 }
 static_assert(kMaxCheckBlocks * sizeof(BlockStats) % 16 == 0, "cleared in 16-byte words");
 
-// Whether the screen can decide for these constants (u: the model's, cg: Gamma with its guard factor; see linear_screen.hip).
-bool screen_usable(long K, double u, double cg, double alpha, double uflow);
+// The real sum of |a||w| lies in [lower P, upper P] of the chain's result P (see linear_screen.hip).
+constexpr int kScreenGroup = 32;              // reductions go by whole groups of 32 k
+inline double accumulation_error(long K) { return (2.01 * (double)((K + kScreenGroup - 1) / kScreenGroup * kScreenGroup) / 8.0 + 8.0) * 0x1p-24; }
+struct ScreenLimits { double lower, upper; };
+inline ScreenLimits screen_limits(long K) {
+    const double acc = accumulation_error(K), half = 0x1p-8;
+    return {(1.0 - half) * (1.0 - half) / std::exp(acc), (1.0 + half) * (1.0 + half) / (1.0 - acc)};
+}
+// Whether the screen can decide for these constants (u: the model's, cg: Gamma with its guard factor): a bound inflated by its own 11.4u
+// well within 2^-14, factors that stay ordinary in binary32 (bounds of at least 2^-120, limits below 2^109), absolute terms below 2^-20 of them.
+inline bool screen_usable(long K, double u, double cg, double alpha, double uflow) {
+    const double a = alpha * cg;
+    return K > 0 && u <= 0x1p-20 && accumulation_error(K) <= 0x1p-6 && cg >= 0x1p-40 && cg <= 0x1p10 && a >= 0x1p-40 && a <= 0x1p20 &&
+           uflow <= cg * (double)K * 0x1p-100;
+}
 int launch_screen(const ScreenOperand& A, const ScreenOperand& W, const float* bias, long M, long N, long K, long batch,
                   double cg, const ScreenCheck& chk, const CheckWorkspace& ws, hipStream_t st);
 

@@ -1,10 +1,12 @@
 """The enclosure that the screen of a checked matmul bound rests on: the real sum of |a||w| against one chain of BF16 products
 of the operands rounded to nearest, with the matrix-core instruction as modelled in tests/bf16_mfma_model.py."""
+import math
 from fractions import Fraction
 
 import numpy as np
 import pytest
 
+import hostcode
 from bf16_mfma_model import SCALE, exact_sum, f32_value, mfma
 
 U = Fraction(1, 1 << 24)
@@ -46,3 +48,32 @@ def test_real_sum_lies_in_the_enclosure(family, K):
         assert abs(Fraction(acc - rounded, rounded)) <= chain
         got, half = Fraction(acc << SCALE), Fraction(1, 256)
         assert got * (1 - half) ** 2 / (1 + chain) <= real <= got * (1 + half) ** 2 / (1 - chain)
+
+
+LIMITS = r"""
+#include <cstdio>
+#include "linear_screen.hpp"
+namespace tao { thread_local int g_last_hip_error = 0; void launch_profile_reduce(const CheckWorkspace&, int, unsigned long long, tao_profile*, hipStream_t) {} }
+int main() {
+    using namespace tao;
+    long most = 1;                                           // the longest reduction that is screened
+    for (long step = 1L << 40; step; step >>= 1)
+        if (screen_usable(most + step, 0x1p-24, 0x1p-4, 1.0, 0.0)) most += step;
+    for (long K : {1L, 32L, 1000L, 1L << 14, 1L << 17, 1L << 19, (most + 1) / 2, most - 32, most})
+        std::printf("%ld %a %a\n", K, screen_limits(K).lower, screen_limits(K).upper);
+}
+"""
+
+
+def test_limits_cover_errors_that_compound(tmp_path):
+    """Every step errs by its full 2.01u of the sum so far and 7u of its own, all upwards or all downwards: the host's factors, without the
+    2^-14 that is kept for the bound's own slack and the comparison's roundings, still enclose the real sum."""
+    u = 2.0 ** -24
+    for line in hostcode.run(LIMITS, tmp_path):
+        K, lower, upper = line.split()
+        n, lower, upper = (int(K) + 31) // 32 * 4, float.fromhex(lower), float.fromhex(upper)
+        up = n * math.log1p(2.01 * u) + math.log1p(7 * u)
+        down = n * math.log1p(-2.01 * u) + math.log1p(-7 * u)
+        assert math.log(lower) + up <= 2 * math.log1p(-2.0 ** -8) + 1e-14, K
+        assert math.log(upper) + down >= 2 * math.log1p(2.0 ** -8) - 1e-14, K
+        assert lower >= 0.97 and upper <= 1.03, K            # (what is admitted stays narrow)
