@@ -386,7 +386,8 @@ __global__ __launch_bounds__(WVM * WVN * 64, WVM * WVN * PER_CU / 4) void screen
             int inside = fmaxf(fmaxf(over[0], over[1]), fmaxf(over[2], over[3])) <= bias_low;
             inside &= min(min(least[0], least[1]), min(least[2], least[3])) >= __float_as_uint(p.tiny);
             const unsigned most_bits = max(max(bits[0], bits[1]), max(bits[2], bits[3]));      // (a NaN's are the largest)
-            int ok = most_bits + 16u <= known;
+            // (no larger than an error that occurs; or all 0, and then exactly: the edges leave estimates that came down to 0 open)
+            int ok = most_bits <= max(known, 16u) - 16u;
             ok &= min(min(edge[0], edge[1]), min(edge[2], edge[3])) >= 32u << 12;
             ok &= fmaxf(fmaxf(den[0], den[1]), fmaxf(den[2], den[3])) <= 0x1p100f;
             if (!inside || most_bits > 0x7f800000u) {

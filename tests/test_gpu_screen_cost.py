@@ -1,0 +1,65 @@
+"""What a checked matmul bound costs for claims that differ in a few elements or not at all: about as much as for ordinary honest ones.
+The ratios are of times taken side by side; the limits lie far from both what is measured and what they guard against."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def tao():
+    import paper_2510_16028_amd as t
+    t.lib()
+    assert torch.cuda.is_available()
+    return t
+
+
+def _times(calls):
+    """The shortest time of each call among rounds that take them in turn (ms per call)."""
+    best = [float("inf")] * len(calls)
+    a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    for _ in range(8):
+        for i, f in enumerate(calls):
+            f()
+            a.record()
+            for _ in range(10):
+                f()
+            b.record()
+            b.synchronize()
+            best[i] = min(best[i], a.elapsed_time(b) / 10)
+    return best
+
+
+def _setup(tao, form):
+    """(tau, y, check of a claim) for a product on images, on binary32 rows, and a convolution."""
+    g = torch.Generator(device="cuda").manual_seed(5)
+    out = tao.new_profile_buffer(torch.device("cuda", 0))
+    scratch = lambda n: torch.empty(int(n), dtype=torch.uint8, device="cuda")
+    if form == "pixels":
+        x = torch.randn((32, 28, 28, 128), generator=g, device="cuda").abs()
+        w = torch.randn((512, 1, 1, 128), generator=g, device="cuda") * 0.1
+        tau = tao.tao_bound_conv2d_split(x, w)
+        y = torch.matmul(x.view(-1, 128), w.view(512, 128).t().contiguous()).view(tau.shape)
+        ws = scratch(tao.lib().tao_conv2d_split_workspace_bytes(32, 28, 28, 128, 512, 1, 1, 1, 1, 0, 0, 1, 1, 1))
+        return tau, y, lambda c: tao.tao_bound_check_conv2d(x, w, None, y, c, out=out, ws=ws, readback=False)
+    B, M, N, K = (8, 2048, 2048, 128) if form == "image" else (8, 8192, 128, 2048)
+    A, W = torch.randn((B, M, K), generator=g, device="cuda"), torch.randn((B, N, K), generator=g, device="cuda") * 0.02
+    tau, y = tao.tao_bound_linear_split(A, W), torch.matmul(A, W.transpose(1, 2).contiguous())
+    if form == "rows":
+        ws = scratch(tao.tao_bound_check_linear_workspace_bytes(M, N, K, B, False))
+        return tau, y, lambda c: tao.tao_bound_check_linear(A, W, None, y, c, out=out, ws=ws, readback=False)
+    images = tao.tao_split_operand(A), tao.tao_split_operand(W)
+    ws = scratch(tao.lib().tao_check_linear_images_workspace_bytes(M, N, K, B))
+    return tau, y, lambda c: tao.tao_bound_check_linear_images(*images, M, N, K, y, c, batch=B, shared_w=False, out=out, ws=ws, readback=False)
+
+
+@pytest.mark.parametrize("form", ["image", "rows", "pixels"])
+def test_equal_claims_cost_what_honest_ones_do(tao, form):
+    tau, y, check = _setup(tao, form)
+    g = torch.Generator(device="cuda").manual_seed(6)
+    honest = (y.double() * (1 + 2.0 ** -23 * torch.randint(-2, 3, y.shape, generator=g, device="cuda"))).float()
+    equal = y.clone()
+    assert tao.read_profile(check(equal))["max_rel"] == 0.0
+    t_honest, t_equal = _times([lambda: check(honest), lambda: check(equal)])
+    # (measured: at most 1.0; with equal elements on the exact way 2.3, 1.2 and 2.1)
+    assert t_equal <= 1.15 * t_honest, (form, t_equal, t_honest)
