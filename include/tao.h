@@ -176,14 +176,16 @@ int tao_linear_split_preferred(long M, long N, long K, long batch);
  * tau that tao_bound_linear_split computes from the same operands, but tau is only stored when `tau` is
  * not NULL (layout ldy / strideY, like y_ref and claimed: M x N per batch entry, ldy >= N).
  * With tau == NULL one BF16 product of the rounded operands first encloses every tau to within 0.8 % and
- * decides the comparisons it can; if any is left open (a claim that close to its bound, operands from 2^32 on, NaN)
- * the whole call is then checked against the bound itself: the same result, at the cost of both (up to
- * 1.4 times the second alone for large products, 2 to 3 times for small ones).  The bound itself is compared in
- * registers in the matrix kernel's epilogue; where that would cost more than it saves -- `tau` asked for, reductions up to
+ * decides the comparisons it can.  What it leaves open -- claims that close to their bounds, all claims of a tile (128 x 128 outputs)
+ * with an operand from 2^32 on or not finite -- is then decided tile by tile, by the real sum of the products where that is enough and
+ * against the bound itself where not: the same result.  Few such claims cost little; where all are, both
+ * products are formed (1.1 to 1.2 times the time of the second alone for large products, up to 2.4 times for the smallest).
+ * The bound itself is compared in registers in the matrix kernel's epilogue; where that would cost more than it saves -- `tau` asked for, reductions up to
  * 1024 long with contiguous outputs that are not cut into parts -- it is stored and the streaming check reads it.
  * y_ref: the verifier's re-executed output, claimed: the proposer's.  out: DEVICE, fully overwritten,
- * valid once the stream has drained.  ws / ws_bytes: DEVICE scratch of at least
- * tao_bound_check_linear_workspace_bytes(...), 256-byte aligned.  Runs the BF16-split kernel for every
+ * valid once the stream has drained.  ws / ws_bytes: DEVICE scratch of
+ * tao_bound_check_linear_workspace_bytes(...), 256-byte aligned (64 bytes of it per tile are the records of what is open: a workspace
+ * without that part is accepted, and the bound itself checked; so for the other checked entry points).  Runs the BF16-split kernel for every
  * shape (tao_linear_split_preferred tells where that is the faster one).  Errors as for
  * tao_bound_linear_split and tao_check_and_profile; TAO_ERR_SHAPE also for M N batch >= 2^36. */
 int tao_bound_check_linear(const float *A, const float *W, const float *bias, const float *y_ref,

@@ -14,12 +14,15 @@
 // Hence  d <= alpha cg (P lower + |b|)  proves that the exact check finds no violation and  d > alpha cg (P upper + |b|)
 // that it finds one.  The enclosure holds where every operand is below 2^32 in magnitude (nothing overflows, and what
 // operands below 2^-126 lose in BF16's subnormal range, 2^-134 each, weighs at most K 2^-101) and the sum at least
-// Kp 2^-80; an element with d = 0 never violates a bound that is not NaN.  Whatever else is met -- a larger or
-// non-finite operand anywhere in a tile, a bias beyond 2^60, a claim between the two limits, NaN -- sets the `unsettled`
-// flag: the screen's results are then void and the exact route, enqueued behind it, does the whole work; otherwise
-// that route's kernels return at once.  So every profile is the exact route's, bit for bit.
+// Kp 2^-80; an element with d = 0 never violates a bound that is not NaN, and one whose d is NaN violates every bound.  Other
+// comparisons -- a claim between the two limits, a smaller sum -- are left open, and so are all of a tile with a larger or
+// non-finite operand or a bias beyond 2^60: a record per tile of the exact route (OpenTile) keeps their places, and that route,
+// enqueued behind the screen, decides these and nothing else.  So every profile is the exact route's, bit for bit.
 // The errors' bins and maximum do not depend on tau: quick settlement as in tao_check.hpp, exact arithmetic where
 // an estimate does not decide.
+// A workgroup that has met a tile with much open everywhere forms no further products and leaves all comparisons open: where that route
+// forms most bounds anyway they are work for nothing (us of the whole call, every claim at its bound, with all products / so:
+// 2048 x 12288 over 4096 1577 / 1425, the 3 x 3 convolution of 32 x 56 x 56 x 256 1378 / 1214, 8 x 8192 x 128 over 2048 428 / 364).
 #include <cmath>
 #include <type_traits>
 #include "tao_device.hpp"
@@ -63,7 +66,7 @@ struct ScreenArgs {
     int stream;                        // claims and outputs are more than the memory-side cache holds: streaming loads
     double eps_rel;
     float low, high, low_b, high_b, tiny;
-    unsigned int* unsettled;
+    OpenTile* open; unsigned open_m, open_n;                // records, and how many tiles they are down and across
     unsigned int* hist; unsigned int* coarse; BlockStats* stats;
 };
 
@@ -103,8 +106,8 @@ __global__ __launch_bounds__(WVM * WVN * 64, WVM * WVN * PER_CU / 4) void screen
     unsigned int* const hist = reinterpret_cast<unsigned int*>(lds);
     char* const stages = lds + kHistWords * 4;
     unsigned int& largest = hist[2041];                      // a lower bound of an error that occurs (its bits)
-    volatile unsigned int& void_seen = hist[2042];           // another workgroup / this one has met what it cannot settle
-    volatile unsigned int& open_seen = hist[2043];
+    volatile unsigned int& large_in = hist[2042];            // 1 + the last tile with an operand that is not screened
+    unsigned int& heavy = hist[2043];                        // wavefronts that had to leave whole blocks open
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave / WVN, wn = wave % WVN;
@@ -142,7 +145,9 @@ __global__ __launch_bounds__(WVM * WVN * 64, WVM * WVN * PER_CU / 4) void screen
     const unsigned xcd = blockIdx.x & 7u, per = gridDim.x >> 3;
     const unsigned t_end = (unsigned)((unsigned long long)p.ntiles * (xcd + 1) >> 3);
     const unsigned per_z = p.tiles_m * p.tiles_n;
-    bool dropped = false;
+    unsigned opened = 0;                                     // records that this wavefront was the first to write to
+    unsigned heavy_before = 0;
+    int groups = p.groups;                                   // 0: the products are not formed any more
     for (unsigned t = (unsigned)((unsigned long long)p.ntiles * xcd >> 3) + (blockIdx.x >> 3); t < t_end; t += per) {
         const unsigned z = t / per_z, b = t - z * per_z;
         const unsigned grp = b / (8 * p.tiles_n), in = b - grp * 8 * p.tiles_n;
@@ -150,9 +155,6 @@ __global__ __launch_bounds__(WVM * WVN * 64, WVM * WVN * PER_CU / 4) void screen
         const unsigned tx = in / deep, ty = grp * 8 + (in - tx * deep);
         const long m0 = (long)ty * TM, n0 = (long)tx * TN;
         const int rows_left = (int)min((long)TM, p.M - m0), cols_left = (int)min((long)TN, p.N - n0);
-        // (whether another workgroup has met an element that it could not settle: then nothing here counts any more)
-        unsigned gone = 0;
-        if (wave == 0) gone = __hip_atomic_load(p.unsettled, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 
         // claims and outputs of a strip; positions beyond the edge read the edge's elements.  The first strip's are requested before
         // the product: their latency passes under it.
@@ -302,9 +304,11 @@ __global__ __launch_bounds__(WVM * WVN * 64, WVM * WVN * PER_CU / 4) void screen
         };
 
         __syncthreads();                                     // the strips of the tile before have been read
-        if (void_seen | open_seen) { dropped = true; break; }
+        const unsigned heavy_now = __builtin_amdgcn_readfirstlane(newest(&heavy));
+        if (heavy_now - heavy_before == WAVES) groups = 0;
+        heavy_before = heavy_now;
         constexpr int COPIES = GPS * (NA + NW);
-        const int slabs = (p.groups + GPS - 1) / GPS;
+        const int slabs = (groups + GPS - 1) / GPS;
 #pragma unroll
         for (int i = 0; i + 1 < NST; ++i)
             if (i < slabs) request(i);
@@ -319,7 +323,7 @@ __global__ __launch_bounds__(WVM * WVN * 64, WVM * WVN * PER_CU / 4) void screen
             compute(stages + cur * STAGE);
 #pragma unroll
             for (int sub = 1; sub < GPS; ++sub)
-                if (g * GPS + sub < p.groups) compute(stages + cur * STAGE + sub * GROUP);
+                if (g * GPS + sub < groups) compute(stages + cur * STAGE + sub * GROUP);
             cur = cur == NST - 1 ? 0 : cur + 1;
         }
         if (CHAINS == 2) {
@@ -358,13 +362,17 @@ __global__ __launch_bounds__(WVM * WVN * 64, WVM * WVN * PER_CU / 4) void screen
             // (rows and columns beyond the edge repeat elements that exist)
             if (known) atomicMax(&largest, known);
         }
+        if (large) large_in = t + 1;
         __syncthreads();                                     // every wavefront is done with the stages
         known = max(known, newest(&largest));
+        const bool none_decided = groups == 0 || large_in == t + 1;      // (its first half of k is one wavefront's, the tile's concern all the same)
 
-        unsigned open = 0;                                   // elements that were not settled
+        using Places = typename std::conditional<(RM * STEPS * 4 > 32), unsigned long long, unsigned>::type;
+        Places open = 0;                                     // comparisons that were not decided: bit 4 (i STEPS + k) + e
+        const unsigned vio_before = vio;
         // Four elements of a lane: violations, and bins and maximum where the estimates decide (false: exact4).  Tests are made for the
         // four together first: a test per element costs as much as the estimate.
-        auto check4 = [&](const floatv4& c, const floatv4& r, const floatv4& s) __attribute__((always_inline)) -> bool {
+        auto check4 = [&](const floatv4& c, const floatv4& r, const floatv4& s, int step) __attribute__((always_inline)) -> bool {
             unsigned word[4], bits[4], edge[4], least[4];
             float over[4], den[4];
             int found = 0;
@@ -394,9 +402,9 @@ __global__ __launch_bounds__(WVM * WVN * 64, WVM * WVN * PER_CU / 4) void screen
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     const float d = fabsf(c[e] - r[e]);
-                    const bool above = d > fmaf(s[e], p.high, bh[e]);
+                    const bool sure = s[e] >= p.tiny, above = (d != d) | ((d > fmaf(s[e], p.high, bh[e])) & sure);
                     vio += above;
-                    open += !((d == 0.f) | (((d <= fmaf(s[e], p.low, bl[e])) | above) & (s[e] >= p.tiny)));
+                    open |= (Places)!(above | (d == 0.f) | ((d <= fmaf(s[e], p.low, bl[e])) & sure)) << (4 * step + e);
                 }
             }
             if (ok) {
@@ -453,7 +461,7 @@ __global__ __launch_bounds__(WVM * WVN * 64, WVM * WVN * PER_CU / 4) void screen
                         s[e] = out ? p.tiny : s[e];
                     }
                 }
-                if (!check4(cv[k], rv[k], s)) again |= 1u << (i * STEPS + k);
+                if (!check4(cv[k], rv[k], s, i * STEPS + k)) again |= 1u << (i * STEPS + k);
                 if (i + 1 < RM) fetch(i + 1, k);             // the next strip's, as soon as the registers are free
             }
         }
@@ -462,18 +470,39 @@ __global__ __launch_bounds__(WVM * WVN * 64, WVM * WVN * PER_CU / 4) void screen
             again &= again - 1;
             exact4(at / STEPS, at % STEPS);
         }
-        if (__any(open != 0 || large) && lane == 0) open_seen = 1;
-        if (wave == 0 && lane == 0 && gone) void_seen = 1;
+        // What was left open goes to the record of the 128 x 128 tile: a few comparisons by their places; many, or all of them, as the
+        // wavefront's blocks, in which it then counts no violations.
+        if (__any(open != 0) || none_decided) {
+            OpenTile* const rec = p.open + ((size_t)z * p.open_m + (unsigned)(m0 >> 7)) * p.open_n + (unsigned)(n0 >> 7);
+            const unsigned r0 = ((unsigned)m0 & 127u) + srow, c0 = ((unsigned)n0 & 127u) + scol;
+            const unsigned mine = (unsigned)__popcll((unsigned long long)open), upto = (unsigned)wave_scan(mine), all = wave_sum(mine);
+            unsigned was = 0;
+            bool listed = !none_decided && all <= (unsigned)kOpenList;
+            if (listed) {
+                if (lane == 0) was = atomicAdd(&rec->state, all << 16);
+                was = __builtin_amdgcn_readfirstlane(was);
+                listed = (was >> 16) + all <= (unsigned)kOpenList;
+                unsigned at = (was >> 16) + upto - mine;
+                for (Places left = open; left && at < (unsigned)kOpenList; left &= left - 1, ++at) {
+                    const int bit = __ffsll((unsigned long long)left) - 1, step = bit >> 2;
+                    const unsigned row = r0 + (unsigned)(step / STEPS * 32 + lrow + step % STEPS * RPI), col = c0 + (unsigned)(lcol + (bit & 3));
+                    rec->at[at] = listed ? row << 7 | col : kNoPlace;
+                }
+                opened += was == 0;
+            }
+            if (!listed) {
+                const unsigned before = was;
+                constexpr unsigned across = (1u << RN) - 1u;
+                const unsigned blocks = (RM == 2 ? across | across << 4 : across) << (r0 / 32 * 4 + c0 / 32);
+                if (lane == 0) { was = atomicOr(&rec->state, blocks); atomicAdd(&heavy, 1u); }
+                was = __builtin_amdgcn_readfirstlane(was);
+                opened += before == 0 && was == 0;
+                vio = vio_before;
+            }
+        }
     }
     // this workgroup's counts to one of the partial results (integer atomics: the sums do not depend on the order)
     __syncthreads();
-    if (open_seen) {
-        // (once per workgroup, and not where it is known: stores to one word are served one after the other, 60 us of them from 400 workgroups)
-        if (tid == 0 && !void_seen && __hip_atomic_load(p.unsettled, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0)
-            __hip_atomic_store(p.unsettled, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        return;
-    }
-    if (dropped || void_seen) return;
     zeros = wave_sum(zeros) + all_zeros;
     vio = wave_sum(vio); nans = wave_sum(nans); max_bits = wave_max(max_bits);
     const unsigned slot = blockIdx.x % (unsigned)kScreenSlots;
@@ -487,6 +516,7 @@ __global__ __launch_bounds__(WVM * WVN * 64, WVM * WVN * PER_CU / 4) void screen
         if (vio) atomicAdd(&st->violations, (unsigned long long)vio);
         if (nans) atomicAdd(&st->nans, (unsigned long long)nans);
         if (max_bits) atomicMax(&st->max_bits, max_bits);
+        if (opened) atomicAdd(&st->flag, opened);
     }
     __syncthreads();
     // (eight bins a thread, eight threads a group of 64)
@@ -528,7 +558,7 @@ int launch_config(ScreenArgs& p, long batch, hipStream_t st) {
 }  // namespace
 
 int launch_screen(const ScreenOperand& A, const ScreenOperand& W, const float* bias, long M, long N, long K, long batch,
-                  double cg, const ScreenCheck& chk, const CheckWorkspace& ws, hipStream_t st) {
+                  double cg, const ScreenCheck& chk, const CheckWorkspace& ws, OpenTile* open, hipStream_t st) {
     const long groups = (K + SBK - 1) / SBK, blocksA = (M + 127) / 128, blocksW = (N + 127) / 128;
     ScreenArgs p = {};
     const bool rows = A.ld != 0, pixels = A.pixels != nullptr;
@@ -548,7 +578,7 @@ int launch_screen(const ScreenOperand& A, const ScreenOperand& W, const float* b
     p.low = (float)(a * lim.lower * (1.0 - 0x1p-14)); p.high = (float)(a * lim.upper * (1.0 + 0x1p-14));
     p.low_b = (float)(a * (1.0 - 0x1p-14)); p.high_b = (float)(a * (1.0 + 0x1p-14));
     p.tiny = (float)(groups * SBK) * kTinyPerStep;
-    p.unsettled = &ws.stats[kOpenFlag].flag;
+    p.open = open; p.open_m = (unsigned)blocksA; p.open_n = (unsigned)blocksW;
     p.hist = ws.hist; p.coarse = ws.coarse; p.stats = ws.stats;
     if (chk.ldy >= kScreenMaxLd) return TAO_ERR_SHAPE;
     const long n = device_cus();

@@ -24,20 +24,31 @@ constexpr long kScreenMaxLd = 1L << 22;      // rows of claims and outputs, and 
 
 struct ScreenCheck { const float* claimed; const float* ref; long ldy, strideY; double alpha, eps_rel; };
 
-// A screened check keeps few partial results (they are cleared before and added up after each call): the screen adds to the
-// first kScreenSlots, the exact route behind it to the next kSettleSlots; these and all counters are zero before the screen.  The
-// words of the counters that no check writes hold the flag that the screen could not settle every element and the exact
-// route's counts of finished tiles and parts.
-constexpr int kScreenSlots = 64, kSettleSlots = 32;     // (the screen's: 32 cost perturbed claims of 1111 x 3001 2 us, 128 honest ones 0.4)
-constexpr int kOpenFlag = kMaxCheckBlocks - 1, kDoneFlag = kMaxCheckBlocks - 2, kMaxTileFlags = kMaxCheckBlocks - 2;
-inline CheckWorkspace settle_partials(const CheckWorkspace& w) {
-    return {w.hist + (size_t)kScreenSlots * kBins, w.coarse + (size_t)kScreenSlots * kGroups, w.stats + kScreenSlots};
+// A screened check keeps few partial results (they are cleared before and added up after each call): the first kScreenSlots, to which
+// the screen adds, and the exact route its violations.  The words of the counters that no check writes hold, one for each of them, in how
+// many tiles the screen left comparisons open, and how many of these the exact route has finished.
+constexpr int kScreenSlots = 64;              // (32 cost perturbed claims of 1111 x 3001 2 us, 128 honest ones 0.4)
+constexpr int kDoneFlag = kMaxCheckBlocks - 1;
+static_assert(kScreenSlots == kWave, "a lane for each");
+// The comparisons that the screen left open in a tile of the exact route (128 x 128 outputs; tiles row by row, batch entries one after
+// the other).  All zero before the screen; zero after it where none is open.
+constexpr int kOpenTile = 128, kOpenList = 14;
+constexpr unsigned kNoPlace = ~0u;
+struct OpenTile {
+    unsigned state;            // bit 4 r + c: every comparison of block (r, c), 32 x 32; from bit 16 on: how many places were asked for
+    unsigned arrived;          // parts of the reduction that the exact route has finished
+    unsigned at[kOpenList];    // places: 128 row + column, or kNoPlace
+};
+static_assert(sizeof(OpenTile) == 64, "cleared in 16-byte words");
+inline size_t open_tiles_of(long M, long N, long batch) {
+    return (size_t)((M + kOpenTile - 1) / kOpenTile) * (size_t)((N + kOpenTile - 1) / kOpenTile) * (size_t)batch;
 }
-// What a launch before a check clears, in 16-byte words: of `slots` partial results the histograms and coarse counts, and all counters.
-struct ClearJob { void* at[3]; long words[3]; };
-inline ClearJob clear_job(const CheckWorkspace& w, int slots) {
-    return {{w.hist, w.coarse, w.stats},
-            {(long)slots * kBins / 4, (long)slots * kGroups / 4, (long)(kMaxCheckBlocks * sizeof(BlockStats) / 16)}};
+// What a launch before a check clears, in 16-byte words: of `slots` partial results the histograms and coarse counts, all counters, and
+// a screened check's records.
+struct ClearJob { void* at[4]; long words[4]; };
+inline ClearJob clear_job(const CheckWorkspace& w, int slots, OpenTile* open = nullptr, size_t tiles = 0) {
+    return {{w.hist, w.coarse, w.stats, open},
+            {(long)slots * kBins / 4, (long)slots * kGroups / 4, (long)(kMaxCheckBlocks * sizeof(BlockStats) / 16), (long)(tiles * sizeof(OpenTile) / 16)}};
 }
 static_assert(kMaxCheckBlocks * sizeof(BlockStats) % 16 == 0, "cleared in 16-byte words");
 
@@ -57,6 +68,6 @@ inline bool screen_usable(long K, double u, double cg, double alpha, double uflo
            uflow <= cg * (double)K * 0x1p-100;
 }
 int launch_screen(const ScreenOperand& A, const ScreenOperand& W, const float* bias, long M, long N, long K, long batch,
-                  double cg, const ScreenCheck& chk, const CheckWorkspace& ws, hipStream_t st);
+                  double cg, const ScreenCheck& chk, const CheckWorkspace& ws, OpenTile* open, hipStream_t st);
 
 }  // namespace tao

@@ -40,7 +40,7 @@
 //
 // A check needs only the comparisons d <= alpha tau.  Where the caller does not want tau, one BF16 product
 // (linear_screen.hip) decides them first, and the kernels of this file form the bound only if it left one open
-// (absgemm_settle*, launched behind it in either case; screened() holds the rule).
+// (absgemm_settle*, launched behind it in either case, for the tiles that hold open ones; screened() holds the rule).
 #include <algorithm>
 #include <cstring>
 #include <type_traits>
@@ -134,7 +134,7 @@ struct SplitOperands {
 };
 __device__ __forceinline__ void clear_words(const ClearJob& c, long i0, long step) {
 #pragma unroll
-    for (int j = 0; j < 3; ++j)
+    for (int j = 0; j < 4; ++j)
         for (long i = i0; i < c.words[j]; i += step) static_cast<uintx4*>(c.at[j])[i] = uintx4{0, 0, 0, 0};
 }
 typedef float floatx4u __attribute__((ext_vector_type(4), aligned(4)));          // (16-byte loads need no more than 4-byte alignment)
@@ -274,35 +274,45 @@ __device__ __forceinline__ const float* patch_values(const SplitArgs& p, int ih0
     inside = (unsigned)(ih0 + dr) < (unsigned)p.cH && (unsigned)(iw0 + ds) < (unsigned)p.cW;
     return p.Af + (inside ? base + ((long)dr * p.cW + ds) * p.cC + c0 : 0L) + unit * 8;
 }
+// One output's operands: where they lie, and the products of unit `unit` of group g added to s.
+template <bool AREG, bool CONV>
+struct OutputOperands {
+    long row, col, blocksA, blocksW, base = 0;
+    const unsigned short* w; const unsigned short* a; const float* af;
+    int ih0 = 0, iw0 = 0;
+    __device__ __forceinline__ OutputOperands(const SplitArgs& p, long row_, long col_, unsigned z)
+        : row(row_), col(col_), blocksA((p.M + STILE - 1) / STILE), blocksW((p.N + STILE - 1) / STILE),
+          w(p.W3 + (long)z * p.batchW3), a(p.A3 + (long)z * p.batchA3), af(p.Af + (long)z * p.strideA + row_ * p.lda) {
+        if (CONV) patch_origin(p, (unsigned)row, ih0, iw0, base);
+    }
+    __device__ __forceinline__ double add(const SplitArgs& p, long g, int unit, double s) const {
+        double av[8], wv[8];
+        if (AREG) {
+            bool inside = true;
+            const float* src = CONV ? patch_values(p, ih0, iw0, base, g, unit, inside) : af + g * SBK + unit * 8;
+            float v[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) v[j] = inside ? src[j] : 0.f;
+            uintx4 H, Mi, L;
+            split_pack8(v, H, Mi, L);
+            piece_sums(H, Mi, L, av);
+        } else {
+            image_values(a, blocksA, row, g, unit, av);
+        }
+        image_values(w, blocksW, col, g, unit, wv);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) s = fma(av[j], wv[j], s);
+        return s;
+    }
+};
 template <bool AREG, bool CONV>
 __device__ __forceinline__ double sum_in_binary64(const SplitArgs& p, long row, long col, unsigned z, long g0, long ngroup) {
-    const long blocksA = (p.M + STILE - 1) / STILE, blocksW = (p.N + STILE - 1) / STILE;
-    const unsigned short* w = p.W3 + (long)z * p.batchW3;
-    int ih0 = 0, iw0 = 0; long base = 0;
-    if (CONV) patch_origin(p, (unsigned)row, ih0, iw0, base);
+    const OutputOperands<AREG, CONV> operands(p, row, col, z);
     double s = 0.0;
 #pragma unroll 1
     for (long g = g0; g < g0 + ngroup; ++g) {
 #pragma unroll 1
-        for (int unit = 0; unit < 4; ++unit) {
-            double av[8], wv[8];
-            if (AREG) {
-                bool inside = true;
-                const float* src = CONV ? patch_values(p, ih0, iw0, base, g, unit, inside)
-                                        : p.Af + (long)z * p.strideA + row * p.lda + g * SBK + unit * 8;
-                float v[8];
-#pragma unroll
-                for (int j = 0; j < 8; ++j) v[j] = inside ? src[j] : 0.f;
-                uintx4 H, Mi, L;
-                split_pack8(v, H, Mi, L);
-                piece_sums(H, Mi, L, av);
-            } else {
-                image_values(p.A3 + (long)z * p.batchA3, blocksA, row, g, unit, av);
-            }
-            image_values(w, blocksW, col, g, unit, wv);
-#pragma unroll
-            for (int j = 0; j < 8; ++j) s = fma(av[j], wv[j], s);
-        }
+        for (int unit = 0; unit < 4; ++unit) s = operands.add(p, g, unit, s);
         if (s != s) break;
     }
     return s;
@@ -360,15 +370,25 @@ __device__ __forceinline__ void flush_counters(const SplitArgs& p, const ThreadA
     }
 }
 
+template <bool SHARED>
+__device__ __forceinline__ void store_sum(double* at, double s) {
+    if (SHARED) __hip_atomic_store(at, s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    else *at = s;
+}
+
+// The work of slot `wg` of `nwg` (false: the slot has no tile), by all threads of a workgroup.  lds: the stages; chk: the
+// histogram (CHECK) or what is to be compared (OPEN).
 // CHECK: the epilogue also runs the leaf check of Sec. 5.4 and the relative-error profile of Sec. 5.3
 // on every bound it has just formed (the binary32 value the plain instantiation would store), against
 // `claimed` and `ref`, with a 2048-bin histogram in the 16 KB of LDS the three stages leave free; tau
-// itself is stored only if p.tau is not NULL.  Workgroups add their counts to one of kMaxCheckBlocks
+// itself is stored only if p.tau is not NULL.  Workgroups add their counts to one of p.check_slots
 // partial results (integer atomics: the sums do not depend on the order), which profile_reduce
 // finishes as it does for the streaming check.
+// OPEN (with CHECK): behind a screen; only the comparisons whose bits are set in `chk` (a word per 32 columns of a row of the tile) are
+// made, and of the profile only violations are counted.
 // PARTIAL: launches with fewer tiles than compute units cut the reduction into parts; a workgroup
-// then leaves the binary64 sums of its part in the workspace and split_combine adds the parts and
-// forms (and, if asked, checks) the bound.
+// then leaves the binary64 sums of its part in the workspace, and split_combine -- behind a screen the tile's last
+// workgroup (SHARED: the sums are for another workgroup of the same launch) -- adds the parts, forms the bound and, if asked, checks it.
 // WALK: the plain bound as the host launches it.  A workgroup takes the slots blockIdx.x,
 // + gridDim.x, ... and its pipeline of slabs runs on across the tile boundaries: with a workgroup
 // per slot that is one tile, with a workgroup per compute unit (short reductions) a walk over many.
@@ -381,18 +401,11 @@ __device__ __forceinline__ void flush_counters(const SplitArgs& p, const ThreadA
 // of 32), 16-byte aligned rows: the host checks all of it.
 // CONV (with AREG): the A operand is the implicit patch matrix of a convolution, gathered from the
 // channels-last input while loading; taps in the zero padding contribute zeros.
-template <bool SHARED>
-__device__ __forceinline__ void store_sum(double* at, double s) {
-    if (SHARED) __hip_atomic_store(at, s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    else *at = s;
-}
-
-// The work of slot `wg` of `nwg` (false: the slot has no tile).  lds: the stages; chk_hist: see below.
-// SHARED (with PARTIAL): the sums are for another workgroup of the same launch.
-template <bool CHECK, bool PARTIAL, bool WALK, bool AREG, bool CONV, bool SHARED = false>
-__device__ __forceinline__ bool absgemm_split_slot(const SplitArgs& p, unsigned wg, unsigned nwg, char* lds, unsigned int* chk_hist) {
+template <bool CHECK, bool PARTIAL, bool WALK, bool AREG, bool CONV, bool SHARED = false, bool OPEN = false>
+__device__ __forceinline__ bool absgemm_split_slot(const SplitArgs& p, unsigned wg, unsigned nwg, char* lds, unsigned int* chk) {
+    static_assert(CHECK || !OPEN, "a check of what is open");
     static_assert(!CONV || AREG, "the patch matrix exists only as a gather");
-    static_assert(!(CHECK && PARTIAL), "the parts are checked by split_combine");
+    static_assert(!(CHECK && PARTIAL), "the parts are checked when they are added");
     static_assert(!(WALK && (CHECK || PARTIAL)), "only the plain bound walks tiles");
     static_assert(!(AREG && WALK), "the in-load split keeps one tile per workgroup");
     // CHECK: four copies of the 2048-bin histogram with 16-bit counters (a tile has 16384 elements, so
@@ -410,7 +423,7 @@ __device__ __forceinline__ bool absgemm_split_slot(const SplitArgs& p, unsigned 
     // cut into eight patches (ph rows x pw columns, npx of them side by side) and XCD x takes patch x,
     // so its tiles share ph + pw blocks (4 + 8 for a full super-tile).  Slots that fall beyond the
     // output's edge belong to no tile.  (A walk's stride is a multiple of 8, so a workgroup stays
-    // with its XCD's patches.)  CHECK and PARTIAL launches have one workgroup per slot (and part).
+    // with its XCD's patches.)  CHECK and PARTIAL calls take one slot (and part).
     const long part = PARTIAL ? wg / p.ntiles : 0;
     unsigned m0 = 0, n0 = 0, z = 0;                          // first row and column of the tile, batch entry
     auto locate = [&](unsigned t, unsigned& tm0, unsigned& tn0, unsigned& tz) __attribute__((always_inline)) -> bool {
@@ -424,8 +437,8 @@ __device__ __forceinline__ bool absgemm_split_slot(const SplitArgs& p, unsigned 
     };
     unsigned t = next_tile(PARTIAL ? wg % p.ntiles : wg, m0, n0, z);
     if (t >= p.ntiles) return false;                             // whole workgroup
-    if (CHECK) {
-        for (int i = threadIdx.x; i < kBins * 2; i += kSplitThreads) chk_hist[i] = 0;
+    if (CHECK && !OPEN) {
+        for (int i = threadIdx.x; i < kBins * 2; i += kSplitThreads) chk[i] = 0;
         __syncthreads();
     }
     // groups [g0, g0 + ngroup) of the reduction
@@ -732,9 +745,17 @@ __device__ __forceinline__ bool absgemm_split_slot(const SplitArgs& p, unsigned 
             const long col = (long)ne + ecol + tj * 32;
             const double ab = fabs((double)bias_c[tj]);
             const double off_pos = bound_offset(p, p.si, ab), off_zero = bound_offset(p, p.si0, ab);
+            const unsigned int* asked = chk + erow * (STILE / 32) + wn * 2 + tj;
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
                 const long row = (long)me + erow + 8 * (v >> 2) + (v & 3);
+                if (OPEN) {
+                    if (row < p.M && col < p.N && (asked[(8 * (v >> 2) + (v & 3)) * (STILE / 32)] >> r32 & 1u)) {
+                        const float t32 = up32(bound_of_sum(p, S[tj][v], off_pos, off_zero));
+                        acc.violations += !(fabs((double)pc[tj][v] - (double)pr[tj][v]) <= p.alpha * (double)t32);
+                    }
+                    continue;
+                }
                 if (PARTIAL) {
                     if (row < p.M && col < p.N) store_sum<SHARED>(p.partial + ((part * nbatch + z) * p.M + row) * p.N + col, S[tj][v]);
                     continue;
@@ -745,14 +766,14 @@ __device__ __forceinline__ bool absgemm_split_slot(const SplitArgs& p, unsigned 
                         T[row * p.ldt + col] = t32;
                     } else {
                         if (T) T[row * p.ldt + col] = t32;
-                        check_one_packed(pc[tj][v], pr[tj][v], t32, p.alpha, p.eps_rel, chk_hist, lane & 3, acc);
+                        check_one_packed(pc[tj][v], pr[tj][v], t32, p.alpha, p.eps_rel, chk, lane & 3, acc);
                     }
                 }
             }
         }
-        if (CHECK) {
+        if (CHECK && !OPEN) {
             __syncthreads();
-            flush_packed(p, chk_hist);                       // (a checking workgroup has one tile, so the histogram is not cleared again)
+            flush_packed(p, chk);
         }
         if (!more) break;
         // Everything this tile has in flight ends here (the next tile's first two slabs were requested
@@ -808,60 +829,29 @@ __global__ __launch_bounds__(kSplitThreads) void absgemm_split(SplitArgs p) {
 }
 
 // ---- behind a screen (linear_screen.hip) -------------------------------------------------------
-// One launch that settles the check: where the screen has settled every element, the first workgroups form the profile of its
-// partial results and nothing else happens; otherwise the bound is formed and checked by the code above, and the
-// workgroup that finishes the last tile (counted in the workspace; nobody waits) forms the profile.
+// One launch that settles the check.  Its first workgroups form the profile of the screen's partial results; where no comparison is open
+// nothing else happens.  The tiles with open ones are taken one by one: places that the real sum decides are done with it, for the others the
+// bound is formed by the code above.  What is found there are violations alone; the workgroup that finishes the last such tile (counted in the
+// workspace; nobody waits) adds them up.
 struct SettleArgs {
-    CheckWorkspace check;              // the whole of it (linear_screen.hpp)
-    unsigned tiles;
+    CheckWorkspace check;
+    OpenTile* open;
     ProfileSize size;
     tao_profile* out;
 };
-// true: settled by the screen, nothing is left to do
-__device__ __forceinline__ bool settled_by_screen(const SettleArgs& r, char* lds) {
-    const unsigned open = r.check.stats[kOpenFlag].flag;
-    if (blockIdx.x >= (unsigned)kGroups) return open == 0;
-    ProfileGroup<kSplitThreads, kScreenSlots> group(r.check, kScreenSlots, blockIdx.x);      // (on its way before the flag is known)
-    if (open != 0) return false;
-    group.finish(r.size, r.out, reinterpret_cast<unsigned long long*>(lds));
-    return true;
+__device__ __forceinline__ size_t open_index(const SplitArgs& p, unsigned m0, unsigned n0, unsigned z) {
+    static_assert(STILE == kOpenTile, "a record per tile");
+    return ((size_t)z * p.tiles_m + m0 / STILE) * p.tiles_n + n0 / STILE;
 }
-// The profile of all partial results by one workgroup (profile_group takes one per 64 bins): four bins a thread.
-__device__ __forceinline__ void profile_alone(const CheckWorkspace& w, int nblocks, const ProfileSize& size, tao_profile* out, unsigned long long* smem) {
-    static_assert(kSplitThreads * 4 == kBins, "four bins a thread");
-    constexpr int WAVES = kSplitThreads / kWave;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    unsigned long long c[4] = {0, 0, 0, 0}, v = 0, q = 0; unsigned m = 0;
-    for (int k = 0; k < nblocks; ++k) {
-        const uintx4 h = *reinterpret_cast<const uintx4*>(w.hist + (size_t)k * kBins + tid * 4);
-#pragma unroll
-        for (int j = 0; j < 4; ++j) c[j] += h[j];
-    }
-    for (int k = tid; k < nblocks; k += kSplitThreads) { v += w.stats[k].violations; q += w.stats[k].nans; m = max(m, w.stats[k].max_bits); }
-    const unsigned long long mine = c[0] + c[1] + c[2] + c[3];
-    unsigned long long upto = wave_scan(mine);               // elements in this thread's bins and all below, within the wavefront first
-    v = wave_sum(v); q = wave_sum(q); m = wave_max(m);
-    if (lane == kWave - 1) { smem[wave] = upto; smem[WAVES + wave] = v; smem[2 * WAVES + wave] = q; smem[3 * WAVES + wave] = m; }
-    __syncthreads();
-    for (int k = 0; k < wave; ++k) upto += smem[k];
-    unsigned long long below = upto - mine;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const unsigned bin = tid * 4 + j;
-        out->hist[bin] = c[j];
-#pragma unroll
-        for (int i = 0; i < 3; ++i) {
-            const unsigned long long r = size.ranks.at[i];
-            if (below < r && r <= below + c[j]) { (&out->p50_bin)[i] = bin; (&out->p50)[i] = bin_upper_edge(bin); }
-        }
-        below += c[j];
-    }
-    if (tid == 0) {
-        v = q = 0; m = 0;
-        for (int k = 0; k < WAVES; ++k) { v += smem[WAVES + k]; q += smem[2 * WAVES + k]; m = max(m, (unsigned)smem[3 * WAVES + k]); }
-        out->n = size.n; out->violations = v; out->nan_count = q;
-        out->max_rel = __uint_as_float(m); out->accept = v == 0 ? 1u : 0u; out->pad_ = 0;
-    }
+// How many tiles have open comparisons; the profile but for what their violations change.
+__device__ __forceinline__ unsigned screened_profile(const SettleArgs& r, char* lds) {
+    const BlockStats& mine = r.check.stats[threadIdx.x & (kWave - 1)];
+    if (blockIdx.x >= (unsigned)kGroups) return wave_sum(mine.flag);
+    ProfileGroup<kSplitThreads, kScreenSlots> group(r.check, kScreenSlots, blockIdx.x);      // (on its way before the counts are known)
+    const unsigned tiles = wave_sum(mine.flag);
+    group.finish(r.size, r.out, reinterpret_cast<unsigned long long*>(lds), tiles == 0);
+    if (tiles) __syncthreads();                              // (its sums have been read)
+    return tiles;
 }
 // What workgroups exchange within a launch goes past the XCDs' caches (atomics and write-through stores of agent scope), so a count that
 // follows its completion publishes it; a release fence would write back an L2 for every workgroup (100 us of them at 256).
@@ -869,75 +859,148 @@ __device__ __forceinline__ unsigned publish(unsigned int* count, unsigned add, u
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
     __builtin_amdgcn_s_waitcnt(0x0F70);                      // vmcnt(0): this wavefront's are complete
     __syncthreads();
-    if (threadIdx.x == 0) word = add ? __hip_atomic_fetch_add(count, add, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + add : 0;
+    if (threadIdx.x == 0) word = __hip_atomic_fetch_add(count, add, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + add;
     __syncthreads();
     return word;
 }
-// Counts `done` more tiles, whose results this workgroup has added; the workgroup that completes the count forms the profile.
-__device__ __forceinline__ void tiles_done(const SplitArgs& p, const SettleArgs& r, unsigned done, char* lds, unsigned int& word) {
-    if (publish(&r.check.stats[kDoneFlag].flag, done, word) != r.tiles) return;
+// Counts `done` more tiles, whose violations this workgroup has added; the workgroup that completes the count adds all of them up.
+__device__ __forceinline__ void tiles_done(const SettleArgs& r, unsigned tiles, unsigned done, unsigned int& word) {
+    if (publish(&r.check.stats[kDoneFlag].flag, done, word) != tiles) return;
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-    profile_alone(CheckWorkspace{p.ws_hist, p.ws_coarse, p.ws_stats}, (int)p.check_slots, r.size, r.out, reinterpret_cast<unsigned long long*>(lds));
+    if (threadIdx.x < kWave) {
+        const unsigned long long v = wave_sum(__hip_atomic_load(&r.check.stats[threadIdx.x].violations, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+        if (threadIdx.x == 0) { r.out->violations = v; r.out->accept = v == 0 ? 1u : 0u; }
+    }
 }
-// On images a workgroup per compute unit walks the slots (where the screen has settled everything, thousands would only be given LDS
-// and leave); the in-load forms have no registers for that (39 spilled instead of 12) and take a workgroup per slot.
+// A comparison by the real sum of its products, by a wavefront: 0 or 1 violations, or -1 where the sum does not decide.  The sum of
+// binary64 products is exact but for 2^-40 of it; the one that the bound is formed of lies within 11.4u below and 3.3u above (and 8u more
+// where operands below 2^-110 were raised), so the bound lies between those of the sum's limits 2^-20 off, as both are formed alike.
+template <bool AREG, bool CONV>
+__device__ __forceinline__ int decide_by_sum(const SplitArgs& p, unsigned row, unsigned col, unsigned z) {
+    const OutputOperands<AREG, CONV> operands(p, row, col, z);
+    const int units = (int)(p.Kp / 8), lane = threadIdx.x & 63;
+    double s = 0.0;
+    for (int u = lane; u < units; u += kWave) s = operands.add(p, u >> 2, u & 3, s);
+    s = wave_sum(s);
+    if (!(s >= (double)p.Kp * 0x1p-80 && s <= 0x1p120)) return -1;
+    const double ab = p.bias ? fabs((double)p.bias[col]) : 0.0, off = bound_offset(p, p.si, ab);
+    const long at = (long)z * p.strideY + (long)row * p.ldy + col;
+    const double d = fabs((double)p.claimed[at] - (double)p.ref[at]);
+    if (d <= p.alpha * (double)up32(bound_of_sum(p, s * (1.0 - 0x1p-20), off, off))) return 0;
+    if (!(d <= p.alpha * (double)up32(bound_of_sum(p, s * (1.0 + 0x1p-20), off, off)))) return 1;
+    return -1;
+}
+// The open comparisons of a tile: `todo` receives those that take the bound itself, counts[0] the violations among the others.
+// Returns whether any are left.
+struct OpenLds { unsigned int todo[STILE * STILE / 32], counts[2], word; };
+template <bool AREG, bool CONV>
+__device__ __forceinline__ bool sift_open(const SplitArgs& p, const OpenTile& rec, unsigned state, unsigned m0, unsigned n0, unsigned z, OpenLds& o) {
+    static_assert(STILE * STILE / 32 == kSplitThreads, "a word a thread");
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const unsigned blocks = state & 0xffffu;
+    __syncthreads();                                         // (the tile before has read its words)
+    o.todo[tid] = blocks >> ((tid >> 7) * 4 + (tid & 3)) & 1u ? ~0u : 0u;
+    if (tid == 0) { o.counts[0] = 0; o.counts[1] = blocks; }
+    __syncthreads();
+    const int n = min((int)(state >> 16), kOpenList);
+    if (n == 0) return true;
+    for (int e = wave; e < n; e += kSplitThreads / kWave) {
+        const unsigned at = rec.at[e];
+        if (at == kNoPlace) continue;
+        // (with whole blocks the bound is formed in any case)
+        const int v = blocks ? -1 : decide_by_sum<AREG, CONV>(p, m0 + (at >> 7), n0 + (at & 127u), z);
+        if (lane == 0 && v > 0) atomicAdd(&o.counts[0], 1u);
+        if (lane == 0 && v < 0) { atomicOr(&o.todo[at >> 5], 1u << (at & 31u)); o.counts[1] = 1; }
+    }
+    __syncthreads();
+    return o.counts[1] != 0;
+}
+__device__ __forceinline__ void add_violations(const SplitArgs& p, unsigned n) {
+    if (threadIdx.x == 0 && n) atomicAdd(&p.ws_stats[blockIdx.x % p.check_slots].violations, (unsigned long long)n);
+}
+// On images a workgroup per compute unit walks the slots (where nothing is open, thousands would only be given LDS and leave); the
+// in-load forms have no registers for that (39 spilled instead of 12) and take a workgroup per slot.
 template <bool AREG, bool CONV>
 __global__ __launch_bounds__(kSplitThreads) void absgemm_settle(SplitArgs p, SettleArgs r) {
     extern __shared__ __attribute__((aligned(16))) char lds[];
-    __shared__ unsigned int chk_hist[kBins * 2];
-    if (settled_by_screen(r, lds)) return;
-    unsigned done = 0;
+    __shared__ OpenLds o;
+    const unsigned tiles = screened_profile(r, lds);
+    if (tiles == 0) return;
+    unsigned done = 0, m0, n0, z;
     if (AREG) {
-        if (blockIdx.x < p.ntiles) done = absgemm_split_slot<true, false, false, AREG, CONV>(p, blockIdx.x, gridDim.x, lds, chk_hist);
+        if (blockIdx.x >= p.ntiles || !locate_tile(p, blockIdx.x, m0, n0, z)) return;
+        const OpenTile& rec = r.open[open_index(p, m0, n0, z)];
+        const unsigned state = rec.state;
+        if (state == 0) return;
+        if (sift_open<AREG, CONV>(p, rec, state, m0, n0, z, o)) absgemm_split_slot<true, false, false, AREG, CONV, false, true>(p, blockIdx.x, gridDim.x, lds, o.todo);
+        add_violations(p, o.counts[0]);
+        done = 1;
     } else {
-        for (unsigned wg = blockIdx.x; wg < p.ntiles; wg += gridDim.x) {
-            __syncthreads();                                 // the tile before has read its histogram
-            // (the arguments are read anew for each tile: kept in registers through it they cost the loop of the product some)
-            typedef const SplitArgs __attribute__((address_space(4)))* ArgsPtr;
-            ArgsPtr q = (ArgsPtr)__builtin_amdgcn_kernarg_segment_ptr();
-            asm volatile("" : "+s"(q));
-            done += absgemm_split_slot<true, false, false, AREG, CONV>(*(const SplitArgs*)q, wg, gridDim.x, lds, chk_hist);
-            __builtin_amdgcn_s_waitcnt(0x0F70);              // vmcnt(0): nothing of it counts in the next tile's waits
+        // (64 slots' records at a time, one a lane; all wavefronts see the same)
+        for (unsigned first = blockIdx.x; first < p.ntiles; first += gridDim.x * kWave) {
+            const unsigned slot = first + (threadIdx.x & 63) * gridDim.x;
+            const unsigned state = slot < p.ntiles && locate_tile(p, slot, m0, n0, z) ? r.open[open_index(p, m0, n0, z)].state : 0u;
+            for (unsigned long long left = __ballot(state != 0); left; left &= left - 1) {
+                // (the arguments are read anew for each tile: kept in registers through it they cost the loop of the product some)
+                typedef const SplitArgs __attribute__((address_space(4)))* ArgsPtr;
+                ArgsPtr q = (ArgsPtr)__builtin_amdgcn_kernarg_segment_ptr();
+                asm volatile("" : "+s"(q));
+                const SplitArgs& a = *(const SplitArgs*)q;
+                const int at = __ffsll(left) - 1;
+                const unsigned wg = first + (unsigned)at * gridDim.x;
+                locate_tile(a, wg, m0, n0, z);
+                if (sift_open<AREG, CONV>(a, r.open[open_index(a, m0, n0, z)], (unsigned)__builtin_amdgcn_readlane((int)state, at), m0, n0, z, o)) {
+                    absgemm_split_slot<true, false, false, AREG, CONV, false, true>(a, wg, gridDim.x, lds, o.todo);
+                    __builtin_amdgcn_s_waitcnt(0x0F70);      // vmcnt(0): nothing of it counts in the next tile's waits
+                }
+                add_violations(a, o.counts[0]);
+                ++done;
+            }
         }
     }
-    tiles_done(p, r, done, lds, chk_hist[0]);
+    if (done) tiles_done(r, tiles, done, o.word);
 }
-// The reduction in parts: a workgroup leaves its part's sums in the workspace, and the one that brings a tile's last part adds
-// them in split_combine's order, forms the bound and checks it.
+// The reduction in parts: every workgroup of an open tile sifts its places (all come to the same), leaves its part's sums in the workspace if any
+// are left, and the one that brings the tile's last part adds them in split_combine's order and compares.
 template <bool AREG>
 __global__ __launch_bounds__(kSplitThreads) void absgemm_settle_parts(SplitArgs p, SettleArgs r) {
     extern __shared__ __attribute__((aligned(16))) char lds[];
-    __shared__ unsigned int chk_hist[kBins * 2];
-    if (settled_by_screen(r, lds)) return;
-    if (blockIdx.x >= p.ntiles * (unsigned)p.ksplit) return;
-    if (!absgemm_split_slot<false, true, false, AREG, false, true>(p, blockIdx.x, gridDim.x, lds, chk_hist)) return;
-    const unsigned tile = blockIdx.x % p.ntiles;
-    const bool last = publish(&r.check.stats[tile].flag, 1u, chk_hist[0]) == (unsigned)p.ksplit;
-    if (!last) return;
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-    __syncthreads();
-    for (int i = threadIdx.x; i < kBins * 2; i += kSplitThreads) chk_hist[i] = 0;
-    __syncthreads();
+    __shared__ OpenLds o;
+    const unsigned tiles = screened_profile(r, lds);
+    if (tiles == 0 || blockIdx.x >= p.ntiles * (unsigned)p.ksplit) return;
     unsigned m0, n0, z;
-    locate_tile(p, tile, m0, n0, z);
-    const long per = p.M * p.N, total = per * (long)(p.ntiles / p.slots_per_z);
+    const unsigned slot = blockIdx.x % p.ntiles;
+    if (!locate_tile(p, slot, m0, n0, z)) return;
+    OpenTile& rec = r.open[open_index(p, m0, n0, z)];
+    const unsigned state = rec.state;
+    if (state == 0) return;
     ThreadAcc acc;
-    const QuickCheck quick(1.f, p.eps_rel);                  // (of the estimates only the bins: the bound is at hand)
-    unsigned known = 0;
-    // a thread has a column of every fourth row, eight of them at a time: the loads' latency is what the loop waits for
-    constexpr int BATCH = 8, RSTEP = kSplitThreads / STILE;
-    const long col = (long)n0 + (threadIdx.x & (STILE - 1)), row0 = (long)m0 + threadIdx.x / STILE;
-    if (col < p.N) {
-        const double ab = p.bias ? fabs((double)p.bias[col]) : 0.0;
+    if (sift_open<AREG, false>(p, rec, state, m0, n0, z, o)) {
+        absgemm_split_slot<false, true, false, AREG, false, true>(p, blockIdx.x, gridDim.x, lds, nullptr);
+        if (publish(&rec.arrived, 1u, o.word) != (unsigned)p.ksplit) return;
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+        const long per = p.M * p.N, total = per * (long)(p.ntiles / p.slots_per_z);
+        // a thread has a column of every fourth row, eight of them at a time: the loads' latency is what the loop waits for
+        constexpr int BATCH = 8, RSTEP = kSplitThreads / STILE;
+        const int lcol = threadIdx.x & (STILE - 1), lrow = threadIdx.x / STILE;
+        const long col = (long)n0 + lcol;
+        const double ab = p.bias && col < p.N ? fabs((double)p.bias[col]) : 0.0;
         const double off_pos = bound_offset(p, p.si, ab), off_zero = bound_offset(p, p.si0, ab);
 #pragma unroll 1
         for (int i0 = 0; i0 < STILE / RSTEP; i0 += BATCH) {
             double sv[BATCH];
             float c[BATCH], rf[BATCH];
             long at[BATCH];
+            unsigned asked = 0;
 #pragma unroll
             for (int i = 0; i < BATCH; ++i) {
-                const long row = min(row0 + (i0 + i) * RSTEP, p.M - 1), y = (long)z * p.strideY + row * p.ldy + col;
+                const int row = lrow + (i0 + i) * RSTEP;
+                if (m0 + row < p.M && col < p.N) asked |= (o.todo[row * (STILE / 32) + (lcol >> 5)] >> (lcol & 31) & 1u) << i;
+            }
+            if (!asked) continue;
+#pragma unroll
+            for (int i = 0; i < BATCH; ++i) {
+                const long row = min((long)m0 + lrow + (i0 + i) * RSTEP, p.M - 1), y = (long)z * p.strideY + row * p.ldy + col;
                 at[i] = (long)z * per + row * p.N + col;
                 sv[i] = 0.0; c[i] = p.claimed[y]; rf[i] = p.ref[y];
             }
@@ -946,23 +1009,16 @@ __global__ __launch_bounds__(kSplitThreads) void absgemm_settle_parts(SplitArgs 
                 for (int i = 0; i < BATCH; ++i) sv[i] += p.partial[(long)k * total + at[i]];
 #pragma unroll
             for (int i = 0; i < BATCH; ++i) {
-                if (row0 + (i0 + i) * RSTEP >= p.M) continue;
                 const float t32 = up32(bound_of_sum(p, sv[i], off_pos, off_zero));
-                unsigned bin;
-                if (fabsf(c[i] - rf[i]) <= 0x1p100f && quick_settled(c[i], rf[i], 0x1p120f, quick, known, bin)) {
-                    acc.violations += !(fabs((double)c[i] - (double)rf[i]) <= p.alpha * (double)t32);
-                    atomicAdd(&chk_hist[(bin >> 1) * 4 + (threadIdx.x & 3)], (bin & 1) ? 0x10000u : 1u);
-                } else {
-                    check_one_packed(c[i], rf[i], t32, p.alpha, p.eps_rel, chk_hist, threadIdx.x & 3, acc);
-                    known = acc.max_bits;
-                }
+                acc.violations += (asked >> i & 1u) && !(fabs((double)c[i] - (double)rf[i]) <= p.alpha * (double)t32);
             }
         }
+        flush_counters(p, acc);
+    } else if (blockIdx.x >= p.ntiles) {
+        return;                                              // (a tile that needs no sums is its first part's)
     }
-    __syncthreads();
-    flush_packed(p, chk_hist);
-    flush_counters(p, acc);
-    tiles_done(p, r, 1u, lds, chk_hist[0]);
+    add_violations(p, o.counts[0]);
+    tiles_done(r, tiles, 1u, o.word);
 }
 
 // Adds the parts of a PARTIAL launch in a fixed order and forms the bound exactly as the epilogue
@@ -1209,6 +1265,15 @@ static size_t core_workspace_bytes(long M, long N, long K, long batch, bool chec
     }
     return b;
 }
+// The records of what a screen leaves open, behind everything else (a workspace without them is accepted, and nothing is screened).
+static size_t open_bytes(long M, long N, long batch) {
+    return M <= 0 || N <= 0 || batch <= 0 ? 0 : round_up_256(open_tiles_of(M, N, batch) * sizeof(OpenTile));
+}
+static size_t with_open(size_t need, long M, long N, long K, long batch) { return K > 0 ? round_up_256(need) + open_bytes(M, N, batch) : need; }
+// What the launch before a screen clears.
+static ClearJob screen_clear(const CheckWorkspace& cw, OpenTile* open, long M, long N, long batch) {
+    return clear_job(cw, kScreenSlots, open, open_tiles_of(M, N, batch));
+}
 }  // namespace tao
 
 extern "C" {
@@ -1227,7 +1292,7 @@ size_t tao_linear_images_workspace_bytes(long M, long N, long K, long batch) {
     return tao::core_workspace_bytes(M, N, K, batch, false);
 }
 size_t tao_check_linear_images_workspace_bytes(long M, long N, long K, long batch) {
-    return tao::core_workspace_bytes(M, N, K, batch, true);
+    return tao::with_open(tao::core_workspace_bytes(M, N, K, batch, true), M, N, K, batch);
 }
 
 int tao_linear_split_preferred(long M, long N, long K, long batch) {
@@ -1292,17 +1357,18 @@ static void launch_split3(const SplitOperand* ops, int n, const ClearJob& clear,
 // claimed as well when tau is stored.
 // Af != NULL: the A operand is split while it is loaded (AREG instantiations; the caller has
 // checked in_load_split_ok); A3 is then unused.
-// screened: a screen has been enqueued with this workspace; one launch here settles the check.
+// open: a screen has been enqueued with this workspace and these records; one launch here settles the check.
 struct ConvHost { int H, W, C, OW, S, sh, sw, ph, pw, dh, dw; unsigned ohow; };
 // cv != NULL (with Af): Af is a convolution's channels-last input and A its implicit patch matrix.
 static int split_core(const unsigned short* A3, const unsigned short* W3, const float* bias, float* tau,
                       long M, long N, long K, long ldt, long batch, long strideT, bool shared_w,
                       const tao_fp_model& md, void* ws, void* stream, const SplitCheckHost* chk, bool cleared,
                       const float* Af = nullptr, long lda = 0, long strideA = 0, const ConvHost* cv = nullptr,
-                      bool screened = false) {
+                      OpenTile* open = nullptr) {
     const long Kp_ = K + (bias ? 1 : 0);
     const double c = gamma_up(Kp_, md);
     if (!(c == c)) return TAO_ERR_K_RANGE;
+    const bool screened = open != nullptr;
     hipStream_t st = (hipStream_t)stream;
     const int parts = split_k_parts(M, N, K, batch);
     char* wsb = static_cast<char*>(ws);
@@ -1425,11 +1491,7 @@ static int split_core(const unsigned short* A3, const unsigned short* W3, const 
         p.claimed = chk->claimed; p.ref = chk->ref; p.ldy = chk->ldy; p.strideY = chk->strideY;
         p.alpha = chk->alpha; p.eps_rel = chk->eps_rel;
         p.ws_hist = cw.hist; p.ws_coarse = cw.coarse; p.ws_stats = cw.stats;
-        if (screened) {
-            const CheckWorkspace half = settle_partials(cw);
-            p.ws_hist = half.hist; p.ws_coarse = half.coarse; p.ws_stats = half.stats;
-            p.check_slots = kSettleSlots;
-        }
+        if (screened) p.check_slots = kScreenSlots;
     }
     // the streaming check of a stored bound, after the launches that store it
     auto then_check = [&]() -> int {
@@ -1438,7 +1500,7 @@ static int split_core(const unsigned short* A3, const unsigned short* W3, const 
         return tao_check_and_profile(chk->claimed, chk->ref, tau, M * N * batch, chk->alpha, chk->eps_rel, chk->out,
                                      check_ws, check_workspace_bytes(), stream);
     };
-    const SettleArgs settle = {cw, (unsigned)ntiles, profile_size((unsigned long long)((__int128)M * N * batch)), chk ? chk->out : nullptr};
+    const SettleArgs settle = {cw, open, profile_size((unsigned long long)((__int128)M * N * batch)), chk ? chk->out : nullptr};
     if (parts >= 2) {
         // the reduction in parts, then one pass that adds them and forms (and checks) the bound
         const long groups = Kp / SBK;
@@ -1509,8 +1571,9 @@ static bool epilogue_check_without_parts(long M, long N, long K, long batch, con
 
 // The screen of a checked bound (linear_screen.hip).  Whether one goes ahead of the exact route: the bound itself is not asked for,
 // and its constants allow it.
-static bool screened(long M, long N, long K, long batch, const float* bias, const float* tau, const tao_fp_model& md, const SplitCheckHost* chk) {
-    if (!chk || tau || K <= 0 || (md.flags & TAO_FLAG_CHECK_IN_EPILOGUE) || chk->ldy >= kScreenMaxLd) return false;
+// A workspace that has no room for what the screen takes beyond the exact route, `extra` bytes at `at`, gets none.
+static bool screened(long K, const float* bias, const float* tau, const tao_fp_model& md, const SplitCheckHost* chk, size_t at, size_t extra, size_t ws_bytes) {
+    if (!chk || tau || K <= 0 || ws_bytes < at + extra || (md.flags & TAO_FLAG_CHECK_IN_EPILOGUE) || chk->ldy >= kScreenMaxLd) return false;
     const long Kp_ = K + (bias ? 1 : 0);
     const double uflow = (md.flags & TAO_FLAG_UNDERFLOW_TERMS) ? (double)Kp_ * 0x1p-148 : 0.0;
     return screen_usable(K, md.u, gamma_up(Kp_, md) * kGuard, chk->alpha, uflow);
@@ -1522,9 +1585,9 @@ static CheckWorkspace core_check_workspace(void* rest, long M, long N, long K, l
     return carve_check_workspace(static_cast<char*>(rest) + partial_bytes);
 }
 static int run_screen(const ScreenOperand& A, const ScreenOperand& W, const float* bias, long M, long N, long K, long batch,
-                      const tao_fp_model& md, const SplitCheckHost* chk, const CheckWorkspace& cw, hipStream_t st) {
+                      const tao_fp_model& md, const SplitCheckHost* chk, const CheckWorkspace& cw, OpenTile* open, hipStream_t st) {
     const ScreenCheck sc = {chk->claimed, chk->ref, chk->ldy, chk->strideY, chk->alpha, chk->eps_rel};
-    return launch_screen(A, W, bias, M, N, K, batch, gamma_up(K + (bias ? 1 : 0), md) * kGuard, sc, cw, st);
+    return launch_screen(A, W, bias, M, N, K, batch, gamma_up(K + (bias ? 1 : 0), md) * kGuard, sc, cw, open, st);
 }
 
 // Validation shared by the entry points below (everything but the operands themselves).
@@ -1595,7 +1658,9 @@ static int split_run(const float* A, const float* W, const float* bias, float* t
     // not a launch whose short reduction is better served by the tile walk.
     const bool rows_ok = K > 0 && K % SBK == 0 && N <= 2 * STILE && aligned(A, 16) && lda % 4 == 0 && strideA % 4 == 0 &&
                          (__int128)M * lda < ((__int128)1 << 40);
-    const bool scr = screened(M, N, K, batch, bias, tau, md, chk) && !(rows_ok && lda >= kScreenMaxLd);
+    const size_t open_at = round_up_256(need);
+    const bool scr = screened(K, bias, tau, md, chk, open_at, open_bytes(M, N, batch), ws_bytes) && !(rows_ok && lda >= kScreenMaxLd);
+    OpenTile* const open = scr ? reinterpret_cast<OpenTile*>(wsb + open_at) : nullptr;
     const bool in_load = rows_ok && (scr || (split_k_parts(M, N, K, batch) < 2 && K / SBK > kWalkMaxGroups));
     const CheckWorkspace cw = core_check_workspace(rest, M, N, K, batch);
     bool cleared = false;
@@ -1604,18 +1669,18 @@ static int split_run(const float* A, const float* W, const float* bias, float* t
         // are checked by the combining pass, which needs none)
         cleared = scr || epilogue_check_without_parts(M, N, K, batch, md, chk);
         const SplitOperand ops[2] = {{W, N, K, ldw, shared_w ? 1 : batch, strideW, W3, trans_w ? TRANSPOSED : STRAIGHT}, {A, M, K, lda, batch, strideA, A3, STRAIGHT}};
-        launch_split3(ops, in_load ? 1 : 2, cleared ? clear_job(cw, scr ? kScreenSlots + kSettleSlots : kMaxCheckBlocks) : ClearJob{}, st);
+        launch_split3(ops, in_load ? 1 : 2, scr ? screen_clear(cw, open, M, N, batch) : cleared ? clear_job(cw, kMaxCheckBlocks) : ClearJob{}, st);
     }
     if (scr) {
         const long groups = (K + SBK - 1) / SBK;
         ScreenOperand oa = {A3, groups * ((M + STILE - 1) / STILE) * kBlock, 0, nullptr};
         if (in_load) oa = {A, strideA * 4, lda, nullptr};
         const ScreenOperand ow = {W3, shared_w ? 0 : groups * ((N + STILE - 1) / STILE) * kBlock, 0, nullptr};
-        rc = run_screen(oa, ow, bias, M, N, K, batch, md, chk, cw, st);
+        rc = run_screen(oa, ow, bias, M, N, K, batch, md, chk, cw, open, st);
         if (rc != TAO_OK) return rc;
     }
     return split_core(A3, W3, bias, tau, M, N, K, ldt, batch, strideT, shared_w, md, rest, stream, chk, cleared,
-                      in_load ? A : nullptr, lda, strideA, nullptr, scr);
+                      in_load ? A : nullptr, lda, strideA, nullptr, open);
 }
 
 // The same on images the caller has prepared with tao_split_operand.
@@ -1638,20 +1703,22 @@ static int images_run(const void* A_image, const void* W_image, const float* bia
     const unsigned short* A3 = static_cast<const unsigned short*>(A_image);
     const unsigned short* W3 = static_cast<const unsigned short*>(W_image);
     bool cleared = false;
-    const bool scr = screened(M, N, K, batch, bias, tau, md, chk);
-    if (scr) {
+    const size_t open_at = round_up_256(need);
+    OpenTile* open = nullptr;
+    if (screened(K, bias, tau, md, chk, open_at, open_bytes(M, N, batch), ws_bytes)) {
+        open = reinterpret_cast<OpenTile*>(static_cast<char*>(ws) + open_at);
         hipStream_t st = (hipStream_t)stream;
         const CheckWorkspace cw = core_check_workspace(ws, M, N, K, batch);
         cleared = true;
-        launch_clear(clear_job(cw, kScreenSlots + kSettleSlots), st);
+        launch_clear(screen_clear(cw, open, M, N, batch), st);
         const long groups = (K + SBK - 1) / SBK;
         const ScreenOperand oa = {A3, groups * ((M + STILE - 1) / STILE) * kBlock, 0, nullptr};
         const ScreenOperand ow = {W3, sw ? 0 : groups * ((N + STILE - 1) / STILE) * kBlock, 0, nullptr};
-        rc = run_screen(oa, ow, bias, M, N, K, batch, md, chk, cw, st);
+        rc = run_screen(oa, ow, bias, M, N, K, batch, md, chk, cw, open, st);
         if (rc != TAO_OK) return rc;
     }
     return split_core(A3, W3, bias, tau, M, N, K, ldt, batch, strideT, sw, md, ws, stream, chk, cleared,
-                      nullptr, 0, 0, nullptr, scr);
+                      nullptr, 0, 0, nullptr, open);
 }
 }  // namespace tao
 
@@ -1735,22 +1802,22 @@ static int conv_split_run(const float* x, const float* w, const float* bias, flo
     cv.H = (int)H; cv.W = (int)W; cv.C = (int)C; cv.OW = (int)OW; cv.S = (int)S;
     cv.sh = (int)stride_h; cv.sw = (int)stride_w; cv.ph = (int)pad_h; cv.pw = (int)pad_w; cv.dh = (int)dil_h; cv.dw = (int)dil_w;
     cv.ohow = (unsigned)(OH * OW);
-    // (a workspace without room for the input's magnitudes, as the exact route needs none, gets no screen)
-    const size_t pixel_bytes = conv_pixel_bytes(batch, H, W, C), pixels_at = round_up_256(need);
-    const bool scr = pixel_bytes > 0 && ws_bytes >= pixels_at + pixel_bytes && screened(M, N, K, 1, bias, tau, md, chk);
+    const size_t open_at = round_up_256(need), pixels_at = open_at + open_bytes(M, N, 1), pixel_bytes = conv_pixel_bytes(batch, H, W, C);
+    const bool scr = pixel_bytes > 0 && screened(K, bias, tau, md, chk, open_at, open_bytes(M, N, 1) + pixel_bytes, ws_bytes);
+    OpenTile* const open = scr ? reinterpret_cast<OpenTile*>(wsb + open_at) : nullptr;
     const bool cleared = scr || epilogue_check_without_parts(M, N, K, 1, md, chk);
     const CheckWorkspace cw = carve_check_workspace(rest);
     unsigned short* px = reinterpret_cast<unsigned short*>(wsb + pixels_at);
     const SplitOperand ops[2] = {{w, N, K, K, 1, 0, W3, STRAIGHT}, {x, 1, batch * H * W * C, 0, 1, 0, px, MAGNITUDES}};
-    launch_split3(ops, scr ? 2 : 1, cleared ? clear_job(cw, scr ? kScreenSlots + kSettleSlots : kMaxCheckBlocks) : ClearJob{}, (hipStream_t)stream);
+    launch_split3(ops, scr ? 2 : 1, scr ? screen_clear(cw, open, M, N, 1) : cleared ? clear_job(cw, kMaxCheckBlocks) : ClearJob{}, (hipStream_t)stream);
     if (scr) {
         const ScreenPixels pixels = {cv.H, cv.W, cv.C, cv.OW, cv.S, cv.sh, cv.sw, cv.ph, cv.pw, cv.dh, cv.dw, cv.ohow, cv.C / SBK,
                                      (unsigned)(batch * H * W * C * 2)};
         const ScreenOperand oa = {px, 0, 0, &pixels}, ow = {W3, 0, 0, nullptr};
-        rc = run_screen(oa, ow, bias, M, N, K, 1, md, chk, cw, (hipStream_t)stream);
+        rc = run_screen(oa, ow, bias, M, N, K, 1, md, chk, cw, open, (hipStream_t)stream);
         if (rc != TAO_OK) return rc;
     }
-    return split_core(nullptr, W3, bias, tau, M, N, K, N, 1, M * N, true, md, rest, stream, chk, cleared, x, K, 0, &cv, scr);
+    return split_core(nullptr, W3, bias, tau, M, N, K, N, 1, M * N, true, md, rest, stream, chk, cleared, x, K, 0, &cv, open);
 }
 }  // namespace tao
 
@@ -1771,7 +1838,7 @@ size_t tao_conv2d_split_workspace_bytes(long batch, long H, long W, long C, long
     if (tao::conv_geometry(batch, H, W, C, Cout, R, S, stride_h, stride_w, pad_h, pad_w, dil_h, dil_w, &OH, &OW, &M, &K) != TAO_OK) return 0;
     const size_t img = (M == 0 || Cout == 0) ? 0 : tao::image_bytes(Cout, K, 1);
     const size_t need = img + tao::core_workspace_bytes(M, Cout, K, 1, with_check != 0);
-    return with_check && img ? tao::round_up_256(need) + tao::conv_pixel_bytes(batch, H, W, C) : need;
+    return with_check && img ? tao::round_up_256(need) + tao::open_bytes(M, Cout, 1) + tao::conv_pixel_bytes(batch, H, W, C) : need;
 }
 
 int tao_bound_conv2d_split(const float* x, const float* w, const float* bias, float* tau,
@@ -1807,7 +1874,7 @@ size_t tao_bound_check_linear_workspace_bytes(long M, long N, long K, long batch
     const size_t a = (K > 0 && !empty) ? tao::image_bytes(M, K, batch) : 0;
     const size_t w = (K > 0 && !empty) ? tao::image_bytes(N, K, shared_w ? 1 : batch) : 0;
     if (K > 0 && !empty && (a == 0 || w == 0)) return 0;
-    return a + w + tao::core_workspace_bytes(M, N, K, batch, true);
+    return tao::with_open(a + w + tao::core_workspace_bytes(M, N, K, batch, true), M, N, K, batch);
 }
 
 int tao_bound_check_linear_in_epilogue(long M, long N, long K, long batch) {

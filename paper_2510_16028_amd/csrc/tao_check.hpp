@@ -216,7 +216,8 @@ struct ProfileGroup {
                 if (k < nblocks) { v += w.stats[k].violations; q += w.stats[k].nans; m = max(m, w.stats[k].max_bits); }
         }
     }
-    __device__ __forceinline__ void finish(const ProfileSize& size, tao_profile* out, unsigned long long* smem) {
+    // counted: all violations are in the partial results (else violations and accept are left to the caller)
+    __device__ __forceinline__ void finish(const ProfileSize& size, tao_profile* out, unsigned long long* smem, bool counted = true) {
         constexpr int WAVES = THREADS / kWave;
         const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
         unsigned long long* wv = smem + THREADS + WAVES;
@@ -233,10 +234,9 @@ struct ProfileGroup {
 #pragma unroll
             for (int k = 0; k < WAVES; ++k) { v += wv[k]; q += wq[k]; m = max(m, wm[k]); }
             out->n = size.n;
-            out->violations = v;
+            if (counted) { out->violations = v; out->accept = (v == 0) ? 1u : 0u; }
             out->nan_count = q;
             out->max_rel = __uint_as_float(m);
-            out->accept = (v == 0) ? 1u : 0u;
             out->pad_ = 0;
             if (size.n == 0) {
                 out->p50_bin = out->p99_bin = out->p999_bin = 0;

@@ -63,3 +63,16 @@ def test_equal_claims_cost_what_honest_ones_do(tao, form):
     t_honest, t_equal = _times([lambda: check(honest), lambda: check(equal)])
     # (measured: at most 1.0; with equal elements on the exact way 2.3, 1.2 and 2.1)
     assert t_equal <= 1.15 * t_honest, (form, t_equal, t_honest)
+
+
+@pytest.mark.parametrize("form", ["image", "rows", "pixels"])
+def test_a_comparison_left_open_costs_a_tile_at_most(tao, form):
+    tau, y, check = _setup(tao, form)
+    honest = (y.double() * (1 + 2.0 ** -23)).float()
+    one, nan = honest.clone(), honest.clone()
+    at = y.numel() // 2
+    one.view(-1)[at] = (y.double() + tau.double()).float().view(-1)[at]
+    nan.view(-1)[at] = float("nan")
+    t_honest, t_one, t_nan = _times([lambda: check(honest), lambda: check(one), lambda: check(nan)])
+    # (measured: one at most 1.3, NaN 1.0; with the whole call formed again 2.6 to 3.3)
+    assert t_one <= 1.8 * t_honest and t_nan <= 1.3 * t_honest, (form, t_one, t_nan, t_honest)
