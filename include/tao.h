@@ -183,9 +183,8 @@ int tao_linear_split_preferred(long M, long N, long K, long batch);
  * The bound itself is compared in registers in the matrix kernel's epilogue; where that would cost more than it saves -- `tau` asked for, reductions up to
  * 1024 long with contiguous outputs that are not cut into parts -- it is stored and the streaming check reads it.
  * y_ref: the verifier's re-executed output, claimed: the proposer's.  out: DEVICE, fully overwritten,
- * valid once the stream has drained.  ws / ws_bytes: DEVICE scratch of
- * tao_bound_check_linear_workspace_bytes(...), 256-byte aligned (64 bytes of it per tile are the records of what is open: a workspace
- * without that part is accepted, and the bound itself checked; so for the other checked entry points).  Runs the BF16-split kernel for every
+ * valid once the stream has drained.  ws / ws_bytes: DEVICE scratch of at least
+ * tao_bound_check_linear_workspace_bytes(...), 256-byte aligned.  Runs the BF16-split kernel for every
  * shape (tao_linear_split_preferred tells where that is the faster one).  Errors as for
  * tao_bound_linear_split and tao_check_and_profile; TAO_ERR_SHAPE also for M N batch >= 2^36. */
 int tao_bound_check_linear(const float *A, const float *W, const float *bias, const float *y_ref,

@@ -16,7 +16,7 @@
 // operands below 2^-126 lose in BF16's subnormal range, 2^-134 each, weighs at most K 2^-101) and the sum at least
 // Kp 2^-80; an element with d = 0 never violates a bound that is not NaN, and one whose d is NaN violates every bound.  Other
 // comparisons -- a claim between the two limits, a smaller sum -- are left open, and so are all of a tile with a larger or
-// non-finite operand or a bias beyond 2^60: a record per tile of the exact route (OpenTile) keeps their places, and that route,
+// non-finite operand or a bias beyond 2^60: a record per tile of the exact route (OpenRecords) keeps their places, and that route,
 // enqueued behind the screen, decides these and nothing else.  So every profile is the exact route's, bit for bit.
 // The errors' bins and maximum do not depend on tau: quick settlement as in tao_check.hpp, exact arithmetic where
 // an estimate does not decide.
@@ -66,7 +66,7 @@ struct ScreenArgs {
     int stream;                        // claims and outputs are more than the memory-side cache holds: streaming loads
     double eps_rel;
     float low, high, low_b, high_b, tiny;
-    OpenTile* open; unsigned open_m, open_n;                // records, and how many tiles they are down and across
+    OpenRecords open; unsigned open_m, open_n;              // and how many tiles they are down and across
     unsigned int* hist; unsigned int* coarse; BlockStats* stats;
 };
 
@@ -473,20 +473,21 @@ __global__ __launch_bounds__(WVM * WVN * 64, WVM * WVN * PER_CU / 4) void screen
         // What was left open goes to the record of the 128 x 128 tile: a few comparisons by their places; many, or all of them, as the
         // wavefront's blocks, in which it then counts no violations.
         if (__any(open != 0) || none_decided) {
-            OpenTile* const rec = p.open + ((size_t)z * p.open_m + (unsigned)(m0 >> 7)) * p.open_n + (unsigned)(n0 >> 7);
+            unsigned* const rec = p.open.of(((size_t)z * p.open_m + (unsigned)(m0 >> 7)) * p.open_n + (unsigned)(n0 >> 7));
+            const unsigned places = (unsigned)p.open.places();
             const unsigned r0 = ((unsigned)m0 & 127u) + srow, c0 = ((unsigned)n0 & 127u) + scol;
             const unsigned mine = (unsigned)__popcll((unsigned long long)open), upto = (unsigned)wave_scan(mine), all = wave_sum(mine);
             unsigned was = 0;
-            bool listed = !none_decided && all <= (unsigned)kOpenList;
+            bool listed = !none_decided && all <= places;
             if (listed) {
-                if (lane == 0) was = atomicAdd(&rec->state, all << 16);
+                if (lane == 0) was = atomicAdd(rec, all << 16);
                 was = __builtin_amdgcn_readfirstlane(was);
-                listed = (was >> 16) + all <= (unsigned)kOpenList;
+                listed = (was >> 16) + all <= places;
                 unsigned at = (was >> 16) + upto - mine;
-                for (Places left = open; left && at < (unsigned)kOpenList; left &= left - 1, ++at) {
+                for (Places left = open; left && at < places; left &= left - 1, ++at) {
                     const int bit = __ffsll((unsigned long long)left) - 1, step = bit >> 2;
                     const unsigned row = r0 + (unsigned)(step / STEPS * 32 + lrow + step % STEPS * RPI), col = c0 + (unsigned)(lcol + (bit & 3));
-                    rec->at[at] = listed ? row << 7 | col : kNoPlace;
+                    rec[2 + at] = listed ? row << 7 | col : kNoPlace;
                 }
                 opened += was == 0;
             }
@@ -494,7 +495,7 @@ __global__ __launch_bounds__(WVM * WVN * 64, WVM * WVN * PER_CU / 4) void screen
                 const unsigned before = was;
                 constexpr unsigned across = (1u << RN) - 1u;
                 const unsigned blocks = (RM == 2 ? across | across << 4 : across) << (r0 / 32 * 4 + c0 / 32);
-                if (lane == 0) { was = atomicOr(&rec->state, blocks); atomicAdd(&heavy, 1u); }
+                if (lane == 0) { was = atomicOr(rec, blocks); atomicAdd(&heavy, 1u); }
                 was = __builtin_amdgcn_readfirstlane(was);
                 opened += before == 0 && was == 0;
                 vio = vio_before;
@@ -558,7 +559,7 @@ int launch_config(ScreenArgs& p, long batch, hipStream_t st) {
 }  // namespace
 
 int launch_screen(const ScreenOperand& A, const ScreenOperand& W, const float* bias, long M, long N, long K, long batch,
-                  double cg, const ScreenCheck& chk, const CheckWorkspace& ws, OpenTile* open, hipStream_t st) {
+                  double cg, const ScreenCheck& chk, const CheckWorkspace& ws, const OpenRecords& open, hipStream_t st) {
     const long groups = (K + SBK - 1) / SBK, blocksA = (M + 127) / 128, blocksW = (N + 127) / 128;
     ScreenArgs p = {};
     const bool rows = A.ld != 0, pixels = A.pixels != nullptr;

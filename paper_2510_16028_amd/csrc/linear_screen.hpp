@@ -30,25 +30,32 @@ struct ScreenCheck { const float* claimed; const float* ref; long ldy, strideY; 
 constexpr int kScreenSlots = 64;              // (32 cost perturbed claims of 1111 x 3001 2 us, 128 honest ones 0.4)
 constexpr int kDoneFlag = kMaxCheckBlocks - 1;
 static_assert(kScreenSlots == kWave, "a lane for each");
-// The comparisons that the screen left open in a tile of the exact route (128 x 128 outputs; tiles row by row, batch entries one after
-// the other).  All zero before the screen; zero after it where none is open.
-constexpr int kOpenTile = 128, kOpenList = 14;
+// The comparisons that the screen left open, a record per tile of the exact route (128 x 128 outputs; tiles row by row, batch entries one
+// after the other), in the room of the partial results that a screened check does not use.  A record's first word is its state -- bit 4 r + c:
+// every comparison of block (r, c), 32 x 32; from bit 16 on: how many places were asked for --, the second the number of parts of the
+// reduction that the exact route has finished, the others are places: 128 row + column, or kNoPlace.  All zero before the screen.  Outputs of
+// more tiles than fit so (0.4 G outputs) have records of the state alone, and those of more than these (6.4 G) are not screened.
+constexpr int kOpenTile = 128, kOpenWords = 16;
 constexpr unsigned kNoPlace = ~0u;
-struct OpenTile {
-    unsigned state;            // bit 4 r + c: every comparison of block (r, c), 32 x 32; from bit 16 on: how many places were asked for
-    unsigned arrived;          // parts of the reduction that the exact route has finished
-    unsigned at[kOpenList];    // places: 128 row + column, or kNoPlace
+struct OpenRecords {
+    unsigned* first;
+    int words;                 // of a record: kOpenWords or 1
+    __host__ __device__ unsigned* of(size_t tile) const { return first + tile * (size_t)words; }
+    __host__ __device__ int places() const { return words == kOpenWords ? kOpenWords - 2 : 0; }
 };
-static_assert(sizeof(OpenTile) == 64, "cleared in 16-byte words");
+constexpr size_t kOpenRoom = (size_t)(kMaxCheckBlocks - kScreenSlots) * kBins;           // words
 inline size_t open_tiles_of(long M, long N, long batch) {
     return (size_t)((M + kOpenTile - 1) / kOpenTile) * (size_t)((N + kOpenTile - 1) / kOpenTile) * (size_t)batch;
 }
-// What a launch before a check clears, in 16-byte words: of `slots` partial results the histograms and coarse counts, all counters, and
-// a screened check's records.
-struct ClearJob { void* at[4]; long words[4]; };
-inline ClearJob clear_job(const CheckWorkspace& w, int slots, OpenTile* open = nullptr, size_t tiles = 0) {
-    return {{w.hist, w.coarse, w.stats, open},
-            {(long)slots * kBins / 4, (long)slots * kGroups / 4, (long)(kMaxCheckBlocks * sizeof(BlockStats) / 16), (long)(tiles * sizeof(OpenTile) / 16)}};
+inline OpenRecords open_records(const CheckWorkspace& w, size_t tiles) {
+    return {w.hist + (size_t)kScreenSlots * kBins, tiles * kOpenWords <= kOpenRoom ? kOpenWords : 1};
+}
+// What a launch before a check clears, in 16-byte words: of `slots` partial results the histograms and coarse counts, `more` words behind the
+// histograms, and all counters.
+struct ClearJob { void* at[3]; long words[3]; };
+inline ClearJob clear_job(const CheckWorkspace& w, int slots, size_t more = 0) {
+    return {{w.hist, w.coarse, w.stats},
+            {(long)(((size_t)slots * kBins + more + 3) / 4), (long)slots * kGroups / 4, (long)(kMaxCheckBlocks * sizeof(BlockStats) / 16)}};
 }
 static_assert(kMaxCheckBlocks * sizeof(BlockStats) % 16 == 0, "cleared in 16-byte words");
 
@@ -68,6 +75,6 @@ inline bool screen_usable(long K, double u, double cg, double alpha, double uflo
            uflow <= cg * (double)K * 0x1p-100;
 }
 int launch_screen(const ScreenOperand& A, const ScreenOperand& W, const float* bias, long M, long N, long K, long batch,
-                  double cg, const ScreenCheck& chk, const CheckWorkspace& ws, OpenTile* open, hipStream_t st);
+                  double cg, const ScreenCheck& chk, const CheckWorkspace& ws, const OpenRecords& open, hipStream_t st);
 
 }  // namespace tao

@@ -134,7 +134,7 @@ struct SplitOperands {
 };
 __device__ __forceinline__ void clear_words(const ClearJob& c, long i0, long step) {
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
+    for (int j = 0; j < 3; ++j)
         for (long i = i0; i < c.words[j]; i += step) static_cast<uintx4*>(c.at[j])[i] = uintx4{0, 0, 0, 0};
 }
 typedef float floatx4u __attribute__((ext_vector_type(4), aligned(4)));          // (16-byte loads need no more than 4-byte alignment)
@@ -835,7 +835,7 @@ __global__ __launch_bounds__(kSplitThreads) void absgemm_split(SplitArgs p) {
 // workspace; nobody waits) adds them up.
 struct SettleArgs {
     CheckWorkspace check;
-    OpenTile* open;
+    OpenRecords open;
     ProfileSize size;
     tao_profile* out;
 };
@@ -894,7 +894,7 @@ __device__ __forceinline__ int decide_by_sum(const SplitArgs& p, unsigned row, u
 // Returns whether any are left.
 struct OpenLds { unsigned int todo[STILE * STILE / 32], counts[2], word; };
 template <bool AREG, bool CONV>
-__device__ __forceinline__ bool sift_open(const SplitArgs& p, const OpenTile& rec, unsigned state, unsigned m0, unsigned n0, unsigned z, OpenLds& o) {
+__device__ __forceinline__ bool sift_open(const SplitArgs& p, const OpenRecords& open, const unsigned* rec, unsigned state, unsigned m0, unsigned n0, unsigned z, OpenLds& o) {
     static_assert(STILE * STILE / 32 == kSplitThreads, "a word a thread");
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const unsigned blocks = state & 0xffffu;
@@ -902,10 +902,10 @@ __device__ __forceinline__ bool sift_open(const SplitArgs& p, const OpenTile& re
     o.todo[tid] = blocks >> ((tid >> 7) * 4 + (tid & 3)) & 1u ? ~0u : 0u;
     if (tid == 0) { o.counts[0] = 0; o.counts[1] = blocks; }
     __syncthreads();
-    const int n = min((int)(state >> 16), kOpenList);
+    const int n = min((int)(state >> 16), open.places());
     if (n == 0) return true;
     for (int e = wave; e < n; e += kSplitThreads / kWave) {
-        const unsigned at = rec.at[e];
+        const unsigned at = rec[2 + e];
         if (at == kNoPlace) continue;
         // (with whole blocks the bound is formed in any case)
         const int v = blocks ? -1 : decide_by_sum<AREG, CONV>(p, m0 + (at >> 7), n0 + (at & 127u), z);
@@ -929,27 +929,27 @@ __global__ __launch_bounds__(kSplitThreads) void absgemm_settle(SplitArgs p, Set
     unsigned done = 0, m0, n0, z;
     if (AREG) {
         if (blockIdx.x >= p.ntiles || !locate_tile(p, blockIdx.x, m0, n0, z)) return;
-        const OpenTile& rec = r.open[open_index(p, m0, n0, z)];
-        const unsigned state = rec.state;
+        const unsigned* rec = r.open.of(open_index(p, m0, n0, z));
+        const unsigned state = rec[0];
         if (state == 0) return;
-        if (sift_open<AREG, CONV>(p, rec, state, m0, n0, z, o)) absgemm_split_slot<true, false, false, AREG, CONV, false, true>(p, blockIdx.x, gridDim.x, lds, o.todo);
+        if (sift_open<AREG, CONV>(p, r.open, rec, state, m0, n0, z, o)) absgemm_split_slot<true, false, false, AREG, CONV, false, true>(p, blockIdx.x, gridDim.x, lds, o.todo);
         add_violations(p, o.counts[0]);
         done = 1;
     } else {
         // (64 slots' records at a time, one a lane; all wavefronts see the same)
         for (unsigned first = blockIdx.x; first < p.ntiles; first += gridDim.x * kWave) {
             const unsigned slot = first + (threadIdx.x & 63) * gridDim.x;
-            const unsigned state = slot < p.ntiles && locate_tile(p, slot, m0, n0, z) ? r.open[open_index(p, m0, n0, z)].state : 0u;
-            for (unsigned long long left = __ballot(state != 0); left; left &= left - 1) {
+            const unsigned states = slot < p.ntiles && locate_tile(p, slot, m0, n0, z) ? r.open.of(open_index(p, m0, n0, z))[0] : 0u;
+            for (unsigned long long left = __ballot(states != 0); left; left &= left - 1) {
                 // (the arguments are read anew for each tile: kept in registers through it they cost the loop of the product some)
                 typedef const SplitArgs __attribute__((address_space(4)))* ArgsPtr;
                 ArgsPtr q = (ArgsPtr)__builtin_amdgcn_kernarg_segment_ptr();
                 asm volatile("" : "+s"(q));
                 const SplitArgs& a = *(const SplitArgs*)q;
                 const int at = __ffsll(left) - 1;
-                const unsigned wg = first + (unsigned)at * gridDim.x;
+                const unsigned wg = first + (unsigned)at * gridDim.x, state = (unsigned)__builtin_amdgcn_readlane((int)states, at);
                 locate_tile(a, wg, m0, n0, z);
-                if (sift_open<AREG, CONV>(a, r.open[open_index(a, m0, n0, z)], (unsigned)__builtin_amdgcn_readlane((int)state, at), m0, n0, z, o)) {
+                if (sift_open<AREG, CONV>(a, r.open, r.open.of(open_index(a, m0, n0, z)), state, m0, n0, z, o)) {
                     absgemm_split_slot<true, false, false, AREG, CONV, false, true>(a, wg, gridDim.x, lds, o.todo);
                     __builtin_amdgcn_s_waitcnt(0x0F70);      // vmcnt(0): nothing of it counts in the next tile's waits
                 }
@@ -971,13 +971,13 @@ __global__ __launch_bounds__(kSplitThreads) void absgemm_settle_parts(SplitArgs 
     unsigned m0, n0, z;
     const unsigned slot = blockIdx.x % p.ntiles;
     if (!locate_tile(p, slot, m0, n0, z)) return;
-    OpenTile& rec = r.open[open_index(p, m0, n0, z)];
-    const unsigned state = rec.state;
+    unsigned* rec = r.open.of(open_index(p, m0, n0, z));     // (so few tiles have whole records)
+    const unsigned state = rec[0];
     if (state == 0) return;
     ThreadAcc acc;
-    if (sift_open<AREG, false>(p, rec, state, m0, n0, z, o)) {
+    if (sift_open<AREG, false>(p, r.open, rec, state, m0, n0, z, o)) {
         absgemm_split_slot<false, true, false, AREG, false, true>(p, blockIdx.x, gridDim.x, lds, nullptr);
-        if (publish(&rec.arrived, 1u, o.word) != (unsigned)p.ksplit) return;
+        if (publish(rec + 1, 1u, o.word) != (unsigned)p.ksplit) return;
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
         const long per = p.M * p.N, total = per * (long)(p.ntiles / p.slots_per_z);
         // a thread has a column of every fourth row, eight of them at a time: the loads' latency is what the loop waits for
@@ -1265,14 +1265,10 @@ static size_t core_workspace_bytes(long M, long N, long K, long batch, bool chec
     }
     return b;
 }
-// The records of what a screen leaves open, behind everything else (a workspace without them is accepted, and nothing is screened).
-static size_t open_bytes(long M, long N, long batch) {
-    return M <= 0 || N <= 0 || batch <= 0 ? 0 : round_up_256(open_tiles_of(M, N, batch) * sizeof(OpenTile));
-}
-static size_t with_open(size_t need, long M, long N, long K, long batch) { return K > 0 ? round_up_256(need) + open_bytes(M, N, batch) : need; }
 // What the launch before a screen clears.
-static ClearJob screen_clear(const CheckWorkspace& cw, OpenTile* open, long M, long N, long batch) {
-    return clear_job(cw, kScreenSlots, open, open_tiles_of(M, N, batch));
+static ClearJob screen_clear(const CheckWorkspace& cw, long M, long N, long batch) {
+    const size_t tiles = open_tiles_of(M, N, batch);
+    return clear_job(cw, kScreenSlots, tiles * (size_t)open_records(cw, tiles).words);
 }
 }  // namespace tao
 
@@ -1292,7 +1288,7 @@ size_t tao_linear_images_workspace_bytes(long M, long N, long K, long batch) {
     return tao::core_workspace_bytes(M, N, K, batch, false);
 }
 size_t tao_check_linear_images_workspace_bytes(long M, long N, long K, long batch) {
-    return tao::with_open(tao::core_workspace_bytes(M, N, K, batch, true), M, N, K, batch);
+    return tao::core_workspace_bytes(M, N, K, batch, true);
 }
 
 int tao_linear_split_preferred(long M, long N, long K, long batch) {
@@ -1357,18 +1353,17 @@ static void launch_split3(const SplitOperand* ops, int n, const ClearJob& clear,
 // claimed as well when tau is stored.
 // Af != NULL: the A operand is split while it is loaded (AREG instantiations; the caller has
 // checked in_load_split_ok); A3 is then unused.
-// open: a screen has been enqueued with this workspace and these records; one launch here settles the check.
+// screened: a screen has been enqueued with this workspace; one launch here settles the check.
 struct ConvHost { int H, W, C, OW, S, sh, sw, ph, pw, dh, dw; unsigned ohow; };
 // cv != NULL (with Af): Af is a convolution's channels-last input and A its implicit patch matrix.
 static int split_core(const unsigned short* A3, const unsigned short* W3, const float* bias, float* tau,
                       long M, long N, long K, long ldt, long batch, long strideT, bool shared_w,
                       const tao_fp_model& md, void* ws, void* stream, const SplitCheckHost* chk, bool cleared,
                       const float* Af = nullptr, long lda = 0, long strideA = 0, const ConvHost* cv = nullptr,
-                      OpenTile* open = nullptr) {
+                      bool screened = false) {
     const long Kp_ = K + (bias ? 1 : 0);
     const double c = gamma_up(Kp_, md);
     if (!(c == c)) return TAO_ERR_K_RANGE;
-    const bool screened = open != nullptr;
     hipStream_t st = (hipStream_t)stream;
     const int parts = split_k_parts(M, N, K, batch);
     char* wsb = static_cast<char*>(ws);
@@ -1500,7 +1495,7 @@ static int split_core(const unsigned short* A3, const unsigned short* W3, const 
         return tao_check_and_profile(chk->claimed, chk->ref, tau, M * N * batch, chk->alpha, chk->eps_rel, chk->out,
                                      check_ws, check_workspace_bytes(), stream);
     };
-    const SettleArgs settle = {cw, open, profile_size((unsigned long long)((__int128)M * N * batch)), chk ? chk->out : nullptr};
+    const SettleArgs settle = {cw, open_records(cw, (size_t)ntiles), profile_size((unsigned long long)((__int128)M * N * batch)), chk ? chk->out : nullptr};
     if (parts >= 2) {
         // the reduction in parts, then one pass that adds them and forms (and checks) the bound
         const long groups = Kp / SBK;
@@ -1571,9 +1566,8 @@ static bool epilogue_check_without_parts(long M, long N, long K, long batch, con
 
 // The screen of a checked bound (linear_screen.hip).  Whether one goes ahead of the exact route: the bound itself is not asked for,
 // and its constants allow it.
-// A workspace that has no room for what the screen takes beyond the exact route, `extra` bytes at `at`, gets none.
-static bool screened(long K, const float* bias, const float* tau, const tao_fp_model& md, const SplitCheckHost* chk, size_t at, size_t extra, size_t ws_bytes) {
-    if (!chk || tau || K <= 0 || ws_bytes < at + extra || (md.flags & TAO_FLAG_CHECK_IN_EPILOGUE) || chk->ldy >= kScreenMaxLd) return false;
+static bool screened(long M, long N, long K, long batch, const float* bias, const float* tau, const tao_fp_model& md, const SplitCheckHost* chk) {
+    if (!chk || tau || K <= 0 || open_tiles_of(M, N, batch) > kOpenRoom || (md.flags & TAO_FLAG_CHECK_IN_EPILOGUE) || chk->ldy >= kScreenMaxLd) return false;
     const long Kp_ = K + (bias ? 1 : 0);
     const double uflow = (md.flags & TAO_FLAG_UNDERFLOW_TERMS) ? (double)Kp_ * 0x1p-148 : 0.0;
     return screen_usable(K, md.u, gamma_up(Kp_, md) * kGuard, chk->alpha, uflow);
@@ -1585,9 +1579,9 @@ static CheckWorkspace core_check_workspace(void* rest, long M, long N, long K, l
     return carve_check_workspace(static_cast<char*>(rest) + partial_bytes);
 }
 static int run_screen(const ScreenOperand& A, const ScreenOperand& W, const float* bias, long M, long N, long K, long batch,
-                      const tao_fp_model& md, const SplitCheckHost* chk, const CheckWorkspace& cw, OpenTile* open, hipStream_t st) {
+                      const tao_fp_model& md, const SplitCheckHost* chk, const CheckWorkspace& cw, hipStream_t st) {
     const ScreenCheck sc = {chk->claimed, chk->ref, chk->ldy, chk->strideY, chk->alpha, chk->eps_rel};
-    return launch_screen(A, W, bias, M, N, K, batch, gamma_up(K + (bias ? 1 : 0), md) * kGuard, sc, cw, open, st);
+    return launch_screen(A, W, bias, M, N, K, batch, gamma_up(K + (bias ? 1 : 0), md) * kGuard, sc, cw, open_records(cw, open_tiles_of(M, N, batch)), st);
 }
 
 // Validation shared by the entry points below (everything but the operands themselves).
@@ -1658,9 +1652,7 @@ static int split_run(const float* A, const float* W, const float* bias, float* t
     // not a launch whose short reduction is better served by the tile walk.
     const bool rows_ok = K > 0 && K % SBK == 0 && N <= 2 * STILE && aligned(A, 16) && lda % 4 == 0 && strideA % 4 == 0 &&
                          (__int128)M * lda < ((__int128)1 << 40);
-    const size_t open_at = round_up_256(need);
-    const bool scr = screened(K, bias, tau, md, chk, open_at, open_bytes(M, N, batch), ws_bytes) && !(rows_ok && lda >= kScreenMaxLd);
-    OpenTile* const open = scr ? reinterpret_cast<OpenTile*>(wsb + open_at) : nullptr;
+    const bool scr = screened(M, N, K, batch, bias, tau, md, chk) && !(rows_ok && lda >= kScreenMaxLd);
     const bool in_load = rows_ok && (scr || (split_k_parts(M, N, K, batch) < 2 && K / SBK > kWalkMaxGroups));
     const CheckWorkspace cw = core_check_workspace(rest, M, N, K, batch);
     bool cleared = false;
@@ -1669,18 +1661,18 @@ static int split_run(const float* A, const float* W, const float* bias, float* t
         // are checked by the combining pass, which needs none)
         cleared = scr || epilogue_check_without_parts(M, N, K, batch, md, chk);
         const SplitOperand ops[2] = {{W, N, K, ldw, shared_w ? 1 : batch, strideW, W3, trans_w ? TRANSPOSED : STRAIGHT}, {A, M, K, lda, batch, strideA, A3, STRAIGHT}};
-        launch_split3(ops, in_load ? 1 : 2, scr ? screen_clear(cw, open, M, N, batch) : cleared ? clear_job(cw, kMaxCheckBlocks) : ClearJob{}, st);
+        launch_split3(ops, in_load ? 1 : 2, scr ? screen_clear(cw, M, N, batch) : cleared ? clear_job(cw, kMaxCheckBlocks) : ClearJob{}, st);
     }
     if (scr) {
         const long groups = (K + SBK - 1) / SBK;
         ScreenOperand oa = {A3, groups * ((M + STILE - 1) / STILE) * kBlock, 0, nullptr};
         if (in_load) oa = {A, strideA * 4, lda, nullptr};
         const ScreenOperand ow = {W3, shared_w ? 0 : groups * ((N + STILE - 1) / STILE) * kBlock, 0, nullptr};
-        rc = run_screen(oa, ow, bias, M, N, K, batch, md, chk, cw, open, st);
+        rc = run_screen(oa, ow, bias, M, N, K, batch, md, chk, cw, st);
         if (rc != TAO_OK) return rc;
     }
     return split_core(A3, W3, bias, tau, M, N, K, ldt, batch, strideT, shared_w, md, rest, stream, chk, cleared,
-                      in_load ? A : nullptr, lda, strideA, nullptr, open);
+                      in_load ? A : nullptr, lda, strideA, nullptr, scr);
 }
 
 // The same on images the caller has prepared with tao_split_operand.
@@ -1703,22 +1695,20 @@ static int images_run(const void* A_image, const void* W_image, const float* bia
     const unsigned short* A3 = static_cast<const unsigned short*>(A_image);
     const unsigned short* W3 = static_cast<const unsigned short*>(W_image);
     bool cleared = false;
-    const size_t open_at = round_up_256(need);
-    OpenTile* open = nullptr;
-    if (screened(K, bias, tau, md, chk, open_at, open_bytes(M, N, batch), ws_bytes)) {
-        open = reinterpret_cast<OpenTile*>(static_cast<char*>(ws) + open_at);
+    const bool scr = screened(M, N, K, batch, bias, tau, md, chk);
+    if (scr) {
         hipStream_t st = (hipStream_t)stream;
         const CheckWorkspace cw = core_check_workspace(ws, M, N, K, batch);
         cleared = true;
-        launch_clear(screen_clear(cw, open, M, N, batch), st);
+        launch_clear(screen_clear(cw, M, N, batch), st);
         const long groups = (K + SBK - 1) / SBK;
         const ScreenOperand oa = {A3, groups * ((M + STILE - 1) / STILE) * kBlock, 0, nullptr};
         const ScreenOperand ow = {W3, sw ? 0 : groups * ((N + STILE - 1) / STILE) * kBlock, 0, nullptr};
-        rc = run_screen(oa, ow, bias, M, N, K, batch, md, chk, cw, open, st);
+        rc = run_screen(oa, ow, bias, M, N, K, batch, md, chk, cw, st);
         if (rc != TAO_OK) return rc;
     }
     return split_core(A3, W3, bias, tau, M, N, K, ldt, batch, strideT, sw, md, ws, stream, chk, cleared,
-                      nullptr, 0, 0, nullptr, open);
+                      nullptr, 0, 0, nullptr, scr);
 }
 }  // namespace tao
 
@@ -1802,22 +1792,22 @@ static int conv_split_run(const float* x, const float* w, const float* bias, flo
     cv.H = (int)H; cv.W = (int)W; cv.C = (int)C; cv.OW = (int)OW; cv.S = (int)S;
     cv.sh = (int)stride_h; cv.sw = (int)stride_w; cv.ph = (int)pad_h; cv.pw = (int)pad_w; cv.dh = (int)dil_h; cv.dw = (int)dil_w;
     cv.ohow = (unsigned)(OH * OW);
-    const size_t open_at = round_up_256(need), pixels_at = open_at + open_bytes(M, N, 1), pixel_bytes = conv_pixel_bytes(batch, H, W, C);
-    const bool scr = pixel_bytes > 0 && screened(K, bias, tau, md, chk, open_at, open_bytes(M, N, 1) + pixel_bytes, ws_bytes);
-    OpenTile* const open = scr ? reinterpret_cast<OpenTile*>(wsb + open_at) : nullptr;
+    // (a workspace without room for the input's magnitudes, as the exact route needs none, gets no screen)
+    const size_t pixel_bytes = conv_pixel_bytes(batch, H, W, C), pixels_at = round_up_256(need);
+    const bool scr = pixel_bytes > 0 && ws_bytes >= pixels_at + pixel_bytes && screened(M, N, K, 1, bias, tau, md, chk);
     const bool cleared = scr || epilogue_check_without_parts(M, N, K, 1, md, chk);
     const CheckWorkspace cw = carve_check_workspace(rest);
     unsigned short* px = reinterpret_cast<unsigned short*>(wsb + pixels_at);
     const SplitOperand ops[2] = {{w, N, K, K, 1, 0, W3, STRAIGHT}, {x, 1, batch * H * W * C, 0, 1, 0, px, MAGNITUDES}};
-    launch_split3(ops, scr ? 2 : 1, scr ? screen_clear(cw, open, M, N, 1) : cleared ? clear_job(cw, kMaxCheckBlocks) : ClearJob{}, (hipStream_t)stream);
+    launch_split3(ops, scr ? 2 : 1, scr ? screen_clear(cw, M, N, 1) : cleared ? clear_job(cw, kMaxCheckBlocks) : ClearJob{}, (hipStream_t)stream);
     if (scr) {
         const ScreenPixels pixels = {cv.H, cv.W, cv.C, cv.OW, cv.S, cv.sh, cv.sw, cv.ph, cv.pw, cv.dh, cv.dw, cv.ohow, cv.C / SBK,
                                      (unsigned)(batch * H * W * C * 2)};
         const ScreenOperand oa = {px, 0, 0, &pixels}, ow = {W3, 0, 0, nullptr};
-        rc = run_screen(oa, ow, bias, M, N, K, 1, md, chk, cw, open, (hipStream_t)stream);
+        rc = run_screen(oa, ow, bias, M, N, K, 1, md, chk, cw, (hipStream_t)stream);
         if (rc != TAO_OK) return rc;
     }
-    return split_core(nullptr, W3, bias, tau, M, N, K, N, 1, M * N, true, md, rest, stream, chk, cleared, x, K, 0, &cv, open);
+    return split_core(nullptr, W3, bias, tau, M, N, K, N, 1, M * N, true, md, rest, stream, chk, cleared, x, K, 0, &cv, scr);
 }
 }  // namespace tao
 
@@ -1838,7 +1828,7 @@ size_t tao_conv2d_split_workspace_bytes(long batch, long H, long W, long C, long
     if (tao::conv_geometry(batch, H, W, C, Cout, R, S, stride_h, stride_w, pad_h, pad_w, dil_h, dil_w, &OH, &OW, &M, &K) != TAO_OK) return 0;
     const size_t img = (M == 0 || Cout == 0) ? 0 : tao::image_bytes(Cout, K, 1);
     const size_t need = img + tao::core_workspace_bytes(M, Cout, K, 1, with_check != 0);
-    return with_check && img ? tao::round_up_256(need) + tao::open_bytes(M, Cout, 1) + tao::conv_pixel_bytes(batch, H, W, C) : need;
+    return with_check && img ? tao::round_up_256(need) + tao::conv_pixel_bytes(batch, H, W, C) : need;
 }
 
 int tao_bound_conv2d_split(const float* x, const float* w, const float* bias, float* tau,
@@ -1874,7 +1864,7 @@ size_t tao_bound_check_linear_workspace_bytes(long M, long N, long K, long batch
     const size_t a = (K > 0 && !empty) ? tao::image_bytes(M, K, batch) : 0;
     const size_t w = (K > 0 && !empty) ? tao::image_bytes(N, K, shared_w ? 1 : batch) : 0;
     if (K > 0 && !empty && (a == 0 || w == 0)) return 0;
-    return tao::with_open(a + w + tao::core_workspace_bytes(M, N, K, batch, true), M, N, K, batch);
+    return a + w + tao::core_workspace_bytes(M, N, K, batch, true);
 }
 
 int tao_bound_check_linear_in_epilogue(long M, long N, long K, long batch) {

@@ -1,4 +1,4 @@
-"""What the screen of a checked matmul bound leaves open, and what settles it: the records behind the workspace hold the comparisons
+"""What the screen of a checked matmul bound leaves open, and what settles it: the records in the workspace hold the comparisons
 that the one product cannot decide, by place or by block, and nothing else; the profile is the stored bound's in every case."""
 import numpy as np
 import pytest
@@ -26,7 +26,8 @@ def _same(got, want):
 
 class Product:
     """A checked bound on a workspace of exactly the size asked for, its stored bound, and the records after a call.  form: both
-    operands as images, both as matrices, or a 1 x 1 convolution (rows its pixels)."""
+    operands as images, both as matrices, or a 1 x 1 convolution (rows its pixels).  The workspace: images of the operands, sums of a reduction's
+    parts, the check's partial results (64 histograms of 2048 words, then the records), a stored bound, a convolution's magnitudes."""
 
     def __init__(self, tao, form, batch, M, N, K, seed=0):
         self.tao, self.batch, self.M, self.N = tao, batch, M, N
@@ -35,10 +36,12 @@ class Product:
         A, W = torch.randn((*shape, M, K), generator=g, device="cuda"), torch.randn((*shape, N, K), generator=g, device="cuda") * 0.1
         self.A, self.W = A, W
         self.out = tao.new_profile_buffer(A.device)
-        behind = 0                                           # bytes of the workspace behind the records
+        r256 = lambda n: (int(n) + 255) // 256 * 256
+        behind = r256(tao.tao_check_workspace_bytes(1)) + (r256(4 * batch * M * N) if K < 1025 else 0)
         if form == "pixels":
             assert batch == 1 and tao.tao_conv2d_split_supported((1, 1, M, K), (N, 1, 1, K))
-            n, behind = tao.lib().tao_conv2d_split_workspace_bytes(1, 1, M, K, N, 1, 1, 1, 1, 0, 0, 1, 1, 1), M * K * 2 + 64
+            n = tao.lib().tao_conv2d_split_workspace_bytes(1, 1, M, K, N, 1, 1, 1, 1, 0, 0, 1, 1, 1)
+            behind += M * K * 2 + 64
             self.bound = lambda: tao.tao_bound_conv2d_split(A.view(1, 1, M, K), W.view(N, 1, 1, K)).view(M, N)
             self.call = lambda y, c, ws: tao.tao_bound_check_conv2d(A.view(1, 1, M, K), W.view(N, 1, 1, K), None, y.view(1, 1, M, N), c.view(1, 1, M, N),
                                                                     out=self.out, ws=ws)
@@ -52,7 +55,7 @@ class Product:
                 n = tao.tao_bound_check_linear_workspace_bytes(M, N, K, batch, batch == 1)
                 self.call = lambda y, c, ws: tao.tao_bound_check_linear(A, W, None, y, c, out=self.out, ws=ws)
         self.tiles = (batch, (M + 127) // 128, (N + 127) // 128)
-        self.at = int(n) - behind - (int(np.prod(self.tiles)) * 64 + 255) // 256 * 256
+        self.at = int(n) - behind + 64 * 2048 * 4
         self.ws = torch.empty(int(n), dtype=torch.uint8, device="cuda")
         # (outputs of the size of their bounds, so that a claim's rounding moves it by no more than 2^-23 of the bound)
         self.tau = self.bound()
@@ -144,3 +147,17 @@ def test_open_regions(tao, form, batch, M, N, K):
     rows, cols = torch.arange(M, device="cuda")[:, None], torch.arange(N, device="cuda")[None, :]
     for where in (rows >= 0, rows < M // 3, cols >= N // 2, (rows // 128 + cols // 128) % 5 == 0, torch.rand((M, N), generator=p.g, device="cuda") < 0.01):
         p.check(torch.where(where, near, p.honest()))
+
+
+def test_more_tiles_than_whole_records(tao):
+    """25000 batch entries are as many tiles: their records are the state alone, without places."""
+    B, M, N, K = 25000, 2, 3, 40
+    g = torch.Generator(device="cuda").manual_seed(2)
+    A, W = torch.randn((B, M, K), generator=g, device="cuda"), torch.randn((B, N, K), generator=g, device="cuda")
+    tau = tao.tao_bound_linear_split(A, W)
+    y = tau * torch.randn(tau.shape, generator=g, device="cuda")
+    honest = y * (1 + 2.0 ** -23)
+    for share in (0.0, 1e-4, 0.3, 1.0):
+        near = (y.double() + (1 + 2e-3 * torch.randn(y.shape, generator=g, device="cuda", dtype=torch.float64)) * tau.double()).float()
+        c = torch.where(torch.rand(y.shape, generator=g, device="cuda") < share, near, honest)
+        _same(tao.tao_bound_check_linear(A, W, None, y, c), tao.tao_check_and_profile(c, y, tau))
