@@ -119,14 +119,18 @@ __device__ __forceinline__ void split_pack8(const float (&v)[8], uintx4& H, uint
 
 // One thread per 8 consecutive k of one row, for one or two operands in one launch; a workgroup's unit is 64 rows of one 32-k group,
 // 4 KB contiguous per piece.  STRAIGHT: four threads to a row, 128 contiguous bytes; units run along k, so the workgroups in
-// flight read rows on.  TRANSPOSED: the source is [K][ld] with the row index running along its columns (W stored K x N); the lanes of
-// a wavefront take the unit's rows.  MAGNITUDES: no image but the BF16 magnitudes alone, in the source's layout (K a
-// multiple of 8, one row), and 64 bytes of zeros behind them.
+// flight read rows on; of an operand of up to 16 rows and many units each is one wavefront's (4 x 100000 3.8 us, with a workgroup each 5.6;
+// 8 x 4096, 128 units, 2.7 / 2.6).  TRANSPOSED: the source is [K][ld] with the row index running along its columns (W stored
+// K x N); the lanes of a wavefront take the unit's rows.  MAGNITUDES: no image but the BF16 magnitudes alone, in the source's
+// layout (K a multiple of 8, one row), and 64 bytes of zeros behind them.
 // What bounds it: HBM for large operands, else one unit's latency -- its position takes scalar 32-bit arithmetic only (a thread's own
 // 64-bit divisions, units of 256 k, which a short reduction leaves empty, and loads behind branches took 8 x 8192 x 128 19.2 us, now
 // 13.6, 1111 x 1001 5.2, now 4.2, 8 x 128 x 2048 transposed 10.3, now 8.1; 12288 x 4096 103, at 4.9 TB/s).
 enum { STRAIGHT, TRANSPOSED, MAGNITUDES };
-struct SplitOperand { const float* src; long rows, K, ld, batch, stride; unsigned short* dst; int form; };
+struct SplitOperand {
+    const float* src; long rows, K, ld, batch, stride; unsigned short* dst; int form;
+    __host__ __device__ bool flat() const { return form == STRAIGHT && rows <= 16 && (K + SBK - 1) / SBK * batch >= 512; }
+};
 struct SplitOperands {
     SplitOperand op[2];
     long first[3];                     // workgroups [first[o], first[o + 1]) serve operand o
@@ -142,8 +146,11 @@ __global__ __launch_bounds__(256) void split3_bf16(SplitOperands a) {
     // (side job for the launch that follows: clears the partial results of a check, so that no launch of its own is needed for that)
     clear_words(a.clear, (long)blockIdx.x * 256 + threadIdx.x, (long)gridDim.x * 256);
     const int o = (long)blockIdx.x >= a.first[1] ? 1 : 0;
-    const SplitOperand& p = a.op[o];
-    const long nblk = a.first[o + 1] - a.first[o], blk = (long)blockIdx.x - a.first[o];
+    // (both operands' fields are requested at once: the choice would be one more step of the chain of scalar loads)
+    const SplitOperand &q0 = a.op[0], &q1 = a.op[1];
+    const SplitOperand p = {o ? q1.src : q0.src, o ? q1.rows : q0.rows, o ? q1.K : q0.K, o ? q1.ld : q0.ld, o ? q1.batch : q0.batch,
+                            o ? q1.stride : q0.stride, o ? q1.dst : q0.dst, o ? q1.form : q0.form};
+    const long nblk = o ? a.first[2] - a.first[1] : a.first[1], blk = o ? (long)blockIdx.x - a.first[1] : (long)blockIdx.x;
     if (p.form == MAGNITUDES) {
         for (long i = blk * 256 + threadIdx.x; i < p.K / 8 + 4; i += nblk * 256) {
             uintx4 H = {0, 0, 0, 0};
@@ -163,21 +170,23 @@ __global__ __launch_bounds__(256) void split3_bf16(SplitOperands a) {
     // rows up to the next multiple of four are zeros: the product's epilogue looks at its sums by groups of four rows
     const long rows4 = (p.rows + 3) & ~3L;
     const unsigned units = (unsigned)(groups * (unsigned long long)rgroups * p.batch);
-    const int urow = trans ? threadIdx.x & 63 : threadIdx.x >> 2, uch = trans ? threadIdx.x >> 6 : threadIdx.x & 3;
-    for (unsigned u = (unsigned)blk; u < units; u += (unsigned)nblk) {
+    const bool flat = p.flat();
+    const int tid = threadIdx.x, urow = trans ? tid & 63 : (flat ? tid & 63 : tid) >> 2, uch = trans ? tid >> 6 : tid & 3;
+    const unsigned first = flat ? (unsigned)blk * 4 + __builtin_amdgcn_readfirstlane(tid >> 6) : (unsigned)blk;
+    for (unsigned u = first; u < units; u += (unsigned)nblk * (flat ? 4 : 1)) {
         const unsigned rz = u / groups, g = u - rz * groups, z = rz / rgroups, rg = rz - z * rgroups;
         const long row = (long)rg * 64 + urow, k0 = (long)g * SBK + uch * 8;
         if (row >= rows4) continue;
         const float* s = p.src + z * p.stride;
         float v[8];
-        if (!trans && row < p.rows && k0 + 8 <= p.K) {
-            const floatx4u* q = reinterpret_cast<const floatx4u*>(s + row * p.ld + k0);
+        // (positions beyond the operand read its last row or element: loads without branches all leave at once)
+        const long rc = row < p.rows ? row : p.rows - 1;
+        if (!trans && k0 + 8 <= p.K) {
+            const floatx4u* q = reinterpret_cast<const floatx4u*>(s + rc * p.ld + k0);
             const floatx4u x = q[0], y = q[1];
 #pragma unroll
-            for (int j = 0; j < 4; ++j) { v[j] = x[j]; v[4 + j] = y[j]; }
+            for (int j = 0; j < 4; ++j) { v[j] = row < p.rows ? x[j] : 0.f; v[4 + j] = row < p.rows ? y[j] : 0.f; }
         } else {
-            // (positions beyond the operand read its last element: loads without branches all leave at once)
-            const long rc = row < p.rows ? row : p.rows - 1;
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
                 const long kc = k0 + j < p.K ? k0 + j : p.K - 1;
@@ -1339,7 +1348,8 @@ static void launch_split3(const SplitOperand* ops, int n, const ClearJob& clear,
         const SplitOperand& p = ops[o];
         a.op[o] = p;
         const long groups = (p.K + SBK - 1) / SBK;
-        const long b = p.form == MAGNITUDES ? (p.K / 8 + 4 + 255) / 256 : groups * ((p.rows + 63) / 64) * p.batch;      // units of split3_bf16
+        const long units = groups * ((p.rows + 63) / 64) * p.batch;
+        const long b = p.form == MAGNITUDES ? (p.K / 8 + 4 + 255) / 256 : p.flat() ? (units + 3) / 4 : units;
         a.first[o] = first;
         first += b < 1 ? 1 : (b > 256L * 64 ? 256L * 64 : b);
     }

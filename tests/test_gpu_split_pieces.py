@@ -134,3 +134,20 @@ def test_conv_of_finite_operands_beyond_the_range(tao):
     assert not torch.isnan(tau).any()
     assert (tau.double() >= exact * (1 - slack)).all()
     assert (tau.double() <= exact * (1 + 1e-6) * (1 + slack))[exact * (1 + 1e-6) < 2.0 ** 128].all()
+
+
+@pytest.mark.parametrize("rows", [1, 3, 4, 13, 16, 17])
+@pytest.mark.parametrize("batch,K", [(1, 511 * 32), (1, 512 * 32 + 5), (3, 6000), (600, 9), (1, 33)])
+def test_images_of_few_rows(tao, rows, batch, K):
+    """The image of a few rows, cut by workgroups or by wavefronts, is what the same rows have in the image of more (the layout does not depend on
+    the number of rows up to 128): every piece of every row that exists, and zeros up to a multiple of four rows and of 32 k."""
+    g = torch.Generator(device="cuda").manual_seed(rows + K)
+    few = torch.randn((batch, rows, K), generator=g, device="cuda")
+    more = torch.zeros((batch, 40, K), device="cuda")
+    more[:, :rows] = few
+    images = []
+    for x in (few, more):
+        out = torch.full((tao.tao_split_image_bytes(x.shape[1], K, batch),), 0x5a, dtype=torch.uint8, device="cuda")
+        n = batch * ((K + 31) // 32) * 3 * 128 * 64
+        images.append(tao.tao_split_operand(x, out=out)[:n].view(-1, 128, 64)[:, :(rows + 3) // 4 * 4])
+    assert torch.equal(*images)
