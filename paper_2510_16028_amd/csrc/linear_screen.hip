@@ -20,9 +20,10 @@
 // enqueued behind the screen, decides these and nothing else.  So every profile is the exact route's, bit for bit.
 // The errors' bins and maximum do not depend on tau: quick settlement as in tao_check.hpp, exact arithmetic where
 // an estimate does not decide.
-// A workgroup that has met a tile with much open everywhere forms no further products and leaves all comparisons open: where that route
-// forms most bounds anyway they are work for nothing (us of the whole call, every claim at its bound, with all products / so:
-// 2048 x 12288 over 4096 1577 / 1425, the 3 x 3 convolution of 32 x 56 x 56 x 256 1378 / 1214, 8 x 8192 x 128 over 2048 428 / 364).
+// A workgroup forms no further products and leaves all comparisons open once all of its wavefronts have found much open in a tile, or some
+// in two tiles running: where that route forms most bounds anyway they are work for nothing (us of the whole call, every claim at its
+// bound, with all products / so: 2048 x 12288 over 4096 1577 / 1425, the 3 x 3 convolution of 32 x 56 x 56 x 256 1378 / 1214, 8 x 8192 x 128
+// over 2048 428 / 364; 8192 x 8192 over 8192, heavy-tailed operands and two thirds of the claims 1 % from their bounds, 7690 / 6990).
 #include <cmath>
 #include <type_traits>
 #include "tao_device.hpp"
@@ -146,7 +147,7 @@ __global__ __launch_bounds__(WVM * WVN * 64, WVM * WVN * PER_CU / 4) void screen
     const unsigned t_end = (unsigned)((unsigned long long)p.ntiles * (xcd + 1) >> 3);
     const unsigned per_z = p.tiles_m * p.tiles_n;
     unsigned opened = 0;                                     // records that this wavefront was the first to write to
-    unsigned heavy_before = 0;
+    unsigned heavy_before = 0, by_before = 0;                // (as of the last tile, and by how many wavefronts in that one)
     int groups = p.groups;                                   // 0: the products are not formed any more
     for (unsigned t = (unsigned)((unsigned long long)p.ntiles * xcd >> 3) + (blockIdx.x >> 3); t < t_end; t += per) {
         const unsigned z = t / per_z, b = t - z * per_z;
@@ -304,9 +305,9 @@ __global__ __launch_bounds__(WVM * WVN * 64, WVM * WVN * PER_CU / 4) void screen
         };
 
         __syncthreads();                                     // the strips of the tile before have been read
-        const unsigned heavy_now = __builtin_amdgcn_readfirstlane(newest(&heavy));
-        if (heavy_now - heavy_before == WAVES) groups = 0;
-        heavy_before = heavy_now;
+        const unsigned heavy_now = __builtin_amdgcn_readfirstlane(newest(&heavy)), by = heavy_now - heavy_before;
+        if (by == WAVES || (by && by_before)) groups = 0;
+        heavy_before = heavy_now; by_before = by;
         constexpr int COPIES = GPS * (NA + NW);
         const int slabs = (groups + GPS - 1) / GPS;
 #pragma unroll
