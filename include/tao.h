@@ -201,8 +201,8 @@ size_t tao_bound_check_linear_workspace_bytes(long M, long N, long K, long batch
  *                              stride `stride` (trans == 0), or [batch][K][rows] (trans != 0: a weight
  *                              stored K x N); rows = M for the A side, N for the W side.  image: DEVICE,
  *                              256-byte aligned, at least tao_split_image_bytes(rows, K, batch) bytes
- *                              (about 6 bytes per element, rows and K padded to 128 and 32).  An image
- *                              depends on (rows, K, batch) only and may be used on either side.
+ *                              (about 6 bytes per element, rows and K padded to 128 and 32), fewer than 65536
+ *                              batch entries.  An image depends on (rows, K, batch) only and may be used on either side.
  *   tao_bound_linear_images    tao_bound_linear_split on two images: the same tau, bit for bit.
  *                              shared_w != 0: one W image for every batch entry.  ws: DEVICE scratch of
  *                              tao_linear_images_workspace_bytes(M, N, K, batch) bytes (0 unless the

@@ -36,7 +36,7 @@
 // 2^-110 in magnitude lose low bits of their lo piece in BF16's subnormal range; that piece is then raised
 // (see split_pack8), so the bound stays an upper bound but can exceed 1e-6 there.  Sums that reach
 // down into the binary32 subnormal range carry an absolute error instead of a relative one; the
-// epilogue adds a bound on it (see split_run), which is far below 1e-6 of any bound above 2^-120.
+// epilogue adds a bound on it (see split_core), which is far below 1e-6 of any bound above 2^-120.
 //
 // A check needs only the comparisons d <= alpha tau.  Where the caller does not want tau, one BF16 product
 // (linear_screen.hip) decides them first, and the kernels of this file form the bound only if it left one open
@@ -1514,6 +1514,7 @@ static int split_core(const unsigned short* A3, const unsigned short* W3, const 
         p.ksplit = (int)((groups + p.gpp - 1) / p.gpp);             // no empty part
         p.partial = reinterpret_cast<double*>(wsb);
         if (screened) {
+            if (settle.open.words != kOpenWords) return TAO_ERR_SHAPE;      // (cannot happen, as above: the parts are counted in whole records)
             const long wgs = (long)p.ntiles * p.ksplit;              // (the profile's 32 groups have a workgroup each)
             const dim3 grid((unsigned)(wgs < kGroups ? kGroups : wgs));
             if (Af) hipLaunchKernelGGL(absgemm_settle_parts<true>, grid, dim3(kSplitThreads), lds_bytes, st, p, settle);
@@ -1736,7 +1737,7 @@ int tao_split_operand(const float* src, long rows, long K, long ld, int trans, l
     if (!aligned(src, 4)) return TAO_ERR_ALIGN;
     const size_t need = tao::image_bytes(rows, K, batch);
     if (need == 0 || !image || !aligned(image, 256) || image_bytes < need) return TAO_ERR_WORKSPACE;
-    if (batch >= 65536) return TAO_ERR_SHAPE;                      // (second grid dimension)
+    if (batch >= 65536) return TAO_ERR_SHAPE;                      // (an image's limit, whatever a launch could take)
     const SplitOperand op = {src, rows, K, ld, batch, stride, static_cast<unsigned short*>(image), trans ? TRANSPOSED : STRAIGHT};
     launch_split3(&op, 1, ClearJob{}, (hipStream_t)stream);
     return launch_status();

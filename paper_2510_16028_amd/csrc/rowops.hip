@@ -3,7 +3,7 @@
 // One "row group" of TPR threads (a wavefront, or a whole 256-thread workgroup
 // for long rows) owns one row.  The row is read once with 16-byte loads and
 // kept in registers (V vectors per thread); row statistics are accumulated in
-// binary64 and combined with wavefront shuffles (plus one LDS exchange when the
+// binary64 and combined over the lanes by register moves (plus one LDS exchange when the
 // group spans four wavefronts); the bound is written once.  HBM traffic is the
 // algorithmic minimum: each input element read once, each tau written once.
 // Rows longer than 8192 columns take the V == 0 variant, which re-reads the row

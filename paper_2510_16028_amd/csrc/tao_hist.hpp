@@ -53,7 +53,6 @@ __device__ __forceinline__ void flush_histogram(const unsigned int* hist, unsign
     }
 }
 
-struct RankQuery { unsigned int num, den; };
 template <int NQ> struct Ranks { unsigned long long at[NQ]; };        // ranks max(1, ceil(n num / den)), formed on the host; 0: no elements
 
 // Second level, one workgroup (THREADS threads) per group `grp` of 64 bins: sums the partial histograms
