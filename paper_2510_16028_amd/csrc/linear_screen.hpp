@@ -34,7 +34,8 @@ static_assert(kScreenSlots == kWave, "a lane for each");
 // after the other), in the room of the partial results that a screened check does not use.  A record's first word is its state -- bit 4 r + c:
 // every comparison of block (r, c), 32 x 32; from bit 16 on: how many places were asked for --, the second the number of parts of the
 // reduction that the exact route has finished, the others are places: 128 row + column, or kNoPlace.  All zero before the screen.  Outputs of
-// more tiles than fit so (0.4 G outputs) have records of the state alone, and those of more than these (6.4 G) are not screened.
+// more tiles than fit so (0.4 G outputs) have their records where a short reduction's stored bound would lie, or records of the state
+// alone; those of more than these (6.4 G, over more than 1024 k) are not screened.
 constexpr int kOpenTile = 128, kOpenWords = 16;
 constexpr unsigned kNoPlace = ~0u;
 struct OpenRecords {
@@ -47,15 +48,19 @@ constexpr size_t kOpenRoom = (size_t)(kMaxCheckBlocks - kScreenSlots) * kBins;  
 inline size_t open_tiles_of(long M, long N, long batch) {
     return (size_t)((M + kOpenTile - 1) / kOpenTile) * (size_t)((N + kOpenTile - 1) / kOpenTile) * (size_t)batch;
 }
-inline OpenRecords open_records(const CheckWorkspace& w, size_t tiles) {
-    return {w.hist + (size_t)kScreenSlots * kBins, tiles * kOpenWords <= kOpenRoom ? kOpenWords : 1};
+// bound, bound_bytes: the stored bound's place (16-byte aligned) and size.  words 0: no room.
+inline OpenRecords open_records(const CheckWorkspace& w, size_t tiles, void* bound, size_t bound_bytes) {
+    unsigned* const spare = w.hist + (size_t)kScreenSlots * kBins;
+    if (tiles * kOpenWords <= kOpenRoom) return {spare, kOpenWords};
+    if (tiles * kOpenWords * 4 <= bound_bytes) return {static_cast<unsigned*>(bound), kOpenWords};
+    return {spare, tiles <= kOpenRoom ? 1 : 0};
 }
-// What a launch before a check clears, in 16-byte words: of `slots` partial results the histograms and coarse counts, `more` words behind the
-// histograms, and all counters.
-struct ClearJob { void* at[3]; long words[3]; };
-inline ClearJob clear_job(const CheckWorkspace& w, int slots, size_t more = 0) {
-    return {{w.hist, w.coarse, w.stats},
-            {(long)(((size_t)slots * kBins + more + 3) / 4), (long)slots * kGroups / 4, (long)(kMaxCheckBlocks * sizeof(BlockStats) / 16)}};
+// What a launch before a check clears, in 16-byte words: of `slots` partial results the histograms and coarse counts, all counters, and
+// the records of `tiles` tiles.
+struct ClearJob { void* at[4]; long words[4]; };
+inline ClearJob clear_job(const CheckWorkspace& w, int slots, const OpenRecords& open = {nullptr, 0}, size_t tiles = 0) {
+    return {{w.hist, w.coarse, w.stats, open.first},
+            {(long)slots * kBins / 4, (long)slots * kGroups / 4, (long)(kMaxCheckBlocks * sizeof(BlockStats) / 16), (long)((tiles * open.words + 3) / 4)}};
 }
 static_assert(kMaxCheckBlocks * sizeof(BlockStats) % 16 == 0, "cleared in 16-byte words");
 

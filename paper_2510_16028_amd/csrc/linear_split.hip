@@ -138,7 +138,7 @@ struct SplitOperands {
 };
 __device__ __forceinline__ void clear_words(const ClearJob& c, long i0, long step) {
 #pragma unroll
-    for (int j = 0; j < 3; ++j)
+    for (int j = 0; j < 4; ++j)
         for (long i = i0; i < c.words[j]; i += step) static_cast<uintx4*>(c.at[j])[i] = uintx4{0, 0, 0, 0};
 }
 typedef float floatx4u __attribute__((ext_vector_type(4), aligned(4)));          // (16-byte loads need no more than 4-byte alignment)
@@ -1274,10 +1274,13 @@ static size_t core_workspace_bytes(long M, long N, long K, long batch, bool chec
     }
     return b;
 }
-// What the launch before a screen clears.
-static ClearJob screen_clear(const CheckWorkspace& cw, long M, long N, long batch) {
-    const size_t tiles = open_tiles_of(M, N, batch);
-    return clear_job(cw, kScreenSlots, tiles * (size_t)open_records(cw, tiles).words);
+// The records of what a screen leaves open, within that, and what the launch before the screen clears.
+static OpenRecords core_open_records(const CheckWorkspace& cw, long M, long N, long K, long batch) {
+    const size_t bound = K < kEpilogueCheckMinK ? round_up_256((size_t)M * N * batch * 4) : 0;
+    return open_records(cw, open_tiles_of(M, N, batch), reinterpret_cast<char*>(cw.hist) + round_up_256(check_workspace_bytes()), bound);
+}
+static ClearJob screen_clear(const CheckWorkspace& cw, long M, long N, long K, long batch) {
+    return clear_job(cw, kScreenSlots, core_open_records(cw, M, N, K, batch), open_tiles_of(M, N, batch));
 }
 }  // namespace tao
 
@@ -1505,7 +1508,7 @@ static int split_core(const unsigned short* A3, const unsigned short* W3, const 
         return tao_check_and_profile(chk->claimed, chk->ref, tau, M * N * batch, chk->alpha, chk->eps_rel, chk->out,
                                      check_ws, check_workspace_bytes(), stream);
     };
-    const SettleArgs settle = {cw, open_records(cw, (size_t)ntiles), profile_size((unsigned long long)((__int128)M * N * batch)), chk ? chk->out : nullptr};
+    const SettleArgs settle = {cw, screened ? core_open_records(cw, M, N, K, batch) : OpenRecords{}, profile_size((unsigned long long)((__int128)M * N * batch)), chk ? chk->out : nullptr};
     if (parts >= 2) {
         // the reduction in parts, then one pass that adds them and forms (and checks) the bound
         const long groups = Kp / SBK;
@@ -1578,7 +1581,7 @@ static bool epilogue_check_without_parts(long M, long N, long K, long batch, con
 // The screen of a checked bound (linear_screen.hip).  Whether one goes ahead of the exact route: the bound itself is not asked for,
 // and its constants allow it.
 static bool screened(long M, long N, long K, long batch, const float* bias, const float* tau, const tao_fp_model& md, const SplitCheckHost* chk) {
-    if (!chk || tau || K <= 0 || open_tiles_of(M, N, batch) > kOpenRoom || (md.flags & TAO_FLAG_CHECK_IN_EPILOGUE) || chk->ldy >= kScreenMaxLd) return false;
+    if (!chk || tau || K <= 0 || core_open_records({}, M, N, K, batch).words == 0 || (md.flags & TAO_FLAG_CHECK_IN_EPILOGUE) || chk->ldy >= kScreenMaxLd) return false;
     const long Kp_ = K + (bias ? 1 : 0);
     const double uflow = (md.flags & TAO_FLAG_UNDERFLOW_TERMS) ? (double)Kp_ * 0x1p-148 : 0.0;
     return screen_usable(K, md.u, gamma_up(Kp_, md) * kGuard, chk->alpha, uflow);
@@ -1592,7 +1595,7 @@ static CheckWorkspace core_check_workspace(void* rest, long M, long N, long K, l
 static int run_screen(const ScreenOperand& A, const ScreenOperand& W, const float* bias, long M, long N, long K, long batch,
                       const tao_fp_model& md, const SplitCheckHost* chk, const CheckWorkspace& cw, hipStream_t st) {
     const ScreenCheck sc = {chk->claimed, chk->ref, chk->ldy, chk->strideY, chk->alpha, chk->eps_rel};
-    return launch_screen(A, W, bias, M, N, K, batch, gamma_up(K + (bias ? 1 : 0), md) * kGuard, sc, cw, open_records(cw, open_tiles_of(M, N, batch)), st);
+    return launch_screen(A, W, bias, M, N, K, batch, gamma_up(K + (bias ? 1 : 0), md) * kGuard, sc, cw, core_open_records(cw, M, N, K, batch), st);
 }
 
 // Validation shared by the entry points below (everything but the operands themselves).
@@ -1672,7 +1675,7 @@ static int split_run(const float* A, const float* W, const float* bias, float* t
         // are checked by the combining pass, which needs none)
         cleared = scr || epilogue_check_without_parts(M, N, K, batch, md, chk);
         const SplitOperand ops[2] = {{W, N, K, ldw, shared_w ? 1 : batch, strideW, W3, trans_w ? TRANSPOSED : STRAIGHT}, {A, M, K, lda, batch, strideA, A3, STRAIGHT}};
-        launch_split3(ops, in_load ? 1 : 2, scr ? screen_clear(cw, M, N, batch) : cleared ? clear_job(cw, kMaxCheckBlocks) : ClearJob{}, st);
+        launch_split3(ops, in_load ? 1 : 2, scr ? screen_clear(cw, M, N, K, batch) : cleared ? clear_job(cw, kMaxCheckBlocks) : ClearJob{}, st);
     }
     if (scr) {
         const long groups = (K + SBK - 1) / SBK;
@@ -1711,7 +1714,7 @@ static int images_run(const void* A_image, const void* W_image, const float* bia
         hipStream_t st = (hipStream_t)stream;
         const CheckWorkspace cw = core_check_workspace(ws, M, N, K, batch);
         cleared = true;
-        launch_clear(screen_clear(cw, M, N, batch), st);
+        launch_clear(screen_clear(cw, M, N, K, batch), st);
         const long groups = (K + SBK - 1) / SBK;
         const ScreenOperand oa = {A3, groups * ((M + STILE - 1) / STILE) * kBlock, 0, nullptr};
         const ScreenOperand ow = {W3, sw ? 0 : groups * ((N + STILE - 1) / STILE) * kBlock, 0, nullptr};
@@ -1810,7 +1813,7 @@ static int conv_split_run(const float* x, const float* w, const float* bias, flo
     const CheckWorkspace cw = carve_check_workspace(rest);
     unsigned short* px = reinterpret_cast<unsigned short*>(wsb + pixels_at);
     const SplitOperand ops[2] = {{w, N, K, K, 1, 0, W3, STRAIGHT}, {x, 1, batch * H * W * C, 0, 1, 0, px, MAGNITUDES}};
-    launch_split3(ops, scr ? 2 : 1, scr ? screen_clear(cw, M, N, 1) : cleared ? clear_job(cw, kMaxCheckBlocks) : ClearJob{}, (hipStream_t)stream);
+    launch_split3(ops, scr ? 2 : 1, scr ? screen_clear(cw, M, N, K, 1) : cleared ? clear_job(cw, kMaxCheckBlocks) : ClearJob{}, (hipStream_t)stream);
     if (scr) {
         const ScreenPixels pixels = {cv.H, cv.W, cv.C, cv.OW, cv.S, cv.sh, cv.sw, cv.ph, cv.pw, cv.dh, cv.dw, cv.ohow, cv.C / SBK,
                                      (unsigned)(batch * H * W * C * 2)};

@@ -149,9 +149,11 @@ def test_open_regions(tao, form, batch, M, N, K):
         p.check(torch.where(where, near, p.honest()))
 
 
-def test_more_tiles_than_whole_records(tao):
-    """25000 batch entries are as many tiles: their records are the state alone, without places."""
-    B, M, N, K = 25000, 2, 3, 40
+@pytest.mark.parametrize("M,N", [(2, 3), (8, 4)])
+def test_more_tiles_than_whole_records(tao, M, N):
+    """25000 batch entries are as many tiles: their records lie where the bound of so short a reduction would be stored, or, where that is
+    too small for them, are the state alone, without places."""
+    B, K = 25000, 40
     g = torch.Generator(device="cuda").manual_seed(2)
     A, W = torch.randn((B, M, K), generator=g, device="cuda"), torch.randn((B, N, K), generator=g, device="cuda")
     tau = tao.tao_bound_linear_split(A, W)
