@@ -361,7 +361,9 @@ __global__ __launch_bounds__(WVM * WVN * 64, WVM * WVN * PER_CU / 4) void screen
                 if (den <= 0x1p100f && bits <= 0x7f800000u && bits > 16u) known = max(known, bits - 16u);
             }
             // (rows and columns beyond the edge repeat elements that exist)
-            if (known) atomicMax(&largest, known);
+            // (one atomic of a wavefront: 256 lanes' on the one word took 2.3 us; 512 x 3072 over 768 24.7 -> 23.0 us)
+            known = wave_max(known);
+            if (known && lane == 0) atomicMax(&largest, known);
         }
         if (large) large_in = t + 1;
         __syncthreads();                                     // every wavefront is done with the stages
@@ -521,18 +523,15 @@ __global__ __launch_bounds__(WVM * WVN * 64, WVM * WVN * PER_CU / 4) void screen
         if (opened) atomicAdd(&st->flag, opened);
     }
     __syncthreads();
-    // (eight bins a thread, eight threads a group of 64)
-    for (int b8 = tid; b8 < kBins / 8; b8 += THREADS) {
-        unsigned gsum = 0;
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const int bin = b8 * 8 + j;
-            const unsigned cnt = bin <= 2040 ? hist[bin] : 0u;
-            if (cnt) atomicAdd(&p.hist[(size_t)slot * kBins + bin], cnt);
-            gsum += cnt;
-        }
-        gsum = wave_all<0, 3>(gsum, [](unsigned a, unsigned b) { return a + b; });
-        if ((b8 & 7) == 0 && gsum) atomicAdd(&p.coarse[slot * kGroups + b8 / 8], gsum);
+    // (a group of 64 bins to a wavefront: its atomics fall into two lines, and few groups are not empty; with eight bins to a thread
+    // 1111 x 3001 over 1001 took 44.0 us, so 42.3)
+    for (int base = wave * kWave; base < kBins; base += THREADS) {
+        const int bin = base + lane;
+        const unsigned cnt = bin <= 2040 ? hist[bin] : 0u;
+        if (!__any(cnt != 0)) continue;
+        if (cnt) atomicAdd(&p.hist[(size_t)slot * kBins + bin], cnt);
+        const unsigned gsum = wave_sum(cnt);
+        if (lane == 0) atomicAdd(&p.coarse[slot * kGroups + base / kWave], gsum);
     }
 }
 
