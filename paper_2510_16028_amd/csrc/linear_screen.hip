@@ -149,37 +149,55 @@ __global__ __launch_bounds__(WVM * WVN * 64, WVM * WVN * PER_CU / 4) void screen
     unsigned opened = 0;                                     // records that this wavefront was the first to write to
     unsigned heavy_before = 0, by_before = 0;                // (as of the last tile, and by how many wavefronts in that one)
     int groups = p.groups;                                   // 0: the products are not formed any more
-    for (unsigned t = (unsigned)((unsigned long long)p.ntiles * xcd >> 3) + (blockIdx.x >> 3); t < t_end; t += per) {
+    // A tile: its place, and where its claims and outputs begin.
+    struct Tile { unsigned z; long m0, n0; int rows_left, cols_left; const float* C; const float* Y; };
+    auto tile_of = [&](unsigned t) __attribute__((always_inline)) {
         const unsigned z = t / per_z, b = t - z * per_z;
         const unsigned grp = b / (8 * p.tiles_n), in = b - grp * 8 * p.tiles_n;
         const unsigned deep = min(8u, p.tiles_m - grp * 8);
         const unsigned tx = in / deep, ty = grp * 8 + (in - tx * deep);
-        const long m0 = (long)ty * TM, n0 = (long)tx * TN;
-        const int rows_left = (int)min((long)TM, p.M - m0), cols_left = (int)min((long)TN, p.N - n0);
-
-        // claims and outputs of a strip; positions beyond the edge read the edge's elements.  The first strip's are requested before
-        // the product: their latency passes under it.
-        const float* __restrict__ C = p.claimed + (long)z * p.strideY + m0 * p.ldy + n0;
-        const float* __restrict__ Y = p.ref + (long)z * p.strideY + m0 * p.ldy + n0;
-        const int ldy = (int)p.ldy, srow = wm * RM * 32, scol = wn * COLS;
-        floatv4 cv[STEPS], rv[STEPS];
-        auto fetch = [&](int i, int k) __attribute__((always_inline)) {
-            const int row = min(srow + i * 32 + lrow + k * RPI, rows_left - 1) * ldy, col = scol + lcol;
-            if (col + 4 <= cols_left) {
-                const floatx4u* cp = reinterpret_cast<const floatx4u*>(C + (unsigned)(row + col));      // (at any alignment)
-                const floatx4u* rp = reinterpret_cast<const floatx4u*>(Y + (unsigned)(row + col));
-                if (p.stream) { cv[k] = __builtin_nontemporal_load(cp); rv[k] = __builtin_nontemporal_load(rp); }
-                else          { cv[k] = *cp; rv[k] = *rp; }
-            } else {
+        const long m0 = (long)ty * TM, n0 = (long)tx * TN, at = (long)z * p.strideY + m0 * p.ldy + n0;
+        return Tile{z, m0, n0, (int)min((long)TM, p.M - m0), (int)min((long)TN, p.N - n0), p.claimed + at, p.ref + at};
+    };
+    // claims and outputs of a strip; positions beyond the edge read the edge's elements
+    const int ldy = (int)p.ldy, srow = wm * RM * 32, scol = wn * COLS;
+    floatv4 cv[STEPS], rv[STEPS];
+    auto fetch = [&](const Tile& T, int i, int k) __attribute__((always_inline)) {
+        const int row = min(srow + i * 32 + lrow + k * RPI, T.rows_left - 1) * ldy, col = scol + lcol;
+        if (col + 4 <= T.cols_left) {
+            const floatx4u* cp = reinterpret_cast<const floatx4u*>(T.C + (unsigned)(row + col));        // (at any alignment)
+            const floatx4u* rp = reinterpret_cast<const floatx4u*>(T.Y + (unsigned)(row + col));
+            if (p.stream) { cv[k] = __builtin_nontemporal_load(cp); rv[k] = __builtin_nontemporal_load(rp); }
+            else          { cv[k] = *cp; rv[k] = *rp; }
+        } else {
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const unsigned at = (unsigned)(row + min(col + e, cols_left - 1));
-                    cv[k][e] = C[at]; rv[k][e] = Y[at];
-                }
+            for (int e = 0; e < 4; ++e) {
+                const unsigned at = (unsigned)(row + min(col + e, T.cols_left - 1));
+                cv[k][e] = T.C[at]; rv[k][e] = T.Y[at];
             }
-        };
+        }
+    };
+    // The first strip's are requested before the product, and by tiles that are walked (the larger ones) while the last strip of the tile
+    // before is checked, as its registers become free: a copy into LDS that is waited for has all older loads waited for too, so
+    // requested behind the tile's barrier they held its first slab up (8 x 8192 x 2048 over 128 246 -> 233 us, the convolution of
+    // 32 x 56 x 56 x 256 with its affine operator 314 -> 305; 512 x 3072 over 768, whose workgroups have a tile each, 22.8 -> 24).
+    constexpr bool ACROSS = RM * RN > 1;
+    const unsigned t_first = (unsigned)((unsigned long long)p.ntiles * xcd >> 3) + (blockIdx.x >> 3);
+    Tile tile;
+    if (ACROSS && t_first < t_end) {
+        tile = tile_of(t_first);
 #pragma unroll
-        for (int k = 0; k < STEPS; ++k) fetch(0, k);
+        for (int k = 0; k < STEPS; ++k) fetch(tile, 0, k);
+    }
+    for (unsigned t = t_first; t < t_end; t += per) {
+        if (!ACROSS) {
+            tile = tile_of(t);
+#pragma unroll
+            for (int k = 0; k < STEPS; ++k) fetch(tile, 0, k);
+        }
+        const unsigned z = tile.z;
+        const long m0 = tile.m0, n0 = tile.n0;
+        const int rows_left = tile.rows_left, cols_left = tile.cols_left;
 
         // sources of this wavefront's copies: scalar bases, 32-bit lane offsets
         const char* baseA[NA]; const char* baseW[NW];
@@ -425,7 +443,7 @@ __global__ __launch_bounds__(WVM * WVN * 64, WVM * WVN * PER_CU / 4) void screen
             for (int e = 0; e < 4; ++e) {
                 in_range[e] = row < rows_left && col + e < cols_left;
                 const unsigned at = in_range[e] ? (unsigned)(row * ldy + col + e) : 0u;
-                c[e] = C[at]; r[e] = Y[at];
+                c[e] = tile.C[at]; r[e] = tile.Y[at];
             }
             CheckedElement o[4];
 #pragma unroll
@@ -441,6 +459,8 @@ __global__ __launch_bounds__(WVM * WVN * 64, WVM * WVN * PER_CU / 4) void screen
             known = max(known, newest(&largest));
         };
         unsigned again = 0;                                  // steps for exact4
+        const bool last = t + per >= t_end;
+        const Tile next = ACROSS ? tile_of(last ? t : t + per) : tile;
 #pragma unroll
         for (int i = 0; i < RM; ++i) {
 #pragma unroll
@@ -465,7 +485,8 @@ __global__ __launch_bounds__(WVM * WVN * 64, WVM * WVN * PER_CU / 4) void screen
                     }
                 }
                 if (!check4(cv[k], rv[k], s, i * STEPS + k)) again |= 1u << (i * STEPS + k);
-                if (i + 1 < RM) fetch(i + 1, k);             // the next strip's, as soon as the registers are free
+                if (i + 1 < RM) fetch(tile, i + 1, k);       // the next strip's, as soon as the registers are free
+                else if (ACROSS && !last) fetch(next, 0, k);
             }
         }
         while (again) {
@@ -504,6 +525,7 @@ __global__ __launch_bounds__(WVM * WVN * 64, WVM * WVN * PER_CU / 4) void screen
                 vio = vio_before;
             }
         }
+        if (ACROSS) tile = next;
     }
     // this workgroup's counts to one of the partial results (integer atomics: the sums do not depend on the order)
     __syncthreads();
