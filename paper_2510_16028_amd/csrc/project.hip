@@ -11,7 +11,9 @@
 // its place among them plus the number of others in lower bins.  With a heavy upper tail over a calibrated
 // threshold that is a tenth of the tensor; where every bin is a candidate the histogram is the only extra work.
 // (8.4 M elements: none capped 257 -> 74 us, a heavy tail against calibrated thresholds 260 -> 104 us, all capped 343 -> 350 us;
-// 67 M: 1608 -> 325, 1621 -> 354, 2406 -> 2415 us.)  What bounds it now: three passes over delta and some fifteen launches.
+// 67 M: 1608 -> 325, 1621 -> 354, 2406 -> 2415 us.  Since the counting pass leaves each
+// tile its candidates closed up, and the first scatter reads those and not delta: none capped 74 -> 67 us, 34 M 168 -> 147.)  What bounds it
+// now: two passes over delta and some fifteen launches.
 // The sort is a least-significant-digit radix sort of the 31 magnitude bits (a non-negative binary32 orders like
 // its bit pattern, NaN above infinity) in four 8-bit passes; the payload is the element's index
 // with its sign bit on top.  Per pass: count (digit histogram per tile), scan (of each digit's counters over
@@ -94,13 +96,12 @@ __device__ __forceinline__ void build_cap_table(const float* __restrict__ thr, d
         const double c1 = (double)thr[j] * alpha;
         const double c0 = j == 0 ? 0.0 : (double)thr[j - 1] * alpha;
         s.c0 = c0; s.dc = c1 - c0; s.p0 = grid_percent(j - 1); s.dp = grid_percent(j) - grid_percent(j - 1);
-        // smallest rank k in [1, n + 1] with r_k > P[j - 1]  (r_k is nondecreasing in k)
-        long lo = 1, hi = n + 1;
-        while (lo < hi) {
-            const long mid = lo + (hi - lo) / 2;
-            if (rank_percent((double)mid, dn) > s.p0) hi = mid; else lo = mid + 1;
-        }
-        first_rank[j] = lo;
+        // smallest rank k in [1, n + 1] with r_k > P[j - 1]  (r_k is nondecreasing in k): near n P / 100 + 1/2, then settled by comparisons
+        // (by bisection, some 23 divisions one after the other, the kernel took 1.5 us more)
+        long k = min(max((long)(dn * (s.p0 * 0.01) + 0.5), 1L), n + 1);
+        while (k <= n && !(rank_percent((double)k, dn) > s.p0)) ++k;
+        while (k > 1 && rank_percent((double)(k - 1), dn) > s.p0) --k;
+        first_rank[j] = k;
     }
     if (j == TAO_NGRID) first_rank[j] = n + 1;
     __syncthreads();
@@ -217,13 +218,24 @@ __device__ __forceinline__ long tile_of_block(long tiles_per_xcd) {
     return i < tiles_per_xcd ? (long)(blockIdx.x % kXcds) * tiles_per_xcd + i : -1;
 }
 
+// A first pass's tile with few candidates leaves them closed up in the place of its keys and payloads in the second pair of buffers
+// (free until the second pass), with how many there are in the last key's place, where no key has the top bit; the scatter kernel then reads
+// those and not delta again.  Up to a quarter of the tile, beyond which writing and reading 16 bytes per candidate is more than reading
+// 4 per element; tiles that are not read in whole vectors do not either.
+constexpr unsigned kClosedUp = 1u << 31, kNotClosedUp = ~0u;
+constexpr int kMostClosedUp = kSortTile / 4;
+// (no tile is looked at where most of the tensor is to be sorted)
+__device__ __forceinline__ bool closes_up(const MagTable* __restrict__ mag, long n) { return (long)mag->candidates * 2 <= n; }
+
 // Digit histogram of every tile: hist[digit * row + tile].  Counting does not depend on the
 // order inside the tile, so a thread takes four runs of four consecutive keys (16-byte loads, all
 // issued before the first is used).  The first pass also copies delta to out on the way.
 template <bool FIRST>
 __global__ void __launch_bounds__(kSortThreads) radix_count(const float* delta, const unsigned* __restrict__ keys,
                                                             long all, int shift, int vec_ok, const MagTable* __restrict__ mag,
-                                                            unsigned* __restrict__ hist, unsigned* copy_to) {
+                                                            unsigned* __restrict__ hist, unsigned* copy_to,
+                                                            unsigned* __restrict__ closed_keys, unsigned* __restrict__ closed_vals) {
+    __shared__ unsigned piece[FIRST ? kSortItems / 4 : 1][kSortWaves];
     __shared__ unsigned cnt[kSortWaves][kCountCopies][kCountStride];
     __shared__ unsigned flag[FIRST ? kMagBins / 32 : 1];
     const PassShape shape = pass_shape<FIRST>(all, mag);
@@ -231,10 +243,8 @@ __global__ void __launch_bounds__(kSortThreads) radix_count(const float* delta, 
     const int items = FIRST ? kSortItems : shape.items;
     const long tile = tile_of_block((tiles + kXcds - 1) / kXcds);
     if (tile < 0 || tile >= tiles) return;                     // whole workgroup
-    if (FIRST) {
-        if (threadIdx.x < kMagBins / 32) flag[threadIdx.x] = mag->flag[threadIdx.x];
-        __syncthreads();
-    }
+    unsigned flags = 0;                                        // (requested ahead of the keys, put down behind them)
+    if (FIRST && threadIdx.x < kMagBins / 32) flags = mag->flag[threadIdx.x];
     const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
     for (int d = lane; d < kCountCopies * kCountStride; d += kWave) (&cnt[wave][0][0])[d] = 0;
     __builtin_amdgcn_wave_barrier();
@@ -242,6 +252,7 @@ __global__ void __launch_bounds__(kSortThreads) radix_count(const float* delta, 
     const long tile_base = tile * (items * kSortThreads);
     unsigned key[kSortItems];
     const bool full = tile_base + items * kSortThreads <= n;
+    bool closed = false;                                       // FIRST: counted as closed up
     if (full && vec_ok) {
 #pragma unroll
         for (int q = 0; q < kSortItems / 4; ++q) {
@@ -259,9 +270,69 @@ __global__ void __launch_bounds__(kSortThreads) radix_count(const float* delta, 
             if (FIRST && copy_to && e < n) copy_to[e] = key[i];
         }
     }
+    if (FIRST) {
+        if (threadIdx.x < kMagBins / 32) flag[threadIdx.x] = flags;
+        __syncthreads();
+        // A tile's candidates, where they are few, in order (by vector of the thread, thread, place in the vector): closed up in LDS, and
+        // then stored and counted from there, as sixteen steps with a tenth of the lanes each cost more than the loads
+        const unsigned long long lanes_below = (1ull << lane) - 1ull;
+        unsigned mine = 0, at[kSortItems / 4];                 // mine: a bit per key
+        const bool whole = full && vec_ok && closes_up(mag, n);
+        if (whole) {
+#pragma unroll
+            for (int q = 0; q < kSortItems / 4; ++q) {
+                unsigned all = 0;
+                at[q] = 0;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const unsigned bin = (key[4 * q + j] & 0x7fffffffu) >> kMagShift;
+                    const bool c = (flag[bin >> 5] >> (bin & 31)) & 1u;
+                    const unsigned long long b = __ballot(c);
+                    mine |= (unsigned)c << (4 * q + j);
+                    at[q] += (unsigned)__popcll(b & lanes_below);
+                    all += (unsigned)__popcll(b);
+                }
+                if (lane == 0) piece[q][wave] = all;
+            }
+        }
+        __syncthreads();
+        unsigned count = 0;
+        if (whole) {
+#pragma unroll
+            for (int q = 0; q < kSortItems / 4; ++q)
+#pragma unroll
+                for (int w = 0; w < kSortWaves; ++w) {
+                    if (w == wave) at[q] += count;
+                    count += piece[q][w];
+                }
+        }
+        closed = whole && count <= (unsigned)kMostClosedUp;
+        if (threadIdx.x == 0) closed_keys[min(tile_base + kSortTile, n) - 1] = closed ? kClosedUp | count : kNotClosedUp;
+        if (closed) {
+            // (they lie in the counters of the other wavefronts: all count in the first one's; with room of their own fewer workgroups fit)
+            unsigned* const found_key = &cnt[1][0][0];
+            unsigned short* const found_at = reinterpret_cast<unsigned short*>(&cnt[2][0][0]);
+            static_assert(kMostClosedUp <= kCountCopies * kCountStride, "in a wavefront's counters");
+#pragma unroll
+            for (int i = 0; i < kSortItems; ++i) {
+                if ((mine >> i) & 1u) {
+                    const unsigned to = at[i / 4] + (unsigned)__popc(mine >> (i & ~3) & ((1u << (i & 3)) - 1u));
+                    found_key[to] = key[i];
+                    found_at[to] = (unsigned short)(((i >> 2) * kSortThreads + threadIdx.x) * 4 + (i & 3));
+                }
+            }
+            __syncthreads();
+            for (unsigned e = threadIdx.x; e < count; e += kSortThreads) {
+                const unsigned k = found_key[e];
+                closed_keys[tile_base + e] = k & 0x7fffffffu;
+                closed_vals[tile_base + e] = ((unsigned)tile_base + found_at[e]) | (k & 0x80000000u);
+                atomicAdd(&cnt[0][lane & (kCountCopies - 1)][(k >> shift) & (kRadix - 1)], 1u);          // (the first digit: no sign in it)
+            }
+        }
+    }
 #pragma unroll
     for (int i = 0; i < kSortItems; ++i) {
-        if (i < items) {
+        if (i < items && !closed) {
             // element index of key[i] in the scalar layout (the vector layout is only used on full tiles)
             bool valid = full || tile_base + (long)i * kSortThreads + threadIdx.x < n;
             if (FIRST) {
@@ -292,7 +363,7 @@ __global__ void __launch_bounds__(kSortThreads) radix_count(const float* delta, 
 #pragma unroll
     for (int w = 0; w < kSortWaves; ++w)
 #pragma unroll
-        for (int c = 0; c < kCountCopies; ++c) total += cnt[w][c][d];
+        for (int c = 0; c < kCountCopies; ++c) total += w == 0 || !closed ? cnt[w][c][d] : 0u;
     hist[(long)d * shape.row + tile] = total;
 }
 
@@ -512,46 +583,58 @@ __global__ void __launch_bounds__(kSortThreads, LAST ? 3 : 4) radix_scatter(cons
 
     unsigned key[kSortItems], val[kSortItems];
     if (FIRST) {
-        if (threadIdx.x < kMagBins / 32) flag[threadIdx.x] = mag->flag[threadIdx.x];
-        __syncthreads();
-        // every wavefront closes up its quarter of the tile in its quarter of the LDS arrays ...
-        const unsigned* src = reinterpret_cast<const unsigned*>(delta) + tile_base;
-        const unsigned long long lanes_below = (1ull << lane) - 1ull;
-        unsigned at = 0;
+        const unsigned found = closes_up(mag, n) ? keys_in[tile_base + count - 1] : kNotClosedUp;
+        if (found != kNotClosedUp) {
+            count = (int)min(found & ~kClosedUp, (unsigned)kMostClosedUp);
+            items = (count + kSortThreads - 1) / kSortThreads;
 #pragma unroll
-        for (int i = 0; i < kSortItems; ++i) {
-            const int e = wave * (kSortItems * kWave) + i * kWave + lane;
-            key[i] = e < count ? src[e] : 0xffffffffu;         // (a NaN: never a candidate)
-        }
-#pragma unroll
-        for (int i = 0; i < kSortItems; ++i) {
-            const int e = wave * (kSortItems * kWave) + i * kWave + lane;
-            const unsigned k = key[i] & 0x7fffffffu, bin = k >> kMagShift;
-            const bool c = e < count && ((flag[bin >> 5] >> (bin & 31)) & 1u);
-            const unsigned long long b = __ballot(c);
-            if (c) {
-                const unsigned pos = wave * (kSortItems * kWave) + at + (unsigned)__popcll(b & lanes_below);
-                sh.skey[pos] = k;
-                sh.sval[pos] = ((unsigned)tile_base + (unsigned)e) | (key[i] & 0x80000000u);
+            for (int i = 0; i < kSortItems; ++i) {
+                const int e = (wave * items + i) * kWave + lane;
+                key[i] = 0xffffffffu; val[i] = 0;
+                if (i < items && e < count) { key[i] = keys_in[tile_base + e]; val[i] = vals_in[tile_base + e]; }
             }
-            at += (unsigned)__popcll(b);
-        }
-        if (lane == 0) sh.wave_tot[wave] = at;
-        __syncthreads();
-        // ... and the workgroup takes the four pieces one after the other
-        const int p1 = (int)sh.wave_tot[0], p2 = p1 + (int)sh.wave_tot[1], p3 = p2 + (int)sh.wave_tot[2];
-        count = p3 + (int)sh.wave_tot[3];
-        items = (count + kSortThreads - 1) / kSortThreads;
+        } else {
+            if (threadIdx.x < kMagBins / 32) flag[threadIdx.x] = mag->flag[threadIdx.x];
+            __syncthreads();
+            // every wavefront closes up its quarter of the tile in its quarter of the LDS arrays ...
+            const unsigned* src = reinterpret_cast<const unsigned*>(delta) + tile_base;
+            const unsigned long long lanes_below = (1ull << lane) - 1ull;
+            unsigned at = 0;
 #pragma unroll
-        for (int i = 0; i < kSortItems; ++i) {
-            const int e = (wave * items + i) * kWave + lane;
-            key[i] = 0xffffffffu; val[i] = 0;
-            if (i < items && e < count) {
-                const int from = e < p1 ? e : e < p2 ? e - p1 + kSortItems * kWave : e < p3 ? e - p2 + 2 * kSortItems * kWave : e - p3 + 3 * kSortItems * kWave;
-                key[i] = sh.skey[from]; val[i] = sh.sval[from];
+            for (int i = 0; i < kSortItems; ++i) {
+                const int e = wave * (kSortItems * kWave) + i * kWave + lane;
+                key[i] = e < count ? src[e] : 0xffffffffu;         // (a NaN: never a candidate)
             }
+#pragma unroll
+            for (int i = 0; i < kSortItems; ++i) {
+                const int e = wave * (kSortItems * kWave) + i * kWave + lane;
+                const unsigned k = key[i] & 0x7fffffffu, bin = k >> kMagShift;
+                const bool c = e < count && ((flag[bin >> 5] >> (bin & 31)) & 1u);
+                const unsigned long long b = __ballot(c);
+                if (c) {
+                    const unsigned pos = wave * (kSortItems * kWave) + at + (unsigned)__popcll(b & lanes_below);
+                    sh.skey[pos] = k;
+                    sh.sval[pos] = ((unsigned)tile_base + (unsigned)e) | (key[i] & 0x80000000u);
+                }
+                at += (unsigned)__popcll(b);
+            }
+            if (lane == 0) sh.wave_tot[wave] = at;
+            __syncthreads();
+            // ... and the workgroup takes the four pieces one after the other
+            const int p1 = (int)sh.wave_tot[0], p2 = p1 + (int)sh.wave_tot[1], p3 = p2 + (int)sh.wave_tot[2];
+            count = p3 + (int)sh.wave_tot[3];
+            items = (count + kSortThreads - 1) / kSortThreads;
+#pragma unroll
+            for (int i = 0; i < kSortItems; ++i) {
+                const int e = (wave * items + i) * kWave + lane;
+                key[i] = 0xffffffffu; val[i] = 0;
+                if (i < items && e < count) {
+                    const int from = e < p1 ? e : e < p2 ? e - p1 + kSortItems * kWave : e < p3 ? e - p2 + 2 * kSortItems * kWave : e - p3 + 3 * kSortItems * kWave;
+                    key[i] = sh.skey[from]; val[i] = sh.sval[from];
+                }
+            }
+            __syncthreads();                                   // (wave_tot and the tile are written again)
         }
-        __syncthreads();                                       // (wave_tot and the tile are written again)
     } else {
 #pragma unroll
         for (int i = 0; i < kSortItems; ++i) {
@@ -709,11 +792,11 @@ int tao_project_empirical(const float* delta, const float* thr_abs, double alpha
         const int shift = 8 * pass;
         if (pass == 0) {
             hipLaunchKernelGGL((radix_count<true>), grid, blk, 0, st, delta, kin, n, shift, (int)(vec_in && aligned(out, 16)), w.mag,
-                               w.hist, out != delta ? reinterpret_cast<unsigned*>(out) : nullptr);
+                               w.hist, out != delta ? reinterpret_cast<unsigned*>(out) : nullptr, w.keys_b, w.vals_b);
             hipLaunchKernelGGL((scan_digit<true>), digits, blk, 0, st, w.hist, n, w.mag);
-            hipLaunchKernelGGL((radix_scatter<true, false>), grid, blk, 0, st, delta, kin, vin, kout, vout, n, shift, w.hist, w.mag, w.tab, out);
+            hipLaunchKernelGGL((radix_scatter<true, false>), grid, blk, 0, st, delta, w.keys_b, w.vals_b, kout, vout, n, shift, w.hist, w.mag, w.tab, out);
         } else {
-            hipLaunchKernelGGL((radix_count<false>), grid, blk, 0, st, delta, kin, n, shift, 1, w.mag, w.hist, nullptr);
+            hipLaunchKernelGGL((radix_count<false>), grid, blk, 0, st, delta, kin, n, shift, 1, w.mag, w.hist, nullptr, nullptr, nullptr);
             hipLaunchKernelGGL((scan_digit<false>), digits, blk, 0, st, w.hist, n, w.mag);
             if (pass < 3) hipLaunchKernelGGL((radix_scatter<false, false>), grid, blk, 0, st, delta, kin, vin, kout, vout, n, shift, w.hist, w.mag, w.tab, out);
             else          hipLaunchKernelGGL((radix_scatter<false, true>), grid, blk, 0, st, delta, kin, vin, kout, vout, n, shift, w.hist, w.mag, w.tab, out);

@@ -63,3 +63,22 @@ def test_empirical_tile_counts(tao, oracle_mod, tiles, missing, share):
     want = oracle_mod.project_empirical(d, thr, 1.0)
     got = tao.tao_project_empirical(torch.from_numpy(d).cuda(), torch.from_numpy(thr).cuda(), 1.0).cpu().numpy()
     assert _same(got, want)
+
+
+@pytest.mark.parametrize("offset,missing", [(0, 0), (0, 1), (0, 4095), (1, 0), (2, 77)])
+def test_empirical_tiles_of_few_and_many_candidates(tao, oracle_mod, offset, missing):
+    """Tiles of 4096 whose candidates are closed up (up to 1024) next to tiles that are read as they are, aligned and not."""
+    counts = [0, 1, 64, 1023, 1024, 1025, 2048, 4095, 4096, 3, 1000, 500]
+    n = len(counts) * 4096 - missing
+    rng = np.random.Generator(np.random.Philox(n + offset))
+    d = (rng.standard_normal(n) * 1e-6).astype(np.float32)
+    for t, c in enumerate(counts):
+        at = t * 4096 + rng.permutation(min(4096, n - t * 4096))[:c]
+        d[at] = np.where(rng.random(len(at)) < 0.3, 1.25, 1 + rng.random(len(at))) * np.where(rng.random(len(at)) < 0.5, -1, 1)
+    share = 1 - np.mean(np.abs(d) >= 1)                      # below it no cap binds, above every one does
+    thr = np.array([1e-3 if p / 100 < share else 0.5 + p / 200 for p in [1] + list(range(5, 100, 5)) + [99, 100]], np.float32)
+    want = oracle_mod.project_empirical(d, thr, 1.0)
+    x = torch.empty(n + 4, dtype=torch.float32, device="cuda")[offset:offset + n].copy_(torch.from_numpy(d))
+    out = torch.full((n + 4,), -7.0, dtype=torch.float32, device="cuda")[offset:offset + n]
+    assert _same(tao.tao_project_empirical(x, torch.from_numpy(thr).cuda(), 1.0, out=out).cpu().numpy(), want)
+    assert _same(tao.tao_project_empirical(x, torch.from_numpy(thr).cuda(), 1.0, out=x).cpu().numpy(), want)
