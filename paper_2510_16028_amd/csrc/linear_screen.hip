@@ -46,6 +46,10 @@ constexpr int kImageBlock = 3 * 128 * 64;               // bytes of an image's b
 constexpr unsigned kLargeBf16 = (127u + 32u) << 7;      // 2^32: operands from here on are not screened
 constexpr float kTinyPerStep = 0x1p-80f;
 constexpr int kHistWords = 2044;                        // bins up to infinity's, 2040 (NaN is counted apart), then three words more
+// Words behind them that count errors of 0, one for each lane, so that these need no ballots (three scalar instructions and a comparison an
+// element: 8 x 8192 x 2048 over 128 234 -> 231 us).  The small tiles, four workgroups of which fill the LDS, have none: there the
+// errors of 0 are counted by ballots.
+constexpr int spare_words(int blocks) { return blocks > 1 ? 64 : 0; }
 
 __device__ __forceinline__ unsigned pack_abs_bf16(float even, float odd) {
     return __builtin_bit_cast(unsigned, __builtin_convertvector((floatx2{fabsf(even), fabsf(odd)}), bf16x2));
@@ -102,10 +106,11 @@ __global__ __launch_bounds__(WVM * WVN * 64, WVM * WVN * PER_CU / 4) void screen
     static_assert(NA * WAVES * 1024 == SLAB_A && NW * WAVES * 1024 == SLAB_W, "whole copies");
     constexpr int COLS = RN * 32, STRIP = COLS + 4;                            // a wavefront's strip of sums: 32 x COLS, padded rows
     static_assert(WAVES * 32 * STRIP * 4 <= NST * STAGE, "the strips lie in the stages");
+    constexpr bool ACROSS = RM * RN > 1, SPARE = spare_words(RM * RN) > 0;
     constexpr int CHAINS = RM * RN == 1 ? 2 : 1;                               // (a single accumulator would be one serial chain)
     extern __shared__ __attribute__((aligned(16))) char lds[];
     unsigned int* const hist = reinterpret_cast<unsigned int*>(lds);
-    char* const stages = lds + kHistWords * 4;
+    char* const stages = lds + (kHistWords + spare_words(RM * RN)) * 4;
     unsigned int& largest = hist[2041];                      // a lower bound of an error that occurs (its bits)
     volatile unsigned int& large_in = hist[2042];            // 1 + the last tile with an operand that is not screened
     unsigned int& heavy = hist[2043];                        // wavefronts that had to leave whole blocks open
@@ -113,7 +118,7 @@ __global__ __launch_bounds__(WVM * WVN * 64, WVM * WVN * PER_CU / 4) void screen
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave / WVN, wn = wave % WVN;
     const int r32 = lane & 31, h = lane >> 5;
-    for (int i = tid; i < kHistWords / 4; i += THREADS) reinterpret_cast<uintx4*>(hist)[i] = uintx4{0, 0, 0, 0};
+    for (int i = tid; i < (kHistWords + spare_words(RM * RN)) / 4; i += THREADS) reinterpret_cast<uintx4*>(hist)[i] = uintx4{0, 0, 0, 0};
 
     // fragments: lane (r32, h) holds k = 16 kg + 8 h .. + 7 of its row.  The first k half a wavefront takes is (wm ^ wn) & 1, so that
     // the first halves of all wavefronts cover every operand value of the tile: only those are looked at for large ones.
@@ -138,7 +143,7 @@ __global__ __launch_bounds__(WVM * WVN * 64, WVM * WVN * PER_CU / 4) void screen
     // first strip
     constexpr int SPARE_ROWS = 22;
     static_assert(kHistWords + SPARE_ROWS * STRIP < 4096, "twelve bits of bin");
-    const unsigned zero_bits = (unsigned)(kHistWords + (lane % SPARE_ROWS) * STRIP + COLS + lane / SPARE_ROWS) << 20 | 0x80000u;
+    const unsigned zero_bits = (unsigned)(SPARE ? kHistWords + lane : kHistWords + (lane % SPARE_ROWS) * STRIP + COLS + lane / SPARE_ROWS) << 20 | 0x80000u;
     // elements of a strip: a lane has four consecutive columns of one row per step
     constexpr int LPR = COLS / 4, RPI = 64 / LPR, STEPS = 32 / RPI;           // lanes per row, rows per step
     const int lrow = lane / LPR, lcol = (lane % LPR) * 4;
@@ -181,7 +186,6 @@ __global__ __launch_bounds__(WVM * WVN * 64, WVM * WVN * PER_CU / 4) void screen
     // before is checked, as its registers become free: a copy into LDS that is waited for has all older loads waited for too, so
     // requested behind the tile's barrier they held its first slab up (8 x 8192 x 2048 over 128 246 -> 233 us, the convolution of
     // 32 x 56 x 56 x 256 with its affine operator 314 -> 305; 512 x 3072 over 768, whose workgroups have a tile each, 22.8 -> 24).
-    constexpr bool ACROSS = RM * RN > 1;
     const unsigned t_first = (unsigned)((unsigned long long)p.ntiles * xcd >> 3) + (blockIdx.x >> 3);
     Tile tile;
     if (ACROSS && t_first < t_end) {
@@ -402,16 +406,24 @@ __global__ __launch_bounds__(WVM * WVN * 64, WVM * WVN * PER_CU / 4) void screen
                 const float d = fabsf(c[e] - r[e]);
                 den[e] = fabsf(r[e]) + qc.eps;
                 bits[e] = __float_as_uint(d * __builtin_amdgcn_rcpf(den[e]));
-                const bool zero = d == 0.f;
-                found += __popcll(__ballot(zero));
                 over[e] = fmaf(s[e], -p.low, d);
-                const unsigned b = zero ? zero_bits : bits[e];
-                edge[e] = (b + 16u) << 12;                   // (below 32 << 12 within 16 steps of a bin's edge)
-                word[e] = b >> 20;
+                if (SPARE) {
+                    const unsigned b = min(bits[e] - 1u, zero_bits);         // (one below: another bin only within 16 steps of an edge)
+                    edge[e] = (b + 17u) << 12;               // (below 32 << 12 within 16 steps of a bin's edge)
+                    word[e] = b >> 20;
+                } else {
+                    const bool zero = d == 0.f;
+                    found += __popcll(__ballot(zero));
+                    const unsigned b = zero ? zero_bits : bits[e];
+                    edge[e] = (b + 16u) << 12;
+                    word[e] = b >> 20;
+                }
                 least[e] = __float_as_uint(s[e]);            // (sums are not negative)
             }
-            asm volatile("" : "+s"(found));                  // (counted here: masks kept until later exceed the scalar registers)
-            all_zeros += found;
+            if (!SPARE) {
+                asm volatile("" : "+s"(found));              // (counted here: masks kept until later exceed the scalar registers)
+                all_zeros += found;
+            }
             int inside = fmaxf(fmaxf(over[0], over[1]), fmaxf(over[2], over[3])) <= bias_low;
             inside &= min(min(least[0], least[1]), min(least[2], least[3])) >= __float_as_uint(p.tiny);
             const unsigned most_bits = max(max(bits[0], bits[1]), max(bits[2], bits[3]));      // (a NaN's are the largest)
@@ -450,8 +462,8 @@ __global__ __launch_bounds__(WVM * WVN * 64, WVM * WVN * PER_CU / 4) void screen
             for (int e = 0; e < 4; ++e) o[e] = check_arith<false>(c[e], r[e], 0.f, 1.0, p.eps_rel);
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                if (!in_range[e]) continue;
-                if (c[e] == r[e] && fabsf(c[e]) < INFINITY) zeros -= 1;              // (counted in check4)
+                if (!in_range[e]) { zeros += SPARE; continue; }                      // (not counted in check4, where elements with SPARE are if settled)
+                if (!SPARE && c[e] == r[e] && fabsf(c[e]) < INFINITY) zeros -= 1;    // (counted in check4)
                 nans += o[e].is_nan;
                 if (!o[e].is_nan) { max_bits = max(max_bits, o[e].bits); atomicAdd(&hist[o[e].bin], 1u); }
             }
@@ -529,6 +541,7 @@ __global__ __launch_bounds__(WVM * WVN * 64, WVM * WVN * PER_CU / 4) void screen
     }
     // this workgroup's counts to one of the partial results (integer atomics: the sums do not depend on the order)
     __syncthreads();
+    if (SPARE && wave == 0) zeros += (int)hist[kHistWords + lane];
     zeros = wave_sum(zeros) + all_zeros;
     vio = wave_sum(vio); nans = wave_sum(nans); max_bits = wave_max(max_bits);
     const unsigned slot = blockIdx.x % (unsigned)kScreenSlots;
@@ -560,7 +573,7 @@ __global__ __launch_bounds__(WVM * WVN * 64, WVM * WVN * PER_CU / 4) void screen
 template <int RM, int RN, int WVM, int WVN, int GPS, int NST, int PER_CU, int SRC>
 int launch_config(ScreenArgs& p, long batch, hipStream_t st) {
     constexpr int TM = WVM * RM * 32, TN = WVN * RN * 32;
-    constexpr int lds_bytes = GPS * NST * (TM * (SRC == ROWS ? 128 : 64) + TN * 64) + kHistWords * 4;
+    constexpr int lds_bytes = GPS * NST * (TM * (SRC == ROWS ? 128 : 64) + TN * 64) + (kHistWords + spare_words(RM * RN)) * 4;
     auto kernel = &screen_product<RM, RN, WVM, WVN, GPS, NST, PER_CU, SRC>;
     static OncePerDevice configured;
     const hipError_t e = configured.run([&] {
