@@ -1,0 +1,37 @@
+"""Tiles that a workgroup walks: the next tile's claims and outputs are requested while the one before is checked.  More tiles than workgroups
+that fit the chip at once, in each form of the left operand, with edges among a workgroup's first, middle and last tiles, errors of 0
+alone, among others and not at all: every profile equals that of the stored bound and the streaming check, field for field."""
+import pytest
+import torch
+
+from test_gpu_screen import _claim, _same, tao  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+
+# 64 x 128 tiles (33 x 26 and 3 x 17 x 17 on 768 places), 128 x 128 (23 x 24 on 512, K a whole number of stages and not), rows (1032 tiles on 512)
+@pytest.mark.parametrize("batch,M,N,K", [(1, 2085, 3205, 100), (3, 1069, 2060, 33), (1, 2850, 3061, 300), (1, 2944, 3072, 320), (1, 33005, 130, 64),
+                                         (1, 65600, 128, 96)])
+def test_walked_tiles(tao, batch, M, N, K):  # noqa: F811
+    g = torch.Generator(device="cuda").manual_seed(M + N + K)
+    shape = (batch,) if batch > 1 else ()
+    A = torch.randn((*shape, M, K), generator=g, device="cuda")
+    W = torch.randn((*shape, N, K), generator=g, device="cuda") * 0.02
+    y = torch.matmul(A, W.transpose(-1, -2).contiguous())
+    tau = tao.tao_bound_linear_split(A, W, None)
+    for kind in ("honest", "equal", "far", "values"):
+        c = _claim(kind, y, tau, g)
+        want = tao.tao_check_and_profile(c, y, tau)
+        _same(tao.tao_bound_check_linear(A, W, None, y, c), want)
+
+
+@pytest.mark.parametrize("B,H,C,Co,R,pad", [(11, 57, 32, 250, 1, 0), (11, 56, 32, 256, 3, 1)])
+def test_walked_tiles_of_a_convolution(tao, B, H, C, Co, R, pad):  # noqa: F811
+    g = torch.Generator(device="cuda").manual_seed(B + H + Co)
+    x = torch.randn((B, H, H, C), generator=g, device="cuda")
+    w = torch.randn((Co, R, R, C), generator=g, device="cuda") * 0.05
+    tau = tao.tao_bound_conv2d_split(x, w, None, 1, pad)
+    y = torch.randn(tau.shape, generator=g, device="cuda") * tau.mean() * 1e3      # (the check does not ask where outputs come from)
+    for kind in ("honest", "equal", "far", "values"):
+        c = _claim(kind, y, tau, g)
+        _same(tao.tao_bound_check_conv2d(x, w, None, y, c, 1, pad), tao.tao_check_and_profile(c, y, tau))
