@@ -47,7 +47,7 @@ constexpr unsigned kLargeBf16 = (127u + 32u) << 7;      // 2^32: operands from h
 constexpr float kTinyPerStep = 0x1p-80f;
 constexpr int kHistWords = 2044;                        // bins up to infinity's, 2040 (NaN is counted apart), then three words more
 // Words behind them that count errors of 0, one for each lane, so that these need no ballots (three scalar instructions and a comparison an
-// element: 8 x 8192 x 2048 over 128 234 -> 231 us).  The small tiles, four workgroups of which fill the LDS, have none: there the
+// element: 16384 x 8192 over 128 234 -> 231 us).  The small tiles, four workgroups of which fill the LDS, have none: there the
 // errors of 0 are counted by ballots.
 constexpr int spare_words(int blocks) { return blocks > 1 ? 64 : 0; }
 
@@ -184,8 +184,8 @@ __global__ __launch_bounds__(WVM * WVN * 64, WVM * WVN * PER_CU / 4) void screen
     };
     // The first strip's are requested before the product, and by tiles that are walked (the larger ones) while the last strip of the tile
     // before is checked, as its registers become free: a copy into LDS that is waited for has all older loads waited for too, so
-    // requested behind the tile's barrier they held its first slab up (8 x 8192 x 2048 over 128 246 -> 233 us, the convolution of
-    // 32 x 56 x 56 x 256 with its affine operator 314 -> 305; 512 x 3072 over 768, whose workgroups have a tile each, 22.8 -> 24).
+    // requested behind the tile's barrier they held its first slab up (16384 x 8192 over 128 246 -> 233 us, the convolution of
+    // 32 x 56 x 56 x 256 with its affine operator 317 -> 308; 512 x 3072 over 768, whose workgroups have a tile each, 22.8 -> 24).
     const unsigned t_first = (unsigned)((unsigned long long)p.ntiles * xcd >> 3) + (blockIdx.x >> 3);
     Tile tile;
     if (ACROSS && t_first < t_end) {
@@ -326,6 +326,9 @@ __global__ __launch_bounds__(WVM * WVN * 64, WVM * WVN * PER_CU / 4) void screen
             }
         };
 
+        // (All wavefronts have to read the same of `heavy` behind this barrier -- otherwise they would not meet at the same ones --, and nothing
+        // else makes the compiler wait for an addition to it whose result is not used before it signals the barrier.)
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         __syncthreads();                                     // the strips of the tile before have been read
         const unsigned heavy_now = __builtin_amdgcn_readfirstlane(newest(&heavy)), by = heavy_now - heavy_before;
         if (by == WAVES || (by && by_before)) groups = 0;

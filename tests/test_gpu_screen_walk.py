@@ -35,3 +35,18 @@ def test_walked_tiles_of_a_convolution(tao, B, H, C, Co, R, pad):  # noqa: F811
     for kind in ("honest", "equal", "far", "values"):
         c = _claim(kind, y, tau, g)
         _same(tao.tao_bound_check_conv2d(x, w, None, y, c, 1, pad), tao.tao_check_and_profile(c, y, tau))
+
+
+# operands beyond what is screened: nothing is decided, all wavefronts of a workgroup stop forming products at the same tile (they meet at
+# fewer barriers from there on), and every error's bin still counts
+@pytest.mark.parametrize("M,N,K", [(4200, 4100, 64), (2850, 3061, 300), (33005, 130, 64), (2300, 2050, 64)])
+def test_walked_tiles_without_products(tao, M, N, K):  # noqa: F811
+    g = torch.Generator(device="cuda").manual_seed(M + N)
+    A = torch.randn((M, K), generator=g, device="cuda") * 2.0 ** 40
+    W = torch.randn((N, K), generator=g, device="cuda")
+    y = torch.matmul(A, W.t().contiguous())
+    c = _claim("honest", y, y, g)
+    c[::2] = y[::2] * 1.5
+    want = tao.tao_check_and_profile(c, y, tao.tao_bound_linear_split(A, W, None))
+    for _ in range(3):
+        _same(tao.tao_bound_check_linear(A, W, None, y, c), want)
