@@ -624,7 +624,7 @@ int launch_screen(const ScreenOperand& A, const ScreenOperand& W, const float* b
     const long t128 = ((M + 127) / 128) * ((N + 127) / 128) * batch;
     // Tiles of 128 x 128, two workgroups to a compute unit, where they give every compute unit one (us of the whole call on images, with
     // them / with 64 x 64: 2048 x 12288 over 4096 248 / 362, 2048 x 4096 over 4096 94 / 122, 1111 x 3001 over 1001, 216 tiles, 37 / 33);
-    // up to 256 k, where the check is most of the work, 64 x 128 and three (8 x 8192 x 2048 over 128 250, with 128 x 128 280).
+    // up to 256 k, where the check is most of the work, 64 x 128 and three (8 x 8192 x 2048 over 128 250, with 128 x 128 280; 237 now).
     // Otherwise, and where a column tile would be half empty, 64 x 64: four to a compute unit, or two with four groups to a barrier
     // where there are no more, as a group's copies, barrier and reads of LDS then are a chain that nothing else hides (512 x 3072 over
     // 768 21, with a group to a barrier 24, with 128 x 128 31; 512 x 768 over 3072 29 / 37 / 57; 256 x 1024 over 8192 51 / 71 / 110).
