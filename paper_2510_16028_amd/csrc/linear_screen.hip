@@ -139,8 +139,8 @@ __global__ __launch_bounds__(WVM * WVN * 64, WVM * WVN * PER_CU / 4) void screen
     int zeros = 0;                                           // elements with d = 0 (a lane's own, to be added to all_zeros)
     int all_zeros = 0;                                       // (the same in all lanes)
     float* strip = reinterpret_cast<float*>(stages) + wave * 32 * STRIP;
-    // what stands for the bits of an error of 0, which is counted elsewhere: the middle of a "bin" that is a padding word of the
-    // first strip
+    // what stands for the bits of an error of 0, which is counted elsewhere: the middle of a "bin" that is one of the words behind the
+    // bins, or, where there are none, a padding word of the first strip
     constexpr int SPARE_ROWS = 22;
     static_assert(kHistWords + SPARE_ROWS * STRIP < 4096, "twelve bits of bin");
     const unsigned zero_bits = (unsigned)(SPARE ? kHistWords + lane : kHistWords + (lane % SPARE_ROWS) * STRIP + COLS + lane / SPARE_ROWS) << 20 | 0x80000u;
@@ -410,17 +410,11 @@ __global__ __launch_bounds__(WVM * WVN * 64, WVM * WVN * PER_CU / 4) void screen
                 den[e] = fabsf(r[e]) + qc.eps;
                 bits[e] = __float_as_uint(d * __builtin_amdgcn_rcpf(den[e]));
                 over[e] = fmaf(s[e], -p.low, d);
-                if (SPARE) {
-                    const unsigned b = min(bits[e] - 1u, zero_bits);         // (one below: another bin only within 16 steps of an edge)
-                    edge[e] = (b + 17u) << 12;               // (below 32 << 12 within 16 steps of a bin's edge)
-                    word[e] = b >> 20;
-                } else {
-                    const bool zero = d == 0.f;
-                    found += __popcll(__ballot(zero));
-                    const unsigned b = zero ? zero_bits : bits[e];
-                    edge[e] = (b + 16u) << 12;
-                    word[e] = b >> 20;
-                }
+                const bool zero = d == 0.f;                  // (an estimate may be 0 though d is not: it lies at an edge, and is left open)
+                const unsigned b = zero ? zero_bits : bits[e];
+                edge[e] = (b + 16u) << 12;                   // (below 32 << 12 within 16 steps of a bin's edge)
+                word[e] = b >> 20;
+                if (!SPARE) found += __popcll(__ballot(zero));
                 least[e] = __float_as_uint(s[e]);            // (sums are not negative)
             }
             if (!SPARE) {

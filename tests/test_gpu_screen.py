@@ -162,6 +162,34 @@ def test_convolution(tao, B, H, C, Co, R, st, pad, dil):
                 _same(tao.tao_bound_check_conv2d(x, w, bias, y, c, st, pad, dil, ws=ws), want)
 
 
+# An error of which a binary32 estimate leaves 0, though claim and output differ: the quotient is a half of the smallest subnormal and a
+# little more, and rounds up to it; the estimate, whose denominator is rounded to the next even binary32 value, comes down to a tie and rounds
+# to 0.  unit: half the denominator, times 2^-149 (for the smaller ones as a binary32 value's bits).
+@pytest.mark.parametrize("eps,unit", [(2 - 2.0 ** -40, 2.0 ** -149), (6 - 2.0 ** -40, 3 * 2.0 ** -149), (2.0 ** 40 - 1, 2.0 ** -110), (1.0, 2.0 ** -149)])
+@pytest.mark.parametrize("batch,M,N,K", [(1, 300, 260, 100), (1, 2085, 3205, 100), (1, 2850, 3061, 300), (1, 16500, 130, 64)])
+def test_estimates_that_underflow(tao, batch, M, N, K, eps, unit):
+    g = torch.Generator(device="cuda").manual_seed(M)
+    A, W = torch.randn((M, K), generator=g, device="cuda"), torch.randn((N, K), generator=g, device="cuda")
+    y, tau = torch.zeros((M, N), device="cuda"), tao.tao_bound_linear_split(A, W)
+    bits = int(np.float32(unit).view(np.int32))
+    for share in (0.5, 1e-3):                                # (the others are errors of 0)
+        c = ((torch.rand((M, N), generator=g, device="cuda") < share).to(torch.int32) * bits).view(torch.float32)
+        want = tao.tao_check_and_profile(c, y, tau, eps_rel=eps)
+        assert want["max_rel"] == 2.0 ** -149, want["max_rel"]
+        _same(tao.tao_bound_check_linear(A, W, None, y, c, eps_rel=eps), want)
+
+
+def test_estimates_that_underflow_in_a_convolution(tao):
+    g = torch.Generator(device="cuda").manual_seed(7)
+    x, w = torch.randn((11, 57, 57, 32), generator=g, device="cuda"), torch.randn((250, 1, 1, 32), generator=g, device="cuda")
+    tau = tao.tao_bound_conv2d_split(x, w)
+    y, eps = torch.zeros_like(tau), 2 - 2.0 ** -40
+    c = (torch.rand(tau.shape, generator=g, device="cuda") < 0.5).to(torch.int32).view(torch.float32)
+    want = tao.tao_check_and_profile(c, y, tau, eps_rel=eps)
+    assert want["max_rel"] == 2.0 ** -149, want["max_rel"]
+    _same(tao.tao_bound_check_conv2d(x, w, None, y, c, eps_rel=eps), want)
+
+
 def test_replays_on_claims_of_either_kind(tao):
     g = torch.Generator(device="cuda").manual_seed(1)
     M, N, K = 520, 1030, 200
