@@ -50,3 +50,24 @@ def test_walked_tiles_without_products(tao, M, N, K):  # noqa: F811
     want = tao.tao_check_and_profile(c, y, tao.tao_bound_linear_split(A, W, None))
     for _ in range(3):
         _same(tao.tao_bound_check_linear(A, W, None, y, c), want)
+
+
+# Claims that equal the outputs but for a few elements: workgroups meet their first error late, in one lane or a few, and go on to tiles at which
+# some of their lanes know of an error and the others do not.  The largest is met after smaller ones, before them, alone.  (A bias whose bits
+# are larger than any error's: none may pass for one.)
+@pytest.mark.parametrize("batch,M,N,K", [(1, 2085, 3205, 100), (1, 4200, 3205, 33), (1, 2850, 3061, 300), (1, 33005, 130, 64)])
+def test_walked_tiles_with_few_errors(tao, batch, M, N, K):  # noqa: F811
+    g = torch.Generator(device="cuda").manual_seed(M * 3 + K)
+    A, W = torch.randn((M, K), generator=g, device="cuda"), torch.randn((N, K), generator=g, device="cuda")
+    y = torch.rand((M, N), generator=g, device="cuda") + 1
+    bias = torch.full((N,), 1e6, device="cuda")
+    tau = tao.tao_bound_linear_split(A, W, bias)
+    for few, kind in ((1, "one"), (30, "growing"), (700, "growing"), (700, "shrinking"), (7000, "growing")):
+        c = y.clone()
+        at = torch.randint(0, M * N, (few,), generator=g, device="cuda").sort().values
+        # (relative errors over 2^-22 .. 2^-4, along the walk)
+        size = torch.linspace(-22, -4, few, device="cuda") if few > 1 else torch.tensor([-12.0], device="cuda")
+        if kind == "shrinking":
+            size = size.flip(0)
+        c.view(-1)[at] = y.view(-1)[at] * (1 + torch.exp2(size))
+        _same(tao.tao_bound_check_linear(A, W, bias, y, c), tao.tao_check_and_profile(c, y, tau))
