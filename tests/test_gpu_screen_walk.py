@@ -1,5 +1,5 @@
 """Tiles that a workgroup walks: the next tile's claims and outputs are requested while the one before is checked.  More tiles than workgroups
-that fit the chip at once, in each form of the left operand, with edges among a workgroup's first, middle and last tiles, errors of 0
+that fit the chip at once, in each form of the left operand, with edges among a workgroup's tiles, errors of 0
 alone, among others and not at all: every profile equals that of the stored bound and the streaming check, field for field."""
 import pytest
 import torch
@@ -9,9 +9,10 @@ from test_gpu_screen import _claim, _same, tao  # noqa: F401
 pytestmark = pytest.mark.gpu
 
 
-# 64 x 128 tiles (33 x 26 and 3 x 17 x 17 on 768 places), 128 x 128 (23 x 24 on 512, K a whole number of stages and not), rows (1032 tiles on 512)
-@pytest.mark.parametrize("batch,M,N,K", [(1, 2085, 3205, 100), (3, 1069, 2060, 33), (1, 2850, 3061, 300), (1, 2944, 3072, 320), (1, 33005, 130, 64),
-                                         (1, 65600, 128, 96)])
+# 64 x 128 tiles (33 x 26 and 3 x 17 x 17 on 768 places, 66 x 26: a first, a middle and a last tile for a workgroup), 128 x 128 (23 x 24 on
+# 512, K a whole number of stages and not; 33 x 33), rows (1032 and 1025 tiles on 512)
+@pytest.mark.parametrize("batch,M,N,K", [(1, 2085, 3205, 100), (3, 1069, 2060, 33), (1, 4200, 3205, 100), (1, 2850, 3061, 300), (1, 2944, 3072, 320),
+                                         (1, 4200, 4100, 264), (1, 33005, 130, 64), (1, 65600, 128, 96)])
 def test_walked_tiles(tao, batch, M, N, K):  # noqa: F811
     g = torch.Generator(device="cuda").manual_seed(M + N + K)
     shape = (batch,) if batch > 1 else ()
@@ -25,7 +26,8 @@ def test_walked_tiles(tao, batch, M, N, K):  # noqa: F811
         _same(tao.tao_bound_check_linear(A, W, None, y, c), want)
 
 
-@pytest.mark.parametrize("B,H,C,Co,R,pad", [(11, 57, 32, 250, 1, 0), (11, 56, 32, 256, 3, 1)])
+# 128 x 128 tiles on 512 places: 280 x 2 and 270 x 2, and 559 x 2
+@pytest.mark.parametrize("B,H,C,Co,R,pad", [(11, 57, 32, 250, 1, 0), (11, 56, 32, 256, 3, 1), (22, 57, 32, 250, 3, 1)])
 def test_walked_tiles_of_a_convolution(tao, B, H, C, Co, R, pad):  # noqa: F811
     g = torch.Generator(device="cuda").manual_seed(B + H + Co)
     x = torch.randn((B, H, H, C), generator=g, device="cuda")
@@ -38,8 +40,8 @@ def test_walked_tiles_of_a_convolution(tao, B, H, C, Co, R, pad):  # noqa: F811
 
 
 # operands beyond what is screened: nothing is decided, all wavefronts of a workgroup stop forming products at the same tile (they meet at
-# fewer barriers from there on), and every error's bin still counts
-@pytest.mark.parametrize("M,N,K", [(4200, 4100, 64), (2850, 3061, 300), (33005, 130, 64), (2300, 2050, 64)])
+# fewer barriers from there on), and every error's bin still counts.  Workgroups of three tiles and of two in each form; of one, where none stop
+@pytest.mark.parametrize("M,N,K", [(4200, 4100, 64), (3300, 3300, 64), (4200, 4100, 264), (2850, 3061, 300), (33005, 130, 64), (2300, 2050, 64)])
 def test_walked_tiles_without_products(tao, M, N, K):  # noqa: F811
     g = torch.Generator(device="cuda").manual_seed(M + N)
     A = torch.randn((M, K), generator=g, device="cuda") * 2.0 ** 40
