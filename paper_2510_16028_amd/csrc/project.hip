@@ -277,8 +277,9 @@ __global__ void __launch_bounds__(kSortThreads) radix_count(const float* delta, 
         // then stored and counted from there, as sixteen steps with a tenth of the lanes each cost more than the loads
         const unsigned long long lanes_below = (1ull << lane) - 1ull;
         unsigned mine = 0, at[kSortItems / 4];                 // mine: a bit per key
-        const bool whole = full && vec_ok && closes_up(mag, n);
-        if (whole) {
+        const bool closing = closes_up(mag, n), whole = closing && full && vec_ok;
+        unsigned count = 0;
+        if (whole) {                                           // (the same in the whole workgroup)
 #pragma unroll
             for (int q = 0; q < kSortItems / 4; ++q) {
                 unsigned all = 0;
@@ -294,10 +295,7 @@ __global__ void __launch_bounds__(kSortThreads) radix_count(const float* delta, 
                 }
                 if (lane == 0) piece[q][wave] = all;
             }
-        }
-        __syncthreads();
-        unsigned count = 0;
-        if (whole) {
+            __syncthreads();
 #pragma unroll
             for (int q = 0; q < kSortItems / 4; ++q)
 #pragma unroll
@@ -307,7 +305,7 @@ __global__ void __launch_bounds__(kSortThreads) radix_count(const float* delta, 
                 }
         }
         closed = whole && count <= (unsigned)kMostClosedUp;
-        if (threadIdx.x == 0) closed_keys[min(tile_base + kSortTile, n) - 1] = closed ? kClosedUp | count : kNotClosedUp;
+        if (closing && threadIdx.x == 0) closed_keys[min(tile_base + kSortTile, n) - 1] = closed ? kClosedUp | count : kNotClosedUp;
         if (closed) {
             // (they lie in the counters of the other wavefronts: all count in the first one's; with room of their own fewer workgroups fit)
             unsigned* const found_key = &cnt[1][0][0];
@@ -330,31 +328,33 @@ __global__ void __launch_bounds__(kSortThreads) radix_count(const float* delta, 
             }
         }
     }
+    if (!closed) {
 #pragma unroll
-    for (int i = 0; i < kSortItems; ++i) {
-        if (i < items && !closed) {
-            // element index of key[i] in the scalar layout (the vector layout is only used on full tiles)
-            bool valid = full || tile_base + (long)i * kSortThreads + threadIdx.x < n;
-            if (FIRST) {
-                const unsigned bin = (key[i] & 0x7fffffffu) >> kMagShift;
-                valid = valid && ((flag[bin >> 5] >> (bin & 31)) & 1u);
-            }
-            const unsigned d = ((FIRST ? key[i] & 0x7fffffffu : key[i]) >> shift) & (kRadix - 1);
-            // A wave whose valid lanes all hold one digit (the rule in the top byte of narrow data) adds
-            // once.  Otherwise LDS atomics, spread over eight copies of the histogram chosen by the lane
-            // (a few distinct digits per wave -- exponent bytes, trailing zero bytes of deviations that are
-            // differences of nearby values -- would serialise 64 atomics on a handful of addresses); the
-            // copies are 260 counters apart, so equal digits of different copies fall into different banks.
-            const unsigned long long vmask = __ballot(valid);
-            if (vmask != 0) {
-                const unsigned d0 = __shfl(d, (int)__builtin_ctzll(vmask), kWave);
-                if (__ballot(valid && d == d0) == vmask) {
-                    if (lane == (int)__builtin_ctzll(vmask)) cnt[wave][0][d0] += (unsigned)__popcll(vmask);
-                } else if (valid) {
-                    atomicAdd(&cnt[wave][lane & (kCountCopies - 1)][d], 1u);
+        for (int i = 0; i < kSortItems; ++i) {
+            if (i < items) {
+                // element index of key[i] in the scalar layout (the vector layout is only used on full tiles)
+                bool valid = full || tile_base + (long)i * kSortThreads + threadIdx.x < n;
+                if (FIRST) {
+                    const unsigned bin = (key[i] & 0x7fffffffu) >> kMagShift;
+                    valid = valid && ((flag[bin >> 5] >> (bin & 31)) & 1u);
                 }
+                const unsigned d = ((FIRST ? key[i] & 0x7fffffffu : key[i]) >> shift) & (kRadix - 1);
+                // A wave whose valid lanes all hold one digit (the rule in the top byte of narrow data) adds
+                // once.  Otherwise LDS atomics, spread over eight copies of the histogram chosen by the lane
+                // (a few distinct digits per wave -- exponent bytes, trailing zero bytes of deviations that are
+                // differences of nearby values -- would serialise 64 atomics on a handful of addresses); the
+                // copies are 260 counters apart, so equal digits of different copies fall into different banks.
+                const unsigned long long vmask = __ballot(valid);
+                if (vmask != 0) {
+                    const unsigned d0 = __shfl(d, (int)__builtin_ctzll(vmask), kWave);
+                    if (__ballot(valid && d == d0) == vmask) {
+                        if (lane == (int)__builtin_ctzll(vmask)) cnt[wave][0][d0] += (unsigned)__popcll(vmask);
+                    } else if (valid) {
+                        atomicAdd(&cnt[wave][lane & (kCountCopies - 1)][d], 1u);
+                    }
+                }
+                __builtin_amdgcn_wave_barrier();
             }
-            __builtin_amdgcn_wave_barrier();
         }
     }
     __syncthreads();
@@ -583,6 +583,9 @@ __global__ void __launch_bounds__(kSortThreads, LAST ? 3 : 4) radix_scatter(cons
 
     unsigned key[kSortItems], val[kSortItems];
     if (FIRST) {
+        // (requested before it is known whether they are needed: behind that answer they were one more latency for every tile)
+        unsigned flags = 0;
+        if (threadIdx.x < kMagBins / 32) flags = mag->flag[threadIdx.x];
         const unsigned found = closes_up(mag, n) ? keys_in[tile_base + count - 1] : kNotClosedUp;
         if (found != kNotClosedUp) {
             count = (int)min(found & ~kClosedUp, (unsigned)kMostClosedUp);
@@ -594,8 +597,6 @@ __global__ void __launch_bounds__(kSortThreads, LAST ? 3 : 4) radix_scatter(cons
                 if (i < items && e < count) { key[i] = keys_in[tile_base + e]; val[i] = vals_in[tile_base + e]; }
             }
         } else {
-            if (threadIdx.x < kMagBins / 32) flag[threadIdx.x] = mag->flag[threadIdx.x];
-            __syncthreads();
             // every wavefront closes up its quarter of the tile in its quarter of the LDS arrays ...
             const unsigned* src = reinterpret_cast<const unsigned*>(delta) + tile_base;
             const unsigned long long lanes_below = (1ull << lane) - 1ull;
@@ -605,6 +606,8 @@ __global__ void __launch_bounds__(kSortThreads, LAST ? 3 : 4) radix_scatter(cons
                 const int e = wave * (kSortItems * kWave) + i * kWave + lane;
                 key[i] = e < count ? src[e] : 0xffffffffu;         // (a NaN: never a candidate)
             }
+            if (threadIdx.x < kMagBins / 32) flag[threadIdx.x] = flags;
+            __syncthreads();
 #pragma unroll
             for (int i = 0; i < kSortItems; ++i) {
                 const int e = wave * (kSortItems * kWave) + i * kWave + lane;
