@@ -108,6 +108,9 @@ __global__ __launch_bounds__(WVM * WVN * 64, WVM * WVN * PER_CU / 4) void screen
     static_assert(WAVES * 32 * STRIP * 4 <= NST * STAGE, "the strips lie in the stages");
     constexpr bool ACROSS = RM * RN > 1, SPARE = spare_words(RM * RN) > 0;
     constexpr int CHAINS = RM * RN == 1 ? 2 : 1;                               // (a single accumulator would be one serial chain)
+    // Both halves of a group are read before its two products where the registers allow it: the wait for the second then passes under the
+    // first product (137 x 144 over 4930 38.1 -> 36.1 us).
+    constexpr bool AHEAD = RM * RN == 1 && PER_CU == 2 && SRC == IMAGE;
     extern __shared__ __attribute__((aligned(16))) char lds[];
     unsigned int* const hist = reinterpret_cast<unsigned int*>(lds);
     char* const stages = lds + (kHistWords + spare_words(RM * RN)) * 4;
@@ -294,6 +297,7 @@ __global__ __launch_bounds__(WVM * WVN * 64, WVM * WVN * PER_CU / 4) void screen
             }
         };
         auto compute = [&](const char* stage) __attribute__((always_inline)) {
+            bf16x8 second_a, second_w;
 #pragma unroll
             for (int s = 0; s < 2; ++s) {
                 bf16x8 a[RM], w[RN];
@@ -310,6 +314,12 @@ __global__ __launch_bounds__(WVM * WVN * 64, WVM * WVN * PER_CU / 4) void screen
                 }
 #pragma unroll
                 for (int j = 0; j < RN; ++j) w[j] = *reinterpret_cast<const bf16x8*>(stage + fragW + j * 32 * 64 + unitW[s]);
+                if (AHEAD && s == 0) {
+                    second_a = *reinterpret_cast<const bf16x8*>(stage + fragA + unitA[1][0]);
+                    second_w = *reinterpret_cast<const bf16x8*>(stage + fragW + unitW[1]);
+                    __builtin_amdgcn_sched_barrier(0);       // (the compiler would wait for one half before it reads the other)
+                }
+                if (AHEAD && s == 1) { a[0] = second_a; w[0] = second_w; }
 #pragma unroll
                 for (int i = 0; i < RM; ++i)
 #pragma unroll
