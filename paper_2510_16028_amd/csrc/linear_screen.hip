@@ -96,7 +96,13 @@ __device__ __forceinline__ void wait_for_copies(int behind) {
 // of one row; the sums pass through LDS (32 rows of a wavefront at a time) so that claims and outputs are read along their
 // rows.  Workgroups walk the tiles; each XCD (workgroups are dealt to them in turn) owns a contiguous eighth of them, eight
 // tile rows deep, for its L2.
-template <int RM, int RN, int WVM, int WVN, int GPS, int NST, int PER_CU, int SRC>
+//
+// UNDERFLOW: an estimated error may come down to 0 though claim and output differ (denominators of 2 and more next to the smallest
+// subnormals), so an error of 0 is told by the difference; otherwise by the estimate, which then is 0 only if the difference is: with
+// eps_rel <= 1 the denominator is at most 1 + 2^-20 where |output| is below 2^-20, and elsewhere a difference is at least 2^-25 of |output|.
+// The test of the difference takes 1 to 2 % (33000 x 128 over 1056 with its cut 52.1 -> 53.1 us, 2048 x 12288 over 4096 228.5 -> 231.5), so forms
+// that could go without it have an instantiation for either.
+template <int RM, int RN, int WVM, int WVN, int GPS, int NST, int PER_CU, int SRC, bool UNDERFLOW>
 __global__ __launch_bounds__(WVM * WVN * 64, WVM * WVN * PER_CU / 4) void screen_product(ScreenArgs p) {
     constexpr int WAVES = WVM * WVN, THREADS = WAVES * 64;
     constexpr int TM = WVM * RM * 32, TN = WVN * RN * 32;
@@ -106,10 +112,10 @@ __global__ __launch_bounds__(WVM * WVN * 64, WVM * WVN * PER_CU / 4) void screen
     static_assert(NA * WAVES * 1024 == SLAB_A && NW * WAVES * 1024 == SLAB_W, "whole copies");
     constexpr int COLS = RN * 32, STRIP = COLS + 4;                            // a wavefront's strip of sums: 32 x COLS, padded rows
     static_assert(WAVES * 32 * STRIP * 4 <= NST * STAGE, "the strips lie in the stages");
-    constexpr bool ACROSS = RM * RN > 1, SPARE = spare_words(RM * RN) > 0;
+    constexpr bool ACROSS = RM * RN > 1, SPARE = spare_words(RM * RN) > 0, BY_ESTIMATE = SPARE && !UNDERFLOW;
     constexpr int CHAINS = RM * RN == 1 ? 2 : 1;                               // (a single accumulator would be one serial chain)
     // Both halves of a group are read before its two products where the registers allow it: the wait for the second then passes under the
-    // first product (137 x 144 over 4930 38.1 -> 36.1 us).
+    // first product (64 x 200 over 8192 52.0 -> 46.0 us, 512 x 768 over 3072 28.4 -> 26.6).
     constexpr bool AHEAD = RM * RN == 1 && PER_CU == 2 && SRC == IMAGE;
     extern __shared__ __attribute__((aligned(16))) char lds[];
     unsigned int* const hist = reinterpret_cast<unsigned int*>(lds);
@@ -422,11 +428,17 @@ __global__ __launch_bounds__(WVM * WVN * 64, WVM * WVN * PER_CU / 4) void screen
                 den[e] = fabsf(r[e]) + qc.eps;
                 bits[e] = __float_as_uint(d * __builtin_amdgcn_rcpf(den[e]));
                 over[e] = fmaf(s[e], -p.low, d);
-                const bool zero = d == 0.f;                  // (an estimate may be 0 though d is not: it lies at an edge, and is left open)
-                const unsigned b = zero ? zero_bits : bits[e];
-                edge[e] = (b + 16u) << 12;                   // (below 32 << 12 within 16 steps of a bin's edge)
-                word[e] = b >> 20;
-                if (!SPARE) found += __popcll(__ballot(zero));
+                if (BY_ESTIMATE) {
+                    const unsigned b = min(bits[e] - 1u, zero_bits);         // (one below: another bin only within 16 steps of an edge)
+                    edge[e] = (b + 17u) << 12;               // (below 32 << 12 within 16 steps of a bin's edge)
+                    word[e] = b >> 20;
+                } else {
+                    const bool zero = d == 0.f;              // (an estimate of 0 where it is not: at an edge, and so left open)
+                    const unsigned b = zero ? zero_bits : bits[e];
+                    edge[e] = (b + 16u) << 12;
+                    word[e] = b >> 20;
+                    if (!SPARE) found += __popcll(__ballot(zero));
+                }
                 least[e] = __float_as_uint(s[e]);            // (sums are not negative)
             }
             if (!SPARE) {
@@ -436,7 +448,7 @@ __global__ __launch_bounds__(WVM * WVN * 64, WVM * WVN * PER_CU / 4) void screen
             int inside = fmaxf(fmaxf(over[0], over[1]), fmaxf(over[2], over[3])) <= bias_low;
             inside &= min(min(least[0], least[1]), min(least[2], least[3])) >= __float_as_uint(p.tiny);
             const unsigned most_bits = max(max(bits[0], bits[1]), max(bits[2], bits[3]));      // (a NaN's are the largest)
-            // (no larger than an error that occurs; or all 0, and then exactly: the edges leave estimates that came down to 0 open)
+            // (no larger than an error that occurs; or all 0, and then exactly: none comes down to 0, or the edges leave it open)
             int ok = most_bits <= max(known, 16u) - 16u;
             ok &= min(min(edge[0], edge[1]), min(edge[2], edge[3])) >= 32u << 12;
             ok &= fmaxf(fmaxf(den[0], den[1]), fmaxf(den[2], den[3])) <= 0x1p100f;
@@ -579,11 +591,12 @@ __global__ __launch_bounds__(WVM * WVN * 64, WVM * WVN * PER_CU / 4) void screen
     }
 }
 
-template <int RM, int RN, int WVM, int WVN, int GPS, int NST, int PER_CU, int SRC>
+template <int RM, int RN, int WVM, int WVN, int GPS, int NST, int PER_CU, int SRC, bool UNDERFLOW = spare_words(RM * RN) == 0>
 int launch_config(ScreenArgs& p, long batch, hipStream_t st) {
+    if (!UNDERFLOW && p.eps_rel > 1.0) return launch_config<RM, RN, WVM, WVN, GPS, NST, PER_CU, SRC, true>(p, batch, st);
     constexpr int TM = WVM * RM * 32, TN = WVN * RN * 32;
     constexpr int lds_bytes = GPS * NST * (TM * (SRC == ROWS ? 128 : 64) + TN * 64) + (kHistWords + spare_words(RM * RN)) * 4;
-    auto kernel = &screen_product<RM, RN, WVM, WVN, GPS, NST, PER_CU, SRC>;
+    auto kernel = &screen_product<RM, RN, WVM, WVN, GPS, NST, PER_CU, SRC, UNDERFLOW>;
     static OncePerDevice configured;
     const hipError_t e = configured.run([&] {
         return hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
