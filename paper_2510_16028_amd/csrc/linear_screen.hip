@@ -47,8 +47,8 @@ constexpr unsigned kLargeBf16 = (127u + 32u) << 7;      // 2^32: operands from h
 constexpr float kTinyPerStep = 0x1p-80f;
 constexpr int kHistWords = 2044;                        // bins up to infinity's, 2040 (NaN is counted apart), then three words more
 // Words behind them that count errors of 0, one for each lane, so that these need no ballots (three scalar instructions and a comparison an
-// element: 16384 x 8192 over 128 234 -> 231 us).  The small tiles, four workgroups of which fill the LDS, have none: there the
-// errors of 0 are counted by ballots.
+// element: 8 x 8192 x 2048 over 128 234 -> 231 us).  Tiles of 64 x 64 have none and count by ballots: in all of their forms but one the
+// workgroups of a compute unit fill the LDS to its last 64 bytes (the form for few tiles has room; its workgroups check one tile or two).
 constexpr int spare_words(int blocks) { return blocks > 1 ? 64 : 0; }
 
 __device__ __forceinline__ unsigned pack_abs_bf16(float even, float odd) {
@@ -193,7 +193,7 @@ __global__ __launch_bounds__(WVM * WVN * 64, WVM * WVN * PER_CU / 4) void screen
     };
     // The first strip's are requested before the product, and by tiles that are walked (the larger ones) while the last strip of the tile
     // before is checked, as its registers become free: a copy into LDS that is waited for has all older loads waited for too, so
-    // requested behind the tile's barrier they held its first slab up (16384 x 8192 over 128 246 -> 233 us, the convolution of
+    // requested behind the tile's barrier they held its first slab up (8 x 8192 x 2048 over 128 246 -> 233 us, the convolution of
     // 32 x 56 x 56 x 256 with its affine operator 317 -> 308; 512 x 3072 over 768, whose workgroups have a tile each, 22.8 -> 24).
     const unsigned t_first = (unsigned)((unsigned long long)p.ntiles * xcd >> 3) + (blockIdx.x >> 3);
     Tile tile;
@@ -404,7 +404,7 @@ __global__ __launch_bounds__(WVM * WVN * 64, WVM * WVN * PER_CU / 4) void screen
                 if (den <= 0x1p100f && bits <= 0x7f800000u && bits > 16u) first = max(first, bits - 16u);
             }
             // (rows and columns beyond the edge repeat elements that exist)
-            // (one atomic of a wavefront: 256 lanes' on the one word took 2.3 us; 512 x 3072 over 768 24.05 -> 22.7 us with the histograms in lines)
+            // (one atomic of a wavefront: 256 lanes' on the one word took 2.3 us; 512 x 3072 over 768 24.05 -> 22.7 us with the histogram in lines below)
             first = wave_max(first);
             if (first && lane == 0) atomicMax(&largest, first);
         }
@@ -579,8 +579,8 @@ __global__ __launch_bounds__(WVM * WVN * 64, WVM * WVN * PER_CU / 4) void screen
         if (opened) atomicAdd(&st->flag, opened);
     }
     __syncthreads();
-    // (a group of 64 bins to a wavefront: its atomics fall into two lines, and few groups are not empty; with eight bins to a thread
-    // 1111 x 3001 over 1001 took 44.0 us, so 42.3)
+    // (a group of 64 bins to a wavefront: its atomics fall into two lines, and few groups are not empty.  With eight bins to a thread, and 256
+    // lanes' atomics for the first error: 1111 x 3001 over 1001 with its cut 41.98 us, so 40.57)
     for (int base = wave * kWave; base < kBins; base += THREADS) {
         const int bin = base + lane;
         const unsigned cnt = bin <= 2040 ? hist[bin] : 0u;
@@ -643,7 +643,7 @@ int launch_screen(const ScreenOperand& A, const ScreenOperand& W, const float* b
     const long t128 = ((M + 127) / 128) * ((N + 127) / 128) * batch;
     // Tiles of 128 x 128, two workgroups to a compute unit, where they give every compute unit one (us of the whole call on images, with
     // them / with 64 x 64: 2048 x 12288 over 4096 248 / 362, 2048 x 4096 over 4096 94 / 122, 1111 x 3001 over 1001, 216 tiles, 37 / 33);
-    // up to 256 k, where the check is most of the work, 64 x 128 and three (8 x 8192 x 2048 over 128 250, with 128 x 128 280; 237 now).
+    // up to 256 k, where the check is most of the work, 64 x 128 and three (8 x 8192 x 2048 over 128 250, with 128 x 128 280; 228 now).
     // Otherwise, and where a column tile would be half empty, 64 x 64: four to a compute unit, or two with four groups to a barrier
     // where there are no more, as a group's copies, barrier and reads of LDS then are a chain that nothing else hides (512 x 3072 over
     // 768 21, with a group to a barrier 24, with 128 x 128 31; 512 x 768 over 3072 29 / 37 / 57; 256 x 1024 over 8192 51 / 71 / 110).

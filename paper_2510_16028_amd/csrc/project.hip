@@ -12,17 +12,17 @@
 // threshold that is a tenth of the tensor; where every bin is a candidate the histogram is the only extra work.
 // (8.4 M elements: none capped 257 -> 74 us, a heavy tail against calibrated thresholds 260 -> 104 us, all capped 343 -> 350 us;
 // 67 M: 1608 -> 325, 1621 -> 354, 2406 -> 2415 us.  Since the counting pass leaves each
-// tile its candidates closed up, and the first scatter reads those and not delta: none capped 74 -> 67 us, 34 M 168 -> 147.)  What bounds it
-// now: two passes over delta and some fifteen launches.
+// tile its candidates closed up, and the first scatter reads those and not delta: none capped 74 -> 67 us, 34 M 168 -> 147, 67 M 325 -> 287;
+// where most is sorted, and no tile is closed up, 67 M and 134 M take 0.3 % longer.)  What bounds it now: two passes over delta and some fifteen launches.
 // The sort is a least-significant-digit radix sort of the 31 magnitude bits (a non-negative binary32 orders like
 // its bit pattern, NaN above infinity) in four 8-bit passes; the payload is the element's index
 // with its sign bit on top.  Per pass: count (digit histogram per tile), scan (of each digit's counters over
 // the tiles; the digits' own totals are scanned by every workgroup of the next kernel), scatter (stable
 // rank inside the tile by wave-wide digit matching, elements
-// reordered in LDS so that runs of one digit leave as contiguous writes).  The first pass reads
-// delta itself and drops what is no candidate (its count kernel copies delta to out when the two differ); the last
-// pass writes no sorted array at
-// all: the destination of an element gives its rank, so the cap is evaluated there and only the
+// reordered in LDS so that runs of one digit leave as contiguous writes).  The first pass drops
+// what is no candidate: its count kernel reads delta (and copies it to out when the two differ) and leaves tiles of few
+// candidates closed up, its scatter kernel reads those, and delta where a tile is not closed up.  The last pass writes no
+// sorted array at all: the destination of an element gives its rank, so the cap is evaluated there and only the
 // elements that exceed their cap are written, straight to out[index] -- the one access of the
 // whole path that is random, 4 bytes per 64-byte line, and therefore kept to the elements that
 // need it.
@@ -553,7 +553,7 @@ __device__ __forceinline__ void cap_and_store(const CapTable& tab, unsigned rank
 }
 
 // Scatter pass.  `hist` holds the scanned counters: hist[d * row + tile] elements with digit d lie in the tiles before.
-// The first pass closes up the tile's candidates in LDS, in order, and sorts those.
+// The first pass sorts the tile's candidates: as the counting pass left them, or closed up here, in LDS and in order.
 template <bool FIRST, bool LAST>
 __global__ void __launch_bounds__(kSortThreads, LAST ? 3 : 4) radix_scatter(const float* delta,
                                                               const unsigned* __restrict__ keys_in, const unsigned* __restrict__ vals_in,
