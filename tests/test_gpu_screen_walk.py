@@ -73,3 +73,26 @@ def test_walked_tiles_with_few_errors(tao, batch, M, N, K):  # noqa: F811
             size = size.flip(0)
         c.view(-1)[at] = y.view(-1)[at] * (1 + torch.exp2(size))
         _same(tao.tao_bound_check_linear(A, W, bias, y, c), tao.tao_check_and_profile(c, y, tau))
+
+
+# both ways of telling an error of 0, and the line between them, in each larger form
+@pytest.mark.parametrize("eps", [1.0, 1.0000000000000002, 3.0])
+@pytest.mark.parametrize("M,N,K", [(2085, 3205, 100), (2850, 3061, 300), (33005, 130, 64)])
+def test_walked_tiles_with_large_denominators(tao, M, N, K, eps):  # noqa: F811
+    g = torch.Generator(device="cuda").manual_seed(M + K)
+    A, W = torch.randn((M, K), generator=g, device="cuda"), torch.randn((N, K), generator=g, device="cuda") * 0.02
+    y = torch.matmul(A, W.t().contiguous())
+    tau = tao.tao_bound_linear_split(A, W, None)
+    for kind in ("honest", "equal", "far", "values"):
+        c = _claim(kind, y, tau, g)
+        _same(tao.tao_bound_check_linear(A, W, None, y, c, eps_rel=eps), tao.tao_check_and_profile(c, y, tau, eps_rel=eps))
+
+
+def test_walked_convolution_with_large_denominators(tao):  # noqa: F811
+    g = torch.Generator(device="cuda").manual_seed(2)
+    x, w = torch.randn((11, 57, 57, 32), generator=g, device="cuda"), torch.randn((250, 1, 1, 32), generator=g, device="cuda") * 0.05
+    tau = tao.tao_bound_conv2d_split(x, w)
+    y = torch.randn(tau.shape, generator=g, device="cuda") * tau.mean() * 1e3
+    for kind in ("honest", "equal", "far", "values"):
+        c = _claim(kind, y, tau, g)
+        _same(tao.tao_bound_check_conv2d(x, w, None, y, c, eps_rel=3.0), tao.tao_check_and_profile(c, y, tau, eps_rel=3.0))
