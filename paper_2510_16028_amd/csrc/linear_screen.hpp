@@ -9,16 +9,25 @@ namespace tao {
 // Rows: the binary32 matrix itself (16-byte aligned rows, whole groups of 32 k).
 // Pixels: BF16 magnitudes [batch][H][W][C] of a convolution's input, whose patch matrix the operand is (C a multiple of 32).
 struct ScreenPixels {
-    int H, W, C, OW, S, sh, sw, ph, pw, dh, dw;
+    int H, W, C, OW, R, S, sh, sw, ph, pw, dh, dw;
+    int r0, s0;                // the tap that its product begins with: the middle one, which lies in the padding last
     unsigned ohow;
     int slabs;                 // C / 32
     unsigned zeros;            // offset in bytes of 64 bytes of zeros
 };
+// Marks that say whether all of an operand is ordinary, that is below 2^32: the workgroups that cut it leave a byte each at the end of its
+// image, kOrdinary if all that they read was (the sum of any eight neighbours, that is), and places without a workgroup hold that too.  An operand
+// passes for ordinary only where all bytes say so: an image's leading pieces, which a caller that passes a part of a batch as an image of its
+// own has in this place, never do (their sign bits are 0).
+constexpr int kMarks = 512;
+constexpr unsigned char kOrdinary = 0xa5;
+
 struct ScreenOperand {
     const void* data;
     long batch_bytes;          // 0: shared
     long ld;                   // rows: elements between rows; otherwise 0
     const ScreenPixels* pixels;
+    const unsigned char* marks;    // (rows: none)
 };
 constexpr long kScreenMaxLd = 1L << 22;      // rows of claims and outputs, and of binary32 operands: 32-bit offsets within a tile
 
@@ -79,6 +88,7 @@ inline bool screen_usable(long K, double u, double cg, double alpha, double uflo
     return K > 0 && u <= 0x1p-20 && accumulation_error(K) <= 0x1p-6 && cg >= 0x1p-40 && cg <= 0x1p10 && a >= 0x1p-40 && a <= 0x1p20 &&
            uflow <= cg * (double)K * 0x1p-100;
 }
+bool screen_reads_marks(long M, long N, long K, long batch, bool rows, bool pixels);       // whether launch_screen's choice does
 int launch_screen(const ScreenOperand& A, const ScreenOperand& W, const float* bias, long M, long N, long K, long batch,
                   double cg, const ScreenCheck& chk, const CheckWorkspace& ws, const OpenRecords& open, hipStream_t st);
 

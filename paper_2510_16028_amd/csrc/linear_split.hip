@@ -129,6 +129,7 @@ __device__ __forceinline__ void split_pack8(const float (&v)[8], uintx4& H, uint
 enum { STRAIGHT, TRANSPOSED, MAGNITUDES };
 struct SplitOperand {
     const float* src; long rows, K, ld, batch, stride; unsigned short* dst; int form;
+    unsigned char* marks; int nmarks;  // where this operand's workgroups say that all they have read is ordinary, a byte each (linear_screen.hpp)
     __host__ __device__ bool flat() const { return form == STRAIGHT && rows <= 16 && (K + SBK - 1) / SBK * batch >= 512; }
 };
 struct SplitOperands {
@@ -141,27 +142,44 @@ __device__ __forceinline__ void clear_words(const ClearJob& c, long i0, long ste
     for (int j = 0; j < 4; ++j)
         for (long i = i0; i < c.words[j]; i += step) static_cast<uintx4*>(c.at[j])[i] = uintx4{0, 0, 0, 0};
 }
+// A workgroup's mark, and the first one's for the places of those that there are not.
+__device__ __forceinline__ void leave_mark(const SplitOperand& p, long wg, long wgs, bool ordinary) {
+    const bool all = __syncthreads_and(ordinary);
+    if (threadIdx.x == 0) p.marks[wg] = all ? kOrdinary : 0;
+    if (wg == 0)
+        for (long i = wgs + threadIdx.x; i < p.nmarks; i += blockDim.x) p.marks[i] = kOrdinary;
+}
+constexpr int kMostSplitThreads = 1024;
 typedef float floatx4u __attribute__((ext_vector_type(4), aligned(4)));          // (16-byte loads need no more than 4-byte alignment)
-__global__ __launch_bounds__(256) void split3_bf16(SplitOperands a) {
+template <bool MARKED>
+__global__ __launch_bounds__(MARKED ? kMostSplitThreads : 256) void split3_bf16(SplitOperands a) {
+    const int threads = MARKED ? (int)blockDim.x : 256;
     // (side job for the launch that follows: clears the partial results of a check, so that no launch of its own is needed for that)
-    clear_words(a.clear, (long)blockIdx.x * 256 + threadIdx.x, (long)gridDim.x * 256);
+    clear_words(a.clear, (long)blockIdx.x * threads + threadIdx.x, (long)gridDim.x * threads);
     const int o = (long)blockIdx.x >= a.first[1] ? 1 : 0;
     // (both operands' fields are requested at once: the choice would be one more step of the chain of scalar loads)
     const SplitOperand &q0 = a.op[0], &q1 = a.op[1];
     const SplitOperand p = {o ? q1.src : q0.src, o ? q1.rows : q0.rows, o ? q1.K : q0.K, o ? q1.ld : q0.ld, o ? q1.batch : q0.batch,
-                            o ? q1.stride : q0.stride, o ? q1.dst : q0.dst, o ? q1.form : q0.form};
-    const long nblk = o ? a.first[2] - a.first[1] : a.first[1], blk = o ? (long)blockIdx.x - a.first[1] : (long)blockIdx.x;
+                            o ? q1.stride : q0.stride, o ? q1.dst : q0.dst, o ? q1.form : q0.form, o ? q1.marks : q0.marks, o ? q1.nmarks : q0.nmarks};
+    const long wgs = o ? a.first[2] - a.first[1] : a.first[1], wg = o ? (long)blockIdx.x - a.first[1] : (long)blockIdx.x;
+    // 256 threads are a block of units below; a workgroup holds one or four of them
+    const long nblk = wgs * (threads >> 8), blk = wg * (threads >> 8) + (MARKED ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 8) : 0);
+    const int tid = threadIdx.x & 255;
+    bool ordinary = true;                                    // (by the sums of eight magnitudes)
+    auto look = [&](float s) __attribute__((always_inline)) { if (MARKED) ordinary &= s < 0x1p32f; };
     if (p.form == MAGNITUDES) {
-        for (long i = blk * 256 + threadIdx.x; i < p.K / 8 + 4; i += nblk * 256) {
+        for (long i = blk * 256 + tid; i < p.K / 8 + 4; i += nblk * 256) {
             uintx4 H = {0, 0, 0, 0};
             if (i < p.K / 8) {
                 const floatx4u* q = reinterpret_cast<const floatx4u*>(p.src) + 2 * i;
                 const floatx4u x = q[0], y = q[1];
                 H = uintx4{pack_bf16(fabsf(x[0]), fabsf(x[1])), pack_bf16(fabsf(x[2]), fabsf(x[3])),
                            pack_bf16(fabsf(y[0]), fabsf(y[1])), pack_bf16(fabsf(y[2]), fabsf(y[3]))};
+                look(fabsf(x[0]) + fabsf(x[1]) + fabsf(x[2]) + fabsf(x[3]) + fabsf(y[0]) + fabsf(y[1]) + fabsf(y[2]) + fabsf(y[3]));
             }
             reinterpret_cast<uintx4*>(p.dst)[i] = H;
         }
+        if (MARKED) leave_mark(p, wg, wgs, ordinary);
         return;
     }
     const bool trans = p.form == TRANSPOSED;
@@ -171,7 +189,7 @@ __global__ __launch_bounds__(256) void split3_bf16(SplitOperands a) {
     const long rows4 = (p.rows + 3) & ~3L;
     const unsigned units = (unsigned)(groups * (unsigned long long)rgroups * p.batch);
     const bool flat = p.flat();
-    const int tid = threadIdx.x, urow = trans ? tid & 63 : (flat ? tid & 63 : tid) >> 2, uch = trans ? tid >> 6 : tid & 3;
+    const int urow = trans ? tid & 63 : (flat ? tid & 63 : tid) >> 2, uch = trans ? tid >> 6 : tid & 3;
     const unsigned first = flat ? (unsigned)blk * 4 + __builtin_amdgcn_readfirstlane(tid >> 6) : (unsigned)blk;
     for (unsigned u = first; u < units; u += (unsigned)nblk * (flat ? 4 : 1)) {
         const unsigned rz = u / groups, g = u - rz * groups, z = rz / rgroups, rg = rz - z * rgroups;
@@ -197,6 +215,7 @@ __global__ __launch_bounds__(256) void split3_bf16(SplitOperands a) {
         }
         uintx4 H, Mi, L;
         split_pack8(v, H, Mi, L);
+        look(fabsf(v[0]) + fabsf(v[1]) + fabsf(v[2]) + fabsf(v[3]) + fabsf(v[4]) + fabsf(v[5]) + fabsf(v[6]) + fabsf(v[7]));
         const long r = row & (STILE - 1);
         const long unit = uch ^ ((r >> 2) & 3);
         unsigned short* d = p.dst + (((long)z * groups + g) * rblocks + (row >> 7)) * (kBlock / 2) + r * (SROW / 2) + unit * 8;
@@ -204,6 +223,7 @@ __global__ __launch_bounds__(256) void split3_bf16(SplitOperands a) {
         *reinterpret_cast<uintx4*>(d + (kSlab / 2)) = Mi;
         *reinterpret_cast<uintx4*>(d + 2 * (kSlab / 2)) = L;
     }
+    if (MARKED) leave_mark(p, wg, wgs, ordinary);
 }
 
 // ---- the product ----------------------------------------------------------------------------
@@ -1254,13 +1274,16 @@ static int split_k_parts(long M, long N, long K, long batch) {
 namespace tao {
 // ---- workspace layout -------------------------------------------------------------------------
 // An operand image: per 32 k-steps and 128-row block the LDS image of the three pieces (kBlock bytes),
-// batch entries one after the other; 512 bytes of slack at the end.
+// batch entries one after the other; at the end 512 bytes of marks (kMarks).
 static size_t image_bytes(long rows, long K, long batch) {
     if (rows <= 0 || K <= 0 || batch <= 0) return 0;
     const long Kp = (K + SBK - 1) / SBK * SBK;
     const __int128 blocks = (__int128)(Kp / SBK) * ((rows + STILE - 1) / STILE) * batch;
     if (blocks * kBlock + 512 >= ((__int128)1 << 62)) return 0;
-    return round_up_256((size_t)(blocks * kBlock) + 512);
+    return round_up_256((size_t)(blocks * kBlock) + kMarks);
+}
+static unsigned char* image_marks(const void* image, long rows, long K, long batch) {
+    return static_cast<unsigned char*>(const_cast<void*>(image)) + (size_t)((K + SBK - 1) / SBK) * (size_t)((rows + STILE - 1) / STILE) * (size_t)batch * kBlock;
 }
 // What the product itself needs beyond the images: the binary64 partial sums of a reduction cut into
 // parts and, with a check, the check's partial results and (short reductions) the stored bound.
@@ -1346,18 +1369,23 @@ struct SplitCheckHost {
 static void launch_split3(const SplitOperand* ops, int n, const ClearJob& clear, hipStream_t st) {
     SplitOperands a = {};
     a.clear = clear;
+    auto blocks = [](const SplitOperand& p) {
+        const long units = (p.K + SBK - 1) / SBK * ((p.rows + 63) / 64) * p.batch;
+        return p.form == MAGNITUDES ? (p.K / 8 + 4 + 255) / 256 : p.flat() ? (units + 3) / 4 : units;
+    };
+    // A mark for every workgroup, so there are as many as marks at most; of 1024 threads where 256 would be too few.
+    const bool marked = ops[0].nmarks > 0;
+    bool wide = false;
+    for (int o = 0; o < n; ++o) wide |= marked && blocks(ops[o]) > ops[o].nmarks;
     long first = 0;
     for (int o = 0; o < n; ++o) {
-        const SplitOperand& p = ops[o];
-        a.op[o] = p;
-        const long groups = (p.K + SBK - 1) / SBK;
-        const long units = groups * ((p.rows + 63) / 64) * p.batch;
-        const long b = p.form == MAGNITUDES ? (p.K / 8 + 4 + 255) / 256 : p.flat() ? (units + 3) / 4 : units;
+        a.op[o] = ops[o];
         a.first[o] = first;
-        first += b < 1 ? 1 : (b > 256L * 64 ? 256L * 64 : b);
+        first += std::clamp(wide ? (blocks(ops[o]) + 3) / 4 : blocks(ops[o]), 1L, marked ? (long)ops[o].nmarks : 256L * 64);
     }
     for (int o = n; o < 3; ++o) a.first[o] = first;
-    hipLaunchKernelGGL(split3_bf16, dim3((unsigned)first), dim3(256), 0, st, a);
+    if (marked) hipLaunchKernelGGL(split3_bf16<true>, dim3((unsigned)first), dim3(wide ? kMostSplitThreads : 256), 0, st, a);
+    else        hipLaunchKernelGGL(split3_bf16<false>, dim3((unsigned)first), dim3(256), 0, st, a);
 }
 
 // The product on prepared images.  ws: what core_workspace_bytes(M, N, K, batch, chk != NULL) asks for.
@@ -1674,14 +1702,16 @@ static int split_run(const float* A, const float* W, const float* bias, float* t
         // the operand pre-pass also clears the partial results of a screen and of an epilogue check (no parts: those
         // are checked by the combining pass, which needs none)
         cleared = scr || epilogue_check_without_parts(M, N, K, batch, md, chk);
-        const SplitOperand ops[2] = {{W, N, K, ldw, shared_w ? 1 : batch, strideW, W3, trans_w ? TRANSPOSED : STRAIGHT}, {A, M, K, lda, batch, strideA, A3, STRAIGHT}};
+        const int nmarks = scr && screen_reads_marks(M, N, K, batch, in_load, false) ? kMarks : 0;
+        const SplitOperand ops[2] = {{W, N, K, ldw, shared_w ? 1 : batch, strideW, W3, trans_w ? TRANSPOSED : STRAIGHT, image_marks(W3, N, K, shared_w ? 1 : batch), nmarks},
+                                     {A, M, K, lda, batch, strideA, A3, STRAIGHT, image_marks(A3, M, K, batch), nmarks}};
         launch_split3(ops, in_load ? 1 : 2, scr ? screen_clear(cw, M, N, K, batch) : cleared ? clear_job(cw, kMaxCheckBlocks) : ClearJob{}, st);
     }
     if (scr) {
         const long groups = (K + SBK - 1) / SBK;
-        ScreenOperand oa = {A3, groups * ((M + STILE - 1) / STILE) * kBlock, 0, nullptr};
-        if (in_load) oa = {A, strideA * 4, lda, nullptr};
-        const ScreenOperand ow = {W3, shared_w ? 0 : groups * ((N + STILE - 1) / STILE) * kBlock, 0, nullptr};
+        ScreenOperand oa = {A3, groups * ((M + STILE - 1) / STILE) * kBlock, 0, nullptr, image_marks(A3, M, K, batch)};
+        if (in_load) oa = {A, strideA * 4, lda, nullptr, nullptr};
+        const ScreenOperand ow = {W3, shared_w ? 0 : groups * ((N + STILE - 1) / STILE) * kBlock, 0, nullptr, image_marks(W3, N, K, shared_w ? 1 : batch)};
         rc = run_screen(oa, ow, bias, M, N, K, batch, md, chk, cw, st);
         if (rc != TAO_OK) return rc;
     }
@@ -1716,8 +1746,8 @@ static int images_run(const void* A_image, const void* W_image, const float* bia
         cleared = true;
         launch_clear(screen_clear(cw, M, N, K, batch), st);
         const long groups = (K + SBK - 1) / SBK;
-        const ScreenOperand oa = {A3, groups * ((M + STILE - 1) / STILE) * kBlock, 0, nullptr};
-        const ScreenOperand ow = {W3, sw ? 0 : groups * ((N + STILE - 1) / STILE) * kBlock, 0, nullptr};
+        const ScreenOperand oa = {A3, groups * ((M + STILE - 1) / STILE) * kBlock, 0, nullptr, image_marks(A3, M, K, batch)};
+        const ScreenOperand ow = {W3, sw ? 0 : groups * ((N + STILE - 1) / STILE) * kBlock, 0, nullptr, image_marks(W3, N, K, sw ? 1 : batch)};
         rc = run_screen(oa, ow, bias, M, N, K, batch, md, chk, cw, st);
         if (rc != TAO_OK) return rc;
     }
@@ -1741,7 +1771,8 @@ int tao_split_operand(const float* src, long rows, long K, long ld, int trans, l
     const size_t need = tao::image_bytes(rows, K, batch);
     if (need == 0 || !image || !aligned(image, 256) || image_bytes < need) return TAO_ERR_WORKSPACE;
     if (batch >= 65536) return TAO_ERR_SHAPE;                      // (an image's limit, whatever a launch could take)
-    const SplitOperand op = {src, rows, K, ld, batch, stride, static_cast<unsigned short*>(image), trans ? TRANSPOSED : STRAIGHT};
+    const SplitOperand op = {src, rows, K, ld, batch, stride, static_cast<unsigned short*>(image), trans ? TRANSPOSED : STRAIGHT,
+                             image_marks(image, rows, K, batch), kMarks};
     launch_split3(&op, 1, ClearJob{}, (hipStream_t)stream);
     return launch_status();
 }
@@ -1812,12 +1843,17 @@ static int conv_split_run(const float* x, const float* w, const float* bias, flo
     const bool cleared = scr || epilogue_check_without_parts(M, N, K, 1, md, chk);
     const CheckWorkspace cw = carve_check_workspace(rest);
     unsigned short* px = reinterpret_cast<unsigned short*>(wsb + pixels_at);
-    const SplitOperand ops[2] = {{w, N, K, K, 1, 0, W3, STRAIGHT}, {x, 1, batch * H * W * C, 0, 1, 0, px, MAGNITUDES}};
+    // (the input's magnitudes have no place for marks: both operands' lie behind the filters' image)
+    unsigned char* const marks = image_marks(W3, N, K, 1);
+    const long units = (K + SBK - 1) / SBK * ((N + 63) / 64);
+    const int own = (int)std::min((units + 3) / 4, kMarks / 2L), nmarks = scr && screen_reads_marks(M, N, K, 1, false, true) ? kMarks : 0;
+    const SplitOperand ops[2] = {{w, N, K, K, 1, 0, W3, STRAIGHT, marks, std::min(own, nmarks)},
+                                 {x, 1, batch * H * W * C, 0, 1, 0, px, MAGNITUDES, marks + own, std::max(0, nmarks - own)}};
     launch_split3(ops, scr ? 2 : 1, scr ? screen_clear(cw, M, N, K, 1) : cleared ? clear_job(cw, kMaxCheckBlocks) : ClearJob{}, (hipStream_t)stream);
     if (scr) {
-        const ScreenPixels pixels = {cv.H, cv.W, cv.C, cv.OW, cv.S, cv.sh, cv.sw, cv.ph, cv.pw, cv.dh, cv.dw, cv.ohow, cv.C / SBK,
+        const ScreenPixels pixels = {cv.H, cv.W, cv.C, cv.OW, (int)R, cv.S, cv.sh, cv.sw, cv.ph, cv.pw, cv.dh, cv.dw, (int)R / 2, cv.S / 2, cv.ohow, cv.C / SBK,
                                      (unsigned)(batch * H * W * C * 2)};
-        const ScreenOperand oa = {px, 0, 0, &pixels}, ow = {W3, 0, 0, nullptr};
+        const ScreenOperand oa = {px, 0, 0, &pixels, marks}, ow = {W3, 0, 0, nullptr, marks};
         rc = run_screen(oa, ow, bias, M, N, K, 1, md, chk, cw, (hipStream_t)stream);
         if (rc != TAO_OK) return rc;
     }
