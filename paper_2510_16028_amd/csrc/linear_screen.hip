@@ -123,17 +123,16 @@ __device__ __forceinline__ void wait_for_copies(int behind) {
 // claims are far off or whose sums they exceed in numbers; from there on with all products; and then those of the first walk that
 // are not decided once more, with all products and without the errors, which are settled.
 //
-// Forms that do so.  Not: 64 x 128 tiles of up to 256 k, whose time is the check's (8 x 8192 x 2048 over 128 231 -> 240 us, 22 spilled
+// Forms that do so: 128 x 128, and few 64 x 64 tiles of more than a slab.  Not: 64 x 128 tiles of up to 256 k, whose time is the check's (8 x 8192 x 2048 over 128 231 -> 240 us, 22 spilled
 // registers), 64 x 64 with four workgroups to a compute unit (128 registers: 19 spilled; 1111 x 3001 over 1001 40.7 -> 50.7), and rows, which are
 // read whole in any case.
-constexpr bool tries_early(int RM, int RN, int PER_CU, int SRC) { return RM * RN == 4 || (RM * RN == 1 && PER_CU == 2 && SRC == IMAGE); }
 // Bytes behind the histogram: the stages, or the strips of sums with the slab that is requested under them.
-constexpr int stage_bytes(int RM, int RN, int WVM, int WVN, int GPS, int NST, int SRC) {
+constexpr int stage_bytes(int RM, int RN, int WVM, int WVN, int GPS, int NST, int SRC, bool EARLY) {
     const int group = WVM * RM * 32 * (SRC == ROWS ? 128 : 64) + WVN * RN * 32 * 64;
-    const int early = tries_early(RM, RN, 2, SRC) && RM * RN > 1 ? WVM * WVN * RN * 4096 + GPS * group : 0;
+    const int early = EARLY && RM * RN > 1 ? WVM * WVN * RN * 4096 + GPS * group : 0;
     return early > NST * GPS * group ? early : NST * GPS * group;
 }
-template <int RM, int RN, int WVM, int WVN, int GPS, int NST, int PER_CU, int SRC, bool UNDERFLOW>
+template <int RM, int RN, int WVM, int WVN, int GPS, int NST, int PER_CU, int SRC, bool EARLY, bool UNDERFLOW>
 __global__ __launch_bounds__(WVM * WVN * 64, WVM * WVN * PER_CU / 4) void screen_product(ScreenArgs p) {
     constexpr int WAVES = WVM * WVN, THREADS = WAVES * 64;
     constexpr int TM = WVM * RM * 32, TN = WVN * RN * 32;
@@ -145,12 +144,11 @@ __global__ __launch_bounds__(WVM * WVN * 64, WVM * WVN * PER_CU / 4) void screen
     // a wavefront's strip of sums: 32 x COLS, rows padded, or (no padding: the LDS holds one workgroup more) their 16-byte units at u ^ (row & 15)
     constexpr int COLS = RN * 32, STRIP = COLS + (SPARE ? 0 : 4);
     static_assert(!SPARE || COLS == 64, "sixteen units to a row");
-    static_assert(WAVES * 32 * STRIP * 4 <= stage_bytes(RM, RN, WVM, WVN, GPS, NST, SRC), "the strips lie in the stages");
+    static_assert(WAVES * 32 * STRIP * 4 <= stage_bytes(RM, RN, WVM, WVN, GPS, NST, SRC, EARLY), "the strips lie in the stages");
     constexpr int CHAINS = RM * RN == 1 ? 2 : 1;                               // (a single accumulator would be one serial chain)
     // Both halves of a group are read before its two products where the registers allow it: the wait for the second then passes under the
     // first product (64 x 200 over 8192 52.0 -> 46.0 us, 512 x 768 over 3072 28.4 -> 26.6).
     constexpr bool AHEAD = RM * RN == 1 && PER_CU == 2 && SRC == IMAGE;
-    constexpr bool EARLY = tries_early(RM, RN, PER_CU, SRC);
     static_assert(!EARLY || THREADS >= kMarks / 2, "a thread for four marks");
     extern __shared__ __attribute__((aligned(16))) char lds[];
     unsigned int* const hist = reinterpret_cast<unsigned int*>(lds);
@@ -841,12 +839,12 @@ __global__ __launch_bounds__(WVM * WVN * 64, WVM * WVN * PER_CU / 4) void screen
     }
 }
 
-template <int RM, int RN, int WVM, int WVN, int GPS, int NST, int PER_CU, int SRC, bool UNDERFLOW = spare_words(RM * RN) == 0>
+template <int RM, int RN, int WVM, int WVN, int GPS, int NST, int PER_CU, int SRC, bool EARLY, bool UNDERFLOW = spare_words(RM * RN) == 0>
 int launch_config(ScreenArgs& p, long batch, hipStream_t st) {
-    if (!UNDERFLOW && p.eps_rel > 1.0) return launch_config<RM, RN, WVM, WVN, GPS, NST, PER_CU, SRC, true>(p, batch, st);
+    if (!UNDERFLOW && p.eps_rel > 1.0) return launch_config<RM, RN, WVM, WVN, GPS, NST, PER_CU, SRC, EARLY, true>(p, batch, st);
     constexpr int TM = WVM * RM * 32, TN = WVN * RN * 32;
-    constexpr int lds_bytes = stage_bytes(RM, RN, WVM, WVN, GPS, NST, SRC) + (kHistWords + spare_words(RM * RN) + (tries_early(RM, RN, PER_CU, SRC) ? kEarlyWords : 0)) * 4;
-    auto kernel = &screen_product<RM, RN, WVM, WVN, GPS, NST, PER_CU, SRC, UNDERFLOW>;
+    constexpr int lds_bytes = stage_bytes(RM, RN, WVM, WVN, GPS, NST, SRC, EARLY) + (kHistWords + spare_words(RM * RN) + (EARLY ? kEarlyWords : 0)) * 4;
+    auto kernel = &screen_product<RM, RN, WVM, WVN, GPS, NST, PER_CU, SRC, EARLY, UNDERFLOW>;
     static OncePerDevice configured;
     const hipError_t e = configured.run([&] {
         return hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
@@ -863,13 +861,15 @@ int launch_config(ScreenArgs& p, long batch, hipStream_t st) {
     return launch_status();
 }
 
-enum Config { kRows64x128, kRows64x64, kPixels128x128, kPixels64x64, kImages64x128, kImages128x128, kImages64x64Few, kImages64x64 };
+enum Config { kRows64x128, kRows64x64, kPixels128x128, kPixels64x64, kImages64x128, kImages128x128, kImages64x64Few, kImages64x64Short, kImages64x64 };
 // Tiles of 128 x 128, two workgroups to a compute unit, where they give every compute unit one (us of the whole call on images, with
 // them / with 64 x 64: 2048 x 12288 over 4096 248 / 362, 2048 x 4096 over 4096 94 / 122, 1111 x 3001 over 1001, 216 tiles, 37 / 33);
 // up to 256 k, where the check is most of the work, 64 x 128 and three (8 x 8192 x 2048 over 128 250, with 128 x 128 280; 228 now).
 // Otherwise, and where a column tile would be half empty, 64 x 64: four to a compute unit, or two with four groups to a barrier
 // where there are no more, as a group's copies, barrier and reads of LDS then are a chain that nothing else hides (512 x 3072 over
 // 768 21, with a group to a barrier 24, with 128 x 128 31; 512 x 768 over 3072 29 / 37 / 57; 256 x 1024 over 8192 51 / 71 / 110).
+// Few 64 x 64 tiles try first slabs, of 128 k, where there are four or more (512 x 768 over 416 18.2 -> 17.6, 300 x 300 over 1000 19.3 -> 15.9; with
+// two, 912 x 64 over 228, the screen alone 9.2 -> 11.3).
 // A read as rows: 64 x 128 where they fill the chip (8 x 8192 x 128 over 2048 145, with 64 x 64 183), else 64 x 64 (12 x 512 x 64 over
 // 512 22 / 26).
 Config screen_config(long M, long N, long K, long batch, bool rows, bool pixels) {
@@ -879,7 +879,7 @@ Config screen_config(long M, long N, long K, long batch, bool rows, bool pixels)
     if (rows) return ((M + 63) / 64) * ((N + 127) / 128) * batch >= n && N > 64 ? kRows64x128 : kRows64x64;
     if (pixels) return wide ? kPixels128x128 : kPixels64x64;
     if (wide) return groups <= 8 ? kImages64x128 : kImages128x128;
-    return t64 <= 2 * n ? kImages64x64Few : kImages64x64;
+    return t64 > 2 * n ? kImages64x64 : groups > 12 ? kImages64x64Few : kImages64x64Short;
 }
 
 }  // namespace
@@ -915,14 +915,15 @@ int launch_screen(const ScreenOperand& A, const ScreenOperand& W, const float* b
     p.hist = ws.hist; p.coarse = ws.coarse; p.stats = ws.stats;
     if (chk.ldy >= kScreenMaxLd) return TAO_ERR_SHAPE;
     switch (screen_config(M, N, K, batch, rows, pixels)) {
-        case kRows64x128:     return launch_config<1, 2, 2, 2, 1, 4, 2, ROWS>(p, batch, st);
-        case kRows64x64:      return launch_config<1, 1, 2, 2, 2, 3, 2, ROWS>(p, batch, st);
-        case kPixels128x128:  return launch_config<2, 2, 2, 2, 2, 2, 2, PIXELS>(p, batch, st);
-        case kPixels64x64:    return launch_config<1, 1, 2, 2, 2, 2, 4, PIXELS>(p, batch, st);
-        case kImages64x128:   return launch_config<1, 2, 2, 2, 1, 3, 3, IMAGE>(p, batch, st);
-        case kImages128x128:  return launch_config<2, 2, 2, 2, 2, 2, 2, IMAGE>(p, batch, st);
-        case kImages64x64Few: return launch_config<1, 1, 2, 2, 4, 2, 2, IMAGE>(p, batch, st);
-        case kImages64x64:    return launch_config<1, 1, 2, 2, 2, 2, 4, IMAGE>(p, batch, st);
+        case kRows64x128:     return launch_config<1, 2, 2, 2, 1, 4, 2, ROWS, false>(p, batch, st);
+        case kRows64x64:      return launch_config<1, 1, 2, 2, 2, 3, 2, ROWS, false>(p, batch, st);
+        case kPixels128x128:  return launch_config<2, 2, 2, 2, 2, 2, 2, PIXELS, true>(p, batch, st);
+        case kPixels64x64:    return launch_config<1, 1, 2, 2, 2, 2, 4, PIXELS, false>(p, batch, st);
+        case kImages64x128:   return launch_config<1, 2, 2, 2, 1, 3, 3, IMAGE, false>(p, batch, st);
+        case kImages128x128:  return launch_config<2, 2, 2, 2, 2, 2, 2, IMAGE, true>(p, batch, st);
+        case kImages64x64Few: return launch_config<1, 1, 2, 2, 4, 2, 2, IMAGE, true>(p, batch, st);
+        case kImages64x64Short: return launch_config<1, 1, 2, 2, 4, 2, 2, IMAGE, false>(p, batch, st);
+        case kImages64x64:    return launch_config<1, 1, 2, 2, 2, 2, 4, IMAGE, false>(p, batch, st);
     }
     return TAO_ERR_SHAPE;                                    // (not reached)
 }
