@@ -184,7 +184,8 @@ __global__ __launch_bounds__(kRowThreads) void softmax_bound(
 // end around every one of them), four wavefronts met at three barriers per row, and an element took 58 vector instructions.
 template <int TPR>
 __device__ __forceinline__ void wide_group_sum(double* v, int count, double* smem) {
-    for (int i = 0; i < count; ++i) v[i] = wave_sum(v[i]);
+    constexpr int STEPS = TPR >= kWave ? 6 : TPR == 32 ? 5 : 4;       // (a row group is 16 lanes at least)
+    for (int i = 0; i < count; ++i) v[i] = wave_all<0, STEPS>(v[i], [](double a, double b) { return a + b; });
     if (TPR > kWave) {
         const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
         const int first = (threadIdx.x / TPR) * (TPR / kWave);       // first wavefront of this row group
@@ -213,26 +214,53 @@ __device__ __forceinline__ void wide_group_max_or(float& m, int& flag, double* s
 }
 
 // The four values of a thread's vector, loaded without a branch: from clamped positions that exist; row_fill then
-// replaces those at and beyond `limit`.  (Behind a test for the row's end every load waited for the one before it.)
-// FULL: 16-byte aligned rows of whole vectors, four consecutive columns from idx on.  Otherwise the columns idx,
-// idx + step, ...: with step the row group's size neighbouring threads read neighbouring columns.
-// last: the last position of a vector (FULL) or value.
-template <bool FULL, bool STREAM, int STEP, class Idx>
+// replaces those that are not the thread's.  (Behind a test for the row's end every load waited for the one before it.)
+// WHOLE: 16-byte aligned rows of whole vectors, four consecutive columns from idx on.  ANY: four consecutive columns by one 16-byte load
+// as well, at any alignment, of rows of four columns or more; a vector that the row's end cuts is read from the row's last four columns, of which
+// the first belong to the vector before it.  SINGLE: the columns idx, idx + step, ..., with step the row group's size: neighbouring threads
+// read neighbouring columns, four loads to a vector, but a row that ends early in its last vectors is spread more evenly (row_form).
+// last: the last position of a vector or (SINGLE) value.
+enum { SINGLE, WHOLE, ANY };
+typedef float floatx4u __attribute__((ext_vector_type(4), aligned(4)));
+template <int FULL, bool STREAM, int STEP, class Idx>
 __device__ __forceinline__ float4 row_vec(const float* __restrict__ row, Idx idx, Idx last) {
-    if (FULL) {
+    if (FULL == WHOLE) {
         const float4* p = reinterpret_cast<const float4*>(row + min(idx, last));
         return STREAM ? ntload4(p) : *p;
     }
+    if (FULL == ANY) {
+        const floatx4u* p = reinterpret_cast<const floatx4u*>(row + min(idx, last));
+        if (STREAM) return __builtin_bit_cast(float4, __builtin_nontemporal_load(p));
+        return __builtin_bit_cast(float4, *p);
+    }
     return make_float4(row[min(idx, last)], row[min((Idx)(idx + STEP), last)], row[min((Idx)(idx + 2 * STEP), last)], row[min((Idx)(idx + 3 * STEP), last)]);
 }
-template <bool FULL, int STEP, class Idx>
-__device__ __forceinline__ float4 row_fill(float4 r, Idx idx, Idx limit, float fill) {
-    const bool i0 = idx < limit, i1 = FULL ? i0 : idx + STEP < limit, i2 = FULL ? i0 : idx + 2 * STEP < limit, i3 = FULL ? i0 : idx + 3 * STEP < limit;
-    return make_float4(i0 ? r.x : fill, i1 ? r.y : fill, i2 ? r.z : fill, i3 ? r.w : fill);
+// Whether value c of the vector at idx is the thread's; and whether all four are.
+template <int FULL, int STEP, class Idx>
+__device__ __forceinline__ bool row_has(Idx idx, Idx limit, Idx last, int c) {
+    return FULL == WHOLE ? idx < limit : FULL == ANY ? idx < limit && idx - min(idx, last) <= (Idx)c : idx + c * STEP < limit;
+}
+// How many of the vector at idx, inside the row, belong to the one before; and a bit for each that does not.
+template <int FULL, class Idx>
+__device__ __forceinline__ unsigned row_others(Idx idx, Idx last) { return FULL == ANY ? (unsigned)(idx - min(idx, last)) : 0u; }
+// A vector's claims, outputs and estimates for quick_check_four.
+template <int FULL>
+__device__ __forceinline__ void leave_others(unsigned others, floatv4& c, floatv4& y, floatv4& at) {
+    if (FULL != ANY) return;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        const bool other = (unsigned)i < others;
+        c[i] = other ? 0.f : c[i]; y[i] = other ? 0.f : y[i]; at[i] = other ? 0.f : at[i];
+    }
+}
+template <int FULL, int STEP, class Idx>
+__device__ __forceinline__ float4 row_fill(float4 r, Idx idx, Idx limit, Idx last, float fill) {
+    auto has = [&](int c) __attribute__((always_inline)) { return row_has<FULL, STEP>(idx, limit, last, c); };
+    return make_float4(has(0) ? r.x : fill, has(1) ? r.y : fill, has(2) ? r.z : fill, has(3) ? r.w : fill);
 }
 #define TAO_VEC_IDX(v) (FULL ? ((Idx)(v) * TPR + lt) * 4 : (Idx)(v) * (4 * TPR) + lt)
 
-template <int TPR, int V, bool FULL, bool QUICK>
+template <int TPR, int V, int FULL, bool QUICK>
 __global__ __launch_bounds__(kCheckThreads) void softmax_check(
     const float* __restrict__ x, const float* __restrict__ y, const float* __restrict__ claimed,
     long rows, long cols, long ld, RowConsts k, double alpha, double eps_rel,
@@ -253,6 +281,7 @@ __global__ __launch_bounds__(kCheckThreads) void softmax_check(
     if (tid == 0) largest = 0;
     __syncthreads();
     ThreadAcc acc_chk;
+    unsigned beyond = 0;                                     // counted in bin 0, but another vector's
     const int rep = tid & (kReplicas - 1);
     const int nv = CACHED ? V : (int)((cols + TPR * 4 - 1) / (TPR * 4));
     const long nblocks = (rows + RPB - 1) / RPB;
@@ -298,8 +327,8 @@ __global__ __launch_bounds__(kCheckThreads) void softmax_check(
             __builtin_amdgcn_sched_barrier(0);               // (all requests leave before the first is waited for)
         }
         for (int v = 0; v < nv; ++v) {
-            const float4 X = row_fill<FULL, TPR>(CACHED ? xv[v] : row_vec<FULL, false, TPR>(x + roff, TAO_VEC_IDX(v), last), TAO_VEC_IDX(v), limit, -INFINITY);
-            if (CACHED) { xv[v] = X; yv[v] = row_fill<FULL, TPR>(yv[v], TAO_VEC_IDX(v), limit, 0.f); }
+            const float4 X = row_fill<FULL, TPR>(CACHED ? xv[v] : row_vec<FULL, false, TPR>(x + roff, TAO_VEC_IDX(v), last), TAO_VEC_IDX(v), limit, last, -INFINITY);
+            if (CACHED) { xv[v] = X; yv[v] = row_fill<FULL, TPR>(yv[v], TAO_VEC_IDX(v), limit, last, 0.f); }
             const float e[4] = {X.x, X.y, X.z, X.w};
 #pragma unroll
             for (int c = 0; c < 4; ++c) { bad |= (e[c] != e[c]) | (e[c] == INFINITY); m = fmaxf(m, e[c]); }
@@ -317,8 +346,8 @@ __global__ __launch_bounds__(kCheckThreads) void softmax_check(
             q = (double)(masked ? 0.f : fabsf(ye)) * k.inv1mu;
         };
         for (int v = 0; v < nv; ++v) {
-            const float4 X = CACHED ? xv[v] : row_fill<FULL, TPR>(row_vec<FULL, false, TPR>(x + roff, TAO_VEC_IDX(v), last), TAO_VEC_IDX(v), limit, -INFINITY);
-            const float4 Y = CACHED ? yv[v] : row_fill<FULL, TPR>(row_vec<FULL, false, TPR>(y + roff, TAO_VEC_IDX(v), last), TAO_VEC_IDX(v), limit, 0.f);
+            const float4 X = CACHED ? xv[v] : row_fill<FULL, TPR>(row_vec<FULL, false, TPR>(x + roff, TAO_VEC_IDX(v), last), TAO_VEC_IDX(v), limit, last, -INFINITY);
+            const float4 Y = CACHED ? yv[v] : row_fill<FULL, TPR>(row_vec<FULL, false, TPR>(y + roff, TAO_VEC_IDX(v), last), TAO_VEC_IDX(v), limit, last, 0.f);
             const float xe[4] = {X.x, X.y, X.z, X.w}, ye[4] = {Y.x, Y.y, Y.z, Y.w};
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
@@ -356,11 +385,12 @@ __global__ __launch_bounds__(kCheckThreads) void softmax_check(
                 q_rho(xe[c], ye[c], q, rho);
                 return up32g(q * fma(rho, w1, w0), up.mul, up.sub);
             };
-            if (FULL || idx + 3 * TPR < limit) {
+            const unsigned others = row_others<FULL>(idx, last), own = 15u & 15u << others;
+            if (FULL != SINGLE || idx + 3 * TPR < limit) {
                 if (!QUICK) {
                     const float c4[4] = {ce[0], ce[1], ce[2], ce[3]}, y4[4] = {ye[0], ye[1], ye[2], ye[3]};
                     const float t4[4] = {tau(0), tau(1), tau(2), tau(3)};
-                    check_four(c4, y4, t4, alpha, eps_rel, hist, rep, acc_chk);
+                    check_four(c4, y4, t4, alpha, eps_rel, hist, rep, acc_chk, own);
                     continue;
                 }
                 floatv4 at;
@@ -370,16 +400,18 @@ __global__ __launch_bounds__(kCheckThreads) void softmax_check(
                     const float rho = fminf(fmaf(fmaf(a, a, a), invf, cef), 0x1p60f);
                     at[c] = (xe[c] == -INFINITY ? 0.f : fabsf(ye[c])) * fmaf(rho, w1f, w0f);
                 }
-                quick_check_four<(V == 1 || (V == 2 && TPR < 1024))>(ce, ye, at, tau, qc, alpha, eps_rel, hist, rep, acc_chk, &largest, known, known != 0);
+                leave_others<FULL>(others, ce, ye, at);
+                if (quick_check_four<(V == 1 || (V == 2 && TPR < 1024))>(ce, ye, at, tau, qc, alpha, eps_rel, hist, rep, acc_chk, &largest, known, known != 0, own)) beyond += others;
                 continue;
             }
 #pragma unroll
-            for (int c = 0; c < 3; ++c) {
-                if (idx + c * TPR >= limit) break;
+            for (int c = 0; c < 4; ++c) {
+                if (!row_has<FULL, TPR>(idx, limit, last, c)) continue;
                 check_one(ce[c], ye[c], tau(c), alpha, eps_rel, hist, rep, acc_chk);
             }
         }
     }
+    if (FULL == ANY && QUICK && beyond) atomicSub(&hist[rep], beyond);
     __syncthreads();
     finish_pass(hist, acc_chk, red, pass);
 }
@@ -714,7 +746,7 @@ __global__ __launch_bounds__(kRowThreads) void rmsnorm_bound_noy(
 // What bounds it: HBM for many rows (32768 x 768: LayerNorm 180 -> 90 us, RMSNorm 128 -> 65 us; LayerNorm 8192 x 2048 170 -> 67 us,
 // whose rows are now kept instead of read again), the chain of one row -- loads, two reductions, a square root and divisions in
 // binary64 -- for few (2048 x 4096 RMSNorm 34.4 -> 29.7 us with its finalising launch), which is why the next rows are requested early.
-template <bool RMS, int TPR, int V, bool FULL, bool QUICK>
+template <bool RMS, int TPR, int V, int FULL, bool QUICK>
 __global__ __launch_bounds__(kCheckThreads) void norm_check(
     const float* __restrict__ x, const float* __restrict__ y, const float* __restrict__ g, const float* __restrict__ claimed,
     long rows, long cols, long ld, RowConsts k, double alpha, double eps_rel,
@@ -735,6 +767,7 @@ __global__ __launch_bounds__(kCheckThreads) void norm_check(
     if (tid == 0) largest = 0;
     __syncthreads();
     ThreadAcc acc_chk;
+    unsigned beyond = 0;                                     // counted in bin 0, but another vector's
     const int rep = tid & (kReplicas - 1);
     const int nv = CACHED ? V : (int)((cols + TPR * 4 - 1) / (TPR * 4));
     const long nblocks = (rows + RPB - 1) / RPB;
@@ -782,7 +815,7 @@ __global__ __launch_bounds__(kCheckThreads) void norm_check(
             __builtin_amdgcn_sched_barrier(0);               // (all requests leave before the first is waited for)
         }
         for (int v = 0; v < nv; ++v) {
-            const float4 X = row_fill<FULL, TPR>(CACHED ? xv[v] : row_vec<FULL, false, TPR>(x + roff, TAO_VEC_IDX(v), last), TAO_VEC_IDX(v), limit, 0.f);
+            const float4 X = row_fill<FULL, TPR>(CACHED ? xv[v] : row_vec<FULL, false, TPR>(x + roff, TAO_VEC_IDX(v), last), TAO_VEC_IDX(v), limit, last, 0.f);
             if (CACHED) xv[v] = X;
             const float e[4] = {X.x, X.y, X.z, X.w};
 #pragma unroll
@@ -806,11 +839,11 @@ __global__ __launch_bounds__(kCheckThreads) void norm_check(
             const double E_mu = ((k.G * a1[1]) * k.inv_n + k.cd_u * fabs(mu)) * k.inv1mcd;
             double a2[2] = {0.0, 0.0};                                   // sum |d|, sum d^2
             for (int v = 0; v < nv; ++v) {
-                const float4 X = CACHED ? xv[v] : row_fill<FULL, TPR>(row_vec<FULL, false, TPR>(x + roff, TAO_VEC_IDX(v), last), TAO_VEC_IDX(v), limit, 0.f);
+                const float4 X = CACHED ? xv[v] : row_fill<FULL, TPR>(row_vec<FULL, false, TPR>(x + roff, TAO_VEC_IDX(v), last), TAO_VEC_IDX(v), limit, last, 0.f);
                 const float e[4] = {X.x, X.y, X.z, X.w};
 #pragma unroll
                 for (int c = 0; c < 4; ++c) {
-                    const double d = (TAO_VEC_IDX(v) + (FULL ? c : c * TPR) < limit) ? (double)e[c] - mu : 0.0;
+                    const double d = row_has<FULL, TPR>(TAO_VEC_IDX(v), limit, last, c) ? (double)e[c] - mu : 0.0;
                     a2[0] += fabs(d);
                     a2[1] = fma(d, d, a2[1]);
                 }
@@ -854,29 +887,32 @@ __global__ __launch_bounds__(kCheckThreads) void norm_check(
                 const double ep = (double)fabsf(ge[c]) * fma(K1, ad, K0);
                 return up32g(fma(k.u, (double)fabsf(ye[c]), ep), up.mul, up.sub);
             };
-            if (QUICK && (FULL || idx + 3 * TPR < limit)) {
+            const unsigned others = row_others<FULL>(idx, last), own = 15u & 15u << others;
+            if (QUICK && (FULL != SINGLE || idx + 3 * TPR < limit)) {
                 floatv4 at;
 #pragma unroll
                 for (int c = 0; c < 4; ++c) {
                     if (RMS) at[c] = fmaf(fabsf(xe[c] * ge[c]), ff, uf * fabsf(ye[c]));
                     else     at[c] = fmaf(fabsf(ge[c]), fmaf(K1f, fabsf(xe[c] - muf), K0f), uf * fabsf(ye[c]));
                 }
-                quick_check_four<(V == 1 || (V == 2 && TPR < 1024))>(ce, ye, at, tau, qc, alpha, eps_rel, hist, rep, acc_chk, &largest, known, known != 0);
+                leave_others<FULL>(others, ce, ye, at);
+                if (quick_check_four<(V == 1 || (V == 2 && TPR < 1024))>(ce, ye, at, tau, qc, alpha, eps_rel, hist, rep, acc_chk, &largest, known, known != 0, own)) beyond += others;
                 continue;
             }
-            if (CACHED && (FULL || idx + 3 * TPR < limit)) {
+            if (CACHED && (FULL != SINGLE || idx + 3 * TPR < limit)) {
                 const float c4[4] = {ce[0], ce[1], ce[2], ce[3]}, y4[4] = {ye[0], ye[1], ye[2], ye[3]};
                 const float t4[4] = {tau(0), tau(1), tau(2), tau(3)};
-                check_four(c4, y4, t4, alpha, eps_rel, hist, rep, acc_chk);
+                check_four(c4, y4, t4, alpha, eps_rel, hist, rep, acc_chk, own);
                 continue;
             }
 #pragma unroll
             for (int c = 0; c < 4; ++c) {                    // (rows re-read from memory: no registers for four side by side)
-                if (idx + (FULL ? c : c * TPR) >= limit) break;
+                if (!row_has<FULL, TPR>(idx, limit, last, c)) continue;
                 check_one(ce[c], ye[c], tau(c), alpha, eps_rel, hist, rep, acc_chk);
             }
         }
     }
+    if (FULL == ANY && QUICK && beyond) atomicSub(&hist[rep], beyond);
     __syncthreads();
     finish_pass(hist, acc_chk, red, pass);
 }
@@ -938,14 +974,23 @@ __global__ __launch_bounds__(kRowThreads) void bn_affine_bound(
     }
 }
 
+// How a ragged row is read whose group holds V vectors of 4 TPR columns: by vectors unless most of the last one would be empty (us, by single
+// values / by vectors: LayerNorm 30000 x 511 58.2 / 51.5, 6442 x 861 48.1 / 38.8, softmax of 4 x 2045 x 2045 with its products 175 / 158; but LayerNorm
+// 10000 x 1031 58.4 / 63.2, 30000 x 259 45.7 / 48.8, 155 x 3233 13.8 / 14.5).
+static int row_form(bool whole, long cols, long tpr, long V) {
+    if (whole) return WHOLE;
+    return cols < 4 || (V == 2 && cols * 5 < tpr * V * 4 * 4) ? SINGLE : ANY;
+}
 // The one-pass checks of rows.  Quick settlement pays from eight rows per row group on, four where that is a wavefront; below, too many elements are
 // among the first a workgroup sees and the second route is only more code to fetch (us with / without: softmax 512 x 512
 // 20 / 16, RMSNorm 4096 x 768 28 / 25, but RMSNorm 8192 x 2048 55 / 59, 8192 x 4096 94 / 109).
 // From two rows per wavefront on a row of 513 to 1024 (softmax: 2048) columns belongs to one wavefront -- no barrier, the
 // wavefronts of a workgroup drift apart, so that some load while others calculate; fewer rows are divided
 // among four wavefronts, which fill the chip sooner (8192 x 1024 34 against 46 us, 4096 x 2048 45 against 40).
+// Rows of the norms of up to 64 and 128 columns belong to 16 and 32 lanes (a wavefront each, most of whose lanes then held nothing: RMSNorm 161713 x 56
+// 96.9 us, now 35.3, LayerNorm 130000 x 64 121.7 / 37.6, 100000 x 100 88.5 / 49.1, RMSNorm 60 x 61 10.7 / 8.0).
 constexpr long kWaveRows = 2L * kMaxCheckBlocks * (kCheckThreads / kWave);
-static bool quick_pays(long rows, int tpr) { return rows >= (tpr == kWave ? 4L : 8L) * kMaxCheckBlocks * (kCheckThreads / tpr); }
+static bool quick_pays(long rows, int tpr) { return rows >= (tpr <= kWave ? 4L : 8L) * kMaxCheckBlocks * (kCheckThreads / tpr); }
 
 // Pick the row-group shape for a row length and launch KERNEL<TPR, V>.  A single wavefront owns
 // a row of up to WMAX columns (no barrier, no LDS exchange); longer rows take a workgroup.
@@ -1165,11 +1210,19 @@ int tao_bound_check_norm(int kind, const float* x, const float* y_ref, const flo
     };
     auto quick = [&](int tpr) { return quick_pays(rows, tpr); };
 #define TAO_NORM_CHECK_Q(RMS, TPR, V, Q) \
-    (full ? launch(norm_check<RMS, TPR, V, true, Q>, TPR, rows, cols, ld) : launch(norm_check<RMS, TPR, V, false, Q>, TPR, rows, cols, ld))
+    do {                                                                                                    \
+        const int form = row_form(full, cols, TPR, V);                                                      \
+        if (form == WHOLE)    launch(norm_check<RMS, TPR, V, WHOLE, Q>, TPR, rows, cols, ld);               \
+        else if (form == ANY) launch(norm_check<RMS, TPR, V, ANY, Q>, TPR, rows, cols, ld);                 \
+        else                  launch(norm_check<RMS, TPR, V, V == 2 ? SINGLE : ANY, Q>, TPR, rows, cols, ld); \
+    } while (0)
 #define TAO_NORM_CHECK(RMS, TPR, V) do { if (quick(TPR)) TAO_NORM_CHECK_Q(RMS, TPR, V, true); else TAO_NORM_CHECK_Q(RMS, TPR, V, false); } while (0)
 #define TAO_NORM_CHECK_ROWS(RMS)                                                                            \
     do {                                                                                                    \
-        if (cols <= 256)                     TAO_NORM_CHECK(RMS, 64, 1);                                    \
+        if (cols < 4)                        launch(norm_check<RMS, 64, 1, SINGLE, false>, 64, rows, cols, ld); \
+        else if (cols <= 64)                 TAO_NORM_CHECK(RMS, 16, 1);                                    \
+        else if (cols <= 128)                TAO_NORM_CHECK(RMS, 32, 1);                                    \
+        else if (cols <= 256)                TAO_NORM_CHECK(RMS, 64, 1);                                    \
         else if (cols <= 512)                TAO_NORM_CHECK(RMS, 64, 2);                                    \
         else if (cols <= 1024 && rows >= kWaveRows) TAO_NORM_CHECK_Q(RMS, 64, 4, true);                    \
         else if (cols <= 1024)               TAO_NORM_CHECK(RMS, 256, 1);                                   \
@@ -1179,7 +1232,7 @@ int tao_bound_check_norm(int kind, const float* x, const float* y_ref, const flo
         else                                 TAO_NORM_CHECK_Q(RMS, 1024, 0, false);                         \
     } while (0)
     if (n == 0) {
-        if (rms) launch(norm_check<true, 64, 1, false, false>, 64, 0L, 1L, 1L); else launch(norm_check<false, 64, 1, false, false>, 64, 0L, 1L, 1L);
+        if (rms) launch(norm_check<true, 64, 1, SINGLE, false>, 64, 0L, 1L, 1L); else launch(norm_check<false, 64, 1, SINGLE, false>, 64, 0L, 1L, 1L);
     } else if (rms) {
         TAO_NORM_CHECK_ROWS(true);
     } else {
@@ -1223,13 +1276,20 @@ int tao_bound_check_softmax(const float* x, const float* y_ref, const float* cla
                                k, alpha, eps_rel, pass_out(w, nblocks, n, out));
         };
         auto quick = [&](int tpr) { return quick_pays(rows, tpr); };
-#define TAO_SOFTMAX_CHECK_Q(TPR, V, Q) (full ? launch(softmax_check<TPR, V, true, Q>, TPR) : launch(softmax_check<TPR, V, false, Q>, TPR))
+#define TAO_SOFTMAX_CHECK_Q(TPR, V, Q) \
+    do {                                                                                        \
+        const int form = row_form(full, cols, TPR, V);                                          \
+        if (form == WHOLE)    launch(softmax_check<TPR, V, WHOLE, Q>, TPR);                     \
+        else if (form == ANY) launch(softmax_check<TPR, V, ANY, Q>, TPR);                       \
+        else                  launch(softmax_check<TPR, V, V == 2 ? SINGLE : ANY, Q>, TPR);     \
+    } while (0)
 #define TAO_SOFTMAX_CHECK(TPR, V) do { if (quick(TPR)) TAO_SOFTMAX_CHECK_Q(TPR, V, true); else TAO_SOFTMAX_CHECK_Q(TPR, V, false); } while (0)
-        if (cols <= 256)       TAO_SOFTMAX_CHECK(64, 1);
+        if (cols < 4)          launch(softmax_check<64, 1, SINGLE, false>, 64);
+        else if (cols <= 256)  TAO_SOFTMAX_CHECK(64, 1);
         else if (cols <= 512)  TAO_SOFTMAX_CHECK(64, 2);
         else if (cols <= 1024 && rows >= kWaveRows) TAO_SOFTMAX_CHECK_Q(64, 4, true);
         else if (cols <= 1024) TAO_SOFTMAX_CHECK(256, 1);
-        else if (cols <= 2048 && rows >= kWaveRows && full) launch(softmax_check<64, 8, true, true>, 64);   // (four addresses to a vector: no registers for eight)
+        else if (cols <= 2048 && rows >= kWaveRows) TAO_SOFTMAX_CHECK_Q(64, 8, true);
         else if (cols <= 2048) TAO_SOFTMAX_CHECK(256, 2);
         else if (cols <= 4096) TAO_SOFTMAX_CHECK(512, 2);
         else if (cols <= 8192) TAO_SOFTMAX_CHECK(1024, 2);
@@ -1238,7 +1298,7 @@ int tao_bound_check_softmax(const float* x, const float* y_ref, const float* cla
 #undef TAO_SOFTMAX_CHECK_Q
     } else {
         // nothing to examine: an empty partial, so that the profile reports n = 0
-        hipLaunchKernelGGL((softmax_check<64, 1, false, false>), dim3(1), dim3(kCheckThreads), 0, st, x, y_ref, claimed, 0L, 1L, 1L,
+        hipLaunchKernelGGL((softmax_check<64, 1, SINGLE, false>), dim3(1), dim3(kCheckThreads), 0, st, x, y_ref, claimed, 0L, 1L, 1L,
                            k, alpha, eps_rel, pass_out(w, nblocks, n, out));
     }
     launch_finish(w, nblocks, n, out, st);

@@ -58,9 +58,10 @@ __device__ __forceinline__ CheckedElement check_arith(float c, float r, float t,
 // for the shortcut, that is what happened).  The shortcut is taken for the four together or not at
 // all; the full arithmetic returns the shortcut's result for an element that qualifies (d = 0, e = 0 or
 // 0/0), so the profile does not depend on the route.
+// own: a bit for each that counts (all of them, unless a row's end cuts the four).
 template <int R = kReplicas>
 __device__ __forceinline__ void check_four(const float (&c)[4], const float (&r)[4], const float (&t)[4], double alpha,
-                                           double eps_rel, unsigned int* hist, int rep, ThreadAcc& acc) {
+                                           double eps_rel, unsigned int* hist, int rep, ThreadAcc& acc, unsigned own = 15u) {
     bool same = true;
 #pragma unroll
     for (int i = 0; i < 4; ++i) same = same && c[i] == r[i] && fabsf(c[i]) != INFINITY;
@@ -74,10 +75,11 @@ __device__ __forceinline__ void check_four(const float (&c)[4], const float (&r)
     }
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        acc.violations += o[i].violation;
-        acc.nans += o[i].is_nan;
-        acc.max_bits = max(acc.max_bits, o[i].is_nan ? 0u : o[i].bits);
-        atomicAdd(&hist[o[i].bin * R + rep], 1u);
+        const unsigned int mine = own >> i & 1u;
+        acc.violations += o[i].violation & mine;
+        acc.nans += o[i].is_nan & mine;
+        acc.max_bits = max(acc.max_bits, o[i].is_nan || !mine ? 0u : o[i].bits);
+        atomicAdd(&hist[o[i].bin * R + rep], mine);
     }
 }
 
@@ -130,11 +132,13 @@ typedef float floatv4 __attribute__((ext_vector_type(4)));      // (indexed by a
 // exact way takes the four side by side, for kernels that have the registers (small tensors see little else);
 // otherwise one after the other in a loop, as four binary64 divisions would set the kernel's register count.
 // attempt: false goes the exact way at once (before any error is known, known == 0, only equal values can be settled).
+// own: as in check_four; with any that does not count the caller passes 0 for its c, r and at, and the estimates, which take it for an error of
+// 0, add one to bin 0 for it (`beyond`, to be taken off).
 // Returns whether the estimates settled them.
 template <bool WIDE, int R = kReplicas, class Tau>
 __device__ __forceinline__ bool quick_check_four(floatv4 c, floatv4 r, floatv4 at, Tau&& tau,
                                                  const QuickCheck& q, double alpha, double eps_rel, unsigned int* hist, int rep,
-                                                 ThreadAcc& acc, unsigned int* largest, unsigned& known, bool attempt) {
+                                                 ThreadAcc& acc, unsigned int* largest, unsigned& known, bool attempt, unsigned own = 15u) {
     if (attempt) {
         unsigned bin[4];
         bool ok = true;
@@ -149,10 +153,11 @@ __device__ __forceinline__ bool quick_check_four(floatv4 c, floatv4 r, floatv4 a
     if (WIDE) {
         const float c4[4] = {c[0], c[1], c[2], c[3]}, r4[4] = {r[0], r[1], r[2], r[3]};
         const float t4[4] = {tau(0), tau(1), tau(2), tau(3)};
-        check_four<R>(c4, r4, t4, alpha, eps_rel, hist, rep, acc);
+        check_four<R>(c4, r4, t4, alpha, eps_rel, hist, rep, acc, own);
     } else {
 #pragma unroll 1
-        for (int i = 0; i < 4; ++i) check_one<R>(c[i], r[i], tau(i), alpha, eps_rel, hist, rep, acc);
+        for (int i = 0; i < 4; ++i)
+            if (own >> i & 1u) check_one<R>(c[i], r[i], tau(i), alpha, eps_rel, hist, rep, acc);
     }
     if (acc.max_bits > known) atomicMax(largest, acc.max_bits);
     known = max(known, acc.max_bits);
