@@ -367,59 +367,62 @@ __global__ void __launch_bounds__(kSortThreads) radix_count(const float* delta, 
     hist[(long)d * shape.row + tile] = total;
 }
 
-// Exclusive scan of one value per thread over the workgroup; ends with a barrier.
+// Exclusive scan of one value per thread over a workgroup of WAVES wavefronts; ends with a barrier.
+// (By row shifts, and with the wavefronts' totals read at once: through LDS permutes and in a loop over the totals a projection of
+// 8.4 M elements took 96.5 us against 90.9, one of 50000 62.8 against 58.3.)
+template <int WAVES>
 __device__ __forceinline__ unsigned block_exclusive_scan(unsigned v, unsigned* wave_tot, unsigned& block_total) {
     const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
-    unsigned inc = v;
-#pragma unroll
-    for (int o = 1; o < kWave; o <<= 1) {
-        const unsigned t = __shfl_up(inc, o, kWave);
-        if (lane >= o) inc += t;
-    }
+    const unsigned inc = wave_scan(v);
     if (lane == kWave - 1) wave_tot[wave] = inc;
     __syncthreads();
     unsigned before = 0, all = 0;
-    const int nw = blockDim.x / kWave;
-    for (int w = 0; w < nw; ++w) { const unsigned t = wave_tot[w]; if (w < wave) before += t; all += t; }
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) { const unsigned t = wave_tot[w]; before += w < wave ? t : 0u; all += t; }
     __syncthreads();
     block_total = all;
     return before + inc - v;
+}
+
+// Whether some element of a magnitude bin of `count` elements, the first of them at 0-based rank `first`, may exceed its cap.
+__device__ __forceinline__ bool holds_candidates(const CapTable& tab, unsigned bin, unsigned count, unsigned first) {
+    if (count == 0 || bin >= (0x7f800000u >> kMagShift) + 1u) return false;                // (NaN stays whatever its rank)
+    const float top = bin == (0x7f800000u >> kMagShift) ? INFINITY : __uint_as_float(((bin + 1u) << kMagShift) - 1u);
+    const double r = rank_percent((double)first + 1.0, tab.n);
+    const CapSeg& sg = tab.seg[segment_of(r)];
+    return !((double)top <= fmax(sg.head, cap_in_segment(sg, r)));
+}
+// Thread t of 1024 has the flags of bins 2 t and 2 t + 1: 16 threads make a word.
+__device__ __forceinline__ void leave_flags(bool c0, bool c1, unsigned* flag) {
+    const int t = threadIdx.x;
+    unsigned bits = ((unsigned)c0 | ((unsigned)c1 << 1)) << 2 * (t & 15);
+#pragma unroll
+    for (int o = 1; o < 16; o <<= 1) bits |= __shfl_xor(bits, o, kWave);
+    if ((t & 15) == 0) flag[t >> 4] = bits;
 }
 
 // First rank of every bin, the bins whose elements may exceed their caps, and the numbers that lead from a
 // candidate's place to its rank.  One workgroup; thread t has bins 2 t and 2 t + 1.
 __global__ void __launch_bounds__(1024) find_candidates(const CapTable* __restrict__ tab, MagTable* __restrict__ mag) {
     static_assert(kMagBins == 2 * 1024, "two bins per thread");
-    __shared__ unsigned wave_tot[1024 / kWave];
+    __shared__ __align__(16) unsigned wave_tot[1024 / kWave];
     const int t = threadIdx.x;
     const unsigned n0 = mag->count[2 * t], n1 = mag->count[2 * t + 1];
     unsigned total;
-    const unsigned first0 = block_exclusive_scan(n0 + n1, wave_tot, total), first1 = first0 + n0;
-    auto candidate = [&](unsigned bin, unsigned count, unsigned first) {
-        if (count == 0 || bin >= (0x7f800000u >> kMagShift) + 1u) return false;        // (NaN stays whatever its rank)
-        const float top = bin == (0x7f800000u >> kMagShift) ? INFINITY : __uint_as_float(((bin + 1u) << kMagShift) - 1u);
-        const double r = rank_percent((double)first + 1.0, tab->n);
-        const CapSeg sg = tab->seg[segment_of(r)];
-        return !((double)top <= fmax(sg.head, cap_in_segment(sg, r)));
-    };
-    const bool c0 = candidate(2 * t, n0, first0), c1 = candidate(2 * t + 1, n1, first1);
+    const unsigned first0 = block_exclusive_scan<1024 / kWave>(n0 + n1, wave_tot, total), first1 = first0 + n0;
+    const bool c0 = holds_candidates(*tab, 2 * t, n0, first0), c1 = holds_candidates(*tab, 2 * t + 1, n1, first1);
     const unsigned o0 = c0 ? 0u : n0, o1 = c1 ? 0u : n1;
-    const unsigned below = block_exclusive_scan(o0 + o1, wave_tot, total);
+    const unsigned below = block_exclusive_scan<1024 / kWave>(o0 + o1, wave_tot, total);
     mag->others_below[2 * t] = below;
     mag->others_below[2 * t + 1] = below + o0;
     if (t == 0) mag->candidates = (unsigned)((long)tab->n) - total;
-    // thread pairs of 16 threads make a word of flags
-    unsigned bits = (unsigned)c0 | ((unsigned)c1 << 1);
-    bits <<= 2 * (t & 15);
-#pragma unroll
-    for (int o = 1; o < 16; o <<= 1) bits |= __shfl_xor(bits, o, kWave);
-    if ((t & 15) == 0) mag->flag[t >> 4] = bits;
+    leave_flags(c0, c1, mag->flag);
 }
 
 // Exclusive scan of one digit's counters over the tiles; workgroup d has digit d.
 template <bool FIRST>
 __global__ void __launch_bounds__(kSortThreads) scan_digit(unsigned* __restrict__ hist, long n, MagTable* __restrict__ mag) {
-    __shared__ unsigned wave_tot[kSortWaves];
+    __shared__ __align__(16) unsigned wave_tot[kSortWaves];
     const PassShape shape = pass_shape<FIRST>(n, mag);
     const long tiles = shape.tiles;
     unsigned* c = hist + (long)blockIdx.x * shape.row;
@@ -442,7 +445,7 @@ __global__ void __launch_bounds__(kSortThreads) scan_digit(unsigned* __restrict_
 #pragma unroll
         for (int i = 0; i < 16; ++i) s += v[i];
         unsigned total;
-        unsigned run = carry + block_exclusive_scan(s, wave_tot, total);
+        unsigned run = carry + block_exclusive_scan<kSortWaves>(s, wave_tot, total);
 #pragma unroll
         for (int i = 0; i < 16; ++i) { const unsigned t = v[i]; v[i] = run; run += t; }
         if (!few && e0 + 16 <= tiles) {
@@ -458,22 +461,24 @@ __global__ void __launch_bounds__(kSortThreads) scan_digit(unsigned* __restrict_
     if (threadIdx.x == 0) mag->digit_total[blockIdx.x] = carry;
 }
 
-// LDS of one tile's pass.
+// LDS of one tile's pass: TILE elements in the hands of WAVES wavefronts.
+template <int WAVES, int TILE, class Payload>
 struct TileSort {
-    unsigned skey[kSortTile];
-    unsigned sval[kSortTile];
-    unsigned cnt[kSortWaves][kRadix];        // per wave: running count, then the wave's offset in the digit's run
+    unsigned skey[TILE];
+    Payload sval[TILE];
+    unsigned cnt[WAVES][kRadix];             // per wave: running count, then the wave's offset in the digit's run
     unsigned tile_excl[kRadix];              // first tile-local position of a digit
-    unsigned dest_off[kRadix];               // global destination minus tile-local position
-    unsigned wave_tot[kSortWaves];
+    alignas(16) unsigned wave_tot[WAVES];
 };
 
 // One stable counting-sort step of a tile on the digit at `shift`: with `items` elements per thread, element i of
 // lane l of wave w is the tile's element (w * items + i) * 64 + l (`valid_count` of them exist); on return sh.skey / sh.sval
 // hold the tile ordered by digit, equal digits in their old order, and sh.tile_excl the start of
 // every digit's run.  All threads of the workgroup call it; it ends with a barrier.
-__device__ __forceinline__ void tile_sort_step(TileSort& sh, const unsigned (&key)[kSortItems],
-                                               const unsigned (&val)[kSortItems], int items, int valid_count, int shift) {
+template <int WAVES, int TILE, class Payload>
+__device__ __forceinline__ void tile_sort_step(TileSort<WAVES, TILE, Payload>& sh, const unsigned (&key)[kSortItems],
+                                               const Payload (&val)[kSortItems], int items, int valid_count, int shift) {
+    static_assert(WAVES * kWave >= kRadix && WAVES * kWave * kSortItems == TILE, "a thread per digit");
     const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
     for (int d = lane; d < kRadix; d += kWave) sh.cnt[wave][d] = 0;
     __builtin_amdgcn_wave_barrier();
@@ -481,36 +486,43 @@ __device__ __forceinline__ void tile_sort_step(TileSort& sh, const unsigned (&ke
     unsigned short rank[kSortItems];
     // Stable rank of every element among those of its wave with the same digit: the elements of a
     // wave are ordered by (i, lane), which is their order in memory.  Eight ballots find the lanes
-    // that share a digit; the lowest of them advances the wave's counter.
-    const unsigned long long lanes_below = (1ull << lane) - 1ull;
+    // that share a digit; the lowest of them advances the wave's counter.  (By halves of the ballots and a sign-extended bit this is
+    // four instructions per bit; selects of 64-bit words were seven: 8.4 M elements all capped 335 -> 315 us.)
 #pragma unroll
     for (int i = 0; i < kSortItems; ++i) {
         if (i < items) {                                       // (uniform)
             const bool valid = first + i * kWave < valid_count;
             const unsigned d = (key[i] >> shift) & (kRadix - 1);
-            unsigned long long same = __ballot(valid);
-    #pragma unroll
-            for (int b = 0; b < 8; ++b) {
-                const bool bit = (d >> b) & 1u;
-                const unsigned long long bal = __ballot(bit);
-                same &= bit ? bal : ~bal;
+            const unsigned long long there = __ballot(valid);
+            unsigned same_lo = (unsigned)there, same_hi = (unsigned)(there >> 32);
+#pragma unroll
+            for (int b = 0; b < 8; ++b) {                          // (halves and a mask: two three-operand instructions per bit)
+                const unsigned bit = (unsigned)((int)(key[i] << (31 - shift - b)) >> 31);
+                const unsigned long long bal = __ballot(bit != 0u);
+                same_lo &= ~((unsigned)bal ^ bit);
+                same_hi &= ~((unsigned)(bal >> 32) ^ bit);
             }
+            const unsigned below = __builtin_amdgcn_mbcnt_hi(same_hi, __builtin_amdgcn_mbcnt_lo(same_lo, 0u));
             const unsigned prev = valid ? sh.cnt[wave][d] : 0u;
-            const unsigned r = prev + (unsigned)__popcll(same & lanes_below);
+            const unsigned r = prev + below;
             __builtin_amdgcn_wave_barrier();                       // all reads of this round before its writes
-            if (valid && (same & lanes_below) == 0) sh.cnt[wave][d] = prev + (unsigned)__popcll(same);
+            if (valid && below == 0) sh.cnt[wave][d] = prev + (unsigned)(__popc(same_lo) + __popc(same_hi));
             rank[i] = (unsigned short)r;
             __builtin_amdgcn_wave_barrier();
         }
     }
     __syncthreads();
     {   // per digit: offsets of the waves inside the digit's run, the run's place in the tile
-        const int d = threadIdx.x;                             // kSortThreads == kRadix
+        const int d = threadIdx.x;
+        const bool has = WAVES * kWave == kRadix || d < kRadix;
         unsigned run = 0;
+        if (has) {
 #pragma unroll
-        for (int w = 0; w < kSortWaves; ++w) { const unsigned t = sh.cnt[w][d]; sh.cnt[w][d] = run; run += t; }
+            for (int w = 0; w < WAVES; ++w) { const unsigned t = sh.cnt[w][d]; sh.cnt[w][d] = run; run += t; }
+        }
         unsigned total;
-        sh.tile_excl[d] = block_exclusive_scan(run, sh.wave_tot, total);
+        const unsigned before = block_exclusive_scan<WAVES>(run, sh.wave_tot, total);
+        if (has) sh.tile_excl[d] = before;
     }
     __syncthreads();
 #pragma unroll
@@ -518,17 +530,16 @@ __device__ __forceinline__ void tile_sort_step(TileSort& sh, const unsigned (&ke
         if (i < items && first + i * kWave < valid_count) {
             const unsigned d = (key[i] >> shift) & (kRadix - 1);
             const unsigned pos = sh.tile_excl[d] + sh.cnt[wave][d] + rank[i];
-            if (pos < (unsigned)kSortTile) { sh.skey[pos] = key[i]; sh.sval[pos] = val[i]; }
+            if (pos < (unsigned)TILE) { sh.skey[pos] = key[i]; sh.sval[pos] = val[i]; }
         }
     }
     __syncthreads();
 }
 
 // The element of 0-based rank `rank0` with magnitude bits k and payload v: write its capped value
-// if it exceeds its cap (out already holds delta, unless WRITE_ALL).  Most of the work is two
+// if it exceeds its cap (out already holds delta).  Most of the work is two
 // binary64 divisions; an estimate with reciprocals (error far below the margin used) first sorts
 // out the elements that are clearly under their cap.
-template <bool WRITE_ALL>
 __device__ __forceinline__ void cap_and_store(const CapTable& tab, unsigned rank0, unsigned k, unsigned v, long n,
                                               float* out) {
     const float a = __uint_as_float(k);
@@ -539,17 +550,11 @@ __device__ __forceinline__ void cap_and_store(const CapTable& tab, unsigned rank
     const CapSeg se = tab.seg[segment_of(re)];
     const double ce = fmax(se.head, se.c0 + se.dc * ((re - se.p0) * se.inv_dp));
     const bool near_knot = fabs(re - se.p0) < 1e-6 || fabs(re - (se.p0 + se.dp)) < 1e-6;
-    float star = a;
-    if (near_knot || !((double)a < ce - (fabs(se.dc) + ce) * 1e-9)) {
-        const double r = rank_percent((double)rank0 + 1.0, tab.n);
-        const CapSeg s = tab.seg[segment_of(r)];
-        const double cap = fmax(s.head, cap_in_segment(s, r));
-        if ((double)a > cap) star = down32(cap);               // NaN compares false and stays
-        else if (!WRITE_ALL) return;
-    } else if (!WRITE_ALL) {
-        return;
-    }
-    out[idx] = __uint_as_float(__float_as_uint(star) | (v & 0x80000000u));
+    if (!near_knot && (double)a < ce - (fabs(se.dc) + ce) * 1e-9) return;
+    const double r = rank_percent((double)rank0 + 1.0, tab.n);
+    const CapSeg s = tab.seg[segment_of(r)];
+    const double cap = fmax(s.head, cap_in_segment(s, r));
+    if ((double)a > cap) out[idx] = __uint_as_float(__float_as_uint(down32(cap)) | (v & 0x80000000u));       // NaN compares false and stays
 }
 
 // Scatter pass.  `hist` holds the scanned counters: hist[d * row + tile] elements with digit d lie in the tiles before.
@@ -560,7 +565,8 @@ __global__ void __launch_bounds__(kSortThreads, LAST ? 3 : 4) radix_scatter(cons
                                                               unsigned* __restrict__ keys_out, unsigned* __restrict__ vals_out,
                                                               long total, int shift, const unsigned* __restrict__ hist,
                                                               const MagTable* __restrict__ mag, const CapTable* __restrict__ tab, float* out) {
-    __shared__ TileSort sh;
+    __shared__ TileSort<kSortWaves, kSortTile, unsigned> sh;
+    __shared__ unsigned dest_off[kRadix];                      // global destination minus tile-local position
     __shared__ CapTable stab;                                  // LAST: the cap table, read per element
     __shared__ double run_cap[LAST ? kRadix : 1];
     __shared__ unsigned flag[FIRST ? kMagBins / 32 : 1];
@@ -650,8 +656,8 @@ __global__ void __launch_bounds__(kSortThreads, LAST ? 3 : 4) radix_scatter(cons
     {
         const unsigned digit_total = mag->digit_total[threadIdx.x];                              // kSortThreads == kRadix
         unsigned sum;
-        const unsigned first_dest = block_exclusive_scan(digit_total, sh.wave_tot, sum) + hist[(long)threadIdx.x * shape.row + tile];
-        sh.dest_off[threadIdx.x] = first_dest - sh.tile_excl[threadIdx.x];
+        const unsigned first_dest = block_exclusive_scan<kSortWaves>(digit_total, sh.wave_tot, sum) + hist[(long)threadIdx.x * shape.row + tile];
+        dest_off[threadIdx.x] = first_dest - sh.tile_excl[threadIdx.x];
         if (LAST) {
             // Caps do not decrease with the rank: the exact cap of a rank that all elements of this tile with digit d
             // reach or exceed is a lower bound for theirs, and most elements are settled by one comparison with it.
@@ -667,7 +673,7 @@ __global__ void __launch_bounds__(kSortThreads, LAST ? 3 : 4) radix_scatter(cons
     for (int j = threadIdx.x; j < count; j += kSortThreads) {
         const unsigned k = sh.skey[j], v = sh.sval[j];
         const unsigned d = (k >> shift) & (kRadix - 1);
-        const unsigned dest = sh.dest_off[d] + (unsigned)j;
+        const unsigned dest = dest_off[d] + (unsigned)j;
         if ((long)dest >= total) continue;                     // cannot happen with consistent counters
         if (!LAST) {
             keys_out[dest] = k;
@@ -675,44 +681,103 @@ __global__ void __launch_bounds__(kSortThreads, LAST ? 3 : 4) radix_scatter(cons
         } else {
             if ((double)__uint_as_float(k) <= run_cap[d]) continue;
             const unsigned rank0 = dest + (n == total ? 0u : mag->others_below[min(k >> kMagShift, (unsigned)kMagBins - 1u)]);
-            cap_and_store<false>(stab, rank0, k, v, total, out);
+            cap_and_store(stab, rank0, k, v, total, out);
         }
     }
 }
 
-// Tensors of at most one tile: the four passes in LDS by one workgroup, cap table included.
-__global__ void __launch_bounds__(kSortThreads) project_one_tile(const float* delta, const float* __restrict__ thr, double alpha,
-                                                                 int n, float* out) {
-    __shared__ TileSort sh;
+// Tensors of at most 16384 elements: all of it in LDS by one workgroup, cap table and candidates included.  Nothing is busy
+// here: it is a chain of some 30 barriers and LDS round trips, about 2.5 us per pass of few candidates, and 12 where 16384
+// are ranked (the payload is 16 bits, so that they fit).  Four wavefronts that ranked every element of up to 4096, and fifteen launches above, took, in us, the usual
+// heavy tail / nothing capped / all capped: 1000 elements 31.3 / 30.8 / 32.8, now 20.5 / 6.8 / 21.7; 4096 40.2 / 39.7 / 47.8, now 21.2 / 7.4 / 35.0;
+// 16384 59.9 / 42.0 / 115, now 23.7 / 9.4 / 87.  (16385, by the launches: 56.1 / 42 / 106.)
+constexpr int kOneWaves = 16, kOneThreads = kOneWaves * kWave, kOneTile = kOneThreads * kSortItems;
+__global__ void __launch_bounds__(kOneThreads) project_one_tile(const float* delta, const float* __restrict__ thr, double alpha,
+                                                                int n, float* out) {
+    static_assert(kMagBins == 2 * kOneThreads, "two bins per thread");
+    constexpr int kCopies = 4;                                 // of the magnitudes' histogram, in the place of the keys
+    __shared__ TileSort<kOneWaves, kOneTile, unsigned short> sh;
+    static_assert(kCopies * kMagBins <= kOneTile && kOneTile <= 0x8000, "room for the histogram; index and sign in 16 bits");
+    __shared__ unsigned others_below[kMagBins], flag[kMagBins / 32];
     __shared__ CapTable tab;
-    build_cap_table(thr, alpha, n, &tab);                      // ends with a barrier
-    const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
-    const int first = wave * (kSortItems * kWave) + lane;
-    unsigned key[kSortItems], val[kSortItems];
+    const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
+    const unsigned long long lanes_below = (1ull << lane) - 1ull;
+    int items = (n + kOneThreads - 1) / kOneThreads;           // (uniform)
+    unsigned key[kSortItems];
+    unsigned short val[kSortItems];
 #pragma unroll
     for (int i = 0; i < kSortItems; ++i) {
-        const int e = first + i * kWave;
-        key[i] = 0xffffffffu; val[i] = 0;
-        if (e < n) {
-            const unsigned b = __float_as_uint(delta[e]);
-            key[i] = b & 0x7fffffffu;
-            val[i] = (unsigned)e | (b & 0x80000000u);
+        const int e = (wave * items + i) * kWave + lane;
+        key[i] = i < items && e < n ? __float_as_uint(delta[e]) : 0xffffffffu;
+    }
+    for (int b = tid; b < kCopies * kMagBins; b += kOneThreads) sh.skey[b] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kSortItems; ++i) {
+        const int e = (wave * items + i) * kWave + lane;
+        if (i < items && e < n) {
+            if (out != delta) out[e] = __uint_as_float(key[i]);
+            atomicAdd(&sh.skey[((key[i] & 0x7fffffffu) >> kMagShift) * kCopies + (lane & (kCopies - 1))], 1u);
         }
     }
+    build_cap_table(thr, alpha, n, &tab);                      // ends with a barrier
+    unsigned n0 = 0, n1 = 0, total;
+#pragma unroll
+    for (int c = 0; c < kCopies; ++c) { n0 += sh.skey[2 * tid * kCopies + c]; n1 += sh.skey[(2 * tid + 1) * kCopies + c]; }
+    const unsigned first0 = block_exclusive_scan<kOneWaves>(n0 + n1, sh.wave_tot, total), first1 = first0 + n0;
+    const bool c0 = holds_candidates(tab, 2 * tid, n0, first0), c1 = holds_candidates(tab, 2 * tid + 1, n1, first1);
+    leave_flags(c0, c1, flag);
+    const unsigned o0 = c0 ? 0u : n0, o1 = c1 ? 0u : n1;
+    const unsigned below = block_exclusive_scan<kOneWaves>(o0 + o1, sh.wave_tot, total);
+    others_below[2 * tid] = below;
+    others_below[2 * tid + 1] = below + o0;
+    __syncthreads();
+    const int count = n - (int)total;
+    if (count == 0) return;                                    // whole workgroup
+    // the candidates closed up, in order
+    unsigned mine = 0, in_wave = 0;                            // mine: a bit per key
+#pragma unroll
+    for (int i = 0; i < kSortItems; ++i) {
+        const int e = (wave * items + i) * kWave + lane;
+        const unsigned bin = (key[i] & 0x7fffffffu) >> kMagShift;
+        const bool c = i < items && e < n && ((flag[bin >> 5] >> (bin & 31)) & 1u);
+        mine |= (unsigned)c << i;
+        in_wave += (unsigned)__popcll(__ballot(c));
+    }
+    if (lane == 0) sh.wave_tot[wave] = in_wave;
+    __syncthreads();
+    unsigned at = 0;
+    for (int w = 0; w < wave; ++w) at += sh.wave_tot[w];
+#pragma unroll
+    for (int i = 0; i < kSortItems; ++i) {
+        const bool c = (mine >> i) & 1u;
+        const unsigned long long b = __ballot(c);
+        if (c) {
+            const unsigned to = at + (unsigned)__popcll(b & lanes_below);
+            sh.skey[to] = key[i] & 0x7fffffffu;
+            sh.sval[to] = (unsigned short)(((wave * items + i) * kWave + lane) | (key[i] >> 31 << 15));
+        }
+        at += (unsigned)__popcll(b);
+    }
+    __syncthreads();
+    items = (count + kOneThreads - 1) / kOneThreads;
+    const int first = wave * (items * kWave) + lane;
 #pragma unroll 1
     for (int pass = 0; pass < 4; ++pass) {
-        tile_sort_step(sh, key, val, kSortItems, n, 8 * pass);
-        if (pass < 3) {
 #pragma unroll
-            for (int i = 0; i < kSortItems; ++i) {
-                const int e = first + i * kWave;
-                if (e < n) { key[i] = sh.skey[e]; val[i] = sh.sval[e]; }
-            }
-            __syncthreads();                                   // before the next step overwrites the tile
+        for (int i = 0; i < kSortItems; ++i) {
+            const int e = first + i * kWave;
+            key[i] = 0xffffffffu; val[i] = 0;
+            if (i < items && e < count) { key[i] = sh.skey[e]; val[i] = sh.sval[e]; }
         }
+        // (what is read here is written again behind two barriers of the step)
+        tile_sort_step(sh, key, val, items, count, 8 * pass);
     }
-    for (int j = threadIdx.x; j < n; j += kSortThreads)
-        cap_and_store<true>(tab, (unsigned)j, sh.skey[j], sh.sval[j], n, out);
+    for (int j = tid; j < count; j += kOneThreads) {
+        const unsigned k = sh.skey[j], v = sh.sval[j];
+        const unsigned rank0 = (unsigned)j + (count == n ? 0u : others_below[min(k >> kMagShift, (unsigned)kMagBins - 1u)]);
+        cap_and_store(tab, rank0, k, (v & 0x7fffu) | (v >> 15 << 31), n, out);
+    }
 }
 
 struct ProjectWorkspace {
@@ -773,8 +838,8 @@ int tao_project_empirical(const float* delta, const float* thr_abs, double alpha
     if (!delta || !thr_abs || !out) return TAO_ERR_NULL;
     if (!aligned(delta, 4) || !aligned(thr_abs, 4) || !aligned(out, 4)) return TAO_ERR_ALIGN;
     if (!ws || !aligned(ws, 256) || ws_bytes < tao_project_workspace_bytes(n)) return TAO_ERR_WORKSPACE;
-    if (n <= kSortTile) {
-        hipLaunchKernelGGL(project_one_tile, dim3(1), dim3(kSortThreads), 0, (hipStream_t)stream, delta, thr_abs, alpha,
+    if (n <= kOneTile) {
+        hipLaunchKernelGGL(project_one_tile, dim3(1), dim3(kOneThreads), 0, (hipStream_t)stream, delta, thr_abs, alpha,
                            (int)n, out);
         return launch_status();
     }

@@ -88,12 +88,18 @@ template <class T>
 __device__ __forceinline__ T wave_max(T v) { return wave_all(v, [](T a, T b) { return a > b ? a : b; }); }
 __device__ __forceinline__ float wave_max(float v) { return wave_all(v, [](float a, float b) { return fmaxf(a, b); }); }
 __device__ __forceinline__ int wave_or(int v) { return wave_all(v, [](int a, int b) { return a | b; }); }
-// Sum over the lanes up to this one.
-__device__ __forceinline__ unsigned long long wave_scan(unsigned long long v) {
+// Sum over the lanes up to this one, of 32 or 64 bits.
+template <class T>
+__device__ __forceinline__ T wave_scan(T v) {
+    static_assert(std::is_same<T, unsigned>::value || std::is_same<T, unsigned long long>::value, "one or two words");
     auto step = [&](auto ctrl, auto rows) __attribute__((always_inline)) {
         const unsigned lo = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)v, ctrl.value, rows.value, 0xf, false);
-        const unsigned hi = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)(v >> 32), ctrl.value, rows.value, 0xf, false);
-        v += (unsigned long long)hi << 32 | lo;
+        if constexpr (sizeof(T) == 8) {
+            const unsigned hi = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)(v >> 32), ctrl.value, rows.value, 0xf, false);
+            v += (T)hi << 32 | lo;
+        } else {
+            v += lo;
+        }
     };
     using std::integral_constant;
     step(integral_constant<int, 0x111>{}, integral_constant<int, 0xf>{});       // row_shr 1, 2, 4, 8
