@@ -189,30 +189,34 @@ def lib():
 
 
 _torch_module = None
+# what every call asks torch for, looked up once with the module
+_Tensor = _float32 = _raw_stream = _current_device = None
 
 
 def _torch():
     # (asked once: the answer costs more than the launch of a small kernel)
-    global _torch_module
+    global _torch_module, _Tensor, _float32, _raw_stream, _current_device
     if _torch_module is None:
         import torch
         if not torch.cuda.is_available():
             raise RuntimeError("paper_2510_16028_amd needs a GPU: no CPU fallback exists")
+        _Tensor, _float32 = torch.Tensor, torch.float32
+        _raw_stream, _current_device = torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice
         _torch_module = torch
     return _torch_module
 
 
 def _stream():
     # (the raw handle of the current device's current stream: a Stream object on every call takes 2.8 us)
-    c = _torch()._C
-    return c._cuda_getCurrentRawStream(c._cuda_getDevice())
+    _torch_module or _torch()
+    return _raw_stream(_current_device())
 
 
 def _dev(t, name):
-    torch = _torch()
+    _torch_module or _torch()
     if t is None:
         return None
-    if not (isinstance(t, torch.Tensor) and t.is_cuda and t.dtype == torch.float32):
+    if not (isinstance(t, _Tensor) and t.is_cuda and t.dtype is _float32):
         raise TypeError("%s must be a float32 CUDA tensor" % name)
     return t
 
@@ -234,18 +238,20 @@ def _check(status, where):
 def _rows_view(t, name):
     """(rows, cols, ld) of a tensor whose last dimension is contiguous and whose
     leading dimensions collapse to one uniform row stride."""
-    if t.dim() == 0:
+    shape = t.shape
+    dims = len(shape)
+    if dims == 0:
         raise ValueError("%s: need at least one dimension" % name)
-    cols = t.shape[-1]
-    if t.dim() == 1:
+    cols = shape[-1]
+    if dims == 1:
         return 1, cols, cols
-    if cols > 1 and t.stride(-1) != 1:
+    stride = t.stride()
+    if cols > 1 and stride[-1] != 1:
         raise ValueError("%s: last dimension must be contiguous" % name)
-    t2 = t if t.is_contiguous() else None
-    if t2 is not None:
+    if t.is_contiguous():
         return t.numel() // max(cols, 1), cols, cols
-    if t.dim() == 2:
-        return t.shape[0], cols, t.stride(0)
+    if dims == 2:
+        return shape[0], cols, stride[0]
     raise ValueError("%s: only 2-D tensors may have a padded row stride" % name)
 
 
@@ -297,7 +303,7 @@ def _linear_args(A, W, bias, trans_w, out):
 def tao_bound_linear(A, W, bias=None, trans_w=False, model=None, out=None):
     """tau[..., M, N] for A[..., M, K] and W[N, K] / [B, N, K] (trans_w: [K, N] / [B, K, N])."""
     A, W, bias, out, dims = _linear_args(A, W, bias, trans_w, out)
-    rc = lib().tao_bound_linear(_ptr(A), _ptr(W), _ptr(bias), _ptr(out), *dims, _mref(model), _stream())
+    rc = lib().tao_bound_linear(A.data_ptr(), W.data_ptr(), _ptr(bias), out.data_ptr(), *dims, _mref(model), _stream())
     _check(rc, "tao_bound_linear")
     return out
 
@@ -327,8 +333,8 @@ def tao_bound_linear_split(A, W, bias=None, trans_w=False, model=None, out=None,
     M, N, K, batch, sW = dims[0], dims[1], dims[2], dims[7], dims[9]
     if ws is None:
         ws = _scratch(A.device, tao_linear_split_workspace_bytes(M, N, K, batch, sW == 0 or batch == 1))
-    rc = lib().tao_bound_linear_split(_ptr(A), _ptr(W), _ptr(bias), _ptr(out), *dims, _mref(model),
-                                      _ptr(ws), ws.numel(), _stream())
+    rc = lib().tao_bound_linear_split(A.data_ptr(), W.data_ptr(), _ptr(bias), out.data_ptr(), *dims, _mref(model),
+                                      ws.data_ptr(), ws.numel(), _stream())
     _check(rc, "tao_bound_linear_split")
     return out
 
@@ -363,9 +369,9 @@ def tao_bound_check_linear(A, W, bias, y_ref, claimed, trans_w=False, alpha=1.0,
         out = new_profile_buffer(A.device)
     if ws is None:
         ws = _scratch(A.device, tao_bound_check_linear_workspace_bytes(M, N, K, batch, sW == 0 or batch == 1))
-    rc = lib().tao_bound_check_linear(_ptr(A), _ptr(W), _ptr(bias), _ptr(y_ref), _ptr(claimed), _ptr(tau_out),
-                                      *dims, float(alpha), float(eps_rel), _mref(model), _ptr(out),
-                                      _ptr(ws), ws.numel(), _stream())
+    rc = lib().tao_bound_check_linear(A.data_ptr(), W.data_ptr(), _ptr(bias), y_ref.data_ptr(), claimed.data_ptr(), _ptr(tau_out),
+                                      *dims, float(alpha), float(eps_rel), _mref(model), out.data_ptr(),
+                                      ws.data_ptr(), ws.numel(), _stream())
     _check(rc, "tao_bound_check_linear")
     return read_profile(out) if readback else out
 
@@ -388,7 +394,7 @@ def tao_split_operand(X, trans=False, out=None):
     need = tao_split_image_bytes(rows, K, batch)
     if out is None:
         out = torch.empty(max(need, 256), dtype=torch.uint8, device=X.device)
-    rc = lib().tao_split_operand(_ptr(X), rows, K, ld, int(bool(trans)), batch, stride, _ptr(out), out.numel(), _stream())
+    rc = lib().tao_split_operand(X.data_ptr(), rows, K, ld, int(bool(trans)), batch, stride, out.data_ptr(), out.numel(), _stream())
     _check(rc, "tao_split_operand")
     return out
 
@@ -404,8 +410,8 @@ def tao_bound_linear_images(A_image, W_image, M, N, K, bias=None, batch=1, share
         raise ValueError("out must be contiguous with %d elements" % (batch * M * N))
     if ws is None:
         ws = _scratch(A_image.device, lib().tao_linear_images_workspace_bytes(M, N, K, batch))
-    rc = lib().tao_bound_linear_images(_ptr(A_image), _ptr(W_image), _ptr(bias), _ptr(out), M, N, K, N, batch, M * N,
-                                       int(bool(shared_w)), _mref(model), _ptr(ws), ws.numel(), _stream())
+    rc = lib().tao_bound_linear_images(_ptr(A_image), _ptr(W_image), _ptr(bias), out.data_ptr(), M, N, K, N, batch, M * N,
+                                       int(bool(shared_w)), _mref(model), ws.data_ptr(), ws.numel(), _stream())
     _check(rc, "tao_bound_linear_images")
     return out
 
@@ -423,7 +429,7 @@ def tao_bound_check_linear_images(A_image, W_image, M, N, K, y_ref, claimed, bia
         ws = _scratch(y_ref.device, lib().tao_check_linear_images_workspace_bytes(M, N, K, batch))
     rc = lib().tao_bound_check_linear_images(_ptr(A_image), _ptr(W_image), _ptr(bias), _ptr(y_ref), _ptr(claimed), _ptr(tau_out),
                                              M, N, K, N, batch, M * N, int(bool(shared_w)), float(alpha), float(eps_rel),
-                                             _mref(model), _ptr(out), _ptr(ws), ws.numel(), _stream())
+                                             _mref(model), out.data_ptr(), ws.data_ptr(), ws.numel(), _stream())
     _check(rc, "tao_bound_check_linear_images")
     return read_profile(out) if readback else out
 
@@ -461,7 +467,7 @@ def tao_bound_conv2d(x, w, bias=None, stride=1, padding=0, dilation=1, model=Non
         out = torch.empty(shape, dtype=torch.float32, device=x.device)
     elif tuple(out.shape) != shape or not out.is_contiguous() or out.dtype != torch.float32:
         raise ValueError("out must be a contiguous float32 tensor of shape %s" % (shape,))
-    rc = lib().tao_bound_conv2d(_ptr(x), _ptr(w), _ptr(bias), _ptr(out), B, H, W, C, Cout, R, S,
+    rc = lib().tao_bound_conv2d(x.data_ptr(), w.data_ptr(), _ptr(bias), out.data_ptr(), B, H, W, C, Cout, R, S,
                                 sh, sw, ph, pw, dh, dw, _mref(model), _stream())
     _check(rc, "tao_bound_conv2d")
     return out
@@ -523,8 +529,8 @@ def tao_bound_check_conv2d(x, w, bias, y_ref, claimed, stride=1, padding=0, dila
         out = new_profile_buffer(x.device)
     if ws is None:
         ws = _scratch(x.device, lib().tao_conv2d_split_workspace_bytes(*geom, 1))
-    rc = lib().tao_bound_check_conv2d(_ptr(x), _ptr(w), _ptr(bias), _ptr(y_ref), _ptr(claimed), _ptr(tau_out), *geom,
-                                      float(alpha), float(eps_rel), _mref(model), _ptr(out), _ptr(ws), ws.numel(), _stream())
+    rc = lib().tao_bound_check_conv2d(x.data_ptr(), w.data_ptr(), _ptr(bias), _ptr(y_ref), _ptr(claimed), _ptr(tau_out), *geom,
+                                      float(alpha), float(eps_rel), _mref(model), out.data_ptr(), ws.data_ptr(), ws.numel(), _stream())
     _check(rc, "tao_bound_check_conv2d")
     return read_profile(out) if readback else out
 
@@ -569,7 +575,7 @@ def tao_bound_norm(kind, x, y_ref=None, gamma_or_scale=None, beta_or_shift=None,
             out = torch.empty_strided(x.shape, x.stride(), dtype=torch.float32, device=x.device)
         elif out.shape != x.shape or out.stride() != x.stride():
             raise ValueError("out must match x in shape and strides")
-    rc = lib().tao_bound_norm(int(kind), _ptr(x), _ptr(y_ref), _ptr(g), _ptr(b), float(eps), _ptr(out),
+    rc = lib().tao_bound_norm(int(kind), x.data_ptr(), _ptr(y_ref), _ptr(g), _ptr(b), float(eps), out.data_ptr(),
                               rows, cols, ld, _mref(model), _stream())
     _check(rc, "tao_bound_norm")
     return out
@@ -614,7 +620,7 @@ def tao_bound_act(kind, x, y_ref, x2=None, model=None, out=None):
         out = torch.empty_like(y_ref)
     elif out.shape != y_ref.shape or not out.is_contiguous():
         raise ValueError("out must be contiguous and shaped like y_ref")
-    rc = lib().tao_bound_act(int(kind), _ptr(x), _ptr(x2), _ptr(y_ref), _ptr(out), y_ref.numel(),
+    rc = lib().tao_bound_act(int(kind), _ptr(x), _ptr(x2), _ptr(y_ref), out.data_ptr(), y_ref.numel(),
                              _mref(model), _stream())
     _check(rc, "tao_bound_act")
     return out
@@ -687,8 +693,8 @@ def tao_check_and_profile(claimed, ref, tau, alpha=1.0, eps_rel=1e-12, out=None,
         out = new_profile_buffer(claimed.device)
     if ws is None:
         ws = _workspace(claimed.device, n)
-    rc = lib().tao_check_and_profile(_ptr(claimed), _ptr(ref), _ptr(tau), n, float(alpha),
-                                     float(eps_rel), _ptr(out), _ptr(ws), ws.numel(), _stream())
+    rc = lib().tao_check_and_profile(claimed.data_ptr(), ref.data_ptr(), tau.data_ptr(), n, float(alpha),
+                                     float(eps_rel), out.data_ptr(), ws.data_ptr(), ws.numel(), _stream())
     _check(rc, "tao_check_and_profile")
     return read_profile(out) if readback else out
 
@@ -719,16 +725,16 @@ def tao_bound_check_act(kind, x, y_ref, claimed, x2=None, alpha=1.0, eps_rel=1e-
                         ws=None, readback=True):
     """tao_bound_act checked against `claimed` in one pass, tau never stored."""
     x = _dev(x, "x"); x2 = _dev(x2, "x2"); y_ref = _dev(y_ref, "y_ref"); claimed = _dev(claimed, "claimed")
-    for t, nm in ((x, "x"), (x2, "x2"), (y_ref, "y_ref"), (claimed, "claimed")):
-        if t is not None and (not t.is_contiguous() or t.numel() != y_ref.numel()):
-            raise ValueError("%s must be contiguous and sized like y_ref" % nm)
     n = y_ref.numel()
+    for t, nm in ((x, "x"), (x2, "x2"), (y_ref, "y_ref"), (claimed, "claimed")):
+        if t is not None and (not t.is_contiguous() or t.numel() != n):
+            raise ValueError("%s must be contiguous and sized like y_ref" % nm)
     if out is None:
         out = new_profile_buffer(y_ref.device)
     if ws is None:
         ws = _workspace(y_ref.device, n)
-    rc = lib().tao_bound_check_act(int(kind), _ptr(x), _ptr(x2), _ptr(y_ref), _ptr(claimed), n, float(alpha),
-                                   float(eps_rel), _mref(model), _ptr(out), _ptr(ws), ws.numel(), _stream())
+    rc = lib().tao_bound_check_act(int(kind), _ptr(x), _ptr(x2), y_ref.data_ptr(), _ptr(claimed), n, float(alpha),
+                                   float(eps_rel), _mref(model), out.data_ptr(), ws.data_ptr(), ws.numel(), _stream())
     _check(rc, "tao_bound_check_act")
     return read_profile(out) if readback else out
 
@@ -737,8 +743,9 @@ def tao_bound_check_norm(kind, x, y_ref, claimed, g=None, b=None, eps=0.0, alpha
                          out=None, ws=None, readback=True):
     """tao_bound_norm (LayerNorm or RMSNorm) checked against `claimed` in one pass, tau never stored."""
     x = _dev(x, "x"); y_ref = _dev(y_ref, "y_ref"); claimed = _dev(claimed, "claimed"); g = _dev(g, "g"); b = _dev(b, "b")
+    shape, stride = x.shape, x.stride()
     for t, nm in ((y_ref, "y_ref"), (claimed, "claimed")):
-        if t.shape != x.shape or t.stride() != x.stride():
+        if t.shape != shape or t.stride() != stride:
             raise ValueError("%s must have the shape and strides of x" % nm)
     rows, cols, ld = _rows_view(x, "x")
     for t, nm in ((g, "g"), (b, "b")):
@@ -748,9 +755,9 @@ def tao_bound_check_norm(kind, x, y_ref, claimed, g=None, b=None, eps=0.0, alpha
         out = new_profile_buffer(x.device)
     if ws is None:
         ws = _workspace(x.device, rows * cols)
-    rc = lib().tao_bound_check_norm(int(kind), _ptr(x), _ptr(y_ref), _ptr(g), _ptr(b), float(eps), _ptr(claimed),
-                                    rows, cols, ld, float(alpha), float(eps_rel), _mref(model), _ptr(out),
-                                    _ptr(ws), ws.numel(), _stream())
+    rc = lib().tao_bound_check_norm(int(kind), x.data_ptr(), y_ref.data_ptr(), _ptr(g), _ptr(b), float(eps), claimed.data_ptr(),
+                                    rows, cols, ld, float(alpha), float(eps_rel), _mref(model), out.data_ptr(),
+                                    ws.data_ptr(), ws.numel(), _stream())
     _check(rc, "tao_bound_check_norm")
     return read_profile(out) if readback else out
 
