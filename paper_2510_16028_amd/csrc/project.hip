@@ -13,7 +13,7 @@
 // (8.4 M elements: none capped 257 -> 74 us, a heavy tail against calibrated thresholds 260 -> 104 us, all capped 343 -> 350 us;
 // 67 M: 1608 -> 325, 1621 -> 354, 2406 -> 2415 us.  Since the counting pass leaves each
 // tile its candidates closed up, and the first scatter reads those and not delta: none capped 74 -> 67 us, 34 M 168 -> 147, 67 M 325 -> 287;
-// where most is sorted, and no tile is closed up, 67 M and 134 M take 0.3 % longer.)  What bounds it now: two passes over delta and some fifteen launches.
+// where most is sorted, and no tile is closed up, 67 M and 134 M take 0.3 % longer.)  What bounds it now (8.4 M elements, a heavy tail 86 us): two passes over delta, 30 us, and the latencies of some fifteen launches.
 // The sort is a least-significant-digit radix sort of the 31 magnitude bits (a non-negative binary32 orders like
 // its bit pattern, NaN above infinity) in four 8-bit passes; the payload is the element's index
 // with its sign bit on top.  Per pass: count (digit histogram per tile), scan (of each digit's counters over
@@ -46,6 +46,10 @@ constexpr int kScanChunk = kSortThreads * 16;                 // counters per st
 constexpr int kMagBins = 2048;                                // bins of the leading 11 magnitude bits
 constexpr int kMagShift = 20;
 constexpr int kXcds = 8;
+// Up to which a scatter pass adds up the tiles' counters itself and the candidates' launch the workgroups' histograms: ten launches for fifteen
+// (a usual tail / all capped, us: 50000 elements 58.3 / 107 by fifteen launches, 43.8 / 95.5 so; 262144 64.6 / 111 and 48.9 / 108; at 128 tiles
+// 500000 elements 59.5 / 114 and 57.5 / 122).
+constexpr int kFewTiles = 64;
 constexpr int kCountCopies = 4;                               // histogram copies per wave in radix_count
 constexpr int kCountStride = kRadix + 4;                      // copy c of digit d in LDS bank (d + 4c) % 32
 
@@ -142,8 +146,11 @@ __global__ void __launch_bounds__(kWave) cap_table_kernel(const float* __restric
     build_cap_table(thr, alpha, n, tab);
 }
 
-// Histogram of the leading magnitude bits: 4 bytes per element read, one set of integer atomics per workgroup.
-__global__ void __launch_bounds__(1024) magnitude_bins(const float* __restrict__ delta, long n, int vec_ok, MagTable* __restrict__ mag) {
+// Histogram of the leading magnitude bits: 4 bytes per element read, one set of integer atomics per workgroup (PARTS: a histogram of
+// its own instead, which no launch has to clear beforehand).
+template <bool PARTS>
+__global__ void __launch_bounds__(1024) magnitude_bins(const float* __restrict__ delta, long n, int vec_ok, MagTable* __restrict__ mag,
+                                                       unsigned* __restrict__ parts) {
     constexpr int kCopies = 4;
     __shared__ unsigned cnt[kMagBins * kCopies];
     for (int i = threadIdx.x; i < kMagBins * kCopies; i += 1024) cnt[i] = 0;
@@ -153,19 +160,22 @@ __global__ void __launch_bounds__(1024) magnitude_bins(const float* __restrict__
     auto add = [&](unsigned v) __attribute__((always_inline)) { atomicAdd(&cnt[((v & 0x7fffffffu) >> kMagShift) * kCopies + copy], 1u); };
     const long nvec = vec_ok ? n >> 2 : 0, stride = (long)gridDim.x * 1024;
     long i = (long)blockIdx.x * 1024 + threadIdx.x;
-    for (; i + stride < nvec; i += 2 * stride) {
-        const uint4 a = reinterpret_cast<const uint4*>(src)[i], b = reinterpret_cast<const uint4*>(src)[i + stride];
-        add(a.x); add(a.y); add(a.z); add(a.w);
-        add(b.x); add(b.y); add(b.z); add(b.w);
+    for (; i + 3 * stride < nvec; i += 4 * stride) {           // (four loads under way: 8.4 M elements 10.8 us, two 11.5)
+        uint4 v[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) v[j] = reinterpret_cast<const uint4*>(src)[i + j * stride];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) { add(v[j].x); add(v[j].y); add(v[j].z); add(v[j].w); }
     }
-    if (i < nvec) { const uint4 a = reinterpret_cast<const uint4*>(src)[i]; add(a.x); add(a.y); add(a.z); add(a.w); }
+    for (; i < nvec; i += stride) { const uint4 a = reinterpret_cast<const uint4*>(src)[i]; add(a.x); add(a.y); add(a.z); add(a.w); }
     for (long e = (nvec << 2) + (long)blockIdx.x * 1024 + threadIdx.x; e < n; e += stride) add(src[e]);
     __syncthreads();
     for (int b = threadIdx.x; b < kMagBins; b += 1024) {
         unsigned t = 0;
 #pragma unroll
         for (int c = 0; c < kCopies; ++c) t += cnt[b * kCopies + c];
-        if (t) atomicAdd(&mag->count[b], t);
+        if (PARTS) parts[(size_t)blockIdx.x * kMagBins + b] = t;
+        else if (t) atomicAdd(&mag->count[b], t);
     }
 }
 
@@ -402,20 +412,35 @@ __device__ __forceinline__ void leave_flags(bool c0, bool c1, unsigned* flag) {
 }
 
 // First rank of every bin, the bins whose elements may exceed their caps, and the numbers that lead from a
-// candidate's place to its rank.  One workgroup; thread t has bins 2 t and 2 t + 1.
-__global__ void __launch_bounds__(1024) find_candidates(const CapTable* __restrict__ tab, MagTable* __restrict__ mag) {
+// candidate's place to its rank.  One workgroup; thread t has bins 2 t and 2 t + 1.  PARTS: the histogram is the sum of `nparts`
+// workgroups', and the cap table is built here.
+template <bool PARTS>
+__global__ void __launch_bounds__(1024) find_candidates(const float* __restrict__ thr, double alpha, long n, CapTable* __restrict__ tab,
+                                                        MagTable* __restrict__ mag, const unsigned* __restrict__ parts, int nparts) {
     static_assert(kMagBins == 2 * 1024, "two bins per thread");
+    __shared__ CapTable stab;
     __shared__ __align__(16) unsigned wave_tot[1024 / kWave];
     const int t = threadIdx.x;
-    const unsigned n0 = mag->count[2 * t], n1 = mag->count[2 * t + 1];
-    unsigned total;
+    unsigned n0 = 0, n1 = 0, total;
+    if (PARTS) {
+#pragma unroll 4
+        for (int k = 0; k < nparts; ++k) {
+            const uint2 c = reinterpret_cast<const uint2*>(parts + (size_t)k * kMagBins)[t];
+            n0 += c.x; n1 += c.y;
+        }
+        build_cap_table(thr, alpha, n, &stab);                 // ends with a barrier
+        if (t < (int)(sizeof(CapTable) / sizeof(double))) reinterpret_cast<double*>(tab)[t] = reinterpret_cast<const double*>(&stab)[t];
+    } else {
+        n0 = mag->count[2 * t]; n1 = mag->count[2 * t + 1];
+    }
+    const CapTable& caps = PARTS ? stab : *tab;
     const unsigned first0 = block_exclusive_scan<1024 / kWave>(n0 + n1, wave_tot, total), first1 = first0 + n0;
-    const bool c0 = holds_candidates(*tab, 2 * t, n0, first0), c1 = holds_candidates(*tab, 2 * t + 1, n1, first1);
+    const bool c0 = holds_candidates(caps, 2 * t, n0, first0), c1 = holds_candidates(caps, 2 * t + 1, n1, first1);
     const unsigned o0 = c0 ? 0u : n0, o1 = c1 ? 0u : n1;
     const unsigned below = block_exclusive_scan<1024 / kWave>(o0 + o1, wave_tot, total);
     mag->others_below[2 * t] = below;
     mag->others_below[2 * t + 1] = below + o0;
-    if (t == 0) mag->candidates = (unsigned)((long)tab->n) - total;
+    if (t == 0) mag->candidates = (unsigned)n - total;
     leave_flags(c0, c1, mag->flag);
 }
 
@@ -558,8 +583,10 @@ __device__ __forceinline__ void cap_and_store(const CapTable& tab, unsigned rank
 }
 
 // Scatter pass.  `hist` holds the scanned counters: hist[d * row + tile] elements with digit d lie in the tiles before.
+// FEW: it holds the counters themselves, of at most kFewTiles tiles, and every workgroup adds up a digit's row per thread; a launch
+// takes the host 3.6 us, and tensors of that size wait for it.
 // The first pass sorts the tile's candidates: as the counting pass left them, or closed up here, in LDS and in order.
-template <bool FIRST, bool LAST>
+template <bool FIRST, bool LAST, bool FEW>
 __global__ void __launch_bounds__(kSortThreads, LAST ? 3 : 4) radix_scatter(const float* delta,
                                                               const unsigned* __restrict__ keys_in, const unsigned* __restrict__ vals_in,
                                                               unsigned* __restrict__ keys_out, unsigned* __restrict__ vals_out,
@@ -581,6 +608,23 @@ __global__ void __launch_bounds__(kSortThreads, LAST ? 3 : 4) radix_scatter(cons
         // visible after the barriers of the sort step
     }
     const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
+    unsigned digit_total = 0, digit_before = 0;                // kSortThreads == kRadix
+    if (FEW) {
+        const uint4* const row = reinterpret_cast<const uint4*>(hist + (long)threadIdx.x * shape.row);
+#pragma unroll 4
+        for (int q = 0; q < (int)(shape.row / 4); ++q) {
+            const uint4 c = row[q];
+            const unsigned v[4] = {c.x, c.y, c.z, c.w};
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {                      // (the row's last counters, past the tiles, hold anything)
+                digit_total += 4 * q + j < (int)tiles ? v[j] : 0u;
+                digit_before += 4 * q + j < (int)tile ? v[j] : 0u;
+            }
+        }
+    } else {
+        digit_total = mag->digit_total[threadIdx.x];
+        digit_before = hist[(long)threadIdx.x * shape.row + tile];
+    }
     int items = FIRST ? kSortItems : shape.items;
     const long tile_base = tile * (items * kSortThreads);
     const long base = tile_base + (long)wave * (items * kWave) + lane;
@@ -654,9 +698,8 @@ __global__ void __launch_bounds__(kSortThreads, LAST ? 3 : 4) radix_scatter(cons
     }
     tile_sort_step(sh, key, val, items, count, shift);
     {
-        const unsigned digit_total = mag->digit_total[threadIdx.x];                              // kSortThreads == kRadix
         unsigned sum;
-        const unsigned first_dest = block_exclusive_scan<kSortWaves>(digit_total, sh.wave_tot, sum) + hist[(long)threadIdx.x * shape.row + tile];
+        const unsigned first_dest = block_exclusive_scan<kSortWaves>(digit_total, sh.wave_tot, sum) + digit_before;
         dest_off[threadIdx.x] = first_dest - sh.tile_excl[threadIdx.x];
         if (LAST) {
             // Caps do not decrease with the rank: the exact cap of a rank that all elements of this tile with digit d
@@ -690,7 +733,7 @@ __global__ void __launch_bounds__(kSortThreads, LAST ? 3 : 4) radix_scatter(cons
 // here: it is a chain of some 30 barriers and LDS round trips, about 2.5 us per pass of few candidates, and 12 where 16384
 // are ranked (the payload is 16 bits, so that they fit).  Four wavefronts that ranked every element of up to 4096, and fifteen launches above, took, in us, the usual
 // heavy tail / nothing capped / all capped: 1000 elements 31.3 / 30.8 / 32.8, now 20.5 / 6.8 / 21.7; 4096 40.2 / 39.7 / 47.8, now 21.2 / 7.4 / 35.0;
-// 16384 59.9 / 42.0 / 115, now 23.7 / 9.4 / 87.  (16385, by the launches: 56.1 / 42 / 106.)
+// 16384 59.9 / 42.0 / 115, now 23.7 / 9.4 / 87.  (16385, by launches: 41.4 / 28.9 / 93.)
 constexpr int kOneWaves = 16, kOneThreads = kOneWaves * kWave, kOneTile = kOneThreads * kSortItems;
 __global__ void __launch_bounds__(kOneThreads) project_one_tile(const float* delta, const float* __restrict__ thr, double alpha,
                                                                 int n, float* out) {
@@ -787,6 +830,32 @@ struct ProjectWorkspace {
     long tiles;
 };
 
+// The twelve launches behind the candidates, eight where the tiles are few.
+template <bool FEW>
+inline void sort_and_cap(const float* delta, long n, int vec_in, float* out, const ProjectWorkspace& w, hipStream_t st) {
+    const long per_xcd = (w.tiles + kXcds - 1) / kXcds;
+    const dim3 grid((unsigned)(per_xcd * kXcds)), blk(kSortThreads), digits(kRadix);
+    unsigned* kin = nullptr; unsigned* vin = nullptr;
+    unsigned* kout = w.keys_a; unsigned* vout = w.vals_a;
+    for (int pass = 0; pass < 4; ++pass) {
+        const int shift = 8 * pass;
+        if (pass == 0) {
+            hipLaunchKernelGGL((radix_count<true>), grid, blk, 0, st, delta, kin, n, shift, (int)(vec_in && aligned(out, 16)), w.mag,
+                               w.hist, out != delta ? reinterpret_cast<unsigned*>(out) : nullptr, w.keys_b, w.vals_b);
+            if (!FEW) hipLaunchKernelGGL((scan_digit<true>), digits, blk, 0, st, w.hist, n, w.mag);
+            hipLaunchKernelGGL((radix_scatter<true, false, FEW>), grid, blk, 0, st, delta, w.keys_b, w.vals_b, kout, vout, n, shift, w.hist, w.mag, w.tab, out);
+        } else {
+            hipLaunchKernelGGL((radix_count<false>), grid, blk, 0, st, delta, kin, n, shift, 1, w.mag, w.hist, nullptr, nullptr, nullptr);
+            if (!FEW) hipLaunchKernelGGL((scan_digit<false>), digits, blk, 0, st, w.hist, n, w.mag);
+            if (pass < 3) hipLaunchKernelGGL((radix_scatter<false, false, FEW>), grid, blk, 0, st, delta, kin, vin, kout, vout, n, shift, w.hist, w.mag, w.tab, out);
+            else          hipLaunchKernelGGL((radix_scatter<false, true, FEW>), grid, blk, 0, st, delta, kin, vin, kout, vout, n, shift, w.hist, w.mag, w.tab, out);
+        }
+        kin = kout; vin = vout;
+        kout = kin == w.keys_a ? w.keys_b : w.keys_a;
+        vout = vin == w.vals_a ? w.vals_b : w.vals_a;
+    }
+}
+
 inline size_t round256(size_t b) { return (b + 255) / 256 * 256; }
 
 inline size_t carve_project(long n, char* ws, ProjectWorkspace* w) {
@@ -846,32 +915,20 @@ int tao_project_empirical(const float* delta, const float* thr_abs, double alpha
     ProjectWorkspace w;
     carve_project(n, (char*)ws, &w);
     hipStream_t st = (hipStream_t)stream;
-    hipLaunchKernelGGL(cap_table_kernel, dim3(1), dim3(kWave), 0, st, thr_abs, alpha, n, w.tab, w.mag);
     const int vec_in = aligned(delta, 16);
     const long want = (n + 8191) / 8192;                        // two vectors per thread before another workgroup is worth it
-    hipLaunchKernelGGL(magnitude_bins, dim3((unsigned)(want < 256 ? want : 256)), dim3(1024), 0, st, delta, n, vec_in, w.mag);
-    hipLaunchKernelGGL(find_candidates, dim3(1), dim3(1024), 0, st, w.tab, w.mag);
-
-    const long per_xcd = (w.tiles + kXcds - 1) / kXcds;
-    const dim3 grid((unsigned)(per_xcd * kXcds)), blk(kSortThreads), digits(kRadix);
-    unsigned* kin = nullptr; unsigned* vin = nullptr;
-    unsigned* kout = w.keys_a; unsigned* vout = w.vals_a;
-    for (int pass = 0; pass < 4; ++pass) {
-        const int shift = 8 * pass;
-        if (pass == 0) {
-            hipLaunchKernelGGL((radix_count<true>), grid, blk, 0, st, delta, kin, n, shift, (int)(vec_in && aligned(out, 16)), w.mag,
-                               w.hist, out != delta ? reinterpret_cast<unsigned*>(out) : nullptr, w.keys_b, w.vals_b);
-            hipLaunchKernelGGL((scan_digit<true>), digits, blk, 0, st, w.hist, n, w.mag);
-            hipLaunchKernelGGL((radix_scatter<true, false>), grid, blk, 0, st, delta, w.keys_b, w.vals_b, kout, vout, n, shift, w.hist, w.mag, w.tab, out);
-        } else {
-            hipLaunchKernelGGL((radix_count<false>), grid, blk, 0, st, delta, kin, n, shift, 1, w.mag, w.hist, nullptr, nullptr, nullptr);
-            hipLaunchKernelGGL((scan_digit<false>), digits, blk, 0, st, w.hist, n, w.mag);
-            if (pass < 3) hipLaunchKernelGGL((radix_scatter<false, false>), grid, blk, 0, st, delta, kin, vin, kout, vout, n, shift, w.hist, w.mag, w.tab, out);
-            else          hipLaunchKernelGGL((radix_scatter<false, true>), grid, blk, 0, st, delta, kin, vin, kout, vout, n, shift, w.hist, w.mag, w.tab, out);
-        }
-        kin = kout; vin = vout;
-        kout = kin == w.keys_a ? w.keys_b : w.keys_a;
-        vout = vin == w.vals_a ? w.vals_b : w.vals_a;
+    const unsigned blocks = (unsigned)(want < 256 ? want : 256);
+    if (w.tiles <= kFewTiles) {
+        // (the workgroups' histograms lie in the place of the first sorted keys: 8192 bytes of at least 4 * 8192)
+        static_assert(kMagBins <= 8192 && kFewTiles * kSortTile <= 256 * 8192, "a histogram in the place of its elements' keys");
+        hipLaunchKernelGGL((magnitude_bins<true>), dim3(blocks), dim3(1024), 0, st, delta, n, vec_in, w.mag, w.keys_a);
+        hipLaunchKernelGGL((find_candidates<true>), dim3(1), dim3(1024), 0, st, thr_abs, alpha, n, w.tab, w.mag, w.keys_a, (int)blocks);
+        sort_and_cap<true>(delta, n, vec_in, out, w, st);
+    } else {
+        hipLaunchKernelGGL(cap_table_kernel, dim3(1), dim3(kWave), 0, st, thr_abs, alpha, n, w.tab, w.mag);
+        hipLaunchKernelGGL((magnitude_bins<false>), dim3(blocks), dim3(1024), 0, st, delta, n, vec_in, w.mag, nullptr);
+        hipLaunchKernelGGL((find_candidates<false>), dim3(1), dim3(1024), 0, st, thr_abs, alpha, n, w.tab, w.mag, nullptr, 0);
+        sort_and_cap<false>(delta, n, vec_in, out, w, st);
     }
     return launch_status();
 }
