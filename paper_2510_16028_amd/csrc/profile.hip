@@ -8,8 +8,8 @@
 // binary64 arithmetic (no contraction), two lane-replicated 2048-bin LDS histograms, partial
 // histograms and counters to the workspace (no global atomics: the result does not depend on
 // scheduling).  Pass 2 (errors_reduce): one workgroup per 64 bins of either histogram sums the
-// partials and locates the 22 nearest-rank percentiles.  Pass 3 (errors_finalize, one small
-// workgroup): exact maxima, percentile values capped by the maximum, threshold ratios.
+// partials and locates the 22 nearest-rank percentiles; the last of them to finish has the exact
+// maxima, percentile values capped by the maximum and threshold ratios.
 #include "tao_hist.hpp"
 #include "tao_host.hpp"
 
@@ -20,9 +20,11 @@ constexpr int kErrReplicas = 4;              // two histograms of 4 x 2048 count
 constexpr int kGrid = TAO_NGRID;
 
 struct ErrStats {            // one per pass-1 workgroup
-    unsigned long long nans;
+    unsigned int nans;                         // (n < 2^36: at most 2^28 elements each)
+    unsigned int done;                         // the first one's: workgroups of pass 2 that have finished
     unsigned int max_abs_bits, max_rel_bits;   // bit patterns of the largest non-NaN errors (>= 0)
 };
+static_assert(sizeof(ErrStats) == 16, "as the workspace's size counts them");
 
 inline unsigned int grid_percent(int g) {
     return g == 0 ? 1u : (g <= 19 ? 5u * (unsigned)g : (g == 20 ? 99u : 100u));
@@ -60,16 +62,23 @@ __global__ __launch_bounds__(kErrThreads) void errors_pass(
     const int rep = tid & (kErrReplicas - 1);
     const long nvec = vec_ok ? (n >> 2) : 0;
     const long stride = (long)gridDim.x * kErrThreads;
-    for (long i = (long)blockIdx.x * kErrThreads + tid; i < nvec; i += stride) {
-        const float4 c4 = ntload4(reinterpret_cast<const float4*>(claimed) + i);
-        const float4 r4 = ntload4(reinterpret_cast<const float4*>(ref) + i);
+    const auto four = [&](const float4& c4, const float4& r4) __attribute__((always_inline)) {
         error_one(c4.x, r4.x, eps_rel, hist_a, hist_r, rep, nans, max_a, max_r);
         error_one(c4.y, r4.y, eps_rel, hist_a, hist_r, rep, nans, max_a, max_r);
         error_one(c4.z, r4.z, eps_rel, hist_a, hist_r, rep, nans, max_a, max_r);
         error_one(c4.w, r4.w, eps_rel, hist_a, hist_r, rep, nans, max_a, max_r);
+    };
+    const float4* const cv = reinterpret_cast<const float4*>(claimed);
+    const float4* const rv = reinterpret_cast<const float4*>(ref);
+    long i = (long)blockIdx.x * kErrThreads + tid;
+    for (; i + stride < nvec; i += 2 * stride) {               // (two of each under way: 8.4 M elements 16.2 us, one 17.4)
+        const float4 c0 = ntload4(cv + i), r0 = ntload4(rv + i), c1 = ntload4(cv + i + stride), r1 = ntload4(rv + i + stride);
+        four(c0, r0);
+        four(c1, r1);
     }
+    if (i < nvec) four(ntload4(cv + i), ntload4(rv + i));
     // scalar remainder (everything when the inputs are not 16-byte aligned)
-    for (long i = (nvec << 2) + (long)blockIdx.x * kErrThreads + tid; i < n; i += stride)
+    for (i = (nvec << 2) + (long)blockIdx.x * kErrThreads + tid; i < n; i += stride)
         error_one(claimed[i], ref[i], eps_rel, hist_a, hist_r, rep, nans, max_a, max_r);
 
     nans = wave_sum(nans); max_a = wave_max(max_a); max_r = wave_max(max_r);
@@ -78,32 +87,18 @@ __global__ __launch_bounds__(kErrThreads) void errors_pass(
     __syncthreads();
     static_assert(kErrThreads / kWave == 16, "a row of lanes reads the wavefronts' totals");
     if (tid < 16) {
-        const unsigned long long ns = wave_all<0, 4>((unsigned long long)red[tid * 3], [](unsigned long long a, unsigned long long b) { return a + b; });
+        const unsigned int ns = wave_all<0, 4>(red[tid * 3], [](unsigned int a, unsigned int b) { return a + b; });
         const auto larger = [](unsigned int a, unsigned int b) { return max(a, b); };
         const unsigned int as = wave_all<0, 4>(red[tid * 3 + 1], larger), rs = wave_all<0, 4>(red[tid * 3 + 2], larger);
-        if (tid == 0) ws_stats[blockIdx.x] = ErrStats{ns, as, rs};
+        if (tid == 0) ws_stats[blockIdx.x] = ErrStats{ns, 0u, as, rs};
     }
     flush_histogram<kErrReplicas>(hist_a, ws_hist_a + (size_t)blockIdx.x * kBins, ws_coarse_a + blockIdx.x * kGroups);
     flush_histogram<kErrReplicas>(hist_r, ws_hist_r + (size_t)blockIdx.x * kBins, ws_coarse_r + blockIdx.x * kGroups);
 }
 
-// workgroups 0 .. 31: absolute-error histogram; 32 .. 63: relative-error histogram
-__global__ __launch_bounds__(kReduceThreads) void errors_reduce(
-    const unsigned int* __restrict__ ws_hist_a, const unsigned int* __restrict__ ws_hist_r,
-    const unsigned int* __restrict__ ws_coarse_a, const unsigned int* __restrict__ ws_coarse_r,
-    int nblocks, Ranks<kGrid> ranks, tao_error_profile* out) {
-    __shared__ unsigned long long smem[kReduceThreads + kReduceWaves];
-    const bool rel = blockIdx.x >= (unsigned)kGroups;
-    const int grp = rel ? blockIdx.x - kGroups : blockIdx.x;
-    const GroupLoads<kReduceThreads, kMaxPartials> loads(rel ? ws_hist_r : ws_hist_a, rel ? ws_coarse_r : ws_coarse_a, nblocks, grp);
-    reduce_group<kGrid>(loads, grp, rel ? out->hist_rel : out->hist_abs, ranks, rel ? out->rel_bin : out->abs_bin,
-                        rel ? out->rel_p : out->abs_p, smem);
-}
-
 // One wavefront, a lane per grid point (a thread that takes the 22 points and their divisions in turn needs 9 us, this 4).
-__global__ __launch_bounds__(kWave) void errors_finalize(const ErrStats* __restrict__ ws_stats, int nblocks,
-                                                         unsigned long long n, const float* __restrict__ thr_abs,
-                                                         const float* __restrict__ thr_rel, tao_error_profile* out) {
+__device__ __forceinline__ void errors_finalize(const ErrStats* ws_stats, int nblocks, unsigned long long n, const float* __restrict__ thr_abs,
+                                                const float* __restrict__ thr_rel, tao_error_profile* out) {
     static_assert(kGrid <= kWave, "a lane per grid point");
     const int lane = threadIdx.x, g = lane < kGrid ? lane : 0;
     unsigned int ba = out->abs_bin[g], br = out->rel_bin[g];
@@ -131,6 +126,28 @@ __global__ __launch_bounds__(kWave) void errors_finalize(const ErrStats* __restr
     out->n = n; out->nan_count = qn; out->max_abs = max_abs; out->max_rel = max_rel; out->pad_ = 0;
     out->p_max = pmax;
     out->offending = (pmax > 1.0) ? 1u : 0u;
+}
+
+// workgroups 0 .. 31: absolute-error histogram; 32 .. 63: relative-error histogram.  The last one to finish sees the others' percentiles
+// (fences on both sides of the count); in a launch of its own that part took 2 to 4 us, and the host 3.6.
+__global__ __launch_bounds__(kReduceThreads) void errors_reduce(
+    const unsigned int* __restrict__ ws_hist_a, const unsigned int* __restrict__ ws_hist_r,
+    const unsigned int* __restrict__ ws_coarse_a, const unsigned int* __restrict__ ws_coarse_r,
+    ErrStats* ws_stats, int nblocks, unsigned long long n, Ranks<kGrid> ranks, const float* __restrict__ thr_abs,
+    const float* __restrict__ thr_rel, tao_error_profile* out) {
+    __shared__ unsigned long long smem[kReduceThreads + kReduceWaves];
+    const bool rel = blockIdx.x >= (unsigned)kGroups;
+    const int grp = rel ? blockIdx.x - kGroups : blockIdx.x;
+    const GroupLoads<kReduceThreads, kMaxPartials> loads(rel ? ws_hist_r : ws_hist_a, rel ? ws_coarse_r : ws_coarse_a, nblocks, grp);
+    reduce_group<kGrid>(loads, grp, rel ? out->hist_rel : out->hist_abs, ranks, rel ? out->rel_bin : out->abs_bin,
+                        rel ? out->rel_p : out->abs_p, smem);
+    if (threadIdx.x >= kWave) return;                          // (the first wavefront has written the results)
+    __threadfence();
+    unsigned finished = 0;
+    if (threadIdx.x == 0) finished = atomicAdd(&ws_stats[0].done, 1u);
+    if (__builtin_amdgcn_readfirstlane(finished) != gridDim.x - 1) return;
+    __threadfence();
+    errors_finalize(ws_stats, nblocks, n, thr_abs, thr_rel, out);
 }
 
 // Calibration (Sec. 3.2): per grid point the maximum over the runs' percentile values (NaN entries
@@ -203,9 +220,7 @@ int tao_profile_errors(const float* claimed, const float* ref, long n, double ep
     Ranks<kGrid> ranks;
     for (int g = 0; g < kGrid; ++g) ranks.at[g] = rank_of((unsigned long long)n, grid_percent(g), 100);
     hipLaunchKernelGGL(errors_reduce, dim3(2 * kGroups), dim3(kReduceThreads), 0, st, ws_hist_a, ws_hist_r,
-                       ws_coarse_a, ws_coarse_r, nblocks, ranks, out);
-    hipLaunchKernelGGL(errors_finalize, dim3(1), dim3(kWave), 0, st, ws_stats, nblocks, (unsigned long long)n,
-                       thr_abs, thr_rel, out);
+                       ws_coarse_a, ws_coarse_r, ws_stats, nblocks, (unsigned long long)n, ranks, thr_abs, thr_rel, out);
     return launch_status();
 }
 
