@@ -39,9 +39,8 @@ struct RowConsts {
     double mean_f;     // c_div u / (1 - c_div u), upper
     double m;          // rounding margin of a bound of this row length (see make_consts)
     float quick_alpha; // the one-pass checks: alpha of the estimates
-    int trip_rows;     // ... and rows that a workgroup takes at a time (deal_rows)
+    int apart;         // ... and rows between those of neighbouring row groups of a workgroup (row_blocks)
 };
-constexpr bool deals_rows(int tpr, bool quick) { return tpr <= 256 && !quick; }
 
 // Factors of the final upper rounding (up32g) for a rounding margin m.
 struct UpFactors {
@@ -285,16 +284,18 @@ __global__ __launch_bounds__(kCheckThreads) void softmax_check(
     unsigned beyond = 0;                                     // counted in bin 0, but another vector's
     const int rep = tid & (kReplicas - 1);
     const int nv = CACHED ? V : (int)((cols + TPR * 4 - 1) / (TPR * 4));
-    // (a row group beyond the workgroup's rows has none in any trip)
-    constexpr bool DEALT = deals_rows(TPR, QUICK);
-    const int trip_rows = DEALT ? k.trip_rows : kCheckThreads / TPR;
-    const bool spare = DEALT && tid / TPR >= trip_rows;
-    const long nblocks = (rows + trip_rows - 1) / trip_rows, slot = spare ? rows : tid / TPR;
+    // Row group s of workgroup b, of G: rows b + s G, b + (s + all) G, ..., so that what is left for the last trip falls to all workgroups; or, k.apart being 1,
+    // neighbouring rows.  A wavefront of whole rows goes by its first one, a workgroup whose row groups meet at barriers by the first of all.
+    // (OWN: no lane of a wavefront asks whether there is its row; with four vectors the scheduling that comes of it is worse: 8192 x 1024 36.0 us, 30.8 without.)
+    constexpr bool OWN = TPR == kWave && V != 4;
+    const int lead = TPR <= kWave ? __builtin_amdgcn_readfirstlane(tid / kWave) * (kWave / TPR) : 0;
+    const long trip = (long)gridDim.x * (kCheckThreads / TPR), mine = (long)k.apart * (tid / TPR - lead);
+    const long first = (long)blockIdx.x * (k.apart == 1 ? kCheckThreads / TPR : 1) + (long)k.apart * lead;
     float4 xn[PIPE ? V : 1], yn[PIPE ? V : 1], cn[PIPE && CLAIMS ? V : 1];
     auto request = [&](long rb, float4* xr, float4* yr, float4* cr) __attribute__((always_inline)) {
         int lt = tid % TPR;
         asm volatile("" : "+v"(lt));
-        const long row = rb * trip_rows + slot, roff = (row < rows ? row : rows - 1) * ld;
+        const long row = OWN ? rb : rb + mine, roff = (OWN || row < rows ? row : rows - 1) * ld;
         const Idx last = (Idx)cols - (FULL ? 4 : 1);
 #pragma unroll
         for (int v = 0; v < V; ++v) {
@@ -303,13 +304,13 @@ __global__ __launch_bounds__(kCheckThreads) void softmax_check(
             if (CLAIMS) cr[v] = row_vec<FULL, true, TPR>(claimed + roff, TAO_VEC_IDX(v), last);
         }
     };
-    if (PIPE && (long)blockIdx.x < nblocks) request(blockIdx.x, xn, yn, cn);
-    // every thread of the workgroup takes the same number of trips (the reductions hold barriers)
-    for (long rb = DEALT && TPR <= kWave && __all(spare) ? nblocks : (long)blockIdx.x; rb < nblocks; rb += gridDim.x) {
+    if (PIPE && first < rows) request(first, xn, yn, cn);
+    // (every thread of a workgroup takes the same number of trips where the reductions hold barriers)
+    for (long rb = first; rb < rows; rb += trip) {
         int lt = tid % TPR;
         if (CACHED) asm volatile("" : "+v"(lt));            // (positions are formed anew for every row and pass: hoisted they would take the registers of the row)
-        const long row = rb * trip_rows + slot;
-        const bool active = row < rows;
+        const long row = OWN ? rb : rb + mine;
+        const bool active = OWN || row < rows;
         const Idx limit = active ? (Idx)cols : 0, last = (Idx)cols - (FULL ? 4 : 1);
         const long roff = (active ? row : rows - 1) * ld;
         float4 xv[CACHED ? V : 1], yv[CACHED ? V : 1], cv[CLAIMS ? V : 1];
@@ -320,7 +321,7 @@ __global__ __launch_bounds__(kCheckThreads) void softmax_check(
                 xv[v] = xn[v]; yv[v] = yn[v];
                 if (CLAIMS) cv[v] = cn[v];
             }
-            if (rb + gridDim.x < nblocks) request(rb + gridDim.x, xn, yn, cn);
+            if (rb + trip < rows) request(rb + trip, xn, yn, cn);
             __builtin_amdgcn_sched_barrier(0);
         } else if (CACHED) {
 #pragma unroll
@@ -774,17 +775,17 @@ __global__ __launch_bounds__(kCheckThreads) void norm_check(
     unsigned beyond = 0;                                     // counted in bin 0, but another vector's
     const int rep = tid & (kReplicas - 1);
     const int nv = CACHED ? V : (int)((cols + TPR * 4 - 1) / (TPR * 4));
-    // (a row group beyond the workgroup's rows has none in any trip)
-    constexpr bool DEALT = deals_rows(TPR, QUICK);
-    const int trip_rows = DEALT ? k.trip_rows : kCheckThreads / TPR;
-    const bool spare = DEALT && tid / TPR >= trip_rows;
-    const long nblocks = (rows + trip_rows - 1) / trip_rows, slot = spare ? rows : tid / TPR;
+    // Row group s of workgroup b, of G: rows b + s G, b + (s + all) G, ..., so that what is left for the last trip falls to all workgroups; or, k.apart being 1,
+    // neighbouring rows.  A wavefront of whole rows goes by its first one, a workgroup whose row groups meet at barriers by the first of all.
+    const int lead = TPR <= kWave ? __builtin_amdgcn_readfirstlane(tid / kWave) * (kWave / TPR) : 0;
+    const long trip = (long)gridDim.x * (kCheckThreads / TPR), mine = (long)k.apart * (tid / TPR - lead);
+    const long first = (long)blockIdx.x * (k.apart == 1 ? kCheckThreads / TPR : 1) + (long)k.apart * lead;
     const double n = (double)cols;
     float4 xn[PIPE ? V : 1], yn[PIPE ? V : 1], cn[PIPE && CLAIMS ? V : 1];
     auto request = [&](long rb, float4* xr, float4* yr, float4* cr) __attribute__((always_inline)) {
         int lt = tid % TPR;
         asm volatile("" : "+v"(lt));
-        const long row = rb * trip_rows + slot, roff = (row < rows ? row : rows - 1) * ld;
+        const long row = TPR == kWave ? rb : rb + mine, roff = (TPR == kWave || row < rows ? row : rows - 1) * ld;
         const Idx last = (Idx)cols - (FULL ? 4 : 1);
 #pragma unroll
         for (int v = 0; v < V; ++v) {
@@ -793,13 +794,13 @@ __global__ __launch_bounds__(kCheckThreads) void norm_check(
             if (CLAIMS) cr[v] = row_vec<FULL, true, TPR>(claimed + roff, TAO_VEC_IDX(v), last);
         }
     };
-    if (PIPE && (long)blockIdx.x < nblocks) request(blockIdx.x, xn, yn, cn);
-    // every thread of the workgroup takes the same number of trips (the reductions hold barriers)
-    for (long rb = DEALT && TPR <= kWave && __all(spare) ? nblocks : (long)blockIdx.x; rb < nblocks; rb += gridDim.x) {
+    if (PIPE && first < rows) request(first, xn, yn, cn);
+    // (every thread of a workgroup takes the same number of trips where the reductions hold barriers)
+    for (long rb = first; rb < rows; rb += trip) {
         int lt = tid % TPR;
         if (CACHED) asm volatile("" : "+v"(lt));            // (positions are formed anew for every row and pass, as in softmax_check)
-        const long row = rb * trip_rows + slot;
-        const bool active = row < rows;
+        const long row = TPR == kWave ? rb : rb + mine;
+        const bool active = TPR == kWave || row < rows;
         const Idx limit = active ? (Idx)cols : 0, last = (Idx)cols - (FULL ? 4 : 1);
         const long roff = (active ? row : rows - 1) * ld;
         float4 xv[CACHED ? V : 1], yv[CACHED ? V : 1], cv[CLAIMS ? V : 1], gv[CLAIMS ? V : 1];
@@ -811,7 +812,7 @@ __global__ __launch_bounds__(kCheckThreads) void norm_check(
                 xv[v] = xn[v]; yv[v] = yn[v];
                 if (CLAIMS) { cv[v] = cn[v]; gv[v] = scales(TAO_VEC_IDX(v)); }
             }
-            if (rb + gridDim.x < nblocks) request(rb + gridDim.x, xn, yn, cn);
+            if (rb + trip < rows) request(rb + trip, xn, yn, cn);
             __builtin_amdgcn_sched_barrier(0);
         } else if (CACHED) {
 #pragma unroll
@@ -997,28 +998,25 @@ static int row_form(bool whole, long cols, long tpr, long V) {
 // among four wavefronts, which fill the chip sooner (8192 x 1024 34 against 46 us, 4096 x 2048 45 against 40).
 // Rows of the norms of up to 64 and 128 columns belong to 16 and 32 lanes (a wavefront each, most of whose lanes then held nothing: RMSNorm 161713 x 56
 // 96.9 us, now 35.3, LayerNorm 130000 x 64 121.7 / 37.6, 100000 x 100 88.5 / 49.1, RMSNorm 60 x 61 10.7 / 8.0).
-// Workgroups of a one-pass check, and the rows that each takes at a time: one per row group (`groups`), or fewer where that deals the
-// rows out evenly over few trips.  Where all rows fit one trip with workgroups to spare, they go to more of these, down to kFewestElements each.
-// Few rows wait for the arithmetic of a compute unit, which is four to sixteen rows at a time, and for the unit that has most of them (softmax / RMSNorm, us, by full
-// trips and dealt out: 6144 x 512, one trip and a half, 20.5 / 19.1 and 18.2 / 17.1; 9000 x 512 26.6 / 24.2 and 23.2 / 21.4; 64 x 1500, on 16 workgroups and on 64,
-// 13.6 / 12.3 and 11.3 / 10.1; 512 x 768 11.0 / 10.6 and 10.7 / 10.1).  Many wait for memory, and want all the loads a trip has; those, and rows
-// settled quickly, of which there are four trips and more, and rows of a half or a whole workgroup keep a fixed trip: the count in a register costs them 1 to 2 %
-// (RMSNorm 2048 x 4096 31.3, 32.0 with it).
-constexpr long kFewestElements = 1024, kFewTrips = 4;
-static int deal_rows(long rows, long cols, int groups, bool dealt, RowConsts& k) {
+// Workgroups of a one-pass check, `groups` rows at a time each.  Where all rows fit one trip with workgroups to spare, they go to more of these, down to
+// kFewestElements each, as far as that takes rows off the fullest one.  Few rows wait for the arithmetic of the compute unit that has most of them, many end
+// with a trip that only some have; with a workgroup's rows as far apart as there are workgroups that trip is everybody's, and the wavefronts that have none
+// in it are done (softmax / RMSNorm, us, with neighbouring rows and so: 6144 x 512, one trip and a half, 20.5 / 19.1 and 16.8 / 15.8; 9000 x 512 26.7 / 24.2 and 22.1 / 20.5;
+// 21696 x 1356 92.4 / 100 and 79.9 / 100; 16384 x 1024 47.6 / 46.4 and 45.6 / 42.6, but softmax 8192 x 1024 29.4 and 30.8; 64 x 1500, on 16 workgroups and on 64,
+// 13.6 / 12.5 and 11.3 / 10.2; 512 x 768 10.9 / 10.6 and 10.5 / 10.2).  Row groups of more than a wavefront whose last trip is a full one keep neighbouring rows (RMSNorm
+// 2048 x 4096 31.3, 31.8 apart).
+constexpr long kFewestElements = 1024;
+static int row_blocks(long rows, long cols, int tpr, RowConsts& k) {
+    const int groups = kCheckThreads / tpr;
     const long full = (rows + groups - 1) / groups;
     long blocks = full <= alone_row_groups(cols) ? 1 : full < kMaxCheckBlocks ? full : kMaxCheckBlocks;
-    if (dealt && blocks > 1 && blocks < kMaxCheckBlocks) {
+    if (blocks > 1 && blocks < kMaxCheckBlocks) {
         const long most = rows < kMaxCheckBlocks ? rows : (long)kMaxCheckBlocks, spread = rows * cols / kFewestElements;
         blocks = spread < blocks ? blocks : spread < most ? spread : most;
+        const long each = (rows + blocks - 1) / blocks;
+        blocks = (rows + each - 1) / each;
     }
-    const long trips = (full + blocks - 1) / blocks;
-    k.trip_rows = groups;
-    if (dealt && blocks > 1 && trips <= kFewTrips) {
-        k.trip_rows = (int)((rows + blocks * trips - 1) / (blocks * trips));
-        const long all = (rows + k.trip_rows - 1) / k.trip_rows;
-        if (all < blocks) blocks = all;
-    }
+    k.apart = tpr > kWave && rows % (blocks * groups) == 0 ? 1 : (int)blocks;
     return (int)blocks;
 }
 constexpr long kWaveRows = 2L * kMaxCheckBlocks * (kCheckThreads / kWave);
@@ -1234,8 +1232,8 @@ int tao_bound_check_norm(int kind, const float* x, const float* y_ref, const flo
     const CheckWorkspace w = carve_check_workspace(ws);
     int nblocks = 1;
     const bool rms = kind == TAO_NORM_RMSNORM;
-    auto launch = [&](auto kernel, int tpr, bool dealt, long r, long c, long l) {
-        nblocks = deal_rows(r, c, kCheckThreads / tpr, dealt, k);
+    auto launch = [&](auto kernel, int tpr, long r, long c, long l) {
+        nblocks = row_blocks(r, c, tpr, k);
         hipLaunchKernelGGL(kernel, dim3(nblocks), dim3(kCheckThreads), 0, st, x, y_ref, gamma, claimed, r, c, l,
                            k, alpha, eps_rel, pass_out(w, nblocks, n, out));
     };
@@ -1243,14 +1241,14 @@ int tao_bound_check_norm(int kind, const float* x, const float* y_ref, const flo
 #define TAO_NORM_CHECK_Q(RMS, TPR, V, Q) \
     do {                                                                                                    \
         const int form = row_form(full, cols, TPR, V);                                                      \
-        if (form == WHOLE)    launch(norm_check<RMS, TPR, V, WHOLE, Q>, TPR, deals_rows(TPR, Q), rows, cols, ld);               \
-        else if (form == ANY) launch(norm_check<RMS, TPR, V, ANY, Q>, TPR, deals_rows(TPR, Q), rows, cols, ld);                 \
-        else                  launch(norm_check<RMS, TPR, V, V == 2 ? SINGLE : ANY, Q>, TPR, deals_rows(TPR, Q), rows, cols, ld); \
+        if (form == WHOLE)    launch(norm_check<RMS, TPR, V, WHOLE, Q>, TPR, rows, cols, ld);               \
+        else if (form == ANY) launch(norm_check<RMS, TPR, V, ANY, Q>, TPR, rows, cols, ld);                 \
+        else                  launch(norm_check<RMS, TPR, V, V == 2 ? SINGLE : ANY, Q>, TPR, rows, cols, ld); \
     } while (0)
 #define TAO_NORM_CHECK(RMS, TPR, V) do { if (quick(TPR)) TAO_NORM_CHECK_Q(RMS, TPR, V, true); else TAO_NORM_CHECK_Q(RMS, TPR, V, false); } while (0)
 #define TAO_NORM_CHECK_ROWS(RMS)                                                                            \
     do {                                                                                                    \
-        if (cols < 4)                        launch(norm_check<RMS, 64, 1, SINGLE, false>, 64, true, rows, cols, ld); \
+        if (cols < 4)                        launch(norm_check<RMS, 64, 1, SINGLE, false>, 64, rows, cols, ld); \
         else if (cols <= 64)                 TAO_NORM_CHECK(RMS, 16, 1);                                    \
         else if (cols <= 128)                TAO_NORM_CHECK(RMS, 32, 1);                                    \
         else if (cols <= 256)                TAO_NORM_CHECK(RMS, 64, 1);                                    \
@@ -1263,7 +1261,7 @@ int tao_bound_check_norm(int kind, const float* x, const float* y_ref, const flo
         else                                 TAO_NORM_CHECK_Q(RMS, 1024, 0, false);                         \
     } while (0)
     if (n == 0) {
-        if (rms) launch(norm_check<true, 64, 1, SINGLE, false>, 64, true, 0L, 1L, 1L); else launch(norm_check<false, 64, 1, SINGLE, false>, 64, true, 0L, 1L, 1L);
+        if (rms) launch(norm_check<true, 64, 1, SINGLE, false>, 64, 0L, 1L, 1L); else launch(norm_check<false, 64, 1, SINGLE, false>, 64, 0L, 1L, 1L);
     } else if (rms) {
         TAO_NORM_CHECK_ROWS(true);
     } else {
@@ -1300,8 +1298,8 @@ int tao_bound_check_softmax(const float* x, const float* y_ref, const float* cla
     const bool full = aligned(x, 16) && aligned(y_ref, 16) && aligned(claimed, 16) && (ld % 4 == 0) && (cols % 4 == 0);
     int nblocks = 1;
     if (n > 0) {
-        auto launch = [&](auto kernel, int tpr, bool dealt) {
-            nblocks = deal_rows(rows, cols, kCheckThreads / tpr, dealt, k);
+        auto launch = [&](auto kernel, int tpr) {
+            nblocks = row_blocks(rows, cols, tpr, k);
             hipLaunchKernelGGL(kernel, dim3(nblocks), dim3(kCheckThreads), 0, st, x, y_ref, claimed, rows, cols, ld,
                                k, alpha, eps_rel, pass_out(w, nblocks, n, out));
         };
@@ -1309,12 +1307,12 @@ int tao_bound_check_softmax(const float* x, const float* y_ref, const float* cla
 #define TAO_SOFTMAX_CHECK_Q(TPR, V, Q) \
     do {                                                                                        \
         const int form = row_form(full, cols, TPR, V);                                          \
-        if (form == WHOLE)    launch(softmax_check<TPR, V, WHOLE, Q>, TPR, deals_rows(TPR, Q));                     \
-        else if (form == ANY) launch(softmax_check<TPR, V, ANY, Q>, TPR, deals_rows(TPR, Q));                       \
-        else                  launch(softmax_check<TPR, V, V == 2 ? SINGLE : ANY, Q>, TPR, deals_rows(TPR, Q));     \
+        if (form == WHOLE)    launch(softmax_check<TPR, V, WHOLE, Q>, TPR);                     \
+        else if (form == ANY) launch(softmax_check<TPR, V, ANY, Q>, TPR);                       \
+        else                  launch(softmax_check<TPR, V, V == 2 ? SINGLE : ANY, Q>, TPR);     \
     } while (0)
 #define TAO_SOFTMAX_CHECK(TPR, V) do { if (quick(TPR)) TAO_SOFTMAX_CHECK_Q(TPR, V, true); else TAO_SOFTMAX_CHECK_Q(TPR, V, false); } while (0)
-        if (cols < 4)          launch(softmax_check<64, 1, SINGLE, false>, 64, true);
+        if (cols < 4)          launch(softmax_check<64, 1, SINGLE, false>, 64);
         else if (cols <= 256)  TAO_SOFTMAX_CHECK(64, 1);
         else if (cols <= 512)  TAO_SOFTMAX_CHECK(64, 2);
         else if (cols <= 1024 && rows >= kWaveRows) TAO_SOFTMAX_CHECK_Q(64, 4, true);
@@ -1328,7 +1326,6 @@ int tao_bound_check_softmax(const float* x, const float* y_ref, const float* cla
 #undef TAO_SOFTMAX_CHECK_Q
     } else {
         // nothing to examine: an empty partial, so that the profile reports n = 0
-        deal_rows(0, 1, kCheckThreads / 64, true, k);
         hipLaunchKernelGGL((softmax_check<64, 1, SINGLE, false>), dim3(1), dim3(kCheckThreads), 0, st, x, y_ref, claimed, 0L, 1L, 1L,
                            k, alpha, eps_rel, pass_out(w, nblocks, n, out));
     }
