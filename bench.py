@@ -590,12 +590,14 @@ def main():
                 "bound_and_check_in_one_call": [p.name for p in lin if p.fused],
                 "tiles_left_open": {p.name: p.open_share() for p in lin if p.fused},
                 "prepared_weight_images": [p.name for p in lin if p.prepared],
-                # issued flop against the peak of the matrix cores that it runs on (of the paths together: weighted by their flop)
+                # the products' flop in full against the peak of the matrix cores that they run on (of the paths together: weighted by their
+                # flop).  A checked product whose claims its first slab of k decides issues no more of it, so this is no rate of the matrix cores.
+                "flop_counted": "whole products; a checked one issues its first 64 or 128 k where its form tries them, and the rest for tiles that these leave open",
                 "achieved": lin_issued / (lin_ms * 1e-3) / 1e12, "peak": lin_issued / ms_at_peak * 1e-9,
                 "unit": "TFLOP/s", "frac": ms_at_peak / lin_ms,
                 "algorithmic_TFLOP/s": achieved, "frac_fp32_mfma_peak": achieved / PEAK_FP32_MFMA_TFLOPS,
-                # the two paths apart: the FP32 path's algorithmic flop against the FP32 MFMA peak, the BF16-split path's issued
-                # flop (one BF16 product per operand pair in a checked call, 6 in a bound) against the BF16 MFMA peak
+                # the two paths apart: the FP32 path's algorithmic flop against the FP32 MFMA peak, the BF16-split path's
+                # flop (one whole BF16 product per operand pair in a checked call, 6 in a bound) against the BF16 MFMA peak
                 "frac_fp32_path_of_fp32_peak": paths["fp32"]["issued_frac_of_own_peak"] if "fp32" in paths else None,
                 "frac_bf16_path_of_bf16_peak": paths["bf16_split"]["issued_frac_of_own_peak"] if "bf16_split" in paths else None,
                 "paths": paths,
