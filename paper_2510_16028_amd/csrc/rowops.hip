@@ -1070,6 +1070,7 @@ static int make_consts(const tao_fp_model& md, long cols, double eps, RowConsts*
     // through a difference (1 - sigma of the softmax, the lower end w_lo of the variance).
     k->m = ((double)cols + 130.0) * 0x1p-51;
     k->quick_alpha = NAN;
+    k->apart = 1;                                            // (no launch leaves it open, one of no rows either: row_blocks chooses for the others)
     if (!(md.c_exp * u < 0.5) || !(md.c_div * u < 0.5)) return TAO_ERR_MODEL;
     return TAO_OK;
 }

@@ -1,0 +1,61 @@
+"""Launches of the one-pass row checks, by their arguments: of empty tensors, and how rows are dealt out."""
+import launches
+
+# the constants' last two fields
+CONSTS = r"""
+class Consts(ctypes.Structure):
+    _fields_ = [("numbers", ctypes.c_double * 12), ("quick_alpha", ctypes.c_float), ("apart", ctypes.c_int)]
+P = address(1 << 20)
+def softmax(rows, cols, p=P):
+    watch("softmax_check", (3, ctypes.c_long), (6, Consts))
+    assert lib.tao_bound_check_softmax(p, p, p, rows, cols, cols, 1.0, 1e-12, None, P, P, 1 << 24, None) == 0
+    return launched()[0]
+def norm(kind, rows, cols, p=P):
+    watch("norm_check", (4, ctypes.c_long), (7, Consts))
+    assert lib.tao_bound_check_norm(kind, p, p, p, p, 1e-5, p, rows, cols, cols, 1.0, 1e-12, None, P, P, 1 << 24, None) == 0
+    return launched()[0]
+calls = {"softmax": softmax, "layernorm": lambda *a: norm(tao.NORM_LAYERNORM, *a), "rmsnorm": lambda *a: norm(tao.NORM_RMSNORM, *a)}
+"""
+
+EMPTY = CONSTS + r"""
+result = []
+for name, call in calls.items():
+    for rows, cols in ((0, 16), (0, 5000), (7, 0), (0, 0)):
+        kernel, grid, block, (r, k) = call(rows, cols, None)
+        result.append((name, rows, cols, kernel, grid, block, r.value, k.apart))
+"""
+
+
+def test_an_empty_tensor_gives_a_kernel_no_rows(tmp_path):
+    found = launches.run(EMPTY, tmp_path)
+    assert len(found) == 3 * 4
+    for name, rows, cols, kernel, grid, block, r, apart in found:
+        case = (name, rows, cols)
+        assert kernel.startswith("softmax_check<" if name == "softmax" else "norm_check<") and (grid, block) == (1, 1024), case
+        assert r == 0 and apart == 1, (case, r, apart)           # row group s begins at row s, of none
+
+
+DEALT = CONSTS + r"""
+result = []
+for name, call in calls.items():
+    for rows in (1, 2, 3, 17, 255, 256, 257, 4095, 4096, 4097, 8192, 20001):
+        for cols in (1, 3, 4, 61, 128, 200, 512, 513, 1024, 1500, 2048, 4096, 8200):
+            kernel, grid, block, (r, k) = call(rows, cols)
+            result.append((kernel, grid, block, r.value, k.apart, cols))
+"""
+
+
+def test_every_row_belongs_to_one_row_group(tmp_path):
+    """The rows that a kernel's row groups walk, by its threads per row, grid and the distance of neighbouring ones: each row once."""
+    found = launches.run(DEALT, tmp_path)
+    assert len(found) == 3 * 12 * 13
+    for kernel, grid, block, rows, apart, cols in found:
+        inside = kernel[kernel.index("<") + 1:].split(",")
+        tpr = int(inside[0] if kernel.startswith("softmax") else inside[1])
+        groups, seen = block // tpr, [0] * rows
+        assert apart >= 1 and 1 <= grid <= 256, (kernel, grid, rows, apart)
+        for b in range(grid):
+            for s in range(groups):
+                for row in range(b * (groups if apart == 1 else 1) + apart * s, rows, grid * groups):
+                    seen[row] += 1
+        assert seen == [1] * rows, (kernel, grid, rows, apart, cols)
