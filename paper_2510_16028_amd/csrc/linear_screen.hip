@@ -53,12 +53,7 @@ constexpr int SBK = kScreenGroup;
 constexpr int kImageBlock = 3 * 128 * 64;               // bytes of an image's block of 128 rows x 32 k, three pieces
 constexpr unsigned kLargeBf16 = (127u + 32u) << 7;      // 2^32: operands from here on are not screened
 constexpr float kTinyPerStep = 0x1p-80f;
-constexpr int kHistWords = 2048;                        // bins up to infinity's, 2040 (NaN is counted apart), then seven words more
-// Words behind them that count errors of 0, one for each lane, so that these need no ballots (three scalar instructions and a comparison an
-// element: 8 x 8192 x 2048 over 128 234 -> 231 us).  Tiles of 64 x 64 have none and count by ballots: in all of their forms but one the
-// workgroups of a compute unit fill the LDS to its last 64 bytes (the form for few tiles has room; its workgroups check one tile or two).
-constexpr int spare_words(int blocks) { return blocks > 1 ? 64 : 0; }
-constexpr int kEarlyWords = 8, kEarlyTiles = 32 * kEarlyWords;          // tiles of a workgroup that may be tried by their first slabs (2.1 G outputs)
+constexpr int kEarlyTiles = 32 * kEarlyWords;            // tiles of a workgroup that may be tried by their first slabs (2.1 G outputs)
 
 __device__ __forceinline__ unsigned pack_abs_bf16(float even, float odd) {
     return __builtin_bit_cast(unsigned, __builtin_convertvector((floatx2{fabsf(even), fabsf(odd)}), bf16x2));
@@ -152,7 +147,7 @@ __global__ __launch_bounds__(WVM * WVN * 64, WVM * WVN * PER_CU / 4) void screen
     static_assert(!EARLY || THREADS >= kMarks / 2, "a thread for four marks");
     extern __shared__ __attribute__((aligned(16))) char lds[];
     unsigned int* const hist = reinterpret_cast<unsigned int*>(lds);
-    constexpr int WORDS = kHistWords + spare_words(RM * RN) + (EARLY ? kEarlyWords : 0);
+    constexpr int WORDS = words_before_stages(RM * RN, EARLY);
     unsigned int* const pending = hist + kHistWords + spare_words(RM * RN);      // tiles of which a first slab did not decide all, a bit each
     char* const stages = lds + WORDS * 4;
     char* const slab0 = stages + (ACROSS ? WAVES * 32 * STRIP * 4 : 0);        // a first slab's place (ACROSS: behind the strips)
@@ -189,11 +184,10 @@ __global__ __launch_bounds__(WVM * WVN * 64, WVM * WVN * PER_CU / 4) void screen
     int zeros = 0;                                           // elements with d = 0 (a lane's own, to be added to all_zeros)
     int all_zeros = 0;                                       // (the same in all lanes)
     float* strip = reinterpret_cast<float*>(stages) + wave * 32 * STRIP;
-    // what stands for the bits of an error of 0, which is counted elsewhere: the middle of a "bin" that is one of the words behind the
-    // bins, or, where there are none, a padding word of the first strip
-    constexpr int SPARE_ROWS = 22;
-    static_assert(kHistWords + SPARE_ROWS * STRIP < 4096, "twelve bits of bin");
-    const unsigned zero_bits = (unsigned)(SPARE ? kHistWords + lane : kHistWords + (lane % SPARE_ROWS) * STRIP + COLS + lane / SPARE_ROWS) << 20 | 0x80000u;
+    // what stands for the bits of an error of 0, which is counted elsewhere: the middle of a "bin" that is a word of no bin (zero_word)
+    static_assert(SPARE || (COLS + (kWave - 1) / kZeroRows < STRIP && kZeroRows <= 32), "in the padding of the first strip's rows");
+    static_assert(WORDS + kZeroRows * STRIP < 4096, "twelve bits of bin");
+    const unsigned zero_bits = (unsigned)zero_word(lane, RM * RN, EARLY, COLS, STRIP) << 20 | 0x80000u;
     // elements of a strip: a lane has four consecutive columns of one row per step
     constexpr int LPR = COLS / 4, RPI = 64 / LPR, STEPS = 32 / RPI;           // lanes per row, rows per step
     const int lrow = lane / LPR, lcol = (lane % LPR) * 4;
@@ -843,7 +837,7 @@ template <int RM, int RN, int WVM, int WVN, int GPS, int NST, int PER_CU, int SR
 int launch_config(ScreenArgs& p, long batch, hipStream_t st) {
     if (!UNDERFLOW && p.eps_rel > 1.0) return launch_config<RM, RN, WVM, WVN, GPS, NST, PER_CU, SRC, EARLY, true>(p, batch, st);
     constexpr int TM = WVM * RM * 32, TN = WVN * RN * 32;
-    constexpr int lds_bytes = stage_bytes(RM, RN, WVM, WVN, GPS, NST, SRC, EARLY) + (kHistWords + spare_words(RM * RN) + (EARLY ? kEarlyWords : 0)) * 4;
+    constexpr int lds_bytes = stage_bytes(RM, RN, WVM, WVN, GPS, NST, SRC, EARLY) + words_before_stages(RM * RN, EARLY) * 4;
     auto kernel = &screen_product<RM, RN, WVM, WVN, GPS, NST, PER_CU, SRC, EARLY, UNDERFLOW>;
     static OncePerDevice configured;
     const hipError_t e = configured.run([&] {
