@@ -28,14 +28,14 @@ constexpr int kHistWords = 2048;
 // words that count errors of 0, one for each lane, so that these need no ballots (three scalar instructions and a comparison an element:
 // 8 x 8192 x 2048 over 128 234 -> 231 us).  Tiles of 64 x 64 have none and count by ballots: in all of their forms but one the
 // workgroups of a compute unit fill the LDS to its last 64 bytes (the form for few tiles has room; its workgroups check one tile or two);
-constexpr int spare_words(int blocks) { return blocks > 1 ? 64 : 0; }
+__host__ __device__ constexpr int spare_words(int blocks) { return blocks > 1 ? 64 : 0; }
 // and, in forms that try first slabs, a bit for each tile that these left open.
 constexpr int kEarlyWords = 8;
-constexpr int words_before_stages(int blocks, bool early) { return kHistWords + spare_words(blocks) + (early ? kEarlyWords : 0); }
+__host__ __device__ constexpr int words_before_stages(int blocks, bool early) { return kHistWords + spare_words(blocks) + (early ? kEarlyWords : 0); }
 // The word to which a lane adds one for an error of 0: one of these, or, where there are none, a word that nobody reads, of the padding of the
 // first strip's rows.
 constexpr int kZeroRows = 22;
-constexpr int zero_word(int lane, int blocks, bool early, int cols, int strip) {
+__host__ __device__ __forceinline__ constexpr int zero_word(int lane, int blocks, bool early, int cols, int strip) {
     return spare_words(blocks) ? kHistWords + lane : words_before_stages(blocks, early) + (lane % kZeroRows) * strip + cols + lane / kZeroRows;
 }
 
