@@ -563,6 +563,15 @@ __global__ __launch_bounds__(WVM * WVN * 64, WVM * WVN * PER_CU / 4) void screen
         for (int k = 1; k < STEPS; ++k) fetch(T, 0, k);
     };
 
+    // How many of a wavefront's first claims are further from their outputs than limit(e), of those that exist.
+    auto far_off = [&](const Tile& T, auto&& limit) __attribute__((always_inline)) -> int {
+        int n = 0;
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            n += __popcll(__ballot(srow + lrow < T.rows_left && scol + lcol + e < T.cols_left && fabsf(cv[0][e] - rv[0][e]) > limit(e)));
+        return n;
+    };
+
     // ---- first slabs by themselves.  Tiles base, base + per, ...: how many of the next `n` went this way.
     auto early_walk = [&](unsigned base, unsigned n, Tile tile) __attribute__((always_inline)) -> unsigned {
         if (ACROSS) begin(tile, slab0);
@@ -584,15 +593,13 @@ __global__ __launch_bounds__(WVM * WVN * 64, WVM * WVN * PER_CU / 4) void screen
             for (int sub = 0; sub < GPS; ++sub) compute(sums, slab0 + sub * GROUP);
             const bool large = finish_sums(tile, sums);
             first_error();
-            // Whether many of these claims would be left pending: by a lane's first four, against the largest of its first block's sums.
+            // Whether many of these claims would be left pending, by the largest of the wavefront's first block of sums.  (Where an operand has no rows
+            // the sums are of whatever its image held before.)
             float most_sum = sums.acc[0][0][0];
 #pragma unroll
             for (int v = 1; v < 16; ++v) most_sum = fmaxf(most_sum, sums.acc[0][0][v]);
             most_sum = wave_max(most_sum);
-            int above = 0;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) above += __popcll(__ballot(fabsf(cv[0][e] - rv[0][e]) > fmaf(most_sum, p.low, bl[e])));
-            if (large || above >= kWave) refused = t + 1;
+            if (large || far_off(tile, [&](int e) { return fmaf(most_sum, p.low, bl[e]); }) >= kWave) refused = t + 1;
             __syncthreads();                                 // every wavefront is done with the slab
             if (same_in_all(unordinary != 0 || refused == t + 1)) return at;
             known = max(known, newest(&largest));
@@ -693,10 +700,7 @@ __global__ __launch_bounds__(WVM * WVN * 64, WVM * WVN * PER_CU / 4) void screen
             // least that share of the output's own.  (By a wavefront's first elements, more than 5 in 8 of them.)
             begin(first, slab0);
             const float part = p.low * (float)GPS / (float)p.groups;
-            int above = 0;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) above += __popcll(__ballot(fabsf(cv[0][e] - rv[0][e]) > fabsf(rv[0][e]) * part));
-            if (above > 160 || marks != kOrdinary * 0x01010101u) unordinary = 1;
+            if (far_off(first, [&](int e) { return fabsf(rv[0][e]) * part; }) > 160 || marks != kOrdinary * 0x01010101u) unordinary = 1;
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
             __syncthreads();
             attempt = same_in_all(unordinary == 0) != 0;

@@ -76,3 +76,22 @@ def test_a_comparison_left_open_costs_a_tile_at_most(tao, form):
     t_honest, t_one, t_nan = _times([lambda: check(honest), lambda: check(one), lambda: check(nan)])
     # (measured: one at most 1.3, NaN 1.0; with the whole call formed again 2.6 to 3.3)
     assert t_one <= 1.8 * t_honest and t_nan <= 1.3 * t_honest, (form, t_one, t_nan, t_honest)
+
+
+# (a wavefront whose rows, or columns, lie beyond the operand: few 64 x 64 tiles; a tile row of 128 x 128 ones)
+@pytest.mark.parametrize("M,N,K", [(659, 448, 4096), (768, 32, 4096), (2088, 4096, 4096)])
+def test_what_lies_beyond_an_operand_costs_nothing(tao, M, N, K):
+    """An image keeps in its rows beyond the operand what was there before: a first slab decides with zeros as with other values."""
+    g = torch.Generator(device="cuda").manual_seed(7)
+    A, W = torch.randn((M, K), generator=g, device="cuda"), torch.randn((N, K), generator=g, device="cuda") * 0.02
+    y = torch.matmul(A, W.t().contiguous())
+    honest = (y.double() * (1 + 2.0 ** -23)).float()
+    out = tao.new_profile_buffer(torch.device("cuda", 0))
+    ws = torch.empty(int(tao.lib().tao_check_linear_images_workspace_bytes(M, N, K, 1)), dtype=torch.uint8, device="cuda")
+    calls = []
+    for byte in (0x00, 0x3f):
+        images = [tao.tao_split_operand(X, out=torch.full((tao.tao_split_image_bytes(X.shape[0], K),), byte, dtype=torch.uint8, device="cuda")) for X in (A, W)]
+        calls.append(lambda images=images: tao.tao_bound_check_linear_images(*images, M, N, K, y, honest, out=out, ws=ws, readback=False))
+    zeros, others = _times(calls)
+    # (measured: 1.0; where elements beyond the operand were asked about as well 2.1, 2.4 and 1.7)
+    assert zeros <= 1.25 * others, (zeros, others)
