@@ -125,11 +125,13 @@ __device__ __forceinline__ void split_pack8(const float (&v)[8], uintx4& H, uint
 // layout (K a multiple of 8, one row), and 64 bytes of zeros behind them.
 // What bounds it: HBM for large operands, else one unit's latency -- its position takes scalar 32-bit arithmetic only (a thread's own
 // 64-bit divisions, units of 256 k, which a short reduction leaves empty, and loads behind branches took 8 x 8192 x 128 19.2 us, now
-// 13.6, 1111 x 1001 5.2, now 4.2, 8 x 128 x 2048 transposed 10.3, now 8.1; 12288 x 4096 103, at 4.9 TB/s).
+// 13.6, 1111 x 1001 5.2, now 4.2, 8 x 128 x 2048 transposed 10.3, now 8.1; 12288 x 4096 103, at 4.9 TB/s, and 105 with marks, which cost 0.3 to 0.5 us
+// where one unit's latency is all there is).
 enum { STRAIGHT, TRANSPOSED, MAGNITUDES };
 struct SplitOperand {
     const float* src; long rows, K, ld, batch, stride; unsigned short* dst; int form;
     unsigned char* marks; int nmarks;  // where this operand's workgroups say that all they have read is ordinary, a byte each (linear_screen.hpp)
+    bool spread;                       // (launch_split3) units are dealt out to the workgroups' first parts, then to their second ones, and so on
     __host__ __device__ bool flat() const { return form == STRAIGHT && rows <= 16 && (K + SBK - 1) / SBK * batch >= 512; }
 };
 struct SplitOperands {
@@ -142,10 +144,18 @@ __device__ __forceinline__ void clear_words(const ClearJob& c, long i0, long ste
     for (int j = 0; j < 4; ++j)
         for (long i = i0; i < c.words[j]; i += step) static_cast<uintx4*>(c.at[j])[i] = uintx4{0, 0, 0, 0};
 }
-// A workgroup's mark, and the first one's for the places of those that there are not.
+// A workgroup's mark, and the first one's for the places of those that there are not.  (__syncthreads_and has three barriers,
+// this one: 512 x 768 3.8 -> 3.5 us.)
 __device__ __forceinline__ void leave_mark(const SplitOperand& p, long wg, long wgs, bool ordinary) {
-    const bool all = __syncthreads_and(ordinary);
-    if (threadIdx.x == 0) p.marks[wg] = all ? kOrdinary : 0;
+    __shared__ unsigned all_of_wave[16];
+    const int lane = threadIdx.x & (kWave - 1), waves = blockDim.x / kWave;
+    const unsigned all = __all(ordinary);
+    if (lane == 0) all_of_wave[threadIdx.x / kWave] = all;
+    __syncthreads();
+    if (threadIdx.x < kWave) {
+        const bool ok = __all(all_of_wave[lane < waves ? lane : 0]);
+        if (lane == 0) p.marks[wg] = ok ? kOrdinary : 0;
+    }
     if (wg == 0)
         for (long i = wgs + threadIdx.x; i < p.nmarks; i += blockDim.x) p.marks[i] = kOrdinary;
 }
@@ -160,10 +170,12 @@ __global__ __launch_bounds__(MARKED ? kMostSplitThreads : 256) void split3_bf16(
     // (both operands' fields are requested at once: the choice would be one more step of the chain of scalar loads)
     const SplitOperand &q0 = a.op[0], &q1 = a.op[1];
     const SplitOperand p = {o ? q1.src : q0.src, o ? q1.rows : q0.rows, o ? q1.K : q0.K, o ? q1.ld : q0.ld, o ? q1.batch : q0.batch,
-                            o ? q1.stride : q0.stride, o ? q1.dst : q0.dst, o ? q1.form : q0.form, o ? q1.marks : q0.marks, o ? q1.nmarks : q0.nmarks};
+                            o ? q1.stride : q0.stride, o ? q1.dst : q0.dst, o ? q1.form : q0.form, o ? q1.marks : q0.marks, o ? q1.nmarks : q0.nmarks,
+                            o ? q1.spread : q0.spread};
     const long wgs = o ? a.first[2] - a.first[1] : a.first[1], wg = o ? (long)blockIdx.x - a.first[1] : (long)blockIdx.x;
-    // 256 threads are a block of units below; a workgroup holds one or four of them
-    const long nblk = wgs * (threads >> 8), blk = wg * (threads >> 8) + (MARKED ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 8) : 0);
+    // 256 threads take a unit at a time; a workgroup holds one to four such parts
+    const long parts = threads >> 8, part = MARKED ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 8) : 0;
+    const long nblk = wgs * parts, blk = p.spread ? part * wgs + wg : wg * parts + part;
     const int tid = threadIdx.x & 255;
     bool ordinary = true;                                    // (by the sums of eight magnitudes)
     auto look = [&](float s) __attribute__((always_inline)) { if (MARKED) ordinary &= s < 0x1p32f; };
@@ -190,38 +202,74 @@ __global__ __launch_bounds__(MARKED ? kMostSplitThreads : 256) void split3_bf16(
     const unsigned units = (unsigned)(groups * (unsigned long long)rgroups * p.batch);
     const bool flat = p.flat();
     const int urow = trans ? tid & 63 : (flat ? tid & 63 : tid) >> 2, uch = trans ? tid >> 6 : tid & 3;
-    const unsigned first = flat ? (unsigned)blk * 4 + __builtin_amdgcn_readfirstlane(tid >> 6) : (unsigned)blk;
-    for (unsigned u = first; u < units; u += (unsigned)nblk * (flat ? 4 : 1)) {
+    const unsigned first = flat ? (unsigned)blk * 4 + __builtin_amdgcn_readfirstlane(tid >> 6) : (unsigned)blk, step = (unsigned)nblk * (flat ? 4 : 1);
+    struct Place { long row, k0; unsigned z, g; };
+    auto place_of = [&](unsigned u) __attribute__((always_inline)) {
         const unsigned rz = u / groups, g = u - rz * groups, z = rz / rgroups, rg = rz - z * rgroups;
-        const long row = (long)rg * 64 + urow, k0 = (long)g * SBK + uch * 8;
-        if (row >= rows4) continue;
-        const float* s = p.src + z * p.stride;
-        float v[8];
-        // (positions beyond the operand read its last row or element: loads without branches all leave at once)
-        const long rc = row < p.rows ? row : p.rows - 1;
-        if (!trans && k0 + 8 <= p.K) {
-            const floatx4u* q = reinterpret_cast<const floatx4u*>(s + rc * p.ld + k0);
+        return Place{(long)rg * 64 + urow, (long)g * SBK + uch * 8, z, g};
+    };
+    // (positions beyond the operand read its last row or element: loads without branches all leave at once)
+    auto request = [&](const Place& at, float (&v)[8]) __attribute__((always_inline)) {
+        const float* s = p.src + at.z * p.stride;
+        const long rc = at.row < p.rows ? at.row : p.rows - 1;
+        if (!trans && at.k0 + 8 <= p.K) {
+            const floatx4u* q = reinterpret_cast<const floatx4u*>(s + rc * p.ld + at.k0);
             const floatx4u x = q[0], y = q[1];
 #pragma unroll
-            for (int j = 0; j < 4; ++j) { v[j] = row < p.rows ? x[j] : 0.f; v[4 + j] = row < p.rows ? y[j] : 0.f; }
+            for (int j = 0; j < 4; ++j) { v[j] = x[j]; v[4 + j] = y[j]; }
         } else {
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
-                const long kc = k0 + j < p.K ? k0 + j : p.K - 1;
+                const long kc = at.k0 + j < p.K ? at.k0 + j : p.K - 1;
                 v[j] = trans ? s[kc * p.ld + rc] : s[rc * p.ld + kc];
             }
-#pragma unroll
-            for (int j = 0; j < 8; ++j) v[j] = row < p.rows && k0 + j < p.K ? v[j] : 0.f;
         }
+    };
+    auto store = [&](const Place& at, const float (&v)[8]) __attribute__((always_inline)) {
         uintx4 H, Mi, L;
         split_pack8(v, H, Mi, L);
         look(fabsf(v[0]) + fabsf(v[1]) + fabsf(v[2]) + fabsf(v[3]) + fabsf(v[4]) + fabsf(v[5]) + fabsf(v[6]) + fabsf(v[7]));
-        const long r = row & (STILE - 1);
+        const long r = at.row & (STILE - 1);
         const long unit = uch ^ ((r >> 2) & 3);
-        unsigned short* d = p.dst + (((long)z * groups + g) * rblocks + (row >> 7)) * (kBlock / 2) + r * (SROW / 2) + unit * 8;
+        unsigned short* d = p.dst + (((long)at.z * groups + at.g) * rblocks + (at.row >> 7)) * (kBlock / 2) + r * (SROW / 2) + unit * 8;
         *reinterpret_cast<uintx4*>(d) = H;
         *reinterpret_cast<uintx4*>(d + (kSlab / 2)) = Mi;
         *reinterpret_cast<uintx4*>(d + 2 * (kSlab / 2)) = L;
+    };
+    // A walk over whole units has the next one's values under way while it stores: a loop whose loads follow its stores waits for both
+    // (4096 x 4096 27.0 -> 26.3 us).  No access is behind a branch, so that the number of those behind a load is known.
+    if (MARKED && !trans && first + step < units && p.rows % 64 == 0 && p.K % 8 == 0) {
+        floatx4u x[2], y[2];
+        Place at[2];
+        auto ask = [&](int i, unsigned u) __attribute__((always_inline)) {
+            at[i] = place_of(min(u, units - 1));
+            const float* s = p.src + at[i].z * p.stride + at[i].row * p.ld + min(at[i].k0, p.K - 8);
+            x[i] = reinterpret_cast<const floatx4u*>(s)[0]; y[i] = reinterpret_cast<const floatx4u*>(s)[1];
+        };
+        auto put = [&](int i) __attribute__((always_inline)) {
+            const bool in = at[i].k0 < p.K;
+            float v[8];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) { v[j] = in ? x[i][j] : 0.f; v[4 + j] = in ? y[i][j] : 0.f; }
+            store(at[i], v);
+        };
+        ask(0, first);
+        for (unsigned u = first;;) {
+            u += step; ask(1, u); put(0);
+            if (u >= units) break;
+            u += step; ask(0, u); put(1);
+            if (u >= units) break;
+        }
+    } else {
+        for (unsigned u = first; u < units; u += step) {
+            const Place at = place_of(u);
+            if (at.row >= rows4) continue;
+            float v[8];
+            request(at, v);
+#pragma unroll
+            for (int j = 0; j < 8; ++j) v[j] = at.row < p.rows && at.k0 + j < p.K ? v[j] : 0.f;
+            store(at, v);
+        }
     }
     if (MARKED) leave_mark(p, wg, wgs, ordinary);
 }
@@ -1364,27 +1412,33 @@ struct SplitCheckHost {
     const float* claimed; const float* ref; long ldy, strideY; double alpha, eps_rel; tao_profile* out;
 };
 
+// What 256 threads of split3_bf16 take at a time.
+static long split_blocks(const SplitOperand& p) {
+    const long units = (p.K + SBK - 1) / SBK * ((p.rows + 63) / 64) * p.batch;
+    return p.form == MAGNITUDES ? (p.K / 8 + 4 + 255) / 256 : p.flat() ? (units + 3) / 4 : units;
+}
 // Launches split3_bf16 for one or two operands: src [batch][rows][K] with row stride ld (STRAIGHT) or
 // [batch][K][rows] (TRANSPOSED) -> image.  clear: the side job described at the kernel.
+// A workgroup that leaves a mark: as many as there are marks, two to a compute unit, of as many parts of 256 threads as give every unit one, up to four.
+// Dealt out to the workgroups' first parts, then to their second ones, the last units find all compute units (us on the device; a quarter of the
+// workgroups, of 1024 threads, as soon as the marks were too few / so / without marks: 1111 x 1001, 576 units, 5.5 / 4.9 / 4.5, 3072 x 768 7.3 / 6.2 / 5.7,
+// 1500 x 1500 7.5 / 6.5 / 6.0).  A walk of several rounds keeps neighbouring units together (12288 x 4096 105, dealt out 112).
 static void launch_split3(const SplitOperand* ops, int n, const ClearJob& clear, hipStream_t st) {
     SplitOperands a = {};
     a.clear = clear;
-    auto blocks = [](const SplitOperand& p) {
-        const long units = (p.K + SBK - 1) / SBK * ((p.rows + 63) / 64) * p.batch;
-        return p.form == MAGNITUDES ? (p.K / 8 + 4 + 255) / 256 : p.flat() ? (units + 3) / 4 : units;
-    };
-    // A mark for every workgroup, so there are as many as marks at most; of 1024 threads where 256 would be too few.
     const bool marked = ops[0].nmarks > 0;
-    bool wide = false;
-    for (int o = 0; o < n; ++o) wide |= marked && blocks(ops[o]) > ops[o].nmarks;
-    long first = 0;
+    long parts = 1, first = 0;
+    for (int o = 0; o < n && marked; ++o) parts = std::max(parts, (split_blocks(ops[o]) + ops[o].nmarks - 1) / ops[o].nmarks);
+    parts = std::min(parts, (long)kMostSplitThreads / 256);
     for (int o = 0; o < n; ++o) {
+        const long blocks = split_blocks(ops[o]), wgs = std::clamp(blocks, 1L, marked ? (long)ops[o].nmarks : 256L * 64);
         a.op[o] = ops[o];
+        a.op[o].spread = blocks <= wgs * parts;
         a.first[o] = first;
-        first += std::clamp(wide ? (blocks(ops[o]) + 3) / 4 : blocks(ops[o]), 1L, marked ? (long)ops[o].nmarks : 256L * 64);
+        first += wgs;
     }
     for (int o = n; o < 3; ++o) a.first[o] = first;
-    if (marked) hipLaunchKernelGGL(split3_bf16<true>, dim3((unsigned)first), dim3(wide ? kMostSplitThreads : 256), 0, st, a);
+    if (marked) hipLaunchKernelGGL(split3_bf16<true>, dim3((unsigned)first), dim3((unsigned)parts * 256), 0, st, a);
     else        hipLaunchKernelGGL(split3_bf16<false>, dim3((unsigned)first), dim3(256), 0, st, a);
 }
 

@@ -151,3 +151,32 @@ def test_images_of_few_rows(tao, rows, batch, K):
         n = batch * ((K + 31) // 32) * 3 * 128 * 64
         images.append(tao.tao_split_operand(x, out=out)[:n].view(-1, 128, 64)[:, :(rows + 3) // 4 * 4])
     assert torch.equal(*images)
+
+
+# units of 64 rows x 32 k: a workgroup of one, two, three and four parts, some units to spare, and walks of two to five rounds of whole units and of cut ones
+@pytest.mark.parametrize("rows,K,batch,trans", [(1000, 1001, 1, False), (1100, 1000, 1, False), (1500, 1500, 1, False), (1500, 1500, 1, True), (960, 1920, 2, False), (2176, 2056, 1, False),
+                                                (2100, 2056, 1, False), (2176, 2055, 1, False), (2176, 2056, 1, True), (4352, 4096, 1, False), (320, 40, 450, False), (15, 2300 * 32, 1, False)])
+def test_images_of_many_units(tao, rows, K, batch, trans):
+    """Every element's pieces add up to it, whichever part of a workgroup has cut it, and each large one is told by the marks behind the image."""
+    g = torch.Generator(device="cuda").manual_seed(rows + K)
+    x = torch.randn((batch, rows, K), generator=g, device="cuda")
+    groups, blocks = (K + 31) // 32, (rows + 127) // 128
+    size = batch * groups * blocks * 3 * 128 * 64
+    r, k = torch.arange(128, device="cuda"), torch.arange(32, device="cuda")
+    at = ((k[None] // 8) ^ ((r[:, None] >> 2) & 3)) * 8 + k[None] % 8
+    for where in (None, (0, 0, 0), (-1, -1, -1), (batch // 2, rows // 2, K // 3)):
+        if where:
+            x[where] = -2.0 ** 33
+        out = torch.full((tao.tao_split_image_bytes(rows, K, batch),), 0x5a, dtype=torch.uint8, device="cuda")
+        src = x.transpose(1, 2).contiguous() if trans else x
+        tao.tao_split_operand(src if batch > 1 else src[0], trans=trans, out=out)
+        image = out[:size].view(torch.bfloat16).view(batch, groups, blocks, 3, 128, 32)
+        for z in range(0, batch, 64):
+            part = image[z:z + 64].float().sum(3)            # (24 bits in three pieces: exact in any order)
+            part = part.gather(-1, at.expand(part.shape)).permute(0, 2, 3, 1, 4).reshape(part.shape[0], blocks * 128, groups * 32)
+            assert torch.equal(part[:, :rows, :K], x[z:z + 64].abs()), (where, z)
+            assert not part[:, :rows, K:].any() and not part[:, rows:(rows + 3) // 4 * 4].any()
+        marks = out[size:size + 512]
+        assert bool((marks == 0xa5).all()) == (where is None) and set(marks.unique().tolist()) <= {0, 0xa5}, where
+        if where:
+            x[where] = 1.0

@@ -1,0 +1,25 @@
+"""How an operand is dealt out to the workgroups that cut it, by the launch: each leaves a mark, of which there are 512, and few of them leave the chip idle."""
+import launches
+
+CUT = r"""
+result = []
+P = address(1 << 20)
+for rows, K, trans, batch in ((64, 32, 0, 1), (64, 512 * 32, 0, 1), (64, 513 * 32, 0, 1), (739, 739, 0, 2), (600, 1700, 1, 1), (1500, 1500, 0, 1), (3072, 768, 0, 1),
+                              (1111, 1001, 0, 1), (4096, 1024, 0, 1), (4096, 1056, 0, 1), (12288, 4096, 0, 1), (8, 4 * 513 * 32, 0, 1), (64, 64, 0, 3000)):
+    assert lib.tao_split_operand(P, rows, K, rows if trans else K, trans, batch, rows * K, P, 1 << 40, None) == 0
+    (kernel, grid, block, _), = launched()
+    units = (K + 31) // 32 * ((rows + 63) // 64) * batch
+    result.append((kernel, rows, K, batch, units, grid, block))
+"""
+
+
+def test_an_operand_is_cut_on_all_of_the_chip(tmp_path):
+    found = launches.run(CUT, tmp_path)
+    assert len(found) == 13
+    for kernel, rows, K, batch, units, grid, block in found:
+        case = (rows, K, batch, units, grid, block)
+        assert kernel.startswith("split3_bf16") and 1 <= grid <= 512 and block in (256, 512, 768, 1024), case
+        if rows <= 16:                                       # (a wavefront to a unit)
+            units = (units + 3) // 4
+        assert grid == min(units, 512), case                 # two workgroups to a compute unit as soon as there are units for them
+        assert block // 256 == min(4, -(-units // 512)), case        # and no more threads in each than units ask for
