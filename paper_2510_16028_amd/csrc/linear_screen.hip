@@ -222,7 +222,8 @@ __global__ __launch_bounds__(WVM * WVN * 64, WVM * WVN * PER_CU / 4) void screen
         } else {
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                const unsigned at = (unsigned)(row + min(col + e, T.cols_left - 1));
+                unsigned at = (unsigned)(row + min(col + e, T.cols_left - 1));
+                asm volatile("" : "+v"(at));                 // (the last two are the same: copied they were waited for, 1536 x 5119 over 512 28.0 -> 24.3 us)
                 cv[k][e] = T.C[at]; rv[k][e] = T.Y[at];
             }
         }
@@ -563,13 +564,14 @@ __global__ __launch_bounds__(WVM * WVN * 64, WVM * WVN * PER_CU / 4) void screen
         for (int k = 1; k < STEPS; ++k) fetch(T, 0, k);
     };
 
-    // How many of a wavefront's first claims are further from their outputs than limit(e), of those that exist.
-    auto far_off = [&](const Tile& T, auto&& limit) __attribute__((always_inline)) -> int {
+    // Whether, of a wavefront's first claims, `part` eighths of those that exist or more are further from their outputs than limit(e).
+    auto far_off = [&](const Tile& T, int part, auto&& limit) __attribute__((always_inline)) -> bool {
+        const int there = max(0, min(RPI, T.rows_left - srow)) * max(0, min(COLS, T.cols_left - scol));
         int n = 0;
 #pragma unroll
         for (int e = 0; e < 4; ++e)
             n += __popcll(__ballot(srow + lrow < T.rows_left && scol + lcol + e < T.cols_left && fabsf(cv[0][e] - rv[0][e]) > limit(e)));
-        return n;
+        return there && n * 8 >= there * part;
     };
 
     // ---- first slabs by themselves.  Tiles base, base + per, ...: how many of the next `n` went this way.
@@ -593,13 +595,14 @@ __global__ __launch_bounds__(WVM * WVN * 64, WVM * WVN * PER_CU / 4) void screen
             for (int sub = 0; sub < GPS; ++sub) compute(sums, slab0 + sub * GROUP);
             const bool large = finish_sums(tile, sums);
             first_error();
-            // Whether many of these claims would be left pending, by the largest of the wavefront's first block of sums.  (Where an operand has no rows
-            // the sums are of whatever its image held before.)
-            float most_sum = sums.acc[0][0][0];
+            // Whether many of these claims would be left pending, by the largest of the wavefront's first block of sums, of those that exist.
+            // (Where an operand has no rows they are of whatever its image held before.)
+            float most_sum = 0.f;
+            const int cols_there = srow + r32 < tile.rows_left ? tile.cols_left - scol - 4 * h : 0;
 #pragma unroll
-            for (int v = 1; v < 16; ++v) most_sum = fmaxf(most_sum, sums.acc[0][0][v]);
+            for (int v = 0; v < 16; ++v) most_sum = fmaxf(most_sum, v / 4 * 8 + v % 4 < cols_there ? sums.acc[0][0][v] : 0.f);
             most_sum = wave_max(most_sum);
-            if (large || far_off(tile, [&](int e) { return fmaf(most_sum, p.low, bl[e]); }) >= kWave) refused = t + 1;
+            if (large || far_off(tile, 2, [&](int e) { return fmaf(most_sum, p.low, bl[e]); })) refused = t + 1;
             __syncthreads();                                 // every wavefront is done with the slab
             if (same_in_all(unordinary != 0 || refused == t + 1)) return at;
             known = max(known, newest(&largest));
@@ -697,10 +700,10 @@ __global__ __launch_bounds__(WVM * WVN * 64, WVM * WVN * PER_CU / 4) void screen
         bool attempt = true;
         if (!ACROSS) {
             // First slabs are not tried where claims are far off from the start: an error of the share of the bound that they would prove is at
-            // least that share of the output's own.  (By a wavefront's first elements, more than 5 in 8 of them.)
+            // least that share of the output's own.  (By a wavefront's first elements, 5 in 8 of them.)
             begin(first, slab0);
             const float part = p.low * (float)GPS / (float)p.groups;
-            if (far_off(first, [&](int e) { return fabsf(rv[0][e]) * part; }) > 160 || marks != kOrdinary * 0x01010101u) unordinary = 1;
+            if (far_off(first, 5, [&](int e) { return fabsf(rv[0][e]) * part; }) || marks != kOrdinary * 0x01010101u) unordinary = 1;
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
             __syncthreads();
             attempt = same_in_all(unordinary == 0) != 0;

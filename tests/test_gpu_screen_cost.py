@@ -95,3 +95,21 @@ def test_what_lies_beyond_an_operand_costs_nothing(tao, M, N, K):
     zeros, others = _times(calls)
     # (measured: 1.0; where elements beyond the operand were asked about as well 2.1, 2.4 and 1.7)
     assert zeros <= 1.25 * others, (zeros, others)
+
+
+def test_a_ragged_edge_costs_little(tao):
+    """A last tile of eight columns: far-off claims are found by the sums of those, and the rest of a row's vector is not waited for."""
+    M, K = 1536, 512
+    g = torch.Generator(device="cuda").manual_seed(8)
+    calls = []
+    for N, byte in ((5120, 0x3f), (5000, 0x00), (5000, 0x3f)):
+        A, W = torch.randn((M, K), generator=g, device="cuda"), torch.randn((N, K), generator=g, device="cuda") * 0.02
+        y = torch.matmul(A, W.t().contiguous())
+        claimed = (y.double() + 0.5 * tao.tao_bound_linear_split(A, W).double()).float()
+        images = [tao.tao_split_operand(X, out=torch.full((tao.tao_split_image_bytes(X.shape[0], K),), byte, dtype=torch.uint8, device="cuda")) for X in (A, W)]
+        out = tao.new_profile_buffer(torch.device("cuda", 0))
+        ws = torch.empty(int(tao.lib().tao_check_linear_images_workspace_bytes(M, N, K, 1)), dtype=torch.uint8, device="cuda")
+        calls.append(lambda a=images, n=N, y=y, c=claimed, o=out, w=ws: tao.tao_bound_check_linear_images(*a, M, n, K, y, c, out=o, ws=w, readback=False))
+    whole, *ragged = _times(calls)
+    # (measured: 1.04; by whatever an image holds beyond the operand, and with a wait for each row's last vector, 1.34)
+    assert max(ragged) <= 1.18 * whole, (ragged, whole)
