@@ -8,8 +8,14 @@ from test_gpu_screen import _same, tao  # noqa: F401
 
 pytestmark = pytest.mark.gpu
 
-# (64 x 64 tiles, few; 128 x 128: a tile for a workgroup, two and three, with edges; reductions of one slab and of a little more)
-SHAPES = [(1, 300, 200, 2080), (3, 130, 131, 140), (1, 130, 131, 128), (1, 2050, 2052, 288), (1, 2850, 3061, 300), (1, 4200, 4100, 264), (2, 2100, 2060, 1100)]
+# Products by the form that checks them.  Few 64 x 64 tiles: reductions of more than twelve groups of 32 k, of three to five slabs and their remainders,
+# tiles of one row and of one column.  128 x 128: a tile for a workgroup, two and three, with edges; whole slabs and remainders.
+FEW, SHORT, LARGE, NARROW = "1, 1, 2, 2, 4, 2, 2, 0, true", "1, 1, 2, 2, 4, 2, 2, 0, false", "2, 2, 2, 2, 2, 2, 2, 0, true", "1, 2, 2, 2, 1, 3, 3, 0, false"
+SHAPES = {FEW: [(1, 300, 200, 2080), (3, 65, 129, 385), (1, 65, 129, 416), (1, 192, 128, 417), (2, 257, 65, 448), (1, 130, 131, 512), (1, 1, 640, 500), (1, 640, 1, 640)],
+          SHORT: [(3, 65, 129, 384), (1, 130, 131, 128)],
+          LARGE: [(1, 2850, 3061, 300), (1, 4200, 4100, 264), (2, 2100, 2060, 1100), (1, 2050, 2052, 288), (1, 2100, 4004, 320)],
+          NARROW: [(1, 2050, 2052, 256)]}
+ALL_SHAPES = [shape for shapes in SHAPES.values() for shape in shapes]
 
 
 def _claims(y, tau, g):
@@ -29,7 +35,7 @@ def _claims(y, tau, g):
                 beyond=torch.where(u < 1e-3, (y.double() + 2 * tau.double()).float(), honest), infinite=torch.where(u < 1e-3, float("inf"), honest))
 
 
-@pytest.mark.parametrize("batch,M,N,K", SHAPES)
+@pytest.mark.parametrize("batch,M,N,K", ALL_SHAPES)
 def test_claims(tao, batch, M, N, K):  # noqa: F811
     g = torch.Generator(device="cuda").manual_seed(M + K)
     shape = (batch,) if batch > 1 else ()
@@ -67,7 +73,7 @@ def test_claims_of_a_convolution(tao, B, H, C, Co, R, pad, st):  # noqa: F811
         _same(tao.tao_bound_check_conv2d(x2, w, None, y, c, st, pad), tao.tao_check_and_profile(c, y, tau))
 
 
-@pytest.mark.parametrize("M,N,K", [(300, 200, 2080), (2850, 3061, 300), (600, 9000, 1100)])
+@pytest.mark.parametrize("M,N,K", [(300, 200, 2080), (2850, 3061, 300), (600, 9000, 1100), (1500, 700, 1500), (65, 129, 417)])
 def test_operands_behind_the_first_slab(tao, M, N, K):  # noqa: F811
     g = torch.Generator(device="cuda").manual_seed(K)
     A0, W0 = torch.randn((M, K), generator=g, device="cuda"), torch.randn((N, K), generator=g, device="cuda")
