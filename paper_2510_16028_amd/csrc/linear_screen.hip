@@ -862,7 +862,7 @@ int launch_config(ScreenArgs& p, long batch, hipStream_t st) {
     return launch_status();
 }
 
-enum Config { kRows64x128, kRows64x64, kPixels128x128, kPixels64x64, kImages64x128, kImages128x128, kImages64x64Few, kImages64x64Short, kImages64x64 };
+enum Config { kRows64x128, kRows64x64, kPixels128x128, kPixels128x128Short, kPixels64x64, kImages64x128, kImages128x128, kImages64x64Few, kImages64x64Short, kImages64x64 };
 // Tiles of 128 x 128, two workgroups to a compute unit, where they give every compute unit one (us of the whole call on images, with
 // them / with 64 x 64: 2048 x 12288 over 4096 248 / 362, 2048 x 4096 over 4096 94 / 122, 1111 x 3001 over 1001, 216 tiles, 37 / 33);
 // up to 256 k, where the check is most of the work, 64 x 128 and three (8 x 8192 x 2048 over 128 250, with 128 x 128 280; 228 now).
@@ -871,6 +871,8 @@ enum Config { kRows64x128, kRows64x64, kPixels128x128, kPixels64x64, kImages64x1
 // 768 21, with a group to a barrier 24, with 128 x 128 31; 512 x 768 over 3072 29 / 37 / 57; 256 x 1024 over 8192 51 / 71 / 110).
 // Few 64 x 64 tiles try first slabs, of 128 k, where there are four or more (512 x 768 over 416 18.2 -> 17.6, 300 x 300 over 1000 19.3 -> 15.9; with
 // two, 912 x 64 over 228, the screen alone 9.2 -> 11.3).
+// Convolutions of one slab, 64 k, have no first one to try: the form that does not has fewer registers to keep (1 x 1, 32 x 28 x 28 x 64 to 512, with its
+// affine operator, 97.5 -> 94.9; of 96 channels 97.0 without, 96.7 with).
 // A read as rows: 64 x 128 where they fill the chip (8 x 8192 x 128 over 2048 145, with 64 x 64 183), else 64 x 64 (12 x 512 x 64 over
 // 512 22 / 26).
 Config screen_config(long M, long N, long K, long batch, bool rows, bool pixels) {
@@ -878,7 +880,7 @@ Config screen_config(long M, long N, long K, long batch, bool rows, bool pixels)
     const long t128 = ((M + 127) / 128) * ((N + 127) / 128) * batch, t64 = ((M + 63) / 64) * ((N + 63) / 64) * batch;
     const bool wide = t128 >= n && N > 64;
     if (rows) return ((M + 63) / 64) * ((N + 127) / 128) * batch >= n && N > 64 ? kRows64x128 : kRows64x64;
-    if (pixels) return wide ? kPixels128x128 : kPixels64x64;
+    if (pixels) return !wide ? kPixels64x64 : groups > 2 ? kPixels128x128 : kPixels128x128Short;
     if (wide) return groups <= 8 ? kImages64x128 : kImages128x128;
     return t64 > 2 * n ? kImages64x64 : groups > 12 ? kImages64x64Few : kImages64x64Short;
 }
@@ -919,6 +921,7 @@ int launch_screen(const ScreenOperand& A, const ScreenOperand& W, const float* b
         case kRows64x128:     return launch_config<1, 2, 2, 2, 1, 4, 2, ROWS, false>(p, batch, st);
         case kRows64x64:      return launch_config<1, 1, 2, 2, 2, 3, 2, ROWS, false>(p, batch, st);
         case kPixels128x128:  return launch_config<2, 2, 2, 2, 2, 2, 2, PIXELS, true>(p, batch, st);
+        case kPixels128x128Short: return launch_config<2, 2, 2, 2, 2, 2, 2, PIXELS, false>(p, batch, st);
         case kPixels64x64:    return launch_config<1, 1, 2, 2, 2, 2, 4, PIXELS, false>(p, batch, st);
         case kImages64x128:   return launch_config<1, 2, 2, 2, 1, 3, 3, IMAGE, false>(p, batch, st);
         case kImages128x128:  return launch_config<2, 2, 2, 2, 2, 2, 2, IMAGE, true>(p, batch, st);

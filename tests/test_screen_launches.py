@@ -28,3 +28,19 @@ def test_every_shape_reaches_its_form(tmp_path):
         elif screen:                                         # (or binary32 rows, and products that are not screened)
             tries = screen[0].split("<")[1].split(", ")[8]
             assert len(cut) == 1 and cut[0] == "split3_bf16<" + tries, case
+
+
+CONVOLUTIONS = r"""
+P = address(1 << 20)
+result = []
+for C, R in ((32, 1), (64, 1), (96, 1), (128, 1), (32, 3)):
+    assert lib.tao_bound_check_conv2d(P, P, None, P, P, None, 32, 28, 28, C, 512, R, R, 1, 1, R // 2, R // 2, 1, 1, 1.0, 1e-12, None, P, P, 1 << 40, None) == 0
+    result.append((C * R * R, [l[0] for l in launched()]))
+"""
+
+
+def test_a_convolution_of_one_slab_tries_none(tmp_path):
+    for K, kernels in launches.run(CONVOLUTIONS, tmp_path):
+        tries = "true" if K > 64 else "false"
+        assert [k for k in kernels if k.startswith("split3_bf16<")] == ["split3_bf16<" + tries], (K, kernels)
+        assert [k.split("<")[1].split(", ")[8] for k in kernels if k.startswith("screen_product<2, 2, 2, 2, 2, 2, 2, 2, ")] == [tries], (K, kernels)
