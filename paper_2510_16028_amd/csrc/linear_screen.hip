@@ -19,13 +19,16 @@
 // non-finite operand or a bias beyond 2^60: a record per tile of the exact route (OpenRecords) keeps their places, and that route,
 // enqueued behind the screen, decides these and nothing else.  So every profile is the exact route's, bit for bit.
 // Part of the products is enough for most claims: their terms are not negative, so the sum over any k is a lower limit of the sum over all, and
-//     d <= alpha cg (P' lower + |b|),   P' over the first 32 to 128 k,
+//     d <= alpha cg (P' lower + |b|),   P' over the first 64 or 128 k,
 // proves that there is no violation, whatever the rest -- but for operands that are infinite or NaN, so this way is taken only where the
 // operands' marks say that all of both is ordinary (linear_screen.hpp).  Honest claims lie a thousand times below their bounds and are decided
 // so; a tile with a claim that is not takes all products afterwards.  What bounds it then is the traffic of claims and outputs, not
 // of operands (us of the whole call on images, all products / first slabs: 2048 x 12288 over 4096 235 -> 47, 201 MB at 4.3 TB/s; 2048 x 4096 over 1024 39 -> 24;
-// 512 x 768 over 3072 26 -> 13; the 3 x 3 convolution of 32 x 56 x 56 x 256 203 -> 87).  The cost where it decides nothing: 3 us of a tile's time
-// (claims at 0.5 to 1.1 times their bounds: 2048 x 4096 over 1024 41.5 -> 44.3, 512 x 3072 over 768 18.9 -> 20.4, 2048 x 12288 over 4096 240 -> 241).
+// 512 x 768 over 3072 26 -> 13; the 3 x 3 convolution of 32 x 56 x 56 x 256 203 -> 87).  The cost where it decides nothing: 1 us of a workgroup's time
+// with tiles of 64 x 64, 3 with 128 x 128 (claims at 0.5 to 1.1 times their bounds, with the cut of A: 300 x 300 over 448 17.5 -> 18.5, 512 x 3072 over 768
+// 22.0 -> 23.5, 2048 x 4096 over 1024 47.5 -> 50.2, 2048 x 12288 over 4096 the same within the spread).  A far-off claim that is found as a tile's first
+// ones ends the first slabs of its workgroup: a proposer who spoils a corner of an output takes the gain from the later tiles of some workgroups,
+// and no call takes longer than that.
 // The errors' bins and maximum do not depend on tau: quick settlement as in tao_check.hpp, exact arithmetic where
 // an estimate does not decide.
 // A workgroup forms no further products and leaves all comparisons open once all of its wavefronts have found much open in a tile, or some
@@ -97,9 +100,6 @@ __device__ __forceinline__ void wait_for_copies(int behind) {
     }
 }
 
-// EARLY: a workgroup first walks its tiles with one slab of products each, requested while the tile before is checked (early_walk); what that
-// does not decide it walks again, with all products.  Errors are settled in the first walk.
-//
 // WVM x WVN wavefronts of RM x RN accumulator tiles of 32 x 32.  A stage holds a group of 32 k of the tile's operands as the images
 // hold them (ROWS: of A the binary32 values, cut when a fragment is read; PIXELS: gathered from BF16 magnitudes of the input,
 // taps in the padding from a line of zeros), GPS times; NST stages filled by 16-byte copies that go to LDS directly, requested
@@ -115,10 +115,11 @@ __device__ __forceinline__ void wait_for_copies(int behind) {
 // that could go without it have an instantiation for either.
 //
 // EARLY: a workgroup walks its tiles with one slab of products each, requested while the tile before is checked (early_walk), up to one whose first
-// claims are far off or whose sums they exceed in numbers; from there on with all products; and then those of the first walk that
-// are not decided once more, with all products and without the errors, which are settled.
+// claims exceed what the sums prove in numbers; from there on with all products; and then those of the first walk that
+// are not decided once more, with all products and without the errors, which are settled.  Workgroups of 64 x 64 tiles, which have one each, or two, try
+// the first one, unless its claims are far off by the size of the outputs.
 //
-// Forms that do so: 128 x 128, and few 64 x 64 tiles of more than a slab.  Not: 64 x 128 tiles of up to 256 k, whose time is the check's (8 x 8192 x 2048 over 128 231 -> 240 us, 22 spilled
+// Forms that do so: 128 x 128, and few 64 x 64 tiles.  Not: 64 x 128 tiles of up to 256 k, whose time is the check's (8 x 8192 x 2048 over 128 231 -> 240 us, 22 spilled
 // registers), 64 x 64 with four workgroups to a compute unit (128 registers: 19 spilled; 1111 x 3001 over 1001 40.7 -> 50.7), and rows, which are
 // read whole in any case.
 // Bytes behind the histogram: the stages, or the strips of sums with the slab that is requested under them.
@@ -144,7 +145,8 @@ __global__ __launch_bounds__(WVM * WVN * 64, WVM * WVN * PER_CU / 4) void screen
     // Both halves of a group are read before its two products where the registers allow it: the wait for the second then passes under the
     // first product (64 x 200 over 8192 52.0 -> 46.0 us, 512 x 768 over 3072 28.4 -> 26.6).
     constexpr bool AHEAD = RM * RN == 1 && PER_CU == 2 && SRC == IMAGE;
-    static_assert(!EARLY || THREADS >= kMarks / 2, "a thread for four marks");
+    static_assert(!EARLY || THREADS == kMarks / 2, "a thread for four marks");
+    static_assert(!EARLY || ACROSS || (NST == 2 && WAVES * 32 * STRIP * 4 <= STAGE), "a second slab beside the strips");
     extern __shared__ __attribute__((aligned(16))) char lds[];
     unsigned int* const hist = reinterpret_cast<unsigned int*>(lds);
     constexpr int WORDS = words_before_stages(RM * RN, EARLY);
@@ -152,18 +154,19 @@ __global__ __launch_bounds__(WVM * WVN * 64, WVM * WVN * PER_CU / 4) void screen
     char* const stages = lds + WORDS * 4;
     char* const slab0 = stages + (ACROSS ? WAVES * 32 * STRIP * 4 : 0);        // a first slab's place (ACROSS: behind the strips)
     unsigned int& largest = hist[2041];                      // a lower bound of an error that occurs (its bits)
-    volatile unsigned int& large_in = hist[2042];            // 1 + the last tile with an operand that is not screened
+    unsigned int& large_in = hist[2042];                     // 1 + the last tile with an operand that is not screened
     unsigned int& heavy = hist[2043];                        // wavefronts that had to leave whole blocks open
-    volatile unsigned int& refused = hist[2044];             // 1 + the last tile of which the first slab would not decide much
-    volatile unsigned int& unordinary = hist[2045];          // an operand may not be ordinary, or the first claims are far off
-    volatile unsigned int& some_pending = hist[2046];        // whether any of `pending` is set
+    unsigned int& refused = hist[2044];                      // 1 + the last tile of which the first slab would not decide much
+    unsigned int& unordinary = hist[2045];                   // an operand may not be ordinary, or the first claims are far off
+    unsigned int& some_pending = hist[2046];                 // whether any of `pending` is set
+    auto now = [](unsigned int& word) __attribute__((always_inline)) { return same_in_all(newest(&word)); };        // (behind a barrier)
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave / WVN, wn = wave % WVN;
     const int r32 = lane & 31, h = lane >> 5;
     for (int i = tid; i < WORDS / 4; i += THREADS) reinterpret_cast<uintx4*>(hist)[i] = uintx4{0, 0, 0, 0};
     unsigned marks = kOrdinary * 0x01010101u;
-    if (EARLY && tid < kMarks / 2) marks = (tid < kMarks / 4 ? p.marksA : p.marksW)[tid % (kMarks / 4)];
+    if (EARLY) marks = (tid < kMarks / 4 ? p.marksA : p.marksW)[tid % (kMarks / 4)];        // (all lanes: behind a branch it would be waited for here)
 
     // fragments: lane (r32, h) holds k = 16 kg + 8 h .. + 7 of its row.  The first k half a wavefront takes is (wm ^ wn) & 1, so that
     // the first halves of all wavefronts cover every operand value of the tile: only those are looked at for large ones.
@@ -309,20 +312,6 @@ __global__ __launch_bounds__(WVM * WVN * 64, WVM * WVN * PER_CU / 4) void screen
             if (SRC == PIXELS && (GPS == 1 || on)) next_tap(s);
         }
     };
-    // The same without the copies.
-    auto skip = [&](Sources& s) __attribute__((always_inline)) {
-#pragma unroll
-        for (int sub = 0; sub < GPS; ++sub) {
-            const bool on = --s.left > 0;
-#pragma unroll
-            for (int i = 0; i < NA; ++i)
-                if (SRC != PIXELS) s.A[i] += GPS == 1 || on ? p.stepA : 0;
-#pragma unroll
-            for (int i = 0; i < NW; ++i) s.W[i] += GPS == 1 || on ? p.stepW : 0;
-            if (SRC == PIXELS && (GPS == 1 || on)) next_tap(s);
-        }
-    };
-
     // The sums, and the largest operands that went into them (packed, of a fragment's even and odd values).
     struct Sums { floatx16 acc[RM][RN], more; ushortx2 mostA[RM], mostW[RN]; };
     auto clear_sums = [&](Sums& s) __attribute__((always_inline)) {
@@ -554,12 +543,14 @@ __global__ __launch_bounds__(WVM * WVN * 64, WVM * WVN * PER_CU / 4) void screen
     };
 
     // The first requests of a tile.  (The first step's claims go ahead: what waits for these does not wait for all of the chip's first tiles.)
-    auto begin = [&](const Tile& T, const char* stage) __attribute__((always_inline)) {
+    // Where a workgroup tries one tile only, the second slab is requested as well, for claims that turn out to be far off: what has been learnt of the
+    // tile is then kept (300 x 300 over 448, the screen alone, 12.3 -> 11.5 us).  Where they do not its copies land beside the strips, unread.
+    auto begin = [&](const Tile& T, Sources& src) __attribute__((always_inline)) {
         fetch(T, 0, 0);
         asm volatile("" ::: "memory");
-        Sources src;
         sources_of(T, src);
-        request(src, stage);
+        request(src, slab0);
+        if (!ACROSS) request(src, stages + STAGE);
 #pragma unroll
         for (int k = 1; k < STEPS; ++k) fetch(T, 0, k);
     };
@@ -576,15 +567,12 @@ __global__ __launch_bounds__(WVM * WVN * 64, WVM * WVN * PER_CU / 4) void screen
 
     // ---- first slabs by themselves.  Tiles base, base + per, ...: how many of the next `n` went this way.
     auto early_walk = [&](unsigned base, unsigned n, Tile tile) __attribute__((always_inline)) -> unsigned {
-        if (ACROSS) begin(tile, slab0);
+        if (ACROSS) {
+            Sources src;
+            begin(tile, src);
+        }
         for (unsigned at = 0;; ++at) {
             const unsigned t = base + at * per;
-            if (!ACROSS && at) {
-                tile = tile_of(t);
-                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-                __syncthreads();                             // the strips of the tile before have been read
-                begin(tile, slab0);
-            }
             // the copies are older than the claims and outputs behind the first step's (two loads a step at least), which stay on their way
             asm volatile("s_waitcnt vmcnt(%0)" :: "n"(2 * (STEPS - 1)) : "memory");
             if (ACROSS && marks != kOrdinary * 0x01010101u) unordinary = 1;
@@ -604,9 +592,9 @@ __global__ __launch_bounds__(WVM * WVN * 64, WVM * WVN * PER_CU / 4) void screen
             most_sum = wave_max(most_sum);
             if (large || far_off(tile, 2, [&](int e) { return fmaf(most_sum, p.low, bl[e]); })) refused = t + 1;
             __syncthreads();                                 // every wavefront is done with the slab
-            if (same_in_all(unordinary != 0 || refused == t + 1)) return at;
+            if (now(unordinary) != 0 || now(refused) == t + 1) return at;
             known = max(known, newest(&largest));
-            const bool last = at + 1 == n;
+            const bool last = !ACROSS || at + 1 == n;
             const Tile next = ACROSS ? tile_of(last ? t : t + per) : tile;
             Places open = 0;
             check_tile(tile, sums, INFINITY, open,
@@ -623,11 +611,11 @@ __global__ __launch_bounds__(WVM * WVN * 64, WVM * WVN * PER_CU / 4) void screen
                        });
             if (__any(open != 0) && lane == 0) { atomicOr(&pending[at / 32], 1u << (at & 31)); some_pending = 1; }
             if (last) return n;
-            if (ACROSS) tile = next;
+            tile = next;
         }
     };
 
-    // All products of a tile.
+    // All products of a tile (begun: its first two slabs are under way).
     auto product = [&](Sources& src, Sums& sums, bool begun) __attribute__((always_inline)) {
         constexpr int COPIES = GPS * (NA + NW);
         const int slabs = (groups + GPS - 1) / GPS;
@@ -641,7 +629,7 @@ __global__ __launch_bounds__(WVM * WVN * 64, WVM * WVN * PER_CU / 4) void screen
             // separates the last reads of the stage before from its next fill
             wait_for_copies<COPIES, NST - 2>(slabs - 1 - g);
             __syncthreads();
-            if (g + NST - 1 < slabs) request(src, stages + (cur == 0 ? NST - 1 : cur - 1) * STAGE);
+            if (g + NST - 1 < slabs && !(begun && g == 0)) request(src, stages + (cur == 0 ? NST - 1 : cur - 1) * STAGE);
             compute(sums, stages + cur * STAGE);
 #pragma unroll
             for (int sub = 1; sub < GPS; ++sub)
@@ -654,7 +642,7 @@ __global__ __launch_bounds__(WVM * WVN * 64, WVM * WVN * PER_CU / 4) void screen
     auto meet = [&]() __attribute__((always_inline)) {
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         __syncthreads();                                     // the strips of the tile before have been read
-        const unsigned heavy_now = same_in_all(newest(&heavy)), by = heavy_now - heavy_before;
+        const unsigned heavy_now = now(heavy), by = heavy_now - heavy_before;
         if (by == WAVES || (by && by_before)) groups = 0;
         heavy_before = heavy_now; by_before = by;
     };
@@ -693,24 +681,25 @@ __global__ __launch_bounds__(WVM * WVN * 64, WVM * WVN * PER_CU / 4) void screen
 
     unsigned t = (unsigned)((unsigned long long)p.ntiles * xcd >> 3) + (blockIdx.x >> 3);
     const unsigned t_first = t;
-    bool begun = false, fetched = false;                     // the next tile's first slab is on its way to the first stage; its first claims and outputs are
+    bool begun = false, fetched = false;                     // the next tile's first slabs are on their way to their stages; its first claims and outputs are
     if (EARLY) __syncthreads();                              // (the words are clear)
+    Tile tile;
+    Sources src;
     if (EARLY && p.groups > GPS && t < t_end) {
-        const Tile first = tile_of(t);
+        tile = tile_of(t);
         bool attempt = true;
         if (!ACROSS) {
             // First slabs are not tried where claims are far off from the start: an error of the share of the bound that they would prove is at
             // least that share of the output's own.  (By a wavefront's first elements, 5 in 8 of them.)
-            begin(first, slab0);
+            begin(tile, src);
             const float part = p.low * (float)GPS / (float)p.groups;
-            if (far_off(first, 5, [&](int e) { return fabsf(rv[0][e]) * part; }) || marks != kOrdinary * 0x01010101u) unordinary = 1;
-            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            if (far_off(tile, 5, [&](int e) { return fabsf(rv[0][e]) * part; }) || marks != kOrdinary * 0x01010101u) unordinary = 1;
             __syncthreads();
-            attempt = same_in_all(unordinary == 0) != 0;
+            attempt = now(unordinary) == 0;
             begun = fetched = !attempt;
         }
         if (attempt) {
-            const unsigned n = min((unsigned)kEarlyTiles, (t_end - t + per - 1) / per), went = early_walk(t, n, first);
+            const unsigned n = ACROSS ? min((unsigned)kEarlyTiles, (t_end - t + per - 1) / per) : 1u, went = early_walk(t, n, tile);
             t += per * went;
             fetched = went < n;
         }
@@ -719,7 +708,6 @@ __global__ __launch_bounds__(WVM * WVN * 64, WVM * WVN * PER_CU / 4) void screen
     // before is checked, as its registers become free: a copy into LDS that is waited for has all older loads waited for too, so
     // requested behind the tile's barrier they held its first slab up (8 x 8192 x 2048 over 128 246 -> 233 us, the convolution of
     // 32 x 56 x 56 x 256 with its affine operator 317 -> 308; 512 x 3072 over 768, whose workgroups have a tile each, 22.8 -> 24).
-    Tile tile;
     if (ACROSS && t < t_end) {
         tile = tile_of(t);
         if (!fetched) {
@@ -728,16 +716,12 @@ __global__ __launch_bounds__(WVM * WVN * 64, WVM * WVN * PER_CU / 4) void screen
         }
     }
     for (; t < t_end; t += per) {
-        if (!ACROSS) {
+        if (!ACROSS && !(EARLY && fetched)) {
             tile = tile_of(t);
-            if (!fetched) {
 #pragma unroll
-                for (int k = 0; k < STEPS; ++k) fetch(tile, 0, k);
-            }
+            for (int k = 0; k < STEPS; ++k) fetch(tile, 0, k);
         }
-        Sources src;
-        sources_of(tile, src);
-        if (!ACROSS && begun) skip(src);
+        if (!(EARLY && begun)) sources_of(tile, src);
         Sums sums;
         clear_sums(sums);
         meet();
@@ -748,7 +732,7 @@ __global__ __launch_bounds__(WVM * WVN * 64, WVM * WVN * PER_CU / 4) void screen
         if (large) large_in = t + 1;
         __syncthreads();                                     // every wavefront is done with the stages
         known = max(known, newest(&largest));
-        const bool none_decided = groups == 0 || large_in == t + 1;      // (its first half of k is one wavefront's, the tile's concern all the same)
+        const bool none_decided = groups == 0 || now(large_in) == t + 1;      // (its first half of k is one wavefront's, the tile's concern all the same)
         Places open = 0;                                     // comparisons that were not decided: bit 4 (i STEPS + k) + e
         const unsigned vio_before = vio;
         const bool last = t + per >= t_end;
@@ -765,10 +749,10 @@ __global__ __launch_bounds__(WVM * WVN * 64, WVM * WVN * PER_CU / 4) void screen
         // Tiles of which a first slab did not decide all: all products, and the comparisons once more (the errors are settled).
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         __syncthreads();
-        const int words = same_in_all(some_pending) ? kEarlyWords : 0;
+        const int words = now(some_pending) ? kEarlyWords : 0;
 #pragma unroll 1
         for (int w = 0; w < words; ++w) {
-            for (unsigned these = same_in_all(newest(&pending[w])); these; these &= these - 1) {
+            for (unsigned these = now(pending[w]); these; these &= these - 1) {
                 const unsigned at = t_first + (unsigned)(w * 32 + __ffs((int)these) - 1) * per;
                 const Tile again = tile_of(at);
                 Sources src;
@@ -779,7 +763,7 @@ __global__ __launch_bounds__(WVM * WVN * 64, WVM * WVN * PER_CU / 4) void screen
                 product(src, sums, false);
                 if (finish_sums(again, sums)) large_in = at + 1;
                 __syncthreads();                             // every wavefront is done with the stages
-                const bool none_decided = groups == 0 || large_in == at + 1;
+                const bool none_decided = groups == 0 || now(large_in) == at + 1;
                 Places open = 0;
                 unsigned found = 0, counted = 0;             // violations, and NaN claims, which the first slab's check has counted
 #pragma unroll
@@ -809,6 +793,7 @@ __global__ __launch_bounds__(WVM * WVN * 64, WVM * WVN * PER_CU / 4) void screen
             }
         }
     }
+    if (EARLY && !ACROSS) __builtin_amdgcn_s_waitcnt(0x0F70);       // (a second slab that nobody has read has landed)
     // this workgroup's counts to one of the partial results (integer atomics: the sums do not depend on the order)
     __syncthreads();
     if (SPARE && wave == 0) zeros += (int)hist[kHistWords + lane];
