@@ -714,7 +714,7 @@ int tao_bound_conv2d(const float* x, const float* w, const float* bias, float* t
     p.all_clean = p.fast_ok && (M % bm == 0) && (N % BN == 0) && (K % BK == 0);
     const LinearProblem problem = {x, w, bias, tau, M, N, K, K, K, N, false, 1, 0, 0, 0};
     const ConvRows rows = {cv.H, cv.W, cv.C, cv.OW, cv.S, cv.sh, cv.sw, cv.ph, cv.pw, cv.dh, cv.dw, cv.ohow};
-    if (f64_conv_route(problem, rows, xbytes, bm, p.all_clean != 0, p.fast_ok, cus)) return f64_conv_launch(problem, rows, xbytes, md, c, cus, (hipStream_t)stream);
+    if (f64_conv_route(problem, rows, xbytes, bm, p.all_clean != 0, p.fast_ok, fast, cus)) return f64_conv_launch(problem, rows, xbytes, md, c, cus, (hipStream_t)stream);
     dim3 grid((unsigned)ntiles);
     hipStream_t st = (hipStream_t)stream;
     const hipError_t e = small ? launch_conv_shape<2>(fast, p.all_clean != 0, grid, st, p, cv)

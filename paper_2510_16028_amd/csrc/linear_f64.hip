@@ -341,21 +341,25 @@ int f64_launch(const LinearProblem& q, const tao_fp_model& md, double gamma, int
 static bool patches_by_four(const LinearProblem& p, const ConvRows& cv) { return cv.C % 4 == 0 && aligned(p.A, 16) && aligned(p.W, 16); }
 // The FP32 tiles of a convolution (bm rows each, whole: rows, columns and slabs regular; slabs: 32 channels of a tap at a time): times of a
 // round as measured at 220 shapes (49 ... 250 000 rows, 64 ... 512 columns, K = 3 ... 4608, fitted to 15 %), us per 32 k and besides.
-static double conv_fp32_us(long bm, bool whole, bool slabs, bool vec, long M, long N, long K, int cus) {
-    const double rounds = (double)((((M + bm - 1) / bm) * ((N + 127) / 128) + cus - 1) / cus), groups = (double)((K + 31) / 32);
+// fast: one accumulation chain (TAO_FLAG_FAST_ACCUM), at 56 shapes 0.73 to 0.87 of that where tiles are whole, otherwise 0.85 to 0.98, the lower the longer
+// the reduction.
+static double conv_fp32_us(long bm, bool whole, bool slabs, bool vec, bool fast, long M, long N, long K, int cus) {
+    const double chain = !fast ? 1.0 : whole ? 0.74 : 0.87;
+    const double rounds = chain * (double)((((M + bm - 1) / bm) * ((N + 127) / 128) + cus - 1) / cus), groups = (double)((K + 31) / 32);
     if (bm == 64) return rounds * (whole ? groups * 1.5 + 2.5 : slabs ? groups * 2.5 + 2.5 : vec ? groups * 2.65 + 6.5 : groups * 3.05 + 4.5);
     return rounds * (whole ? groups * 2.95 + 2.0 : slabs ? groups * 3.6 + 2.0 : vec ? groups * 4.0 + 13.0 : groups * 4.8 + 7.0);
 }
 // A convolution's few rows leave most of the chip idle while its FP32 tiles walk a long reduction (us, FP32 tiles / here: 49 rows x 64 over 4608
 // 605 / 18, 588 x 64 over 4608 374 / 19, 1200 x 128 over 4608 367 / 58, 972 x 512 over 1152 88 / 28, 4805 x 256 over 4608 353 / 259; 2645 x 512
 // over 576 47 / 50, 16384 x 512 over 288 65 / 181).  The line, at 1.1 times the estimate here and 4 us more, takes the better side within
-// 0.5 % on the mean of the 220 shapes, and nowhere the slower by more than 1 %.
-bool f64_conv_route(const LinearProblem& p, const ConvRows& cv, long xbytes, long bm, bool whole, bool slabs, int cus) {
+// 0.5 % on the mean of the 220 shapes, and nowhere the slower by more than 1 %.  With one accumulation chain, FP32 tiles / here: 3136 x 256 over 2304
+// 81.9 / 92.5, 3267 x 256 over 288 21.2 / 24.4; 576 x 512 over 1152 43 / 27.
+bool f64_conv_route(const LinearProblem& p, const ConvRows& cv, long xbytes, long bm, bool whole, bool slabs, bool fast, int cus) {
     if (p.K < 1 || xbytes <= 0 || xbytes > (1L << 31) - 16) return false;                  // (32-bit offsets)
     const F64Tile t = f64_tile(p.M, p.N, 1, cus);
     if (t.rounds * (double)cus >= 0x1p30) return false;
     const bool vec = patches_by_four(p, cv);
-    return 1.1 * linear_times(t, p.M, p.N, p.K, 1, vec, cus).f64 + 4.0 < conv_fp32_us(bm, whole, slabs, vec, p.M, p.N, p.K, cus);
+    return 1.1 * linear_times(t, p.M, p.N, p.K, 1, vec, cus).f64 + 4.0 < conv_fp32_us(bm, whole, slabs, vec, fast, p.M, p.N, p.K, cus);
 }
 int f64_conv_launch(const LinearProblem& q, const ConvRows& cv, long xbytes, const tao_fp_model& md, double gamma, int cus, hipStream_t st) {
     const F64Tile t = f64_tile(q.M, q.N, 1, cus);
