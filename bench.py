@@ -12,10 +12,12 @@ timed region; every activation is split again in every step, inside it.
 
 Prints ONE JSON line.  `value` = bytes of claimed operator output verified per
 second (4 bytes per element that went through bound + check) on configuration 3.
-`roofline` is for the dominant kernels (the matmul bounds' MFMA products), from HIP events
-recorded around their calls inside the timed region: matrix flop issued per second against
-the peak of the matrix cores they run on (`frac`), and the algorithmic 2 M N K against the
-FP32 MFMA peak (`frac_fp32_mfma_peak`).  `configs` holds the same
+`roofline` is for the dominant kernels (the matmul bounds with their checks), from HIP events
+recorded around their calls inside the timed region: the bytes that the calls cannot do without
+against the HBM peak (`frac`), as the first part of a reduction decides honest claims, and, as the
+rate that forming the products in full would have (`equivalent_TFLOP/s`), their 2 M N K, also
+against the FP32 MFMA peak (`frac_fp32_mfma_peak`).  Bounds that are stored have the
+matrix flop issued against the peak of the matrix cores that they run on instead.  `configs` holds the same
 measurement for the other configurations (1, 2, 4 and the 8192^3 stress case),
 `kernels` the individual kernels, also the bound kernels that store tau at
 100 M elements and more.  `cpu_baseline` times the CPU oracle on a row sample of
@@ -170,9 +172,15 @@ class PlannedOp:
 
     @property
     def issued(self):
-        # matrix products issued per operand pair: six for a bound, one for a checked call and six more in the tiles whose
-        # comparisons that one left open in the last call
-        return 6.0 if self.split and not self.fused else 1.0 + 6.0 * self.open_share()
+        # matrix products issued per operand pair of a stored bound
+        return 6.0 if self.split else 1.0
+
+    @property
+    def checked_bytes(self):
+        # what a checked call cannot do without: claims and outputs, and the operands that come in binary32, read once.  Of prepared
+        # images a few per cent are read where the claims are honest (the first slab of k); they are not counted.
+        a, prepared = self.op.args, self.prepared
+        return 8.0 * self.n + 4.0 * ((a["A"].numel() if not prepared or self.owns_image else 0) + (0 if prepared else a["W"].numel()))
 
     def open_share(self):
         """Share of a checked product's tiles (128 x 128 outputs) in which the one product left a comparison open: the records that the
@@ -569,45 +577,37 @@ def main():
     lin_launches = sum(len(p.bound_events) for p in lin)
     lin_flops = sum(p.flops * len(p.bound_events) for p in lin)
     achieved = lin_flops / (lin_ms * 1e-3) / 1e12
-    # the matmul bound, both paths together: algorithmic flop (2MNK) per second, which `frac_fp32_mfma_peak` relates to the FP32
-    # MFMA peak the metric names; a bound on the BF16 path issues 6 BF16 products per operand pair, a checked call
-    # whose claims that decides one, and either includes the pre-pass of its activation (and of its weight, unless
-    # that was prepared)
     sp = [p for p in lin if p.split]
-    paths, lin_issued, ms_at_peak = {}, 0.0, 0.0
-    for nm, sel, peak in (("bf16_split", sp, PEAK_BF16_MFMA_TFLOPS), ("fp32", [p for p in lin if not p.split], PEAK_FP32_MFMA_TFLOPS)):
-        if sel:
-            ms = sum(sum(_ms(p.bound_events)) for p in sel)
-            fl = sum(p.flops * len(p.bound_events) for p in sel)
-            issued = sum(p.issued * p.flops * len(p.bound_events) for p in sel)
-            lin_issued += issued
-            ms_at_peak += issued / peak * 1e-9
-            paths[nm] = {"ops": [p.name for p in sel], "TFLOP/s": fl / (ms * 1e-3) / 1e12,
-                         "issued_TFLOP/s": issued / (ms * 1e-3) / 1e12, "issued_frac_of_own_peak": issued / (ms * 1e-3) / 1e12 / peak}
-    roofline = {"bound": "mfma", "kernel": "screen_product + absgemm_split" if sp else "absgemm_bound",
+    roofline = {"kernel": "screen_product + absgemm_split" if sp else "absgemm_bound",
                 # operators bounded and checked in one call (tao_bound_check_linear): their launches, and
                 # so this figure, contain the check
                 "bound_and_check_in_one_call": [p.name for p in lin if p.fused],
                 "tiles_left_open": {p.name: p.open_share() for p in lin if p.fused},
-                "prepared_weight_images": [p.name for p in lin if p.prepared],
-                # the products' flop in full against the peak of the matrix cores that they run on (of the paths together: weighted by their
-                # flop).  A checked product whose claims its first slab of k decides issues no more of it, so this is no rate of the matrix cores.
-                "flop_counted": "whole products; a checked one issues its first 64 or 128 k where its form tries them, and the rest for tiles that these leave open",
-                "achieved": lin_issued / (lin_ms * 1e-3) / 1e12, "peak": lin_issued / ms_at_peak * 1e-9,
-                "unit": "TFLOP/s", "frac": ms_at_peak / lin_ms,
-                "algorithmic_TFLOP/s": achieved, "frac_fp32_mfma_peak": achieved / PEAK_FP32_MFMA_TFLOPS,
-                # the two paths apart: the FP32 path's algorithmic flop against the FP32 MFMA peak, the BF16-split path's
-                # flop (one whole BF16 product per operand pair in a checked call, 6 in a bound) against the BF16 MFMA peak
-                "frac_fp32_path_of_fp32_peak": paths["fp32"]["issued_frac_of_own_peak"] if "fp32" in paths else None,
-                "frac_bf16_path_of_bf16_peak": paths["bf16_split"]["issued_frac_of_own_peak"] if "bf16_split" in paths else None,
-                "paths": paths,
-                # not measured by this run: the figure of the committed rocprofv3 --pmc summary of this command
-                "traffic": measured_traffic("absgemm" if sp else "absgemm_bound") if args.scale == 1 else None,
-                "traffic_source": "offline: profiles/bench_c3_hbm_traffic.md (rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE of this command)",
-                "compulsory_bytes_per_launch": sum(p.min_bytes for p in lin) / len(lin),
-                "launches": lin_launches, "avg_launch_ms": lin_ms / lin_launches,
-                "flop_per_launch": lin_flops / lin_launches,
-                "share_of_step": lin_ms / args.steps / ms_per_step}
+                "prepared_weight_images": [p.name for p in lin if p.prepared]}
+    if all(p.fused for p in lin):
+        # Honest claims are decided by the first 64 or 128 terms of their bounds wherever a form tries them, so it is the traffic of
+        # claims and outputs that bounds these calls, and that of the activations cut.
+        nbytes = sum(p.checked_bytes * len(p.bound_events) for p in lin)
+        roofline.update({"bound": "hbm", "achieved": nbytes / (lin_ms * 1e-3) / 1e9, "peak": PEAK_HBM_GBS, "unit": "GB/s",
+                         "frac": nbytes / (lin_ms * 1e-3) / 1e9 / PEAK_HBM_GBS,
+                         "bytes_counted": "claims, outputs and binary32 operands of the calls, read once",
+                         "compulsory_bytes_per_launch": nbytes / lin_launches})
+    else:
+        # stored bounds: the flop issued on either path (six BF16 products per operand pair, or one FP32 or binary64 product), weighted
+        # by the peak of its matrix cores
+        issued = sum(p.issued * p.flops * len(p.bound_events) for p in lin)
+        at_peak = sum(p.issued * p.flops * len(p.bound_events) / (PEAK_BF16_MFMA_TFLOPS if p.split else PEAK_FP32_MFMA_TFLOPS) for p in lin) * 1e-9
+        roofline.update({"bound": "mfma", "achieved": issued / (lin_ms * 1e-3) / 1e12, "peak": issued / at_peak * 1e-9, "unit": "TFLOP/s",
+                         "frac": at_peak / lin_ms, "compulsory_bytes_per_launch": sum(p.min_bytes for p in lin) / len(lin)})
+    roofline.update({
+        # the products in full (2 M N K), whatever was issued of them
+        "equivalent_TFLOP/s": achieved, "frac_fp32_mfma_peak": achieved / PEAK_FP32_MFMA_TFLOPS,
+        # not measured by this run: the figure of the committed rocprofv3 --pmc summary of this command
+        "traffic": measured_traffic("absgemm" if sp else "absgemm_bound") if args.scale == 1 else None,
+        "traffic_source": "offline: profiles/bench_c3_hbm_traffic.md (rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE of this command)",
+        "launches": lin_launches, "avg_launch_ms": lin_ms / lin_launches,
+        "flop_per_launch": lin_flops / lin_launches,
+        "share_of_step": lin_ms / args.steps / ms_per_step})
 
     kernels = {}
     chk_ms = sum(sum(_ms(p.check_events)) for p in plan)
