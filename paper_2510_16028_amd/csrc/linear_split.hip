@@ -236,14 +236,13 @@ __global__ __launch_bounds__(MARKED ? kMostSplitThreads : 256) void split3_bf16(
         *reinterpret_cast<uintx4*>(d + (kSlab / 2)) = Mi;
         *reinterpret_cast<uintx4*>(d + 2 * (kSlab / 2)) = L;
     };
-    // A walk over whole groups of four rows and eight k has the next one's values under way while it stores: a loop whose loads follow its
-    // stores waits for both (4096 x 4096 27.0 -> 26.3 us, 4100 x 4096 27.1 -> 26.4).  No access is behind a branch, so that the number of those behind a load is known.
-    if (MARKED && !trans && first + step < units && p.rows % 4 == 0 && p.K % 8 == 0) {
+    // A walk over whole units has the next one's values under way while it stores: a loop whose loads follow its stores waits for both
+    // (4096 x 4096 27.0 -> 26.3 us).  No access is behind a branch, so that the number of those behind a load is known.
+    if (MARKED && !trans && first + step < units && p.rows % 64 == 0 && p.K % 8 == 0) {
         floatx4u x[2], y[2];
         Place at[2];
         auto ask = [&](int i, unsigned u) __attribute__((always_inline)) {
             at[i] = place_of(min(u, units - 1));
-            at[i].row = min(at[i].row, p.rows - 1);          // (beyond the operand the last row once more)
             const float* s = p.src + at[i].z * p.stride + at[i].row * p.ld + min(at[i].k0, p.K - 8);
             x[i] = reinterpret_cast<const floatx4u*>(s)[0]; y[i] = reinterpret_cast<const floatx4u*>(s)[1];
         };
