@@ -125,7 +125,7 @@ __device__ __forceinline__ void split_pack8(const float (&v)[8], uintx4& H, uint
 // layout (K a multiple of 8, one row), and 64 bytes of zeros behind them.
 // What bounds it: HBM for large operands, else one unit's latency -- its position takes scalar 32-bit arithmetic only (a thread's own
 // 64-bit divisions, units of 256 k, which a short reduction leaves empty, and loads behind branches took 8 x 8192 x 128 19.2 us, now
-// 13.6, 1111 x 1001 5.2, now 4.2, 8 x 128 x 2048 transposed 10.3, now 8.1; 12288 x 4096 103, at 4.9 TB/s, and 105 with marks, which cost 0.3 to 0.5 us
+// 13.6, 1111 x 1001 5.2, now 4.2, 8 x 128 x 2048 transposed 10.3, now 8.1; 12288 x 4096 103, at 4.9 TB/s, and 104 with marks, which cost 0.2 to 0.4 us
 // where one unit's latency is all there is).
 enum { STRAIGHT, TRANSPOSED, MAGNITUDES };
 struct SplitOperand {
@@ -145,7 +145,7 @@ __device__ __forceinline__ void clear_words(const ClearJob& c, long i0, long ste
         for (long i = i0; i < c.words[j]; i += step) static_cast<uintx4*>(c.at[j])[i] = uintx4{0, 0, 0, 0};
 }
 // A workgroup's mark, and the first one's for the places of those that there are not.  (__syncthreads_and has three barriers,
-// this one: 512 x 768 3.8 -> 3.5 us.)
+// this one: 512 x 768 3.8 -> 3.4 us.)
 __device__ __forceinline__ void leave_mark(const SplitOperand& p, long wg, long wgs, bool ordinary) {
     __shared__ unsigned all_of_wave[16];
     const int lane = threadIdx.x & (kWave - 1), waves = blockDim.x / kWave;
@@ -202,74 +202,38 @@ __global__ __launch_bounds__(MARKED ? kMostSplitThreads : 256) void split3_bf16(
     const unsigned units = (unsigned)(groups * (unsigned long long)rgroups * p.batch);
     const bool flat = p.flat();
     const int urow = trans ? tid & 63 : (flat ? tid & 63 : tid) >> 2, uch = trans ? tid >> 6 : tid & 3;
-    const unsigned first = flat ? (unsigned)blk * 4 + __builtin_amdgcn_readfirstlane(tid >> 6) : (unsigned)blk, step = (unsigned)nblk * (flat ? 4 : 1);
-    struct Place { long row, k0; unsigned z, g; };
-    auto place_of = [&](unsigned u) __attribute__((always_inline)) {
+    const unsigned first = flat ? (unsigned)blk * 4 + __builtin_amdgcn_readfirstlane(tid >> 6) : (unsigned)blk;
+    for (unsigned u = first; u < units; u += (unsigned)nblk * (flat ? 4 : 1)) {
         const unsigned rz = u / groups, g = u - rz * groups, z = rz / rgroups, rg = rz - z * rgroups;
-        return Place{(long)rg * 64 + urow, (long)g * SBK + uch * 8, z, g};
-    };
-    // (positions beyond the operand read its last row or element: loads without branches all leave at once)
-    auto request = [&](const Place& at, float (&v)[8]) __attribute__((always_inline)) {
-        const float* s = p.src + at.z * p.stride;
-        const long rc = at.row < p.rows ? at.row : p.rows - 1;
-        if (!trans && at.k0 + 8 <= p.K) {
-            const floatx4u* q = reinterpret_cast<const floatx4u*>(s + rc * p.ld + at.k0);
+        const long row = (long)rg * 64 + urow, k0 = (long)g * SBK + uch * 8;
+        if (row >= rows4) continue;
+        const float* s = p.src + z * p.stride;
+        float v[8];
+        // (positions beyond the operand read its last row or element: loads without branches all leave at once)
+        const long rc = row < p.rows ? row : p.rows - 1;
+        if (!trans && k0 + 8 <= p.K) {
+            const floatx4u* q = reinterpret_cast<const floatx4u*>(s + rc * p.ld + k0);
             const floatx4u x = q[0], y = q[1];
 #pragma unroll
-            for (int j = 0; j < 4; ++j) { v[j] = x[j]; v[4 + j] = y[j]; }
+            for (int j = 0; j < 4; ++j) { v[j] = row < p.rows ? x[j] : 0.f; v[4 + j] = row < p.rows ? y[j] : 0.f; }
         } else {
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
-                const long kc = at.k0 + j < p.K ? at.k0 + j : p.K - 1;
+                const long kc = k0 + j < p.K ? k0 + j : p.K - 1;
                 v[j] = trans ? s[kc * p.ld + rc] : s[rc * p.ld + kc];
             }
+#pragma unroll
+            for (int j = 0; j < 8; ++j) v[j] = row < p.rows && k0 + j < p.K ? v[j] : 0.f;
         }
-    };
-    auto store = [&](const Place& at, const float (&v)[8]) __attribute__((always_inline)) {
         uintx4 H, Mi, L;
         split_pack8(v, H, Mi, L);
         look(fabsf(v[0]) + fabsf(v[1]) + fabsf(v[2]) + fabsf(v[3]) + fabsf(v[4]) + fabsf(v[5]) + fabsf(v[6]) + fabsf(v[7]));
-        const long r = at.row & (STILE - 1);
+        const long r = row & (STILE - 1);
         const long unit = uch ^ ((r >> 2) & 3);
-        unsigned short* d = p.dst + (((long)at.z * groups + at.g) * rblocks + (at.row >> 7)) * (kBlock / 2) + r * (SROW / 2) + unit * 8;
+        unsigned short* d = p.dst + (((long)z * groups + g) * rblocks + (row >> 7)) * (kBlock / 2) + r * (SROW / 2) + unit * 8;
         *reinterpret_cast<uintx4*>(d) = H;
         *reinterpret_cast<uintx4*>(d + (kSlab / 2)) = Mi;
         *reinterpret_cast<uintx4*>(d + 2 * (kSlab / 2)) = L;
-    };
-    // A walk over whole units has the next one's values under way while it stores: a loop whose loads follow its stores waits for both
-    // (4096 x 4096 27.0 -> 26.3 us).  No access is behind a branch, so that the number of those behind a load is known.
-    if (MARKED && !trans && first + step < units && p.rows % 64 == 0 && p.K % 8 == 0) {
-        floatx4u x[2], y[2];
-        Place at[2];
-        auto ask = [&](int i, unsigned u) __attribute__((always_inline)) {
-            at[i] = place_of(min(u, units - 1));
-            const float* s = p.src + at[i].z * p.stride + at[i].row * p.ld + min(at[i].k0, p.K - 8);
-            x[i] = reinterpret_cast<const floatx4u*>(s)[0]; y[i] = reinterpret_cast<const floatx4u*>(s)[1];
-        };
-        auto put = [&](int i) __attribute__((always_inline)) {
-            const bool in = at[i].k0 < p.K;
-            float v[8];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) { v[j] = in ? x[i][j] : 0.f; v[4 + j] = in ? y[i][j] : 0.f; }
-            store(at[i], v);
-        };
-        ask(0, first);
-        for (unsigned u = first;;) {
-            u += step; ask(1, u); put(0);
-            if (u >= units) break;
-            u += step; ask(0, u); put(1);
-            if (u >= units) break;
-        }
-    } else {
-        for (unsigned u = first; u < units; u += step) {
-            const Place at = place_of(u);
-            if (at.row >= rows4) continue;
-            float v[8];
-            request(at, v);
-#pragma unroll
-            for (int j = 0; j < 8; ++j) v[j] = at.row < p.rows && at.k0 + j < p.K ? v[j] : 0.f;
-            store(at, v);
-        }
     }
     if (MARKED) leave_mark(p, wg, wgs, ordinary);
 }
@@ -1421,8 +1385,8 @@ static long split_blocks(const SplitOperand& p) {
 // [batch][K][rows] (TRANSPOSED) -> image.  clear: the side job described at the kernel.
 // A workgroup that leaves a mark: as many as there are marks, two to a compute unit, of as many parts of 256 threads as give every unit one, up to four.
 // Dealt out to the workgroups' first parts, then to their second ones, the last units find all compute units (us on the device; a quarter of the
-// workgroups, of 1024 threads, as soon as the marks were too few / so / without marks: 1111 x 1001, 576 units, 5.5 / 4.9 / 4.5, 3072 x 768 7.3 / 6.2 / 5.7,
-// 1500 x 1500 7.5 / 6.5 / 6.0).  A walk of several rounds keeps neighbouring units together (12288 x 4096 105, dealt out 112).
+// workgroups, of 1024 threads, as soon as the marks were too few / so / without marks: 1111 x 1001, 576 units, 5.5 / 4.9 / 4.5, 3072 x 768 7.3 / 6.0 / 5.7,
+// 1500 x 1500 7.4 / 6.3 / 6.0).  A walk of several rounds keeps neighbouring units together (12288 x 4096 104, dealt out 112; 2048 x 4096, cold, 16.0 and 18.7).
 static void launch_split3(const SplitOperand* ops, int n, const ClearJob& clear, hipStream_t st) {
     SplitOperands a = {};
     a.clear = clear;

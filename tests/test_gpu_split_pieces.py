@@ -155,7 +155,7 @@ def test_images_of_few_rows(tao, rows, batch, K):
 
 # units of 64 rows x 32 k: a workgroup of one, two, three and four parts, some units to spare, and walks of two to five rounds of whole units and of cut ones
 @pytest.mark.parametrize("rows,K,batch,trans", [(1000, 1001, 1, False), (1100, 1000, 1, False), (1500, 1500, 1, False), (1500, 1500, 1, True), (960, 1920, 2, False), (2176, 2056, 1, False),
-                                                (2100, 2056, 1, False), (2176, 2055, 1, False), (2176, 2056, 1, True), (4352, 4096, 1, False), (320, 40, 450, False), (15, 2300 * 32, 1, False)])
+                                                (2100, 2056, 1, False), (2049, 2056, 1, False), (2052, 2056, 2, False), (2176, 2055, 1, False), (2176, 2056, 1, True), (4352, 4096, 1, False), (320, 40, 450, False), (15, 2300 * 32, 1, False), (8, 8300 * 32, 1, False)])
 def test_images_of_many_units(tao, rows, K, batch, trans):
     """Every element's pieces add up to it, whichever part of a workgroup has cut it, and each large one is told by the marks behind the image."""
     g = torch.Generator(device="cuda").manual_seed(rows + K)
