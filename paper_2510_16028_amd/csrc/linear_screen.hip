@@ -585,10 +585,16 @@ __global__ __launch_bounds__(WVM * WVN * 64, WVM * WVN * PER_CU / 4) void screen
             first_error();
             // Whether many of these claims would be left pending, by the largest of the wavefront's first block of sums, of those that exist.
             // (Where an operand has no rows they are of whatever its image held before.)
-            float most_sum = 0.f;
-            const int cols_there = srow + r32 < tile.rows_left ? tile.cols_left - scol - 4 * h : 0;
+            float most_sum = sums.acc[0][0][0];
+            if (tile.rows_left >= TM && tile.cols_left >= TN) {
 #pragma unroll
-            for (int v = 0; v < 16; ++v) most_sum = fmaxf(most_sum, v / 4 * 8 + v % 4 < cols_there ? sums.acc[0][0][v] : 0.f);
+                for (int v = 1; v < 16; ++v) most_sum = fmaxf(most_sum, sums.acc[0][0][v]);
+            } else {
+                const int cols_there = srow + r32 < tile.rows_left ? tile.cols_left - scol - 4 * h : 0;
+                most_sum = 0.f;
+#pragma unroll
+                for (int v = 0; v < 16; ++v) most_sum = fmaxf(most_sum, v / 4 * 8 + v % 4 < cols_there ? sums.acc[0][0][v] : 0.f);
+            }
             most_sum = wave_max(most_sum);
             if (large || far_off(tile, 2, [&](int e) { return fmaf(most_sum, p.low, bl[e]); })) refused = t + 1;
             __syncthreads();                                 // every wavefront is done with the slab
