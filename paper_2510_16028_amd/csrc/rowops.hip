@@ -1002,9 +1002,10 @@ static int row_form(bool whole, long cols, long tpr, long V) {
 // kFewestElements each, as far as that takes rows off the fullest one.  Few rows wait for the arithmetic of the compute unit that has most of them, many end
 // with a trip that only some have; with a workgroup's rows as far apart as there are workgroups that trip is everybody's, and the wavefronts that have none
 // in it are done (softmax / RMSNorm, us, with neighbouring rows and so: 6144 x 512, one trip and a half, 20.5 / 19.1 and 16.8 / 15.8; 9000 x 512 26.7 / 24.2 and 22.1 / 20.5;
-// 21696 x 1356 92.4 / 100 and 79.9 / 100; 16384 x 1024 47.6 / 46.4 and 45.6 / 42.6, but softmax 8192 x 1024 29.4 and 30.8; 64 x 1500, on 16 workgroups and on 64,
-// 13.6 / 12.5 and 11.3 / 10.2; 512 x 768 10.9 / 10.6 and 10.5 / 10.2).  Row groups of more than a wavefront whose last trip is a full one keep neighbouring rows (RMSNorm
-// 2048 x 4096 31.3, 31.8 apart).
+// 21696 x 1356 92.4 / 100 and 79.9 / 100; 16384 x 1024 47.6 / 46.4 and 45.6 / 42.6; 64 x 1500, on 16 workgroups and on 64,
+// 13.6 / 12.5 and 11.3 / 10.2; 512 x 768 10.9 / 10.6 and 10.5 / 10.2).  Where the last trip is a full one neighbouring rows stay together
+// (RMSNorm 2048 x 4096 31.3, 31.8 apart, 16384 x 512 29.6 / 30.1, softmax 8192 x 2048 56.5 / 61.2, 16384 x 300 30.0 / 30.6), but for a wavefront's rows of four
+// vectors, which drift apart the more (softmax 8192 x 1024 38.8 / 33.9, 12288 x 1024 44.3 / 42.3, LayerNorm 16384 x 1024 47.1 / 44.2).
 constexpr long kFewestElements = 1024;
 static int row_blocks(long rows, long cols, int tpr, RowConsts& k) {
     const int groups = kCheckThreads / tpr;
@@ -1016,7 +1017,8 @@ static int row_blocks(long rows, long cols, int tpr, RowConsts& k) {
         const long each = (rows + blocks - 1) / blocks;
         blocks = (rows + each - 1) / each;
     }
-    k.apart = tpr > kWave && rows % (blocks * groups) == 0 ? 1 : (int)blocks;
+    const bool four_vectors = tpr == kWave && cols > 512 && cols <= 1024;
+    k.apart = !four_vectors && rows % (blocks * groups) == 0 ? 1 : (int)blocks;
     return (int)blocks;
 }
 constexpr long kWaveRows = 2L * kMaxCheckBlocks * (kCheckThreads / kWave);

@@ -59,3 +59,15 @@ def test_every_row_belongs_to_one_row_group(tmp_path):
                 for row in range(b * (groups if apart == 1 else 1) + apart * s, rows, grid * groups):
                     seen[row] += 1
         assert seen == [1] * rows, (kernel, grid, rows, apart, cols)
+
+
+TRIPS = CONSTS + r"""
+result = [(name, rows, cols) + call(rows, cols)[1:2] + (call(rows, cols)[3][1].apart,)
+          for name, call in calls.items() for rows, cols in ((16384, 300), (8192, 2048), (16384, 1024), (9000, 300), (9000, 2048))]
+"""
+
+
+def test_rows_of_whole_trips_stay_together(tmp_path):
+    """Neighbouring rows where every trip is a full one, but for a wavefront's rows of four vectors; otherwise the last trip is everybody's."""
+    for name, rows, cols, grid, apart in launches.run(TRIPS, tmp_path):
+        assert apart == (1 if rows != 9000 and cols != 1024 else grid), (name, rows, cols, grid, apart)
