@@ -985,10 +985,15 @@ __global__ __launch_bounds__(kRowThreads) void bn_affine_bound(
 
 // How a ragged row is read whose group holds V vectors of 4 TPR columns: by vectors unless most of the last one would be empty (us, by single
 // values / by vectors: LayerNorm 30000 x 511 58.2 / 51.5, 6442 x 861 48.1 / 38.8, softmax of 4 x 2045 x 2045 with its products 175 / 158; but LayerNorm
-// 10000 x 1031 58.4 / 63.2, 30000 x 259 45.7 / 48.8, 155 x 3233 13.8 / 14.5).
-static int row_form(bool whole, long cols, long tpr, long V) {
+// 10000 x 1031 58.4 / 63.2, 30000 x 259 45.7 / 48.8, 155 x 3233 13.8 / 14.5).  A wavefront's rows of one vector to a lane by single values where these are one or
+// two to a lane, or three in a few rows: a lane with values takes four by vectors, and the others wait for it (softmax 38 x 51 8.8 / 10.1, 100000 x 51 60.0 / 68.7,
+// 65536 x 65 46.8 / 48.7, 3000 x 190 10.1 / 10.8, 24576 x 190 24.9 / 25.9, but 49152 x 190 41.9 / 41.0 and 16384 x 193 23.9 / 21.6; LayerNorm 300 x 129 9.7 / 10.0, 32768 x 129 37.1 / 36.2).
+constexpr long kFewRaggedRows = 6L * kMaxCheckBlocks * (kCheckThreads / kWave);
+static int row_form(bool whole, long rows, long cols, long tpr, long V) {
     if (whole) return WHOLE;
-    return cols < 4 || (V == 2 && cols * 5 < tpr * V * 4 * 4) ? SINGLE : ANY;
+    if (cols < 4) return SINGLE;
+    if (V == 1 && tpr == kWave) return cols <= 2 * kWave || (cols <= 3 * kWave && rows < kFewRaggedRows) ? SINGLE : ANY;
+    return V == 2 && cols * 5 < tpr * V * 4 * 4 ? SINGLE : ANY;
 }
 // The one-pass checks of rows.  Quick settlement pays from eight rows per row group on, four where that is a wavefront; below, too many elements are
 // among the first a workgroup sees and the second route is only more code to fetch (us with / without: softmax 512 x 512
@@ -1243,10 +1248,10 @@ int tao_bound_check_norm(int kind, const float* x, const float* y_ref, const flo
     auto quick = [&](int tpr) { return quick_pays(rows, tpr); };
 #define TAO_NORM_CHECK_Q(RMS, TPR, V, Q) \
     do {                                                                                                    \
-        const int form = row_form(full, cols, TPR, V);                                                      \
+        const int form = row_form(full, rows, cols, TPR, V);                                                \
         if (form == WHOLE)    launch(norm_check<RMS, TPR, V, WHOLE, Q>, TPR, rows, cols, ld);               \
         else if (form == ANY) launch(norm_check<RMS, TPR, V, ANY, Q>, TPR, rows, cols, ld);                 \
-        else                  launch(norm_check<RMS, TPR, V, V == 2 ? SINGLE : ANY, Q>, TPR, rows, cols, ld); \
+        else                  launch(norm_check<RMS, TPR, V, V == 2 || (V == 1 && TPR == kWave) ? SINGLE : ANY, Q>, TPR, rows, cols, ld); \
     } while (0)
 #define TAO_NORM_CHECK(RMS, TPR, V) do { if (quick(TPR)) TAO_NORM_CHECK_Q(RMS, TPR, V, true); else TAO_NORM_CHECK_Q(RMS, TPR, V, false); } while (0)
 #define TAO_NORM_CHECK_ROWS(RMS)                                                                            \
@@ -1309,10 +1314,10 @@ int tao_bound_check_softmax(const float* x, const float* y_ref, const float* cla
         auto quick = [&](int tpr) { return quick_pays(rows, tpr); };
 #define TAO_SOFTMAX_CHECK_Q(TPR, V, Q) \
     do {                                                                                        \
-        const int form = row_form(full, cols, TPR, V);                                          \
+        const int form = row_form(full, rows, cols, TPR, V);                                    \
         if (form == WHOLE)    launch(softmax_check<TPR, V, WHOLE, Q>, TPR);                     \
         else if (form == ANY) launch(softmax_check<TPR, V, ANY, Q>, TPR);                       \
-        else                  launch(softmax_check<TPR, V, V == 2 ? SINGLE : ANY, Q>, TPR);     \
+        else                  launch(softmax_check<TPR, V, V == 2 || (V == 1 && TPR == kWave) ? SINGLE : ANY, Q>, TPR); \
     } while (0)
 #define TAO_SOFTMAX_CHECK(TPR, V) do { if (quick(TPR)) TAO_SOFTMAX_CHECK_Q(TPR, V, true); else TAO_SOFTMAX_CHECK_Q(TPR, V, false); } while (0)
         if (cols < 4)          launch(softmax_check<64, 1, SINGLE, false>, 64);

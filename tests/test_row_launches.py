@@ -71,3 +71,20 @@ def test_rows_of_whole_trips_stay_together(tmp_path):
     """Neighbouring rows where every trip is a full one, but for a wavefront's rows of four vectors; otherwise the last trip is everybody's."""
     for name, rows, cols, grid, apart in launches.run(TRIPS, tmp_path):
         assert apart == (1 if rows != 9000 and cols != 1024 else grid), (name, rows, cols, grid, apart)
+
+
+FORMS = CONSTS + r"""
+result = [(name, rows, cols, call(rows, cols)[0]) for name, call in calls.items()
+          for rows, cols in ((38, 51), (100000, 51), (38, 126), (100000, 126), (38, 130), (16384, 130), (30000, 130), (38, 195), (30000, 195), (38, 128), (38, 132))]
+"""
+
+
+def test_ragged_rows_of_a_wavefront_are_read_by_what_a_lane_has(tmp_path):
+    """By single values where a lane has one or two, or three in few rows; by vectors otherwise."""
+    for name, rows, cols, kernel in launches.run(FORMS, tmp_path):
+        args = kernel.split("<")[1].split(", ")[0 if name == "softmax" else 1:]
+        if args[0] != "64":                                  # (the norms' short rows: sixteen lanes, thirty-two)
+            continue
+        single, whole, vectors = "0", "1", "2"
+        want = whole if cols % 4 == 0 else single if cols <= 128 or (cols <= 192 and rows < 24576) else vectors
+        assert args[:3] == ["64", "1", want], (name, rows, cols, kernel)
