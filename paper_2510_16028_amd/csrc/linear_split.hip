@@ -1395,7 +1395,9 @@ static void launch_split3(const SplitOperand* ops, int n, const ClearJob& clear,
     for (int o = 0; o < n && marked; ++o) parts = std::max(parts, (split_blocks(ops[o]) + ops[o].nmarks - 1) / ops[o].nmarks);
     parts = std::min(parts, (long)kMostSplitThreads / 256);
     for (int o = 0; o < n; ++o) {
-        const long blocks = split_blocks(ops[o]), wgs = std::clamp(blocks, 1L, marked ? (long)ops[o].nmarks : 256L * 64);
+        const long blocks = split_blocks(ops[o]), most = marked ? ops[o].nmarks : 256L * 64;
+        // (an operand beside a longer one leaves no part of its workgroups idle, whose places that one could have: 1892 x 2560 beside 576 x 2560 13.6 -> 12.0 us)
+        const long wgs = std::clamp((blocks + most - 1) / most < parts ? (blocks + parts - 1) / parts : blocks, 1L, most);
         a.op[o] = ops[o];
         a.op[o].spread = blocks <= wgs * parts;
         a.first[o] = first;

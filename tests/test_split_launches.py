@@ -23,3 +23,23 @@ def test_an_operand_is_cut_on_all_of_the_chip(tmp_path):
             units = (units + 3) // 4
         assert grid == min(units, 512), case                 # two workgroups to a compute unit as soon as there are units for them
         assert block // 256 == min(4, -(-units // 512)), case        # and no more threads in each than units ask for
+
+
+BOTH = r"""
+result = []
+P = address(1 << 20)
+for M, N, K in ((1892, 576, 2560), (1500, 1000, 1000), (1500, 700, 1500), (576, 1892, 2560), (1400, 1300, 500), (1000, 300, 400)):
+    assert lib.tao_bound_check_linear(P, P, None, P, P, None, M, N, K, K, K, N, 0, 1, 0, 0, 0, 1.0, 1e-12, None, P, P, 1 << 40, None) == 0
+    result.append((M, N, K, [l[:3] for l in launched() if l[0] == "split3_bf16<true"]))
+"""
+
+
+def test_the_shorter_of_two_operands_fills_its_workgroups(tmp_path):
+    found = launches.run(BOTH, tmp_path)
+    assert len(found) == 6
+    for M, N, K, cuts in found:
+        (_, grid, block), = cuts
+        units = sorted(-(-K // 32) * -(-rows // 64) for rows in (M, N))
+        parts = min(4, -(-units[1] // 512))
+        shorter = units[0] if -(-units[0] // 512) == parts else -(-units[0] // parts)
+        assert (grid, block) == (min(units[1], 512) + min(shorter, 512), 256 * parts), (M, N, K, units, grid, block)
