@@ -868,13 +868,14 @@ enum Config { kRows64x128, kRows64x64, kPixels128x128, kPixels128x128Short, kPix
 // affine operator, 97.5 -> 94.9; of 96 channels 97.0 without, 96.7 with).
 // A read as rows: 64 x 128 where they fill the chip (8 x 8192 x 128 over 2048 145, with 64 x 64 183), else 64 x 64 (12 x 512 x 64 over
 // 512 22 / 26).
+constexpr long kFewGroups = 8;                               // (up to which no form of images tries first slabs)
 Config screen_config(long M, long N, long K, long batch, bool rows, bool pixels) {
     const long n = device_cus(), groups = (K + SBK - 1) / SBK;
     const long t128 = ((M + 127) / 128) * ((N + 127) / 128) * batch, t64 = ((M + 63) / 64) * ((N + 63) / 64) * batch;
     const bool wide = t128 >= n && N > 64;
     if (rows) return ((M + 63) / 64) * ((N + 127) / 128) * batch >= n && N > 64 ? kRows64x128 : kRows64x64;
     if (pixels) return !wide ? kPixels64x64 : groups > 2 ? kPixels128x128 : kPixels128x128Short;
-    if (wide) return groups <= 8 ? kImages64x128 : kImages128x128;
+    if (wide) return groups <= kFewGroups ? kImages64x128 : kImages128x128;
     return t64 > 2 * n ? kImages64x64 : groups > 12 ? kImages64x64Few : kImages64x64Short;
 }
 
@@ -884,6 +885,8 @@ bool screen_reads_marks(long M, long N, long K, long batch, bool rows, bool pixe
     const Config c = screen_config(M, N, K, batch, rows, pixels);
     return c == kPixels128x128 || c == kImages128x128 || c == kImages64x64Few;
 }
+// (an operand by itself, whose product is not known yet: the cut of 512 x 256 3.3 us with marks, 3.0 without, of 100000 x 64 12.0 / 10.8)
+bool screen_reads_marks(long K) { return (K + SBK - 1) / SBK > kFewGroups; }
 
 int launch_screen(const ScreenOperand& A, const ScreenOperand& W, const float* bias, long M, long N, long K, long batch,
                   double cg, const ScreenCheck& chk, const CheckWorkspace& ws, const OpenRecords& open, hipStream_t st) {

@@ -106,6 +106,7 @@ inline bool screen_usable(long K, double u, double cg, double alpha, double uflo
            uflow <= cg * (double)K * 0x1p-100;
 }
 bool screen_reads_marks(long M, long N, long K, long batch, bool rows, bool pixels);       // whether launch_screen's choice does
+bool screen_reads_marks(long K);                             // whether it can, of prepared images of K columns
 int launch_screen(const ScreenOperand& A, const ScreenOperand& W, const float* bias, long M, long N, long K, long batch,
                   double cg, const ScreenCheck& chk, const CheckWorkspace& ws, const OpenRecords& open, hipStream_t st);
 

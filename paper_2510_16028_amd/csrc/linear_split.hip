@@ -1792,7 +1792,7 @@ int tao_split_operand(const float* src, long rows, long K, long ld, int trans, l
     if (need == 0 || !image || !aligned(image, 256) || image_bytes < need) return TAO_ERR_WORKSPACE;
     if (batch >= 65536) return TAO_ERR_SHAPE;                      // (an image's limit, whatever a launch could take)
     const SplitOperand op = {src, rows, K, ld, batch, stride, static_cast<unsigned short*>(image), trans ? TRANSPOSED : STRAIGHT,
-                             image_marks(image, rows, K, batch), kMarks};
+                             image_marks(image, rows, K, batch), screen_reads_marks(K) ? kMarks : 0};
     launch_split3(&op, 1, ClearJob{}, (hipStream_t)stream);
     return launch_status();
 }

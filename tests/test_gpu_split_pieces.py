@@ -155,9 +155,9 @@ def test_images_of_few_rows(tao, rows, batch, K):
 
 # units of 64 rows x 32 k: a workgroup of one, two, three and four parts, some units to spare, and walks of two to five rounds of whole units and of cut ones
 @pytest.mark.parametrize("rows,K,batch,trans", [(1000, 1001, 1, False), (1100, 1000, 1, False), (1500, 1500, 1, False), (1500, 1500, 1, True), (960, 1920, 2, False), (2176, 2056, 1, False),
-                                                (2100, 2056, 1, False), (2049, 2056, 1, False), (2052, 2056, 2, False), (2176, 2055, 1, False), (2176, 2056, 1, True), (4352, 4096, 1, False), (320, 40, 450, False), (15, 2300 * 32, 1, False), (8, 8300 * 32, 1, False)])
+                                                (2100, 2056, 1, False), (2049, 2056, 1, False), (2052, 2056, 2, False), (2176, 2055, 1, False), (2176, 2056, 1, True), (4352, 4096, 1, False), (320, 40, 450, False), (320, 260, 100, False), (15, 2300 * 32, 1, False), (8, 8300 * 32, 1, False)])
 def test_images_of_many_units(tao, rows, K, batch, trans):
-    """Every element's pieces add up to it, whichever part of a workgroup has cut it, and each large one is told by the marks behind the image."""
+    """Every element's pieces add up to it, whichever part of a workgroup has cut it, and each large one is told by the marks behind the image where a product can read them."""
     g = torch.Generator(device="cuda").manual_seed(rows + K)
     x = torch.randn((batch, rows, K), generator=g, device="cuda")
     groups, blocks = (K + 31) // 32, (rows + 127) // 128
@@ -177,6 +177,7 @@ def test_images_of_many_units(tao, rows, K, batch, trans):
             assert torch.equal(part[:, :rows, :K], x[z:z + 64].abs()), (where, z)
             assert not part[:, :rows, K:].any() and not part[:, rows:(rows + 3) // 4 * 4].any()
         marks = out[size:size + 512]
-        assert bool((marks == 0xa5).all()) == (where is None) and set(marks.unique().tolist()) <= {0, 0xa5}, where
+        if K > 256:                                          # (no form reads shorter ones')
+            assert bool((marks == 0xa5).all()) == (where is None) and set(marks.unique().tolist()) <= {0, 0xa5}, where
         if where:
             x[where] = 1.0
